@@ -68,6 +68,16 @@ bool misaligned(const void *p) { return ((uintptr_t)p & 15u) != 0; }
         if (rc_ != MXC_OK) return rc_; \
     } while (0)
 
+// Set while a call must get by with the least scratch (see mxc_conv2d_bwd_weight_static): no kernel that trades
+// scratch for speed is chosen.
+thread_local bool g_lean = false;
+struct LeanScope {
+    explicit LeanScope(bool on) { g_lean = on; }
+    ~LeanScope() { g_lean = false; }
+};
+
+bool f32_in_place(const ConvShape &s, int dtype) { return dtype == MXC_F32 && !g_lean && f32_supported(s); }
+
 // ---- passes in the working layout (NHWC / KRSC) --------------------------------
 // dry == true: only account workspace.
 
@@ -150,6 +160,11 @@ int fwd_nhwc(const ConvShape &s, int dtype, const void *x, const void *w, void *
         return rc;
     }
     if (dry || !run) return MXC_OK;
+    if (f32_in_place(s, dtype)) {
+        const int rc = f32_fwd(s, false, x, w, y, st, &v, post);
+        set_variant("fwd", v);
+        return rc;
+    }
     set_variant("fwd", "direct");
     return direct_fwd(s, dtype, x, w, y, st, post);
 }
@@ -266,11 +281,60 @@ int bwd_weight_nhwc(const ConvShape &s, int dtype, const void *x, const void *dy
         set_variant("bwd_weight", (std::string("chanpad+") + v).c_str());
         return rc;
     }
+    if (f32_in_place(s, dtype)) {
+        float *partial = (float *)ws.take(f32_wgrad_workspace(s));
+        if (dry) return MXC_OK;
+        const int rc = f32_wgrad(s, false, x, dy, dw, partial, st, &v);
+        set_variant("bwd_weight", v);
+        return rc;
+    }
     const int splits = direct_bwd_weight_splits(s);
     float *partial = (float *)ws.take((size_t)splits * s.K * s.R * s.S * s.C * sizeof(float));
     if (dry) return MXC_OK;
     set_variant("bwd_weight", "direct_splitk");
     return direct_bwd_weight(s, dtype, x, dy, dw, dw_bf16, partial, splits, st);
+}
+
+// ---- fp32, either layout: the matrix-core kernels of fp32.hip read the caller's tensors in place -----------------
+// For NCHW the scratch that the converting path would use is asked for all the same: the size of a call's workspace
+// is a property of its arguments, not of the kernel that runs them, and the converting path still takes tensors of
+// 2 GiB and more.
+
+int run_f32(int pass, const ConvShape &s, int layout, const void *a, const void *b, void *out, const PostOp &post, Carver &fws,
+            Carver &ws, hipStream_t st, bool dry, FilterMode mode)
+{
+    const bool nchw = layout == MXC_NCHW;
+    const size_t nx = (size_t)s.N * s.C * s.H * s.W * 4, nw = (size_t)s.K * s.C * s.R * s.S * 4, ny = (size_t)s.N * s.K * s.P * s.Q * 4;
+    const char *v = "";
+    if (pass == MXC_FWD) {
+        if (nchw) { ws.take(nx); ws.take(nw); ws.take(ny); }
+        if (dry) return MXC_OK;
+        const int rc = f32_fwd(s, nchw, a, b, out, st, &v, post);
+        set_variant("fwd", v);
+        return rc;
+    }
+    if (pass == MXC_BWD_DATA) {
+        // the kernel reads the filter as it lies: its prepared form is a copy
+        const bool run = mode != FILTER_PREPARE_ONLY;
+        void *wc = (nchw || mode != FILTER_RAW) ? fws.take(nw) : nullptr;
+        if (nchw && run) {
+            ws.take(ny); ws.take(nx);
+            if (post.mask != nullptr || post.relu) ws.take(nx);
+        }
+        if (dry) return MXC_OK;
+        if (!run) return launch_copy(b, wc, nw, st);
+        PostOp post2 = post;
+        post2.relu = 0;
+        const int rc = f32_bwd_data(s, nchw, a, mode == FILTER_PREPARED ? wc : b, out, st, &v, post2);
+        set_variant("bwd_data", v);
+        return rc;
+    }
+    if (nchw) { ws.take(nx); ws.take(ny); ws.take(nw); }
+    float *partial = (float *)ws.take(f32_wgrad_workspace(s));
+    if (dry) return MXC_OK;
+    const int rc = f32_wgrad(s, nchw, a, b, out, partial, st, &v);
+    set_variant("bwd_weight", v);
+    return rc;
 }
 
 // ---- one driver per pass: handles the caller's layout ---------------------------
@@ -280,6 +344,7 @@ int run_pass(int pass, const ConvShape &s, int dtype, int layout, const void *a,
              Carver &ws, hipStream_t st, bool dry, Carver *fws_opt = nullptr, FilterMode mode = FILTER_RAW)
 {
     Carver &fws = fws_opt ? *fws_opt : ws;
+    if (f32_in_place(s, dtype)) return run_f32(pass, s, layout, a, b, out, post, fws, ws, st, dry, mode);
     const int eb = (int)elem_size(dtype);
     const size_t nx = (size_t)s.N * s.C * s.H * s.W, nw = (size_t)s.K * s.C * s.R * s.S,
                  ny = (size_t)s.N * s.K * s.P * s.Q;
@@ -434,7 +499,14 @@ int mxc_conv2d_bwd_weight_static(int N, int C, int H, int W, int K, int R, int S
     if (misaligned(x) || misaligned(dy) || misaligned(dw)) return MXC_ERR_ALIGN;
     Carver need(nullptr);
     MXC_TRY(run_pass(MXC_BWD_WEIGHT, s, dtype, layout, nullptr, nullptr, nullptr, PostOp(), need, nullptr, true));
-    if (need.used > MXC_STATIC_SCRATCH_BYTES) return MXC_ERR_WORKSPACE;
+    // the faster kernels may want more scratch than the array holds; the ones that need the least come second
+    const bool lean = need.used > MXC_STATIC_SCRATCH_BYTES;
+    LeanScope scope(lean);
+    if (lean) {
+        Carver least(nullptr);
+        MXC_TRY(run_pass(MXC_BWD_WEIGHT, s, dtype, layout, nullptr, nullptr, nullptr, PostOp(), least, nullptr, true));
+        if (least.used > MXC_STATIC_SCRATCH_BYTES) return MXC_ERR_WORKSPACE;
+    }
     void *ws = nullptr;
     MXC_TRY(static_scratch(&ws));
     // every kernel of this pass writes the part of the scratch it later reads: nothing needs clearing
@@ -792,7 +864,8 @@ int mxc_version(void) { return 400; }
 
 const char *mxc_tile_name(int family, int index)
 {
-    return family == 0 ? igemm_tile_name(index) : family == 1 ? wgrad_tile_name(index) : family == 2 ? igemm_stream_name(index) : nullptr;
+    return family == 0 ? igemm_tile_name(index) : family == 1 ? wgrad_tile_name(index) : family == 2 ? igemm_stream_name(index)
+           : family == 3 ? f32_tile_name(index) : nullptr;
 }
 
 int mxc_probe_mfma(int workgroups, int iters, void *out, size_t out_bytes, double *flops, void *hip_stream)

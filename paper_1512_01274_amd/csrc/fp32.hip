@@ -1,0 +1,756 @@
+// fp32 convolution on the gfx950 fp32 matrix cores, all three passes, both layouts, any channel count.
+//
+// One kernel template runs the three passes as GEMMs  D[i][j] = sum_k A[i][k] * B[k][j]  (fp32 operands, fp32
+// accumulation, v_mfma_f32_32x32x2_f32):
+//   forward:          i = output pixel, j = output channel, k = (tap, c) in NHWC / (c, tap) in NCHW
+//   backward-data:    i = input pixel of one stride residue class, j = input channel, k over (tap, output channel);
+//                     every residue class is part of the one launch, one that no tap reaches has an empty sum
+//   backward-weight:  i = output channel, j = filter element in the filter's own order, k = output pixel
+// The instruction takes ONE float per lane and operand, so an operand tile can sit in LDS with either index
+// contiguous: k-contiguous ("KC", [i][16 k]) or k-slow ("KS", [16 k][i]).  Each operand is laid the way it lies in
+// memory, and therefore no pass needs a transposed or re-packed copy of anything, in NHWC or NCHW:
+//                     A                      B
+//   fwd  NHWC         x gather, KC           w rows, KC
+//   fwd  NCHW         x gather, KS           w rows, KC
+//   bwd  NHWC         dy gather, KC          w, KS (input channels contiguous)
+//   bwd  NCHW         dy gather, KS          w, KC (taps contiguous)
+//   dw   NHWC         dy, KS                 x gather, KS
+//   dw   NCHW         dy, KC                 x gather, KC (pixels contiguous)
+//
+// What bounds it: the fp32 matrix rate (64 flop per clock and SIMD, 1/16 of bf16).  A 128x128 tile needs 2048 matrix
+// clocks per 16-element stage, against which 64 wave-wide 4-byte transfers and their address arithmetic are small
+// change; that is why the transfers can be 4 bytes per lane, which is what makes every channel count, alignment and
+// layout run at the same rate (16-byte transfers are used where the reduction index comes in aligned fours).
+// Tiles are filled by direct global->LDS loads through a ring of NS stages, one barrier per stage; lanes that fall
+// into padding, past a ragged edge or past the reduction end get an offset the buffer rejects, which deposits zeros.
+//
+// Small problems: Z groups of waves of one workgroup take the 16-element stages in turn (group z runs stages z, z+Z,
+// ...), each with a ring of its own, and the Z partial tiles are added in ascending z through LDS: a 32x32 tile with
+// eight one-wave groups (no barrier inside the loop) turns a single-layer problem into many short chains.
+#include <stdlib.h>
+#include <string.h>
+
+#include <type_traits>
+
+#include "mxc_internal.h"
+
+namespace mxc {
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+
+constexpr unsigned OOB = 0x80000000u;   // a buffer offset no operand reaches: the load returns zeros
+constexpr int BK = 16;                  // reduction elements per stage
+constexpr int MAX_CLASSES = 16;         // stride residue classes of backward-data (stride <= 4)
+enum { OP_FWD = 0, OP_BWD = 1, OP_WGRAD = 2 };
+
+template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ void wait_lgkmcnt0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void pin() { __builtin_amdgcn_sched_barrier(0); }
+
+template <int I> using IC = std::integral_constant<int, I>;
+template <class F, int... I> __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) { (f(IC<I>{}), ...); }
+template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
+struct F32Params {
+    const float *a, *b;     // the two operands as the table above names them
+    float *out;             // y, dx, dw or the first split's partial dw
+    unsigned a_bytes, b_bytes;
+    ConvShape s;
+    int M;                  // forward: N*P*Q; backward-weight: the reduction length N*P*Q
+    int n_tiles, tiles, units;      // tiles: per split; units: tiles * splits
+    int span;               // backward-weight: pixels per split (a multiple of 16 * Z)
+    int cls_tile0[MAX_CLASSES + 1];     // backward-data: first row tile of each residue class
+    int n_cls;
+    const float *bias;      // forward, or null
+    int relu;
+    const float *mask;      // backward-data, or null: the result is 0 where mask <= 0
+};
+
+// floor(t / d) for 0 <= t <= 127, 1 <= d <= 127
+__device__ __forceinline__ int small_div(int t, int magic) { return (t * magic) >> 16; }
+__device__ __forceinline__ int small_magic(int d) { return (65536 + d - 1) / d; }
+
+__device__ __forceinline__ int pack_hw(int h, int w) { return (h & 0xFFFF) | (w << 16); }
+// nonzero where (h, w) + (dh, dw) leaves the image; all packed as two 16-bit integers
+__device__ __forceinline__ int outside(int hw, int d, int lim)
+{
+    const s16x2 v = __builtin_bit_cast(s16x2, hw) + __builtin_bit_cast(s16x2, d);
+    const s16x2 e = __builtin_bit_cast(s16x2, lim) - v;
+    return (__builtin_bit_cast(int, v) | __builtin_bit_cast(int, e)) & (int)0x80008000;
+}
+constexpr int FAR = (-16384) & 0xFFFF;  // a packed position that is outside whatever is added to it
+
+// OP, layout; VA / VB: floats per lane and transfer of the two operands (4 only for KC operands); the workgroup has Z
+// groups of WR x WC waves, a wave MI x NI blocks of 32x32.
+template <int OP, bool NCHW, int VA, int VB, int WR, int WC, int MI, int NI, int Z, int NS>
+__global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_conv_kernel(const F32Params p)
+{
+    constexpr int NG = WR * WC, NT = 64 * NG * Z;
+    constexpr int BM = 32 * MI * WR, BN = 32 * NI * WC;
+    constexpr bool A_KC = OP == OP_WGRAD ? NCHW : !NCHW;
+    constexpr bool B_KC = OP == OP_FWD || NCHW;
+    constexpr bool SWAP = NCHW && OP != OP_WGRAD;       // which operand's index runs along the lanes of the result
+    static_assert((VA == 1 || A_KC) && (VB == 1 || B_KC), "16-byte transfers are for k-contiguous operands");
+    constexpr int A_LD = BM * BK / (64 * VA) / NG, B_LD = BN * BK / (64 * VB) / NG;     // transfers per wave and stage
+    constexpr int L = A_LD + B_LD;
+    static_assert(A_LD >= 1 && B_LD >= 1 && A_LD * NG * 64 * VA == BM * BK && B_LD * NG * 64 * VB == BN * BK, "tile/wave mismatch");
+    static_assert(L * (NS - 1) < 64 && NS >= 3, "ring depth against the range of the load counter");
+    static_assert(NG == 1 || NG == 4, "group size");
+    constexpr int STG = (BM + BN) * BK;                 // floats per stage
+    constexpr int RED = Z > 1 ? Z * BM * BN : 0;        // floats of the partial tiles that meet at the end
+    constexpr int SMEM = Z * NS * STG > RED ? Z * NS * STG : RED;
+    __shared__ __attribute__((aligned(1024))) float smem[SMEM];
+    __shared__ int2 tap_tab[MAX_TAPS + 1];
+
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int zg = wave / NG, gw = wave & (NG - 1);
+    const int wave_m = (gw / WC) * (32 * MI), wave_n = (gw % WC) * (32 * NI);
+
+    // workgroup -> unit: a contiguous range of units per XCD, column tile fastest
+    const int per_xcd = (p.units + 7) / 8;
+    const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (unit >= p.units) return;
+    const int tile = unit % p.tiles, split = unit / p.tiles;
+    const ConvShape &s = p.s;
+    const int RS = s.R * s.S;
+    int mt = tile / p.n_tiles;
+    const int n0 = (tile % p.n_tiles) * BN;
+
+    // ---- geometry of this unit ---------------------------------------------------------------------------
+    int cls = 0;
+    if constexpr (OP == OP_BWD) {
+        while (cls + 1 < p.n_cls && mt >= p.cls_tile0[cls + 1]) ++cls;
+        mt -= p.cls_tile0[cls];
+    }
+    const int m0 = mt * BM;
+    // gathered tensor (x, dy, x), tap grid and direction, pixel grid of the rows
+    const int Ci = OP == OP_BWD ? s.K : s.C, Hi = OP == OP_BWD ? s.P : s.H, Wi = OP == OP_BWD ? s.Q : s.W;
+    int TR = s.R, TS = s.S, Mh = s.P, Mw = s.Q;
+    [[maybe_unused]] int ph = 0, pw = 0, hh0 = 0, vv0 = 0, h_first = 0, v_first = 0;
+    if constexpr (OP == OP_BWD) {
+        ph = cls / s.stride; pw = cls % s.stride;
+        TR = ph < s.R ? (s.R - ph + s.stride - 1) / s.stride : 0;
+        TS = pw < s.S ? (s.S - pw + s.stride - 1) / s.stride : 0;
+        hh0 = ph >= s.pad ? 0 : (s.pad - ph + s.stride - 1) / s.stride;
+        vv0 = pw >= s.pad ? 0 : (s.pad - pw + s.stride - 1) / s.stride;
+        h_first = ph - s.pad + s.stride * hh0; v_first = pw - s.pad + s.stride * vv0;
+        Mh = h_first < s.H ? (s.H - 1 - h_first) / s.stride + 1 : 0;
+        Mw = v_first < s.W ? (s.W - 1 - v_first) / s.stride + 1 : 0;
+    }
+    const int T = TR * TS;
+    const int rows = OP == OP_FWD ? p.M : OP == OP_BWD ? s.N * Mh * Mw : s.K;       // extent of i
+    const int cols = OP == OP_FWD ? s.K : OP == OP_BWD ? s.C : s.C * RS;            // extent of j
+    const int k_lo = OP == OP_WGRAD ? split * p.span : 0;
+    const int k_hi = OP == OP_WGRAD ? min(k_lo + p.span, p.M) : T * Ci;
+    const int KT = k_hi > k_lo ? (k_hi - k_lo + BK * Z - 1) / (BK * Z) : 0;         // stages per group
+    const int k0 = k_lo + zg * BK;                      // first reduction element of this group
+    constexpr int KSTEP = BK * Z;
+    const int lim_hw = pack_hw(Hi - 1, Wi - 1);
+    const int plane = Hi * Wi, PQ = s.P * s.Q;
+
+    // ---- tap table: .x = offset (floats), .y = packed (dh, dv).  Forward and backward-data in NHWC: the gathered
+    // tensor's; backward-data in NCHW: .x = the filter element (its gather works the taps out itself).  Entry T: outside.
+    constexpr bool TABLE = OP != OP_WGRAD && (A_KC || (OP == OP_BWD && B_KC));
+    if constexpr (TABLE) {
+        for (int t = tid; t <= T; t += NT) {
+            const int j = t < T ? t / TS : 0, i = t < T ? t % TS : 0;
+            const int sgn = OP == OP_BWD ? -1 : 1;
+            int2 e = make_int2(sgn * (j * Wi + i) * Ci, pack_hw(sgn * j, sgn * i));
+            if constexpr (OP == OP_BWD && NCHW) e.x = (ph + s.stride * j) * s.S + pw + s.stride * i;
+            if (t == T) e = make_int2(0, FAR);
+            tap_tab[t] = e;
+        }
+    }
+    const int ts_magic = small_magic(TS > 0 ? TS : 1);
+
+    const buf_rsrc_t rs_a = make_buf_rsrc(p.a, p.a_bytes), rs_b = make_buf_rsrc(p.b, p.b_bytes);
+
+    // position of output-grid row m: offset of its tap-0 element in the gathered tensor, and packed (h, w)
+    auto pixel = [&](int m, int &off, int &hw) __attribute__((always_inline)) {
+        off = 0; hw = FAR;
+        if (m < rows) {
+            const unsigned b = (unsigned)m % (unsigned)Mw, t2 = (unsigned)m / (unsigned)Mw;
+            const unsigned a = t2 % (unsigned)Mh, n = t2 / (unsigned)Mh;
+            const int h = OP == OP_FWD ? (int)a * s.stride - s.pad : (int)a + hh0;
+            const int w = OP == OP_FWD ? (int)b * s.stride - s.pad : (int)b + vv0;
+            off = NCHW ? (int)n * Ci * plane + h * Wi + w : (((int)n * Hi + h) * Wi + w) * Ci;
+            hw = pack_hw(h, w);
+        }
+    };
+    // the k-slow operands' transfer i of this wave: reduction row and column it covers (a column's 32-float half is
+    // exchanged in every second group of four rows: the two halves of a wave read rows 4 apart)
+    auto ks_row = [&](int BX, int i) __attribute__((always_inline)) { return BX >= 64 ? (gw + NG * i) / (BX / 64) : (gw + NG * i) * 2 + half; };
+    auto ks_col = [&](int BX, int i) __attribute__((always_inline)) {
+        if (BX < 64) return lane & 31;
+        const int r = (gw + NG * i) / (BX / 64);
+        return (((gw + NG * i) % (BX / 64)) * 64 + lane) ^ (((r >> 2) & 1) * 32);
+    };
+    // ... and the k-contiguous operands': tile row, and the lane's reduction element within a stage
+    auto kc_row = [&](int V, int i) __attribute__((always_inline)) { return V == 4 ? 16 * (gw + NG * i) + (lane >> 2) : 4 * (gw + NG * i) + (lane >> 4); };
+    auto kc_k = [&](int V) __attribute__((always_inline)) {
+        return V == 4 ? ((lane & 3) ^ ((lane >> 4) & 3)) * 4 : ((((lane & 15) >> 2) ^ (gw & 3)) << 2) + (lane & 3);
+    };
+    // one-wave groups with 4-byte transfers: the swizzle changes with the transfer (row / 4 = i), the element does too
+    constexpr bool A_VARK = A_KC && VA == 1 && NG == 1, B_VARK = B_KC && VB == 1 && NG == 1;
+    auto kc_k_var = [&](int i) __attribute__((always_inline)) { return ((((lane & 15) >> 2) ^ (i & 3)) << 2) + (lane & 3); };
+    constexpr int NKA = A_VARK ? 4 : 1, NKB = B_VARK ? 4 : 1;   // distinct reduction elements a lane handles per stage
+
+    // ---- per-transfer state -------------------------------------------------------------------------------
+    // A operand
+    int a_off[A_LD], a_hw[A_LD];        // fixed part: row/pixel offset and packed position
+    int a_k[A_KC ? NKA : A_LD], a_t[A_KC ? NKA : A_LD], a_c[A_KC ? NKA : A_LD];     // reduction position: element, tap or pixel, channel
+    // B operand
+    int b_off[B_LD], b_hw[B_LD];
+    int b_k[B_KC ? NKB : B_LD], b_t[B_KC ? NKB : B_LD], b_c[B_KC ? NKB : B_LD];
+    [[maybe_unused]] int b_q[B_KC ? NKB : B_LD];    // backward-weight: column of the pixel
+
+    // a reduction element in (image, pixel) or (image, row, column) form, and its advance by KSTEP
+    const int adv_n = KSTEP / PQ, adv_pq = KSTEP % PQ;          // NCHW backward-weight
+    const int adv_q = KSTEP % s.Q, adv_p = KSTEP / s.Q % s.P, adv_n3 = KSTEP / s.Q / s.P;
+    const int adv_tq = T > 0 ? KSTEP / T : 0, adv_tr = T > 0 ? KSTEP % T : 0;       // (c, tap) order
+    const int adv_cq = KSTEP / Ci, adv_cr = KSTEP % Ci;         // (tap, c) order
+
+#pragma unroll
+    for (int i = 0; i < A_LD; ++i) {
+        if constexpr (OP == OP_WGRAD && !NCHW) {        // dy[m][k], k-slow
+            const int col = m0 + ks_col(BM, i);
+            a_off[i] = col < rows ? col : -1;
+            a_hw[i] = 0;
+            a_k[i] = k0 + ks_row(BM, i);
+        } else if constexpr (OP == OP_WGRAD) {          // dy[n][k][pq], k-contiguous
+            const int row = m0 + kc_row(VA, i);
+            a_off[i] = row < rows ? row * PQ : -1;
+            a_hw[i] = 0;
+        } else if constexpr (A_KC) {
+            pixel(m0 + kc_row(VA, i), a_off[i], a_hw[i]);
+        } else {
+            pixel(m0 + ks_col(BM, i), a_off[i], a_hw[i]);
+            const int kd = k0 + ks_row(BM, i);
+            a_k[i] = kd; a_c[i] = T > 0 ? kd / T : 0; a_t[i] = T > 0 ? kd % T : 0;
+        }
+    }
+    if constexpr (A_KC) {
+#pragma unroll
+        for (int v = 0; v < NKA; ++v) {
+            const int kd = k0 + (A_VARK ? kc_k_var(v) : kc_k(VA));
+            a_k[v] = kd;
+            if constexpr (OP == OP_WGRAD) { a_c[v] = kd / PQ; a_t[v] = kd % PQ; }
+            else { a_t[v] = kd / Ci; a_c[v] = kd % Ci; }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < B_LD; ++i) {
+        b_hw[i] = 0;
+        if constexpr (OP == OP_FWD) {                   // w[co][kd]
+            const int co = n0 + kc_row(VB, i);
+            b_off[i] = co < cols ? co * (T * Ci) : -1;
+        } else if constexpr (OP == OP_BWD && !NCHW) {   // w[k][rs][c], k-slow
+            const int c = n0 + ks_col(BN, i);
+            b_off[i] = c < cols ? c : -1;
+            const int kd = k0 + ks_row(BN, i);
+            b_k[i] = kd; b_t[i] = kd / Ci; b_c[i] = kd % Ci;
+        } else if constexpr (OP == OP_BWD) {            // w[k][c][rs], taps contiguous
+            const int c = n0 + kc_row(VB, i);
+            b_off[i] = c < cols ? c * RS : -1;
+        } else {                                        // x gather: column = (tap, c) or (c, tap)
+            const int col = n0 + (NCHW ? kc_row(VB, i) : ks_col(BN, i));
+            const int tap = NCHW ? col % RS : col / s.C, c = NCHW ? col / RS : col % s.C;
+            const int r = tap / s.S - s.pad, q = tap % s.S - s.pad;
+            b_off[i] = NCHW ? c * plane + r * s.W + q : (r * s.W + q) * s.C + c;
+            b_hw[i] = col < cols ? pack_hw(r, q) : FAR;
+            if constexpr (!NCHW) {
+                const int m = k0 + ks_row(BN, i);
+                b_k[i] = m; b_q[i] = m % s.Q; b_t[i] = m / s.Q % s.P; b_c[i] = m / s.Q / s.P;
+            }
+        }
+    }
+    if constexpr (B_KC) {
+#pragma unroll
+        for (int v = 0; v < NKB; ++v) {
+            const int kd = k0 + (B_VARK ? kc_k_var(v) : kc_k(VB));
+            b_k[v] = kd;
+            if constexpr (OP == OP_BWD) { b_c[v] = T > 0 ? kd / T : 0; b_t[v] = T > 0 ? kd % T : 0; }
+            else if constexpr (OP == OP_WGRAD) { b_q[v] = kd % s.Q; b_t[v] = kd / s.Q % s.P; b_c[v] = kd / s.Q / s.P; }
+        }
+    }
+
+    float *ring = smem + zg * (NS * STG);
+    // backward-weight: reduction pixel v of the x operand, one stage further
+    auto next_pixel = [&](int v) __attribute__((always_inline)) {
+        b_k[v] += KSTEP;
+        const int q = b_q[v] + adv_q, cq = q >= s.Q ? 1 : 0;
+        b_q[v] = q - (cq ? s.Q : 0);
+        const int pr = b_t[v] + adv_p + cq, cp = pr >= s.P ? 1 : 0;
+        b_t[v] = pr - (cp ? s.P : 0);
+        b_c[v] += adv_n3 + cp;
+    };
+    // The transfers of one stage as L tasks (A's, then B's), each with its address arithmetic, so that they can be spread
+    // between matrix instructions; `advance` moves the shared reduction positions one stage further and fetches the tap
+    // entries of the stage after, before the first task that reads them.
+    [[maybe_unused]] int2 te[NKA];
+    [[maybe_unused]] int we[NKB];
+    auto fetch_taps = [&]() __attribute__((always_inline)) {
+        if constexpr (OP != OP_WGRAD && A_KC) {
+#pragma unroll
+            for (int v = 0; v < NKA; ++v) te[v] = tap_tab[a_t[v] < T ? a_t[v] : T];
+        }
+        if constexpr (OP == OP_BWD && B_KC) {
+#pragma unroll
+            for (int v = 0; v < NKB; ++v) we[v] = b_c[v] * s.C * RS + tap_tab[b_t[v]].x;
+        }
+    };
+    auto task = [&](auto tc, int slot) __attribute__((always_inline)) {
+        constexpr int Tk = decltype(tc)::value;
+        unsigned off;
+        if constexpr (Tk < A_LD) {
+            constexpr int i = Tk, v = A_VARK ? i & 3 : 0;
+            if constexpr (OP == OP_WGRAD && !NCHW) {
+                off = (a_off[i] >= 0 && a_k[i] < k_hi) ? (unsigned)(a_k[i] * s.K + a_off[i]) * 4u : OOB;
+                a_k[i] += KSTEP;
+            } else if constexpr (OP == OP_WGRAD) {
+                off = (a_off[i] >= 0 && a_k[v] < k_hi) ? (unsigned)(a_c[v] * s.K * PQ + a_off[i] + a_t[v]) * 4u : OOB;
+            } else if constexpr (A_KC) {
+                off = outside(a_hw[i], te[v].y, lim_hw) == 0 ? (unsigned)(a_off[i] + te[v].x + a_c[v]) * 4u : OOB;
+            } else {
+                const int j = small_div(a_t[i], ts_magic), q = a_t[i] - j * TS;
+                const int dh = OP == OP_BWD ? -j : j, dv = OP == OP_BWD ? -q : q;
+                const bool ok = a_k[i] < k_hi && outside(a_hw[i], pack_hw(dh, dv), lim_hw) == 0;
+                off = ok ? (unsigned)(a_off[i] + a_c[i] * plane + dh * Wi + dv) * 4u : OOB;
+                a_k[i] += KSTEP;
+                const int t = a_t[i] + adv_tr, carry = t >= T ? 1 : 0;
+                a_t[i] = t - (carry ? T : 0);
+                a_c[i] += adv_tq + carry;
+            }
+            float *d = ring + slot * STG + (gw + NG * i) * (64 * VA);
+            if constexpr (VA == 4) lds_dma16(rs_a, off, d); else lds_dma4(rs_a, off, d);
+        } else {
+            constexpr int i = Tk - A_LD, v = B_KC ? (B_VARK ? i & 3 : 0) : i;
+            if constexpr (OP == OP_FWD) {
+                off = (b_off[i] >= 0 && b_k[v] < k_hi) ? (unsigned)(b_off[i] + b_k[v]) * 4u : OOB;
+            } else if constexpr (OP == OP_BWD && !NCHW) {
+                const int j = small_div(b_t[i], ts_magic), q = b_t[i] - j * TS;
+                const int rs = (ph + s.stride * j) * s.S + pw + s.stride * q;
+                off = (b_off[i] >= 0 && b_k[i] < k_hi) ? (unsigned)((b_c[i] * RS + rs) * s.C + b_off[i]) * 4u : OOB;
+                b_k[i] += KSTEP;
+                const int c = b_c[i] + adv_cr, carry = c >= Ci ? 1 : 0;
+                b_c[i] = c - (carry ? Ci : 0);
+                b_t[i] += adv_cq + carry;
+            } else if constexpr (OP == OP_BWD) {
+                off = (b_off[i] >= 0 && b_k[v] < k_hi) ? (unsigned)(we[v] + b_off[i]) * 4u : OOB;
+            } else {
+                const int h = b_t[v] * s.stride, w = b_q[v] * s.stride;
+                const bool ok = b_k[v] < k_hi && outside(pack_hw(h, w), b_hw[i], lim_hw) == 0;
+                const int org = NCHW ? b_c[v] * s.C * plane + h * s.W + w : ((b_c[v] * s.H + h) * s.W + w) * s.C;
+                off = ok ? (unsigned)(org + b_off[i]) * 4u : OOB;
+                if constexpr (!NCHW) next_pixel(v);
+            }
+            float *d = ring + slot * STG + BM * BK + (gw + NG * i) * (64 * VB);
+            if constexpr (VB == 4) lds_dma16(rs_b, off, d); else lds_dma4(rs_b, off, d);
+        }
+    };
+    auto advance = [&]() __attribute__((always_inline)) {
+        if constexpr (A_KC) {
+#pragma unroll
+            for (int v = 0; v < NKA; ++v) {
+                a_k[v] += KSTEP;
+                if constexpr (OP == OP_WGRAD) {
+                    const int t = a_t[v] + adv_pq, carry = t >= PQ ? 1 : 0;
+                    a_t[v] = t - (carry ? PQ : 0);
+                    a_c[v] += adv_n + carry;
+                } else {
+                    const int c = a_c[v] + adv_cr, carry = c >= Ci ? 1 : 0;
+                    a_c[v] = c - (carry ? Ci : 0);
+                    a_t[v] += adv_cq + carry;
+                }
+            }
+        }
+        if constexpr (B_KC) {
+#pragma unroll
+            for (int v = 0; v < NKB; ++v) {
+                if constexpr (OP == OP_WGRAD) next_pixel(v);
+                else b_k[v] += KSTEP;
+                if constexpr (OP == OP_BWD) {
+                    const int t = b_t[v] + adv_tr, carry = t >= T ? 1 : 0;
+                    b_t[v] = t - (carry ? T : 0);
+                    b_c[v] += adv_tq + carry;
+                }
+            }
+        }
+        fetch_taps();
+    };
+
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+    // one stage: two groups of 8 reduction elements; lanes of half h hold elements 4h..4h+3 of the group, so matrix
+    // step j multiplies elements j and 4+j
+    const int l32 = lane & 31;
+    auto frag = [&](auto kc, auto bx, const float *src, int base, int g, float (&f)[4]) __attribute__((always_inline)) {
+        constexpr bool KC = decltype(kc)::value;
+        constexpr int BX = decltype(bx)::value;
+        if constexpr (KC) {
+            const float4 v = *reinterpret_cast<const float4 *>(src + (base + l32) * BK + (((2 * g + half) ^ ((l32 >> 2) & 3)) << 2));
+            f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+        } else {
+            const int col = BX >= 64 ? (base + l32) ^ (half * 32) : base + l32;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[j] = src[(8 * g + 4 * half + j) * BX + col];
+        }
+    };
+    struct Frags { float a[MI][4], b[NI][4]; };
+    constexpr int N_READ = MI + NI, NMF = 4 * MI * NI;
+    auto read_task = [&](auto tc, Frags &f, int slot, int g) __attribute__((always_inline)) {
+        constexpr int Tk = decltype(tc)::value;
+        const float *sa = ring + slot * STG, *sb = sa + BM * BK;
+        if constexpr (Tk < MI) frag(std::integral_constant<bool, A_KC>{}, IC<BM>{}, sa, wave_m + 32 * Tk, g, f.a[Tk]);
+        else frag(std::integral_constant<bool, B_KC>{}, IC<BN>{}, sb, wave_n + 32 * (Tk - MI), g, f.b[Tk - MI]);
+    };
+    // the matrix instructions of one group of 8 reduction elements with N side tasks spread between them, in pinned
+    // order: the wave issues a task while the matrix pipe works on the instruction before it
+    auto mfma_with = [&](const Frags &f, auto n, auto &&side) __attribute__((always_inline)) {
+        constexpr int N = decltype(n)::value;
+        static_for<NMF>([&](auto sc) __attribute__((always_inline)) {
+            constexpr int S = decltype(sc)::value, q = S / (MI * NI), i = S / NI % MI, j = S % NI;
+            acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x2f32(f.b[j][q], f.a[i][q], acc[i][j], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[i][q], f.b[j][q], acc[i][j], 0, 0, 0);
+            static_for<N>([&](auto tc) __attribute__((always_inline)) {
+                if constexpr (decltype(tc)::value * NMF / N == S) side(tc);
+            });
+            pin();
+        });
+    };
+
+    // Pipeline.  Stage kt lives in slot kt % NS.  Its first group of 8 runs beside the fetch of the second group's
+    // operands and the second half of the transfers of stage kt+NS-1; then the wave waits for its reads of this slot and
+    // its transfers of stage kt+1, one barrier publishes stage kt+1 and frees this slot, and the second group runs beside
+    // the first operand fetch of stage kt+1 and the first half of the transfers of stage kt+NS into the freed slot.
+    constexpr int L1 = (L + 1) / 2, L2 = L - L1;
+    if constexpr (TABLE) __syncthreads();
+    fetch_taps();
+    static_for<NS - 1>([&](auto sc) __attribute__((always_inline)) {
+        static_for<L>([&](auto tc) __attribute__((always_inline)) { task(tc, decltype(sc)::value); });
+        advance();
+    });
+    static_for<L1>([&](auto tc) __attribute__((always_inline)) { task(tc, NS - 1); });
+    wait_vmcnt<L * (NS - 2) + L1>();
+    if constexpr (NG > 1) { pin(); __builtin_amdgcn_s_barrier(); pin(); }
+    Frags f0, f1;
+    static_for<N_READ>([&](auto tc) __attribute__((always_inline)) { read_task(tc, f0, 0, 0); });
+    int slot = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+        const int prev = slot == 0 ? NS - 1 : slot - 1, next = slot + 1 == NS ? 0 : slot + 1;
+        mfma_with(f0, IC<N_READ + L2 + 1>{}, [&](auto tc) __attribute__((always_inline)) {
+            constexpr int Tk = decltype(tc)::value;
+            if constexpr (Tk < N_READ) read_task(tc, f1, slot, 1);
+            else if constexpr (Tk < N_READ + L2) task(IC<L1 + Tk - N_READ>{}, prev);
+            else advance();
+        });
+        wait_lgkmcnt0();
+        wait_vmcnt<L * (NS - 2)>();
+        if constexpr (NG > 1) { pin(); __builtin_amdgcn_s_barrier(); pin(); }
+        mfma_with(f1, IC<N_READ + L1>{}, [&](auto tc) __attribute__((always_inline)) {
+            constexpr int Tk = decltype(tc)::value;
+            if constexpr (Tk < N_READ) read_task(tc, f0, next, 0);
+            else task(IC<Tk - N_READ>{}, slot);
+        });
+        slot = next;
+    }
+    wait_vmcnt<0>();                        // zero-fill transfers of the stages past the end
+
+    // ---- results ---------------------------------------------------------------------------------------------
+    float *out = p.out;
+    if constexpr (OP == OP_WGRAD) out += (size_t)split * ((size_t)rows * cols);
+    // offset of result row i (without the column's share), or -1 past the end
+    auto row_off = [&](int i) __attribute__((always_inline)) -> long long {
+        if (i >= rows) return -1;
+        if constexpr (OP == OP_WGRAD) return (long long)i * cols;
+        else if constexpr (OP == OP_FWD) {
+            if (!NCHW) return (long long)i * cols;
+            const unsigned n = (unsigned)i / (unsigned)PQ, pq = (unsigned)i % (unsigned)PQ;
+            return (long long)n * cols * PQ + pq;
+        } else {
+            unsigned pix = (unsigned)i;
+            if (NCHW || s.stride != 1 || h_first != 0 || v_first != 0) {
+                const unsigned b = (unsigned)i % (unsigned)Mw, t2 = (unsigned)i / (unsigned)Mw, a = t2 % (unsigned)Mh, n = t2 / (unsigned)Mh;
+                const unsigned hw = (h_first + s.stride * a) * s.W + v_first + s.stride * b;
+                if (NCHW) return (long long)n * cols * (s.H * s.W) + hw;
+                pix = n * (s.H * s.W) + hw;
+            }
+            return (long long)pix * cols;
+        }
+    };
+    const int col_stride = !NCHW || OP == OP_WGRAD ? 1 : OP == OP_FWD ? PQ : s.H * s.W;
+    auto put = [&](long long ro, int j, float v) __attribute__((always_inline)) {
+        if (ro < 0 || j >= cols) return;
+        const long long o = ro + (long long)j * col_stride;
+        if constexpr (OP == OP_FWD) {
+            if (p.bias != nullptr) v += p.bias[j];
+            if (p.relu) v = fmaxf(v, 0.f);
+        }
+        if constexpr (OP == OP_BWD) {
+            if (p.mask != nullptr && !(p.mask[o] > 0.f)) v = 0.f;
+        }
+        out[o] = v;
+    };
+    // accumulator element e of a block: index along the registers 8*(e/4) + 4*half + e%4, along the lanes lane%32
+    if constexpr (Z == 1) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            if constexpr (SWAP) {
+                const long long ro = row_off(m0 + wave_m + 32 * i + l32);
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) put(ro, n0 + wave_n + 32 * j + 8 * (e >> 2) + 4 * half + (e & 3), acc[i][j][e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const long long ro = row_off(m0 + wave_m + 32 * i + 8 * (e >> 2) + 4 * half + (e & 3));
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) put(ro, n0 + wave_n + 32 * j + l32, acc[i][j][e]);
+                }
+            }
+        }
+    } else {
+        __syncthreads();                    // every group is done with its ring
+        constexpr int WT = MI * NI * 1024;  // floats of a wave's tile: [block][e][lane]
+        float *mine = smem + (zg * NG + gw) * WT;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) mine[(i * NI + j) * 1024 + e * 64 + lane] = acc[i][j][e];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NG * WT / NT; ++q) {
+            const int idx = q * NT + tid;
+            float v = 0.f;
+#pragma unroll
+            for (int z = 0; z < Z; ++z) v += smem[z * NG * WT + idx];
+            const int ln = idx & 63, e = (idx >> 6) & 15, blk = idx >> 10;
+            const int wv = blk / (MI * NI), bi = blk % (MI * NI) / NI, bj = blk % NI;
+            const int reg = 8 * (e >> 2) + 4 * (ln >> 5) + (e & 3), al = ln & 31;
+            const int wm = (wv / WC) * (32 * MI) + 32 * bi, wn = (wv % WC) * (32 * NI) + 32 * bj;
+            put(row_off(m0 + wm + (SWAP ? al : reg)), n0 + wn + (SWAP ? reg : al), v);
+        }
+    }
+}
+
+// ---- tile choice ------------------------------------------------------------------------------------------------
+// bm x bn tile, z groups of waves, waves per SIMD of one workgroup; eff: share of the fp32 matrix rate the tile sustains
+// with one workgroup on a CU, and with several
+struct F32Tile { int bm, bn, z; float eff1, eff; const char *name; };
+const F32Tile kTiles[] = {
+    {128, 128, 1, 0.62f, 0.88f, "f32_128x128"},
+    {128, 64, 1, 0.55f, 0.80f, "f32_128x64"},
+    {64, 64, 2, 0.55f, 0.72f, "f32_64x64_z2"},
+    {128, 32, 1, 0.40f, 0.70f, "f32_128x32"},
+    {32, 128, 1, 0.40f, 0.70f, "f32_32x128"},
+    {32, 32, 8, 0.40f, 0.50f, "f32_32x32_z8"},
+};
+constexpr int N_TILES = sizeof(kTiles) / sizeof(kTiles[0]);
+
+template <int OP, bool NCHW, int VA, int VB, int WR, int WC, int MI, int NI, int Z, int NS>
+int launch(const F32Params &p, hipStream_t st)
+{
+    hipLaunchKernelGGL((f32_conv_kernel<OP, NCHW, VA, VB, WR, WC, MI, NI, Z, NS>), dim3((unsigned)((p.units + 7) / 8 * 8)),
+                       dim3(64 * WR * WC * Z), 0, st, p);
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+}
+
+template <int OP, bool NCHW, int VA, int VB>
+int launch_tile(int t, const F32Params &p, hipStream_t st)
+{
+    switch (t) {
+    case 0: return launch<OP, NCHW, VA, VB, 2, 2, 2, 2, 1, 3>(p, st);
+    case 1: return launch<OP, NCHW, VA, VB, 2, 2, 2, 1, 1, 3>(p, st);
+    case 2: return launch<OP, NCHW, VA, VB, 2, 2, 1, 1, 2, 3>(p, st);
+    // 32 rows of an operand are too few 16-byte transfers for four waves
+    case 3: return launch<OP, NCHW, VA, 1, 4, 1, 1, 1, 1, 3>(p, st);
+    case 4: return launch<OP, NCHW, 1, VB, 1, 4, 1, 1, 1, 3>(p, st);
+    default: return launch<OP, NCHW, VA, VB, 1, 1, 1, 1, 8, 3>(p, st);
+    }
+}
+
+int launch_op(int op, bool nchw, int t, const F32Params &p, hipStream_t st)
+{
+    const ConvShape &s = p.s;
+    if (op == OP_FWD) {
+        if (!nchw) return s.C % 4 == 0 ? launch_tile<OP_FWD, false, 4, 4>(t, p, st) : launch_tile<OP_FWD, false, 1, 1>(t, p, st);
+        return (s.C * s.R * s.S) % 4 == 0 ? launch_tile<OP_FWD, true, 1, 4>(t, p, st) : launch_tile<OP_FWD, true, 1, 1>(t, p, st);
+    }
+    if (op == OP_BWD) {
+        if (!nchw) return s.K % 4 == 0 ? launch_tile<OP_BWD, false, 4, 1>(t, p, st) : launch_tile<OP_BWD, false, 1, 1>(t, p, st);
+        return launch_tile<OP_BWD, true, 1, 1>(t, p, st);
+    }
+    return nchw ? launch_tile<OP_WGRAD, true, 1, 1>(t, p, st) : launch_tile<OP_WGRAD, false, 1, 1>(t, p, st);
+}
+
+// forced tile (tests and tuning sweeps): MXC_FORCE_VARIANT for forward and backward-data, MXC_FORCE_WGRAD=<tile>[/<splits>]
+int forced_tile(const char *env, int *splits)
+{
+    const char *f = getenv(env);
+    if (f == nullptr) return -1;
+    const char *slash = strchr(f, '/');
+    const size_t len = slash ? (size_t)(slash - f) : strlen(f);
+    for (int t = 0; t < N_TILES; ++t)
+        if (strlen(kTiles[t].name) == len && !strncmp(f, kTiles[t].name, len)) {
+            if (splits && slash) *splits = atoi(slash + 1);
+            return t;
+        }
+    return -1;
+}
+
+// Modelled clocks of `tiles` workgroups of tile t that each reduce `k` elements: a CU's workgroups share its matrix
+// pipes; 4000 clocks of launch, pipeline fill and result stores per round of workgroups.
+double model_clocks(const F32Tile &t, long long tiles, long long k)
+{
+    const long long per_cu = (tiles + 255) / 256;
+    const double stages = (double)((k + BK * t.z - 1) / (BK * t.z)) * t.z;
+    const double work = stages * (double)t.bm * t.bn * BK * 2.0 / 256.0;
+    return (double)per_cu * work / (per_cu > 1 ? t.eff : t.eff1) + 4000.0 + 1500.0 * (per_cu - 1);
+}
+
+struct F32Plan { int tile, splits, span; };
+
+long long class_rows(const ConvShape &s, int ph, int pw)
+{
+    const int hh0 = ph >= s.pad ? 0 : (s.pad - ph + s.stride - 1) / s.stride, vv0 = pw >= s.pad ? 0 : (s.pad - pw + s.stride - 1) / s.stride;
+    const int hf = ph - s.pad + s.stride * hh0, vf = pw - s.pad + s.stride * vv0;
+    const int Mh = hf < s.H ? (s.H - 1 - hf) / s.stride + 1 : 0, Mw = vf < s.W ? (s.W - 1 - vf) / s.stride + 1 : 0;
+    return (long long)s.N * Mh * Mw;
+}
+
+F32Plan plan_rows(const ConvShape &s, int op)
+{
+    int t = forced_tile("MXC_FORCE_VARIANT", nullptr);
+    if (t >= 0) return F32Plan{t, 1, 0};
+    double best = 1e300;
+    F32Plan pl{0, 1, 0};
+    for (t = 0; t < N_TILES; ++t) {
+        const long long cols = op == OP_FWD ? s.K : s.C, nt = (cols + kTiles[t].bn - 1) / kTiles[t].bn;
+        const long long k = op == OP_FWD ? (long long)s.R * s.S * s.C
+                                         : (long long)((s.R + s.stride - 1) / s.stride) * ((s.S + s.stride - 1) / s.stride) * s.K;
+        const long long m = op == OP_FWD ? (long long)s.N * s.P * s.Q : (long long)s.N * s.H * s.W;
+        const double c = model_clocks(kTiles[t], (m + kTiles[t].bm - 1) / kTiles[t].bm * nt, k);
+        if (c < best) { best = c; pl.tile = t; }
+    }
+    return pl;
+}
+
+// Backward-weight: tile and number of pixel ranges; every range beyond the first writes and re-reads one fp32 dw
+// (8 bytes per element at about 3 TB/s) and makes the summing launch necessary (about 5000 clocks).
+F32Plan plan_wgrad(const ConvShape &s)
+{
+    int fs = 0;
+    const int ft = forced_tile("MXC_FORCE_WGRAD", &fs);
+    const long long M = (long long)s.N * s.P * s.Q, cols = (long long)s.C * s.R * s.S;
+    double best = 1e300;
+    F32Plan pl{0, 1, (int)M};
+    for (int t = 0; t < N_TILES; ++t) {
+        if (ft >= 0 && t != ft) continue;
+        const F32Tile &tc = kTiles[t];
+        const long long tiles = ((s.K + tc.bm - 1) / tc.bm) * ((cols + tc.bn - 1) / tc.bn), q = (long long)BK * tc.z;
+        long long max_sp = M / (4 * q);
+        if (max_sp > 512) max_sp = 512;
+        if (max_sp < 1) max_sp = 1;
+        for (long long sp = 1; sp <= max_sp; sp += 1 + sp / 16) {
+            if (fs > 0 && sp > 1) break;
+            long long want = fs > 0 ? (fs < max_sp ? fs : max_sp) : sp;
+            const long long span = ((M + want - 1) / want + q - 1) / q * q, used = (M + span - 1) / span;
+            double c = model_clocks(tc, tiles * used, span);
+            if (used > 1) c += 5000.0 + (double)used * s.K * cols * 8.0 / 3e12 * 2.1e9;
+            if (c < best) { best = c; pl = F32Plan{t, (int)used, (int)span}; }
+        }
+    }
+    return pl;
+}
+
+}  // namespace
+
+const char *f32_tile_name(int index) { return index >= 0 && index < N_TILES ? kTiles[index].name : nullptr; }
+
+// The kernel addresses its operands with 31-bit byte offsets, packs positions into 16 bits and holds MAX_TAPS taps.
+bool f32_supported(const ConvShape &s)
+{
+    const long long lim = 0x7FFF0000ll, x = (long long)s.N * s.C * s.H * s.W * 4, y = (long long)s.N * s.K * s.P * s.Q * 4,
+                    w = (long long)s.K * s.C * s.R * s.S * 4;
+    return x < lim && y < lim && w < lim && s.R * s.S <= MAX_TAPS && s.stride <= 4 && s.H + s.pad + s.R <= 8192 && s.W + s.pad + s.S <= 8192 &&
+           (long long)s.P * s.stride <= 8192 && (long long)s.Q * s.stride <= 8192;
+}
+
+static int run(int op, bool nchw, int t, F32Params &p, long long row_tiles, long long cols, int splits, hipStream_t st)
+{
+    const long long nt = (cols + kTiles[t].bn - 1) / kTiles[t].bn;
+    if (row_tiles * nt * splits > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
+    p.n_tiles = (int)nt;
+    p.tiles = (int)(row_tiles * nt);
+    p.units = p.tiles * splits;
+    return launch_op(op, nchw, t, p, st);
+}
+
+int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y, hipStream_t st, const char **variant, const PostOp &post)
+{
+    const int t = plan_rows(s, OP_FWD).tile;
+    F32Params p{};
+    p.a = (const float *)x; p.b = (const float *)w; p.out = (float *)y;
+    p.a_bytes = (unsigned)((long long)s.N * s.C * s.H * s.W * 4);
+    p.b_bytes = (unsigned)((long long)s.K * s.C * s.R * s.S * 4);
+    p.s = s;
+    p.M = s.N * s.P * s.Q;
+    p.bias = post.bias; p.relu = post.relu;
+    *variant = kTiles[t].name;
+    return run(OP_FWD, nchw, t, p, (p.M + kTiles[t].bm - 1) / kTiles[t].bm, s.K, 1, st);
+}
+
+int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, void *dx, hipStream_t st, const char **variant, const PostOp &post)
+{
+    const int t = plan_rows(s, OP_BWD).tile;
+    F32Params p{};
+    p.a = (const float *)dy; p.b = (const float *)w; p.out = (float *)dx;
+    p.a_bytes = (unsigned)((long long)s.N * s.K * s.P * s.Q * 4);
+    p.b_bytes = (unsigned)((long long)s.K * s.C * s.R * s.S * 4);
+    p.s = s;
+    p.mask = (const float *)post.mask;
+    p.n_cls = s.stride * s.stride;
+    long long tiles = 0;
+    for (int c = 0; c < p.n_cls; ++c) {
+        p.cls_tile0[c] = (int)tiles;
+        tiles += (class_rows(s, c / s.stride, c % s.stride) + kTiles[t].bm - 1) / kTiles[t].bm;
+    }
+    p.cls_tile0[p.n_cls] = (int)tiles;
+    *variant = kTiles[t].name;
+    return run(OP_BWD, nchw, t, p, tiles, s.C, 1, st);
+}
+
+size_t f32_wgrad_workspace(const ConvShape &s) { return (size_t)plan_wgrad(s).splits * s.K * s.C * s.R * s.S * sizeof(float); }
+
+int f32_wgrad(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, float *partial, hipStream_t st, const char **variant)
+{
+    const F32Plan pl = plan_wgrad(s);
+    const F32Tile &tc = kTiles[pl.tile];
+    F32Params p{};
+    p.a = (const float *)dy; p.b = (const float *)x; p.out = pl.splits > 1 ? partial : (float *)dw;
+    p.a_bytes = (unsigned)((long long)s.N * s.K * s.P * s.Q * 4);
+    p.b_bytes = (unsigned)((long long)s.N * s.C * s.H * s.W * 4);
+    p.s = s;
+    p.M = s.N * s.P * s.Q;
+    p.span = pl.span;
+    const long long cols = (long long)s.C * s.R * s.S;
+    *variant = tc.name;
+    const int rc = run(OP_WGRAD, nchw, pl.tile, p, (s.K + tc.bm - 1) / tc.bm, cols, pl.splits, st);
+    if (rc != MXC_OK || pl.splits == 1) return rc;
+    return sum_splits(partial, dw, false, s.K * cols, pl.splits, st);
+}
+
+}  // namespace mxc

@@ -91,6 +91,17 @@ __device__ __forceinline__ void lds_dma16(buf_rsrc_t rsrc, unsigned byte_off, co
                  : "memory");
 }
 
+// the same with 4 bytes per lane: lane l's dword lands at lds_base + 4*l
+__device__ __forceinline__ void lds_dma4(buf_rsrc_t rsrc, unsigned byte_off, const void *lds_base_uniform)
+{
+    typedef __attribute__((address_space(3))) const void *lds_cvptr;
+    const unsigned lds_addr = (unsigned)(uintptr_t)(lds_cvptr)lds_base_uniform;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_addr), "v"(byte_off), "s"(rsrc)
+                 : "memory");
+}
+
 // lds_dma16 marked non-temporal: a streaming read that the caches need not keep
 __device__ __forceinline__ void lds_dma16_nt(buf_rsrc_t rsrc, unsigned byte_off, const void *lds_base_uniform)
 {
@@ -156,6 +167,15 @@ int direct_bwd_weight_splits(const ConvShape &s);
 int direct_bwd_weight(const ConvShape &s, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16,
                       float *partial, int splits, hipStream_t st);
 
+// ---- fp32.hip: fp32 matrix-core convolution, NHWC/KRSC or NCHW/KCRS operands read in place -----------------
+bool f32_supported(const ConvShape &s);
+int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y, hipStream_t st, const char **variant, const PostOp &post);
+int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, void *dx, hipStream_t st, const char **variant,
+                 const PostOp &post);
+size_t f32_wgrad_workspace(const ConvShape &s);       // bytes of fp32 partial tensors
+int f32_wgrad(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, float *partial, hipStream_t st, const char **variant);
+const char *f32_tile_name(int index);
+
 // ---- igemm.hip: bf16 MFMA implicit GEMM (NHWC/KRSC) ---------------------------
 bool igemm_fwd_supported(const ConvShape &s);
 // split_ws: scratch of igemm_fwd_split_bytes(s) bytes for a split reduction (may be null: never split)
@@ -184,6 +204,8 @@ const char *igemm_stream_name(int index);   // names of the whole-launch kernels
 // key (rows, output columns, reduction length) of the calling thread's last implicit-GEMM plan lookup
 void igemm_last_plan_key(long long *M, int *Co, int *Kd);
 const char *wgrad_tile_name(int index);
+// dw[i] = sum over z of partial[z][i] in a fixed order (see the reduce kernels of wgrad.hip); dw fp32, or bf16 rounded once
+int sum_splits(const float *partial, void *dw, bool dw_bf16, long long total, int splits, hipStream_t st);
 
 // ---- the implicit GEMM as its kernels see it (igemm.hip, stream.hip) ----------------------------------
 constexpr int MAX_TAPS = 127;   // tap table capacity (11x11 = 121 fits)

@@ -602,6 +602,20 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
+template <typename OUT>
+static int sum_splits_to(const float *partial, OUT *dw, int total, int splits, hipStream_t st)
+{
+    WgradGeom g{};
+    g.K = 1; g.R = 1; g.S = 1; g.C = total; g.s2d = 1;
+    return launch_reduce(g, const_cast<float *>(partial), dw, splits, total, true, st);
+}
+
+int sum_splits(const float *partial, void *dw, bool dw_bf16, long long total, int splits, hipStream_t st)
+{
+    if (total > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
+    return dw_bf16 ? sum_splits_to(partial, (bf16_t *)dw, (int)total, splits, st) : sum_splits_to(partial, (float *)dw, (int)total, splits, st);
+}
+
 int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_bf16, float *partial, hipStream_t st,
           const char **variant)
 {
