@@ -103,6 +103,47 @@ struct InputPrep {
 };
 inline void note_form(const InputPrep &ip, int form) { if (ip.form) *ip.form = form; }
 
+// ---- bf16 channel counts that are no multiple of 8 -----------------------------------------------------------------
+
+ConvShape with_padded_k(const ConvShape &s)
+{
+    ConvShape t = s;
+    t.K = (s.K + 7) / 8 * 8;
+    if (t.K != s.K) t.Kr = s.K;
+    return t;
+}
+
+// ... and the input's too, except for the first layers' (at most 4, which have packings of their own)
+ConvShape with_padded_channels(const ConvShape &s)
+{
+    ConvShape t = with_padded_k(s);
+    if (s.C > 4 && s.C % 8 != 0) { t.C = (s.C + 7) / 8 * 8; t.Cr = s.C; }
+    return t;
+}
+
+// whether a matrix-core path takes the (padded) problem, in the order the passes below try them
+bool mfma_fwd_supported(const ConvShape &s)
+{
+    if (s.C % 8 == 0) return igemm_fwd_supported(s);
+    return (s2d_applicable(s) && igemm_fwd_supported(s2d_shape(s))) || (s.C <= 4 && igemm_fwd_smallc_supported(s));
+}
+// ... by the general kernels on the re-packed filter, not by one of the first layers' packings or from the filter in place
+bool mfma_bwd_data_plain(const ConvShape &s)
+{
+    return !(s2d_applicable(s) && igemm_bwd_data_supported(s2d_shape(s))) && !igemm_bwd_data_smallc_supported(s) && igemm_bwd_data_supported(s) &&
+           !bwd_data_reads_filter_in_place(s);
+}
+bool mfma_bwd_data_supported(const ConvShape &s)
+{
+    return (s2d_applicable(s) && igemm_bwd_data_supported(s2d_shape(s))) || igemm_bwd_data_smallc_supported(s) || igemm_bwd_data_supported(s);
+}
+bool mfma_wgrad_supported(const ConvShape &s)
+{
+    if (s.C % 8 == 0) return wgrad_supported(wgrad_geom_plain(s));
+    return (s2d_applicable(s) && wgrad_supported(wgrad_geom_s2d(s))) || (s.C <= 4 && wgrad_supported(wgrad_geom_smallc(s))) ||
+           wgrad_supported(wgrad_geom_chanpad(s));
+}
+
 int fwd_nhwc(const ConvShape &s, int dtype, const void *x, const void *w, void *y, const PostOp &post, Carver &ws, hipStream_t st,
              bool dry, const InputPrep &ip = InputPrep())
 {
@@ -152,9 +193,12 @@ int fwd_nhwc(const ConvShape &s, int dtype, const void *x, const void *w, void *
         void *xp = xws.take((size_t)s.N * s.H * s.W * C8 * 2);
         void *wp = run ? ws.take((size_t)s.K * s.R * s.S * C8 * 2) : nullptr;
         if (dry) return MXC_OK;
-        if (pack) MXC_TRY(pad_channels(x, xp, (long long)s.N * s.H * s.W, s.C, st));
+        RelayJob jobs[2];
+        int nj = 0;
+        if (pack) jobs[nj++] = relay_pad(x, xp, (long long)s.N * s.H * s.W, s.C, C8);
+        if (run) jobs[nj++] = relay_pad(w, wp, (long long)s.K * s.R * s.S, s.C, C8);
+        MXC_TRY(relayout(jobs, nj, st));
         if (!run) return MXC_OK;
-        MXC_TRY(pad_channels(w, wp, (long long)s.K * s.R * s.S, s.C, st));
         const int rc = igemm_fwd(with_channels(s, C8), xp, wp, y, st, &v, post);
         set_variant("fwd", (std::string("chanpad+") + v).c_str());
         return rc;
@@ -178,9 +222,25 @@ int fwd_nhwc(const ConvShape &s, int dtype, const void *x, const void *w, void *
 enum FilterMode { FILTER_RAW = 0, FILTER_PREPARE_ONLY = 1, FILTER_PREPARED = 2 };
 
 int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, void *dx, const PostOp &post, Carver &fws,
-                  Carver &ws, hipStream_t st, bool dry, FilterMode mode = FILTER_RAW)
+                  Carver &ws, hipStream_t st, bool dry, FilterMode mode = FILTER_RAW, bool kcrs = false)
 {
     const bool prep = mode != FILTER_PREPARED, run = mode != FILTER_PREPARE_ONLY;
+    if (const ConvShape s8 = with_padded_k(s); dtype == MXC_BF16 && s8.K != s.K && !g_lean && mfma_bwd_data_supported(s8)) {
+        // the GEMM reduces over whole 16-byte chunks of dy: zero-pad its channels (the filter form follows, see real_k)
+        void *dy8 = run ? ws.take((size_t)s.N * s.P * s.Q * s8.K * 2) : nullptr;
+        if (!dry && run) {
+            RelayJob jobs[2] = {relay_pad(dy, dy8, (long long)s.N * s.P * s.Q, s.K, s8.K)};
+            int nj = 1;
+            if (mode == FILTER_RAW && mfma_bwd_data_plain(s8)) {        // its filter form in the same launch
+                Carver peek = fws;
+                jobs[nj++] = relay_bwd_filter(s8, w, peek.take(igemm_bwd_data_workspace(s8)), kcrs);
+                MXC_TRY(relayout(jobs, nj, st));
+                return bwd_data_nhwc(s8, dtype, dy8, w, dx, post, fws, ws, st, dry, FILTER_PREPARED, kcrs);
+            }
+            MXC_TRY(relayout(jobs, nj, st));
+        }
+        return bwd_data_nhwc(s8, dtype, dy8, w, dx, post, fws, ws, st, dry, mode, kcrs);
+    }
     if (dtype == MXC_BF16 && s.K % 8 == 0 && s2d_applicable(s) && igemm_bwd_data_supported(s2d_shape(s))) {
         const ConvShape s2 = s2d_shape(s);
         void *w2 = fws.take((size_t)s2.K * s2.R * s2.S * s2.C * 2), *wt = fws.take(igemm_bwd_data_workspace(s2));
@@ -215,7 +275,7 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
         if (dry) return MXC_OK;
         const char *v = "";
         // a filter the kernel reads in place stays where it is unless the caller keeps a prepared copy
-        if (prep) MXC_TRY(igemm_bwd_data_prepare(s, w, wt, st, mode == FILTER_PREPARE_ONLY));
+        if (prep) MXC_TRY(igemm_bwd_data_prepare(s, w, wt, st, mode == FILTER_PREPARE_ONLY, kcrs));
         if (!run) return MXC_OK;
         const int rc = igemm_bwd_data(s, dy, mode == FILTER_RAW ? w : wt, dx, wt, st, &v, post, split_ws);
         set_variant("bwd_data", v);
@@ -232,17 +292,28 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
 
 // ip: see InputMode (the forms are those of fwd_nhwc, chosen by the same tests in the same order; only
 // INPUT_RAW and INPUT_PREPARED reach this function)
-int bwd_weight_nhwc(const ConvShape &s, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16, Carver &ws,
-                    hipStream_t st, bool dry, const InputPrep &ip = InputPrep())
+int bwd_weight_nhwc(const ConvShape &s_in, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16, Carver &ws,
+                    hipStream_t st, bool dry, const InputPrep &ip = InputPrep(), bool kcrs = false)
 {
     const char *v = "";
     Carver &xws = ip.xws ? *ip.xws : ws;
     const bool pack = ip.mode != INPUT_PREPARED;
+    // dy's channels come in whole 16-byte chunks: zero-pad them where they do not (dw keeps its own rows, see real_k)
+    ConvShape s = s_in;
+    RelayJob jobs[2];
+    int nj = 0;
+    if (const ConvShape s8 = with_padded_k(s); dtype == MXC_BF16 && s8.K != s.K && !g_lean && mfma_wgrad_supported(s8)) {
+        void *dy8 = ws.take((size_t)s.N * s.P * s.Q * s8.K * 2);
+        jobs[nj++] = relay_pad(dy, dy8, (long long)s.N * s.P * s.Q, s.K, s8.K);
+        dy = dy8;
+        s = s8;
+    }
     if (dtype == MXC_BF16 && s.C % 8 == 0 && wgrad_supported(wgrad_geom_plain(s))) {
         const WgradGeom g = wgrad_geom_plain(s);
         float *partial = (float *)ws.take(wgrad_workspace(g));
         if (dry) return MXC_OK;
-        const int rc = wgrad(g, x, dy, dw, dw_bf16, partial, st, &v);
+        MXC_TRY(relayout(jobs, nj, st));
+        const int rc = wgrad(g, x, dy, dw, dw_bf16, kcrs, partial, st, &v);
         set_variant("bwd_weight", v);
         return rc;
     }
@@ -254,7 +325,8 @@ int bwd_weight_nhwc(const ConvShape &s, int dtype, const void *x, const void *dy
         float *partial = (float *)ws.take(wgrad_workspace(g));
         if (dry) return MXC_OK;
         if (pack) MXC_TRY(s2d_pack_x(s, x, x2, st));
-        const int rc = wgrad(g, x2, dy, dw, dw_bf16, partial, st, &v);
+        MXC_TRY(relayout(jobs, nj, st));
+        const int rc = wgrad(g, x2, dy, dw, dw_bf16, kcrs, partial, st, &v);
         set_variant("bwd_weight", (std::string("s2d+") + v).c_str());
         return rc;
     }
@@ -266,7 +338,8 @@ int bwd_weight_nhwc(const ConvShape &s, int dtype, const void *x, const void *dy
         float *partial = (float *)ws.take(wgrad_workspace(g));
         if (dry) return MXC_OK;
         if (pack) MXC_TRY(smallc_pack_x(s, x, xp, st));
-        const int rc = wgrad(g, xp, dy, dw, dw_bf16, partial, st, &v);
+        MXC_TRY(relayout(jobs, nj, st));
+        const int rc = wgrad(g, xp, dy, dw, dw_bf16, kcrs, partial, st, &v);
         set_variant("bwd_weight", (std::string("smallc+") + v).c_str());
         return rc;
     }
@@ -276,8 +349,9 @@ int bwd_weight_nhwc(const ConvShape &s, int dtype, const void *x, const void *dy
         void *xp = xws.take((size_t)s.N * s.H * s.W * g.pix * 2);
         float *partial = (float *)ws.take(wgrad_workspace(g));
         if (dry) return MXC_OK;
-        if (pack) MXC_TRY(pad_channels(x, xp, (long long)s.N * s.H * s.W, s.C, st));
-        const int rc = wgrad(g, xp, dy, dw, dw_bf16, partial, st, &v);
+        if (pack) jobs[nj++] = relay_pad(x, xp, (long long)s.N * s.H * s.W, s.C, g.pix);
+        MXC_TRY(relayout(jobs, nj, st));
+        const int rc = wgrad(g, xp, dy, dw, dw_bf16, kcrs, partial, st, &v);
         set_variant("bwd_weight", (std::string("chanpad+") + v).c_str());
         return rc;
     }
@@ -339,6 +413,72 @@ int run_f32(int pass, const ConvShape &s, int layout, const void *a, const void 
 
 // ---- one driver per pass: handles the caller's layout ---------------------------
 
+// bf16 NCHW on the matrix cores.  The converted copies have their channels padded to whole 16-byte chunks (s carries the
+// padded and the problem's own counts), all conversions before the kernel share one launch, the filter goes straight
+// into the form backward-data reads, and dw leaves the split reduction in KCRS order.
+int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, void *out, const PostOp &post, Carver &fws, Carver &ws,
+                  hipStream_t st, bool dry, FilterMode mode)
+{
+    const int C = real_c(s), K = real_k(s), RS = s.R * s.S;
+    const bool first = s.C <= 4;           // first layers: few channels, converted by the kernels made for them
+    const size_t nx = (size_t)s.N * s.C * s.H * s.W * 2, ny = (size_t)s.N * s.K * s.P * s.Q * 2, nw = (size_t)K * s.C * RS * 2;
+    RelayJob jobs[MAX_RELAY_JOBS];
+    int nj = 0;
+    auto convert_x = [&](const void *src, void *dst) -> int {
+        if (first) return launch_transpose(src, dst, s.N, C, s.H * s.W, 2, st);
+        jobs[nj++] = relay_to_nhwc(src, dst, s.N, C, s.H * s.W, s.C);
+        return MXC_OK;
+    };
+    if (pass == MXC_FWD) {
+        void *x2 = ws.take(nx), *w2 = ws.take(nw), *y2 = ws.take(ny);
+        if (!dry) {
+            MXC_TRY(convert_x(a, x2));
+            jobs[nj++] = relay_to_nhwc(b, w2, K, C, RS, s.C);
+            MXC_TRY(relayout(jobs, nj, st));
+        }
+        MXC_TRY(fwd_nhwc(s, MXC_BF16, x2, w2, y2, post, ws, st, dry));
+        if (dry) return MXC_OK;
+        jobs[0] = relay_to_nchw(y2, out, s.N, K, s.P * s.Q, s.K);
+        return relayout(jobs, 1, st);
+    }
+    if (pass == MXC_BWD_DATA) {
+        const bool prep = mode != FILTER_PREPARED, run = mode != FILTER_PREPARE_ONLY;
+        const bool plain = mfma_bwd_data_plain(s);     // the filter form is made here, together with the conversions
+        void *w2 = first ? fws.take(nw) : nullptr;     // first layers: their packings start from KRSC
+        void *dy2 = run ? ws.take(ny) : nullptr, *dx2 = run ? ws.take(nx) : nullptr;
+        void *mask2 = run && (post.mask != nullptr || post.relu) ? ws.take(nx) : nullptr;   // see run_pass
+        PostOp post2 = post;
+        post2.relu = 0;
+        FilterMode inner = mode;
+        if (!dry) {
+            if (run) jobs[nj++] = relay_to_nhwc(a, dy2, s.N, K, s.P * s.Q, s.K);
+            if (run && post.mask != nullptr) {
+                MXC_TRY(convert_x(post.mask, mask2));
+                post2.mask = mask2;
+            }
+            if (prep && first) jobs[nj++] = relay_to_nhwc(b, w2, K, C, RS, C);
+            if (prep && plain && run) {
+                Carver peek = fws;
+                jobs[nj++] = relay_bwd_filter(s, b, peek.take(igemm_bwd_data_workspace(s)), true);
+                inner = FILTER_PREPARED;
+            }
+            MXC_TRY(relayout(jobs, nj, st));
+        }
+        MXC_TRY(bwd_data_nhwc(s, MXC_BF16, dy2, first ? w2 : b, dx2, post2, fws, ws, st, dry, inner, !first));
+        if (dry || !run) return MXC_OK;
+        if (first) return launch_transpose(dx2, out, s.N, s.H * s.W, C, 2, st);
+        jobs[0] = relay_to_nchw(dx2, out, s.N, C, s.H * s.W, s.C);
+        return relayout(jobs, 1, st);
+    }
+    void *x2 = ws.take(nx), *dy2 = ws.take(ny);
+    if (!dry) {
+        MXC_TRY(convert_x(a, x2));
+        jobs[nj++] = relay_to_nhwc(b, dy2, s.N, K, s.P * s.Q, s.K);
+        MXC_TRY(relayout(jobs, nj, st));
+    }
+    return bwd_weight_nhwc(s, MXC_BF16, x2, dy2, out, pass == MXC_BWD_WEIGHT_BF16, ws, st, dry, InputPrep(), true);
+}
+
 // fws / mode: see FilterMode (backward-data only; fws == ws and FILTER_RAW otherwise)
 int run_pass(int pass, const ConvShape &s, int dtype, int layout, const void *a, const void *b, void *out, const PostOp &post,
              Carver &ws, hipStream_t st, bool dry, Carver *fws_opt = nullptr, FilterMode mode = FILTER_RAW)
@@ -354,6 +494,11 @@ int run_pass(int pass, const ConvShape &s, int dtype, int layout, const void *a,
         case MXC_BWD_DATA: return bwd_data_nhwc(s, dtype, a, b, out, post, fws, ws, st, dry, mode);
         default: return bwd_weight_nhwc(s, dtype, a, b, out, pass == MXC_BWD_WEIGHT_BF16, ws, st, dry);
         }
+    }
+    if (dtype == MXC_BF16 && !g_lean) {
+        const ConvShape s8 = with_padded_channels(s);
+        const bool ok = pass == MXC_FWD ? mfma_fwd_supported(s8) : pass == MXC_BWD_DATA ? mfma_bwd_data_supported(s8) : mfma_wgrad_supported(s8);
+        if (ok) return run_bf16_nchw(pass, s8, a, b, out, post, fws, ws, st, dry, mode);
     }
     // NCHW at the boundary: convert operands into the workspace, compute, convert the result back.
     if (pass == MXC_FWD) {
@@ -595,7 +740,8 @@ int prepared_input_plan(const ConvShape &s, int dtype, size_t *bytes, int *form)
     ipw.xws = &xw; ipw.mode = INPUT_PREPARED; ipw.form = &form_w;
     MXC_TRY(fwd_nhwc(s, dtype, nullptr, nullptr, nullptr, PostOp(), none, nullptr, true, ipf));
     MXC_TRY(bwd_weight_nhwc(s, dtype, nullptr, nullptr, nullptr, false, none, nullptr, true, ipw));
-    const bool shared = form_f == form_w && xf.used == xw.used;
+    // (a bf16 layer whose K is no multiple of 8 keeps the empty form that its callers' buffers are sized for)
+    const bool shared = form_f == form_w && xf.used == xw.used && s.K % 8 == 0;
     *bytes = shared ? xf.used : 0;
     *form = shared ? form_f : FORM_AS_IS;
     return MXC_OK;

@@ -279,7 +279,7 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
 
     // this thread's share of the tile's bias vector (column n0 + tid), requested now, used after the loop
     static_assert(NT >= BN, "one bias value per thread");
-    const float bias_t = (p.bias != nullptr && tid < BN && n0 + tid < p.Co) ? p.bias[n0 + tid] : 0.f;
+    const float bias_t = (p.bias != nullptr && tid < BN && n0 + tid < p.Cw) ? p.bias[n0 + tid] : 0.f;
 
     f32x16 acc[MI][NI];
 #pragma unroll
@@ -531,7 +531,9 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
     } else {
-        // output channel counts that are not a multiple of 8: element by element
+        // output channel counts that are not a multiple of 8: four neighbouring columns at a time (8 bytes at any
+        // alignment), the last ones element by element
+        struct __attribute__((packed)) Packed8 { uint32_t lo, hi; };
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             const int m = m0 + wave_m + i * 32 + frag_row;
@@ -540,13 +542,28 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
 #pragma unroll
             for (int j = 0; j < NI; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int co = n0 + wave_n + j * 32 + 8 * (e >> 2) + 4 * frag_kg + (e & 3);
-                    if (co < p.Co) {
-                        float v = acc[i][j][e] + (p.bias != nullptr ? p.bias[co] : 0.f);
-                        if (p.relu) v = fmaxf(v, 0.f);
-                        const bool keep = p.mask == nullptr || mask_keeps(p.mask + orow + co);
-                        p.out[orow + co] = keep ? f32_to_bf16(v) : (bf16_t)0;
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    const int co = n0 + wave_n + j * 32 + 8 * g4 + 4 * frag_kg;
+                    if (co >= p.Co) continue;
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[e] = acc[i][j][4 * g4 + e];
+                        if (p.bias != nullptr && co + e < p.Cw) v[e] += p.bias[co + e];
+                        if (p.relu) v[e] = fmaxf(v[e], 0.f);
+                    }
+                    if (co + 4 <= p.Co) {
+                        Packed8 o{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+                        if (p.mask != nullptr) {
+                            const Packed8 mk = *reinterpret_cast<const Packed8 *>(p.mask + orow + co);
+                            o = Packed8{mask_bf16x2(o.lo, mk.lo), mask_bf16x2(o.hi, mk.hi)};
+                        }
+                        *reinterpret_cast<Packed8 *>(p.out + orow + co) = o;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 3; ++e)
+                            if (co + e < p.Co)
+                                p.out[orow + co + e] = (p.mask == nullptr || mask_keeps(p.mask + orow + co + e)) ? f32_to_bf16(v[e]) : (bf16_t)0;
                     }
                 }
         }
@@ -569,7 +586,8 @@ int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end
     p.m_end = (int)m_end;
     p.m_tiles = (int)mt;
     p.in_bytes = (unsigned)((long long)p.N * p.Hi * p.Wi * p.pix * 2);
-    p.wm_bytes = BT ? p.bt_w_bytes : (unsigned)((long long)p.Co * p.TR * p.TS * p.Ci * 2);
+    if (p.Cw == 0) p.Cw = p.Co;
+    p.wm_bytes = BT ? p.bt_w_bytes : (unsigned)((long long)p.Cw * p.TR * p.TS * p.Ci * 2);
     // MXC_TAP_OUTER=1 (tuning only) keeps the filter's own order, all channels of a tap before the next tap
     p.tap_inner = (!BT && p.Ci % BKT == 0 && p.TR * p.TS > 1 && !tap_outer_forced) ? 1 : 0;
     p.linear_out = (p.out_mul_h == 1 && p.out_mul_w == 1 && p.out_off_h == 0 && p.out_off_w == 0 && p.Mh == p.Ho && p.Mw == p.Wo) ? 1 : 0;
@@ -787,37 +805,6 @@ bool igemm_dims_ok(long long in_elems, long long wm_elems, long long M, int Hi, 
            Wi + span <= 8192 && taps <= MAX_TAPS;
 }
 
-// Re-pack the filter for backward-data.  For the residue class (ph, pw) of (h+pad, v+pad) mod
-// stride the taps are r = ph + stride*j, s = pw + stride*i; its matrix is
-//     wt[c][(j*TS + i)*K + k] = w[k][r][s][c]          (w in KRSC)
-// and the classes are laid out one after another (sizes sum to K*R*S*C).
-__global__ __launch_bounds__(256) void repack_bwd_data_filter_kernel(const bf16_t *__restrict__ w, bf16_t *__restrict__ wt,
-                                                                     int K, int C, int R, int S, int stride)
-{
-    const int total = K * R * S * C;
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    // gid enumerates the destination: phase-major, then c, j, i, k
-    int rem = gid, ph = 0, pw = 0, TR = 0, TS = 0;
-    for (int a = 0; a < stride; ++a) {
-        bool found = false;
-        const int tr_a = a < R ? (R - a + stride - 1) / stride : 0;
-        for (int b = 0; b < stride; ++b) {
-            const int ts_b = b < S ? (S - b + stride - 1) / stride : 0;
-            const int sz = C * tr_a * ts_b * K;
-            if (rem < sz) { ph = a; pw = b; TR = tr_a; TS = ts_b; found = true; break; }
-            rem -= sz;
-        }
-        if (found) break;
-    }
-    const int k = rem % K; rem /= K;
-    const int i = rem % TS; rem /= TS;
-    const int j = rem % TR; rem /= TR;
-    const int c = rem;
-    const int r = ph + stride * j, s = pw + stride * i;
-    wt[gid] = w[(((size_t)k * R + r) * S + s) * C + c];
-}
-
 // dx[n][h_first + stride*a][v_first + stride*b][:] = 0 for the Mh x Mw pixels of one residue class;
 // one thread per cw consecutive channels (cw = 8: one 16-byte store).
 __global__ __launch_bounds__(256) void zero_phase_kernel(bf16_t *__restrict__ dx, long long n_thr, int H, int W, int C, int cw,
@@ -858,7 +845,7 @@ int split_count(long long M, int Co, int Kd)
 
 // out[m][co] = act(sum_z partial[z][m][co] + bias[co]) in ascending z (fixed order), 4 columns per thread
 __global__ __launch_bounds__(256) void split_finish_kernel(const float *__restrict__ partial, bf16_t *__restrict__ out, long long MC,
-                                                           int Co, int splits, const float *__restrict__ bias, int relu,
+                                                           int Co, int Cw, int splits, const float *__restrict__ bias, int relu,
                                                            const bf16_t *__restrict__ mask)
 {
     const long long i4 = ((long long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
@@ -870,7 +857,8 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const float *__restri
     }
     if (bias != nullptr) {
         const int co = (int)(i4 % Co);          // Co % 8 == 0: the four columns share a row
-        acc.x += bias[co]; acc.y += bias[co + 1]; acc.z += bias[co + 2]; acc.w += bias[co + 3];
+        if (co + 4 <= Cw) { acc.x += bias[co]; acc.y += bias[co + 1]; acc.z += bias[co + 2]; acc.w += bias[co + 3]; }
+        else { if (co < Cw) acc.x += bias[co]; if (co + 1 < Cw) acc.y += bias[co + 1]; if (co + 2 < Cw) acc.z += bias[co + 2]; }
     }
     if (relu) { acc.x = fmaxf(acc.x, 0.f); acc.y = fmaxf(acc.y, 0.f); acc.z = fmaxf(acc.z, 0.f); acc.w = fmaxf(acc.w, 0.f); }
     uint2 o = make_uint2((uint32_t)f32_to_bf16(acc.x) | ((uint32_t)f32_to_bf16(acc.y) << 16),
@@ -901,7 +889,7 @@ int launch_split(int tc, IgemmParams p, long long M, int sp, void *split_ws, voi
     snprintf(split_name, sizeof(split_name), "%s%s_split%d", kTiles[tc].name, bt ? "_inplace" : "", used);
     *variant = split_name;
     hipLaunchKernelGGL(split_finish_kernel, dim3((unsigned)((MC / 4 + 255) / 256)), dim3(256), 0, st, (const float *)split_ws,
-                       (bf16_t *)out, MC, p.Co, used, post.bias, post.relu, (const bf16_t *)post.mask);
+                       (bf16_t *)out, MC, p.Co, p.Cw ? p.Cw : p.Co, used, post.bias, post.relu, (const bf16_t *)post.mask);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
@@ -939,7 +927,7 @@ int igemm_fwd(const ConvShape &s, const void *x, const void *w, void *y, hipStre
     IgemmParams p{};
     p.bias = post.bias; p.relu = post.relu;
     p.in = (const bf16_t *)x; p.wm = (const bf16_t *)w; p.out = (bf16_t *)y;
-    p.N = s.N; p.Hi = s.H; p.Wi = s.W; p.Ci = s.C; p.pix = s.C; p.Co = s.K;
+    p.N = s.N; p.Hi = s.H; p.Wi = s.W; p.Ci = s.C; p.pix = s.C; p.Co = s.K; p.Cw = real_k(s);
     p.TR = s.R; p.TS = s.S; p.tstep_h = 1; p.tstep_w = 1;
     p.Mh = s.P; p.Mw = s.Q;
     p.in_mul_h = s.stride; p.in_mul_w = s.stride; p.in_off_h = -s.pad; p.in_off_w = -s.pad;
@@ -991,7 +979,7 @@ int igemm_fwd_smallc(const ConvShape &s, const void *xp, const void *wp, void *y
     IgemmParams p{};
     p.bias = post.bias; p.relu = post.relu;
     p.in = (const bf16_t *)xp; p.wm = (const bf16_t *)wp; p.out = (bf16_t *)y;
-    p.N = s.N; p.Hi = g.Hp; p.Wi = g.Wp; p.Ci = g.run; p.pix = g.pix; p.Co = s.K;
+    p.N = s.N; p.Hi = g.Hp; p.Wi = g.Wp; p.Ci = g.run; p.pix = g.pix; p.Co = s.K; p.Cw = real_k(s);
     p.TR = s.R; p.TS = 1; p.tstep_h = 1; p.tstep_w = 1;
     p.Mh = s.P; p.Mw = s.Q;
     p.in_mul_h = s.stride; p.in_mul_w = s.stride; p.in_off_h = 0; p.in_off_w = 0;
@@ -1012,23 +1000,18 @@ size_t igemm_bwd_data_workspace(const ConvShape &s) { return (size_t)s.K * s.R *
 
 // A large 1x1 filter at stride 1 (FullyConnected) is read in place, as transposed tiles, when the chosen
 // tile has that variant: copying it would cost more than the slower operand fetch.
-static bool bwd_data_reads_filter_in_place(const ConvShape &s)
+bool bwd_data_reads_filter_in_place(const ConvShape &s)
 {
-    return s.R == 1 && s.S == 1 && s.stride == 1 && s.K % 64 == 0 && (long long)s.K * s.C * 2 >= (4ll << 20) &&
+    return real_c(s) == s.C && real_k(s) == s.K && s.R == 1 && s.S == 1 && s.stride == 1 && s.K % 64 == 0 && (long long)s.K * s.C * 2 >= (4ll << 20) &&
            has_bt(choose_tile((long long)s.N * s.H * s.W, s.C, s.K));
 }
 
-int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStream_t st, bool copy_in_place_filter)
+int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStream_t st, bool copy_in_place_filter, bool kcrs)
 {
     if (bwd_data_reads_filter_in_place(s))
         return copy_in_place_filter ? launch_copy(w, wt, (size_t)s.K * s.C * sizeof(bf16_t), st) : MXC_OK;
-    if (s.R == 1 && s.S == 1)
-        // 1x1: the single class's matrix [C][K] is the transpose of w[K][C] (tiled transpose through LDS)
-        return launch_transpose(w, wt, 1, s.K, s.C, 2, st);
-    const int total = s.K * s.R * s.S * s.C;
-    hipLaunchKernelGGL(repack_bwd_data_filter_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                       (const bf16_t *)w, (bf16_t *)wt, s.K, s.C, s.R, s.S, s.stride);
-    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+    const RelayJob job = relay_bwd_filter(s, w, wt, kcrs);
+    return relayout(&job, 1, st);
 }
 
 // wt: the filter as igemm_bwd_data_prepare left it; w_in_place: the filter the in-place variant reads
@@ -1054,7 +1037,7 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
             p.in = (const bf16_t *)dy; p.wm = bt ? (const bf16_t *)w : (const bf16_t *)wt + wt_off; p.out = (bf16_t *)dx;
             p.mask = (const bf16_t *)post.mask;
             p.bt_w_bytes = (unsigned)((long long)s.K * s.C * 2);
-            p.N = s.N; p.Hi = s.P; p.Wi = s.Q; p.Ci = s.K; p.pix = s.K; p.Co = s.C;
+            p.N = s.N; p.Hi = s.P; p.Wi = s.Q; p.Ci = s.K; p.pix = s.K; p.Co = s.C; p.Cw = real_c(s);
             p.TR = TR; p.TS = TS; p.tstep_h = -1; p.tstep_w = -1;
             p.Mh = Mh; p.Mw = Mw;
             p.in_mul_h = 1; p.in_mul_w = 1; p.in_off_h = hh0; p.in_off_w = vv0;
@@ -1110,7 +1093,7 @@ SmallCBwd smallc_bwd_geom(const ConvShape &s)
 
 // all residue classes one after another; class ph holds [G*4][TR_ph*U*K]
 __global__ __launch_bounds__(256) void smallc_bwd_pack_w_kernel(const bf16_t *__restrict__ w, bf16_t *__restrict__ w2, int K,
-                                                               int C, int R, int S, int stride, int pad, int G, int U,
+                                                               int Kr, int C, int R, int S, int stride, int pad, int G, int U,
                                                                int uoff)
 {
     const int rows = G * 4;
@@ -1133,7 +1116,7 @@ __global__ __launch_bounds__(256) void smallc_bwd_pack_w_kernel(const bf16_t *__
     const int r = ph + stride * j;
     const int sidx = g + pad - stride * (u + uoff);
     bf16_t v = 0;
-    if (c < C && sidx >= 0 && sidx < S) v = w[(((size_t)k * R + r) * S + sidx) * C + c];
+    if (k < Kr && c < C && sidx >= 0 && sidx < S) v = w[(((size_t)k * R + r) * S + sidx) * C + c];
     const size_t phase_base = (size_t)(blockIdx.x * blockDim.x + threadIdx.x) - gid;
     w2[phase_base + gid] = v;
 }
@@ -1182,7 +1165,7 @@ int igemm_bwd_data_smallc_prepare(const ConvShape &s, const void *w, void *w2, h
     igemm_bwd_data_smallc_workspace(s, &w2_bytes, &dx4_bytes);
     const int total = (int)(w2_bytes / 2);
     hipLaunchKernelGGL(smallc_bwd_pack_w_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const bf16_t *)w,
-                       (bf16_t *)w2, s.K, s.C, s.R, s.S, s.stride, s.pad, g.G, g.U, g.uoff);
+                       (bf16_t *)w2, s.K, real_k(s), s.C, s.R, s.S, s.stride, s.pad, g.G, g.U, g.uoff);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 

@@ -12,9 +12,14 @@ typedef uint16_t bf16_t;  // raw bf16 bit pattern
 
 // One convolution problem in the library's working layout: activations NHWC,
 // filters KRSC.  P and Q are derived by the ABI layer.
+// Kr, Cr: where the tensors carry more channels than the problem has (padded to a multiple of 8 with zeros), the
+// problem's own counts; 0 = the same.  The filter always has the problem's own K rows.
 struct ConvShape {
     int N, C, H, W, K, R, S, stride, pad, P, Q;
+    int Kr = 0, Cr = 0;
 };
+inline int real_k(const ConvShape &s) { return s.Kr ? s.Kr : s.K; }
+inline int real_c(const ConvShape &s) { return s.Cr ? s.Cr : s.C; }
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 
@@ -142,6 +147,24 @@ int launch_transpose(const void *src, void *dst, int batch, int rows, int cols, 
 bool transpose_launchable(long long batch, long long rows, long long cols);
 int launch_copy(const void *src, void *dst, size_t bytes, hipStream_t stream);
 
+// Re-layouts of 2-byte elements, up to MAX_RELAY_JOBS in one launch (see relayout_kernel).
+enum { RELAY_TRANSPOSE = 0, RELAY_PAD = 1, RELAY_FILTER_KRSC = 2, RELAY_FILTER_KCRS = 3 };
+constexpr int MAX_RELAY_JOBS = 3;
+struct RelayJob {
+    const void *src;
+    void *dst;
+    long long batch, src_batch, dst_batch;
+    int kind, rows, cols, src_pitch, run, dst_pitch, run_tiles;     // run: length of a destination run (>= rows: zeros beyond)
+    int C, class_C, R, S, stride;
+    unsigned blocks;
+};
+RelayJob relay_to_nhwc(const void *src, void *dst, int n, int c, int hw, int c_pitch);      // [n][c][hw] -> [n][hw][c_pitch]
+RelayJob relay_to_nchw(const void *src, void *dst, int n, int c, int hw, int c_pitch);      // [n][hw][c_pitch] -> [n][c][hw]
+RelayJob relay_pad(const void *src, void *dst, long long rows, int c, int c_pitch);         // [rows][c] -> [rows][c_pitch]
+// the filter matrices of backward-data, one per stride residue class: wt[class][c][(j*TS + i)*K + k] (see igemm_bwd_data)
+RelayJob relay_bwd_filter(const ConvShape &s, const void *w, void *wt, bool kcrs);
+int relayout(const RelayJob *jobs, int n, hipStream_t st);
+
 // ---- probe.hip: matrix-pipe ceiling measurement -------------------------------------
 // launches the register-resident MFMA loop; *flops = floating-point operations the launch performs
 int probe_mfma(int workgroups, int iters, float *out, double *flops, hipStream_t st);
@@ -187,7 +210,10 @@ size_t igemm_bwd_data_workspace(const ConvShape &s);   // bytes for the re-packe
 size_t igemm_bwd_data_split_bytes(const ConvShape &s);   // scratch for a split reduction (0: never split)
 // Filter preparation (re-pack per stride residue class / transpose of a 1x1 filter) into wt; a filter that the
 // kernel reads in place is copied to wt only when copy_in_place_filter is set.
-int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStream_t st, bool copy_in_place_filter);
+// (kcrs: w lies in KCRS order)
+int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStream_t st, bool copy_in_place_filter, bool kcrs = false);
+// whether igemm_bwd_data reads this layer's filter as it is; otherwise relay_bwd_filter makes the form it reads
+bool bwd_data_reads_filter_in_place(const ConvShape &s);
 int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, void *dx, const void *wt, hipStream_t st,
                    const char **variant, const PostOp &post = PostOp(), void *split_ws = nullptr);
 
@@ -220,6 +246,7 @@ struct IgemmParams {
     int Ci;              // reduction elements per tap: a contiguous run starting at the tap's pixel
     int pix;             // elements per pixel in memory (== Ci for plain NHWC; smaller when a run spans pixels)
     int Co;
+    int Cw;              // rows of the filter matrix and bias values that exist (columns beyond are zero); 0: Co
     int TR, TS, tstep_h, tstep_w;   // tap grid and the direction (+1 or -1) taps advance in, per axis
     int Mh, Mw;          // output grid of this launch (per image)
     int in_mul_h, in_mul_w, in_off_h, in_off_w;     // input coordinate of tap 0: a*in_mul + in_off
@@ -272,8 +299,6 @@ bool window_applicable(const IgemmParams &p);
 int window_launch(const IgemmParams &p, hipStream_t st);
 
 // ---- prep.hip: re-packing for channel counts that are not a multiple of 8 ---------
-// [rows][C] -> [rows][C8] (C8 = C rounded up to 8, new channels zero); bf16 only.
-int pad_channels(const void *src, void *dst, long long rows, int C, hipStream_t st);
 // Small-C (C <= 4) image packing: `pix` channels per pixel, explicit zero border, padded size Hp x Wp;
 // one filter row's taps form a contiguous run of `run` elements.
 struct SmallCGeom { int pix, Hp, Wp, run; };
@@ -300,6 +325,7 @@ int igemm_fwd_smallc(const ConvShape &s, const void *xp, const void *wp, void *y
 // (r/s2d, s/s2d) at channel ((r%s2d)*s2d + s%s2d)*Cq + c.
 struct WgradGeom {
     int N, H, W, pix, K, P, Q, stride, pad, TR, TS, run, R, S, C, col_r, col_s, s2d, Cq;
+    int Kout;                    // rows of dw (K counts dy's channels, padded to a multiple of 8)
     int oH, oW, ostride, opad;   // the caller's problem (with N, C, K, R, S: the key of the measured-plan table)
 };
 WgradGeom wgrad_geom_s2d(const ConvShape &s);       // x already packed by s2d_pack_x
@@ -308,8 +334,8 @@ WgradGeom wgrad_geom_chanpad(const ConvShape &s);   // x already padded to C8 ch
 WgradGeom wgrad_geom_smallc(const ConvShape &s);    // x already packed by smallc_pack_x
 bool wgrad_supported(const WgradGeom &g);
 size_t wgrad_workspace(const WgradGeom &g);            // bytes of fp32 partial tiles
-// dw: fp32, or bf16 (the fp32 sum rounded once, by the reduce kernel) when dw_bf16
-int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_bf16, float *partial, hipStream_t st,
+// dw: fp32, or bf16 (the fp32 sum rounded once, by the reduce kernel) when dw_bf16; KRSC, or KCRS when kcrs
+int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_bf16, bool kcrs, float *partial, hipStream_t st,
           const char **variant);
 
 }  // namespace mxc

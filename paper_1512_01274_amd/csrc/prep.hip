@@ -3,7 +3,7 @@
 // The MFMA kernels fetch 16-byte chunks (8 bf16) that must not straddle a filter tap.  Two
 // re-packings make any channel count fit:
 //   - channel padding: [rows][C] -> [rows][C8], C8 = C rounded up to 8, zeros in the new channels
-//     (used when C % 8 != 0 and C > 4);
+//     (used when C % 8 != 0 and C > 4; relayout_kernel in layout.hip);
 //   - space-to-depth (C <= 4, stride 2 or 4, first layers): stride x stride pixel blocks become the
 //     channels of one pixel of a stride-1 problem, x2[n][h2][w2][(dh*s+dw)*Cq+c] with the zero border
 //     folded in, filter likewise (zero taps beyond R,S); all three passes then run the ordinary
@@ -21,26 +21,6 @@
 namespace mxc {
 
 namespace {
-
-__global__ __launch_bounds__(256) void pad_channels_kernel(const bf16_t *__restrict__ src, uint4 *__restrict__ dst,
-                                                           long long rows, int C, int C8)
-{
-    const int chunks = C8 >> 3;
-    const long long total = rows * chunks;
-    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    const long long row = gid / chunks;
-    const int c0 = (int)(gid % chunks) * 8;
-    const bf16_t *s = src + row * C;
-    uint32_t v[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int c = c0 + j;
-        const uint32_t e = c < C ? s[c] : 0u;
-        v[j >> 1] |= e << ((j & 1) * 16);
-    }
-    dst[gid] = make_uint4(v[0], v[1], v[2], v[3]);
-}
 
 // xp[n][hp][wp][pix] = x[n][hp-pad][wp-pad][c] inside the image and for c < C, else 0.  One thread per 8 bytes.
 __global__ __launch_bounds__(256) void smallc_pack_x_kernel(const bf16_t *__restrict__ x, uint2 *__restrict__ xp, int N, int C,
@@ -302,17 +282,6 @@ inline int ok() { return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUN
 
 }  // namespace
 
-int pad_channels(const void *src, void *dst, long long rows, int C, hipStream_t st)
-{
-    const int C8 = (C + 7) / 8 * 8;
-    const long long total = rows * (C8 / 8);
-    const long long blocks = (total + 255) / 256;
-    if (blocks > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
-    hipLaunchKernelGGL(pad_channels_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)src, (uint4 *)dst, rows, C,
-                       C8);
-    return ok();
-}
-
 SmallCGeom smallc_geom(const ConvShape &s)
 {
     SmallCGeom g;
@@ -338,9 +307,9 @@ int smallc_pack_x(const ConvShape &s, const void *x, void *xp, hipStream_t st)
 int smallc_pack_w(const ConvShape &s, const void *w, void *wp, hipStream_t st)
 {
     const SmallCGeom g = smallc_geom(s);
-    const int total = s.K * s.R * g.run;
+    const int total = real_k(s) * s.R * g.run;
     hipLaunchKernelGGL(smallc_pack_w_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const bf16_t *)w,
-                       (bf16_t *)wp, s.K, s.C, s.R, s.S, g.pix, g.run);
+                       (bf16_t *)wp, real_k(s), s.C, s.R, s.S, g.pix, g.run);
     return ok();
 }
 
@@ -377,7 +346,7 @@ bool s2d_applicable(const ConvShape &s) { return s.C <= 4 && (s.stride == 2 || s
 ConvShape s2d_shape(const ConvShape &s)
 {
     const S2DGeom g = s2d_geom(s);
-    return ConvShape{s.N, g.C2, g.H2, g.W2, s.K, g.R2, g.S2, 1, 0, s.P, s.Q};
+    return ConvShape{s.N, g.C2, g.H2, g.W2, s.K, g.R2, g.S2, 1, 0, s.P, s.Q, s.Kr, 0};
 }
 
 int s2d_pack_x(const ConvShape &s, const void *x, void *x2, hipStream_t st)
@@ -413,9 +382,9 @@ int s2d_pack_x(const ConvShape &s, const void *x, void *x2, hipStream_t st)
 int s2d_pack_w(const ConvShape &s, const void *w, void *w2, hipStream_t st)
 {
     const S2DGeom g = s2d_geom(s);
-    const int total = s.K * g.R2 * g.S2 * g.C2;
+    const int total = real_k(s) * g.R2 * g.S2 * g.C2;
     hipLaunchKernelGGL(s2d_pack_w_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const bf16_t *)w, (bf16_t *)w2,
-                       s.K, s.C, s.R, s.S, g.s, g.Cq, g.C2, g.R2, g.S2);
+                       real_k(s), s.C, s.R, s.S, g.s, g.Cq, g.C2, g.R2, g.S2);
     return ok();
 }
 

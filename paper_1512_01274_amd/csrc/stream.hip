@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
         tap_tab[t] = e;
     }
 
-    for (int c = tid; c < BN; c += 64 * NW) sBias[c] = (p.bias != nullptr && n0 + c < p.Co) ? p.bias[n0 + c] : 0.f;
+    for (int c = tid; c < BN; c += 64 * NW) sBias[c] = (p.bias != nullptr && n0 + c < p.Cw) ? p.bias[n0 + c] : 0.f;
 
     const buf_rsrc_t rs_in = make_buf_rsrc(p.in, p.in_bytes);
     const buf_rsrc_t rs_wm = make_buf_rsrc(p.wm, p.wm_bytes);
@@ -497,7 +497,8 @@ int stream_launch(const IgemmParams &p, hipStream_t st)
     q.m_begin = 0;
     q.m_end = (int)M;
     q.in_bytes = (unsigned)((long long)p.N * p.Hi * p.Wi * p.pix * 2);
-    q.wm_bytes = (unsigned)((long long)p.Co * p.TR * p.TS * p.Ci * 2);
+    if (q.Cw == 0) q.Cw = q.Co;
+    q.wm_bytes = (unsigned)((long long)q.Cw * p.TR * p.TS * p.Ci * 2);
     q.tap_inner = 0;
     q.linear_out = (p.out_mul_h == 1 && p.out_mul_w == 1 && p.out_off_h == 0 && p.out_off_w == 0 && p.Mh == p.Ho && p.Mw == p.Wo) ? 1 : 0;
     const int Kd = p.TR * p.TS * p.Ci;

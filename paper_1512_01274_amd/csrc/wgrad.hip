@@ -350,7 +350,7 @@ __device__ __forceinline__ void store4(bf16_t *dw, int i4, const float4 v)
 
 template <int G, typename OUT>
 __global__ __launch_bounds__(256) void wgrad_reduce_vec4_kernel(const float4 *partial, OUT *dw,
-                                                                int total4, int splits)
+                                                                int total4, int splits, size_t split_stride4)
 {
     constexpr int LPG = 64 / G;                       // lanes per group
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec4_kernel(const float4 *pa
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (gid < total4)
         for (int zz = grp; zz < splits; zz += G) {
-            const float4 v = partial[(size_t)zz * total4 + gid];
+            const float4 v = partial[(size_t)zz * split_stride4 + gid];
             acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
         }
 #pragma unroll
@@ -393,6 +393,37 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
 #pragma unroll
     for (int d = LPG; d < 64; d <<= 1) acc += __shfl_xor(acc, d);
     if (grp == 0 && gid < total) store_f32(dw + gid, acc);
+}
+
+// The same for dw in KCRS order: one workgroup adds up 64 channels of one k (reads contiguous along the channels),
+// passes the sums through LDS and writes the 64*R*S results as one contiguous run.  G interleaved groups of splits per
+// output keep loads in flight; their sums are added in ascending order.
+template <int G, typename OUT>
+__global__ __launch_bounds__(256) void wgrad_reduce_kcrs_kernel(const float *__restrict__ partial, OUT *__restrict__ dw, int splits, int ncols,
+                                                                int RS, int S, int C, int c_tiles, int col_r, int col_s, int s2d, int Cq,
+                                                                size_t split_stride)
+{
+    extern __shared__ float red[];                    // [G][64 * RS], then the sums as [channel][RS] in group 0's place
+    const int k = blockIdx.x / c_tiles, c0 = blockIdx.x % c_tiles * 64;
+    const int n = min(C - c0, 64), items = 64 * RS;
+    for (int i = threadIdx.x; i < items * G; i += 256) {
+        const int g = i / items, e = i % items, rs = e >> 6, c = e & 63;
+        float acc = 0.f;
+        if (c < n) {
+            const int r = rs / S, s = rs % S;
+            const float *src = partial + (size_t)k * ncols + (r / s2d) * col_r + (s / s2d) * col_s + ((r % s2d) * s2d + s % s2d) * Cq + c0 + c;
+            for (int z = g; z < splits; z += G) acc += src[(size_t)z * split_stride];
+        }
+        red[g * items + c * RS + rs] = acc;
+    }
+    __syncthreads();
+    OUT *out = dw + ((size_t)k * C + c0) * RS;
+    for (int i = threadIdx.x; i < n * RS; i += 256) {
+        float acc = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc += red[g * items + i];
+        store_f32(out + i, acc);
+    }
 }
 
 // slots: workgroups that fit one CU; util: fraction of the CU's matrix peak the tile sustains (measured)
@@ -529,25 +560,25 @@ const char *wgrad_tile_name(int index) { return index >= 0 && index < N_TILES ? 
 
 WgradGeom wgrad_geom_plain(const ConvShape &s)
 {
-    return WgradGeom{s.N, s.H, s.W, s.C, s.K, s.P, s.Q, s.stride, s.pad, s.R, s.S, s.C, s.R, s.S, s.C, s.S * s.C, s.C, 1, 0, s.H, s.W, s.stride, s.pad};
+    return WgradGeom{s.N, s.H, s.W, s.C, s.K, s.P, s.Q, s.stride, s.pad, s.R, s.S, s.C, s.R, s.S, real_c(s), s.S * s.C, s.C, 1, 0, real_k(s), s.H, s.W, s.stride, s.pad};
 }
 
 WgradGeom wgrad_geom_chanpad(const ConvShape &s)
 {
     const int C8 = (s.C + 7) / 8 * 8;
-    return WgradGeom{s.N, s.H, s.W, C8, s.K, s.P, s.Q, s.stride, s.pad, s.R, s.S, C8, s.R, s.S, s.C, s.S * C8, C8, 1, 0, s.H, s.W, s.stride, s.pad};
+    return WgradGeom{s.N, s.H, s.W, C8, s.K, s.P, s.Q, s.stride, s.pad, s.R, s.S, C8, s.R, s.S, s.C, s.S * C8, C8, 1, 0, real_k(s), s.H, s.W, s.stride, s.pad};
 }
 
 WgradGeom wgrad_geom_smallc(const ConvShape &s)
 {
     const SmallCGeom g = smallc_geom(s);
-    return WgradGeom{s.N, g.Hp, g.Wp, g.pix, s.K, s.P, s.Q, s.stride, 0, s.R, 1, g.run, s.R, s.S, s.C, g.run, g.pix, 1, 0, s.H, s.W, s.stride, s.pad};
+    return WgradGeom{s.N, g.Hp, g.Wp, g.pix, s.K, s.P, s.Q, s.stride, 0, s.R, 1, g.run, s.R, s.S, s.C, g.run, g.pix, 1, 0, real_k(s), s.H, s.W, s.stride, s.pad};
 }
 
 WgradGeom wgrad_geom_s2d(const ConvShape &s)
 {
     const S2DGeom g = s2d_geom(s);
-    return WgradGeom{s.N, g.H2, g.W2, g.C2, s.K, s.P, s.Q, 1, 0, g.R2, g.S2, g.C2, s.R, s.S, s.C, g.S2 * g.C2, g.C2, g.s, g.Cq, s.H, s.W, s.stride, s.pad};
+    return WgradGeom{s.N, g.H2, g.W2, g.C2, s.K, s.P, s.Q, 1, 0, g.R2, g.S2, g.C2, s.R, s.S, s.C, g.S2 * g.C2, g.C2, g.s, g.Cq, real_k(s), s.H, s.W, s.stride, s.pad};
 }
 
 bool wgrad_supported(const WgradGeom &g)
@@ -565,9 +596,23 @@ size_t wgrad_workspace(const WgradGeom &g)
 }
 
 template <typename OUT>
-static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits, int ncols, bool identity, hipStream_t st)
+static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits, int ncols, bool identity, bool kcrs, hipStream_t st)
 {
-    const int total = g.K * g.R * g.S * g.C;
+    const int total = g.Kout * g.R * g.S * g.C;
+    const size_t split_stride = (size_t)g.K * ncols;
+    if (kcrs) {
+        const int RS = g.R * g.S, c_tiles = (g.C + 63) / 64;
+        if ((long long)g.Kout * c_tiles > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
+        const dim3 grid((unsigned)(g.Kout * c_tiles));
+        // eight groups of splits while their sums fit 32 KB of LDS
+        if (splits >= 4 && RS <= 16)
+            hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<8, OUT>), grid, dim3(256), (size_t)8 * 64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S,
+                               g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
+        else
+            hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<1, OUT>), grid, dim3(256), (size_t)64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S,
+                               g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
+        return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+    }
     // many splits of a small dw: 16 lane groups keep enough loads in flight; otherwise 4
     const bool wide = splits >= 32 && total < 256 * 1024;
     if (!identity && splits > 1) {
@@ -577,27 +622,27 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
         const int cols4 = g.K * ncols / 4;            // ncols is a multiple of 8
         if (wide)
             hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<16, float>), dim3((unsigned)((cols4 + 15) / 16)), dim3(256), 0, st,
-                               (const float4 *)partial, partial, cols4, splits);
+                               (const float4 *)partial, partial, cols4, splits, (size_t)cols4);
         else
             hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<4, float>), dim3((unsigned)((cols4 + 63) / 64)), dim3(256), 0, st,
-                               (const float4 *)partial, partial, cols4, splits);
+                               (const float4 *)partial, partial, cols4, splits, (size_t)cols4);
         if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
         splits = 1;
     }
-    if (identity && total % 4 == 0) {
+    if (identity && total % 4 == 0 && split_stride % 4 == 0) {
         const int total4 = total / 4;
         if (wide)
             hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<16, OUT>), dim3((unsigned)((total4 + 15) / 16)), dim3(256), 0, st,
-                               (const float4 *)partial, dw, total4, splits);
+                               (const float4 *)partial, dw, total4, splits, split_stride / 4);
         else
             hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<4, OUT>), dim3((unsigned)((total4 + 63) / 64)), dim3(256), 0, st,
-                               (const float4 *)partial, dw, total4, splits);
+                               (const float4 *)partial, dw, total4, splits, split_stride / 4);
     } else if (wide) {
         hipLaunchKernelGGL((wgrad_reduce_kernel<16, OUT>), dim3((unsigned)((total + 15) / 16)), dim3(256), 0, st, partial, dw, total,
-                           splits, ncols, g.R * g.S * g.C, g.S * g.C, g.C, g.col_r, g.col_s, g.s2d, g.Cq, (size_t)g.K * ncols);
+                           splits, ncols, g.R * g.S * g.C, g.S * g.C, g.C, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
     } else {
         hipLaunchKernelGGL((wgrad_reduce_kernel<4, OUT>), dim3((unsigned)((total + 63) / 64)), dim3(256), 0, st, partial, dw, total,
-                           splits, ncols, g.R * g.S * g.C, g.S * g.C, g.C, g.col_r, g.col_s, g.s2d, g.Cq, (size_t)g.K * ncols);
+                           splits, ncols, g.R * g.S * g.C, g.S * g.C, g.C, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
     }
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
@@ -606,8 +651,8 @@ template <typename OUT>
 static int sum_splits_to(const float *partial, OUT *dw, int total, int splits, hipStream_t st)
 {
     WgradGeom g{};
-    g.K = 1; g.R = 1; g.S = 1; g.C = total; g.s2d = 1;
-    return launch_reduce(g, const_cast<float *>(partial), dw, splits, total, true, st);
+    g.K = 1; g.Kout = 1; g.R = 1; g.S = 1; g.C = total; g.s2d = 1;
+    return launch_reduce(g, const_cast<float *>(partial), dw, splits, total, true, false, st);
 }
 
 int sum_splits(const float *partial, void *dw, bool dw_bf16, long long total, int splits, hipStream_t st)
@@ -616,7 +661,7 @@ int sum_splits(const float *partial, void *dw, bool dw_bf16, long long total, in
     return dw_bf16 ? sum_splits_to(partial, (bf16_t *)dw, (int)total, splits, st) : sum_splits_to(partial, (float *)dw, (int)total, splits, st);
 }
 
-int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_bf16, float *partial, hipStream_t st,
+int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_bf16, bool kcrs, float *partial, hipStream_t st,
           const char **variant)
 {
     const Plan pl = make_plan(g);
@@ -640,14 +685,14 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
     if (tiles * p.splits > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
     const bool identity = g.s2d == 1 && g.col_s == g.C && g.col_r == g.S * g.C && p.ncols == g.R * g.S * g.C;
     // one split whose columns are already in KRSC order and an fp32 result: the "partial" tensor is dw itself
-    const bool direct = p.splits == 1 && identity && !dw_bf16;
+    const bool direct = p.splits == 1 && identity && !dw_bf16 && !kcrs && g.K == g.Kout;
     if (direct) p.partial = (float *)dw;
     const int rc = launch_choice(pl.tile, p, (int)tiles, st);
     if (rc != MXC_OK) return rc;
     *variant = tc.name;
     if (direct) return MXC_OK;
-    return dw_bf16 ? launch_reduce(g, p.partial, (bf16_t *)dw, p.splits, p.ncols, identity, st)
-                   : launch_reduce(g, p.partial, (float *)dw, p.splits, p.ncols, identity, st);
+    return dw_bf16 ? launch_reduce(g, p.partial, (bf16_t *)dw, p.splits, p.ncols, identity, kcrs, st)
+                   : launch_reduce(g, p.partial, (float *)dw, p.splits, p.ncols, identity, kcrs, st);
 }
 
 }  // namespace mxc

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
         const int wy = p.tstep_h > 0 ? dh : p.TR - 1 - dh, wx = p.tstep_w > 0 ? dv : p.TS - 1 - dv;
         tap_shift[t] = wy * wp.WW + wx;
     }
-    for (int c = tid; c < BN; c += 64 * NW) sBias[c] = (p.bias != nullptr && n0 + c < p.Co) ? p.bias[n0 + c] : 0.f;
+    for (int c = tid; c < BN; c += 64 * NW) sBias[c] = (p.bias != nullptr && n0 + c < p.Cw) ? p.bias[n0 + c] : 0.f;
 
     const buf_rsrc_t rs_in = make_buf_rsrc(p.in, p.in_bytes);
     const buf_rsrc_t rs_wm = make_buf_rsrc(p.wm, p.wm_bytes);
@@ -399,7 +399,8 @@ int window_launch(const IgemmParams &p, hipStream_t st)
     IgemmParams &q = wp.g;
     const int T = p.TR * p.TS;
     q.in_bytes = (unsigned)((long long)p.N * p.Hi * p.Wi * p.Ci * 2);
-    q.wm_bytes = (unsigned)((long long)p.Co * T * p.Ci * 2);
+    if (q.Cw == 0) q.Cw = q.Co;
+    q.wm_bytes = (unsigned)((long long)q.Cw * T * p.Ci * 2);
     q.n_tiles = (p.Co + c.bn - 1) / c.bn;
     wp.TH = c.th;
     wp.TW = c.tw;
