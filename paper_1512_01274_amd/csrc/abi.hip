@@ -855,7 +855,7 @@ int mxc_bias_grad(int N, int K, int P, int Q, int dtype, int layout, const void 
     if (layout != MXC_NCHW && layout != MXC_NHWC) return MXC_ERR_UNSUPPORTED;
     if (!dy || !db) return MXC_ERR_NULL;
     if (misaligned(dy) || misaligned(db) || misaligned(workspace)) return MXC_ERR_ALIGN;
-    const size_t need = (size_t)bias_grad_parts(N, K, (long long)P * Q, layout) * K * sizeof(float);
+    const size_t need = bias_grad_scratch(N, K, (long long)P * Q, dtype, layout);
     if (!workspace || workspace_bytes < need) return MXC_ERR_WORKSPACE;
     return bias_grad(N, K, (long long)P * Q, dtype, layout, dy, db, (float *)workspace, (hipStream_t)hip_stream);
 }
@@ -918,7 +918,7 @@ int mxc_conv2d_workspace_bytes(int pass, int N, int C, int H, int W, int K, int 
     const int rc = validate_shape(N, C, H, W, K, R, S, stride, pad, dtype, layout, &s);
     if (rc != MXC_OK) return rc;
     if (pass == MXC_BIAS_GRAD) {
-        *out_bytes = align_up((size_t)bias_grad_parts(s.N, s.K, (long long)s.P * s.Q, layout) * s.K * sizeof(float), 256);
+        *out_bytes = align_up(bias_grad_scratch(s.N, s.K, (long long)s.P * s.Q, dtype, layout), 256);
         return MXC_OK;
     }
     if (pass == MXC_FWD_TRANSFORM) {

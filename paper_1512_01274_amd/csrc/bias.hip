@@ -1,114 +1,136 @@
-// Bias gradient: db[k] = sum over images and pixels of dy[n, k, p, q], fp32, deterministic.
+// Bias gradient: db[k] = sum over images and pixels of dy[n, k, p, q], fp32, in a fixed order.
 //
-// HBM-bound (dy is read once).  Two steps, both in a fixed order: every workgroup sums a block of
-// rows of the [rows][K] view (NHWC) or one (n, k) plane (NCHW) into a partial vector, then one
-// kernel adds the partial vectors in ascending order.
+// HBM-bound (dy is read once).  Every workgroup adds up a share of the tensor into a partial vector, and a second
+// kernel adds the partial vectors in ascending order; a tensor small enough for one share per group of columns needs
+// no second kernel.  All global reads are 16 bytes per lane, four in flight, for every channel count and alignment.
 #include "mxc_internal.h"
 
 namespace mxc {
 namespace {
 
-constexpr int BG_THREADS = 256;
+constexpr int BT = 1024;
 
-// NHWC: dy is [rows = N*P*Q][K].  Thread t of a workgroup owns columns t, t+256, ... for the
-// workgroup's rows_per_wg consecutive rows; lanes read consecutive channels (coalesced).
-template <typename T>
-__global__ __launch_bounds__(BG_THREADS) void bias_grad_rows_kernel(const T *__restrict__ dy, float *__restrict__ partial,
-                                                                    long long rows, int K, int rows_per_wg)
+template <typename T> constexpr int VEC = 16 / (int)sizeof(T);
+
+template <typename T> __device__ __forceinline__ void add_vec(float (&acc)[VEC<T>], const uint4 v)
 {
-    const long long r0 = (long long)blockIdx.x * rows_per_wg;
-    long long r1 = r0 + rows_per_wg;
-    if (r1 > rows) r1 = rows;
-    for (int k = threadIdx.x; k < K; k += BG_THREADS) {
-        float acc = 0.f;
-        for (long long r = r0; r < r1; ++r) acc += load_f32(dy + r * K + k);
-        partial[(size_t)blockIdx.x * K + k] = acc;
+    if constexpr (sizeof(T) == 2) {
+        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            acc[2 * e] += __uint_as_float(u[e] << 16);
+            acc[2 * e + 1] += __uint_as_float(u[e] & 0xFFFF0000u);
+        }
+    } else {
+        acc[0] += __uint_as_float(v.x); acc[1] += __uint_as_float(v.y);
+        acc[2] += __uint_as_float(v.z); acc[3] += __uint_as_float(v.w);
     }
 }
 
-// NHWC, K a multiple of VEC (16 bytes of elements) and at most 256*VEC: thread t owns the 16-byte
-// channel chunk t % (K/VEC) of the rows  r0 + t / (K/VEC) + i * groups;  four rows are in flight per
-// thread.  The row groups are then added in LDS in ascending order.
-template <typename T, int VEC>
-__global__ __launch_bounds__(BG_THREADS) void bias_grad_rows_vec_kernel(const T *__restrict__ dy, float *__restrict__ partial,
-                                                                        long long rows, int K, int rows_per_wg)
+// NHWC.  dy as [rows][width]: a row is the fewest pixels whose channels fill whole 16-byte chunks (one pixel where K is
+// a multiple of a chunk, else up to 8), so that a chunk covers the same channels in every row.  Workgroup (x, y) owns
+// chunks [x*cpb, x*cpb + cpb) of the rows [y*rows_per_wg, + rows_per_wg); its 1024 threads form 1024/cpb row groups,
+// whose sums meet in LDS (in two steps, each in ascending order).  out: [gridDim.y][width].
+template <typename T>
+__global__ __launch_bounds__(BT) void bias_grad_rows_kernel(const uint4 *__restrict__ dy, float *__restrict__ out, long long rows, int chunks,
+                                                            int cpb, int rows_per_wg)
 {
-    __shared__ float red[BG_THREADS * VEC];
-    const int chunks = K / VEC, groups = BG_THREADS / chunks;
-    const int chunk = threadIdx.x % chunks, grp = threadIdx.x / chunks;
-    const long long r0 = (long long)blockIdx.x * rows_per_wg;
-    long long r1 = r0 + rows_per_wg;
-    if (r1 > rows) r1 = rows;
-    float acc[VEC];
+    constexpr int V = VEC<T>;
+    __shared__ float red[BT * V];
+    const int groups = BT / cpb, c = threadIdx.x % cpb, grp = threadIdx.x / cpb;
+    const int chunk = blockIdx.x * cpb + c;
+    const long long r0 = (long long)blockIdx.y * rows_per_wg, r1 = min(rows, r0 + rows_per_wg);
+    float acc[V];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-    auto add = [&](const uint4 &v) {
-        if constexpr (sizeof(T) == 2) {
-            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc[2 * e] += __uint_as_float(u[e] << 16);
-                acc[2 * e + 1] += __uint_as_float(u[e] & 0xFFFF0000u);
-            }
-        } else {
-            acc[0] += __uint_as_float(v.x); acc[1] += __uint_as_float(v.y);
-            acc[2] += __uint_as_float(v.z); acc[3] += __uint_as_float(v.w);
-        }
-    };
-    if (grp < groups) {
-        const uint4 *base = reinterpret_cast<const uint4 *>(dy) + chunk;      // row r: base[r * chunks]
+    for (int e = 0; e < V; ++e) acc[e] = 0.f;
+    if (grp < groups && chunk < chunks) {
+        const uint4 *base = dy + chunk;
+        const long long step = (long long)groups * chunks;
         long long r = r0 + grp;
-        for (; r + 3LL * groups < r1; r += 4LL * groups) {
-            const uint4 a = base[r * chunks], b = base[(r + groups) * chunks], c = base[(r + 2LL * groups) * chunks],
-                        d = base[(r + 3LL * groups) * chunks];
-            add(a); add(b); add(c); add(d);
+        const uint4 *p = base + r * chunks;
+        for (; r + 3LL * groups < r1; r += 4LL * groups, p += 4 * step) {
+            const uint4 a = p[0], b = p[step], d = p[2 * step], f = p[3 * step];
+            add_vec<T>(acc, a); add_vec<T>(acc, b); add_vec<T>(acc, d); add_vec<T>(acc, f);
         }
-        for (; r < r1; r += groups) add(base[r * chunks]);
+        for (; r < r1; r += groups, p += step) add_vec<T>(acc, *p);
     }
+    // element e of thread t at [e][t]: conflict-free writes; then thread (e, c, part) adds every PARTS-th row group
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) red[threadIdx.x * VEC + e] = acc[e];
+    for (int e = 0; e < V; ++e) red[e * BT + threadIdx.x] = acc[e];
     __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            float s = 0.f;
-            for (int g = 0; g < groups; ++g) s += red[(g * chunks + chunk) * VEC + e];
-            partial[(size_t)blockIdx.x * K + chunk * VEC + e] = s;
-        }
+    const int items = cpb * V;
+    const int parts = items >= BT ? 1 : BT / items;      // at least 1 thread per output
+    for (int i = threadIdx.x; i < items * parts; i += BT) {
+        const int e = i / cpb % V, col = i % cpb, part = i / items;
+        float s = 0.f;
+        for (int g = part; g < groups; g += parts) s += red[e * BT + g * cpb + col];
+        acc[0] = s;                                      // items*parts <= BT where parts > 1: one value per thread
+        if (parts == 1) { if (blockIdx.x * cpb + col < chunks) out[(size_t)blockIdx.y * chunks * V + (blockIdx.x * cpb + col) * V + e] = s; }
+    }
+    if (parts == 1) return;
+    __syncthreads();
+    if ((int)threadIdx.x < items * parts) red[threadIdx.x] = acc[0];
+    __syncthreads();
+    if ((int)threadIdx.x < items) {
+        const int e = threadIdx.x / cpb, col = threadIdx.x % cpb;
+        float s = 0.f;
+        for (int q = 0; q < parts; ++q) s += red[q * items + threadIdx.x];
+        if (blockIdx.x * cpb + col < chunks) out[(size_t)blockIdx.y * chunks * V + (blockIdx.x * cpb + col) * V + e] = s;
     }
 }
 
-// NCHW: dy is [N][K][PQ]; workgroup (n*K + k) sums its plane; partial is [N][K]
+// NCHW: dy is [N][K][PQ].  Workgroup (k, y) adds the planes (n, k) of images [y*n_per_wg, + n_per_wg), each plane a
+// contiguous run read in 16-byte pieces at whatever alignment it has.  out: [gridDim.y][K].
 template <typename T>
-__global__ __launch_bounds__(BG_THREADS) void bias_grad_planes_kernel(const T *__restrict__ dy, float *__restrict__ partial, int PQ)
+__global__ __launch_bounds__(256) void bias_grad_planes_kernel(const T *__restrict__ dy, float *__restrict__ out, int N, int K, int PQ, int n_per_wg)
 {
-    __shared__ float red[BG_THREADS];
-    const T *src = dy + (size_t)blockIdx.x * PQ;
-    float acc = 0.f;
-    for (int i = threadIdx.x; i < PQ; i += BG_THREADS) acc += load_f32(src + i);
-    red[threadIdx.x] = acc;
+    constexpr int V = VEC<T>;
+    struct __attribute__((packed)) Packed16 { uint32_t v[4]; };
+    __shared__ float red[256];
+    const int k = blockIdx.x, n0 = blockIdx.y * n_per_wg, n1 = min(N, n0 + n_per_wg);
+    const int full = PQ / V, pieces = (PQ + V - 1) / V;
+    float acc[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[e] = 0.f;
+    const long long total = (long long)(n1 - n0) * pieces;
+#pragma unroll 4
+    for (long long i = threadIdx.x; i < total; i += 256) {
+        const int n = (int)((unsigned)i / (unsigned)pieces), q = (int)((unsigned)i % (unsigned)pieces);
+        const T *src = dy + ((size_t)(n0 + n) * K + k) * PQ + (size_t)q * V;
+        if (q < full) {
+            const Packed16 v = *reinterpret_cast<const Packed16 *>(src);
+            add_vec<T>(acc, make_uint4(v.v[0], v.v[1], v.v[2], v.v[3]));
+        } else
+            for (int e = 0; e < PQ - full * V; ++e) acc[0] += load_f32(src + e);
+    }
+    float s = acc[0];
+#pragma unroll
+    for (int e = 1; e < V; ++e) s += acc[e];
+    red[threadIdx.x] = s;
     __syncthreads();
-    for (int half = BG_THREADS / 2; half > 0; half >>= 1) {
+    for (int half = 128; half > 0; half >>= 1) {
         if ((int)threadIdx.x < half) red[threadIdx.x] += red[threadIdx.x + half];
         __syncthreads();
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) out[(size_t)blockIdx.y * K + k] = red[0];
 }
 
-// db[k] = sum of the partial vectors, in a fixed order: a workgroup of 1024 threads owns 32 columns;
-// its 32 thread groups each add every 32nd partial vector, then the 32 sums are added in ascending
-// order.
-constexpr int BG_SUM_THREADS = 1024;
-__global__ __launch_bounds__(BG_SUM_THREADS) void bias_grad_sum_kernel(const float *__restrict__ partial, float *__restrict__ db, int K,
-                                                                       int parts)
+// db[k] = sum of the partial vectors' entries f*K + k, f < fold, and of the last `left` pixels of dy (those that fill no
+// whole row): 32 columns per workgroup, 32 thread groups that each add every 32nd entry, then the 32 sums in order.
+template <typename T>
+__global__ __launch_bounds__(BT) void bias_grad_sum_kernel(const float *__restrict__ partial, float *__restrict__ db, int K, int entries,
+                                                           const T *__restrict__ rest, int left)
 {
-    __shared__ float red[BG_SUM_THREADS];
-    constexpr int GROUPS = BG_SUM_THREADS / 32;
+    __shared__ float red[BT];
+    constexpr int GROUPS = BT / 32;
     const int col = threadIdx.x % 32, grp = threadIdx.x / 32;
     const int k = blockIdx.x * 32 + col;
     float acc = 0.f;
-    if (k < K)
-        for (int i = grp; i < parts; i += GROUPS) acc += partial[(size_t)i * K + k];
+    if (k < K) {
+#pragma unroll 8
+        for (int i = grp; i < entries; i += GROUPS) acc += partial[(size_t)i * K + k];
+        if (grp < left) acc += load_f32(rest + (size_t)grp * K + k);
+    }
     red[threadIdx.x] = acc;
     __syncthreads();
     if (grp == 0 && k < K) {
@@ -118,56 +140,86 @@ __global__ __launch_bounds__(BG_SUM_THREADS) void bias_grad_sum_kernel(const flo
     }
 }
 
-inline int ok() { return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH; }
+// How the tensor is cut.  One share (no second kernel) up to about 256 KB per workgroup: there the second launch costs
+// more than the rest of the chip would save.  Beyond that a workgroup per CU, in 1024 threads with 64 bytes each in
+// flight, reads at the rate of the copy kernel; more partial vectors only make the second kernel longer (1024 of them
+// cost it 9-12 us, 256 cost 3).
+struct BiasPlan { int fold, chunks, cpb, parts; long long rows, left; };
+
+BiasPlan plan(long long N, int K, long long PQ, int dtype, int layout)
+{
+    BiasPlan b{};
+    const int V = dtype == MXC_BF16 ? 8 : 4;
+    b.fold = 1;
+    if (layout == MXC_NCHW) {
+        // at least 512 workgroups, as far as there are images and 16 KB for each of them
+        long long parts = (512 + K - 1) / K;
+        const long long per_image = PQ * (16 / V);
+        long long most = N * per_image / (16 << 10);
+        if (most < 1) most = 1;
+        if (parts > most) parts = most;
+        if (parts > N) parts = N;
+        b.parts = (int)(parts < 1 ? 1 : parts);
+        return b;
+    }
+    while ((long long)K * b.fold % V != 0) b.fold *= 2;
+    b.chunks = K * b.fold / V;
+    b.rows = N * PQ / b.fold;
+    b.left = N * PQ % b.fold;
+    const bool one = b.fold == 1 && b.rows <= 4096;
+    b.cpb = b.chunks < (one ? 4 : BT) ? b.chunks : (one ? 4 : BT);
+    // wide rows: equal column blocks of at most 256 chunks, so that four row groups keep loads in flight
+    if (!one && b.cpb > 256) b.cpb = 256;
+    if (one) { b.parts = 1; return b; }
+    const long long col_blocks = (b.chunks + b.cpb - 1) / b.cpb;
+    long long parts = (256 + col_blocks - 1) / col_blocks;
+    const long long most = (b.rows * b.cpb * 16 + (32 << 10) - 1) / (32 << 10);      // at least 32 KB per workgroup
+    if (parts > most) parts = most;
+    b.parts = (int)(parts < 1 ? 1 : parts);
+    return b;
+}
+
+template <typename T>
+int run(const BiasPlan &b, long long N, int K, long long PQ, int layout, const T *dy, float *db, float *partial, hipStream_t st)
+{
+    const bool one = b.parts == 1 && b.fold == 1;
+    float *out = one ? db : partial;
+    if (layout == MXC_NCHW) {
+        const int per = (int)((N + b.parts - 1) / b.parts);
+        hipLaunchKernelGGL(bias_grad_planes_kernel<T>, dim3((unsigned)K, (unsigned)((N + per - 1) / per)), dim3(256), 0, st, dy, out, (int)N, K,
+                           (int)PQ, per);
+        if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
+        if (one) return MXC_OK;
+        hipLaunchKernelGGL(bias_grad_sum_kernel<T>, dim3((unsigned)((K + 31) / 32)), dim3(BT), 0, st, partial, db, K, (int)((N + per - 1) / per), dy, 0);
+        return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+    }
+    const long long per = b.rows > 0 ? (b.rows + b.parts - 1) / b.parts : 1;
+    if (per > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
+    const int used = (int)((b.rows + per - 1) / per);          // 0: only left-over pixels
+    if (used > 0)
+        hipLaunchKernelGGL(bias_grad_rows_kernel<T>, dim3((unsigned)((b.chunks + b.cpb - 1) / b.cpb), (unsigned)used), dim3(BT), 0, st,
+                           (const uint4 *)dy, out, b.rows, b.chunks, b.cpb, (int)per);
+    if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
+    if (one) return MXC_OK;
+    hipLaunchKernelGGL(bias_grad_sum_kernel<T>, dim3((unsigned)((K + 31) / 32)), dim3(BT), 0, st, partial, db, K, used * b.fold,
+                       dy + (size_t)b.rows * b.fold * K, (int)b.left);
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+}
 
 }  // namespace
 
-// number of partial vectors (each K floats) the first step produces
-int bias_grad_parts(long long N, int K, long long PQ, int layout)
+size_t bias_grad_scratch(long long N, int K, long long PQ, int dtype, int layout)
 {
-    if (layout == MXC_NCHW) return (int)N;
-    (void)K;
-    const long long rows = N * PQ;
-    long long parts = (rows + 255) / 256;      // at least 256 rows per workgroup
-    if (parts > 1024) parts = 1024;
-    return (int)(parts < 1 ? 1 : parts);
+    const BiasPlan b = plan(N, K, PQ, dtype, layout);
+    return (size_t)b.parts * b.fold * K * sizeof(float);
 }
 
 int bias_grad(long long N, int K, long long PQ, int dtype, int layout, const void *dy, float *db, float *partial, hipStream_t st)
 {
-    const int parts = bias_grad_parts(N, K, PQ, layout);
-    if (layout == MXC_NCHW) {
-        if (N * K > 0x7FFFFFFFll || PQ > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
-        if (dtype == MXC_BF16)
-            hipLaunchKernelGGL(bias_grad_planes_kernel<bf16_t>, dim3((unsigned)(N * K)), dim3(BG_THREADS), 0, st, (const bf16_t *)dy,
-                               partial, (int)PQ);
-        else
-            hipLaunchKernelGGL(bias_grad_planes_kernel<float>, dim3((unsigned)(N * K)), dim3(BG_THREADS), 0, st, (const float *)dy,
-                               partial, (int)PQ);
-    } else {
-        const long long rows = N * PQ;
-        const int rows_per_wg = (int)((rows + parts - 1) / parts);
-        const int vec = dtype == MXC_BF16 ? 8 : 4;
-        const bool vector = K % vec == 0 && K / vec <= BG_THREADS;
-        if (dtype == MXC_BF16) {
-            if (vector)
-                hipLaunchKernelGGL((bias_grad_rows_vec_kernel<bf16_t, 8>), dim3((unsigned)parts), dim3(BG_THREADS), 0, st,
-                                   (const bf16_t *)dy, partial, rows, K, rows_per_wg);
-            else
-                hipLaunchKernelGGL(bias_grad_rows_kernel<bf16_t>, dim3((unsigned)parts), dim3(BG_THREADS), 0, st, (const bf16_t *)dy,
-                                   partial, rows, K, rows_per_wg);
-        } else {
-            if (vector)
-                hipLaunchKernelGGL((bias_grad_rows_vec_kernel<float, 4>), dim3((unsigned)parts), dim3(BG_THREADS), 0, st,
-                                   (const float *)dy, partial, rows, K, rows_per_wg);
-            else
-                hipLaunchKernelGGL(bias_grad_rows_kernel<float>, dim3((unsigned)parts), dim3(BG_THREADS), 0, st, (const float *)dy,
-                                   partial, rows, K, rows_per_wg);
-        }
-    }
-    if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
-    hipLaunchKernelGGL(bias_grad_sum_kernel, dim3((unsigned)((K + 31) / 32)), dim3(BG_SUM_THREADS), 0, st, partial, db, K, parts);
-    return ok();
+    if (layout == MXC_NCHW && (PQ > 0x7FFFFFFFll || N > 0x7FFFFFFFll || N * ((PQ + 3) / 4) > 0x7FFFFFFFll)) return MXC_ERR_SHAPE;
+    const BiasPlan b = plan(N, K, PQ, dtype, layout);
+    if (dtype == MXC_BF16) return run(b, N, K, PQ, layout, (const bf16_t *)dy, db, partial, st);
+    return run(b, N, K, PQ, layout, (const float *)dy, db, partial, st);
 }
 
 }  // namespace mxc

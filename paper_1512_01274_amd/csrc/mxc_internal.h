@@ -56,9 +56,10 @@ struct PostOp {
 // keeps the halves of v (two bf16) whose mask half is > 0
 __device__ __forceinline__ uint32_t mask_bf16x2(uint32_t v, uint32_t m)
 {
-    const uint32_t lo = (int16_t)(m & 0xFFFFu) > 0 ? 0x0000FFFFu : 0u;
-    const uint32_t hi = (int16_t)(m >> 16) > 0 ? 0xFFFF0000u : 0u;
-    return v & (lo | hi);
+    // per half: min(m, 1) as signed integers is 1 where m > 0 and at most 0 elsewhere; 0 - max(that, 0) is all ones or zero
+    typedef short s2 __attribute__((ext_vector_type(2)));
+    const s2 one = __builtin_elementwise_max(__builtin_elementwise_min(__builtin_bit_cast(s2, m), s2{1, 1}), s2{0, 0});
+    return v & __builtin_bit_cast(uint32_t, s2{0, 0} - one);
 }
 __device__ __forceinline__ bool mask_keeps(const float *m) { return *m > 0.f; }
 __device__ __forceinline__ bool mask_keeps(const bf16_t *m) { return (int16_t)*m > 0; }
@@ -136,6 +137,18 @@ __device__ __forceinline__ void buffer_store16_nt(out_rsrc_t rsrc, unsigned byte
     __builtin_amdgcn_raw_buffer_store_b128(u32x4{v.x, v.y, v.z, v.w}, rsrc, (int)byte_off, 0, 2);   // 2: non-temporal
 }
 
+// 16-byte load through a buffer resource: a lane whose byte_off lies beyond the resource's size gets zeros
+__device__ __forceinline__ uint4 buffer_load16(out_rsrc_t rsrc, unsigned byte_off)
+{
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)byte_off, 0, 0);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint4 mask_bf16x8(uint4 v, uint4 m)
+{
+    return make_uint4(mask_bf16x2(v.x, m.x), mask_bf16x2(v.y, m.y), mask_bf16x2(v.z, m.z), mask_bf16x2(v.w, m.w));
+}
+
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline size_t elem_size(int dtype) { return dtype == MXC_BF16 ? 2 : 4; }
 
@@ -177,7 +190,7 @@ int softmax_fwd(int N, int K, int dtype, const void *z, void *p, hipStream_t st)
 int softmax_xent_bwd(int N, int K, int dtype, const void *p, const int *labels, void *dz, float scale, hipStream_t st);
 
 // ---- bias.hip: bias gradient ------------------------------------------------------------
-int bias_grad_parts(long long N, int K, long long PQ, int layout);      // partial vectors of K floats the call needs as scratch
+size_t bias_grad_scratch(long long N, int K, long long PQ, int dtype, int layout);      // bytes of partial vectors
 int bias_grad(long long N, int K, long long PQ, int dtype, int layout, const void *dy, float *db, float *partial, hipStream_t st);
 
 // ---- direct.hip: one-thread-per-output kernels, any shape, NHWC/KRSC --------
@@ -236,6 +249,9 @@ int sum_splits(const float *partial, void *dw, bool dw_bf16, long long total, in
 // ---- the implicit GEMM as its kernels see it (igemm.hip, stream.hip) ----------------------------------
 constexpr int MAX_TAPS = 127;   // tap table capacity (11x11 = 121 fits)
 
+struct RowStep { int n, a, b; };
+inline RowStep row_step(int rows, int Mh, int Mw) { return RowStep{rows / (Mh * Mw), rows % (Mh * Mw) / Mw, rows % Mw}; }
+
 // Out[m][co] = sum_{t,ci} In[pixel(m) + tap(t)][ci] * Wm[co][t*Ci + ci]; m runs over (image, row, column) of the
 // launch's output grid, t over a TR x TS grid of filter taps, ci over the channels of a tap's contiguous run.
 struct IgemmParams {
@@ -251,6 +267,9 @@ struct IgemmParams {
     int Mh, Mw;          // output grid of this launch (per image)
     int in_mul_h, in_mul_w, in_off_h, in_off_w;     // input coordinate of tap 0: a*in_mul + in_off
     int Ho, Wo, out_mul_h, out_mul_w, out_off_h, out_off_w;  // output coordinate: a*out_mul + out_off
+    // A step of so many GEMM rows as images + grid rows + grid columns, set by the launcher: of a load's rows to the next
+    // load's, and of a store's rows to the next store's (walked by additions: a division costs a wave some hundred clocks)
+    RowStep in_step, out_step;
     int linear_out;      // output pixel index == m (forward, and stride-1 backward-data)
     int M;               // N*Mh*Mw (< 2^31, checked by the launcher)
     int m_begin, m_end;  // GEMM rows [m_begin, m_end) belong to this launch (a problem may be cut in two launches of
