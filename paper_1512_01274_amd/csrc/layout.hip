@@ -159,14 +159,19 @@ __device__ __forceinline__ void store8(uint16_t *p, uint4 v, int n)
 
 struct RelayJobs { RelayJob job[MAX_RELAY_JOBS]; int n; };
 
+// NJ jobs: with a compile-time count the jobs' fields are fetched together instead of one search step after another
+template <int NJ>
 __global__ __launch_bounds__(256) void relayout_kernel(const RelayJobs jobs)
 {
     constexpr int PITCH = 33;                              // dwords per LDS column: odd, conflict-free dword writes
     __shared__ uint32_t tile[TILE * PITCH];
-    int ji = 0;
     unsigned blk = blockIdx.x;
-    while (ji + 1 < jobs.n && blk >= jobs.job[ji].blocks) blk -= jobs.job[ji++].blocks;
-    const RelayJob &q = jobs.job[ji];
+    RelayJob q = jobs.job[0];
+#pragma unroll
+    for (int i = 1; i < NJ; ++i) {
+        const unsigned before = i == 1 ? jobs.job[0].blocks : jobs.job[0].blocks + jobs.job[1].blocks;
+        if (blockIdx.x >= before) { q = jobs.job[i]; blk = blockIdx.x - before; }
+    }
     const int t = threadIdx.x;
     const uint16_t *src = (const uint16_t *)q.src;
     uint16_t *dst = (uint16_t *)q.dst;
@@ -400,7 +405,27 @@ RelayJob relay_bwd_filter(const ConvShape &s, const void *w, void *wt, bool kcrs
     q.C = real_c(s); q.class_C = s.C; q.R = s.R; q.S = s.S; q.stride = s.stride;
     q.rows = real_k(s); q.cols = q.C * s.R * s.S; q.src_pitch = q.cols;
     q.run = s.K; q.dst_pitch = s.K;
+    if (s.R == 1 && s.S == 1) {        // the one tap's matrix is the filter's transpose
+        q.kind = RELAY_TRANSPOSE;
+        q.src_batch = q.dst_batch = (long long)q.rows * q.cols;
+    }
     return q;
+}
+
+static int launch_relayout(const RelayJobs &all, long long blocks, hipStream_t st)
+{
+    static_assert(MAX_RELAY_JOBS == 3, "job counts the kernel is built for");
+    const dim3 grid((unsigned)blocks), block(256);
+    const RelayJob &q = all.job[0];
+    if (all.n == 1 && q.kind == RELAY_TRANSPOSE && q.rows % 8 == 0 && q.cols % 8 == 0 && q.run == q.rows && q.src_pitch == q.cols &&
+        q.dst_pitch == q.rows && q.src_batch == q.dst_batch)
+        // one dense transpose of whole chunks: the plain kernel (half the time of the general one where it is all launch)
+        hipLaunchKernelGGL((void (*)(const uint16_t *, uint16_t *, int, int))transpose_vec16_kernel, grid, block, 0, st, (const uint16_t *)q.src,
+                           (uint16_t *)q.dst, q.rows, q.cols);
+    else if (all.n == 1) hipLaunchKernelGGL(relayout_kernel<1>, grid, block, 0, st, all);
+    else if (all.n == 2) hipLaunchKernelGGL(relayout_kernel<2>, grid, block, 0, st, all);
+    else hipLaunchKernelGGL(relayout_kernel<3>, grid, block, 0, st, all);
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
 int relayout(const RelayJob *jobs, int n, hipStream_t st)
@@ -420,16 +445,17 @@ int relayout(const RelayJob *jobs, int n, hipStream_t st)
         if (blocks == 0) continue;
         q.blocks = (unsigned)blocks;
         if (total + blocks > 0x7FFFFFFFll) {               // more workgroups than one launch holds: what there is goes first
-            hipLaunchKernelGGL(relayout_kernel, dim3((unsigned)total), dim3(256), 0, st, all);
-            all.job[0] = q;
+            const RelayJob last = q;
+            const int rc = launch_relayout(all, total, st);
+            if (rc != MXC_OK) return rc;
+            all.job[0] = last;
             all.n = 0;
             total = 0;
         }
         total += blocks;
         ++all.n;
     }
-    if (all.n) hipLaunchKernelGGL(relayout_kernel, dim3((unsigned)total), dim3(256), 0, st, all);
-    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+    return all.n ? launch_relayout(all, total, st) : MXC_OK;
 }
 
 int launch_copy(const void *src, void *dst, size_t bytes, hipStream_t stream)

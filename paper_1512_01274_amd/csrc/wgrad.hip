@@ -600,22 +600,12 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
 {
     const int total = g.Kout * g.R * g.S * g.C;
     const size_t split_stride = (size_t)g.K * ncols;
-    if (kcrs) {
-        const int RS = g.R * g.S, c_tiles = (g.C + 63) / 64;
-        if ((long long)g.Kout * c_tiles > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
-        const dim3 grid((unsigned)(g.Kout * c_tiles));
-        // eight groups of splits while their sums fit 32 KB of LDS
-        if (splits >= 4 && RS <= 16)
-            hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<8, OUT>), grid, dim3(256), (size_t)8 * 64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S,
-                               g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
-        else
-            hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<1, OUT>), grid, dim3(256), (size_t)64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S,
-                               g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
-        return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
-    }
     // many splits of a small dw: 16 lane groups keep enough loads in flight; otherwise 4
     const bool wide = splits >= 32 && total < 256 * 1024;
-    if (!identity && splits > 1) {
+    // KCRS: a workgroup of the reordering kernel adds up 64*R*S results; where that would be a long chain for each of its
+    // threads (112 splits of a 50x30x3x3 filter: 65 us) the splits are added first, as below
+    const bool kcrs_long = kcrs && (long long)splits * g.R * g.S > 128;
+    if ((kcrs ? kcrs_long : !identity) && splits > 1) {
         // Packed geometries (first layers): the column remap reads single floats, so first add the splits with the
         // 16-byte kernel - in place, into the first split's partial tensor: every element is read and then written
         // by the same lane group - and remap that one tensor afterwards.
@@ -628,6 +618,19 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
                                (const float4 *)partial, partial, cols4, splits, (size_t)cols4);
         if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
         splits = 1;
+    }
+    if (kcrs) {
+        const int RS = g.R * g.S, c_tiles = (g.C + 63) / 64;
+        if ((long long)g.Kout * c_tiles > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
+        const dim3 grid((unsigned)(g.Kout * c_tiles));
+        // eight groups of splits while their sums fit 32 KB of LDS
+        if (splits >= 4 && RS <= 16)
+            hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<8, OUT>), grid, dim3(256), (size_t)8 * 64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S,
+                               g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
+        else
+            hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<1, OUT>), grid, dim3(256), (size_t)64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S,
+                               g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
+        return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
     }
     if (identity && total % 4 == 0 && split_stride % 4 == 0) {
         const int total4 = total / 4;
