@@ -67,6 +67,33 @@ template <int RC> __device__ __forceinline__ int bt_row_swz(int row)
 template <class F, int... I> __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) { (f(IC<I>{}), ...); }
 template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
+// Position of a GEMM row in the launch's output grid, advanced by a fixed step without a division.
+struct GridPos {
+    int n, a, b;
+    __device__ __forceinline__ GridPos(int m, int Mh, int Mw)
+    {
+        const unsigned t = (unsigned)m / (unsigned)Mw;
+        b = (int)((unsigned)m - t * (unsigned)Mw);
+        n = (int)(t / (unsigned)Mh);
+        a = (int)(t - (unsigned)n * (unsigned)Mh);
+    }
+    // one step further; returns the change of an address that grows by n_len per image, a_len per grid row, b_len per column
+    __device__ __forceinline__ int advance(const RowStep &s, int Mh, int Mw, int n_len, int a_len, int b_len)
+    {
+        int d = s.n * n_len + s.a * a_len + s.b * b_len;
+        b += s.b;
+        const bool cb = b >= Mw;
+        b -= cb ? Mw : 0;
+        a += s.a + (cb ? 1 : 0);
+        d += cb ? a_len - Mw * b_len : 0;
+        const bool ca = a >= Mh;
+        a -= ca ? Mh : 0;
+        n += s.n + (ca ? 1 : 0);
+        d += ca ? n_len - Mh * a_len : 0;
+        return d;
+    }
+};
+
 // BM x BN output tile, BKT reduction elements per stage, NS stages, WR x WC waves.  The register
 // budget is set for two waves per SIMD when the workgroup has 4 waves and its LDS lets two of them
 // share a CU.
@@ -74,9 +101,9 @@ template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { st
 // [reduction row][BN output columns] and its MFMA fragments come from ds_read_b64_tr_b16.
 // TI = true: channel-block-major reduction order (needs Ci % BKT == 0); a compile-time choice so that the
 // stage body is one basic block and the pinned interleave of address work and MFMAs survives.
+// Runs the output tile whose first row is m0 and first column n0 (split_z: its share of a split reduction).
 template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT, bool TI>
-__global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT * 2 <= 80 * 1024) ? 2 : 1) void igemm_kernel(
-    const IgemmParams p)
+__device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, const int n0, const int split_z)
 {
     static_assert(!(BT && TI), "the in-place filter variant has one tap");
     constexpr int NW = WR * WC, NT = 64 * NW;
@@ -127,17 +154,6 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps LDS targets in SGPRs
     const int wave_m = (wave / WC) * WM, wave_n = (wave % WC) * WN;
 
-    // Workgroup -> tile.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs; give each
-    // XCD a contiguous range of tiles, n-tile fastest, so that tiles sharing an activation tile meet
-    // in one L2.
-    const int total = p.m_tiles * p.n_tiles;
-    const int units = total * (p.splits > 1 ? p.splits : 1);
-    const int per_xcd = (units + 7) / 8;
-    const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (unit >= units) return;
-    const int logical = unit % total, split_z = unit / total;
-    const int m0 = p.m_begin + (logical / p.n_tiles) * BM, n0 = (logical % p.n_tiles) * BN;
-
     const int T = p.TR * p.TS;
     const int Kd = T * p.Ci;
     const int KT = (Kd + BKT - 1) / BKT;
@@ -171,20 +187,19 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
     const buf_rsrc_t rs_in = make_buf_rsrc(p.in, p.in_bytes);
     const buf_rsrc_t rs_wm = make_buf_rsrc(p.wm, p.wm_bytes);
 
-    int a_off[A_LD];     // byte offset of (n, base_h, base_w, 0) in `in` (may be negative)
+    int a_off[A_LD];     // byte offset of (n, base_h, base_w, 0) in `in` (wraps below zero in the padding)
     int a_hw[A_LD];      // base_h (low 16 bits) and base_w (high 16), signed; invalid row: h = -16384
+    {
+        const int m = m0 + RPL * wave + ld_sub;                    // this lane's row of the first load; RPL*NW further for each next
+        GridPos g(m, p.Mh, p.Mw);
+        const int px2 = p.pix * 2, row2 = p.Wi * px2;
+        int off = ((g.n * p.Hi + g.a * p.in_mul_h + p.in_off_h) * p.Wi + g.b * p.in_mul_w + p.in_off_w) * px2;
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-        const int m = m0 + RPL * (wave + NW * i) + ld_sub;
-        if (m < p.m_end) {
-            const unsigned b = (unsigned)m % (unsigned)p.Mw, t2 = (unsigned)m / (unsigned)p.Mw;
-            const unsigned a = t2 % (unsigned)p.Mh, n = t2 / (unsigned)p.Mh;
-            const int h = (int)a * p.in_mul_h + p.in_off_h, w = (int)b * p.in_mul_w + p.in_off_w;
-            a_off[i] = (int)((((long long)n * p.Hi + h) * p.Wi + w) * p.pix * 2);
-            a_hw[i] = (h & 0xFFFF) | (w << 16);
-        } else {
-            a_off[i] = 0;
-            a_hw[i] = (-16384) & 0xFFFF;
+        for (int i = 0; i < A_LD; ++i) {
+            a_off[i] = off;
+            const int h = g.a * p.in_mul_h + p.in_off_h, w = g.b * p.in_mul_w + p.in_off_w;
+            a_hw[i] = m + RPL * NW * i < p.m_end ? (h & 0xFFFF) | (w << 16) : (-16384) & 0xFFFF;
+            if (i + 1 < A_LD) off += g.advance(p.in_step, p.Mh, p.Mw, p.Hi * row2, p.in_mul_h * row2, p.in_mul_w * px2);
         }
     }
     unsigned b_off[B_LD];   // byte offset of the filter row, OOB for rows past Co
@@ -473,20 +488,48 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
                     *reinterpret_cast<uint2 *>(stg + frag_row * PW + 4 * ((j * 8 + 2 * g4 + frag_kg) ^ ((frag_row >> 3) & 3))) = pk;
                 }
         };
-        // Common case (output pixel index == GEMM row, no mask, output below 2 GiB, a store instruction covers whole
-        // staged rows): one buffer store per 64/CPR rows; rows past the end and columns past Co get an offset the
-        // resource rejects, which takes the place of a bounds branch.
+        // Outputs below 2 GiB whose staged rows one store instruction covers whole: one buffer store per 64/CPR rows;
+        // rows past the end and columns past Co get an offset the resource rejects, which takes the place of a bounds
+        // branch.  A mask is fetched the same way and all of it before the first conversion, so that its latency lies
+        // under the staging.
         constexpr bool ROWS_PER_STORE_OK = 64 % CPR == 0;
         constexpr int RPI = ROWS_PER_STORE_OK ? 64 / CPR : 1;
-        const bool fast_store = ROWS_PER_STORE_OK && p.linear_out && p.mask == nullptr && p.out_bytes != 0;
+        constexpr int NST = ROWS_PER_STORE_OK ? 32 / RPI : 1;
+        const bool fast_store = ROWS_PER_STORE_OK && p.out_bytes != 0;
         const out_rsrc_t rs_out = make_out_rsrc(p.out, p.out_bytes);
         const int st_r = lane / CPR, st_c = lane % CPR;
+        unsigned st_off[MI][NST];
+        uint4 st_mask[MI][NST];
+        if (fast_store) {
+            const bool col_ok = n0 + wave_n + st_c * 8 < p.Co;
+            const int m = m0 + wave_m + st_r, co2 = p.Co * 2;      // this lane's row of the first store; RPI further for each next
+            unsigned off = (unsigned)((n0 + wave_n + st_c * 8) * 2);
+            if (p.linear_out) {
+                off += (unsigned)m * (unsigned)co2;                // below 2^32: the output is below 2^31 and a tile adds little
+#pragma unroll
+                for (int k = 0; k < MI * NST; ++k) st_off[k / NST][k % NST] = col_ok && m + k * RPI < p.m_end ? off + (unsigned)(k * RPI * co2) : OOB;
+            } else {
+                GridPos g(m, p.Mh, p.Mw);
+                off += (unsigned)(((g.n * p.Ho + g.a * p.out_mul_h + p.out_off_h) * p.Wo + g.b * p.out_mul_w + p.out_off_w) * co2);
+#pragma unroll
+                for (int k = 0; k < MI * NST; ++k) {
+                    st_off[k / NST][k % NST] = col_ok && m + k * RPI < p.m_end ? off : OOB;
+                    if (k + 1 < MI * NST)
+                        off += (unsigned)g.advance(p.out_step, p.Mh, p.Mw, p.Ho * p.Wo * co2, p.out_mul_h * p.Wo * co2, p.out_mul_w * co2);
+                }
+            }
+            if (p.mask != nullptr) {
+                const out_rsrc_t rs_mask = make_out_rsrc(const_cast<bf16_t *>(p.mask), p.out_bytes);
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int k = 0; k < NST; ++k) st_mask[i][k] = buffer_load16(rs_mask, st_off[i][k]);
+            }
+        }
         auto staged_chunk = [&](int r, int c) __attribute__((always_inline)) {
             const uint4 v = *reinterpret_cast<const uint4 *>(stg + r * PW + ((c ^ ((r >> 4) & 1)) << 3));
             return ((r >> 3) & 1) ? make_uint4(v.z, v.w, v.x, v.y) : v;
         };
-        const bool st_col_ok = n0 + wave_n + st_c * 8 < p.Co;
-        const unsigned st_lane_off = (unsigned)((st_r * p.Co + n0 + wave_n + st_c * 8) * 2);
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             if (has_bias) { if (p.relu) stage_block(i, std::true_type{}, std::true_type{}); else stage_block(i, std::true_type{}, std::false_type{}); }
@@ -495,16 +538,12 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             if (fast_store) {
-                const int mb = m0 + wave_m + i * 32;
-                const unsigned blk_off = (unsigned)mb * (unsigned)(p.Co * 2);   // below 2^32: the output is below 2^31 and a tile adds little
-                const int rows_left = p.m_end - mb;
 #pragma unroll
-                for (int k = 0; k < 32 / RPI; ++k) {
-                    const uint4 v = staged_chunk(st_r + k * RPI, st_c);
-                    const bool ok = st_col_ok && st_r + k * RPI < rows_left;
-                    const unsigned off = ok ? st_lane_off + blk_off + (unsigned)(k * RPI * p.Co * 2) : OOB;
-                    if (p.nt_out) buffer_store16_nt(rs_out, off, v);
-                    else buffer_store16(rs_out, off, v);
+                for (int k = 0; k < NST; ++k) {
+                    uint4 v = staged_chunk(st_r + k * RPI, st_c);
+                    if (p.mask != nullptr) v = mask_bf16x8(v, st_mask[i][k]);
+                    if (p.nt_out) buffer_store16_nt(rs_out, st_off[i][k], v);
+                    else buffer_store16(rs_out, st_off[i][k], v);
                 }
             } else {
 #pragma unroll
@@ -517,7 +556,7 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
                         const long long off = out_pixel(m) * p.Co + co;
                         if (p.mask != nullptr) {
                             const uint4 mk = *reinterpret_cast<const uint4 *>(p.mask + off);
-                            v = make_uint4(mask_bf16x2(v.x, mk.x), mask_bf16x2(v.y, mk.y), mask_bf16x2(v.z, mk.z), mask_bf16x2(v.w, mk.w));
+                            v = mask_bf16x8(v, mk);
                         }
                         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
                         const u32x4 vv = {v.x, v.y, v.z, v.w};
@@ -570,6 +609,73 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * (BM + BN) * BKT
     }
 }
 
+// Workgroup -> tile.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs; give each XCD a contiguous range of
+// tiles, n-tile fastest, so that tiles sharing an activation tile meet in one L2.
+__device__ __forceinline__ int tile_unit(int units)
+{
+    const int per_xcd = (units + 7) / 8;
+    return (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+}
+
+template <int BM, int BN, int BKT, int NS, int WR, int WC>
+constexpr int tile_min_blocks = (WR * WC == 4 && NS * (BM + BN) * BKT * 2 <= 80 * 1024) ? 2 : 1;
+
+template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT, bool TI>
+__global__ __launch_bounds__(64 * WR * WC, (tile_min_blocks<BM, BN, BKT, NS, WR, WC>)) void igemm_kernel(const IgemmParams p)
+{
+    const int total = p.m_tiles * p.n_tiles;
+    const int units = total * (p.splits > 1 ? p.splits : 1);
+    const int unit = tile_unit(units);
+    if (unit >= units) return;
+    const int logical = unit % total;
+    igemm_tile<BM, BN, BKT, NS, WR, WC, BT, TI>(p, p.m_begin + (logical / p.n_tiles) * BM, (logical % p.n_tiles) * BN, unit / total);
+}
+
+// Strided backward-data: all residue classes of (h+pad, v+pad) mod stride that some tap reaches in one launch, the classes
+// of one stretch of rows next to each other - they read the same dy rows and together write whole stretches of dx.  One
+// launch per class ran them one after another, each with its own start, drain and part-filled last round (3x3 stride 2,
+// 40->256 at 20x20, batch 12: 42 us in four launches, 14 in one).
+struct IgemmClass {
+    const bf16_t *wm;
+    unsigned wm_bytes;
+    int TR, TS, Mh, Mw, in_off_h, in_off_w, out_off_h, out_off_w;
+    RowStep in_step, out_step;
+};
+struct IgemmClasses {
+    IgemmParams p;       // what the classes share
+    IgemmClass c[16];
+    int n, max_m_tiles;
+};
+
+template <int BM, int BN, int BKT, int NS, int WR, int WC, bool TI>
+__global__ __launch_bounds__(64 * WR * WC, (tile_min_blocks<BM, BN, BKT, NS, WR, WC>)) void igemm_classes_kernel(const IgemmClasses q)
+{
+    const int units = q.max_m_tiles * q.n * q.p.n_tiles;
+    const int unit = tile_unit(units);
+    if (unit >= units) return;
+    const int n_tile = unit % q.p.n_tiles, t2 = unit / q.p.n_tiles;
+    const IgemmClass &c = q.c[t2 % q.n];
+    const int m0 = t2 / q.n * BM;
+    IgemmParams p = q.p;
+    p.wm = c.wm; p.wm_bytes = c.wm_bytes;
+    p.TR = c.TR; p.TS = c.TS; p.Mh = c.Mh; p.Mw = c.Mw;
+    p.in_off_h = c.in_off_h; p.in_off_w = c.in_off_w; p.out_off_h = c.out_off_h; p.out_off_w = c.out_off_w;
+    p.in_step = c.in_step; p.out_step = c.out_step;
+    p.M = p.N * c.Mh * c.Mw;
+    p.m_end = p.M;
+    if (m0 >= p.M) return;
+    igemm_tile<BM, BN, BKT, NS, WR, WC, false, TI>(p, m0, n_tile * BN, 0);
+}
+
+// the kernel's row steps: from load to load of a wave, and from store to store (64 lanes of 16 bytes over the wave's columns)
+template <int BN, int BKT, int WR, int WC>
+void set_steps(RowStep &in, RowStep &out, int Mh, int Mw)
+{
+    constexpr int CPR = BN / WC / 8;
+    in = row_step(64 / (BKT / 8) * WR * WC, Mh, Mw);
+    out = row_step(64 % CPR == 0 ? 64 / CPR : 1, Mh, Mw);
+}
+
 // Launches the tile shape on GEMM rows [m_begin, m_end) of the problem (m_end < 0: to the last row).
 template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT = false>
 int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end = -1)
@@ -581,6 +687,7 @@ int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end
     const long long mt = (m_end - m_begin + BM - 1) / BM;
     p.n_tiles = (p.Co + BN - 1) / BN;
     if (mt * p.n_tiles > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
+    set_steps<BN, BKT, WR, WC>(p.in_step, p.out_step, p.Mh, p.Mw);
     p.M = (int)M;
     p.m_begin = (int)m_begin;
     p.m_end = (int)m_end;
@@ -616,6 +723,27 @@ int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
+template <int BM, int BN, int BKT, int NS, int WR, int WC>
+int launch_classes(IgemmClasses &q, hipStream_t st)
+{
+    IgemmParams &p = q.p;
+    p.n_tiles = (p.Co + BN - 1) / BN;
+    long long most = 0;
+    for (int i = 0; i < q.n; ++i) {
+        const long long mt = ((long long)p.N * q.c[i].Mh * q.c[i].Mw + BM - 1) / BM;
+        if (mt > most) most = mt;
+        set_steps<BN, BKT, WR, WC>(q.c[i].in_step, q.c[i].out_step, q.c[i].Mh, q.c[i].Mw);
+    }
+    const long long total = most * q.n * p.n_tiles;
+    if (total > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
+    q.max_m_tiles = (int)most;
+    const dim3 grid((unsigned)((total + 7) / 8 * 8)), block(64 * WR * WC);
+    p.tap_inner = p.Ci % BKT == 0 ? 1 : 0;
+    if (p.tap_inner) hipLaunchKernelGGL((igemm_classes_kernel<BM, BN, BKT, NS, WR, WC, true>), grid, block, 0, st, q);
+    else hipLaunchKernelGGL((igemm_classes_kernel<BM, BN, BKT, NS, WR, WC, false>), grid, block, 0, st, q);
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+}
+
 // A tile shape the launcher can pick: output tile, workgroups that fit one CU at a time (LDS and
 // register budget) and the matrix-pipe utilisation it reaches relative to the 256x256 tile when the
 // chip is full (fitted to per-layer times of the AlexNet- and VGG-style stacks run back to back).
@@ -642,7 +770,10 @@ const char *const kStreamName = "igemm_stream";
 // ... and of the window kernel (window.hip), likewise
 constexpr int WINDOW_TILE = N_TILE_CHOICES + 1;
 const char *const kWindowName = "igemm_window";
-inline bool whole_launch(int idx) { return idx == STREAM_TILE || idx == WINDOW_TILE; }
+// ... whose form with a mask in the epilogue is a kernel, and a name for the hooks, of its own
+constexpr int MASKED_WINDOW_TILE = N_TILE_CHOICES + 2;
+const char *const kMaskedWindowName = "igemm_patch_masked";
+inline bool whole_launch(int idx) { return idx == STREAM_TILE || idx == WINDOW_TILE || idx == MASKED_WINDOW_TILE; }
 
 // the tiles that also exist reading a 1x1 filter in place (transposed tiles)
 bool has_bt(int idx) { return idx == 0 || idx == 1 || idx == 4; }
@@ -674,6 +805,25 @@ int launch_choice(int idx, const IgemmParams &p, hipStream_t st, bool bt = false
     }
 }
 
+int launch_classes_choice(int idx, IgemmClasses &q, hipStream_t st)
+{
+    switch (idx) {
+    case 0: return launch_classes<128, 128, 64, 2, 2, 2>(q, st);
+    case 1: return launch_classes<256, 256, 64, 2, 2, 4>(q, st);
+    case 2: return launch_classes<256, 128, 64, 3, 4, 2>(q, st);
+    case 3: return launch_classes<128, 256, 64, 3, 2, 4>(q, st);
+    case 4: return launch_classes<128, 64, 64, 2, 2, 2>(q, st);
+    case 5: return launch_classes<256, 64, 32, 3, 4, 1>(q, st);
+    case 6: return launch_classes<128, 32, 64, 2, 4, 1>(q, st);
+    case 7: return launch_classes<256, 32, 64, 2, 4, 1>(q, st);
+    case 8: return launch_classes<256, 192, 64, 2, 4, 2>(q, st);
+    case 9: return launch_classes<192, 256, 64, 2, 2, 4>(q, st);
+    case 10: return launch_classes<64, 256, 64, 3, 2, 4>(q, st);
+    case 11: return launch_classes<64, 128, 64, 3, 2, 2>(q, st);
+    default: return launch_classes<192, 128, 64, 3, 2, 4>(q, st);
+    }
+}
+
 // How a GEMM of M rows is run: every row by tile shape `main`, or - when the last round of main tiles would
 // leave most CUs idle - rows [0, rows_main) by `main` in whole rounds over the chip and the rest by a second
 // launch of the smaller shape `tail` (tail < 0: one launch).
@@ -685,6 +835,7 @@ int tile_index(const char *name, size_t len)
         if (strlen(kTiles[i].name) == len && !strncmp(name, kTiles[i].name, len)) return i;
     if (strlen(kStreamName) == len && !strncmp(name, kStreamName, len)) return STREAM_TILE;
     if (strlen(kWindowName) == len && !strncmp(name, kWindowName, len)) return WINDOW_TILE;
+    if (strlen(kMaskedWindowName) == len && !strncmp(name, kMaskedWindowName, len)) return MASKED_WINDOW_TILE;
     return -1;
 }
 
@@ -720,14 +871,14 @@ double model_time(const TileChoice &t, long long M, int Co, int KT, double fixed
 thread_local long long g_key_M = 0;
 thread_local int g_key_Co = 0, g_key_Kd = 0;
 
-Plan choose_plan(long long M, int Co, int Kd, bool allow_stream = true)
+Plan choose_plan(long long M, int Co, int Kd, bool allow_stream = true, bool masked = false)
 {
     g_key_M = M; g_key_Co = Co; g_key_Kd = Kd;
     if (const char *f = getenv("MXC_FORCE_VARIANT")) {
         const char *plus = strchr(f, '+');
         const int a = tile_index(f, plus ? (size_t)(plus - f) : strlen(f));
         const int b = plus ? tile_index(plus + 1, strlen(plus + 1)) : -1;
-        if (a >= 0 && whole_launch(a) && !plus && allow_stream) return Plan{a, -1, M};
+        if (a >= 0 && whole_launch(a) && !plus && allow_stream && !(a == WINDOW_TILE && masked) && !(a == MASKED_WINDOW_TILE && !masked)) return Plan{a, -1, M};
         if (a >= 0 && !whole_launch(a) && !whole_launch(b) && (!plus || b >= 0)) {
             const long long rows = b >= 0 ? whole_round_rows(kTiles[a], M, Co) : M;
             return (b >= 0 && rows > 0 && rows < M) ? Plan{a, b, rows} : Plan{a, -1, M};
@@ -737,7 +888,7 @@ Plan choose_plan(long long M, int Co, int Kd, bool allow_stream = true)
         if (e.M == M && e.Co == Co && e.Kd == Kd) {
             const int a = tile_index(e.main, strlen(e.main)), b = e.tail[0] ? tile_index(e.tail, strlen(e.tail)) : -1;
             if (a < 0 || whole_launch(b) || (whole_launch(a) && !allow_stream)) break;
-            if (whole_launch(a)) return Plan{a, -1, M};
+            if (whole_launch(a)) return Plan{a == WINDOW_TILE && masked ? MASKED_WINDOW_TILE : a, -1, M};
             const long long rows = b >= 0 ? whole_round_rows(kTiles[a], M, Co) : M;
             return (b >= 0 && rows > 0 && rows < M) ? Plan{a, b, rows} : Plan{a, -1, M};
         }
@@ -769,9 +920,9 @@ int choose_tile(long long M, int Co, int Kd) { return choose_plan(M, Co, Kd, fal
 // the plan for one launch site: the streaming or the window kernel only where it can run the problem
 Plan plan_for(const IgemmParams &p, long long M, int Co, int Kd, bool tiles_only = false)
 {
-    const Plan pl = choose_plan(M, Co, Kd, !tiles_only);
+    const Plan pl = choose_plan(M, Co, Kd, !tiles_only, p.mask != nullptr);
     if (pl.main == STREAM_TILE && !stream_applicable(p)) return choose_plan(M, Co, Kd, false);
-    if (pl.main == WINDOW_TILE && !window_applicable(p)) return choose_plan(M, Co, Kd, false);
+    if ((pl.main == WINDOW_TILE || pl.main == MASKED_WINDOW_TILE) && !window_applicable(p)) return choose_plan(M, Co, Kd, false);
     return pl;
 }
 
@@ -779,7 +930,7 @@ Plan plan_for(const IgemmParams &p, long long M, int Co, int Kd, bool tiles_only
 int launch_plan(const Plan &pl, const IgemmParams &p, hipStream_t st, bool bt = false)
 {
     if (pl.main == STREAM_TILE) return stream_launch(p, st);
-    if (pl.main == WINDOW_TILE) return window_launch(p, st);
+    if (pl.main == WINDOW_TILE || pl.main == MASKED_WINDOW_TILE) return window_launch(p, st);
     if (pl.tail < 0) return launch_choice(pl.main, p, st, bt);
     const int rc = launch_choice(pl.main, p, st, bt, 0, pl.rows_main);
     if (rc != MXC_OK) return rc;
@@ -792,6 +943,7 @@ const char *plan_name(const Plan &pl)
     static thread_local char name[96];
     if (pl.main == STREAM_TILE) return kStreamName;
     if (pl.main == WINDOW_TILE) return kWindowName;
+    if (pl.main == MASKED_WINDOW_TILE) return kMaskedWindowName;
     if (pl.tail < 0) return kTiles[pl.main].name;
     snprintf(name, sizeof(name), "%s+%s", kTiles[pl.main].name, kTiles[pl.tail].name);
     return name;
@@ -805,27 +957,27 @@ bool igemm_dims_ok(long long in_elems, long long wm_elems, long long M, int Hi, 
            Wi + span <= 8192 && taps <= MAX_TAPS;
 }
 
-// dx[n][h_first + stride*a][v_first + stride*b][:] = 0 for the Mh x Mw pixels of one residue class;
-// one thread per cw consecutive channels (cw = 8: one 16-byte store).
-__global__ __launch_bounds__(256) void zero_phase_kernel(bf16_t *__restrict__ dx, long long n_thr, int H, int W, int C, int cw,
-                                                         int stride, int h_first, int v_first, int Mh, int Mw)
+// dx of the residue classes no tap reaches (a 1x1 filter at stride 2 leaves three of four): zeros.  One workgroup per image
+// row; `zero_h` / `zero_w`: bit (coordinate + pad) % stride of the rows / columns without a tap.  Kept out of the launch
+// above: interleaved with the matrix work the same stores ran at a third of the rate they reach alone (1x1 stride-2
+// 256->512 at 56x56, batch 256: 308 MB).
+template <int V>      // channels per store: 8 (16 bytes) or 1
+__global__ __launch_bounds__(256) void zero_classes_kernel(bf16_t *__restrict__ dx, int H, int W, int C, int stride, int pad, unsigned zero_h,
+                                                           unsigned zero_w)
 {
-    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= n_thr) return;
-    const int per_pix = C / cw;
-    const int ch = (int)(gid % per_pix) * cw;
-    long long t = gid / per_pix;
-    const int b = (int)(t % Mw); t /= Mw;
-    const int a = (int)(t % Mh);
-    const long long n = t / Mh;
-    bf16_t *d = dx + ((n * H + (h_first + stride * a)) * W + (v_first + stride * b)) * C + ch;
-    if (cw == 8) *reinterpret_cast<uint4 *>(d) = make_uint4(0, 0, 0, 0);
-    else *d = 0;
+    const int h = blockIdx.x % H, per_pix = C / V;
+    const bool whole = (zero_h >> ((h + pad) % stride)) & 1;
+    if (!whole && zero_w == 0) return;
+    bf16_t *row = dx + (size_t)blockIdx.x * W * C;
+    for (int i = threadIdx.x; i < W * per_pix; i += 256) {
+        const unsigned w = (unsigned)i / (unsigned)per_pix;
+        if (whole || ((zero_w >> ((w + pad) % stride)) & 1)) {
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+            if constexpr (V == 8) __builtin_nontemporal_store(u32x4{0, 0, 0, 0}, reinterpret_cast<u32x4 *>(row) + i);
+            else row[i] = 0;
+        }
+    }
 }
-
-}  // namespace
-
-namespace {
 
 // How many ways to split the reduction of a GEMM whose tiles would leave most of the chip idle
 // (FullyConnected-shaped and small-batch problems): enough workgroups to fill the slots, at least 8
@@ -1020,51 +1172,87 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
                    const char **variant, const PostOp &post, void *split_ws)
 {
     const bool bt = bwd_data_reads_filter_in_place(s);
-    const void *w = w_in_place;
+    IgemmParams p{};
+    p.in = (const bf16_t *)dy; p.out = (bf16_t *)dx;
+    p.mask = (const bf16_t *)post.mask;
+    p.N = s.N; p.Hi = s.P; p.Wi = s.Q; p.Ci = s.K; p.pix = s.K; p.Co = s.C; p.Cw = real_c(s);
+    p.tstep_h = -1; p.tstep_w = -1;
+    p.in_mul_h = 1; p.in_mul_w = 1;
+    p.Ho = s.H; p.Wo = s.W; p.out_mul_h = s.stride; p.out_mul_w = s.stride;
+    if (s.stride == 1) {
+        // one class: rows h = hh - pad of hh = pad, pad + 1, ...
+        p.wm = bt ? (const bf16_t *)w_in_place : (const bf16_t *)wt;
+        p.bt_w_bytes = (unsigned)((long long)s.K * s.C * 2);
+        p.TR = s.R; p.TS = s.S; p.Mh = s.H; p.Mw = s.W; p.in_off_h = s.pad; p.in_off_w = s.pad;
+        const long long M = (long long)s.N * s.H * s.W;
+        const int Kd = s.R * s.S * s.K;
+        const int sp = (split_ws != nullptr && s.C % 8 == 0) ? split_count(M, s.C, Kd) : 1;
+        Plan pl = plan_for(p, M, s.C, Kd, bt || sp > 1);
+        if (bt && !has_bt(pl.tail)) pl = Plan{pl.main, -1, 0};
+        *variant = plan_name(pl);
+        if (sp > 1) return launch_split(pl.main, p, M, sp, split_ws, dx, post, st, variant, bt);
+        return launch_plan(pl, p, st, bt);
+    }
+    IgemmClasses q{};
+    bool zeros = false;
     size_t wt_off = 0;
-    Plan pl{0, -1, 0};
+    long long rows = 0, area = 0;          // GEMM rows with taps, and their taps
     for (int ph = 0; ph < s.stride; ++ph) {
         for (int pw = 0; pw < s.stride; ++pw) {
-            const int TR = ph < s.R ? (s.R - ph + s.stride - 1) / s.stride : 0;
-            const int TS = pw < s.S ? (s.S - pw + s.stride - 1) / s.stride : 0;
+            IgemmClass c{};
+            c.TR = ph < s.R ? (s.R - ph + s.stride - 1) / s.stride : 0;
+            c.TS = pw < s.S ? (s.S - pw + s.stride - 1) / s.stride : 0;
             // output rows h = ph - pad + stride*hh >= 0, h < H
-            const int hh0 = ph >= s.pad ? 0 : (s.pad - ph + s.stride - 1) / s.stride;
-            const int vv0 = pw >= s.pad ? 0 : (s.pad - pw + s.stride - 1) / s.stride;
-            const int h_first = ph - s.pad + s.stride * hh0, v_first = pw - s.pad + s.stride * vv0;
-            const int Mh = h_first < s.H ? (s.H - 1 - h_first) / s.stride + 1 : 0;
-            const int Mw = v_first < s.W ? (s.W - 1 - v_first) / s.stride + 1 : 0;
-            IgemmParams p{};
-            p.in = (const bf16_t *)dy; p.wm = bt ? (const bf16_t *)w : (const bf16_t *)wt + wt_off; p.out = (bf16_t *)dx;
-            p.mask = (const bf16_t *)post.mask;
-            p.bt_w_bytes = (unsigned)((long long)s.K * s.C * 2);
-            p.N = s.N; p.Hi = s.P; p.Wi = s.Q; p.Ci = s.K; p.pix = s.K; p.Co = s.C; p.Cw = real_c(s);
-            p.TR = TR; p.TS = TS; p.tstep_h = -1; p.tstep_w = -1;
-            p.Mh = Mh; p.Mw = Mw;
-            p.in_mul_h = 1; p.in_mul_w = 1; p.in_off_h = hh0; p.in_off_w = vv0;
-            p.Ho = s.H; p.Wo = s.W; p.out_mul_h = s.stride; p.out_mul_w = s.stride; p.out_off_h = h_first; p.out_off_w = v_first;
-            wt_off += (size_t)s.C * TR * TS * s.K;
-            if (Mh <= 0 || Mw <= 0) continue;
-            if (TR * TS == 0) {
-                // no tap reaches this residue class (stride larger than the filter): its pixels are zero
-                const int cw = (s.C % 8 == 0) ? 8 : 1;   // elements written per thread
-                const long long n_thr = (long long)s.N * Mh * Mw * (s.C / cw);
-                if ((n_thr + 255) / 256 > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
-                hipLaunchKernelGGL(zero_phase_kernel, dim3((unsigned)((n_thr + 255) / 256)), dim3(256), 0, st, (bf16_t *)dx, n_thr,
-                                   s.H, s.W, s.C, cw, s.stride, h_first, v_first, Mh, Mw);
-                if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
+            c.in_off_h = ph >= s.pad ? 0 : (s.pad - ph + s.stride - 1) / s.stride;
+            c.in_off_w = pw >= s.pad ? 0 : (s.pad - pw + s.stride - 1) / s.stride;
+            c.out_off_h = ph - s.pad + s.stride * c.in_off_h; c.out_off_w = pw - s.pad + s.stride * c.in_off_w;
+            c.Mh = c.out_off_h < s.H ? (s.H - 1 - c.out_off_h) / s.stride + 1 : 0;
+            c.Mw = c.out_off_w < s.W ? (s.W - 1 - c.out_off_w) / s.stride + 1 : 0;
+            c.wm = (const bf16_t *)wt + wt_off;
+            c.wm_bytes = (unsigned)((long long)p.Cw * c.TR * c.TS * s.K * 2);
+            wt_off += (size_t)s.C * c.TR * c.TS * s.K;
+            if (c.Mh <= 0 || c.Mw <= 0) continue;
+            if (c.TR * c.TS == 0) { zeros = true; continue; }
+            IgemmParams one = p;
+            one.wm = c.wm; one.TR = c.TR; one.TS = c.TS; one.Mh = c.Mh; one.Mw = c.Mw;
+            one.in_off_h = c.in_off_h; one.in_off_w = c.in_off_w; one.out_off_h = c.out_off_h; one.out_off_w = c.out_off_w;
+            const Plan pl = plan_for(one, (long long)s.N * c.Mh * c.Mw, s.C, c.TR * c.TS * s.K);
+            if (pl.main == STREAM_TILE || (s.R == 1 && s.S == 1)) {
+                // one class alone (1x1), or one that the plan gives to the streaming kernel (short reductions): a launch of its own
+                const int rc = launch_plan(pl, one, st);
+                if (rc != MXC_OK) return rc;
+                *variant = plan_name(pl);
                 continue;
             }
-            const int sp = (split_ws != nullptr && s.stride == 1 && s.C % 8 == 0)
-                               ? split_count((long long)s.N * Mh * Mw, s.C, TR * TS * s.K) : 1;
-            pl = plan_for(p, (long long)s.N * Mh * Mw, s.C, TR * TS * s.K, bt || sp > 1);
-            if (bt && !has_bt(pl.tail)) pl = Plan{pl.main, -1, 0};
-            if (sp > 1) return launch_split(pl.main, p, (long long)s.N * Mh * Mw, sp, split_ws, dx, post, st, variant, bt);
-            const int rc = launch_plan(pl, p, st, bt);
-            if (rc != MXC_OK) return rc;
+            rows += (long long)s.N * c.Mh * c.Mw;
+            area += (long long)s.N * c.Mh * c.Mw * c.TR * c.TS;
+            // most taps first: the longest reductions start first
+            int at = q.n++;
+            for (; at > 0 && q.c[at - 1].TR * q.c[at - 1].TS < c.TR * c.TS; --at) q.c[at] = q.c[at - 1];
+            q.c[at] = c;
         }
     }
-    *variant = plan_name(pl);
-    return MXC_OK;
+    if (zeros) {
+        unsigned zh = 0, zw = 0;
+        for (int c = 0; c < s.stride; ++c) {
+            zh |= c >= s.R ? 1u << c : 0u;
+            zw |= c >= s.S ? 1u << c : 0u;
+        }
+        if ((long long)s.N * s.H > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
+        const dim3 grid((unsigned)(s.N * s.H)), block(256);
+        if (s.C % 8 == 0) hipLaunchKernelGGL(zero_classes_kernel<8>, grid, block, 0, st, (bf16_t *)dx, s.H, s.W, s.C, s.stride, s.pad, zh, zw);
+        else hipLaunchKernelGGL(zero_classes_kernel<1>, grid, block, 0, st, (bf16_t *)dx, s.H, s.W, s.C, s.stride, s.pad, zh, zw);
+        if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
+    }
+    if (q.n == 0) return MXC_OK;
+    p.in_bytes = (unsigned)((long long)s.N * s.P * s.Q * s.K * 2);
+    const long long out_bytes = (long long)s.N * s.H * s.W * s.C * 2;
+    p.out_bytes = out_bytes < 0x7FFF0000ll ? (unsigned)out_bytes : 0u;
+    p.nt_out = out_bytes >= (128ll << 20) ? 1 : 0;
+    q.p = p;
+    const int tile = choose_tile(rows, s.C, (int)(area / rows * s.K));
+    *variant = kTiles[tile].name;
+    return launch_classes_choice(tile, q, st);
 }
 
 // ---- backward-data for small C (first layers) ------------------------------------------------

@@ -57,7 +57,8 @@ struct StreamParams {
 
 // NC compute waves (row tile BM = 32*NC), NL loader waves, column tile BN (32, 64 or 128), NS ring stages.
 // Dynamic LDS: [filter BN x KT*64][ring NS x BM x 64][staging NC x 32 x min(BN,64)][tap table][bias BN].
-template <int NC, int NL, int BN, int NS>
+// MASK: results are zeroed where p.mask <= 0 (a variant of its own: its registers would spill the plain one).
+template <int NC, int NL, int BN, int NS, bool MASK>
 __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamParams sp)
 {
     const IgemmParams &p = sp.g;
@@ -307,7 +308,8 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
     // Stores of the common case (output pixel index == GEMM row, no mask): one buffer store per 8 staged rows;
     // rows past the end of this workgroup's range and columns past Co get an offset the resource rejects.
     const out_rsrc_t rs_out = make_out_rsrc(p.out, sp.out_bytes);
-    const bool fast_store = p.linear_out && p.mask == nullptr;
+    const out_rsrc_t rs_mask = make_out_rsrc(const_cast<bf16_t *>(p.mask), MASK ? sp.out_bytes : 0u);
+    const bool fast_store = p.linear_out;
     constexpr int RPI = 64 / CPR;                   // staged rows per store instruction
     const int st_r = lane / CPR, st_c = lane % CPR;
     const unsigned st_lane_off = (unsigned)((st_r * p.Co + n0 + st_c * 8) * 2);
@@ -318,7 +320,15 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
     reset_acc();
     int slot = 0, kt = 0, tile = 0;
     if (total > 0) fetch_b(0, 0);
+    constexpr int NJC = (BN + 63) / 64, NST = 32 / RPI;
+    // byte offset of store k of staging pass jc of the tile whose rows of this wave begin at m0; rows past the end of the
+    // range and columns past Co: an offset the resource rejects
+    auto store_off = [&](int m0, int jc, int k) __attribute__((always_inline)) {
+        const bool ok = n0 + jc * 64 + st_c * 8 < p.Co && st_r + k * RPI < wg_hi - m0;
+        return ok ? st_lane_off + (unsigned)m0 * (unsigned)(p.Co * 2) + (unsigned)(jc * 128 + k * RPI * p.Co * 2) : OOB;   // below 2^32: the output is below 2^31
+    };
     for (int g = 0; g < total; ++g) {
+        [[maybe_unused]] uint4 mk[NJC][NST];
         const bf16_t *a_st = a_base + slot * STG_A;
         bf16x8 a[KS];
 #pragma unroll
@@ -330,6 +340,12 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
             for (int h = 0; h < HB; ++h)
 #pragma unroll
                 for (int j = 0; j < NI; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bq[h][j], a[h0 + h], acc[j], 0, 0, 0);
+        }
+        if (MASK && fast_store && kt == KT - 1) {          // the tile is complete: its mask lands under the barrier and the staging
+#pragma unroll
+            for (int jc = 0; jc < NJC; ++jc)
+#pragma unroll
+                for (int k = 0; k < NST; ++k) mk[jc][k] = buffer_load16(rs_mask, store_off(wg_lo + tile * BM + wave * 32, jc, k));
         }
         // every activation fragment of this slot has been consumed by an MFMA, so its read has returned: the
         // slot can be handed back.  The filter fragments of the next stage are requested first.
@@ -343,22 +359,19 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
         const int m0 = wg_lo + tile * BM + wave * 32;
         ++tile;
 #pragma unroll
-        for (int jc = 0; jc < (BN + 63) / 64; ++jc) {
+        for (int jc = 0; jc < NJC; ++jc) {
             if (p.relu) stage_out(jc, std::true_type{});
             else stage_out(jc, std::false_type{});
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             if (fast_store) {
-                const bool col_ok = n0 + jc * 64 + st_c * 8 < p.Co;
-                const unsigned tile_off = (unsigned)m0 * (unsigned)(p.Co * 2) + (unsigned)(jc * 128);   // below 2^32: the output is below 2^31
-                const int rows_left = wg_hi - m0;
 #pragma unroll
-                for (int k = 0; k < 32 / RPI; ++k) {
-                    const uint4 v = swap_halves(*reinterpret_cast<const uint4 *>(st_src + k * RPI * EW), ((st_r + k * RPI) >> 3) & 1);
-                    const bool ok = col_ok && st_r + k * RPI < rows_left;
-                    if (sp.nt & 1) buffer_store16_nt(rs_out, ok ? st_lane_off + tile_off + (unsigned)(k * RPI * p.Co * 2) : OOB, v);
-                    else buffer_store16(rs_out, ok ? st_lane_off + tile_off + (unsigned)(k * RPI * p.Co * 2) : OOB, v);
+                for (int k = 0; k < NST; ++k) {
+                    uint4 v = swap_halves(*reinterpret_cast<const uint4 *>(st_src + k * RPI * EW), ((st_r + k * RPI) >> 3) & 1);
+                    if constexpr (MASK) v = mask_bf16x8(v, mk[jc][k]);
+                    if (sp.nt & 1) buffer_store16_nt(rs_out, store_off(m0, jc, k), v);
+                    else buffer_store16(rs_out, store_off(m0, jc, k), v);
                 }
             } else
 #pragma unroll
@@ -375,9 +388,9 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
                         pix = ((long long)n * p.Ho + ((int)a * p.out_mul_h + p.out_off_h)) * p.Wo + ((int)b * p.out_mul_w + p.out_off_w);
                     }
                     const long long off = pix * p.Co + co;
-                    if (p.mask != nullptr) {
+                    if constexpr (MASK) {
                         const uint4 mk = *reinterpret_cast<const uint4 *>(p.mask + off);
-                        v = make_uint4(mask_bf16x2(v.x, mk.x), mask_bf16x2(v.y, mk.y), mask_bf16x2(v.z, mk.z), mask_bf16x2(v.w, mk.w));
+                        v = mask_bf16x8(v, mk);
                     }
                     *reinterpret_cast<uint4 *>(p.out + off) = v;
                 }
@@ -422,12 +435,12 @@ StreamConfig stream_config(const IgemmParams &p)
     return StreamConfig{0, 0, 0, 0, false};
 }
 
-template <int NC, int NL, int BN, int NS>
-int launch_stream(StreamParams sp, int lds, hipStream_t st)
+template <int NC, int NL, int BN, int NS, bool MASK>
+int launch_stream_m(StreamParams sp, int lds, hipStream_t st)
 {
     static bool attr_set = false;      // raising the dynamic-LDS limit is idempotent; racing threads set the same value
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&stream_kernel<NC, NL, BN, NS>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&stream_kernel<NC, NL, BN, NS, MASK>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 160 * 1024) != hipSuccess)
             return MXC_ERR_LAUNCH;
         attr_set = true;
@@ -459,8 +472,14 @@ int launch_stream(StreamParams sp, int lds, hipStream_t st)
     sp.d_n = BM / (p.Mh * p.Mw);
     sp.d_a = BM % (p.Mh * p.Mw) / p.Mw;
     sp.d_b = BM % p.Mw;
-    hipLaunchKernelGGL((stream_kernel<NC, NL, BN, NS>), dim3((unsigned)(8 * sp.per_xcd)), dim3(64 * (NC + NL)), (size_t)lds, st, sp);
+    hipLaunchKernelGGL((stream_kernel<NC, NL, BN, NS, MASK>), dim3((unsigned)(8 * sp.per_xcd)), dim3(64 * (NC + NL)), (size_t)lds, st, sp);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+}
+
+template <int NC, int NL, int BN, int NS>
+int launch_stream(const StreamParams &sp, int lds, hipStream_t st)
+{
+    return sp.g.mask != nullptr ? launch_stream_m<NC, NL, BN, NS, true>(sp, lds, st) : launch_stream_m<NC, NL, BN, NS, false>(sp, lds, st);
 }
 
 template <int NC, int NL, int NS>

@@ -63,7 +63,8 @@ struct WindowParams {
 };
 
 // Column tile BN = 32*NI; KSN = Ci/16 k-steps per tap.  Dynamic LDS: [filter T x BN x 64][window 0][window 1][bias BN][tap shifts].
-template <int NI, int KSN>
+// MASK: results are zeroed where p.mask <= 0 (a variant of its own: its registers would spill the plain one)
+template <int NI, int KSN, bool MASK>
 __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
 {
     const IgemmParams &p = wp.g;
@@ -212,6 +213,7 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
     }
     const bool st_col_ok = n0 + st_c * 8 < p.Co;
     const out_rsrc_t rs_out = make_out_rsrc(p.out, wp.out_bytes);
+    [[maybe_unused]] const out_rsrc_t rs_mask = make_out_rsrc(const_cast<bf16_t *>(p.mask), p.mask != nullptr ? wp.out_bytes : 0u);
 
     f32x16 acc[NI];
     auto reset_acc = [&]() __attribute__((always_inline)) {
@@ -261,13 +263,29 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
             mma(f1);
         }
         if (t < T) mma(f0);
-        wg_barrier();                               // B(k): every wave is done reading window k, which becomes the staging area
+        // where this patch's results go (rows outside its valid part get an offset the resource rejects: ty <= th-1 and
+        // tx <= tw-1, tested on both halves at once), and the mask there, which lands under the barrier and the staging
+        unsigned off[32 / RPI];
+        [[maybe_unused]] uint4 mk[32 / RPI];
         {
             const int n = pos.n, y0 = pos.py * wp.TH, x0 = pos.px * wp.TW;
             next_patch(pos);
             const int th = min(wp.TH, p.Mh - y0), tw = min(wp.TW, p.Mw - x0);
             const int lim = (th - 1) | ((tw - 1) << 16);
             const unsigned tile_off = (unsigned)(((n * p.Ho + y0) * p.Wo + x0) * p.Co * 2);   // below 2^31: the output is
+#pragma unroll
+            for (int kk = 0; kk < 32 / RPI; ++kk) {
+                const s16x2 d = __builtin_bit_cast(s16x2, lim) - __builtin_bit_cast(s16x2, st_yx[kk]);
+                const bool ok = st_col_ok && (__builtin_bit_cast(int, d) & (int)0x80008000) == 0;
+                off[kk] = ok ? tile_off + st_off[kk] : OOB;
+            }
+            if constexpr (MASK) {
+#pragma unroll
+                for (int kk = 0; kk < 32 / RPI; ++kk) mk[kk] = buffer_load16(rs_mask, off[kk]);
+            }
+        }
+        wg_barrier();                               // B(k): every wave is done reading window k, which becomes the staging area
+        {
             bf16_t *stg = win0 + (k & 1) * win_elems + wave * 32 * EW;
 #pragma unroll
             for (int j = 0; j < NI; ++j)
@@ -290,12 +308,9 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
                 const int r = st_r + kk * RPI;
                 uint4 v = *reinterpret_cast<const uint4 *>(stg + r * EW + stg_chunk(r, st_c));
                 if ((r >> 3) & 1) v = make_uint4(v.z, v.w, v.x, v.y);
-                // inside the patch's valid part: ty <= th-1 and tx <= tw-1, tested on both halves at once
-                const s16x2 d = __builtin_bit_cast(s16x2, lim) - __builtin_bit_cast(s16x2, st_yx[kk]);
-                const bool ok = st_col_ok && (__builtin_bit_cast(int, d) & (int)0x80008000) == 0;
-                const unsigned off = ok ? tile_off + st_off[kk] : OOB;
-                if (wp.nt) buffer_store16_nt(rs_out, off, v);
-                else buffer_store16(rs_out, off, v);
+                if constexpr (MASK) v = mask_bf16x8(v, mk[kk]);
+                if (wp.nt) buffer_store16_nt(rs_out, off[kk], v);
+                else buffer_store16(rs_out, off[kk], v);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -348,18 +363,24 @@ WindowConfig window_config(const IgemmParams &p)
     return best;
 }
 
-template <int NI, int KSN>
-int launch_window(WindowParams &wp, int lds, hipStream_t st)
+template <int NI, int KSN, bool MASK>
+int launch_window_m(WindowParams &wp, int lds, hipStream_t st)
 {
     static bool attr_set = false;
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&window_kernel<NI, KSN>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&window_kernel<NI, KSN, MASK>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 160 * 1024) != hipSuccess)
             return MXC_ERR_LAUNCH;
         attr_set = true;
     }
-    hipLaunchKernelGGL((window_kernel<NI, KSN>), dim3((unsigned)(8 * wp.per_xcd)), dim3(64 * NW), (size_t)lds, st, wp);
+    hipLaunchKernelGGL((window_kernel<NI, KSN, MASK>), dim3((unsigned)(8 * wp.per_xcd)), dim3(64 * NW), (size_t)lds, st, wp);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+}
+
+template <int NI, int KSN>
+int launch_window(WindowParams &wp, int lds, hipStream_t st)
+{
+    return wp.g.mask != nullptr ? launch_window_m<NI, KSN, true>(wp, lds, st) : launch_window_m<NI, KSN, false>(wp, lds, st);
 }
 
 template <int NI>
@@ -377,7 +398,7 @@ int launch_window_ks(WindowParams &wp, int lds, hipStream_t st)
 
 bool window_applicable(const IgemmParams &p)
 {
-    if (p.splits > 1 || p.partial != nullptr || p.mask != nullptr || p.f32_out) return false;
+    if (p.splits > 1 || p.partial != nullptr || p.f32_out) return false;
     const int T = p.TR * p.TS;
     if (T < 2 || T > MAX_TAPS) return false;
     if (p.in_mul_h != 1 || p.in_mul_w != 1 || (p.tstep_h != 1 && p.tstep_h != -1) || (p.tstep_w != 1 && p.tstep_w != -1)) return false;
