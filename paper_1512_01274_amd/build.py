@@ -1,4 +1,5 @@
-"""Build paper_1512_01274_amd/libmxc.so (gfx950 HIP kernels + C ABI) with hipcc.
+"""Build paper_1512_01274_amd/libmxc.so (gfx950 HIP kernels + C ABI) with hipcc and _native.so (the Python binding's
+call path) with g++.
 
 Usage: python -m paper_1512_01274_amd.build   (cross-compiles without a GPU)
 """
@@ -11,6 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmxc.so")
+NATIVE = os.path.join(HERE, "_native.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed-fp32 VALU forms (v_pk_fma_f32 and its like) are kept off for every HIP file of this library.
@@ -25,28 +27,35 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
+def _run(cmd, verbose):
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed:\n{r.stdout}\n{r.stderr}")
+    if verbose and r.stderr.strip():
+        print(r.stderr, flush=True)
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
     os.makedirs(OBJ_DIR, exist_ok=True)
     srcs = sources()
     objs = [os.path.join(OBJ_DIR, os.path.basename(s)[:-4] + ".o") for s in srcs]
-
-    def compile_one(pair):
-        src, obj = pair
-        cmd = [HIPCC] + FLAGS + ["-c", src, "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
-        if verbose and r.stderr.strip():
-            print(r.stderr, flush=True)
-
-    with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(srcs)))) as ex:
-        list(ex.map(compile_one, zip(srcs, objs)))
-    cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    cmds = [[HIPCC] + FLAGS + ["-c", src, "-o", obj] for src, obj in zip(srcs, objs)]
+    inc = [f for p in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]] for f in ("-isystem", p)]
+    binding = os.path.join(OBJ_DIR, "binding.o")
+    cmds.append(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"] + inc +
+                ["-c", os.path.join(CSRC, "binding.cpp"), "-o", binding])
+    cmds.sort(key=lambda c: -os.path.getsize(c[c.index("-c") + 1]))        # the longest compilations first
+    with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(cmds)))) as ex:
+        list(ex.map(lambda c: _run(c, verbose), cmds))
+    _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,libmxc.so"] + objs + ["-o", LIB], verbose)
+    # found beside the extension at run time, wherever the tree lies
+    _run(["g++", "-shared", binding, "-L" + HERE, "-lmxc", "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python",
+          "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN", "-o", NATIVE], verbose)
     return LIB
 
 

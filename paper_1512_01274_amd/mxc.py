@@ -1,10 +1,10 @@
-"""ctypes binding over libmxc.so: argument marshalling only.
+"""Binding over libmxc.so: argument marshalling only.
 
 Function names and argument order mirror include/mxc.h.  Tensors are torch
 tensors on the GPU (torch is used for device memory and streams, nothing else);
 every step of the computation runs in the library's HIP kernels.  There is no
-CPU or PyTorch fallback: if the library cannot be loaded, importing this module
-raises.
+CPU or PyTorch fallback: if the library or the extension module that holds the
+calls cannot be loaded, importing this module raises.
 """
 import ctypes
 import os
@@ -146,173 +146,40 @@ def _stream(stream):
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
-def mxc_conv2d_workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype, layout) -> int:
-    out = _SZ(0)
-    rc = _lib.mxc_conv2d_workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype, layout, ctypes.byref(out))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-    return int(out.value)
+# The entry points, with these arguments (workspace and stream may be left out; tensors may be None where the header
+# allows it).  They are built-in functions of the extension module (csrc/binding.cpp) and raise MxcError on a status.
+#
+#   mxc_conv2d_workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype, layout) -> int
+#   mxc_conv2d_fwd(N, C, H, W, K, R, S, stride, pad, dtype, layout, x, w, y, workspace=None, stream=None)
+#   mxc_conv2d_bwd_data(N .. layout, dy, w, dx, workspace=None, stream=None)
+#   mxc_conv2d_bwd_weight(N .. layout, x, dy, dw, workspace=None, stream=None)          and ..._bwd_weight_bf16
+#   mxc_conv2d_bwd_weight_static(N .. layout, x, dy, dw, stream=None)
+#   mxc_conv2d_fwd_bias_act(N .. layout, x, w, bias, relu, y, workspace=None, stream=None)
+#   mxc_conv2d_bwd_data_relu(N .. layout, dy, w, x, dx, workspace=None, stream=None)
+#   mxc_conv2d_bwd_data_prepare_filter(N .. layout, w, w_prepared, stream=None)
+#   mxc_conv2d_bwd_data_prepared(N .. layout, dy, w_prepared, x_mask, dx, workspace=None, stream=None)
+#   mxc_conv2d_fwd_transform(N .. layout, x, w, bias, relu, y, workspace=None, stream=None)
+#   mxc_conv2d_prepare_input(N .. layout, x, x_prepared, stream=None)
+#   mxc_conv2d_fwd_prepared_input(N .. layout, x_prepared, w, bias, relu, y, workspace=None, stream=None)
+#   mxc_conv2d_bwd_weight_prepared_input(N .. layout, x_prepared, dy, dw, dw_dtype, workspace=None, stream=None)
+#   mxc_bias_grad(N, K, P, Q, dtype, layout, dy, db, workspace=None, stream=None)
+#   mxc_fc_fwd(N, C, K, dtype, x, w, bias, relu, y, workspace=None, stream=None)
+#   mxc_fc_bwd_data(N, C, K, dtype, dy, w, x_mask, dx, workspace=None, stream=None)
+#   mxc_fc_bwd_weight(N, C, K, dtype, x, dy, dw, workspace=None, stream=None)
+#   mxc_softmax_fwd(N, K, dtype, z, p, stream=None)
+#   mxc_softmax_xent_bwd(N, K, dtype, p, labels, scale, dz, stream=None)
+#   mxc_sgd_update(w, g, v, w_bf16, lr, momentum, wd, stream=None)      in place on w and v (v, w_bf16 may be None)
+#   mxc_layout_convert(n, c, h, w, dtype, src_layout, dst_layout, src, dst, stream=None)
+from paper_1512_01274_amd import _native  # noqa: E402
+from paper_1512_01274_amd._native import (  # noqa: E402,F401
+    mxc_bias_grad, mxc_conv2d_bwd_data, mxc_conv2d_bwd_data_prepare_filter, mxc_conv2d_bwd_data_prepared,
+    mxc_conv2d_bwd_data_relu, mxc_conv2d_bwd_weight, mxc_conv2d_bwd_weight_bf16, mxc_conv2d_bwd_weight_prepared_input,
+    mxc_conv2d_bwd_weight_static, mxc_conv2d_fwd, mxc_conv2d_fwd_bias_act, mxc_conv2d_fwd_prepared_input,
+    mxc_conv2d_fwd_transform, mxc_conv2d_prepare_input, mxc_conv2d_workspace_bytes, mxc_fc_bwd_data, mxc_fc_bwd_weight,
+    mxc_fc_fwd, mxc_layout_convert, mxc_sgd_update, mxc_softmax_fwd, mxc_softmax_xent_bwd)
 
-
-def _call(fn, dims, dtype, layout, a, b, out, workspace, stream):
-    ws_ptr = _ptr(workspace) if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = fn(*dims, dtype, layout, _ptr(a), _ptr(b), _ptr(out), ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_conv2d_fwd(N, C, H, W, K, R, S, stride, pad, dtype, layout, x, w, y, workspace=None, stream=None):
-    _call(_lib.mxc_conv2d_fwd, (N, C, H, W, K, R, S, stride, pad), dtype, layout, x, w, y, workspace, stream)
-
-
-def mxc_conv2d_bwd_data(N, C, H, W, K, R, S, stride, pad, dtype, layout, dy, w, dx, workspace=None, stream=None):
-    _call(_lib.mxc_conv2d_bwd_data, (N, C, H, W, K, R, S, stride, pad), dtype, layout, dy, w, dx, workspace, stream)
-
-
-def mxc_conv2d_bwd_weight(N, C, H, W, K, R, S, stride, pad, dtype, layout, x, dy, dw, workspace=None, stream=None):
-    _call(_lib.mxc_conv2d_bwd_weight, (N, C, H, W, K, R, S, stride, pad), dtype, layout, x, dy, dw, workspace, stream)
-
-
-def mxc_conv2d_bwd_weight_bf16(N, C, H, W, K, R, S, stride, pad, dtype, layout, x, dy, dw, workspace=None, stream=None):
-    _call(_lib.mxc_conv2d_bwd_weight_bf16, (N, C, H, W, K, R, S, stride, pad), dtype, layout, x, dy, dw, workspace, stream)
-
-
-def mxc_conv2d_bwd_weight_static(N, C, H, W, K, R, S, stride, pad, dtype, layout, x, dy, dw, stream=None):
-    rc = _lib.mxc_conv2d_bwd_weight_static(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(x), _ptr(dy), _ptr(dw),
-                                           _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def _ws(workspace):
-    if workspace is None:
-        return None, 0
-    return _ptr(workspace), workspace.numel() * workspace.element_size()
-
-
-def mxc_conv2d_fwd_bias_act(N, C, H, W, K, R, S, stride, pad, dtype, layout, x, w, bias, relu, y, workspace=None, stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_conv2d_fwd_bias_act(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(x), _ptr(w), _ptr(bias), int(relu),
-                                      _ptr(y), ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_conv2d_bwd_data_relu(N, C, H, W, K, R, S, stride, pad, dtype, layout, dy, w, x, dx, workspace=None, stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_conv2d_bwd_data_relu(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(dy), _ptr(w), _ptr(x), _ptr(dx),
-                                       ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_conv2d_bwd_data_prepare_filter(N, C, H, W, K, R, S, stride, pad, dtype, layout, w, w_prepared, stream=None):
-    rc = _lib.mxc_conv2d_bwd_data_prepare_filter(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(w), _ptr(w_prepared),
-                                                 w_prepared.numel() * w_prepared.element_size(), _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_conv2d_bwd_data_prepared(N, C, H, W, K, R, S, stride, pad, dtype, layout, dy, w_prepared, x_mask, dx, workspace=None,
-                                 stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_conv2d_bwd_data_prepared(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(dy), _ptr(w_prepared),
-                                           w_prepared.numel() * w_prepared.element_size(), _ptr(x_mask), _ptr(dx), ws_ptr, ws_bytes,
-                                           _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_conv2d_fwd_transform(N, C, H, W, K, R, S, stride, pad, dtype, layout, x, w, bias, relu, y, workspace=None, stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_conv2d_fwd_transform(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(x), _ptr(w), _ptr(bias), int(relu),
-                                       _ptr(y), ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def _nbytes(t):
-    return 0 if t is None else t.numel() * t.element_size()
-
-
-def mxc_conv2d_prepare_input(N, C, H, W, K, R, S, stride, pad, dtype, layout, x, x_prepared, stream=None):
-    rc = _lib.mxc_conv2d_prepare_input(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(x), _ptr(x_prepared),
-                                       _nbytes(x_prepared), _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_conv2d_fwd_prepared_input(N, C, H, W, K, R, S, stride, pad, dtype, layout, x_prepared, w, bias, relu, y, workspace=None,
-                                  stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_conv2d_fwd_prepared_input(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(x_prepared), _nbytes(x_prepared),
-                                            _ptr(w), _ptr(bias), int(relu), _ptr(y), ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_conv2d_bwd_weight_prepared_input(N, C, H, W, K, R, S, stride, pad, dtype, layout, x_prepared, dy, dw, dw_dtype,
-                                         workspace=None, stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_conv2d_bwd_weight_prepared_input(N, C, H, W, K, R, S, stride, pad, dtype, layout, _ptr(x_prepared),
-                                                   _nbytes(x_prepared), _ptr(dy), _ptr(dw), dw_dtype, ws_ptr, ws_bytes,
-                                                   _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_bias_grad(N, K, P, Q, dtype, layout, dy, db, workspace=None, stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_bias_grad(N, K, P, Q, dtype, layout, _ptr(dy), _ptr(db), ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_fc_fwd(N, C, K, dtype, x, w, bias, relu, y, workspace=None, stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_fc_fwd(N, C, K, dtype, _ptr(x), _ptr(w), _ptr(bias), int(relu), _ptr(y), ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_fc_bwd_data(N, C, K, dtype, dy, w, x_mask, dx, workspace=None, stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_fc_bwd_data(N, C, K, dtype, _ptr(dy), _ptr(w), _ptr(x_mask), _ptr(dx), ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_fc_bwd_weight(N, C, K, dtype, x, dy, dw, workspace=None, stream=None):
-    ws_ptr, ws_bytes = _ws(workspace)
-    rc = _lib.mxc_fc_bwd_weight(N, C, K, dtype, _ptr(x), _ptr(dy), _ptr(dw), ws_ptr, ws_bytes, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_softmax_fwd(N, K, dtype, z, p, stream=None):
-    rc = _lib.mxc_softmax_fwd(N, K, dtype, _ptr(z), _ptr(p), _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_softmax_xent_bwd(N, K, dtype, p, labels, scale, dz, stream=None):
-    rc = _lib.mxc_softmax_xent_bwd(N, K, dtype, _ptr(p), _ptr(labels), scale, _ptr(dz), _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_sgd_update(w, g, v, w_bf16, lr, momentum, wd, stream=None):
-    """In-place update of the fp32 tensors w (and v, may be None); optional bf16 copy of the new w."""
-    rc = _lib.mxc_sgd_update(w.numel(), _ptr(w), _ptr(g), _ptr(v), _ptr(w_bf16), lr, momentum, wd, _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
-
-
-def mxc_layout_convert(n, c, h, w, dtype, src_layout, dst_layout, src, dst, stream=None):
-    rc = _lib.mxc_layout_convert(n, c, h, w, dtype, src_layout, dst_layout, _ptr(src), _ptr(dst), _stream(stream))
-    if rc != MXC_OK:
-        raise MxcError(rc)
+_native.set_hooks(MxcError, getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None),
+                  lambda: torch.cuda.current_stream().cuda_stream)
 
 
 def mxc_probe_mfma(workgroups, iters, out, stream=None) -> float:
