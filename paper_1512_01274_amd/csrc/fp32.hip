@@ -54,6 +54,33 @@ template <int I> using IC = std::integral_constant<int, I>;
 template <class F, int... I> __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) { (f(IC<I>{}), ...); }
 template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
+// n / d for 0 <= n < 2^31 as a multiplication: the compiler's division by a variable is some thirty instructions, and a
+// tile's setup has dozens of them (they were two thirds of a small layer's kernel time)
+struct FastDiv {
+    unsigned mul = 0, shift = 0;
+    int d = 1;
+    FastDiv() = default;
+    explicit FastDiv(int divisor) : d(divisor > 0 ? divisor : 1)
+    {
+        while (shift < 31 && (1u << shift) < (unsigned)d) ++shift;
+        mul = (unsigned)(((1ull << 32) * ((1ull << shift) - (unsigned)d)) / (unsigned)d + 1);
+    }
+    __device__ __forceinline__ int div(int n) const { return (int)((__umulhi(mul, (unsigned)n) + (unsigned)n) >> shift); }
+    __device__ __forceinline__ int mod(int n) const { return n - div(n) * d; }
+};
+
+// A stride residue class of backward-data; forward has one, the whole problem.
+struct F32Class {
+    int tile0;              // first row tile
+    int TR, TS;             // tap grid
+    int Mh, Mw;             // pixel grid of the rows
+    int off_h, off_w;       // gathered position of row (0, 0), tap 0
+    int ph, pw;             // first filter row / column
+    int h_first, v_first;   // output position of row (0, 0)
+    FastDiv mw, mh, t, ts;
+    int ts_magic;           // see small_div
+};
+
 struct F32Params {
     const float *a, *b;     // the two operands as the table above names them
     float *out;             // y, dx, dw or the first split's partial dw
@@ -62,8 +89,9 @@ struct F32Params {
     int M;                  // forward: N*P*Q; backward-weight: the reduction length N*P*Q
     int n_tiles, tiles, units;      // tiles: per split; units: tiles * splits
     int span;               // backward-weight: pixels per split (a multiple of 16 * Z)
-    int cls_tile0[MAX_CLASSES + 1];     // backward-data: first row tile of each residue class
+    F32Class cls[MAX_CLASSES];
     int n_cls;
+    FastDiv by_ntiles, by_tiles, by_ci, by_c, by_rs, by_s, by_pq, by_q, by_p;
     const float *bias;      // forward, or null
     int relu;
     const float *mask;      // backward-data, or null: the result is 0 where mask <= 0
@@ -71,7 +99,7 @@ struct F32Params {
 
 // floor(t / d) for 0 <= t <= 127, 1 <= d <= 127
 __device__ __forceinline__ int small_div(int t, int magic) { return (t * magic) >> 16; }
-__device__ __forceinline__ int small_magic(int d) { return (65536 + d - 1) / d; }
+inline int small_magic(int d) { return (65536 + d - 1) / d; }
 
 __device__ __forceinline__ int pack_hw(int h, int w) { return (h & 0xFFFF) | (w << 16); }
 // nonzero where (h, w) + (dh, dw) leaves the image; all packed as two 16-bit integers
@@ -114,34 +142,25 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
     const int per_xcd = (p.units + 7) / 8;
     const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (unit >= p.units) return;
-    const int tile = unit % p.tiles, split = unit / p.tiles;
+    const int split = p.by_tiles.div(unit), tile = unit - split * p.tiles;
     const ConvShape &s = p.s;
     const int RS = s.R * s.S;
-    int mt = tile / p.n_tiles;
-    const int n0 = (tile % p.n_tiles) * BN;
+    int mt = p.by_ntiles.div(tile);
+    const int n0 = (tile - mt * p.n_tiles) * BN;
 
     // ---- geometry of this unit ---------------------------------------------------------------------------
-    int cls = 0;
+    int ci = 0;
     if constexpr (OP == OP_BWD) {
-        while (cls + 1 < p.n_cls && mt >= p.cls_tile0[cls + 1]) ++cls;
-        mt -= p.cls_tile0[cls];
+        while (ci + 1 < p.n_cls && mt >= p.cls[ci + 1].tile0) ++ci;
+        mt -= p.cls[ci].tile0;
     }
+    const F32Class &cls = p.cls[ci];
     const int m0 = mt * BM;
     // gathered tensor (x, dy, x), tap grid and direction, pixel grid of the rows
     const int Ci = OP == OP_BWD ? s.K : s.C, Hi = OP == OP_BWD ? s.P : s.H, Wi = OP == OP_BWD ? s.Q : s.W;
-    int TR = s.R, TS = s.S, Mh = s.P, Mw = s.Q;
-    [[maybe_unused]] int ph = 0, pw = 0, hh0 = 0, vv0 = 0, h_first = 0, v_first = 0;
-    if constexpr (OP == OP_BWD) {
-        ph = cls / s.stride; pw = cls % s.stride;
-        TR = ph < s.R ? (s.R - ph + s.stride - 1) / s.stride : 0;
-        TS = pw < s.S ? (s.S - pw + s.stride - 1) / s.stride : 0;
-        hh0 = ph >= s.pad ? 0 : (s.pad - ph + s.stride - 1) / s.stride;
-        vv0 = pw >= s.pad ? 0 : (s.pad - pw + s.stride - 1) / s.stride;
-        h_first = ph - s.pad + s.stride * hh0; v_first = pw - s.pad + s.stride * vv0;
-        Mh = h_first < s.H ? (s.H - 1 - h_first) / s.stride + 1 : 0;
-        Mw = v_first < s.W ? (s.W - 1 - v_first) / s.stride + 1 : 0;
-    }
-    const int T = TR * TS;
+    const int TS = cls.TS, Mh = cls.Mh, Mw = cls.Mw;
+    [[maybe_unused]] const int ph = cls.ph, pw = cls.pw, h_first = cls.h_first, v_first = cls.v_first;
+    const int T = cls.TR * TS;
     const int rows = OP == OP_FWD ? p.M : OP == OP_BWD ? s.N * Mh * Mw : s.K;       // extent of i
     const int cols = OP == OP_FWD ? s.K : OP == OP_BWD ? s.C : s.C * RS;            // extent of j
     const int k_lo = OP == OP_WGRAD ? split * p.span : 0;
@@ -157,7 +176,7 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
     constexpr bool TABLE = OP != OP_WGRAD && (A_KC || (OP == OP_BWD && B_KC));
     if constexpr (TABLE) {
         for (int t = tid; t <= T; t += NT) {
-            const int j = t < T ? t / TS : 0, i = t < T ? t % TS : 0;
+            const int j = t < T ? cls.ts.div(t) : 0, i = t < T ? t - j * TS : 0;
             const int sgn = OP == OP_BWD ? -1 : 1;
             int2 e = make_int2(sgn * (j * Wi + i) * Ci, pack_hw(sgn * j, sgn * i));
             if constexpr (OP == OP_BWD && NCHW) e.x = (ph + s.stride * j) * s.S + pw + s.stride * i;
@@ -165,7 +184,7 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
             tap_tab[t] = e;
         }
     }
-    const int ts_magic = small_magic(TS > 0 ? TS : 1);
+    const int ts_magic = cls.ts_magic;
 
     const buf_rsrc_t rs_a = make_buf_rsrc(p.a, p.a_bytes), rs_b = make_buf_rsrc(p.b, p.b_bytes);
 
@@ -173,11 +192,10 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
     auto pixel = [&](int m, int &off, int &hw) __attribute__((always_inline)) {
         off = 0; hw = FAR;
         if (m < rows) {
-            const unsigned b = (unsigned)m % (unsigned)Mw, t2 = (unsigned)m / (unsigned)Mw;
-            const unsigned a = t2 % (unsigned)Mh, n = t2 / (unsigned)Mh;
-            const int h = OP == OP_FWD ? (int)a * s.stride - s.pad : (int)a + hh0;
-            const int w = OP == OP_FWD ? (int)b * s.stride - s.pad : (int)b + vv0;
-            off = NCHW ? (int)n * Ci * plane + h * Wi + w : (((int)n * Hi + h) * Wi + w) * Ci;
+            const int t2 = cls.mw.div(m), b = m - t2 * Mw, n = cls.mh.div(t2), a = t2 - n * Mh;
+            const int mul = OP == OP_FWD ? s.stride : 1;
+            const int h = a * mul + cls.off_h, w = b * mul + cls.off_w;
+            off = NCHW ? n * Ci * plane + h * Wi + w : ((n * Hi + h) * Wi + w) * Ci;
             hw = pack_hw(h, w);
         }
     };
@@ -199,188 +217,188 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
     auto kc_k_var = [&](int i) __attribute__((always_inline)) { return ((((lane & 15) >> 2) ^ (i & 3)) << 2) + (lane & 3); };
     constexpr int NKA = A_VARK ? 4 : 1, NKB = B_VARK ? 4 : 1;   // distinct reduction elements a lane handles per stage
 
-    // ---- per-transfer state -------------------------------------------------------------------------------
-    // A operand
-    int a_off[A_LD], a_hw[A_LD];        // fixed part: row/pixel offset and packed position
-    int a_k[A_KC ? NKA : A_LD], a_t[A_KC ? NKA : A_LD], a_c[A_KC ? NKA : A_LD];     // reduction position: element, tap or pixel, channel
-    // B operand
-    int b_off[B_LD], b_hw[B_LD];
-    int b_k[B_KC ? NKB : B_LD], b_t[B_KC ? NKB : B_LD], b_c[B_KC ? NKB : B_LD];
-    [[maybe_unused]] int b_q[B_KC ? NKB : B_LD];    // backward-weight: column of the pixel
+    // ---- positions ------------------------------------------------------------------------------------------
+    // Each transfer has a fixed part (its tile row or column: byte offset, packed position) and a moving one (the
+    // reduction element).  A lane of a k-contiguous operand handles one reduction element per stage (NKA / NKB where the
+    // swizzle makes it four) and keeps it itself.  A k-slow operand has 16 reduction rows per stage, each shared by all
+    // lanes of a transfer: lane r keeps row r % 16, works out its share of the addresses once per stage, and every
+    // transfer picks its row's up with a lane read.  (Kept per transfer, the same arithmetic was eight times as much and
+    // most of a small tile's time.)  An invalid part is 2^31, which no operand reaches; sums saturate.
+    unsigned a_off[A_LD], b_off[B_LD];
+    int a_hw[A_LD], b_hw[B_LD];
+    int a_k[NKA], a_t[NKA], a_c[NKA];               // element; tap, or pixel within the image; channel, or image
+    int b_k[NKB], b_t[NKB], b_c[NKB];
+    [[maybe_unused]] int b_q[NKB];                  // backward-weight: b_c image, b_t row, b_q column
+    [[maybe_unused]] unsigned ar_off = 0, br_off = 0;       // this lane's reduction row: byte offset and packed position
+    [[maybe_unused]] int ar_d = 0, br_d = 0;
 
-    // a reduction element in (image, pixel) or (image, row, column) form, and its advance by KSTEP
-    const int adv_n = KSTEP / PQ, adv_pq = KSTEP % PQ;          // NCHW backward-weight
-    const int adv_q = KSTEP % s.Q, adv_p = KSTEP / s.Q % s.P, adv_n3 = KSTEP / s.Q / s.P;
-    const int adv_tq = T > 0 ? KSTEP / T : 0, adv_tr = T > 0 ? KSTEP % T : 0;       // (c, tap) order
-    const int adv_cq = KSTEP / Ci, adv_cr = KSTEP % Ci;         // (tap, c) order
-
+    const int adv_n = p.by_pq.div(KSTEP), adv_pq = KSTEP - adv_n * PQ;          // NCHW backward-weight
+    const int adv_row = p.by_q.div(KSTEP), adv_q = KSTEP - adv_row * s.Q, adv_n3 = p.by_p.div(adv_row), adv_p = adv_row - adv_n3 * s.P;
+    const int adv_tq = cls.t.div(KSTEP), adv_tr = KSTEP - adv_tq * T;           // (c, tap) order
+    const int adv_cq = p.by_ci.div(KSTEP), adv_cr = KSTEP - adv_cq * Ci;        // (tap, c) order
+    auto pixel_of = [&](int m, int &k, int &q, int &row, int &n) __attribute__((always_inline)) {
+        const int t = p.by_q.div(m);
+        k = m; q = m - t * s.Q; n = p.by_p.div(t); row = t - n * s.P;
+    };
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
-        if constexpr (OP == OP_WGRAD && !NCHW) {        // dy[m][k], k-slow
-            const int col = m0 + ks_col(BM, i);
-            a_off[i] = col < rows ? col : -1;
-            a_hw[i] = 0;
-            a_k[i] = k0 + ks_row(BM, i);
-        } else if constexpr (OP == OP_WGRAD) {          // dy[n][k][pq], k-contiguous
-            const int row = m0 + kc_row(VA, i);
-            a_off[i] = row < rows ? row * PQ : -1;
-            a_hw[i] = 0;
-        } else if constexpr (A_KC) {
-            pixel(m0 + kc_row(VA, i), a_off[i], a_hw[i]);
+        a_hw[i] = 0;
+        if constexpr (OP == OP_WGRAD) {                 // dy[m][k] or dy[n][k][pq]
+            const int row = m0 + (NCHW ? kc_row(VA, i) : ks_col(BM, i));
+            a_off[i] = row < rows ? (unsigned)(NCHW ? row * PQ : row) * 4u : OOB;
         } else {
-            pixel(m0 + ks_col(BM, i), a_off[i], a_hw[i]);
-            const int kd = k0 + ks_row(BM, i);
-            a_k[i] = kd; a_c[i] = T > 0 ? kd / T : 0; a_t[i] = T > 0 ? kd % T : 0;
+            int off;
+            pixel(m0 + (A_KC ? kc_row(VA, i) : ks_col(BM, i)), off, a_hw[i]);
+            a_off[i] = (unsigned)off * 4u;
         }
     }
-    if constexpr (A_KC) {
 #pragma unroll
-        for (int v = 0; v < NKA; ++v) {
-            const int kd = k0 + (A_VARK ? kc_k_var(v) : kc_k(VA));
-            a_k[v] = kd;
-            if constexpr (OP == OP_WGRAD) { a_c[v] = kd / PQ; a_t[v] = kd % PQ; }
-            else { a_t[v] = kd / Ci; a_c[v] = kd % Ci; }
-        }
+    for (int v = 0; v < NKA; ++v) {
+        const int kd = k0 + (!A_KC ? lane & 15 : A_VARK ? kc_k_var(v) : kc_k(VA));
+        a_k[v] = kd;
+        if constexpr (OP == OP_WGRAD) { a_c[v] = p.by_pq.div(kd); a_t[v] = kd - a_c[v] * PQ; }
+        else if constexpr (A_KC) { a_t[v] = p.by_ci.div(kd); a_c[v] = kd - a_t[v] * Ci; }
+        else { a_c[v] = cls.t.div(kd); a_t[v] = kd - a_c[v] * T; }
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
         b_hw[i] = 0;
-        if constexpr (OP == OP_FWD) {                   // w[co][kd]
-            const int co = n0 + kc_row(VB, i);
-            b_off[i] = co < cols ? co * (T * Ci) : -1;
-        } else if constexpr (OP == OP_BWD && !NCHW) {   // w[k][rs][c], k-slow
-            const int c = n0 + ks_col(BN, i);
-            b_off[i] = c < cols ? c : -1;
-            const int kd = k0 + ks_row(BN, i);
-            b_k[i] = kd; b_t[i] = kd / Ci; b_c[i] = kd % Ci;
-        } else if constexpr (OP == OP_BWD) {            // w[k][c][rs], taps contiguous
-            const int c = n0 + kc_row(VB, i);
-            b_off[i] = c < cols ? c * RS : -1;
-        } else {                                        // x gather: column = (tap, c) or (c, tap)
-            const int col = n0 + (NCHW ? kc_row(VB, i) : ks_col(BN, i));
-            const int tap = NCHW ? col % RS : col / s.C, c = NCHW ? col / RS : col % s.C;
-            const int r = tap / s.S - s.pad, q = tap % s.S - s.pad;
-            b_off[i] = NCHW ? c * plane + r * s.W + q : (r * s.W + q) * s.C + c;
-            b_hw[i] = col < cols ? pack_hw(r, q) : FAR;
-            if constexpr (!NCHW) {
-                const int m = k0 + ks_row(BN, i);
-                b_k[i] = m; b_q[i] = m % s.Q; b_t[i] = m / s.Q % s.P; b_c[i] = m / s.Q / s.P;
-            }
+        const int j = n0 + (B_KC ? kc_row(VB, i) : ks_col(BN, i));
+        if constexpr (OP == OP_FWD) b_off[i] = j < cols ? (unsigned)(j * (T * Ci)) * 4u : OOB;         // w[co][kd]
+        else if constexpr (OP == OP_BWD) b_off[i] = j < cols ? (unsigned)(NCHW ? j * RS : j) * 4u : OOB;  // w[k][c][rs] or w[k][rs][c]
+        else {                                          // x gather: column = (c, tap) or (tap, c)
+            const int hi = NCHW ? p.by_rs.div(j) : p.by_c.div(j), lo = j - hi * (NCHW ? RS : s.C);
+            const int tap = NCHW ? lo : hi, c = NCHW ? hi : lo;
+            const int tr = p.by_s.div(tap), r = tr - s.pad, q = tap - tr * s.S - s.pad;
+            b_off[i] = (unsigned)(NCHW ? c * plane + r * s.W + q : (r * s.W + q) * s.C + c) * 4u;
+            b_hw[i] = j < cols ? pack_hw(r, q) : FAR;
         }
     }
-    if constexpr (B_KC) {
 #pragma unroll
-        for (int v = 0; v < NKB; ++v) {
-            const int kd = k0 + (B_VARK ? kc_k_var(v) : kc_k(VB));
-            b_k[v] = kd;
-            if constexpr (OP == OP_BWD) { b_c[v] = T > 0 ? kd / T : 0; b_t[v] = T > 0 ? kd % T : 0; }
-            else if constexpr (OP == OP_WGRAD) { b_q[v] = kd % s.Q; b_t[v] = kd / s.Q % s.P; b_c[v] = kd / s.Q / s.P; }
-        }
+    for (int v = 0; v < NKB; ++v) {
+        const int kd = k0 + (!B_KC ? lane & 15 : B_VARK ? kc_k_var(v) : kc_k(VB));
+        b_k[v] = kd;
+        if constexpr (OP == OP_WGRAD) pixel_of(kd, b_k[v], b_q[v], b_t[v], b_c[v]);
+        else if constexpr (OP == OP_BWD && B_KC) { b_c[v] = cls.t.div(kd); b_t[v] = kd - b_c[v] * T; }
+        else if constexpr (OP == OP_BWD) { b_t[v] = p.by_ci.div(kd); b_c[v] = kd - b_t[v] * Ci; }
     }
 
     float *ring = smem + zg * (NS * STG);
-    // backward-weight: reduction pixel v of the x operand, one stage further
-    auto next_pixel = [&](int v) __attribute__((always_inline)) {
-        b_k[v] += KSTEP;
-        const int q = b_q[v] + adv_q, cq = q >= s.Q ? 1 : 0;
-        b_q[v] = q - (cq ? s.Q : 0);
-        const int pr = b_t[v] + adv_p + cq, cp = pr >= s.P ? 1 : 0;
-        b_t[v] = pr - (cp ? s.P : 0);
-        b_c[v] += adv_n3 + cp;
-    };
     // The transfers of one stage as L tasks (A's, then B's), each with its address arithmetic, so that they can be spread
-    // between matrix instructions; `advance` moves the shared reduction positions one stage further and fetches the tap
-    // entries of the stage after, before the first task that reads them.
+    // between matrix instructions; `advance` moves the reduction positions one stage further, `fetch_rows` works out
+    // what the coming stage's tasks share.
     [[maybe_unused]] int2 te[NKA];
-    [[maybe_unused]] int we[NKB];
-    auto fetch_taps = [&]() __attribute__((always_inline)) {
+    [[maybe_unused]] unsigned we[NKB];
+    auto fetch_rows = [&]() __attribute__((always_inline)) {
         if constexpr (OP != OP_WGRAD && A_KC) {
 #pragma unroll
             for (int v = 0; v < NKA; ++v) te[v] = tap_tab[a_t[v] < T ? a_t[v] : T];
         }
+        if constexpr (OP == OP_WGRAD && !NCHW) ar_off = a_k[0] < k_hi ? (unsigned)(a_k[0] * s.K) * 4u : OOB;
+        if constexpr (OP != OP_WGRAD && !A_KC) {
+            const int j = small_div(a_t[0], ts_magic), q = a_t[0] - j * TS;
+            const int dh = OP == OP_BWD ? -j : j, dv = OP == OP_BWD ? -q : q;
+            ar_off = (unsigned)(a_c[0] * plane + dh * Wi + dv) * 4u;
+            ar_d = a_k[0] < k_hi ? pack_hw(dh, dv) : FAR;
+        }
         if constexpr (OP == OP_BWD && B_KC) {
 #pragma unroll
-            for (int v = 0; v < NKB; ++v) we[v] = b_c[v] * s.C * RS + tap_tab[b_t[v]].x;
+            for (int v = 0; v < NKB; ++v) we[v] = b_k[v] < k_hi ? (unsigned)(b_c[v] * s.C * RS + tap_tab[b_t[v]].x) * 4u : OOB;
+        } else if constexpr (OP == OP_BWD) {
+            const int j = small_div(b_t[0], ts_magic), q = b_t[0] - j * TS;
+            const int rs = (ph + s.stride * j) * s.S + pw + s.stride * q;
+            br_off = b_k[0] < k_hi ? (unsigned)((b_c[0] * RS + rs) * s.C) * 4u : OOB;
+        } else if constexpr (OP == OP_FWD) {
+#pragma unroll
+            for (int v = 0; v < NKB; ++v) we[v] = b_k[v] < k_hi ? (unsigned)b_k[v] * 4u : OOB;
+        } else {
+            if constexpr (NCHW) {
+#pragma unroll
+                for (int v = 0; v < NKB; ++v) {
+                    const int h = b_t[v] * s.stride, w = b_q[v] * s.stride;
+                    we[v] = (unsigned)(b_c[v] * s.C * plane + h * s.W + w) * 4u;
+                    te[v & (NKA - 1)].y = b_k[v] < k_hi ? pack_hw(h, w) : FAR;      // NKA == NKB here
+                    te[v & (NKA - 1)].x = b_k[v] < k_hi ? (a_c[v & (NKA - 1)] * s.K * PQ + a_t[v & (NKA - 1)]) * 4 : (int)OOB;
+                }
+            } else {
+                const int h = b_t[0] * s.stride, w = b_q[0] * s.stride;
+                br_off = (unsigned)(((b_c[0] * s.H + h) * s.W + w) * s.C) * 4u;
+                br_d = b_k[0] < k_hi ? pack_hw(h, w) : FAR;
+            }
         }
     };
+    // reduction row r's value, held by lane r: the row is the same for the whole wave, or one per half of it
+    auto of_row = [&](int BX, int i, int v) __attribute__((always_inline)) -> int {
+        if (BX >= 64) return __builtin_amdgcn_readlane(v, ks_row(BX, i));
+        const int r = (gw + NG * i) * 2, lo = __builtin_amdgcn_readlane(v, r), hi = __builtin_amdgcn_readlane(v, r + 1);
+        return half ? hi : lo;
+    };
+    auto add_sat = [](unsigned x, unsigned y) __attribute__((always_inline)) { return __builtin_elementwise_add_sat(x, y); };
     auto task = [&](auto tc, int slot) __attribute__((always_inline)) {
         constexpr int Tk = decltype(tc)::value;
         unsigned off;
         if constexpr (Tk < A_LD) {
             constexpr int i = Tk, v = A_VARK ? i & 3 : 0;
-            if constexpr (OP == OP_WGRAD && !NCHW) {
-                off = (a_off[i] >= 0 && a_k[i] < k_hi) ? (unsigned)(a_k[i] * s.K + a_off[i]) * 4u : OOB;
-                a_k[i] += KSTEP;
-            } else if constexpr (OP == OP_WGRAD) {
-                off = (a_off[i] >= 0 && a_k[v] < k_hi) ? (unsigned)(a_c[v] * s.K * PQ + a_off[i] + a_t[v]) * 4u : OOB;
-            } else if constexpr (A_KC) {
-                off = outside(a_hw[i], te[v].y, lim_hw) == 0 ? (unsigned)(a_off[i] + te[v].x + a_c[v]) * 4u : OOB;
-            } else {
-                const int j = small_div(a_t[i], ts_magic), q = a_t[i] - j * TS;
-                const int dh = OP == OP_BWD ? -j : j, dv = OP == OP_BWD ? -q : q;
-                const bool ok = a_k[i] < k_hi && outside(a_hw[i], pack_hw(dh, dv), lim_hw) == 0;
-                off = ok ? (unsigned)(a_off[i] + a_c[i] * plane + dh * Wi + dv) * 4u : OOB;
-                a_k[i] += KSTEP;
-                const int t = a_t[i] + adv_tr, carry = t >= T ? 1 : 0;
-                a_t[i] = t - (carry ? T : 0);
-                a_c[i] += adv_tq + carry;
+            if constexpr (OP == OP_WGRAD && !NCHW) off = add_sat(a_off[i], (unsigned)of_row(BM, i, (int)ar_off));
+            else if constexpr (OP == OP_WGRAD) off = add_sat(a_off[i], (unsigned)te[v].x);
+            else if constexpr (A_KC) off = outside(a_hw[i], te[v].y, lim_hw) == 0 ? a_off[i] + (unsigned)(te[v].x + a_c[v]) * 4u : OOB;
+            else {
+                const unsigned to = a_off[i] + (unsigned)of_row(BM, i, (int)ar_off);      // lane reads: never under a condition
+                off = outside(a_hw[i], of_row(BM, i, ar_d), lim_hw) == 0 ? to : OOB;
             }
             float *d = ring + slot * STG + (gw + NG * i) * (64 * VA);
             if constexpr (VA == 4) lds_dma16(rs_a, off, d); else lds_dma4(rs_a, off, d);
         } else {
-            constexpr int i = Tk - A_LD, v = B_KC ? (B_VARK ? i & 3 : 0) : i;
-            if constexpr (OP == OP_FWD) {
-                off = (b_off[i] >= 0 && b_k[v] < k_hi) ? (unsigned)(b_off[i] + b_k[v]) * 4u : OOB;
-            } else if constexpr (OP == OP_BWD && !NCHW) {
-                const int j = small_div(b_t[i], ts_magic), q = b_t[i] - j * TS;
-                const int rs = (ph + s.stride * j) * s.S + pw + s.stride * q;
-                off = (b_off[i] >= 0 && b_k[i] < k_hi) ? (unsigned)((b_c[i] * RS + rs) * s.C + b_off[i]) * 4u : OOB;
-                b_k[i] += KSTEP;
-                const int c = b_c[i] + adv_cr, carry = c >= Ci ? 1 : 0;
-                b_c[i] = c - (carry ? Ci : 0);
-                b_t[i] += adv_cq + carry;
-            } else if constexpr (OP == OP_BWD) {
-                off = (b_off[i] >= 0 && b_k[v] < k_hi) ? (unsigned)(we[v] + b_off[i]) * 4u : OOB;
-            } else {
-                const int h = b_t[v] * s.stride, w = b_q[v] * s.stride;
-                const bool ok = b_k[v] < k_hi && outside(pack_hw(h, w), b_hw[i], lim_hw) == 0;
-                const int org = NCHW ? b_c[v] * s.C * plane + h * s.W + w : ((b_c[v] * s.H + h) * s.W + w) * s.C;
-                off = ok ? (unsigned)(org + b_off[i]) * 4u : OOB;
-                if constexpr (!NCHW) next_pixel(v);
+            constexpr int i = Tk - A_LD, v = B_VARK ? i & 3 : 0;
+            if constexpr (OP == OP_FWD || (OP == OP_BWD && NCHW)) off = add_sat(b_off[i], we[v]);
+            else if constexpr (OP == OP_BWD) off = add_sat(b_off[i], (unsigned)of_row(BN, i, (int)br_off));
+            else if constexpr (NCHW) off = outside(te[v].y, b_hw[i], lim_hw) == 0 ? b_off[i] + we[v] : OOB;
+            else {
+                const unsigned to = b_off[i] + (unsigned)of_row(BN, i, (int)br_off);
+                off = outside(of_row(BN, i, br_d), b_hw[i], lim_hw) == 0 ? to : OOB;
             }
             float *d = ring + slot * STG + BM * BK + (gw + NG * i) * (64 * VB);
             if constexpr (VB == 4) lds_dma16(rs_b, off, d); else lds_dma4(rs_b, off, d);
         }
     };
     auto advance = [&]() __attribute__((always_inline)) {
-        if constexpr (A_KC) {
 #pragma unroll
-            for (int v = 0; v < NKA; ++v) {
-                a_k[v] += KSTEP;
-                if constexpr (OP == OP_WGRAD) {
-                    const int t = a_t[v] + adv_pq, carry = t >= PQ ? 1 : 0;
-                    a_t[v] = t - (carry ? PQ : 0);
-                    a_c[v] += adv_n + carry;
-                } else {
-                    const int c = a_c[v] + adv_cr, carry = c >= Ci ? 1 : 0;
-                    a_c[v] = c - (carry ? Ci : 0);
-                    a_t[v] += adv_cq + carry;
-                }
+        for (int v = 0; v < NKA; ++v) {
+            a_k[v] += KSTEP;
+            if constexpr (OP == OP_WGRAD) {
+                const int t = a_t[v] + adv_pq, carry = t >= PQ ? 1 : 0;
+                a_t[v] = t - (carry ? PQ : 0);
+                a_c[v] += adv_n + carry;
+            } else if constexpr (A_KC) {
+                const int c = a_c[v] + adv_cr, carry = c >= Ci ? 1 : 0;
+                a_c[v] = c - (carry ? Ci : 0);
+                a_t[v] += adv_cq + carry;
+            } else {
+                const int t = a_t[v] + adv_tr, carry = t >= T ? 1 : 0;
+                a_t[v] = t - (carry ? T : 0);
+                a_c[v] += adv_tq + carry;
             }
         }
-        if constexpr (B_KC) {
 #pragma unroll
-            for (int v = 0; v < NKB; ++v) {
-                if constexpr (OP == OP_WGRAD) next_pixel(v);
-                else b_k[v] += KSTEP;
-                if constexpr (OP == OP_BWD) {
-                    const int t = b_t[v] + adv_tr, carry = t >= T ? 1 : 0;
-                    b_t[v] = t - (carry ? T : 0);
-                    b_c[v] += adv_tq + carry;
-                }
+        for (int v = 0; v < NKB; ++v) {
+            b_k[v] += KSTEP;
+            if constexpr (OP == OP_WGRAD) {
+                const int q = b_q[v] + adv_q, cq = q >= s.Q ? 1 : 0;
+                b_q[v] = q - (cq ? s.Q : 0);
+                const int pr = b_t[v] + adv_p + cq, cp = pr >= s.P ? 1 : 0;
+                b_t[v] = pr - (cp ? s.P : 0);
+                b_c[v] += adv_n3 + cp;
+            } else if constexpr (OP == OP_BWD && B_KC) {
+                const int t = b_t[v] + adv_tr, carry = t >= T ? 1 : 0;
+                b_t[v] = t - (carry ? T : 0);
+                b_c[v] += adv_tq + carry;
+            } else if constexpr (OP == OP_BWD) {
+                const int c = b_c[v] + adv_cr, carry = c >= Ci ? 1 : 0;
+                b_c[v] = c - (carry ? Ci : 0);
+                b_t[v] += adv_cq + carry;
             }
         }
-        fetch_taps();
+        fetch_rows();
     };
 
     f32x16 acc[MI][NI];
@@ -435,7 +453,7 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
     // the first operand fetch of stage kt+1 and the first half of the transfers of stage kt+NS into the freed slot.
     constexpr int L1 = (L + 1) / 2, L2 = L - L1;
     if constexpr (TABLE) __syncthreads();
-    fetch_taps();
+    fetch_rows();
     static_for<NS - 1>([&](auto sc) __attribute__((always_inline)) {
         static_for<L>([&](auto tc) __attribute__((always_inline)) { task(tc, decltype(sc)::value); });
         advance();
@@ -475,13 +493,13 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
         if constexpr (OP == OP_WGRAD) return (long long)i * cols;
         else if constexpr (OP == OP_FWD) {
             if (!NCHW) return (long long)i * cols;
-            const unsigned n = (unsigned)i / (unsigned)PQ, pq = (unsigned)i % (unsigned)PQ;
-            return (long long)n * cols * PQ + pq;
+            const int n = p.by_pq.div(i);
+            return (long long)n * cols * PQ + (i - n * PQ);
         } else {
-            unsigned pix = (unsigned)i;
-            if (NCHW || s.stride != 1 || h_first != 0 || v_first != 0) {
-                const unsigned b = (unsigned)i % (unsigned)Mw, t2 = (unsigned)i / (unsigned)Mw, a = t2 % (unsigned)Mh, n = t2 / (unsigned)Mh;
-                const unsigned hw = (h_first + s.stride * a) * s.W + v_first + s.stride * b;
+            int pix = i;
+            if (NCHW || s.stride != 1) {
+                const int t2 = cls.mw.div(i), b = i - t2 * Mw, n = cls.mh.div(t2), a = t2 - n * Mh;
+                const int hw = (h_first + s.stride * a) * s.W + v_first + s.stride * b;
                 if (NCHW) return (long long)n * cols * (s.H * s.W) + hw;
                 pix = n * (s.H * s.W) + hw;
             }
@@ -623,12 +641,24 @@ double model_clocks(const F32Tile &t, long long tiles, long long k)
 
 struct F32Plan { int tile, splits, span; };
 
-long long class_rows(const ConvShape &s, int ph, int pw)
+F32Class residue_class(const ConvShape &s, int ph, int pw)
 {
-    const int hh0 = ph >= s.pad ? 0 : (s.pad - ph + s.stride - 1) / s.stride, vv0 = pw >= s.pad ? 0 : (s.pad - pw + s.stride - 1) / s.stride;
-    const int hf = ph - s.pad + s.stride * hh0, vf = pw - s.pad + s.stride * vv0;
-    const int Mh = hf < s.H ? (s.H - 1 - hf) / s.stride + 1 : 0, Mw = vf < s.W ? (s.W - 1 - vf) / s.stride + 1 : 0;
-    return (long long)s.N * Mh * Mw;
+    F32Class c{};
+    c.ph = ph; c.pw = pw;
+    c.TR = ph < s.R ? (s.R - ph + s.stride - 1) / s.stride : 0;
+    c.TS = pw < s.S ? (s.S - pw + s.stride - 1) / s.stride : 0;
+    c.off_h = ph >= s.pad ? 0 : (s.pad - ph + s.stride - 1) / s.stride;
+    c.off_w = pw >= s.pad ? 0 : (s.pad - pw + s.stride - 1) / s.stride;
+    c.h_first = ph - s.pad + s.stride * c.off_h; c.v_first = pw - s.pad + s.stride * c.off_w;
+    c.Mh = c.h_first < s.H ? (s.H - 1 - c.h_first) / s.stride + 1 : 0;
+    c.Mw = c.v_first < s.W ? (s.W - 1 - c.v_first) / s.stride + 1 : 0;
+    return c;
+}
+
+void set_divisors(F32Class &c)
+{
+    c.mw = FastDiv(c.Mw); c.mh = FastDiv(c.Mh); c.t = FastDiv(c.TR * c.TS); c.ts = FastDiv(c.TS);
+    c.ts_magic = small_magic(c.TS > 0 ? c.TS : 1);
 }
 
 F32Plan plan_rows(const ConvShape &s, int op)
@@ -696,6 +726,10 @@ static int run(int op, bool nchw, int t, F32Params &p, long long row_tiles, long
     p.n_tiles = (int)nt;
     p.tiles = (int)(row_tiles * nt);
     p.units = p.tiles * splits;
+    const ConvShape &s = p.s;
+    p.by_ntiles = FastDiv(p.n_tiles); p.by_tiles = FastDiv(p.tiles);
+    p.by_ci = FastDiv(op == OP_BWD ? s.K : s.C); p.by_c = FastDiv(s.C); p.by_rs = FastDiv(s.R * s.S); p.by_s = FastDiv(s.S);
+    p.by_pq = FastDiv(s.P * s.Q); p.by_q = FastDiv(s.Q); p.by_p = FastDiv(s.P);
     return launch_op(op, nchw, t, p, st);
 }
 
@@ -709,6 +743,9 @@ int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y
     p.s = s;
     p.M = s.N * s.P * s.Q;
     p.bias = post.bias; p.relu = post.relu;
+    F32Class &c = p.cls[0];
+    c.TR = s.R; c.TS = s.S; c.Mh = s.P; c.Mw = s.Q; c.off_h = c.off_w = -s.pad;
+    set_divisors(c);
     *variant = kTiles[t].name;
     return run(OP_FWD, nchw, t, p, (p.M + kTiles[t].bm - 1) / kTiles[t].bm, s.K, 1, st);
 }
@@ -725,10 +762,12 @@ int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, v
     p.n_cls = s.stride * s.stride;
     long long tiles = 0;
     for (int c = 0; c < p.n_cls; ++c) {
-        p.cls_tile0[c] = (int)tiles;
-        tiles += (class_rows(s, c / s.stride, c % s.stride) + kTiles[t].bm - 1) / kTiles[t].bm;
+        F32Class &f = p.cls[c];
+        f = residue_class(s, c / s.stride, c % s.stride);
+        set_divisors(f);
+        f.tile0 = (int)tiles;
+        tiles += ((long long)s.N * f.Mh * f.Mw + kTiles[t].bm - 1) / kTiles[t].bm;
     }
-    p.cls_tile0[p.n_cls] = (int)tiles;
     *variant = kTiles[t].name;
     return run(OP_BWD, nchw, t, p, tiles, s.C, 1, st);
 }
