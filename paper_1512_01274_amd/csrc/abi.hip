@@ -252,7 +252,7 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
             MXC_TRY(igemm_bwd_data_prepare(s2, w2, wt, st, true));
         }
         if (!run) return MXC_OK;
-        MXC_TRY(igemm_bwd_data(s2, dy, wt, dx2, wt, st, &v));
+        MXC_TRY(igemm_bwd_data(s2, dy, bwd_data_reads_filter_in_place(s2) ? wt : nullptr, dx2, wt, st, &v));
         set_variant("bwd_data", (std::string("s2d+") + v).c_str());
         return s2d_unpack_dx(s, dx2, dx, st, post.mask);      // the mask is applied where dx itself is written
     }
@@ -275,9 +275,12 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
         if (dry) return MXC_OK;
         const char *v = "";
         // a filter the kernel reads in place stays where it is unless the caller keeps a prepared copy
-        if (prep) MXC_TRY(igemm_bwd_data_prepare(s, w, wt, st, mode == FILTER_PREPARE_ONLY, kcrs));
+        const void *in_place = nullptr;
+        if (bwd_data_reads_filter_in_place(s)) in_place = mode == FILTER_RAW ? w : wt;
+        else if (mode == FILTER_RAW && (!kcrs || s.R * s.S == 1) && bwd_data_small_in_place(s, post.mask != nullptr)) in_place = w;
+        if (prep && !(in_place != nullptr && mode == FILTER_RAW)) MXC_TRY(igemm_bwd_data_prepare(s, w, wt, st, mode == FILTER_PREPARE_ONLY, kcrs));
         if (!run) return MXC_OK;
-        const int rc = igemm_bwd_data(s, dy, mode == FILTER_RAW ? w : wt, dx, wt, st, &v, post, split_ws);
+        const int rc = igemm_bwd_data(s, dy, in_place, dx, wt, st, &v, post, split_ws);
         set_variant("bwd_data", v);
         return rc;
     }

@@ -105,7 +105,6 @@ struct GridPos {
 template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT, bool TI>
 __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, const int n0, const int split_z)
 {
-    static_assert(!(BT && TI), "the in-place filter variant has one tap");
     constexpr int NW = WR * WC, NT = 64 * NW;
     constexpr int WM = BM / WR, WN = BN / WC;     // wave tile
     constexpr int MI = WM / 32, NI = WN / 32;     // 32x32 MFMA blocks per wave
@@ -203,15 +202,16 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
         }
     }
     unsigned b_off[B_LD];   // byte offset of the filter row, OOB for rows past Co
-    // BT: lane -> row RPLB*i' + lane/RCB of the stage's 64 reduction rows, output-column chunk lane%RCB (swizzled);
-    // b_off = byte offset of (row, column chunk) relative to the stage's first filter row
+    // BT: lane -> row RPLB*i' + lane/RCB of the stage's 64 reduction rows, output-column chunk lane%RCB (swizzled).  A
+    // reduction row is (tap, k) and lies at row k*T + tap of the filter; b_off = byte offset of the lane's column chunk,
+    // plus (channel-block-major order) that of the row within the stage's channel block
     [[maybe_unused]] const int lb_sub = lane / RCB;
     [[maybe_unused]] const int lb_chunk = (lane % RCB) ^ bt_row_swz<RCB>(RPLB * wave + lb_sub);   // RPLB*NW*i never changes the swizzle
     [[maybe_unused]] const bool bt_col_ok = n0 + lb_chunk * 8 < p.Co;
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
         if constexpr (BT) {
-            b_off[i] = (unsigned)((RPLB * (wave + NW * i) + lb_sub) * p.Co * 2 + (n0 + lb_chunk * 8) * 2);
+            b_off[i] = (unsigned)((TI ? (RPLB * (wave + NW * i) + lb_sub) * T * p.Co * 2 : 0) + (n0 + lb_chunk * 8) * 2);
         } else {
             const int co = n0 + RPL * (wave + NW * i) + ld_sub;
             b_off[i] = co < p.Co ? (unsigned)co * (unsigned)Kd * 2u : OOB;
@@ -231,6 +231,16 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
         ci2 = (k_lo / T) * (BKT * 2) + ld_chunk * 16;
     }
     const int lim_hw = ((p.Hi - 1) & 0xFFFF) | ((p.Wi - 1) << 16);
+    // BT, tap-major order: (tap, k) of this lane's filter rows in the next stage
+    [[maybe_unused]] int bt_tap[B_LD], bt_k[B_LD];
+    if constexpr (BT && !TI) {
+#pragma unroll
+        for (int i = 0; i < B_LD; ++i) {
+            const int kd = k_lo * BKT + RPLB * (wave + NW * i) + lb_sub;
+            bt_tap[i] = kd / p.Ci;
+            bt_k[i] = kd - bt_tap[i] * p.Ci;
+        }
+    }
 
     unsigned va[A_LD], vb[B_LD];   // byte offsets of the next stage's loads
 
@@ -249,13 +259,15 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
             const int bad = (__builtin_bit_cast(int, hw) | __builtin_bit_cast(int, d)) & (int)0x80008000;
             va[i] = bad == 0 ? (unsigned)(a_off[i] + tap_e.x + ci2) : OOB;
         } else {
-            if constexpr (BT) {
-                // one tap: stage s covers filter rows 64*s .. 64*s+63; kd2 tracks this lane's byte offset 2*(64*s + chunk*8)
-                const bool ok = bt_col_ok && kd2 < Kd2;
-                const unsigned base = (unsigned)((kd2 - ld_chunk * 16) / 2) * (unsigned)(p.Co * 2);
+            if constexpr (BT && !TI) {
 #pragma unroll
-                for (int i = 0; i < B_LD; ++i) vb[i] = ok ? b_off[i] + base : OOB;
-                kd2 += BKT * 2;
+                for (int i = 0; i < B_LD; ++i) {
+                    vb[i] = bt_col_ok && bt_tap[i] < T ? b_off[i] + (unsigned)(bt_k[i] * T + bt_tap[i]) * (unsigned)(p.Co * 2) : OOB;
+                    bt_k[i] += kr2 / 2;
+                    const int carry = bt_k[i] >= p.Ci ? 1 : 0;
+                    bt_k[i] -= carry ? p.Ci : 0;
+                    bt_tap[i] += kq + carry;
+                }
                 ci2 += kr2;
                 const int carry = ci2 >= Ci2 ? 1 : 0;
                 ci2 -= carry ? Ci2 : 0;
@@ -263,10 +275,17 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
             } else if constexpr (TI) {
                 // Order (channel block, tap): the pixels a workgroup reads for one channel block serve all
                 // its taps back to back, so they are still in the XCD's L2 when the next tap asks for them.
-                const bool k_ok = tap < T;
-                const unsigned kd = (unsigned)(tap * Ci2 + ci2);
+                if constexpr (BT) {
+                    const bool ok = bt_col_ok && tap < T;
+                    const unsigned base = (unsigned)((ci2 - ld_chunk * 16) / 2 * T + tap) * (unsigned)(p.Co * 2);
 #pragma unroll
-                for (int i = 0; i < B_LD; ++i) vb[i] = k_ok ? b_off[i] + kd : OOB;
+                    for (int i = 0; i < B_LD; ++i) vb[i] = ok ? b_off[i] + base : OOB;
+                } else {
+                    const bool k_ok = tap < T;
+                    const unsigned kd = (unsigned)(tap * Ci2 + ci2);
+#pragma unroll
+                    for (int i = 0; i < B_LD; ++i) vb[i] = k_ok ? b_off[i] + kd : OOB;
+                }
                 const int last = tap + 1 >= T ? 1 : 0;           // wrap to the next channel block
                 tap = last ? 0 : tap + 1;
                 ci2 += last ? BKT * 2 : 0;
@@ -696,7 +715,7 @@ int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end
     if (p.Cw == 0) p.Cw = p.Co;
     p.wm_bytes = BT ? p.bt_w_bytes : (unsigned)((long long)p.Cw * p.TR * p.TS * p.Ci * 2);
     // MXC_TAP_OUTER=1 (tuning only) keeps the filter's own order, all channels of a tap before the next tap
-    p.tap_inner = (!BT && p.Ci % BKT == 0 && p.TR * p.TS > 1 && !tap_outer_forced) ? 1 : 0;
+    p.tap_inner = (p.Ci % BKT == 0 && p.TR * p.TS > 1 && !tap_outer_forced) ? 1 : 0;
     p.linear_out = (p.out_mul_h == 1 && p.out_mul_w == 1 && p.out_off_h == 0 && p.out_off_w == 0 && p.Mh == p.Ho && p.Mw == p.Wo) ? 1 : 0;
     // results of a large layer leave as non-temporal stores: the caches keep serving this kernel's operand reads
     static const char *nt_forced = getenv("MXC_NT_OUT");                      // tuning sweeps only; read once
@@ -713,11 +732,9 @@ int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end
     const long long total = (long long)p.m_tiles * p.n_tiles * (p.splits > 1 ? p.splits : 1);
     if (total > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
     const int grid = (int)((total + 7) / 8) * 8;
-    if constexpr (!BT) {
-        if (p.tap_inner) {
-            hipLaunchKernelGGL((igemm_kernel<BM, BN, BKT, NS, WR, WC, false, true>), dim3((unsigned)grid), dim3(64 * WR * WC), 0, st, p);
-            return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
-        }
+    if (p.tap_inner) {
+        hipLaunchKernelGGL((igemm_kernel<BM, BN, BKT, NS, WR, WC, BT, true>), dim3((unsigned)grid), dim3(64 * WR * WC), 0, st, p);
+        return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
     }
     hipLaunchKernelGGL((igemm_kernel<BM, BN, BKT, NS, WR, WC, BT, false>), dim3((unsigned)grid), dim3(64 * WR * WC), 0, st, p);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
@@ -775,8 +792,8 @@ constexpr int MASKED_WINDOW_TILE = N_TILE_CHOICES + 2;
 const char *const kMaskedWindowName = "igemm_patch_masked";
 inline bool whole_launch(int idx) { return idx == STREAM_TILE || idx == WINDOW_TILE || idx == MASKED_WINDOW_TILE; }
 
-// the tiles that also exist reading a 1x1 filter in place (transposed tiles)
-bool has_bt(int idx) { return idx == 0 || idx == 1 || idx == 4; }
+// the tiles that also exist reading the filter in place (transposed tiles)
+bool has_bt(int idx) { return idx == 0 || idx == 1 || idx == 4 || idx == 6 || idx == 11; }
 
 int launch_choice(int idx, const IgemmParams &p, hipStream_t st, bool bt = false, long long m_begin = 0, long long m_end = -1)
 {
@@ -785,6 +802,8 @@ int launch_choice(int idx, const IgemmParams &p, hipStream_t st, bool bt = false
         case 0: return launch<128, 128, 64, 2, 2, 2, true>(p, st, m_begin, m_end);
         case 1: return launch<256, 256, 64, 2, 2, 4, true>(p, st, m_begin, m_end);
         case 4: return launch<128, 64, 64, 2, 2, 2, true>(p, st, m_begin, m_end);
+        case 6: return launch<128, 32, 64, 2, 4, 1, true>(p, st, m_begin, m_end);
+        case 11: return launch<64, 128, 64, 3, 2, 2, true>(p, st, m_begin, m_end);
         default: return MXC_ERR_UNSUPPORTED;
         }
     }
@@ -875,8 +894,8 @@ Plan choose_plan(long long M, int Co, int Kd, bool allow_stream = true, bool mas
 {
     g_key_M = M; g_key_Co = Co; g_key_Kd = Kd;
     if (const char *f = getenv("MXC_FORCE_VARIANT")) {
-        const char *plus = strchr(f, '+');
-        const int a = tile_index(f, plus ? (size_t)(plus - f) : strlen(f));
+        const char *plus = strchr(f, '+'), *slash = strchr(f, '/');
+        const int a = tile_index(f, plus ? (size_t)(plus - f) : slash ? (size_t)(slash - f) : strlen(f));
         const int b = plus ? tile_index(plus + 1, strlen(plus + 1)) : -1;
         if (a >= 0 && whole_launch(a) && !plus && allow_stream && !(a == WINDOW_TILE && masked) && !(a == MASKED_WINDOW_TILE && !masked)) return Plan{a, -1, M};
         if (a >= 0 && !whole_launch(a) && !whole_launch(b) && (!plus || b >= 0)) {
@@ -985,6 +1004,11 @@ __global__ __launch_bounds__(256) void zero_classes_kernel(bf16_t *__restrict__ 
 int split_count(long long M, int Co, int Kd)
 {
     const TileChoice &t = kTiles[choose_tile(M, Co, Kd)];
+    if (const char *f = getenv("MXC_FORCE_VARIANT"))
+        if (const char *slash = strchr(f, '/')) {
+            const int most = (Kd + t.bk - 1) / t.bk, sp = atoi(slash + 1);
+            return sp < 1 ? 1 : sp < most ? sp : most;
+        }
     const long long tiles = ((M + t.bm - 1) / t.bm) * ((Co + t.bn - 1) / t.bn);
     const long long slots = 256LL * t.slots;
     if (tiles * 2 > slots) return 1;
@@ -1150,6 +1174,21 @@ bool igemm_bwd_data_supported(const ConvShape &s)
 
 size_t igemm_bwd_data_workspace(const ConvShape &s) { return (size_t)s.K * s.R * s.S * s.C * sizeof(bf16_t); }
 
+// Whether a call that is handed the KRSC filter itself reads it in place although a prepared filter would be re-packed:
+// the re-pack is a launch of 4-5 us, which a small problem's slower operand fetch does not cost.  Same tile, same order
+// of the reduction, same bits.  Measured over 60 shapes, masked or not: below 2 GFLOP every tile with the variant gains
+// (64x128 2 us, 128x32 and 128x64 3.6 us of 12), at 4-10 GFLOP 2-3 us of 25-35, and from 12 GFLOP on it loses with
+// 64x128 (15%) and breaks even with the others, which is where the line lies.
+bool bwd_data_small_in_place(const ConvShape &s, bool masked)
+{
+    if (real_c(s) != s.C || s.C % 8 != 0 || s.stride != 1 || bwd_data_reads_filter_in_place(s)) return false;
+    const long long M = (long long)s.N * s.H * s.W;
+    const int Kd = s.R * s.S * s.K;
+    const Plan pl = choose_plan(M, s.C, Kd, true, masked);
+    if (whole_launch(pl.main) || !has_bt(pl.main) || (pl.tail >= 0 && !has_bt(pl.tail))) return false;
+    return 2.0 * M * s.C * Kd < 1e10;
+}
+
 // A large 1x1 filter at stride 1 (FullyConnected) is read in place, as transposed tiles, when the chosen
 // tile has that variant: copying it would cost more than the slower operand fetch.
 bool bwd_data_reads_filter_in_place(const ConvShape &s)
@@ -1166,12 +1205,11 @@ int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStrea
     return relayout(&job, 1, st);
 }
 
-// wt: the filter as igemm_bwd_data_prepare left it; w_in_place: the filter the in-place variant reads
-// (the caller's KRSC filter, or its copy in wt)
+// wt: the filter as igemm_bwd_data_prepare left it; w_in_place: if not null, the KRSC filter that the in-place variant reads
 int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, void *dx, const void *wt, hipStream_t st,
                    const char **variant, const PostOp &post, void *split_ws)
 {
-    const bool bt = bwd_data_reads_filter_in_place(s);
+    const bool bt = w_in_place != nullptr;
     IgemmParams p{};
     p.in = (const bf16_t *)dy; p.out = (bf16_t *)dx;
     p.mask = (const bf16_t *)post.mask;
@@ -1182,7 +1220,7 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
     if (s.stride == 1) {
         // one class: rows h = hh - pad of hh = pad, pad + 1, ...
         p.wm = bt ? (const bf16_t *)w_in_place : (const bf16_t *)wt;
-        p.bt_w_bytes = (unsigned)((long long)s.K * s.C * 2);
+        p.bt_w_bytes = (unsigned)((long long)real_k(s) * s.R * s.S * s.C * 2);
         p.TR = s.R; p.TS = s.S; p.Mh = s.H; p.Mw = s.W; p.in_off_h = s.pad; p.in_off_w = s.pad;
         const long long M = (long long)s.N * s.H * s.W;
         const int Kd = s.R * s.S * s.K;

@@ -227,6 +227,8 @@ size_t igemm_bwd_data_split_bytes(const ConvShape &s);   // scratch for a split 
 int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStream_t st, bool copy_in_place_filter, bool kcrs = false);
 // whether igemm_bwd_data reads this layer's filter as it is; otherwise relay_bwd_filter makes the form it reads
 bool bwd_data_reads_filter_in_place(const ConvShape &s);
+// ... or reads the KRSC filter it is handed in place although its prepared form is the re-packed one
+bool bwd_data_small_in_place(const ConvShape &s, bool masked);
 int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, void *dx, const void *wt, hipStream_t st,
                    const char **variant, const PostOp &post = PostOp(), void *split_ws = nullptr);
 
@@ -276,8 +278,8 @@ struct IgemmParams {
                          // different tile shapes: see Plan); tile 0 starts at m_begin
     int m_tiles, n_tiles;
     unsigned in_bytes, wm_bytes;   // sizes of the two operand buffers (< 2^31)
-    // BT kernels (1x1 stride-1 backward-data straight from the filter, no transposed copy): wm = w[K][Co];
-    // reduction index k reads filter row k, whose Co output columns are contiguous.  Needs Ci % 64 == 0.
+    // BT kernels (stride-1 backward-data straight from the filter, no re-packed copy): wm = w[K][T][Co]; reduction element
+    // (tap, k) is filter row k*T + tap, whose Co output columns are contiguous.
     unsigned bt_w_bytes; // size of the filter
     // split reduction (few tiles, long reduction): workgroup (tile, z) runs stages [z*split_stages, (z+1)*split_stages)
     // and stores its fp32 accumulators to partial[z][m][co]; a second kernel adds the splits in ascending z and

@@ -29,7 +29,7 @@ def _check(mxc, oracle, dims, seed, expect):
     run = util.Runner(mxc, dims, "bf16", "nhwc")
     dx = torch.full((N * C * H * W,), float("nan"), dtype=torch.bfloat16, device="cuda")
     mxc.mxc_conv2d_bwd_data_relu(*dims, run.dt, run.lay, run._in(dy), run._in(w), run._in(x), dx, run._ws(mxc.MXC_BWD_DATA_RELU))
-    assert mxc.mxc_last_variant().split(":")[-1] == expect, mxc.mxc_last_variant()
+    assert mxc.mxc_last_variant().split(":")[-1].split("_inplace")[0] == expect, mxc.mxc_last_variant()
     ref, den = oracle.conv2d_bwd_data_relu(dy, w, x, st, pad)
     got = run._out(dx, (N, C, H, W))
     assert np.all(np.abs(got - ref) <= util.tight_bound(ref, den, "bf16", True)), dims
@@ -53,3 +53,13 @@ def test_masked_stream(mxc, oracle, monkeypatch, dims):
 def test_strided_classes(mxc, oracle, monkeypatch, tile, dims):
     monkeypatch.setenv("MXC_FORCE_VARIANT", tile)
     _check(mxc, oracle, dims, 3, tile)
+
+
+# filters read in place as transposed tiles: taps with channels that fill stages or straddle them, column remainders, a
+# reduction shorter than one stage, split and whole reductions
+@pytest.mark.parametrize("dims", [(2, 72, 9, 11, 64, 3, 3, 1, 1), (1, 136, 7, 9, 24, 5, 3, 1, 2), (2, 8, 13, 12, 8, 1, 1, 1, 0), (1, 264, 8, 9, 192, 3, 3, 1, 0)])
+@pytest.mark.parametrize("splits", ["/1", "/2"])
+@pytest.mark.parametrize("tile", ["igemm_128x128_k64s2_w4", "igemm_256x256_k64s2_w8", "igemm_128x64_k64s2_w4", "igemm_128x32_k64s2_w4", "igemm_64x128_k64s3_w4"])
+def test_in_place_filter(mxc, oracle, monkeypatch, tile, splits, dims):
+    monkeypatch.setenv("MXC_FORCE_VARIANT", tile + splits)
+    _check(mxc, oracle, dims, 4, tile)
