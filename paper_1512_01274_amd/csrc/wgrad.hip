@@ -370,6 +370,53 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec4_kernel(const float4 *pa
     if (grp == 0 && gid < total4) store4(dw, gid, acc);
 }
 
+// Where an element of the summed [K][ncols] tensor belongs: dw has the same order, or it is dw[k][r][s][c] (or
+// dw[k][c][r][s]) of column (r/d)*col_r + (s/d)*col_s + ((r%d)*d + s%d)*Cq + c, and padded rows and columns are dropped.
+enum { DW_SAME = 0, DW_KRSC = 1, DW_KCRS = 2 };
+struct DwMap {
+    int order, ncols, Kout, R, S, C, col_r, col_s, d, Cq;
+};
+
+// Many splits of a small dw, and every dw whose order differs from the columns': the four waves of a workgroup share 64/G
+// groups of four outputs, so 4*G splits are in flight per output, and the sums go to their places from LDS.  What bounds
+// it is the chain of dependent additions and the launch: as two launches (a wave's 16 groups, then the re-ordering one
+// float at a time) 512 splits of 64x3x3x3 took 16 us, 170 of 64x11x11x3 11; the training step of the first (224x224, batch
+// 32) went from 226 to 218 us with one, that of a ragged 30->50 NCHW layer from 81 to 78.
+template <int G, typename OUT>
+__global__ __launch_bounds__(256) void wgrad_reduce_map_kernel(const float4 *__restrict__ partial, OUT *__restrict__ dw, int total4, int splits,
+                                                               size_t split_stride4, const DwMap m)
+{
+    constexpr int LPG = 64 / G;
+    __shared__ float4 red[4][LPG];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int at = blockIdx.x * LPG + lane % LPG;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (at < total4)
+#pragma unroll 4
+        for (int z = wave * G + lane / LPG; z < splits; z += 4 * G) {
+            const float4 v = partial[(size_t)z * split_stride4 + at];
+            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+        }
+#pragma unroll
+    for (int d = LPG; d < 64; d <<= 1) {
+        const float4 o = shfl_xor4(acc, d);
+        acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w;
+    }
+    if (lane < LPG) red[wave][lane] = acc;
+    __syncthreads();
+    const int t = threadIdx.x, e = blockIdx.x * (LPG * 4) + t;
+    if (t >= LPG * 4 || e >= total4 * 4) return;
+    const float *r0 = reinterpret_cast<const float *>(red);
+    const float v = ((r0[t] + r0[LPG * 4 + t]) + r0[LPG * 8 + t]) + r0[LPG * 12 + t];
+    if (m.order == DW_SAME) { store_f32(dw + e, v); return; }
+    const int k = e / m.ncols, col = e - k * m.ncols;
+    const int rb = col / m.col_r, in_r = col - rb * m.col_r, sb = in_r / m.col_s, in_s = in_r - sb * m.col_s;
+    const int blk = m.d > 1 ? in_s / m.Cq : 0, c = in_s - blk * m.Cq;
+    const int r = rb * m.d + blk / m.d, sc = sb * m.d + blk % m.d;
+    if (k >= m.Kout || r >= m.R || sc >= m.S || c >= m.C) return;
+    store_f32(dw + (m.order == DW_KRSC ? (((size_t)k * m.R + r) * m.S + sc) * m.C + c : (((size_t)k * m.C + c) * m.R + r) * m.S + sc), v);
+}
+
 // General form: dw[k][r][s][c] is read back from column (r/d)*col_r + (s/d)*col_s + ((r%d)*d + s%d)*Cq + c of
 // partial[z][k][.], d = s2d (1 for everything but space-to-depth operands, where it is the stride).  The
 // re-packed operands of odd channel counts have wider columns that are dropped here.  One output per lane.
@@ -603,21 +650,22 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
     // many splits of a small dw: 16 lane groups keep enough loads in flight; otherwise 4
     const bool wide = splits >= 32 && total < 256 * 1024;
     // KCRS: a workgroup of the reordering kernel adds up 64*R*S results; where that would be a long chain for each of its
-    // threads (112 splits of a 50x30x3x3 filter: 65 us) the splits are added first, as below
+    // threads (112 splits of a 50x30x3x3 filter: 65 us) the mapped reduction does it
     const bool kcrs_long = kcrs && (long long)splits * g.R * g.S > 128;
-    if ((kcrs ? kcrs_long : !identity) && splits > 1) {
-        // Packed geometries (first layers): the column remap reads single floats, so first add the splits with the
-        // 16-byte kernel - in place, into the first split's partial tensor: every element is read and then written
-        // by the same lane group - and remap that one tensor afterwards.
-        const int cols4 = g.K * ncols / 4;            // ncols is a multiple of 8
-        if (wide)
-            hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<16, float>), dim3((unsigned)((cols4 + 15) / 16)), dim3(256), 0, st,
-                               (const float4 *)partial, partial, cols4, splits, (size_t)cols4);
+    const bool same = identity && total % 4 == 0 && split_stride % 4 == 0;
+    if (splits > 1 && (kcrs ? kcrs_long : !identity || (same && wide))) {
+        const bool ident = !kcrs && identity;
+        const DwMap m{ident ? DW_SAME : kcrs ? DW_KCRS : DW_KRSC, ncols, g.Kout, g.R, g.S, g.C, g.col_r, g.col_s, g.s2d, g.Cq};
+        const int total4 = ident ? total / 4 : g.K * ncols / 4;       // ncols is a multiple of 8 where the order differs
+        const size_t stride4 = split_stride / 4;
+        // below 32 splits 16 in flight are enough, and four times as many outputs share a cache line's worth of a split
+        if (splits >= 32)
+            hipLaunchKernelGGL((wgrad_reduce_map_kernel<16, OUT>), dim3((unsigned)((total4 + 3) / 4)), dim3(256), 0, st, (const float4 *)partial, dw,
+                               total4, splits, stride4, m);
         else
-            hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<4, float>), dim3((unsigned)((cols4 + 63) / 64)), dim3(256), 0, st,
-                               (const float4 *)partial, partial, cols4, splits, (size_t)cols4);
-        if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
-        splits = 1;
+            hipLaunchKernelGGL((wgrad_reduce_map_kernel<4, OUT>), dim3((unsigned)((total4 + 15) / 16)), dim3(256), 0, st, (const float4 *)partial, dw,
+                               total4, splits, stride4, m);
+        return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
     }
     if (kcrs) {
         const int RS = g.R * g.S, c_tiles = (g.C + 63) / 64;
@@ -632,13 +680,9 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
                                g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
         return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
     }
-    if (identity && total % 4 == 0 && split_stride % 4 == 0) {
+    if (same) {
         const int total4 = total / 4;
-        if (wide)
-            hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<16, OUT>), dim3((unsigned)((total4 + 15) / 16)), dim3(256), 0, st,
-                               (const float4 *)partial, dw, total4, splits, split_stride / 4);
-        else
-            hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<4, OUT>), dim3((unsigned)((total4 + 63) / 64)), dim3(256), 0, st,
+        hipLaunchKernelGGL((wgrad_reduce_vec4_kernel<4, OUT>), dim3((unsigned)((total4 + 63) / 64)), dim3(256), 0, st,
                                (const float4 *)partial, dw, total4, splits, split_stride / 4);
     } else if (wide) {
         hipLaunchKernelGGL((wgrad_reduce_kernel<16, OUT>), dim3((unsigned)((total + 15) / 16)), dim3(256), 0, st, partial, dw, total,
