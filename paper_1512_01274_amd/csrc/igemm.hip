@@ -1174,16 +1174,45 @@ bool igemm_bwd_data_supported(const ConvShape &s)
 
 size_t igemm_bwd_data_workspace(const ConvShape &s) { return (size_t)s.K * s.R * s.S * s.C * sizeof(bf16_t); }
 
+namespace {
+// stride 1: the one launch of the pass
+IgemmParams bwd_data_params(const ConvShape &s)
+{
+    IgemmParams p{};
+    p.N = s.N; p.Hi = s.P; p.Wi = s.Q; p.Ci = s.K; p.pix = s.K; p.Co = s.C; p.Cw = real_c(s);
+    p.tstep_h = -1; p.tstep_w = -1;
+    p.in_mul_h = 1; p.in_mul_w = 1;
+    p.Ho = s.H; p.Wo = s.W; p.out_mul_h = s.stride; p.out_mul_w = s.stride;
+    if (s.stride == 1) {
+        // one class: rows h = hh - pad of hh = pad, pad + 1, ...
+        p.TR = s.R; p.TS = s.S; p.Mh = s.H; p.Mw = s.W; p.in_off_h = s.pad; p.in_off_w = s.pad;
+        p.bt_w_bytes = (unsigned)((long long)real_k(s) * s.R * s.S * s.C * 2);
+    }
+    return p;
+}
+
+// whether the whole pass is one launch of the streaming kernel, which then can take the filter as it is
+bool bwd_data_streams_filter(const ConvShape &s, bool masked)
+{
+    const long long M = (long long)s.N * s.H * s.W;
+    const int Kd = s.R * s.S * s.K;
+    return s.stride == 1 && choose_plan(M, s.C, Kd, true, masked).main == STREAM_TILE && split_count(M, s.C, Kd) == 1 &&
+           stream_applicable(bwd_data_params(s));
+}
+}  // namespace
+
 // Whether a call that is handed the KRSC filter itself reads it in place although a prepared filter would be re-packed:
 // the re-pack is a launch of 4-5 us, which a small problem's slower operand fetch does not cost.  Same tile, same order
 // of the reduction, same bits.  Measured over 60 shapes, masked or not: below 2 GFLOP every tile with the variant gains
 // (64x128 2 us, 128x32 and 128x64 3.6 us of 12), at 4-10 GFLOP 2-3 us of 25-35, and from 12 GFLOP on it loses with
 // 64x128 (15%) and breaks even with the others, which is where the line lies.
+// The streaming kernel transposes the filter into its resident copy at any size.
 bool bwd_data_small_in_place(const ConvShape &s, bool masked)
 {
     if (real_c(s) != s.C || s.C % 8 != 0 || s.stride != 1 || bwd_data_reads_filter_in_place(s)) return false;
     const long long M = (long long)s.N * s.H * s.W;
     const int Kd = s.R * s.S * s.K;
+    if (bwd_data_streams_filter(s, masked)) return true;
     const Plan pl = choose_plan(M, s.C, Kd, true, masked);
     if (whole_launch(pl.main) || !has_bt(pl.main) || (pl.tail >= 0 && !has_bt(pl.tail))) return false;
     return 2.0 * M * s.C * Kd < 1e10;
@@ -1210,23 +1239,17 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
                    const char **variant, const PostOp &post, void *split_ws)
 {
     const bool bt = w_in_place != nullptr;
-    IgemmParams p{};
+    IgemmParams p = bwd_data_params(s);
     p.in = (const bf16_t *)dy; p.out = (bf16_t *)dx;
     p.mask = (const bf16_t *)post.mask;
-    p.N = s.N; p.Hi = s.P; p.Wi = s.Q; p.Ci = s.K; p.pix = s.K; p.Co = s.C; p.Cw = real_c(s);
-    p.tstep_h = -1; p.tstep_w = -1;
-    p.in_mul_h = 1; p.in_mul_w = 1;
-    p.Ho = s.H; p.Wo = s.W; p.out_mul_h = s.stride; p.out_mul_w = s.stride;
     if (s.stride == 1) {
-        // one class: rows h = hh - pad of hh = pad, pad + 1, ...
         p.wm = bt ? (const bf16_t *)w_in_place : (const bf16_t *)wt;
-        p.bt_w_bytes = (unsigned)((long long)real_k(s) * s.R * s.S * s.C * 2);
-        p.TR = s.R; p.TS = s.S; p.Mh = s.H; p.Mw = s.W; p.in_off_h = s.pad; p.in_off_w = s.pad;
+        p.wm_by_k = bt && !bwd_data_reads_filter_in_place(s) && bwd_data_streams_filter(s, p.mask != nullptr);
         const long long M = (long long)s.N * s.H * s.W;
         const int Kd = s.R * s.S * s.K;
         const int sp = (split_ws != nullptr && s.C % 8 == 0) ? split_count(M, s.C, Kd) : 1;
-        Plan pl = plan_for(p, M, s.C, Kd, bt || sp > 1);
-        if (bt && !has_bt(pl.tail)) pl = Plan{pl.main, -1, 0};
+        Plan pl = plan_for(p, M, s.C, Kd, (bt && !p.wm_by_k) || sp > 1);
+        if (bt && !p.wm_by_k && !has_bt(pl.tail)) pl = Plan{pl.main, -1, 0};
         *variant = plan_name(pl);
         if (sp > 1) return launch_split(pl.main, p, M, sp, split_ws, dx, post, st, variant, bt);
         return launch_plan(pl, p, st, bt);

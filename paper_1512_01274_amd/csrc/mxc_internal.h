@@ -281,6 +281,7 @@ struct IgemmParams {
     // BT kernels (stride-1 backward-data straight from the filter, no re-packed copy): wm = w[K][T][Co]; reduction element
     // (tap, k) is filter row k*T + tap, whose Co output columns are contiguous.
     unsigned bt_w_bytes; // size of the filter
+    int wm_by_k;         // streaming kernel: wm is that filter too, transposed on its way into LDS
     // split reduction (few tiles, long reduction): workgroup (tile, z) runs stages [z*split_stages, (z+1)*split_stages)
     // and stores its fp32 accumulators to partial[z][m][co]; a second kernel adds the splits in ascending z and
     // applies bias / ReLU / mask.  splits <= 1: off.

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
 
     // ---- resident filter: every wave fetches its share once.  Row r, 16-byte chunk c of stage kt lives at
     // chunk position c ^ ((r/2) % 8) of that row (the swizzle the operand reads below undo).
-    {
+    if (!p.wm_by_k) {
         const int per_stage = BN / 8;               // wave-wide loads per stage (8 rows each)
         for (int idx = wave; idx < KT * per_stage; idx += NW) {
             const int kt = idx / per_stage, i = idx % per_stage;
@@ -315,6 +315,36 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
     const unsigned st_lane_off = (unsigned)((st_r * p.Co + n0 + st_c * 8) * 2);
     const bf16_t *st_src = stg + st_r * EW + stg_chunk(st_r, st_c);   // RPI is a multiple of CPR << LB: same chunk position for every k
 
+    if (p.wm_by_k) {
+        // Backward-data straight from w[K][T][Co]: a thread fetches 8 output columns of 8 consecutive reduction elements and
+        // turns the block over in registers.  At most three blocks a thread, fetched while the loaders fill the ring (by all
+        // waves, before the ring starts, cost a small layer 1.3 us more), where the transposed copy was a launch of its own:
+        // training step of 1x1 192->64 at 28x28, batch 128: 63.0 -> 60.9 us.
+        const out_rsrc_t rs_w = make_out_rsrc(const_cast<bf16_t *>(p.wm), p.bt_w_bytes);
+        for (int idx = tid; idx < BN * KT; idx += 64 * NC) {
+            const int cb = idx % (BN / 8), q = idx / (BN / 8), kd = q * 8;      // Ci % 8 == 0: one tap per block
+            const int tap = kd / p.Ci, k = kd - tap * p.Ci;
+            const bool ok = kd < Kd && n0 + cb * 8 < p.Co;
+            const unsigned off = (unsigned)((k * T + tap) * p.Co + n0 + cb * 8) * 2u, step = (unsigned)(T * p.Co) * 2u;
+            uint32_t v[8][4];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {           // rows of a padded K lie past the end: zeros
+                const uint4 row = buffer_load16(rs_w, ok ? off + (unsigned)j * step : OOB);
+                v[j][0] = row.x; v[j][1] = row.y; v[j][2] = row.z; v[j][3] = row.w;
+            }
+            bf16_t *dst = sB + (size_t)(q >> 3) * BN * BK + cb * 8 * BK;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const uint32_t sel = r & 1 ? 0x07060302u : 0x05040100u;
+                uint32_t o[4];
+#pragma unroll
+                for (int d = 0; d < 4; ++d) o[d] = __builtin_amdgcn_perm(v[2 * d + 1][r >> 1], v[2 * d][r >> 1], sel);
+                // row cb*8 + r: its (row / 2) % 8 is (4*cb + r/2) % 8
+                *reinterpret_cast<uint4 *>(dst + r * BK + (((q & 7) ^ ((4 * cb + (r >> 1)) & 7)) << 3)) = make_uint4(o[0], o[1], o[2], o[3]);
+            }
+        }
+        wait_lgkmcnt0();
+    }
     wait_vmcnt<0>();                                // this wave's share of the filter
     wg_barrier();                                   // filter and stage 0 complete
     reset_acc();

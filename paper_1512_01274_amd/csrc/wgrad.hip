@@ -380,7 +380,7 @@ struct DwMap {
 // Many splits of a small dw, and every dw whose order differs from the columns': the four waves of a workgroup share 64/G
 // groups of four outputs, so 4*G splits are in flight per output, and the sums go to their places from LDS.  What bounds
 // it is the chain of dependent additions and the launch: as two launches (a wave's 16 groups, then the re-ordering one
-// float at a time) 512 splits of 64x3x3x3 took 16 us, 170 of 64x11x11x3 11; the training step of the first (224x224, batch
+// float at a time) 512 splits of 64x3x3x3 took 16 us, 170 of 64x11x11x3 11 (now 5 and 8.5); the training step of the first (224x224, batch
 // 32) went from 226 to 218 us with one, that of a ragged 30->50 NCHW layer from 81 to 78.
 template <int G, typename OUT>
 __global__ __launch_bounds__(256) void wgrad_reduce_map_kernel(const float4 *__restrict__ partial, OUT *__restrict__ dw, int total4, int splits,

@@ -63,3 +63,12 @@ def test_strided_classes(mxc, oracle, monkeypatch, tile, dims):
 def test_in_place_filter(mxc, oracle, monkeypatch, tile, splits, dims):
     monkeypatch.setenv("MXC_FORCE_VARIANT", tile + splits)
     _check(mxc, oracle, dims, 4, tile)
+
+
+# the streaming kernel transposes the filter on its way into LDS: one and several taps, reductions that end inside a stage,
+# one and two column tiles with remainders, channels of dy that are padding
+@pytest.mark.parametrize("dims", [(3, 64, 19, 17, 192, 1, 1, 1, 0), (2, 8, 13, 15, 8, 1, 1, 1, 0), (1, 136, 9, 8, 72, 1, 1, 1, 0), (2, 24, 12, 11, 24, 3, 3, 1, 1),
+                                  (2, 40, 10, 9, 20, 3, 2, 1, 1)])
+def test_stream_filter_in_place(mxc, oracle, monkeypatch, dims):
+    monkeypatch.setenv("MXC_FORCE_VARIANT", "igemm_stream")
+    _check(mxc, oracle, dims, 5, "igemm_stream")
