@@ -247,14 +247,20 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
         void *dx2 = run ? ws.take((size_t)s2.N * s2.H * s2.W * s2.C * 2) : nullptr;
         if (dry) return MXC_OK;
         const char *v = "";
+        const S2DStore image{s.stride, s.pad, s.C, s2d_geom(s).Cq, s.H, s.W};
+        const ImageStore direct = post.mask == nullptr ? igemm_bwd_data_image_store(s2, image) : IMAGE_NONE;
+        const void *in_place = nullptr;
+        if (bwd_data_reads_filter_in_place(s2)) in_place = wt;
+        else if (mode == FILTER_RAW && (direct == IMAGE_STREAM || (direct == IMAGE_NONE && bwd_data_small_in_place(s2, false)))) in_place = w2;
         if (prep) {
             MXC_TRY(s2d_pack_w(s, w, w2, st));
-            MXC_TRY(igemm_bwd_data_prepare(s2, w2, wt, st, true));
+            if (in_place != w2) MXC_TRY(igemm_bwd_data_prepare(s2, w2, wt, st, true));
         }
         if (!run) return MXC_OK;
-        MXC_TRY(igemm_bwd_data(s2, dy, bwd_data_reads_filter_in_place(s2) ? wt : nullptr, dx2, wt, st, &v));
+        if (direct != IMAGE_NONE) MXC_TRY(igemm_bwd_data_image(direct, s2, image, dy, in_place, wt, dx, st, &v));
+        else MXC_TRY(igemm_bwd_data(s2, dy, in_place, dx2, wt, st, &v));
         set_variant("bwd_data", (std::string("s2d+") + v).c_str());
-        return s2d_unpack_dx(s, dx2, dx, st, post.mask);      // the mask is applied where dx itself is written
+        return direct != IMAGE_NONE ? MXC_OK : s2d_unpack_dx(s, dx2, dx, st, post.mask);      // the mask is applied where dx itself is written
     }
     if (dtype == MXC_BF16 && igemm_bwd_data_smallc_supported(s)) {
         size_t w2_bytes, dx4_bytes;

@@ -1201,6 +1201,43 @@ bool bwd_data_streams_filter(const ConvShape &s, bool masked)
 }
 }  // namespace
 
+// Needs columns of one staging pass and every image pixel inside some block of the packed grid (one that is not has a zero
+// that nobody would write).
+ImageStore igemm_bwd_data_image_store(const ConvShape &s2, const S2DStore &q)
+{
+    if (s2.stride != 1 || s2.C > 64 || s2.H * q.s - q.pad < q.H || s2.W * q.s - q.pad < q.W || q.H >= 16384 || q.W >= 16384 ||
+        (long long)s2.N * q.H * q.W * q.C * 2 >= 0x7FFF0000ll || bwd_data_reads_filter_in_place(s2))
+        return IMAGE_NONE;
+    IgemmParams p = bwd_data_params(s2);
+    p.s2d = q;
+    const long long M = (long long)s2.N * s2.H * s2.W;
+    const int Kd = s2.R * s2.S * s2.K;
+    const bool stream = stream_applicable(p), window = window_applicable(p);
+    if (getenv("MXC_FORCE_VARIANT")) {
+        const int f = choose_plan(M, s2.C, Kd).main;
+        return f == STREAM_TILE && stream ? IMAGE_STREAM : f == WINDOW_TILE && window ? IMAGE_WINDOW : IMAGE_NONE;
+    }
+    // Against the planned kernel with the separate un-packing (20 us for 128 224x224x3 images), input gradients in us, before ->
+    // streaming / window: Kd = 64 (3x3 stride 2, K = 16, 200 100x100 images) 38 -> 27 / 37; Kd = 128 33 -> 30 / 29; Kd = 256 38 ->
+    // 38 / 33; Kd = 320 36 -> 35 / -; Kd = 384 60 -> 65 / -; 11x11 stride 4, K = 64, batch 128 (Kd = 576) 66 -> 104 / 62; 7x7
+    // stride 2, K = 64, batch 64 (Kd = 1024) 127 -> 256 / 88; with patches half empty (35x35 blocks) or too few the window
+    // kernel loses up to 1 us of 18.
+    if (Kd <= 64 && stream) return IMAGE_STREAM;
+    if (window && window_fills_chip(p)) return IMAGE_WINDOW;
+    return Kd <= 320 && stream ? IMAGE_STREAM : IMAGE_NONE;
+}
+
+int igemm_bwd_data_image(ImageStore kind, const ConvShape &s2, const S2DStore &q, const void *dy, const void *w2, const void *wt, void *dx, hipStream_t st,
+                         const char **variant)
+{
+    IgemmParams p = bwd_data_params(s2);
+    p.in = (const bf16_t *)dy; p.out = (bf16_t *)dx; p.s2d = q;
+    p.wm = (const bf16_t *)(w2 != nullptr ? w2 : wt);
+    p.wm_by_k = w2 != nullptr;
+    *variant = kind == IMAGE_STREAM ? kStreamName : kWindowName;
+    return kind == IMAGE_STREAM ? stream_launch(p, st) : window_launch(p, st);
+}
+
 // Whether a call that is handed the KRSC filter itself reads it in place although a prepared filter would be re-packed:
 // the re-pack is a launch of 4-5 us, which a small problem's slower operand fetch does not cost.  Same tile, same order
 // of the reduction, same bits.  Measured over 60 shapes, masked or not: below 2 GFLOP every tile with the variant gains

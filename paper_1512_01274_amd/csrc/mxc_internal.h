@@ -144,6 +144,72 @@ __device__ __forceinline__ uint4 buffer_load16(out_rsrc_t rsrc, unsigned byte_of
     const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)byte_off, 0, 0);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
+// Results that leave un-packed from space-to-depth order (streaming and window kernels): row (n, h2, w2), column
+// (dh*s + dw)*Cq + c goes to dx[n][h2*s + dh - pad][w2*s + dw - pad][c] of an N x H x W x C tensor; s = 0: off.
+struct S2DStore {
+    int s, pad, C, Cq, H, W;
+};
+
+__host__ __device__ inline bool s2d_pairs(const S2DStore &q)
+{
+    return q.Cq == q.C && (q.s * q.C) % 2 == 0 && (q.pad * q.C) % 2 == 0 && (q.W * q.C) % 2 == 0;
+}
+// store instructions for the 32 rows of a wave (s is even)
+__host__ __device__ inline int s2d_stores(const S2DStore &q) { return q.s * (q.s * q.C / (s2d_pairs(q) ? 2 : 1)) / 2; }
+
+// Stores the 32 rows of a wave from its staging area.  A unit is two neighbouring elements of an image row where the two
+// always share a dword, else one.  Units are numbered (dh, row, place in the row's run of s*C elements): for one dh the
+// units of consecutive rows are consecutive in the image, so a store instruction writes 128 or 256 bytes in a piece.
+struct S2DWave {
+    bool pair;
+    int run_u, u0, r0, du, dr;      // units per run; this lane's first unit, and the step to the one 64 further on
+    __device__ __forceinline__ S2DWave(const S2DStore &q, int lane)
+    {
+        pair = s2d_pairs(q);
+        run_u = q.s * q.C / (pair ? 2 : 1);
+        r0 = lane / run_u; u0 = lane - r0 * run_u;
+        dr = 64 / run_u; du = 64 - dr * run_u;
+    }
+    __device__ __forceinline__ int stores(const S2DStore &q) const { return q.s * run_u / 2; }
+    __device__ __forceinline__ void next(int &u, int &r, int &dh) const
+    {
+        u += du;
+        const int carry = u >= run_u ? 1 : 0;
+        u -= carry ? run_u : 0;
+        r += dr + carry;
+        dh += r >> 5;
+        r &= 31;
+    }
+    // the GEMM's column of element e of the run at dh
+    __device__ __forceinline__ int column(const S2DStore &q, int dh, int e) const
+    {
+        if (q.Cq == q.C) return dh * q.s * q.C + e;
+        const int dw = q.C == 3 ? (e * 86) >> 8 : q.C == 2 ? e >> 1 : e;        // e / C: C <= 3 and e < 16 here
+        return (dh * q.s + dw) * q.Cq + e - dw * q.C;
+    }
+    // lane l (and l + 32) brings row l's position: image n, block (h2, w2), or ok = false; staged(r, col) points at a result
+    template <class F>
+    __device__ __forceinline__ void store(const S2DStore &q, out_rsrc_t rs_out, int n, int h2, int w2, bool row_ok, F &&staged) const
+    {
+        const int h0 = h2 * q.s - q.pad, w0 = w2 * q.s - q.pad;
+        const int base = ((n * q.H + h0) * q.W + w0) * q.C;
+        const int hw = row_ok ? (h0 & 0xFFFF) | (w0 << 16) : (-16384) & 0xFFFF;
+        const int row_e = q.W * q.C, iters = stores(q);
+        int u = u0, r = r0 & 31, dh = r0 >> 5;
+        for (int k = 0; k < iters; ++k) {
+            const int rb = __shfl(base, r), rhw = __shfl(hw, r);
+            const int e = pair ? 2 * u : u;
+            const uint16_t *src = staged(r, column(q, dh, e));
+            const int h = (int)(short)rhw + dh, we = (rhw >> 16) * q.C + e;
+            const bool ok = (unsigned)h < (unsigned)q.H && (unsigned)we < (unsigned)row_e;
+            const unsigned off = ok ? (unsigned)(rb + dh * row_e + e) * 2u : 0x80000000u;      // rejected by the resource
+            if (pair) __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const uint32_t *>(src), rs_out, (int)off, 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b16(*src, rs_out, (int)off, 0, 0);
+            next(u, r, dh);
+        }
+    }
+};
+
 __device__ __forceinline__ uint4 mask_bf16x8(uint4 v, uint4 m)
 {
     return make_uint4(mask_bf16x2(v.x, m.x), mask_bf16x2(v.y, m.y), mask_bf16x2(v.z, m.z), mask_bf16x2(v.w, m.w));
@@ -231,6 +297,12 @@ bool bwd_data_reads_filter_in_place(const ConvShape &s);
 bool bwd_data_small_in_place(const ConvShape &s, bool masked);
 int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, void *dx, const void *wt, hipStream_t st,
                    const char **variant, const PostOp &post = PostOp(), void *split_ws = nullptr);
+// stride-1 backward-data whose result is stored un-packed from space-to-depth order: the kernel that can and should, or none
+enum ImageStore { IMAGE_NONE = 0, IMAGE_STREAM, IMAGE_WINDOW };
+ImageStore igemm_bwd_data_image_store(const ConvShape &s2, const S2DStore &q);
+// w2: the KRSC filter where the streaming kernel is to read it, or null: wt, as igemm_bwd_data_prepare left it
+int igemm_bwd_data_image(ImageStore kind, const ConvShape &s2, const S2DStore &q, const void *dy, const void *w2, const void *wt, void *dx, hipStream_t st,
+                         const char **variant);
 
 // backward-data for C <= 4: G output columns form one GEMM row (see igemm.hip)
 bool igemm_bwd_data_smallc_supported(const ConvShape &s);
@@ -288,6 +360,7 @@ struct IgemmParams {
     float *partial;
     int splits, split_stages;
     int tap_row_inner;   // tap t = (column step)*TR + (row step) instead of (row step)*TS + (column step)
+    S2DStore s2d;        // `out` is the image and not the GEMM's [m][co]
     int f32_out;         // store the fp32 accumulators to `partial` ([m][co], one split) instead of a rounded result to `out`
     int nt_out;          // the 16-byte result stores are non-temporal
     unsigned out_bytes;  // size of the output tensor when below 2 GiB (buffer stores with range-checked offsets), else 0
@@ -318,6 +391,8 @@ int stream_launch(const IgemmParams &p, hipStream_t st);
 // window.hip: the same GEMM for multi-tap stride-1 layers of at most 64 input channels, from an LDS-resident input
 // window and filter (see there); same conventions as the streaming kernel.
 bool window_applicable(const IgemmParams &p);
+// two patches or more for every CU, at most a third of their rows past the image
+bool window_fills_chip(const IgemmParams &p);
 int window_launch(const IgemmParams &p, hipStream_t st);
 
 // ---- prep.hip: re-packing for channel counts that are not a multiple of 8 ---------

@@ -57,11 +57,14 @@ struct StreamParams {
 
 // NC compute waves (row tile BM = 32*NC), NL loader waves, column tile BN (32, 64 or 128), NS ring stages.
 // Dynamic LDS: [filter BN x KT*64][ring NS x BM x 64][staging NC x 32 x min(BN,64)][tap table][bias BN].
-// MASK: results are zeroed where p.mask <= 0 (a variant of its own: its registers would spill the plain one).
-template <int NC, int NL, int BN, int NS, bool MASK>
+// EPI: how results leave.  EPI_MASK: zeroed where p.mask <= 0; EPI_S2D: un-packed into an image (p.s2d).  (Variants of their
+// own: their registers would spill the plain one.)
+enum { EPI_PLAIN = 0, EPI_MASK = 1, EPI_S2D = 2 };
+template <int NC, int NL, int BN, int NS, int EPI>
 __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamParams sp)
 {
     const IgemmParams &p = sp.g;
+    constexpr bool MASK = EPI == EPI_MASK;
     constexpr int BM = 32 * NC, NW = NC + NL;
     constexpr int NI = BN / 32;
     constexpr int A_LD = BM / 8 / NL;               // wave-wide loads per loader wave per stage (8 tile rows each)
@@ -357,6 +360,8 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
         const bool ok = n0 + jc * 64 + st_c * 8 < p.Co && st_r + k * RPI < wg_hi - m0;
         return ok ? st_lane_off + (unsigned)m0 * (unsigned)(p.Co * 2) + (unsigned)(jc * 128 + k * RPI * p.Co * 2) : OOB;   // below 2^32: the output is below 2^31
     };
+    static_assert(EPI != EPI_S2D || BN <= 64, "one staging pass");
+    [[maybe_unused]] S2DWave s2d_wave(p.s2d.s != 0 ? p.s2d : S2DStore{2, 0, 2, 2, 1, 1}, lane);
     for (int g = 0; g < total; ++g) {
         [[maybe_unused]] uint4 mk[NJC][NST];
         const bf16_t *a_st = a_base + slot * STG_A;
@@ -395,7 +400,12 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (fast_store) {
+            if constexpr (EPI == EPI_S2D) {
+                const int m = m0 + frag_row;
+                const unsigned b = (unsigned)m % (unsigned)p.Mw, t2 = (unsigned)m / (unsigned)p.Mw;
+                s2d_wave.store(p.s2d, rs_out, (int)(t2 / (unsigned)p.Mh), (int)(t2 % (unsigned)p.Mh), (int)b, m < wg_hi, [&](int r, int col) {
+                    return stg + r * EW + stg_chunk(r, col >> 3) + ((col & 7) ^ (((r >> 3) & 1) << 2)); });
+            } else if (fast_store) {
 #pragma unroll
                 for (int k = 0; k < NST; ++k) {
                     uint4 v = swap_halves(*reinterpret_cast<const uint4 *>(st_src + k * RPI * EW), ((st_r + k * RPI) >> 3) & 1);
@@ -465,12 +475,12 @@ StreamConfig stream_config(const IgemmParams &p)
     return StreamConfig{0, 0, 0, 0, false};
 }
 
-template <int NC, int NL, int BN, int NS, bool MASK>
+template <int NC, int NL, int BN, int NS, int EPI>
 int launch_stream_m(StreamParams sp, int lds, hipStream_t st)
 {
     static bool attr_set = false;      // raising the dynamic-LDS limit is idempotent; racing threads set the same value
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&stream_kernel<NC, NL, BN, NS, MASK>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&stream_kernel<NC, NL, BN, NS, EPI>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 160 * 1024) != hipSuccess)
             return MXC_ERR_LAUNCH;
         attr_set = true;
@@ -498,18 +508,22 @@ int launch_stream_m(StreamParams sp, int lds, hipStream_t st)
     const long long in_bytes = (long long)p.N * p.Hi * p.Wi * p.pix * 2, out_bytes = (long long)p.N * p.Ho * p.Wo * p.Co * 2;
     sp.nt = (out_bytes >= (32ll << 20) ? 1 : 0) | ((in_bytes >= (64ll << 20) && p.n_tiles == 1 && p.TR * p.TS == 1) ? 2 : 0);
     if (const char *f = getenv("MXC_STREAM_NT")) sp.nt = atoi(f);
-    sp.out_bytes = (unsigned)((long long)p.N * p.Ho * p.Wo * p.Co * 2);
+    sp.out_bytes = EPI == EPI_S2D ? (unsigned)((long long)p.N * p.s2d.H * p.s2d.W * p.s2d.C * 2) : (unsigned)((long long)p.N * p.Ho * p.Wo * p.Co * 2);
     sp.d_n = BM / (p.Mh * p.Mw);
     sp.d_a = BM % (p.Mh * p.Mw) / p.Mw;
     sp.d_b = BM % p.Mw;
-    hipLaunchKernelGGL((stream_kernel<NC, NL, BN, NS, MASK>), dim3((unsigned)(8 * sp.per_xcd)), dim3(64 * (NC + NL)), (size_t)lds, st, sp);
+    hipLaunchKernelGGL((stream_kernel<NC, NL, BN, NS, EPI>), dim3((unsigned)(8 * sp.per_xcd)), dim3(64 * (NC + NL)), (size_t)lds, st, sp);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
 template <int NC, int NL, int BN, int NS>
 int launch_stream(const StreamParams &sp, int lds, hipStream_t st)
 {
-    return sp.g.mask != nullptr ? launch_stream_m<NC, NL, BN, NS, true>(sp, lds, st) : launch_stream_m<NC, NL, BN, NS, false>(sp, lds, st);
+    if (sp.g.s2d.s != 0) {
+        if constexpr (BN <= 64) return launch_stream_m<NC, NL, BN, NS, EPI_S2D>(sp, lds, st);
+        else return MXC_ERR_UNSUPPORTED;
+    }
+    return sp.g.mask != nullptr ? launch_stream_m<NC, NL, BN, NS, EPI_MASK>(sp, lds, st) : launch_stream_m<NC, NL, BN, NS, EPI_PLAIN>(sp, lds, st);
 }
 
 template <int NC, int NL, int NS>

@@ -35,6 +35,7 @@ constexpr unsigned OOB = 0x80000000u;   // a buffer offset no operand reaches: t
 constexpr int NC = 8;                   // compute waves: 256 patch pixels
 constexpr int NL = 4;                   // loader waves
 constexpr int NW = NC + NL;
+constexpr int S2D_STORES = 12;          // store instructions of a wave and patch into an image: up to 3 channels at stride 4
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wg_barrier()
@@ -54,7 +55,8 @@ struct WindowParams {
     int units, per_xcd;  // workgroups in all, and per XCD (a multiple of n_tiles)
     int LWT;             // wave-wide loads per window = ceil(WH*WW / 8)
     int win_bytes;       // bytes of one window buffer (>= the staging area)
-    int b_bytes;         // bytes of the resident filter tile: T * BN * 128
+    int b_rows;          // filter rows of the column tile in LDS: BN, or 16 where there are no more columns
+    int b_bytes;         // bytes of the resident filter tile: T * b_rows * 128
     int oy, ox;          // window origin relative to the patch origin, input coordinates
     unsigned ww_magic;   // ceil(2^22 / WW): exact quotients for dividends < 2^14
     int dq, dr;          // 32 = dq*WW + dr: one loader wave's next load lies 32 window pixels further on
@@ -62,12 +64,15 @@ struct WindowParams {
     int nt;              // results leave as non-temporal stores
 };
 
-// Column tile BN = 32*NI; KSN = Ci/16 k-steps per tap.  Dynamic LDS: [filter T x BN x 64][window 0][window 1][bias BN][tap shifts].
-// MASK: results are zeroed where p.mask <= 0 (a variant of its own: its registers would spill the plain one)
-template <int NI, int KSN, bool MASK>
+// Column tile BN = 32*NI; KSN = Ci/16 k-steps per tap.  Dynamic LDS: [filter T x b_rows x 64][window 0][window 1][bias BN][tap shifts].
+// EPI: how results leave.  EPI_MASK: zeroed where p.mask <= 0; EPI_S2D: un-packed into an image (p.s2d).  (Variants of their
+// own: their registers would spill the plain one.)
+enum { EPI_PLAIN = 0, EPI_MASK = 1, EPI_S2D = 2 };
+template <int NI, int KSN, int EPI>
 __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
 {
     const IgemmParams &p = wp.g;
+    constexpr bool MASK = EPI == EPI_MASK;
     constexpr int BN = 32 * NI;
 
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -102,16 +107,16 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
     const buf_rsrc_t rs_in = make_buf_rsrc(p.in, p.in_bytes);
     const buf_rsrc_t rs_wm = make_buf_rsrc(p.wm, p.wm_bytes);
 
-    // ---- resident filter: every wave fetches its share once.  Tap t is a [BN rows][64 channels] slab; row r keeps
+    // ---- resident filter: every wave fetches its share once.  Tap t is a [b_rows][64 channels] slab; row r keeps
     // 16-byte chunk c at position c ^ ((r/2) % 8); channels past Ci and rows past Co are zeros.
     {
-        constexpr int per_tap = BN / 8;             // wave-wide loads per tap (8 rows each)
+        const int per_tap = wp.b_rows / 8;          // wave-wide loads per tap (8 rows each)
         for (int idx = wave; idx < T * per_tap; idx += NW) {
             const int t = idx / per_tap, i = idx % per_tap;
             const int r = 8 * i + (lane >> 3);
             const int kc = ((lane & 7) ^ ((r >> 1) & 7)) << 3;
             const unsigned off = (n0 + r < p.Co && kc < p.Ci) ? (unsigned)(n0 + r) * (unsigned)(Kd * 2) + (unsigned)((t * p.Ci + kc) * 2) : OOB;
-            lds_dma16(rs_wm, off, sB + (size_t)t * BN * 64 + i * 8 * 64);
+            lds_dma16(rs_wm, off, sB + (t * wp.b_rows + i * 8) * 64);
         }
     }
 
@@ -188,7 +193,7 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
     // ================================= compute waves =======================================================
     const int frag_row = lane & 31, frag_kg = lane >> 5;
     const int frag_swz = (frag_row >> 1) & 7;
-    const bf16_t *b_base = sB + frag_row * 64;
+    const bf16_t *b_base = sB + (frag_row & (wp.b_rows - 1)) * 64;      // 16 rows: the upper half computes columns nobody stores
     constexpr int EW = NI * 32;                     // staging width (columns)
     static_assert(NI == 1 || NI == 2, "one staging pass");
     constexpr int CPR = EW / 8;                     // 16-byte chunks per staged row
@@ -230,7 +235,7 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
         const int P = pbase + tap_shift[t];
         const bf16_t *row = w_st + P * 64;
         const int swz = (P >> 1) & 7;
-        const bf16_t *b_t = b_base + (size_t)t * BN * 64;
+        const bf16_t *b_t = b_base + t * wp.b_rows * 64;
 #pragma unroll
         for (int ks = 0; ks < KSN; ++ks) {
             f.a[ks] = *reinterpret_cast<const bf16x8 *>(row + (((ks * 2 + frag_kg) ^ swz) << 3));
@@ -249,6 +254,28 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
 
     wait_vmcnt<0>();                                // this wave's share of the filter
     PatchPos pos = first_patch();
+    [[maybe_unused]] int patch_n = 0, patch_y = 0, patch_x = 0;
+    // EPI_S2D: every unit this lane stores, worked out once: where it is staged, (dh, place in the wave's run), its offset in
+    // the image (worked out per patch they were as many instructions as the patch's MFMAs took)
+    constexpr int NSD = EPI == EPI_S2D ? S2D_STORES : 1;
+    [[maybe_unused]] int s2d_src[NSD], s2d_at[NSD], s2d_n = 0;
+    [[maybe_unused]] unsigned s2d_off[NSD];
+    [[maybe_unused]] bool s2d_pair = false;
+    [[maybe_unused]] const S2DStore &q = p.s2d;
+    if constexpr (EPI == EPI_S2D) {
+        const S2DWave u(q, lane);
+        s2d_pair = u.pair;
+        s2d_n = u.stores(q);
+        int at = u.u0, r = u.r0 & 31, dh = u.r0 >> 5;
+#pragma unroll
+        for (int k = 0; k < S2D_STORES; ++k) {
+            const int e = u.pair ? 2 * at : at, col = u.column(q, dh, e), x = r * q.s * q.C + e;
+            s2d_src[k] = r * EW + stg_chunk(r, (col >> 3) & (CPR - 1)) + ((col & 7) ^ (((r >> 3) & 1) << 2));
+            s2d_at[k] = (dh & 0xFF) | x << 16;
+            s2d_off[k] = (unsigned)(dh * q.W * q.C + x) * 2u;
+            u.next(at, r, dh);
+        }
+    }
     for (int k = 0; k < my_tiles; ++k) {
         wg_barrier();                               // A(k): window k and (the first time) the filter are whole
         if (k == 0) reset_acc();                    // the bias vector became visible with the barrier
@@ -269,6 +296,7 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
         [[maybe_unused]] uint4 mk[32 / RPI];
         {
             const int n = pos.n, y0 = pos.py * wp.TH, x0 = pos.px * wp.TW;
+            patch_n = n; patch_y = y0; patch_x = x0;
             next_patch(pos);
             const int th = min(wp.TH, p.Mh - y0), tw = min(wp.TW, p.Mw - x0);
             const int lim = (th - 1) | ((tw - 1) << 16);
@@ -303,6 +331,24 @@ __global__ __launch_bounds__(64 * NW) void window_kernel(const WindowParams wp)
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if constexpr (EPI == EPI_S2D) {
+                // the wave's 32 pixels are one run of a row of blocks: bounds for (dh, place in the run) as 16-bit pairs
+                const int ty = row0 / wp.TW, tx = row0 - ty * wp.TW;
+                const int h0 = (patch_y + ty) * q.s - q.pad, e0 = ((patch_x + tx) * q.s - q.pad) * q.C;
+                const bool in = row0 < wp.TH * wp.TW && patch_y + ty < p.Mh;
+                const int h_end = in ? min(q.H - h0, q.s) : 0, e_end = min(q.W * q.C - e0, (min(wp.TW, p.Mw - patch_x) - tx) * q.s * q.C);
+                const int lo = max(-h0, 0) | max(-e0, 0) << 16, hi = (max(h_end, 0) - 1 & 0xFFFF) | (max(e_end, 0) - 1) << 16;
+                const unsigned base = (unsigned)((patch_n * q.H + h0) * q.W * q.C + e0) * 2u;
+#pragma unroll
+                for (int k = 0; k < S2D_STORES; ++k) {
+                    if (k >= s2d_n) break;
+                    const s16x2 d = __builtin_bit_cast(s16x2, s2d_at[k]) - __builtin_bit_cast(s16x2, lo), t2 = __builtin_bit_cast(s16x2, hi) - __builtin_bit_cast(s16x2, s2d_at[k]);
+                    const int bad = (__builtin_bit_cast(int, d) | __builtin_bit_cast(int, t2)) & (int)0x80008000;
+                    const unsigned o = bad == 0 ? base + s2d_off[k] : OOB;
+                    if (s2d_pair) __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const uint32_t *>(stg + s2d_src[k]), rs_out, (int)o, 0, 0);
+                    else __builtin_amdgcn_raw_buffer_store_b16(stg[s2d_src[k]], rs_out, (int)o, 0, 0);
+                }
+            } else
 #pragma unroll
             for (int kk = 0; kk < 32 / RPI; ++kk) {
                 const int r = st_r + kk * RPI;
@@ -330,6 +376,8 @@ int window_bytes(int th, int tw, int TR, int TS, int bn)
     return b < staging ? staging : b;
 }
 
+int slab_rows(const IgemmParams &p) { return p.Co <= 16 ? 16 : p.Co <= 32 ? 32 : 64; }
+
 // Patch shape: TW in {32, 64, 128, 256}, TH = 256 / TW (at most the image height); the one that wastes the fewest rows
 // of the 256-row tiles over an image, ties to the smaller window.  MXC_WINDOW_PATCH=<th>x<tw> (tuning sweeps only).
 WindowConfig window_config(const IgemmParams &p)
@@ -350,7 +398,7 @@ WindowConfig window_config(const IgemmParams &p)
             th = want_th;
         }
         const int wb = window_bytes(th, tw, p.TR, p.TS, bn);
-        const long long lds = (long long)T * bn * 128 + 2ll * wb + bn * 4 + (MAX_TAPS + 1) * 4;
+        const long long lds = (long long)T * slab_rows(p) * 128 + 2ll * wb + bn * 4 + (MAX_TAPS + 1) * 4;
         if (lds > 160 * 1024) continue;
         const long long tiles = (long long)((p.Mh + th - 1) / th) * ((p.Mw + tw - 1) / tw);
         const double eff = (double)p.Mh * p.Mw / (double)(tiles * 256);
@@ -363,24 +411,25 @@ WindowConfig window_config(const IgemmParams &p)
     return best;
 }
 
-template <int NI, int KSN, bool MASK>
+template <int NI, int KSN, int EPI>
 int launch_window_m(WindowParams &wp, int lds, hipStream_t st)
 {
     static bool attr_set = false;
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&window_kernel<NI, KSN, MASK>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&window_kernel<NI, KSN, EPI>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 160 * 1024) != hipSuccess)
             return MXC_ERR_LAUNCH;
         attr_set = true;
     }
-    hipLaunchKernelGGL((window_kernel<NI, KSN, MASK>), dim3((unsigned)(8 * wp.per_xcd)), dim3(64 * NW), (size_t)lds, st, wp);
+    hipLaunchKernelGGL((window_kernel<NI, KSN, EPI>), dim3((unsigned)(8 * wp.per_xcd)), dim3(64 * NW), (size_t)lds, st, wp);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
 template <int NI, int KSN>
 int launch_window(WindowParams &wp, int lds, hipStream_t st)
 {
-    return wp.g.mask != nullptr ? launch_window_m<NI, KSN, true>(wp, lds, st) : launch_window_m<NI, KSN, false>(wp, lds, st);
+    if (wp.g.s2d.s != 0) return launch_window_m<NI, KSN, EPI_S2D>(wp, lds, st);
+    return wp.g.mask != nullptr ? launch_window_m<NI, KSN, EPI_MASK>(wp, lds, st) : launch_window_m<NI, KSN, EPI_PLAIN>(wp, lds, st);
 }
 
 template <int NI>
@@ -407,7 +456,16 @@ bool window_applicable(const IgemmParams &p)
     if ((long long)p.N * p.Hi * p.Wi * p.Ci * 2 >= 0x7FFF0000ll) return false;      // 32-bit byte offsets into the input
     if ((long long)p.N * p.Ho * p.Wo * p.Co * 2 >= 0x7FFF0000ll) return false;      // ... and the output
     if (p.Mh > 0x7FFF || p.Mw > 0x7FFF) return false;
+    if (p.s2d.s != 0 && s2d_stores(p.s2d) > S2D_STORES) return false;
     return window_config(p).ok;
+}
+
+bool window_fills_chip(const IgemmParams &p)
+{
+    const WindowConfig c = window_config(p);
+    if (!c.ok) return false;
+    const long long np = (long long)p.N * ((p.Mh + c.th - 1) / c.th) * ((p.Mw + c.tw - 1) / c.tw);
+    return np >= 512 && np * 512 <= 3ll * p.N * p.Mh * p.Mw;
 }
 
 int window_launch(const IgemmParams &p, hipStream_t st)
@@ -442,13 +500,14 @@ int window_launch(const IgemmParams &p, hipStream_t st)
     wp.per_xcd = ((wp.units + 7) / 8 + q.n_tiles - 1) / q.n_tiles * q.n_tiles;
     wp.LWT = (wp.WH * wp.WW + 7) / 8;
     wp.win_bytes = c.win_bytes;
-    wp.b_bytes = T * c.bn * 128;
+    wp.b_rows = slab_rows(p);
+    wp.b_bytes = T * wp.b_rows * 128;
     wp.oy = p.in_off_h + (p.tstep_h < 0 ? -(p.TR - 1) : 0);
     wp.ox = p.in_off_w + (p.tstep_w < 0 ? -(p.TS - 1) : 0);
     wp.ww_magic = (unsigned)(((1u << 22) + wp.WW - 1) / wp.WW);
     wp.dq = 32 / wp.WW;
     wp.dr = 32 % wp.WW;
-    wp.out_bytes = (unsigned)((long long)p.N * p.Ho * p.Wo * p.Co * 2);
+    wp.out_bytes = p.s2d.s != 0 ? (unsigned)((long long)p.N * p.s2d.H * p.s2d.W * p.s2d.C * 2) : (unsigned)((long long)p.N * p.Ho * p.Wo * p.Co * 2);
     wp.nt = (long long)wp.out_bytes >= (32ll << 20) ? 1 : 0;
     if (c.bn == 32) return launch_window_ks<1>(wp, c.lds, st);
     return launch_window_ks<2>(wp, c.lds, st);
