@@ -17,10 +17,11 @@
 //   dw   NHWC         dy, KS                 x gather, KS
 //   dw   NCHW         dy, KC                 x gather, KC (pixels contiguous)
 //
-// What bounds it: the fp32 matrix rate (64 flop per clock and SIMD, 1/16 of bf16).  A 128x128 tile needs 2048 matrix
-// clocks per 16-element stage, against which 64 wave-wide 4-byte transfers and their address arithmetic are small
-// change; that is why the transfers can be 4 bytes per lane, which is what makes every channel count, alignment and
-// layout run at the same rate (16-byte transfers are used where the reduction index comes in aligned fours).
+// What bounds it: a SIMD runs either an fp32 MFMA or a vector instruction, never both (the coexecution counter reads 0; bf16
+// MFMAs hide half of theirs), so the time is the matrix time (64 flop per clock and SIMD, 1/16 of bf16) plus the address
+// arithmetic.  192->384 3x3 at 13x13, batch 32, NCHW forward: 57 vector instructions per 8 MFMAs, 56% + 36% of the SIMD
+// cycles.  A larger wave tile has fewer of them per MFMA, a smaller one fills the chip.  Transfers are 4 bytes per lane, which
+// is what makes every channel count, alignment and layout run alike (16 bytes where the reduction comes in aligned fours).
 // Tiles are filled by direct global->LDS loads through a ring of NS stages, one barrier per stage; lanes that fall
 // into padding, past a ragged edge or past the reduction end get an offset the buffer rejects, which deposits zeros.
 //
