@@ -88,20 +88,24 @@ __global__ __launch_bounds__(256) void bias_grad_planes_kernel(const T *__restri
     struct __attribute__((packed)) Packed16 { uint32_t v[4]; };
     __shared__ float red[256];
     const int k = blockIdx.x, n0 = blockIdx.y * n_per_wg, n1 = min(N, n0 + n_per_wg);
-    const int full = PQ / V, pieces = (PQ + V - 1) / V;
+    const int full = PQ / V;
     float acc[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] = 0.f;
-    const long long total = (long long)(n1 - n0) * pieces;
+    // Whole pieces first, without a branch between their loads, then what is left of each plane (with the two in one loop no
+    // loads ran ahead of a branch: 64x50x23x19 bf16 9.1 us, now 4.3).
+    const int total = (n1 - n0) * full, rest = PQ - full * V;      // the host checked N * PQ / 4 against 31 bits
+    const long long tails = (long long)(n1 - n0) * rest;
 #pragma unroll 4
-    for (long long i = threadIdx.x; i < total; i += 256) {
-        const int n = (int)((unsigned)i / (unsigned)pieces), q = (int)((unsigned)i % (unsigned)pieces);
-        const T *src = dy + ((size_t)(n0 + n) * K + k) * PQ + (size_t)q * V;
-        if (q < full) {
-            const Packed16 v = *reinterpret_cast<const Packed16 *>(src);
-            add_vec<T>(acc, make_uint4(v.v[0], v.v[1], v.v[2], v.v[3]));
-        } else
-            for (int e = 0; e < PQ - full * V; ++e) acc[0] += load_f32(src + e);
+    for (int i = threadIdx.x; i < total; i += 256) {
+        const int n = (int)((unsigned)i / (unsigned)full), q = i - n * full;
+        const Packed16 v = *reinterpret_cast<const Packed16 *>(dy + ((size_t)(n0 + n) * K + k) * PQ + (size_t)q * V);
+        add_vec<T>(acc, make_uint4(v.v[0], v.v[1], v.v[2], v.v[3]));
+    }
+#pragma unroll 4
+    for (long long i = threadIdx.x; i < tails; i += 256) {
+        const int n = (int)((unsigned)i / (unsigned)rest), e = (int)((unsigned)i % (unsigned)rest);
+        acc[0] += load_f32(dy + ((size_t)(n0 + n) * K + k) * PQ + (size_t)(full * V + e));
     }
     float s = acc[0];
 #pragma unroll
