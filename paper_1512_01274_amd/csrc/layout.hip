@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void transpose_vec16_kernel(const uint32_t *__
 // filter of backward-data (transposed per stride residue class), and plain channel padding.  A call has two or three
 // of them, each a few microseconds of work at ordinary sizes, so they share one launch: a workgroup finds its job by
 // its index.  Rows of any length are read and written 16 bytes at a time (global memory takes unaligned vector
-// accesses); only the last piece of a row goes element by element.  100x30x45x37 to [..][32]: 5.2 us against 6.9 + 5.2
+// accesses); only the last piece of a destination row goes element by element.  100x30x45x37 to [..][32]: 5.2 us against 6.9 + 5.2
 // of a scalar transpose followed by a padding pass.
 struct __attribute__((packed)) Packed16 { uint32_t v[4]; };
 
@@ -143,6 +143,20 @@ __device__ __forceinline__ uint4 load8(const uint16_t *p, int n)        // n >= 
     for (int j = 0; j < 7; ++j)
         if (j < n) v[j >> 1] |= (uint32_t)p[j] << ((j & 1) * 16);
     return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// eight elements at `at` of a tensor of `total`, whatever row they belong to; the tensor's very last go one by one.  The last
+// piece of every row of 30 or 50 channels went element by element before, 7 loads under 7 conditions in every workgroup:
+// 64x45x37 pixels of 30 channels to NCHW 6.2 us, now 5.3.
+__device__ __forceinline__ uint4 load8_of(const uint16_t *src, long long at, long long total)
+{
+    return at < total ? load8(src + at, total - at >= 8 ? 8 : (int)(total - at)) : make_uint4(0, 0, 0, 0);
+}
+
+__device__ __forceinline__ uint4 keep_first(uint4 v, int n)             // the first n of 8 elements, zeros behind them
+{
+    const auto part = [n](uint32_t u, int at) { return n >= at + 2 ? u : n == at + 1 ? u & 0xFFFFu : 0u; };
+    return make_uint4(part(v.x, 0), part(v.y, 2), part(v.z, 4), part(v.w, 6));
 }
 
 __device__ __forceinline__ void store8(uint16_t *p, uint4 v, int n)
@@ -182,7 +196,7 @@ __global__ __launch_bounds__(256) void relayout_kernel(const RelayJobs jobs)
         const long long row = id / chunks;
         if (row >= q.batch) return;
         const int c = (int)(id % chunks) * 8;
-        const uint4 v = c < q.cols ? load8(src + row * q.cols + c, q.cols - c) : make_uint4(0, 0, 0, 0);
+        const uint4 v = c < q.cols ? keep_first(load8_of(src, row * q.cols + c, q.batch * q.cols), q.cols - c) : make_uint4(0, 0, 0, 0);
         *reinterpret_cast<uint4 *>(dst + row * q.run + c) = v;
         return;
     }
@@ -194,10 +208,11 @@ __global__ __launch_bounds__(256) void relayout_kernel(const RelayJobs jobs)
         const int cc = t & 7, rp = t >> 3;                 // 8-column chunk, row pair
         const int r = r0 + 2 * rp, c = c0 + cc * 8;
         uint4 a = make_uint4(0, 0, 0, 0), d = a;
-        const uint16_t *s = src + b * q.src_batch + (long long)r * q.src_pitch + c;
-        if (c < q.cols) {
-            if (r < q.rows) a = load8(s, q.cols - c);
-            if (r + 1 < q.rows) d = load8(s + q.src_pitch, q.cols - c);
+        const long long at = b * q.src_batch + (long long)r * q.src_pitch + c;
+        const long long total = (q.batch - 1) * q.src_batch + (long long)q.rows * q.src_pitch;
+        if (c < q.cols) {                                  // columns past the row's end are not stored
+            if (r < q.rows) a = load8_of(src, at, total);
+            if (r + 1 < q.rows) d = load8_of(src, at + q.src_pitch, total);
         }
         const uint32_t av[4] = {a.x, a.y, a.z, a.w}, dv[4] = {d.x, d.y, d.z, d.w};
 #pragma unroll
