@@ -4,6 +4,7 @@
 // through torch.cuda, a call cost 5 us before the library saw it (a launch is 2 us); this way it is about 0.5 us.
 #include <Python.h>
 
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/mxc.h"
@@ -124,9 +125,12 @@ PyObject *done(int rc)
 #define DIMS "N", "C", "H", "W", "K", "R", "S", "stride", "pad", "dtype", "layout"
 #define D11 d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], d[8], d[9], d[10]
 // Declares the wrapper FN with its argument names (the first REQ required), runs BODY with `a` (Args) and returns its rc.
+// torch's accessors throw C++ exceptions (data_ptr() of a tensor without storage, as torch.func.vmap and torch.func.grad hand
+// out): they become Python exceptions here, for nothing may unwind through the interpreter's C frames.
 #define WRAP(FN, REQ, NAMES, ...)                                                                                      \
     PyObject *py_##FN(PyObject *, PyObject *const *args, Py_ssize_t nargs, PyObject *kw)                                \
     {                                                                                                                   \
+        HANDLE_TH_ERRORS                                                                                                \
         static const char *const names[] = NAMES;                                                                      \
         constexpr int n = (int)(sizeof(names) / sizeof(names[0]));                                                      \
         static_assert(n <= MAX_ARGS, "arguments");                                                                      \
@@ -135,6 +139,7 @@ PyObject *done(int rc)
         int rc = MXC_OK;                                                                                                \
         __VA_ARGS__                                                                                                     \
         return done(rc);                                                                                                \
+        END_HANDLE_TH_ERRORS                                                                                            \
     }
 #define N_(...) {__VA_ARGS__}
 #define RUN(EXPR) do { PyThreadState *ts = PyEval_SaveThread(); rc = EXPR; PyEval_RestoreThread(ts); } while (0)
