@@ -96,6 +96,7 @@ struct F32Params {
     const float *bias;      // forward, or null
     int relu;
     const float *mask;      // backward-data, or null: the result is 0 where mask <= 0
+    int outside;            // whether any result has a tap outside the gathered tensor
 };
 
 // floor(t / d) for 0 <= t <= 127, 1 <= d <= 127
@@ -520,6 +521,60 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
         }
         out[o] = v;
     };
+    // row and column of this lane's result number `at`: element (block, e) of its wave's tile, or (Z > 1) of the workgroup's
+    // summed tile, which the threads share out
+    auto place = [&](int at, int &row, int &col) __attribute__((always_inline)) {
+        const int idx = Z == 1 ? (gw * MI * NI * 16 + at) * 64 + lane : at * NT + tid;
+        const int ln = idx & 63, e = (idx >> 6) & 15, blk = idx >> 10;
+        const int wv = blk / (MI * NI), bi = blk % (MI * NI) / NI, bj = blk % NI;
+        const int reg = 8 * (e >> 2) + 4 * (ln >> 5) + (e & 3), al = ln & 31;
+        row = m0 + (wv / WC) * (32 * MI) + 32 * bi + (SWAP ? al : reg);
+        col = n0 + (wv % WC) * (32 * NI) + 32 * bj + (SWAP ? reg : al);
+    };
+    // A tap outside the tensor is left out of the sum, but here it is a product with a deposited zero, and that is NaN where the
+    // other operand is infinite or NaN.  Such a result is itself NaN and nothing else is wrong about it: it is noted (bit
+    // `at`; one comparison a result) and summed once more over the taps inside, by one lane, in the order tap, channel or
+    // pixel.  A sum that turns NaN again ends there.
+    unsigned long long noted = 0;
+    auto finish = [&](int at, long long ro, int j, float v) __attribute__((always_inline)) {
+        if (v != v) noted |= 1ull << at;
+        put(ro, j, v);
+    };
+    auto sum_inside = [&](int i, int j) __attribute__((always_inline)) -> float {
+        float acc = 0.f;
+        if constexpr (OP == OP_WGRAD) {
+            const int hi = NCHW ? p.by_rs.div(j) : p.by_c.div(j), lo = j - hi * (NCHW ? RS : s.C);
+            const int tap = NCHW ? lo : hi, c = NCHW ? hi : lo, r = p.by_s.div(tap), t = tap - r * s.S;
+            for (int m = k_lo; m < k_hi && acc == acc;) {
+                const int end = min(m + 64, k_hi);
+#pragma unroll 4
+                for (; m < end; ++m) {
+                    const int row = p.by_q.div(m), n = p.by_p.div(row), q = m - row * s.Q;
+                    const int h = (row - n * s.P) * s.stride - s.pad + r, w = q * s.stride - s.pad + t;
+                    const bool in = (unsigned)h < (unsigned)s.H && (unsigned)w < (unsigned)s.W;
+                    const float dy = p.a[NCHW ? (n * s.K + i) * PQ + m - n * PQ : m * s.K + i];
+                    const float x = p.b[!in ? 0 : NCHW ? (n * s.C + c) * plane + h * s.W + w : ((n * s.H + h) * s.W + w) * s.C + c];
+                    if (in) acc = fmaf(dy, x, acc);
+                }
+            }
+        } else {
+            const int t2 = cls.mw.div(i), b = i - t2 * Mw, n = cls.mh.div(t2), a = t2 - n * Mh;
+            const int mul = OP == OP_FWD ? s.stride : 1, sgn = OP == OP_FWD ? 1 : -1;
+            for (int tr = 0; tr < cls.TR; ++tr)
+                for (int ts = 0; ts < TS; ++ts) {
+                    const int h = a * mul + cls.off_h + sgn * tr, w = b * mul + cls.off_w + sgn * ts;
+                    if ((unsigned)h >= (unsigned)Hi || (unsigned)w >= (unsigned)Wi) continue;
+                    const int rs = OP == OP_FWD ? tr * s.S + ts : (ph + s.stride * tr) * s.S + pw + s.stride * ts;
+                    const float *x = p.a + (NCHW ? n * Ci * plane + h * Wi + w : ((n * Hi + h) * Wi + w) * Ci);
+                    const float *f = p.b + (OP == OP_FWD ? (NCHW ? j * Ci * RS + rs : (j * RS + rs) * Ci) : NCHW ? j * RS + rs : rs * s.C + j);
+                    const int xs = NCHW ? plane : 1, fs = OP == OP_BWD ? s.C * RS : NCHW ? RS : 1;
+#pragma unroll 4
+                    for (int c = 0; c < Ci; ++c) acc = fmaf(x[c * xs], f[c * fs], acc);
+                    if (acc != acc) return acc;
+                }
+        }
+        return acc;
+    };
     // accumulator element e of a block: index along the registers 8*(e/4) + 4*half + e%4, along the lanes lane%32
     if constexpr (Z == 1) {
 #pragma unroll
@@ -529,13 +584,13 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) put(ro, n0 + wave_n + 32 * j + 8 * (e >> 2) + 4 * half + (e & 3), acc[i][j][e]);
+                    for (int e = 0; e < 16; ++e) finish((i * NI + j) * 16 + e, ro, n0 + wave_n + 32 * j + 8 * (e >> 2) + 4 * half + (e & 3), acc[i][j][e]);
             } else {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const long long ro = row_off(m0 + wave_m + 32 * i + 8 * (e >> 2) + 4 * half + (e & 3));
 #pragma unroll
-                    for (int j = 0; j < NI; ++j) put(ro, n0 + wave_n + 32 * j + l32, acc[i][j][e]);
+                    for (int j = 0; j < NI; ++j) finish((i * NI + j) * 16 + e, ro, n0 + wave_n + 32 * j + l32, acc[i][j][e]);
                 }
             }
         }
@@ -552,17 +607,21 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < NG * WT / NT; ++q) {
-            const int idx = q * NT + tid;
             float v = 0.f;
 #pragma unroll
-            for (int z = 0; z < Z; ++z) v += smem[z * NG * WT + idx];
-            const int ln = idx & 63, e = (idx >> 6) & 15, blk = idx >> 10;
-            const int wv = blk / (MI * NI), bi = blk % (MI * NI) / NI, bj = blk % NI;
-            const int reg = 8 * (e >> 2) + 4 * (ln >> 5) + (e & 3), al = ln & 31;
-            const int wm = (wv / WC) * (32 * MI) + 32 * bi, wn = (wv % WC) * (32 * NI) + 32 * bj;
-            put(row_off(m0 + wm + (SWAP ? al : reg)), n0 + wn + (SWAP ? reg : al), v);
+            for (int z = 0; z < Z; ++z) v += smem[z * NG * WT + q * NT + tid];
+            int row, col;
+            place(q, row, col);
+            finish(q, row_off(row), col, v);
         }
     }
+    if (p.outside)
+        while (noted != 0) {
+            int row, col;
+            place(__ffsll(noted) - 1, row, col);
+            noted &= noted - 1;
+            if (row < rows && col < cols) put(row_off(row), col, sum_inside(row, col));
+        }
 }
 
 // ---- tile choice ------------------------------------------------------------------------------------------------
@@ -744,6 +803,7 @@ int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y
     p.s = s;
     p.M = s.N * s.P * s.Q;
     p.bias = post.bias; p.relu = post.relu;
+    p.outside = s.pad > 0;
     F32Class &c = p.cls[0];
     c.TR = s.R; c.TS = s.S; c.Mh = s.P; c.Mw = s.Q; c.off_h = c.off_w = -s.pad;
     set_divisors(c);
@@ -760,6 +820,7 @@ int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, v
     p.b_bytes = (unsigned)((long long)s.K * s.C * s.R * s.S * 4);
     p.s = s;
     p.mask = (const float *)post.mask;
+    p.outside = s.pad > 0 || s.R > 1 || s.S > 1;
     p.n_cls = s.stride * s.stride;
     long long tiles = 0;
     for (int c = 0; c < p.n_cls; ++c) {
@@ -786,6 +847,7 @@ int f32_wgrad(const ConvShape &s, bool nchw, const void *x, const void *dy, void
     p.s = s;
     p.M = s.N * s.P * s.Q;
     p.span = pl.span;
+    p.outside = s.pad > 0;
     const long long cols = (long long)s.C * s.R * s.S;
     *variant = tc.name;
     const int rc = run(OP_WGRAD, nchw, pl.tile, p, (s.K + tc.bm - 1) / tc.bm, cols, pl.splits, st);

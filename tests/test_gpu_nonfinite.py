@@ -1,0 +1,78 @@
+"""Infinities and NaN in one operand where the other one has padding: a tap outside the image is left out of the sum, so
+that a border result which does not use a non-finite value stays what it is.  Every fp32 tile, three passes, both layouts,
+against the oracle (which walks the taps inside): NaN and infinities at the same places with the same signs, finite
+results within the usual bound."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1512_01274_amd import inputs as gen
+from tests import util
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    (2, 16, 16, 16, 32, 3, 3, 1, 1),
+    (1, 5, 13, 9, 7, 5, 3, 1, 2),         # nothing is a multiple of 4, R != S
+    (3, 36, 11, 10, 132, 3, 3, 2, 1),     # four residue classes, columns past one 128-wide tile
+    (1, 3, 30, 31, 70, 11, 11, 4, 2),     # 121 taps, sixteen classes
+    (5, 130, 7, 6, 40, 1, 1, 1, 1),       # border results without a single tap
+    (2, 24, 9, 8, 20, 2, 3, 1, 0),        # no padding: the input gradient has taps outside dy all the same
+]
+
+
+@pytest.fixture(scope="module")
+def mxc():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1512_01274_amd import mxc as m
+    return m
+
+
+def _tiles():
+    from paper_1512_01274_amd import mxc as m
+    return m.mxc_tile_names(3)
+
+
+def plant(a, seed):
+    """a with an infinity of each sign and a NaN: one at the first element, one at the last, one in between"""
+    b = a.copy()
+    rng = np.random.Generator(np.random.Philox(key=seed))
+    at = [0, b.size - 1, int(rng.integers(0, b.size))]
+    for i, v in zip(at, rng.permutation([np.inf, -np.inf, np.nan])):
+        b.flat[i] = v
+    return b
+
+
+def finite_abs(a):
+    return np.abs(np.where(np.isfinite(a), a, 0)).astype(np.float32)
+
+
+def check(got, ref, den, dtype, rounded, what):
+    assert np.array_equal(np.isnan(got), np.isnan(ref)), (what, int(np.isnan(got).sum()), int(np.isnan(ref).sum()))
+    inf = np.isinf(ref)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], ref[inf]), what
+    ok = np.isfinite(ref)
+    assert np.all(np.abs(got[ok] - ref[ok]) <= util.tight_bound(ref[ok], den[ok], dtype, rounded)), what
+
+
+@pytest.mark.filterwarnings("ignore:invalid value")
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("dims", SHAPES)
+@pytest.mark.parametrize("tile", _tiles())
+def test_fp32(mxc, oracle, monkeypatch, tile, dims, layout):
+    N, C, H, W, K, R, S, st, pad = dims
+    x, w, dy = gen.random_case(hash(dims) & 0xFFFF, *dims, dtype="f32", dist="normal")
+    w_bad, dy_bad = plant(w, 1), plant(dy, 2)
+    run = util.Runner(mxc, dims, "f32", layout)
+    monkeypatch.setenv("MXC_FORCE_VARIANT", tile)
+    check(run.fwd(x, w_bad), oracle.conv2d_fwd(x, w_bad, st, pad), oracle.conv2d_fwd(np.abs(x), finite_abs(w_bad), st, pad), "f32", False,
+          ("fwd", dims))
+    dx = torch.full((N * C * H * W,), float("nan"), device="cuda")
+    mxc.mxc_conv2d_bwd_data_relu(*dims, run.dt, run.lay, run._in(dy), run._in(w_bad), run._in(x), dx, run._ws(mxc.MXC_BWD_DATA_RELU))
+    ref = np.where(x > 0, oracle.conv2d_bwd_data(dy, w_bad, x.shape, st, pad), 0.0)
+    check(run._out(dx, x.shape), ref, oracle.conv2d_bwd_data(np.abs(dy), finite_abs(w_bad), x.shape, st, pad), "f32", False, ("bwd_data", dims))
+    ref = oracle.conv2d_bwd_weight(x, dy_bad, w.shape, st, pad)
+    den = oracle.conv2d_bwd_weight(np.abs(x), finite_abs(dy_bad), w.shape, st, pad)
+    for splits in (1, 3):
+        monkeypatch.setenv("MXC_FORCE_WGRAD", f"{tile}/{splits}")
+        check(run.bwd_weight(x, dy_bad), ref, den, "f32", False, ("bwd_weight", dims, splits))
