@@ -121,6 +121,20 @@ ConvShape with_padded_channels(const ConvShape &s)
     return t;
 }
 
+// the problem without the padding
+ConvShape without_padding(const ConvShape &s)
+{
+    ConvShape t = s;
+    t.K = real_k(s); t.C = real_c(s);
+    t.Kr = t.Cr = 0;
+    return t;
+}
+
+// Whether the gradients of a layer of ragged K can have terms that are products with padding, so that resum_dx / resum_dw
+// have to follow: taps outside dy, or the packings of first layers, which leave places empty; taps outside x.
+bool padded_k_resums_dx(const ConvShape &s8) { return s8.Kr != 0 && (s8.C <= 4 || s8.pad > 0 || s8.R > 1 || s8.S > 1); }
+bool padded_k_resums_dw(const ConvShape &s8) { return s8.Kr != 0 && s8.pad > 0; }
+
 // whether a matrix-core path takes the (padded) problem, in the order the passes below try them
 bool mfma_fwd_supported(const ConvShape &s)
 {
@@ -227,6 +241,10 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
     const bool prep = mode != FILTER_PREPARED, run = mode != FILTER_PREPARE_ONLY;
     if (const ConvShape s8 = with_padded_k(s); dtype == MXC_BF16 && s8.K != s.K && !g_lean && mfma_bwd_data_supported(s8)) {
         // the GEMM reduces over whole 16-byte chunks of dy: zero-pad its channels (the filter form follows, see real_k)
+        const bool resum = padded_k_resums_dx(s8);
+        const size_t wbytes = (size_t)s.K * s.R * s.S * s.C * 2;
+        void *wc = resum && mode != FILTER_RAW ? fws.take(wbytes) : nullptr;        // a prepared filter brings the filter itself along
+        if (wc != nullptr && mode == FILTER_PREPARE_ONLY && !dry) MXC_TRY(launch_copy(w, wc, wbytes, st));
         void *dy8 = run ? ws.take((size_t)s.N * s.P * s.Q * s8.K * 2) : nullptr;
         if (!dry && run) {
             RelayJob jobs[2] = {relay_pad(dy, dy8, (long long)s.N * s.P * s.Q, s.K, s8.K)};
@@ -235,11 +253,13 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
                 Carver peek = fws;
                 jobs[nj++] = relay_bwd_filter(s8, w, peek.take(igemm_bwd_data_workspace(s8)), kcrs);
                 MXC_TRY(relayout(jobs, nj, st));
-                return bwd_data_nhwc(s8, dtype, dy8, w, dx, post, fws, ws, st, dry, FILTER_PREPARED, kcrs);
+                MXC_TRY(bwd_data_nhwc(s8, dtype, dy8, w, dx, post, fws, ws, st, dry, FILTER_PREPARED, kcrs));
+                return resum ? resum_dx(s, false, dy, w, dx, st) : MXC_OK;
             }
             MXC_TRY(relayout(jobs, nj, st));
         }
-        return bwd_data_nhwc(s8, dtype, dy8, w, dx, post, fws, ws, st, dry, mode, kcrs);
+        MXC_TRY(bwd_data_nhwc(s8, dtype, dy8, w, dx, post, fws, ws, st, dry, mode, kcrs));
+        return resum && run && !dry ? resum_dx(s, false, dy, mode == FILTER_PREPARED ? wc : w, dx, st) : MXC_OK;
     }
     if (dtype == MXC_BF16 && s.K % 8 == 0 && s2d_applicable(s) && igemm_bwd_data_supported(s2d_shape(s))) {
         const ConvShape s2 = s2d_shape(s);
@@ -301,7 +321,7 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
 
 // ip: see InputMode (the forms are those of fwd_nhwc, chosen by the same tests in the same order; only
 // INPUT_RAW and INPUT_PREPARED reach this function)
-int bwd_weight_nhwc(const ConvShape &s_in, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16, Carver &ws,
+int bwd_weight_kernels(const ConvShape &s_in, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16, Carver &ws,
                     hipStream_t st, bool dry, const InputPrep &ip = InputPrep(), bool kcrs = false)
 {
     const char *v = "";
@@ -376,6 +396,16 @@ int bwd_weight_nhwc(const ConvShape &s_in, int dtype, const void *x, const void 
     if (dry) return MXC_OK;
     set_variant("bwd_weight", "direct_splitk");
     return direct_bwd_weight(s, dtype, x, dy, dw, dw_bf16, partial, splits, st);
+}
+
+int bwd_weight_nhwc(const ConvShape &s, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16, Carver &ws, hipStream_t st, bool dry,
+                    const InputPrep &ip = InputPrep())
+{
+    MXC_TRY(bwd_weight_kernels(s, dtype, x, dy, dw, dw_bf16, ws, st, dry, ip));
+    // (x is there: a layer of ragged K has no prepared input, see prepared_input_plan)
+    const ConvShape s8 = with_padded_k(s);
+    if (dry || dtype != MXC_BF16 || g_lean || !padded_k_resums_dw(s8) || !mfma_wgrad_supported(s8)) return MXC_OK;
+    return resum_dw(s, false, x, dy, dw, dw_bf16, st);
 }
 
 // ---- fp32, either layout: the matrix-core kernels of fp32.hip read the caller's tensors in place -----------------
@@ -453,6 +483,10 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
     if (pass == MXC_BWD_DATA) {
         const bool prep = mode != FILTER_PREPARED, run = mode != FILTER_PREPARE_ONLY;
         const bool plain = mfma_bwd_data_plain(s);     // the filter form is made here, together with the conversions
+        const bool resum = padded_k_resums_dx(s);
+        const size_t wbytes = (size_t)K * C * RS * 2;
+        void *wc = resum && mode != FILTER_RAW ? fws.take(wbytes) : nullptr;
+        if (wc != nullptr && mode == FILTER_PREPARE_ONLY && !dry) MXC_TRY(launch_copy(b, wc, wbytes, st));
         void *w2 = first ? fws.take(nw) : nullptr;     // first layers: their packings start from KRSC
         void *dy2 = run ? ws.take(ny) : nullptr, *dx2 = run ? ws.take(nx) : nullptr;
         void *mask2 = run && (post.mask != nullptr || post.relu) ? ws.take(nx) : nullptr;   // see run_pass
@@ -475,9 +509,9 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
         }
         MXC_TRY(bwd_data_nhwc(s, MXC_BF16, dy2, first ? w2 : b, dx2, post2, fws, ws, st, dry, inner, !first));
         if (dry || !run) return MXC_OK;
-        if (first) return launch_transpose(dx2, out, s.N, s.H * s.W, C, 2, st);
         jobs[0] = relay_to_nchw(dx2, out, s.N, C, s.H * s.W, s.C);
-        return relayout(jobs, 1, st);
+        MXC_TRY(first ? launch_transpose(dx2, out, s.N, s.H * s.W, C, 2, st) : relayout(jobs, 1, st));
+        return resum ? resum_dx(without_padding(s), true, a, mode == FILTER_PREPARED ? wc : b, out, st) : MXC_OK;
     }
     void *x2 = ws.take(nx), *dy2 = ws.take(ny);
     if (!dry) {
@@ -485,7 +519,8 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
         jobs[nj++] = relay_to_nhwc(b, dy2, s.N, K, s.P * s.Q, s.K);
         MXC_TRY(relayout(jobs, nj, st));
     }
-    return bwd_weight_nhwc(s, MXC_BF16, x2, dy2, out, pass == MXC_BWD_WEIGHT_BF16, ws, st, dry, InputPrep(), true);
+    MXC_TRY(bwd_weight_kernels(s, MXC_BF16, x2, dy2, out, pass == MXC_BWD_WEIGHT_BF16, ws, st, dry, InputPrep(), true));
+    return !dry && padded_k_resums_dw(s) ? resum_dw(without_padding(s), true, a, b, out, pass == MXC_BWD_WEIGHT_BF16, st) : MXC_OK;
 }
 
 // fws / mode: see FilterMode (backward-data only; fws == ws and FILTER_RAW otherwise)

@@ -269,6 +269,11 @@ int direct_bwd_weight_splits(const ConvShape &s);
 int direct_bwd_weight(const ConvShape &s, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16,
                       float *partial, int splits, hipStream_t st);
 
+// After the matrix-core kernels on zero-padded channels (bf16; s: the problem's own counts, all tensors the caller's):
+// results that a product with padding made NaN, summed again without it
+int resum_dx(const ConvShape &s, bool nchw, const void *dy, const void *w, void *dx, hipStream_t st);
+int resum_dw(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, bool dw_bf16, hipStream_t st);
+
 // ---- fp32.hip: fp32 matrix-core convolution, NHWC/KRSC or NCHW/KCRS operands read in place -----------------
 bool f32_supported(const ConvShape &s);
 int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y, hipStream_t st, const char **variant, const PostOp &post);

@@ -1,7 +1,7 @@
 """Infinities and NaN in one operand where the other one has padding: a tap outside the image is left out of the sum, so
-that a border result which does not use a non-finite value stays what it is.  Every fp32 tile, three passes, both layouts,
-against the oracle (which walks the taps inside): NaN and infinities at the same places with the same signs, finite
-results within the usual bound."""
+that a border result which does not use a non-finite value stays what it is.  Every fp32 tile in the three passes, and the
+gradients of bf16 layers of ragged K, both layouts, against the oracle (which walks the taps inside): NaN and infinities at
+the same places with the same signs, finite results within the usual bound."""
 import numpy as np
 import pytest
 import torch
@@ -76,3 +76,43 @@ def test_fp32(mxc, oracle, monkeypatch, tile, dims, layout):
     for splits in (1, 3):
         monkeypatch.setenv("MXC_FORCE_WGRAD", f"{tile}/{splits}")
         check(run.bwd_weight(x, dy_bad), ref, den, "f32", False, ("bwd_weight", dims, splits))
+
+
+# bf16 layers of ragged K: general, several classes, strided and unstrided first layers (their packings have empty places
+# in the filter, too), channels of both tensors ragged, no padding
+RAGGED = [
+    (2, 30, 13, 11, 50, 3, 3, 2, 1),
+    (3, 16, 9, 9, 70, 5, 5, 1, 2),
+    (1, 3, 20, 18, 13, 3, 3, 1, 1),
+    (2, 3, 35, 35, 9, 11, 11, 4, 2),
+    (2, 2, 17, 16, 130, 2, 2, 2, 0),
+    (4, 40, 10, 7, 100, 3, 3, 1, 0),
+    (2, 100, 6, 6, 66, 1, 1, 2, 1),
+]
+
+
+@pytest.mark.filterwarnings("ignore:invalid value")
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("dims", RAGGED)
+def test_bf16_ragged_k_gradients(mxc, oracle, dims, layout):
+    N, C, H, W, K, R, S, st, pad = dims
+    x, w, dy = gen.random_case(hash(dims) & 0xFFFF, *dims, dtype="bf16", dist="normal")
+    w_bad, dy_bad = plant(w, 3), plant(dy, 4)
+    run = util.Runner(mxc, dims, "bf16", layout)
+    a = (*dims, run.dt, run.lay)
+    prepared = mxc.alloc_workspace(mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BWD_DATA_FILTER, *a))
+    for f, g in ((w_bad, dy), (w, dy_bad)):
+        ref, den = oracle.conv2d_bwd_data(g, f, x.shape, st, pad), oracle.conv2d_bwd_data(finite_abs(g), finite_abs(f), x.shape, st, pad)
+        check(run.bwd_data(g, f), ref, den, "bf16", True, ("bwd_data", dims))
+        mxc.mxc_conv2d_bwd_data_prepare_filter(*a, run._in(f), prepared)
+        dx = torch.full((N * C * H * W,), 7.0, dtype=torch.bfloat16, device="cuda")
+        mxc.mxc_conv2d_bwd_data_prepared(*a, run._in(g), prepared, run._in(x), dx, run._ws(mxc.MXC_BWD_DATA_PREPARED_RELU))
+        check(run._out(dx, x.shape), np.where(x > 0, ref, 0.0), den, "bf16", True, ("bwd_data prepared, masked", dims))
+    ref = oracle.conv2d_bwd_weight(x, dy_bad, w.shape, st, pad)
+    den = oracle.conv2d_bwd_weight(np.abs(x), finite_abs(dy_bad), w.shape, st, pad)
+    check(run.bwd_weight(x, dy_bad), ref, den, "bf16", False, ("bwd_weight", dims))
+    dw = torch.full((w.size,), 7.0, dtype=torch.bfloat16, device="cuda")
+    mxc.mxc_conv2d_bwd_weight_bf16(*a, run._in(x), run._in(dy_bad), dw, run._ws(mxc.MXC_BWD_WEIGHT_BF16))
+    got = util.to_host_f64(dw)
+    got = util.nhwc_to_nchw(got.reshape(K, R, S, C)) if layout == "nhwc" else got.reshape(w.shape)
+    check(got, ref, den, "bf16", True, ("bwd_weight_bf16", dims))
