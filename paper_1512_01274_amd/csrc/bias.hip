@@ -87,14 +87,14 @@ __global__ __launch_bounds__(256) void bias_grad_planes_kernel(const T *__restri
     constexpr int V = VEC<T>;
     struct __attribute__((packed)) Packed16 { uint32_t v[4]; };
     __shared__ float red[256];
-    const int k = blockIdx.x, n0 = blockIdx.y * n_per_wg, n1 = min(N, n0 + n_per_wg);
+    const int k = blockIdx.x, n0 = blockIdx.y * n_per_wg, n1 = (int)min((long long)N, (long long)n0 + n_per_wg);
     const int full = PQ / V;
     float acc[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] = 0.f;
     // Whole pieces first, without a branch between their loads, then what is left of each plane (with the two in one loop no
     // loads ran ahead of a branch: 64x50x23x19 bf16 9.1 us, now 4.3).
-    const int total = (n1 - n0) * full, rest = PQ - full * V;      // the host checked N * PQ / 4 against 31 bits
+    const int total = (n1 - n0) * full, rest = PQ - full * V;      // below 2^30: see plan
     const long long tails = (long long)(n1 - n0) * rest;
 #pragma unroll 4
     for (int i = threadIdx.x; i < total; i += 256) {
@@ -156,7 +156,8 @@ BiasPlan plan(long long N, int K, long long PQ, int dtype, int layout)
     const int V = dtype == MXC_BF16 ? 8 : 4;
     b.fold = 1;
     if (layout == MXC_NCHW) {
-        // at least 512 workgroups, as far as there are images and 16 KB for each of them
+        // at least 512 workgroups, as far as there are images and 16 KB for each of them.  With below 2^40 elements, and
+        // planes below 2^31, a workgroup's whole pieces are below 2^40 / (512 * 4) + 2^29, and its planes below 2^23.
         long long parts = (512 + K - 1) / K;
         const long long per_image = PQ * (16 / V);
         long long most = N * per_image / (16 << 10);
@@ -220,7 +221,7 @@ size_t bias_grad_scratch(long long N, int K, long long PQ, int dtype, int layout
 
 int bias_grad(long long N, int K, long long PQ, int dtype, int layout, const void *dy, float *db, float *partial, hipStream_t st)
 {
-    if (layout == MXC_NCHW && (PQ > 0x7FFFFFFFll || N > 0x7FFFFFFFll || N * ((PQ + 3) / 4) > 0x7FFFFFFFll)) return MXC_ERR_SHAPE;
+    if (layout == MXC_NCHW && (PQ > 0x7FFFFFFFll || N * K > 0x7FFFFFFFll)) return MXC_ERR_SHAPE;
     const BiasPlan b = plan(N, K, PQ, dtype, layout);
     if (dtype == MXC_BF16) return run(b, N, K, PQ, layout, (const bf16_t *)dy, db, partial, st);
     return run(b, N, K, PQ, layout, (const float *)dy, db, partial, st);

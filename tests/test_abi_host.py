@@ -225,3 +225,33 @@ def test_grouped_entry_points_validate_on_the_host(mxc):
     # probe
     assert lib.mxc_probe_mfma(0, 10, 4096, 1 << 20, ctypes.byref(ctypes.c_double()), None) == mxc.MXC_ERR_SHAPE
     assert lib.mxc_probe_mfma(4, 10, 4096, 16, ctypes.byref(ctypes.c_double()), None) == mxc.MXC_ERR_WORKSPACE
+
+
+def test_bias_gradient_limits(mxc):
+    """NCHW: planes and the number of planes fit 31 bits, the tensor itself need not.  The last case passes every check, so that
+    it is the launch that fails on a machine without a GPU (elsewhere the made-up pointers would reach it)."""
+    import torch
+    lib = mxc.raw()
+    call = lambda N, K, P, Q, dt: lib.mxc_bias_grad(N, K, P, Q, dt, mxc.MXC_NCHW, 4096, 8192, 16384, 1 << 40, None)
+    assert call(1, 1, 65536, 32768, mxc.MXC_BF16) == mxc.MXC_ERR_SHAPE
+    assert call(65536, 32768, 1, 1, mxc.MXC_BF16) == mxc.MXC_ERR_SHAPE
+    if torch.cuda.is_available():
+        pytest.skip("no launch with made-up pointers")
+    for N, K, P, Q, dt in [(65536, 1, 512, 512, mxc.MXC_BF16), (32768, 1, 1024, 512, mxc.MXC_F32), (2 ** 31 - 1, 1, 16, 16, mxc.MXC_BF16)]:
+        assert call(N, K, P, Q, dt) == mxc.MXC_ERR_LAUNCH, (N, K, P, Q)
+        dims = (N, 1, P, Q, K, 1, 1, 1, 0)
+        assert mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BIAS_GRAD, *dims, dt, mxc.MXC_NHWC) > 0
+
+
+def test_bias_gradient_shares_of_planes():
+    """The two 31-bit counts of the NCHW kernel, over the plan's rule replayed here: whole 16-byte pieces of a workgroup's planes,
+    and its planes times the elements behind the last piece."""
+    for V in (4, 8):
+        for K in (1, 2, 3, 7, 64, 511, 512, 513, 5000, 1 << 20):
+            for PQ in (1, 3, 4, 7, 8, 9, 100, 1 << 12, (1 << 18) + 7, 2 ** 31 - 1):
+                for N in (1, 2, 3, 511, 512, 65536, 1 << 24, 1 << 30, (2 ** 31 - 1) // K):
+                    if N * K > 2 ** 31 - 1 or N * K * PQ >= 2 ** 40:
+                        continue
+                    parts = max(1, min((512 + K - 1) // K, max(1, N * PQ * (16 // V) // (16 << 10)), N))
+                    per = (N + parts - 1) // parts
+                    assert per * (PQ // V) < 2 ** 30 and per * (PQ % V) < 2 ** 32, (V, K, PQ, N)

@@ -28,3 +28,17 @@ def test_bias_gradient(N, K, P, Q, layout, dtype):
     assert torch.equal(got[0], got[1]) and bool((got[:, K:] == 7.0).all())
     err = np.abs(got[0][:K].double().cpu().numpy() - a.sum(1))
     assert np.all(err <= 64 * 2.0 ** -24 * np.abs(a).sum(1) + 1e-30)
+
+
+def test_planes_of_more_than_two_to_the_31_pieces():
+    """65536 NCHW images of one 512x512 channel, 34 GB of bf16: small whole numbers, so that every partial sum is exact."""
+    from paper_1512_01274_amd import mxc
+    N, P, Q = 65536, 512, 512
+    value = (torch.arange(N, device="cuda") * 5 % 7 - 2).to(torch.bfloat16)
+    dy = torch.empty(N, 1, P, Q, dtype=torch.bfloat16, device="cuda").copy_(value.view(N, 1, 1, 1))
+    ws = mxc.alloc_workspace(mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BIAS_GRAD, N, 1, P, Q, 1, 1, 1, 1, 0, mxc.MXC_BF16, mxc.MXC_NCHW))
+    db = torch.full((4,), 7.0, device="cuda")
+    mxc.mxc_bias_grad(N, 1, P, Q, mxc.MXC_BF16, mxc.MXC_NCHW, dy, db[:1], ws)
+    assert db.tolist() == [float(value.double().sum() * (P * Q)), 7.0, 7.0, 7.0]
+    del dy
+    torch.cuda.empty_cache()
