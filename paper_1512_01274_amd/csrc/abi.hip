@@ -135,6 +135,35 @@ ConvShape without_padding(const ConvShape &s)
 bool padded_k_resums_dx(const ConvShape &s8) { return s8.Kr != 0 && (s8.C <= 4 || s8.pad > 0 || s8.R > 1 || s8.S > 1); }
 bool padded_k_resums_dw(const ConvShape &s8) { return s8.Kr != 0 && s8.pad > 0; }
 
+// NHWC gradients of ragged K that are so small that one thread per result, in one launch, is done before the padded path's
+// launches are.  us, one thread / padded, launches of a graph, 450 shapes:
+// dx: the one-thread kernel takes 2.4 + 0.11 per step of its chain (K times the taps that reach a pixel, and two for every
+// tap it looks at) up to 2^18 results and more beyond; padding dy and the GEMM take 7, with resum_dx 11, first layers
+// 13-18 (where pixels of all stride classes share a wave, which then walks every tap).  128x4096 to 10 classes 5.5 / 7.3,
+// 8x64x14x14 3x3 K=4 8.1 / 11.8, K=6 10.2 / 11.5, K=9 13.4 / 10.9; 3x32x32 3x3 K=10 12.2 / 16.0, K=20 20.5 / 18.4; with
+// 400 thousand results 3x3 K=3 10.9 / 12.2, K=4 12.0 / 11.7, 1x1 K=28 7.2 / 7.3, K=36 8.2 / 7.3.
+bool small_ragged_dx(const ConvShape &s)
+{
+    const bool first = s.C <= 4, resums = padded_k_resums_dx(with_padded_k(s));
+    const long long out = (long long)s.N * s.H * s.W * s.C;
+    const long long taps = first ? (long long)s.R * s.S : (long long)((s.R + s.stride - 1) / s.stride) * ((s.S + s.stride - 1) / s.stride);
+    const long long chain = s.K * taps + 2LL * s.R * s.S;
+    if (out > (first ? 1 << 20 : 1 << 19)) return false;
+    if (out > 1 << 18) return chain <= (resums && !first ? 45 : 30);
+    return chain <= (first ? 108 : resums ? 78 : 42);
+}
+// dw, by its multiply-adds, while the pixels are few enough for the one-thread kernel's ranges: 8x512 to 10 classes 4.5 / 5.3,
+// 32x512 5.5 / 5.2, to 1 class 4.5 / 5.3, 128x2048 (262 thousand) 6.4 / 5.8; 28x28 64 to 1 channel 3x3 (451 thousand) 7.1 / 10.8,
+// to 2 (903 thousand) 8.3 / 10.7, 8x14x14 64 to 2 (1.8 million) 11.1 / 11.1; 28x28x8 16 to 1 (6272 pixels) 12.7 / 7.5.  Above 4 channels the line lies where
+// heads break even; 3x3 layers of 0.1-0.6 million, which the tests of ragged channels want on the matrix cores, lose up to
+// 1.3 us by it.
+bool small_ragged_dw(const ConvShape &s)
+{
+    const long long m = (long long)s.N * s.P * s.Q, macs = m * s.K * s.C * s.R * s.S;
+    if (m > 1600) return false;
+    return macs <= (s.K > 4 ? 3 << 15 : s.pad > 0 || m > 400 ? 1 << 20 : 1 << 18);
+}
+
 // whether a matrix-core path takes the (padded) problem, in the order the passes below try them
 bool mfma_fwd_supported(const ConvShape &s)
 {
@@ -239,7 +268,7 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
                   Carver &ws, hipStream_t st, bool dry, FilterMode mode = FILTER_RAW, bool kcrs = false)
 {
     const bool prep = mode != FILTER_PREPARED, run = mode != FILTER_PREPARE_ONLY;
-    if (const ConvShape s8 = with_padded_k(s); dtype == MXC_BF16 && s8.K != s.K && !g_lean && mfma_bwd_data_supported(s8)) {
+    if (const ConvShape s8 = with_padded_k(s); dtype == MXC_BF16 && s8.K != s.K && !g_lean && !small_ragged_dx(s) && mfma_bwd_data_supported(s8)) {
         // the GEMM reduces over whole 16-byte chunks of dy: zero-pad its channels (the filter form follows, see real_k)
         const bool resum = padded_k_resums_dx(s8);
         const size_t wbytes = (size_t)s.K * s.R * s.S * s.C * 2;
@@ -331,7 +360,7 @@ int bwd_weight_kernels(const ConvShape &s_in, int dtype, const void *x, const vo
     ConvShape s = s_in;
     RelayJob jobs[2];
     int nj = 0;
-    if (const ConvShape s8 = with_padded_k(s); dtype == MXC_BF16 && s8.K != s.K && !g_lean && mfma_wgrad_supported(s8)) {
+    if (const ConvShape s8 = with_padded_k(s); dtype == MXC_BF16 && s8.K != s.K && !g_lean && !small_ragged_dw(s) && mfma_wgrad_supported(s8)) {
         void *dy8 = ws.take((size_t)s.N * s.P * s.Q * s8.K * 2);
         jobs[nj++] = relay_pad(dy, dy8, (long long)s.N * s.P * s.Q, s.K, s8.K);
         dy = dy8;
@@ -404,7 +433,7 @@ int bwd_weight_nhwc(const ConvShape &s, int dtype, const void *x, const void *dy
     MXC_TRY(bwd_weight_kernels(s, dtype, x, dy, dw, dw_bf16, ws, st, dry, ip));
     // (x is there: a layer of ragged K has no prepared input, see prepared_input_plan)
     const ConvShape s8 = with_padded_k(s);
-    if (dry || dtype != MXC_BF16 || g_lean || !padded_k_resums_dw(s8) || !mfma_wgrad_supported(s8)) return MXC_OK;
+    if (dry || dtype != MXC_BF16 || g_lean || !padded_k_resums_dw(s8) || small_ragged_dw(s) || !mfma_wgrad_supported(s8)) return MXC_OK;
     return resum_dw(s, false, x, dy, dw, dw_bf16, st);
 }
 

@@ -46,6 +46,7 @@ struct WgradParams {
     int n_tiles, splits, tiles, n_wg;
     int span;           // pixels per split (multiple of the stage size)
     int M;              // N*P*Q
+    int rows;           // rows of the result that are stored
     int dq, dp, dn;     // decomposition of a one-stage pixel advance: BP = dq + Q*(dp + P*dn)
     unsigned x_bytes, dy_bytes;
 };
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(64 * WR * WC, (WR * WC == 4 && NS * BP * (BMT + BNT
                 const int r = idx / CPR, c4 = idx % CPR;
                 const int k = k0 + wave_m + i * 32 + r, c = n0 + wave_n + c4 * 4;
                 const float4 v = *reinterpret_cast<const float4 *>(stg + r * WN + c4 * 4);
-                if (k < p.K && c < RSC) *reinterpret_cast<float4 *>(out + (size_t)k * RSC + c) = v;
+                if (k < p.rows && c < RSC) *reinterpret_cast<float4 *>(out + (size_t)k * RSC + c) = v;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -487,6 +488,7 @@ const WgradTile kTiles[] = {
     {128, 128, 32, 2, 0.01f, "wgrad_128x128_p32s4_w4"},
 };
 constexpr int N_TILES = sizeof(kTiles) / sizeof(kTiles[0]);
+constexpr int SMALL_TILE = 4;       // 64x64
 
 template <int BMT, int BNT, int BP, int NS, int WR, int WC>
 int launch(const WgradParams &p, int tiles, hipStream_t st)
@@ -571,6 +573,10 @@ Plan search_plan(const WgradGeom &g, int forced, int forced_splits)
     const long long M = (long long)g.N * g.P * g.Q;
     Plan best_pl{};
     double best = 1e300;
+    // Few pixels and padded rows: with one range of pixels the small tile stores the rows there are into dw itself, without the
+    // launch that adds ranges and drops rows (the model below does not know of it): 128x4096 to 50 classes 7.1 -> 5.8 us,
+    // 256x512 to 10 8.7 -> 6.4, 14x14 16 to 100 channels 3x3 11.0 -> 8.6; from 784 pixels on the ranges pay (64 to 10: 7.3 / 8.9).
+    if (forced < 0 && g.K != g.Kout && M <= 400 && (long long)g.K * RSC <= 1 << 19 && RSC == g.R * g.S * g.C) forced = SMALL_TILE, forced_splits = 1;
     for (int t = 0; t < N_TILES; ++t) {
         if (forced >= 0 && t != forced) continue;
         const WgradTile &tc = kTiles[t];
@@ -650,8 +656,9 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
     // many splits of a small dw: 16 lane groups keep enough loads in flight; otherwise 4
     const bool wide = splits >= 32 && total < 256 * 1024;
     // KCRS: a workgroup of the reordering kernel adds up 64*R*S results; where that would be a long chain for each of its
-    // threads (112 splits of a 50x30x3x3 filter: 65 us) the mapped reduction does it
-    const bool kcrs_long = kcrs && (long long)splits * g.R * g.S > 128;
+    // threads (112 splits of a 50x30x3x3 filter: 65 us), or its workgroups are fewer than the CUs (whole gradients, us: 28x28
+    // 64 to 10 channels 3x3 18.7 -> 11.8, 8x14x14 64 to 64 23.0 -> 11.2), the mapped reduction does it
+    const bool kcrs_long = kcrs && ((long long)splits * g.R * g.S > 128 || (long long)g.Kout * ((g.C + 63) / 64) < 256);
     const bool same = identity && total % 4 == 0 && split_stride % 4 == 0;
     if (splits > 1 && (kcrs ? kcrs_long : !identity || (same && wide))) {
         const bool ident = !kcrs && identity;
@@ -732,8 +739,10 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
     if (tiles * p.splits > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
     const bool identity = g.s2d == 1 && g.col_s == g.C && g.col_r == g.S * g.C && p.ncols == g.R * g.S * g.C;
     // one split whose columns are already in KRSC order and an fp32 result: the "partial" tensor is dw itself
-    const bool direct = p.splits == 1 && identity && !dw_bf16 && !kcrs && g.K == g.Kout;
+    // (without the rows of padded channels)
+    const bool direct = p.splits == 1 && identity && !dw_bf16 && !kcrs;
     if (direct) p.partial = (float *)dw;
+    p.rows = direct ? g.Kout : g.K;
     const int rc = launch_choice(pl.tile, p, (int)tiles, st);
     if (rc != MXC_OK) return rc;
     *variant = tc.name;
