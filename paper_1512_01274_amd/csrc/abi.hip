@@ -283,12 +283,12 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
                 jobs[nj++] = relay_bwd_filter(s8, w, peek.take(igemm_bwd_data_workspace(s8)), kcrs);
                 MXC_TRY(relayout(jobs, nj, st));
                 MXC_TRY(bwd_data_nhwc(s8, dtype, dy8, w, dx, post, fws, ws, st, dry, FILTER_PREPARED, kcrs));
-                return resum ? resum_dx(s, false, dy, w, dx, st) : MXC_OK;
+                return resum ? resum_dx(Resum{s, false, (const bf16_t *)dy, (const bf16_t *)w}, dx, st) : MXC_OK;
             }
             MXC_TRY(relayout(jobs, nj, st));
         }
         MXC_TRY(bwd_data_nhwc(s8, dtype, dy8, w, dx, post, fws, ws, st, dry, mode, kcrs));
-        return resum && run && !dry ? resum_dx(s, false, dy, mode == FILTER_PREPARED ? wc : w, dx, st) : MXC_OK;
+        return resum && run && !dry ? resum_dx(Resum{s, false, (const bf16_t *)dy, (const bf16_t *)(mode == FILTER_PREPARED ? wc : w)}, dx, st) : MXC_OK;
     }
     if (dtype == MXC_BF16 && s.K % 8 == 0 && s2d_applicable(s) && igemm_bwd_data_supported(s2d_shape(s))) {
         const ConvShape s2 = s2d_shape(s);
@@ -349,15 +349,17 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
 }
 
 // ip: see InputMode (the forms are those of fwd_nhwc, chosen by the same tests in the same order; only
-// INPUT_RAW and INPUT_PREPARED reach this function)
-int bwd_weight_kernels(const ConvShape &s_in, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16, Carver &ws,
-                    hipStream_t st, bool dry, const InputPrep &ip = InputPrep(), bool kcrs = false)
+// INPUT_RAW and INPUT_PREPARED reach this function).  resum: the caller's operands where x and dy are copies whose padding may
+// have to be left out of dw (of operands padded here it is done anyway)
+int bwd_weight_nhwc(const ConvShape &s_in, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16, Carver &ws,
+                    hipStream_t st, bool dry, const InputPrep &ip = InputPrep(), bool kcrs = false, const Resum *resum = nullptr)
 {
     const char *v = "";
     Carver &xws = ip.xws ? *ip.xws : ws;
     const bool pack = ip.mode != INPUT_PREPARED;
     // dy's channels come in whole 16-byte chunks: zero-pad them where they do not (dw keeps its own rows, see real_k)
     ConvShape s = s_in;
+    const Resum own{s_in, false, (const bf16_t *)x, (const bf16_t *)dy};
     RelayJob jobs[2];
     int nj = 0;
     if (const ConvShape s8 = with_padded_k(s); dtype == MXC_BF16 && s8.K != s.K && !g_lean && !small_ragged_dw(s) && mfma_wgrad_supported(s8)) {
@@ -365,13 +367,14 @@ int bwd_weight_kernels(const ConvShape &s_in, int dtype, const void *x, const vo
         jobs[nj++] = relay_pad(dy, dy8, (long long)s.N * s.P * s.Q, s.K, s8.K);
         dy = dy8;
         s = s8;
+        if (padded_k_resums_dw(s8)) resum = &own;        // x is the caller's: a layer of ragged K has no prepared input
     }
     if (dtype == MXC_BF16 && s.C % 8 == 0 && wgrad_supported(wgrad_geom_plain(s))) {
         const WgradGeom g = wgrad_geom_plain(s);
         float *partial = (float *)ws.take(wgrad_workspace(g));
         if (dry) return MXC_OK;
         MXC_TRY(relayout(jobs, nj, st));
-        const int rc = wgrad(g, x, dy, dw, dw_bf16, kcrs, partial, st, &v);
+        const int rc = wgrad(g, x, dy, dw, dw_bf16, kcrs, partial, st, &v, resum);
         set_variant("bwd_weight", v);
         return rc;
     }
@@ -384,7 +387,7 @@ int bwd_weight_kernels(const ConvShape &s_in, int dtype, const void *x, const vo
         if (dry) return MXC_OK;
         if (pack) MXC_TRY(s2d_pack_x(s, x, x2, st));
         MXC_TRY(relayout(jobs, nj, st));
-        const int rc = wgrad(g, x2, dy, dw, dw_bf16, kcrs, partial, st, &v);
+        const int rc = wgrad(g, x2, dy, dw, dw_bf16, kcrs, partial, st, &v, resum);
         set_variant("bwd_weight", (std::string("s2d+") + v).c_str());
         return rc;
     }
@@ -397,7 +400,7 @@ int bwd_weight_kernels(const ConvShape &s_in, int dtype, const void *x, const vo
         if (dry) return MXC_OK;
         if (pack) MXC_TRY(smallc_pack_x(s, x, xp, st));
         MXC_TRY(relayout(jobs, nj, st));
-        const int rc = wgrad(g, xp, dy, dw, dw_bf16, kcrs, partial, st, &v);
+        const int rc = wgrad(g, xp, dy, dw, dw_bf16, kcrs, partial, st, &v, resum);
         set_variant("bwd_weight", (std::string("smallc+") + v).c_str());
         return rc;
     }
@@ -409,7 +412,7 @@ int bwd_weight_kernels(const ConvShape &s_in, int dtype, const void *x, const vo
         if (dry) return MXC_OK;
         if (pack) jobs[nj++] = relay_pad(x, xp, (long long)s.N * s.H * s.W, s.C, g.pix);
         MXC_TRY(relayout(jobs, nj, st));
-        const int rc = wgrad(g, xp, dy, dw, dw_bf16, kcrs, partial, st, &v);
+        const int rc = wgrad(g, xp, dy, dw, dw_bf16, kcrs, partial, st, &v, resum);
         set_variant("bwd_weight", (std::string("chanpad+") + v).c_str());
         return rc;
     }
@@ -425,16 +428,6 @@ int bwd_weight_kernels(const ConvShape &s_in, int dtype, const void *x, const vo
     if (dry) return MXC_OK;
     set_variant("bwd_weight", "direct_splitk");
     return direct_bwd_weight(s, dtype, x, dy, dw, dw_bf16, partial, splits, st);
-}
-
-int bwd_weight_nhwc(const ConvShape &s, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16, Carver &ws, hipStream_t st, bool dry,
-                    const InputPrep &ip = InputPrep())
-{
-    MXC_TRY(bwd_weight_kernels(s, dtype, x, dy, dw, dw_bf16, ws, st, dry, ip));
-    // (x is there: a layer of ragged K has no prepared input, see prepared_input_plan)
-    const ConvShape s8 = with_padded_k(s);
-    if (dry || dtype != MXC_BF16 || g_lean || !padded_k_resums_dw(s8) || small_ragged_dw(s) || !mfma_wgrad_supported(s8)) return MXC_OK;
-    return resum_dw(s, false, x, dy, dw, dw_bf16, st);
 }
 
 // ---- fp32, either layout: the matrix-core kernels of fp32.hip read the caller's tensors in place -----------------
@@ -538,9 +531,13 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
         }
         MXC_TRY(bwd_data_nhwc(s, MXC_BF16, dy2, first ? w2 : b, dx2, post2, fws, ws, st, dry, inner, !first));
         if (dry || !run) return MXC_OK;
+        const Resum rs{without_padding(s), true, (const bf16_t *)a, (const bf16_t *)(mode == FILTER_PREPARED ? wc : b)};
+        if (first) {
+            MXC_TRY(launch_transpose(dx2, out, s.N, s.H * s.W, C, 2, st));
+            return resum ? resum_dx(rs, out, st) : MXC_OK;
+        }
         jobs[0] = relay_to_nchw(dx2, out, s.N, C, s.H * s.W, s.C);
-        MXC_TRY(first ? launch_transpose(dx2, out, s.N, s.H * s.W, C, 2, st) : relayout(jobs, 1, st));
-        return resum ? resum_dx(without_padding(s), true, a, mode == FILTER_PREPARED ? wc : b, out, st) : MXC_OK;
+        return relayout(jobs, 1, st, resum ? &rs : nullptr);
     }
     void *x2 = ws.take(nx), *dy2 = ws.take(ny);
     if (!dry) {
@@ -548,8 +545,9 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
         jobs[nj++] = relay_to_nhwc(b, dy2, s.N, K, s.P * s.Q, s.K);
         MXC_TRY(relayout(jobs, nj, st));
     }
-    MXC_TRY(bwd_weight_kernels(s, MXC_BF16, x2, dy2, out, pass == MXC_BWD_WEIGHT_BF16, ws, st, dry, InputPrep(), true));
-    return !dry && padded_k_resums_dw(s) ? resum_dw(without_padding(s), true, a, b, out, pass == MXC_BWD_WEIGHT_BF16, st) : MXC_OK;
+    const Resum rs{without_padding(s), true, (const bf16_t *)a, (const bf16_t *)b};
+    return bwd_weight_nhwc(s, MXC_BF16, x2, dy2, out, pass == MXC_BWD_WEIGHT_BF16, ws, st, dry, InputPrep(), true,
+                           padded_k_resums_dw(s) ? &rs : nullptr);
 }
 
 // fws / mode: see FilterMode (backward-data only; fws == ws and FILTER_RAW otherwise)

@@ -3,7 +3,7 @@
 // These cover every shape and both element types and are the path for fp32 and
 // for shapes the MFMA kernels do not take.  Working layout: activations NHWC,
 // filters KRSC, fp32 accumulation in a fixed order (deterministic).
-#include "mxc_internal.h"
+#include "resum.h"
 
 namespace mxc {
 
@@ -36,32 +36,6 @@ __global__ __launch_bounds__(256) void direct_fwd_kernel(ConvShape s, const T *_
     if (bias != nullptr) acc += bias[k];
     if (relu) acc = fmaxf(acc, 0.f);
     store_f32(y + gid, acc);
-}
-
-// dx[n,h,v,c] = sum over taps (r,s) with (h+pad-r)%st==0, (v+pad-s)%st==0, p,q in range, and k.
-template <typename T, bool NCHW>
-__device__ __forceinline__ float sum_dx(const ConvShape &s, const T *__restrict__ dy, const T *__restrict__ w, int n, int h, int v, int c)
-{
-    const size_t plane = (size_t)s.P * s.Q, wk = (size_t)s.R * s.S * s.C;
-    float acc = 0.f;
-    for (int r = 0; r < s.R; ++r) {
-        const int hp = h + s.pad - r;
-        if (hp < 0 || hp % s.stride != 0) continue;
-        const int p = hp / s.stride;
-        if (p >= s.P) continue;
-        for (int ss = 0; ss < s.S; ++ss) {
-            const int vq = v + s.pad - ss;
-            if (vq < 0 || vq % s.stride != 0) continue;
-            const int q = vq / s.stride;
-            if (q >= s.Q) continue;
-            const size_t pq = (size_t)p * s.Q + q, rs = (size_t)r * s.S + ss;
-            const T *dyp = dy + (NCHW ? (size_t)n * s.K * plane + pq : ((size_t)n * plane + pq) * s.K);
-            const T *wp = w + (NCHW ? (size_t)c * (s.R * s.S) + rs : rs * s.C + c);
-            const size_t dk = NCHW ? plane : 1;
-            for (int k = 0; k < s.K; ++k) acc = fmaf(load_f32(dyp + (size_t)k * dk), load_f32(wp + (size_t)k * wk), acc);
-        }
-    }
-    return acc;
 }
 
 template <typename T>
@@ -111,15 +85,11 @@ __global__ __launch_bounds__(256) void direct_bwd_weight_kernel(ConvShape s, con
     partial[(size_t)blockIdx.y * wtotal + gid] = acc;
 }
 
-// ---- results of the matrix-core kernels that padding made NaN ---------------------------------------------------
-// Zero-padded channels brought bf16 layers of ragged K to the matrix cores, where a tap outside the image, and a place that a
-// first layer's packing leaves empty, is a product with zero: NaN where the other operand is infinite or NaN, although the
-// sum does not have that term.  Such a result is NaN itself, so the two kernels below read the results and sum those that
-// are NaN once more over the terms there are.  What bounds them is the launch: they read what was just written (a 64x30x45x37
-// dx 2.5 us, a 50x30x3x3 dw 2.2; the NCHW training step of that layer 71.1 us without the two, 75.9 with them).
-__device__ __forceinline__ bool is_nan(float v) { return v != v; }
-__device__ __forceinline__ bool is_nan(bf16_t v) { return (v & 0x7FFFu) > 0x7F80u; }
-
+// ---- results of the matrix-core kernels that padding made NaN (see resum.h) --------------------------------------
+// The two kernels below read the results and sum those that are NaN once more.  What bounds them is the launch: they read what
+// was just written (a 64x30x45x37 dx 2.5 us, a 50x30x3x3 dw 2.2).  Where a kernel passes over the results anyway - the last
+// conversion to NCHW, the mapped split reduction - it does so itself: the NCHW training step of that layer is 71.1 us without,
+// 75.9 with the two kernels, 72.1 that way.
 // dx, eight elements per thread
 template <bool NCHW>
 __global__ __launch_bounds__(256) void resum_dx_kernel(ConvShape s, const bf16_t *__restrict__ dy, const bf16_t *__restrict__ w, bf16_t *dx,
@@ -159,22 +129,11 @@ __global__ __launch_bounds__(256) void resum_dw_kernel(ConvShape s, const bf16_t
     const bool mine = tid < per && gid < total && is_nan(dw[gid]);
     bad[tid] = mine;
     if (!__syncthreads_or(mine)) return;
-    const long long npq = (long long)s.N * s.P * s.Q;
-    const size_t plane = (size_t)s.P * s.Q, xplane = (size_t)s.H * s.W;
     for (int i = 0; i < per; ++i) {
         if (!bad[i]) continue;                       // the same for every thread
         const int at = blockIdx.x * per + i;
-        const int c = NCHW ? at / RS % s.C : at % s.C, rs = NCHW ? at % RS : at / s.C % RS, k = at / (RS * s.C), r = rs / s.S, ss = rs % s.S;
-        float acc = 0.f;
-        for (long long m = tid; m < npq; m += 256) {
-            const int q = (int)(m % s.Q), p = (int)(m / s.Q % s.P), n = (int)(m / (long long)plane);
-            const int h = p * s.stride - s.pad + r, v = q * s.stride - s.pad + ss;
-            if (h < 0 || h >= s.H || v < 0 || v >= s.W) continue;
-            const bf16_t d = dy[NCHW ? ((size_t)n * s.K + k) * plane + (size_t)p * s.Q + q : (size_t)m * s.K + k];
-            const bf16_t a = x[NCHW ? ((size_t)n * s.C + c) * xplane + (size_t)h * s.W + v : ((size_t)n * xplane + (size_t)h * s.W + v) * s.C + c];
-            acc = fmaf(load_f32(&d), load_f32(&a), acc);
-        }
-        red[tid] = acc;
+        const int c = NCHW ? at / RS % s.C : at % s.C, rs = NCHW ? at % RS : at / s.C % RS, k = at / (RS * s.C);
+        red[tid] = sum_dw<NCHW>(s, x, dy, k, c, rs / s.S, rs % s.S, tid, 256);
         __syncthreads();
         for (int half = 128; half > 0; half >>= 1) {
             if (tid < half) red[tid] += red[tid + half];
@@ -217,33 +176,33 @@ int direct_bwd_data(const ConvShape &s, int dtype, const void *dy, const void *w
     return ok();
 }
 
-int resum_dx(const ConvShape &s, bool nchw, const void *dy, const void *w, void *dx, hipStream_t st)
+int resum_dx(const Resum &q, void *dx, hipStream_t st)
 {
+    const ConvShape &s = q.s;
     const size_t total = (size_t)s.N * s.H * s.W * s.C, blocks = (total + 2047) / 2048;
     if (blocks > 0x7FFFFFFFull) return MXC_ERR_SHAPE;
-    if (nchw)
-        hipLaunchKernelGGL(resum_dx_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, s, (const bf16_t *)dy, (const bf16_t *)w, (bf16_t *)dx, total);
-    else
-        hipLaunchKernelGGL(resum_dx_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, s, (const bf16_t *)dy, (const bf16_t *)w, (bf16_t *)dx, total);
+    if (q.nchw) hipLaunchKernelGGL(resum_dx_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, s, q.a, q.b, (bf16_t *)dx, total);
+    else hipLaunchKernelGGL(resum_dx_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, s, q.a, q.b, (bf16_t *)dx, total);
     return ok();
 }
 
 template <typename OUT>
-static int resum_dw_to(const ConvShape &s, bool nchw, const void *x, const void *dy, OUT *dw, hipStream_t st)
+static int resum_dw_to(const Resum &q, OUT *dw, hipStream_t st)
 {
+    const ConvShape &s = q.s;
     const int total = s.K * s.R * s.S * s.C;        // below 2^31: checked with the shape
     // few elements per workgroup where there are few: should they all be NaN, the chip shares the work
     int per = (total + 1023) / 1024;
     per = per < 4 ? 4 : per > 256 ? 256 : per;
     const dim3 grid((unsigned)((total + (long long)per - 1) / per)), block(256);
-    if (nchw) hipLaunchKernelGGL((resum_dw_kernel<OUT, true>), grid, block, 0, st, s, (const bf16_t *)x, (const bf16_t *)dy, dw, total, per);
-    else hipLaunchKernelGGL((resum_dw_kernel<OUT, false>), grid, block, 0, st, s, (const bf16_t *)x, (const bf16_t *)dy, dw, total, per);
+    if (q.nchw) hipLaunchKernelGGL((resum_dw_kernel<OUT, true>), grid, block, 0, st, s, q.a, q.b, dw, total, per);
+    else hipLaunchKernelGGL((resum_dw_kernel<OUT, false>), grid, block, 0, st, s, q.a, q.b, dw, total, per);
     return ok();
 }
 
-int resum_dw(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, bool dw_bf16, hipStream_t st)
+int resum_dw(const Resum &q, void *dw, bool dw_bf16, hipStream_t st)
 {
-    return dw_bf16 ? resum_dw_to(s, nchw, x, dy, (bf16_t *)dw, st) : resum_dw_to(s, nchw, x, dy, (float *)dw, st);
+    return dw_bf16 ? resum_dw_to(q, (bf16_t *)dw, st) : resum_dw_to(q, (float *)dw, st);
 }
 
 int direct_bwd_weight_splits(const ConvShape &s)

@@ -3,7 +3,9 @@
 // NCHW -> NHWC of an activation tensor is, per image, the transpose of a
 // [C][H*W] matrix; KCRS -> KRSC of a filter bank is the same with [C][R*S].
 // Pure data movement: 1 read + 1 write of every element, HBM-bound.
-#include "mxc_internal.h"
+#include <type_traits>
+
+#include "resum.h"
 
 namespace mxc {
 
@@ -173,9 +175,11 @@ __device__ __forceinline__ void store8(uint16_t *p, uint4 v, int n)
 
 struct RelayJobs { RelayJob job[MAX_RELAY_JOBS]; int n; };
 
-// NJ jobs: with a compile-time count the jobs' fields are fetched together instead of one search step after another
-template <int NJ>
-__global__ __launch_bounds__(256) void relayout_kernel(const RelayJobs jobs)
+// NJ jobs: with a compile-time count the jobs' fields are fetched together instead of one search step after another.  R = Resum:
+// the job brings dx to its NCHW place, and what is NaN is summed again.
+struct NoResum {};
+template <int NJ, class R = NoResum>
+__global__ __launch_bounds__(256) void relayout_kernel(const RelayJobs jobs, const R rs)
 {
     constexpr int PITCH = 33;                              // dwords per LDS column: odd, conflict-free dword writes
     __shared__ uint32_t tile[TILE * PITCH];
@@ -241,6 +245,15 @@ __global__ __launch_bounds__(256) void relayout_kernel(const RelayJobs jobs)
         }
         const uint32_t *l = tile + oc * PITCH + part * 4;
         store8(dst + off + r, make_uint4(l[0], l[1], l[2], l[3]), q.run - r);
+        if constexpr (std::is_same_v<R, Resum>) {
+            unsigned bad = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bad |= (is_nan((bf16_t)(l[e >> 1] >> ((e & 1) * 16))) ? 1u : 0u) << e;
+            for (; bad != 0; bad &= bad - 1) {
+                const int pix = r + __ffs(bad) - 1;
+                if (pix < q.run) store_f32(dst + off + pix, sum_dx<bf16_t, true>(rs.s, rs.a, rs.b, (int)b, pix / rs.s.W, pix % rs.s.W, c));
+            }
+        }
     }
 }
 
@@ -427,23 +440,24 @@ RelayJob relay_bwd_filter(const ConvShape &s, const void *w, void *wt, bool kcrs
     return q;
 }
 
-static int launch_relayout(const RelayJobs &all, long long blocks, hipStream_t st)
+static int launch_relayout(const RelayJobs &all, long long blocks, hipStream_t st, const Resum *resum)
 {
     static_assert(MAX_RELAY_JOBS == 3, "job counts the kernel is built for");
     const dim3 grid((unsigned)blocks), block(256);
     const RelayJob &q = all.job[0];
-    if (all.n == 1 && q.kind == RELAY_TRANSPOSE && q.rows % 8 == 0 && q.cols % 8 == 0 && q.run == q.rows && q.src_pitch == q.cols &&
+    if (resum != nullptr) hipLaunchKernelGGL((relayout_kernel<1, Resum>), grid, block, 0, st, all, *resum);
+    else if (all.n == 1 && q.kind == RELAY_TRANSPOSE && q.rows % 8 == 0 && q.cols % 8 == 0 && q.run == q.rows && q.src_pitch == q.cols &&
         q.dst_pitch == q.rows && q.src_batch == q.dst_batch)
         // one dense transpose of whole chunks: the plain kernel (half the time of the general one where it is all launch)
         hipLaunchKernelGGL((void (*)(const uint16_t *, uint16_t *, int, int))transpose_vec16_kernel, grid, block, 0, st, (const uint16_t *)q.src,
                            (uint16_t *)q.dst, q.rows, q.cols);
-    else if (all.n == 1) hipLaunchKernelGGL(relayout_kernel<1>, grid, block, 0, st, all);
-    else if (all.n == 2) hipLaunchKernelGGL(relayout_kernel<2>, grid, block, 0, st, all);
-    else hipLaunchKernelGGL(relayout_kernel<3>, grid, block, 0, st, all);
+    else if (all.n == 1) hipLaunchKernelGGL(relayout_kernel<1>, grid, block, 0, st, all, NoResum{});
+    else if (all.n == 2) hipLaunchKernelGGL(relayout_kernel<2>, grid, block, 0, st, all, NoResum{});
+    else hipLaunchKernelGGL(relayout_kernel<3>, grid, block, 0, st, all, NoResum{});
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
-int relayout(const RelayJob *jobs, int n, hipStream_t st)
+int relayout(const RelayJob *jobs, int n, hipStream_t st, const Resum *resum)
 {
     RelayJobs all{};
     long long total = 0;
@@ -461,7 +475,7 @@ int relayout(const RelayJob *jobs, int n, hipStream_t st)
         q.blocks = (unsigned)blocks;
         if (total + blocks > 0x7FFFFFFFll) {               // more workgroups than one launch holds: what there is goes first
             const RelayJob last = q;
-            const int rc = launch_relayout(all, total, st);
+            const int rc = launch_relayout(all, total, st, nullptr);
             if (rc != MXC_OK) return rc;
             all.job[0] = last;
             all.n = 0;
@@ -470,7 +484,7 @@ int relayout(const RelayJob *jobs, int n, hipStream_t st)
         total += blocks;
         ++all.n;
     }
-    return all.n ? launch_relayout(all, total, st) : MXC_OK;
+    return all.n ? launch_relayout(all, total, st, resum) : MXC_OK;
 }
 
 int launch_copy(const void *src, void *dst, size_t bytes, hipStream_t stream)

@@ -21,6 +21,14 @@ struct ConvShape {
 inline int real_k(const ConvShape &s) { return s.Kr ? s.Kr : s.K; }
 inline int real_c(const ConvShape &s) { return s.Cr ? s.Cr : s.C; }
 
+// The caller's operands of a gradient whose results may have to be summed again (see resum.h), with the problem's own
+// channel counts: dx: a = dy, b = w; dw: a = x, b = dy
+struct Resum {
+    ConvShape s;
+    bool nchw;
+    const bf16_t *a, *b;
+};
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 
 // Round-to-nearest-even; inputs are finite in this library's use.
@@ -242,7 +250,8 @@ RelayJob relay_to_nchw(const void *src, void *dst, int n, int c, int hw, int c_p
 RelayJob relay_pad(const void *src, void *dst, long long rows, int c, int c_pitch);         // [rows][c] -> [rows][c_pitch]
 // the filter matrices of backward-data, one per stride residue class: wt[class][c][(j*TS + i)*K + k] (see igemm_bwd_data)
 RelayJob relay_bwd_filter(const ConvShape &s, const void *w, void *wt, bool kcrs);
-int relayout(const RelayJob *jobs, int n, hipStream_t st);
+// resum: the one job brings dx to its place
+int relayout(const RelayJob *jobs, int n, hipStream_t st, const Resum *resum = nullptr);
 
 // ---- probe.hip: matrix-pipe ceiling measurement -------------------------------------
 // launches the register-resident MFMA loop; *flops = floating-point operations the launch performs
@@ -269,10 +278,9 @@ int direct_bwd_weight_splits(const ConvShape &s);
 int direct_bwd_weight(const ConvShape &s, int dtype, const void *x, const void *dy, void *dw, bool dw_bf16,
                       float *partial, int splits, hipStream_t st);
 
-// After the matrix-core kernels on zero-padded channels (bf16; s: the problem's own counts, all tensors the caller's):
-// results that a product with padding made NaN, summed again without it
-int resum_dx(const ConvShape &s, bool nchw, const void *dy, const void *w, void *dx, hipStream_t st);
-int resum_dw(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, bool dw_bf16, hipStream_t st);
+// After the matrix-core kernels on zero-padded channels (see resum.h): results that padding made NaN, summed again without it
+int resum_dx(const Resum &q, void *dx, hipStream_t st);
+int resum_dw(const Resum &q, void *dw, bool dw_bf16, hipStream_t st);
 
 // ---- fp32.hip: fp32 matrix-core convolution, NHWC/KRSC or NCHW/KCRS operands read in place -----------------
 bool f32_supported(const ConvShape &s);
@@ -438,6 +446,6 @@ bool wgrad_supported(const WgradGeom &g);
 size_t wgrad_workspace(const WgradGeom &g);            // bytes of fp32 partial tiles
 // dw: fp32, or bf16 (the fp32 sum rounded once, by the reduce kernel) when dw_bf16; KRSC, or KCRS when kcrs
 int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_bf16, bool kcrs, float *partial, hipStream_t st,
-          const char **variant);
+          const char **variant, const Resum *resum = nullptr);
 
 }  // namespace mxc

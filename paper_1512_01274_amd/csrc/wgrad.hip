@@ -21,7 +21,7 @@
 
 #include <type_traits>
 
-#include "mxc_internal.h"
+#include "resum.h"
 
 namespace mxc {
 
@@ -46,9 +46,9 @@ struct WgradParams {
     int n_tiles, splits, tiles, n_wg;
     int span;           // pixels per split (multiple of the stage size)
     int M;              // N*P*Q
-    int rows;           // rows of the result that are stored
     int dq, dp, dn;     // decomposition of a one-stage pixel advance: BP = dq + Q*(dp + P*dn)
     unsigned x_bytes, dy_bytes;
+    int rows;           // rows of the result that are stored
 };
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
@@ -383,9 +383,11 @@ struct DwMap {
 // it is the chain of dependent additions and the launch: as two launches (a wave's 16 groups, then the re-ordering one
 // float at a time) 512 splits of 64x3x3x3 took 16 us, 170 of 64x11x11x3 11 (now 5 and 8.5); the training step of the first (224x224, batch
 // 32) went from 226 to 218 us with one, that of a ragged 30->50 NCHW layer from 81 to 78.
-template <int G, typename OUT>
+// R = Resum: what is NaN is summed again over the taps inside (see resum.h), by the one lane that stores it.
+struct NoResum {};
+template <int G, typename OUT, class R>
 __global__ __launch_bounds__(256) void wgrad_reduce_map_kernel(const float4 *__restrict__ partial, OUT *__restrict__ dw, int total4, int splits,
-                                                               size_t split_stride4, const DwMap m)
+                                                               size_t split_stride4, const DwMap m, const R rs)
 {
     constexpr int LPG = 64 / G;
     __shared__ float4 red[4][LPG];
@@ -408,13 +410,15 @@ __global__ __launch_bounds__(256) void wgrad_reduce_map_kernel(const float4 *__r
     const int t = threadIdx.x, e = blockIdx.x * (LPG * 4) + t;
     if (t >= LPG * 4 || e >= total4 * 4) return;
     const float *r0 = reinterpret_cast<const float *>(red);
-    const float v = ((r0[t] + r0[LPG * 4 + t]) + r0[LPG * 8 + t]) + r0[LPG * 12 + t];
+    float v = ((r0[t] + r0[LPG * 4 + t]) + r0[LPG * 8 + t]) + r0[LPG * 12 + t];
     if (m.order == DW_SAME) { store_f32(dw + e, v); return; }
     const int k = e / m.ncols, col = e - k * m.ncols;
     const int rb = col / m.col_r, in_r = col - rb * m.col_r, sb = in_r / m.col_s, in_s = in_r - sb * m.col_s;
     const int blk = m.d > 1 ? in_s / m.Cq : 0, c = in_s - blk * m.Cq;
     const int r = rb * m.d + blk / m.d, sc = sb * m.d + blk % m.d;
     if (k >= m.Kout || r >= m.R || sc >= m.S || c >= m.C) return;
+    if constexpr (std::is_same_v<R, Resum>)
+        if (is_nan(v)) v = rs.nchw ? sum_dw<true>(rs.s, rs.a, rs.b, k, c, r, sc, 0, 1) : sum_dw<false>(rs.s, rs.a, rs.b, k, c, r, sc, 0, 1);
     store_f32(dw + (m.order == DW_KRSC ? (((size_t)k * m.R + r) * m.S + sc) * m.C + c : (((size_t)k * m.C + c) * m.R + r) * m.S + sc), v);
 }
 
@@ -649,7 +653,8 @@ size_t wgrad_workspace(const WgradGeom &g)
 }
 
 template <typename OUT>
-static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits, int ncols, bool identity, bool kcrs, hipStream_t st)
+static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits, int ncols, bool identity, bool kcrs, hipStream_t st,
+                         const Resum *resum = nullptr)
 {
     const int total = g.Kout * g.R * g.S * g.C;
     const size_t split_stride = (size_t)g.K * ncols;
@@ -661,18 +666,26 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
     const bool kcrs_long = kcrs && ((long long)splits * g.R * g.S > 128 || (long long)g.Kout * ((g.C + 63) / 64) < 256);
     const bool same = identity && total % 4 == 0 && split_stride % 4 == 0;
     if (splits > 1 && (kcrs ? kcrs_long : !identity || (same && wide))) {
-        const bool ident = !kcrs && identity;
+        // (a lane adds up 2^15 pixels in some 20 ms, should it come to that; the kernel of its own shares them out)
+        const bool fused = resum != nullptr && (long long)g.N * g.P * g.Q <= 1 << 15;
+        const bool ident = !kcrs && identity && !fused;
         const DwMap m{ident ? DW_SAME : kcrs ? DW_KCRS : DW_KRSC, ncols, g.Kout, g.R, g.S, g.C, g.col_r, g.col_s, g.s2d, g.Cq};
         const int total4 = ident ? total / 4 : g.K * ncols / 4;       // ncols is a multiple of 8 where the order differs
         const size_t stride4 = split_stride / 4;
         // below 32 splits 16 in flight are enough, and four times as many outputs share a cache line's worth of a split
-        if (splits >= 32)
-            hipLaunchKernelGGL((wgrad_reduce_map_kernel<16, OUT>), dim3((unsigned)((total4 + 3) / 4)), dim3(256), 0, st, (const float4 *)partial, dw,
-                               total4, splits, stride4, m);
-        else
-            hipLaunchKernelGGL((wgrad_reduce_map_kernel<4, OUT>), dim3((unsigned)((total4 + 15) / 16)), dim3(256), 0, st, (const float4 *)partial, dw,
-                               total4, splits, stride4, m);
-        return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+        const int per = splits >= 32 ? 4 : 16;       // groups of four outputs per workgroup
+        const dim3 grid((unsigned)((total4 + per - 1) / per)), block(256);
+        const float4 *p4 = (const float4 *)partial;
+        if (fused && splits >= 32) hipLaunchKernelGGL((wgrad_reduce_map_kernel<16, OUT, Resum>), grid, block, 0, st, p4, dw, total4, splits, stride4, m, *resum);
+        else if (fused) hipLaunchKernelGGL((wgrad_reduce_map_kernel<4, OUT, Resum>), grid, block, 0, st, p4, dw, total4, splits, stride4, m, *resum);
+        else if (splits >= 32) hipLaunchKernelGGL((wgrad_reduce_map_kernel<16, OUT, NoResum>), grid, block, 0, st, p4, dw, total4, splits, stride4, m, NoResum{});
+        else hipLaunchKernelGGL((wgrad_reduce_map_kernel<4, OUT, NoResum>), grid, block, 0, st, p4, dw, total4, splits, stride4, m, NoResum{});
+        if (hipGetLastError() != hipSuccess) return MXC_ERR_LAUNCH;
+        return resum != nullptr && !fused ? resum_dw(*resum, dw, sizeof(OUT) == 2, st) : MXC_OK;
+    }
+    if (resum != nullptr) {                           // every other form: a pass of its own
+        const int rc = launch_reduce(g, partial, dw, splits, ncols, identity, kcrs, st);
+        return rc == MXC_OK ? resum_dw(*resum, dw, sizeof(OUT) == 2, st) : rc;
     }
     if (kcrs) {
         const int RS = g.R * g.S, c_tiles = (g.C + 63) / 64;
@@ -716,7 +729,7 @@ int sum_splits(const float *partial, void *dw, bool dw_bf16, long long total, in
 }
 
 int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_bf16, bool kcrs, float *partial, hipStream_t st,
-          const char **variant)
+          const char **variant, const Resum *resum)
 {
     const Plan pl = make_plan(g);
     const WgradTile &tc = kTiles[pl.tile];
@@ -746,9 +759,9 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
     const int rc = launch_choice(pl.tile, p, (int)tiles, st);
     if (rc != MXC_OK) return rc;
     *variant = tc.name;
-    if (direct) return MXC_OK;
-    return dw_bf16 ? launch_reduce(g, p.partial, (bf16_t *)dw, p.splits, p.ncols, identity, kcrs, st)
-                   : launch_reduce(g, p.partial, (float *)dw, p.splits, p.ncols, identity, kcrs, st);
+    if (direct) return resum != nullptr ? resum_dw(*resum, dw, false, st) : MXC_OK;
+    return dw_bf16 ? launch_reduce(g, p.partial, (bf16_t *)dw, p.splits, p.ncols, identity, kcrs, st, resum)
+                   : launch_reduce(g, p.partial, (float *)dw, p.splits, p.ncols, identity, kcrs, st, resum);
 }
 
 }  // namespace mxc

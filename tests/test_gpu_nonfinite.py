@@ -88,6 +88,7 @@ RAGGED = [
     (2, 2, 17, 16, 130, 2, 2, 2, 0),
     (4, 40, 10, 7, 100, 3, 3, 1, 0),
     (2, 100, 6, 6, 66, 1, 1, 2, 1),
+    (1, 8, 290, 301, 9, 3, 3, 1, 1),      # more pixels than one lane adds up
 ]
 
 
