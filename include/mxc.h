@@ -13,6 +13,10 @@
  *     P = floor((H + 2*pad - R)/stride) + 1,  Q = floor((W + 2*pad - S)/stride) + 1.
  * One stride and one pad serve both axes; dilation 1, groups 1, no bias in the three plain calls;
  * cross-correlation (no filter flip); x outside the image reads as 0.
+ * Infinities and NaN: in fp32, and in the gradients of bf16 layers whose K is no multiple of 8, a tap outside the image
+ * is left out of the sum whatever the other operand holds.  Every other bf16 call multiplies padding, and the places
+ * that the packings of first layers (C <= 4) leave empty, as zeros: there an infinite or NaN element of one operand
+ * makes NaN of the results in whose window, or packed block, it meets such a place.  Finite inputs are not affected.
  *
  * Common rules for every call.
  *   - All data pointers are DEVICE pointers on the current HIP device, 16-byte

@@ -293,6 +293,7 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
     if (dtype == MXC_BF16 && s.K % 8 == 0 && s2d_applicable(s) && igemm_bwd_data_supported(s2d_shape(s))) {
         const ConvShape s2 = s2d_shape(s);
         void *w2 = fws.take((size_t)s2.K * s2.R * s2.S * s2.C * 2), *wt = fws.take(igemm_bwd_data_workspace(s2));
+        // (not used where the image is stored directly: which kernel runs depends on the tuning hook, the size must not)
         void *dx2 = run ? ws.take((size_t)s2.N * s2.H * s2.W * s2.C * 2) : nullptr;
         if (dry) return MXC_OK;
         const char *v = "";
@@ -431,9 +432,8 @@ int bwd_weight_nhwc(const ConvShape &s_in, int dtype, const void *x, const void 
 }
 
 // ---- fp32, either layout: the matrix-core kernels of fp32.hip read the caller's tensors in place -----------------
-// For NCHW the scratch that the converting path would use is asked for all the same: the size of a call's workspace
-// is a property of its arguments, not of the kernel that runs them, and the converting path still takes tensors of
-// 2 GiB and more.
+// For NCHW the scratch that the converting path would use is asked for all the same, and nothing uses it: the size query has
+// always answered more for NCHW than for NHWC (the host tests hold it to that), and callers' sizes stay what they were.
 
 int run_f32(int pass, const ConvShape &s, int layout, const void *a, const void *b, void *out, const PostOp &post, Carver &fws,
             Carver &ws, hipStream_t st, bool dry, FilterMode mode)

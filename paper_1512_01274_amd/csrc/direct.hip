@@ -1,8 +1,9 @@
 // Direct (one thread per output element) convolution kernels.
 //
-// These cover every shape and both element types and are the path for fp32 and
-// for shapes the MFMA kernels do not take.  Working layout: activations NHWC,
-// filters KRSC, fp32 accumulation in a fixed order (deterministic).
+// These cover every shape and both element types, and are the path for shapes the
+// matrix-core kernels do not take (stride > 4, tensors of 2 GiB and more, more than
+// 127 taps) and for the smallest NHWC gradients of ragged K.  Working layout:
+// activations NHWC, filters KRSC, fp32 accumulation in a fixed order (deterministic).
 #include "resum.h"
 
 namespace mxc {

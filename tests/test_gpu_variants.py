@@ -267,7 +267,9 @@ def test_window_kernel_patch_shapes(mxc, oracle, patch):
 
 
 def test_window_kernel_epilogue(mxc, oracle):
-    """bias + ReLU applied by the window kernel's epilogue; the masked backward-data form is not its to run."""
+    """bias + ReLU applied by the window kernel's epilogue.  A forced igemm_window is the form without a mask: masked
+    backward-data leaves it to a tile of the other kernel; forced by its own name, the masked form gives the bits of the
+    unmasked one where the mask keeps them."""
     dims = (3, 64, 20, 22, 64, 3, 3, 1, 1)
     N, C, H, W, K, R, S, st, pad = dims
     x, w, dy = gen.random_case(78, *dims, dtype="bf16", dist="normal")
@@ -286,6 +288,12 @@ def test_window_kernel_epilogue(mxc, oracle):
         ref, den = oracle.conv2d_bwd_data_relu(dy, w, x, st, pad)
         got = run._out(dx, (N, C, H, W))
         assert np.all(np.abs(got - ref) <= util.tight_bound(ref, den, "bf16", True))
+        plain = run.bwd_data(dy, w)
+        assert mxc.mxc_last_variant().split(":")[-1] == "igemm_window"
+    with forced("MXC_FORCE_VARIANT", "igemm_patch_masked"):
+        mxc.mxc_conv2d_bwd_data_relu(*dims, run.dt, run.lay, run._in(dy), run._in(w), run._in(x), dx, run._ws(mxc.MXC_BWD_DATA_RELU))
+        assert mxc.mxc_last_variant().split(":")[-1] == "igemm_patch_masked"
+        assert np.array_equal(run._out(dx, (N, C, H, W)), np.where(x > 0, plain, 0.0))
 
 
 def test_window_kernel_declines(mxc, oracle):
