@@ -100,12 +100,8 @@ __global__ __launch_bounds__(256) void resum_dx_kernel(ConvShape s, const bf16_t
     if (at >= total) return;
     const int n_el = total - at < 8 ? (int)(total - at) : 8;
     unsigned bad = 0;
-    if (n_el == 8) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(dx + at);
-        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) bad |= (is_nan((bf16_t)(u[e >> 1] >> ((e & 1) * 16))) ? 1u : 0u) << e;
-    } else
+    if (n_el == 8) bad = nan_bits(*reinterpret_cast<const uint4 *>(dx + at));
+    else
         for (int e = 0; e < n_el; ++e) bad |= (is_nan(dx[at + e]) ? 1u : 0u) << e;
     for (; bad != 0; bad &= bad - 1) {
         const size_t i = at + (__ffs(bad) - 1);

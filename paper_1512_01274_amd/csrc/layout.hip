@@ -245,15 +245,11 @@ __global__ __launch_bounds__(256) void relayout_kernel(const RelayJobs jobs, con
         }
         const uint32_t *l = tile + oc * PITCH + part * 4;
         store8(dst + off + r, make_uint4(l[0], l[1], l[2], l[3]), q.run - r);
-        if constexpr (std::is_same_v<R, Resum>) {
-            unsigned bad = 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) bad |= (is_nan((bf16_t)(l[e >> 1] >> ((e & 1) * 16))) ? 1u : 0u) << e;
-            for (; bad != 0; bad &= bad - 1) {
+        if constexpr (std::is_same_v<R, Resum>)
+            for (unsigned bad = nan_bits(make_uint4(l[0], l[1], l[2], l[3])); bad != 0; bad &= bad - 1) {
                 const int pix = r + __ffs(bad) - 1;
                 if (pix < q.run) store_f32(dst + off + pix, sum_dx<bf16_t, true>(rs.s, rs.a, rs.b, (int)b, pix / rs.s.W, pix % rs.s.W, c));
             }
-        }
     }
 }
 

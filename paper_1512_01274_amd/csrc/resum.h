@@ -9,6 +9,19 @@ namespace mxc {
 
 __device__ __forceinline__ bool is_nan(float v) { return v != v; }
 __device__ __forceinline__ bool is_nan(bf16_t v) { return (v & 0x7FFFu) > 0x7F80u; }
+// which of eight bf16 are NaN, as bits; the usual answer is none
+__device__ __forceinline__ unsigned nan_bits(uint4 v)
+{
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    const auto mag = [](uint32_t u) { return __builtin_bit_cast(u16x2, u & 0x7FFF7FFFu); };
+    const u16x2 most = __builtin_elementwise_max(__builtin_elementwise_max(mag(v.x), mag(v.y)), __builtin_elementwise_max(mag(v.z), mag(v.w)));
+    if (most.x <= 0x7F80u && most.y <= 0x7F80u) return 0;
+    const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+    unsigned bad = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bad |= (is_nan((bf16_t)(u[e >> 1] >> ((e & 1) * 16))) ? 1u : 0u) << e;
+    return bad;
+}
 
 // dx[n,h,v,c] = sum over taps (r,s) with (h+pad-r)%st==0, (v+pad-s)%st==0, p,q in range, and k.
 template <typename T, bool NCHW>
