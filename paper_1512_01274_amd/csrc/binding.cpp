@@ -110,6 +110,12 @@ bool to_stream(PyObject *o, void **stream)
     return !PyErr_Occurred();
 }
 
+// the interpreter runs on while a call enqueues its work; an exception, too, takes the lock back before Python sees it
+struct WithoutGil {
+    PyThreadState *ts = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(ts); }
+};
+
 PyObject *done(int rc)
 {
     if (rc == MXC_OK) Py_RETURN_NONE;
@@ -142,7 +148,7 @@ PyObject *done(int rc)
         END_HANDLE_TH_ERRORS                                                                                            \
     }
 #define N_(...) {__VA_ARGS__}
-#define RUN(EXPR) do { PyThreadState *ts = PyEval_SaveThread(); rc = EXPR; PyEval_RestoreThread(ts); } while (0)
+#define RUN(EXPR) do { WithoutGil off; rc = EXPR; } while (0)
 #define INTS(COUNT) int d[COUNT]; if (!to_ints(a.v, d, COUNT)) return nullptr
 #define PTR(NAME, AT) void *NAME; if (!to_ptr(a.v[AT], &NAME)) return nullptr
 #define BUF(NAME, AT) void *NAME; size_t NAME##_n; if (!to_ptr(a.v[AT], &NAME, &NAME##_n)) return nullptr
@@ -212,6 +218,7 @@ WRAP(mxc_layout_convert, 9, N_("n", "c", "h", "w", "dtype", "src_layout", "dst_l
 
 PyObject *py_mxc_conv2d_workspace_bytes(PyObject *, PyObject *const *args, Py_ssize_t nargs, PyObject *kw)
 {
+    HANDLE_TH_ERRORS
     static const char *const names[] = {"op", DIMS};
     Args a("mxc_conv2d_workspace_bytes", names, 12, 12, args, nargs, kw);
     if (!a.ok) return nullptr;
@@ -220,6 +227,7 @@ PyObject *py_mxc_conv2d_workspace_bytes(PyObject *, PyObject *const *args, Py_ss
     size_t bytes = 0;
     const int rc = mxc_conv2d_workspace_bytes(d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], d[8], d[9], d[10], d[11], &bytes);
     return rc == MXC_OK ? PyLong_FromSize_t(bytes) : done(rc);
+    END_HANDLE_TH_ERRORS
 }
 
 // set_hooks(MxcError, raw_stream, device, slow_stream)
