@@ -153,15 +153,15 @@ bool small_ragged_dx(const ConvShape &s)
     return chain <= (first ? 108 : resums ? 78 : 42);
 }
 // dw, by its multiply-adds, while the pixels are few enough for the one-thread kernel's ranges: 8x512 to 10 classes 4.5 / 5.3,
-// 32x512 5.5 / 5.2, to 1 class 4.5 / 5.3, 128x2048 (262 thousand) 6.4 / 5.8; 28x28 64 to 1 channel 3x3 (451 thousand) 7.1 / 10.8,
-// to 2 (903 thousand) 8.3 / 10.7, 8x14x14 64 to 2 (1.8 million) 11.1 / 11.1; 28x28x8 16 to 1 (6272 pixels) 12.7 / 7.5.  Above 4 channels the line lies where
-// heads break even; 3x3 layers of 0.1-0.6 million, which the tests of ragged channels want on the matrix cores, lose up to
-// 1.3 us by it.
+// 32x512 to 10 5.5 / 5.2; 128x512 to 2 (131 thousand) 5.3 / 5.7, to 4 (262 thousand) 6.2 / 5.6; 28x28 64 to 1 channel 3x3 (451
+// thousand) 7.1 / 10.8, to 2 (903 thousand) 8.3 / 10.7, 8x14x14 64 to 2 (1.8 million) 11.1 / 11.1; 8x28x28 16 to 1 (6272 pixels)
+// 12.7 / 7.5.  Above 4 channels the line lies where heads break even; convolutions of 0.1-0.6 million, which the tests of ragged
+// channels want on the matrix cores, lose up to 1.7 us by it.
 bool small_ragged_dw(const ConvShape &s)
 {
-    const long long m = (long long)s.N * s.P * s.Q, macs = m * s.K * s.C * s.R * s.S;
+    const long long m = (long long)s.N * s.P * s.Q;
     if (m > 1600) return false;
-    return macs <= (s.K > 4 ? 3 << 15 : s.pad > 0 || m > 400 ? 1 << 20 : 1 << 18);
+    return m * s.K * s.C * s.R * s.S <= (s.K > 4 ? 3 << 15 : s.pad > 0 || m > 400 ? 1 << 20 : 1 << 17);
 }
 
 // whether a matrix-core path takes the (padded) problem, in the order the passes below try them

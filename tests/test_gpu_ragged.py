@@ -67,6 +67,8 @@ def test_ragged_channels(mxc, oracle, dims, layout):
 SMALL = [
     ((128, 512, 1, 1, 10, 1, 1, 1, 0), True, False),
     ((8, 512, 1, 1, 10, 1, 1, 1, 0), True, True),
+    ((128, 512, 1, 1, 2, 1, 1, 1, 0), True, True),
+    ((128, 513, 1, 1, 2, 1, 1, 1, 0), True, False),
     ((24, 72, 1, 1, 39, 1, 1, 1, 0), True, True),
     ((24, 72, 1, 1, 41, 1, 1, 1, 0), False, True),
     ((300, 64, 1, 1, 100, 1, 1, 1, 0), False, False),
