@@ -55,23 +55,6 @@ template <int I> using IC = std::integral_constant<int, I>;
 template <class F, int... I> __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) { (f(IC<I>{}), ...); }
 template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
-// n / d for 0 <= n < 2^31 as a multiplication, by the method of Granlund and Montgomery (Division by Invariant Integers using
-// Multiplication, PLDI 1994): m = floor(2^32 * (2^l - d) / d) + 1 with 2^(l-1) < d <= 2^l, and n / d = (mulhi(m, n) + n) >> l.
-// The compiler's division by a variable is some thirty instructions, and a tile's setup has dozens of them (they were two thirds
-// of a small layer's kernel time).
-struct FastDiv {
-    unsigned mul = 0, shift = 0;
-    int d = 1;
-    FastDiv() = default;
-    explicit FastDiv(int divisor) : d(divisor > 0 ? divisor : 1)
-    {
-        while (shift < 31 && (1u << shift) < (unsigned)d) ++shift;
-        mul = (unsigned)(((1ull << 32) * ((1ull << shift) - (unsigned)d)) / (unsigned)d + 1);
-    }
-    __device__ __forceinline__ int div(int n) const { return (int)((__umulhi(mul, (unsigned)n) + (unsigned)n) >> shift); }
-    __device__ __forceinline__ int mod(int n) const { return n - div(n) * d; }
-};
-
 // A stride residue class of backward-data; forward has one, the whole problem.
 struct F32Class {
     int tile0;              // first row tile
@@ -100,10 +83,6 @@ struct F32Params {
     const float *mask;      // backward-data, or null: the result is 0 where mask <= 0
     int outside;            // whether any result has a tap outside the gathered tensor
 };
-
-// floor(t / d) for 0 <= t <= 127, 1 <= d <= 127
-__device__ __forceinline__ int small_div(int t, int magic) { return (t * magic) >> 16; }
-inline int small_magic(int d) { return (65536 + d - 1) / d; }
 
 __device__ __forceinline__ int pack_hw(int h, int w) { return (h & 0xFFFF) | (w << 16); }
 // nonzero where (h, w) + (dh, dw) leaves the image; all packed as two 16-bit integers

@@ -893,9 +893,8 @@ double model_time(const TileChoice &t, long long M, int Co, int KT, double fixed
 thread_local long long g_key_M = 0;
 thread_local int g_key_Co = 0, g_key_Kd = 0;
 
-Plan choose_plan(long long M, int Co, int Kd, bool allow_stream = true, bool masked = false)
+Plan search_plan(long long M, int Co, int Kd, bool allow_stream, bool masked)
 {
-    g_key_M = M; g_key_Co = Co; g_key_Kd = Kd;
     if (const char *f = getenv("MXC_FORCE_VARIANT")) {
         const char *plus = strchr(f, '+'), *slash = strchr(f, '/');
         const int a = tile_index(f, plus ? (size_t)(plus - f) : slash ? (size_t)(slash - f) : strlen(f));
@@ -935,6 +934,20 @@ Plan choose_plan(long long M, int Co, int Kd, bool allow_stream = true, bool mas
         }
     }
     return best;
+}
+
+// The search walks the table and every pair of shapes, and a call asks several times (size query, filter form, launch): the
+// calling thread keeps its last answers.
+Plan choose_plan(long long M, int Co, int Kd, bool allow_stream = true, bool masked = false)
+{
+    g_key_M = M; g_key_Co = Co; g_key_Kd = Kd;
+    if (getenv("MXC_FORCE_VARIANT")) return search_plan(M, Co, Kd, allow_stream, masked);
+    struct Entry { long long M; int Co, Kd, flags; Plan plan; };
+    static thread_local Entry cache[64] = {};
+    const int flags = 1 + (allow_stream ? 2 : 0) + (masked ? 4 : 0);       // never 0, as an unused entry's are
+    Entry &e = cache[(unsigned)(M * 31 + Co * 7 + Kd * 3 + flags) % 64];
+    if (e.M != M || e.Co != Co || e.Kd != Kd || e.flags != flags) e = Entry{M, Co, Kd, flags, search_plan(M, Co, Kd, allow_stream, masked)};
+    return e.plan;
 }
 
 int choose_tile(long long M, int Co, int Kd) { return choose_plan(M, Co, Kd, false).main; }
@@ -1020,6 +1033,40 @@ int split_count(long long M, int Co, int Kd)
     if (sp > KT / 8) sp = KT / 8;
     if (sp > 32) sp = 32;
     return sp >= 2 ? (int)sp : 1;
+}
+
+// Modelled time (us, fitted to the 828 GEMMs of wave.hip's model, 9% off) of one tile shape on all rows in `splits` ranges of
+// the reduction: launch, the CU's share of padded tile area, partial tiles, rounds, results and mask.
+double tile_us(const TileChoice &t, long long M, int Co, int Kd, int splits, bool masked)
+{
+    const long long tiles = ((M + t.bm - 1) / t.bm) * ((Co + t.bn - 1) / t.bn) * splits, per_cu = (tiles + 255) / 256;
+    const long long resident = per_cu < t.slots ? per_cu : t.slots, rounds = (per_cu + t.slots - 1) / t.slots;
+    const int KT = ((Kd + 63) / 64 + splits - 1) / splits;
+    const double util = t.util * (0.6 + 0.4 * resident / t.slots), mc = 1e-6 * M * Co;
+    return 2.37 + 1.38 * per_cu * t.bm * t.bn / 65536.0 / util * KT + 2.14 * rounds + (splits > 1 ? 1.7 + 2.19 * splits * mc : 0) + (masked ? 0.92 : 0.46) * mc;
+}
+
+// The shape of the wave kernel (wave.hip) that runs this GEMM, or -1: the planned kernel does.  Of the 828 GEMMs the planned
+// kernel takes below 8, 8-12, 12-20, 20-40 and more us, this choice runs 1.39, 1.64, 1.33, 1.18 and 1.08 times as fast (best
+// shape of all: 1.42, 1.67, 1.36, 1.22, 1.12).  The models must agree by a margin, larger where tiles are many: there a tile
+// that several waves share moves less per multiply-add, and what the models miss weighs more.
+int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_split)
+{
+    if (const char *f = getenv("MXC_FORCE_VARIANT")) return wave_forced(f, bwd);
+    struct Entry { long long M; int Co, Kd, flags, wave; };
+    static thread_local Entry cache[64] = {};
+    const int flags = 1 + (bwd ? 2 : 0) + (masked ? 4 : 0) + (can_split ? 8 : 0);
+    Entry &e = cache[(unsigned)(M * 31 + Co * 7 + Kd * 3 + flags) % 64];
+    if (e.M == M && e.Co == Co && e.Kd == Kd && e.flags == flags) return e.wave;
+    const Plan pl = choose_plan(M, Co, Kd, true, masked);
+    double us = 0;
+    int wave = whole_launch(pl.main) ? -1 : wave_best(M, Co, Kd, bwd, masked, &us);
+    if (wave >= 0) {
+        const double other = tile_us(kTiles[pl.main], M, Co, Kd, can_split ? split_count(M, Co, Kd) : 1, masked);
+        if (us > other * (us < 20 ? 0.92 : 0.85)) wave = -1;
+    }
+    e = Entry{M, Co, Kd, flags, wave};
+    return wave;
 }
 
 // out[m][co] = act(sum_z partial[z][m][co] + bias[co]) in ascending z (fixed order), 4 columns per thread
@@ -1112,6 +1159,10 @@ int igemm_fwd(const ConvShape &s, const void *x, const void *w, void *y, hipStre
     p.in_mul_h = s.stride; p.in_mul_w = s.stride; p.in_off_h = -s.pad; p.in_off_w = -s.pad;
     p.Ho = s.P; p.Wo = s.Q; p.out_mul_h = 1; p.out_mul_w = 1; p.out_off_h = 0; p.out_off_w = 0;
     const long long M = (long long)s.N * s.P * s.Q;
+    if (const int wv = wave_choice(M, s.K, s.R * s.S * s.C, false, false, split_ws != nullptr && s.K % 8 == 0); wv >= 0) {
+        *variant = wave_name(wv);
+        return wave_launch(wv, p, st, false);
+    }
     const int sp = (split_ws != nullptr && s.K % 8 == 0) ? split_count(M, s.K, s.R * s.S * s.C) : 1;
     const Plan pl = plan_for(p, M, s.K, s.R * s.S * s.C, sp > 1);
     *variant = plan_name(pl);
@@ -1163,6 +1214,10 @@ int igemm_fwd_smallc(const ConvShape &s, const void *xp, const void *wp, void *y
     p.Mh = s.P; p.Mw = s.Q;
     p.in_mul_h = s.stride; p.in_mul_w = s.stride; p.in_off_h = 0; p.in_off_w = 0;
     p.Ho = s.P; p.Wo = s.Q; p.out_mul_h = 1; p.out_mul_w = 1; p.out_off_h = 0; p.out_off_w = 0;
+    if (const int wv = wave_choice((long long)s.N * s.P * s.Q, s.K, s.R * g.run, false, false, false); wv >= 0) {
+        *variant = wave_name(wv);
+        return wave_launch(wv, p, st, false);
+    }
     const Plan pl = plan_for(p, (long long)s.N * s.P * s.Q, s.K, s.R * g.run);
     *variant = plan_name(pl);
     return launch_plan(pl, p, st);
@@ -1252,7 +1307,7 @@ bool bwd_data_small_in_place(const ConvShape &s, bool masked)
     if (real_c(s) != s.C || s.C % 8 != 0 || s.stride != 1 || bwd_data_reads_filter_in_place(s)) return false;
     const long long M = (long long)s.N * s.H * s.W;
     const int Kd = s.R * s.S * s.K;
-    if (bwd_data_streams_filter(s, masked)) return true;
+    if (wave_choice(M, s.C, Kd, true, masked, true) >= 0 || bwd_data_streams_filter(s, masked)) return true;
     const Plan pl = choose_plan(M, s.C, Kd, true, masked);
     if (whole_launch(pl.main) || !has_bt(pl.main) || (pl.tail >= 0 && !has_bt(pl.tail))) return false;
     return 2.0 * M * s.C * Kd < 1e10;
@@ -1287,6 +1342,10 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
         p.wm_by_k = bt && !bwd_data_reads_filter_in_place(s) && bwd_data_streams_filter(s, p.mask != nullptr);
         const long long M = (long long)s.N * s.H * s.W;
         const int Kd = s.R * s.S * s.K;
+        if (const int wv = wave_choice(M, s.C, Kd, true, p.mask != nullptr, s.C % 8 == 0); wv >= 0) {
+            *variant = wave_name(wv);
+            return wave_launch(wv, p, st, bt);
+        }
         const int sp = (split_ws != nullptr && s.C % 8 == 0) ? split_count(M, s.C, Kd) : 1;
         Plan pl = plan_for(p, M, s.C, Kd, (bt && !p.wm_by_k) || sp > 1);
         if (bt && !p.wm_by_k && !has_bt(pl.tail)) pl = Plan{pl.main, -1, 0};

@@ -223,6 +223,27 @@ __device__ __forceinline__ uint4 mask_bf16x8(uint4 v, uint4 m)
     return make_uint4(mask_bf16x2(v.x, m.x), mask_bf16x2(v.y, m.y), mask_bf16x2(v.z, m.z), mask_bf16x2(v.w, m.w));
 }
 
+// n / d for 0 <= n < 2^31 as a multiplication, by the method of Granlund and Montgomery (Division by Invariant Integers using
+// Multiplication, PLDI 1994): m = floor(2^32 * (2^l - d) / d) + 1 with 2^(l-1) < d <= 2^l, and n / d = (mulhi(m, n) + n) >> l.
+// The compiler's division by a variable is some thirty instructions, and a tile's setup has dozens of them (they were two thirds
+// of a small layer's kernel time).
+struct FastDiv {
+    unsigned mul = 0, shift = 0;
+    int d = 1;
+    FastDiv() = default;
+    explicit FastDiv(int divisor) : d(divisor > 0 ? divisor : 1)
+    {
+        while (shift < 31 && (1u << shift) < (unsigned)d) ++shift;
+        mul = (unsigned)(((1ull << 32) * ((1ull << shift) - (unsigned)d)) / (unsigned)d + 1);
+    }
+    __device__ __forceinline__ int div(int n) const { return (int)((__umulhi(mul, (unsigned)n) + (unsigned)n) >> shift); }
+    __device__ __forceinline__ int mod(int n) const { return n - div(n) * d; }
+};
+
+// floor(t / d) for 0 <= t <= 127, 1 <= d <= 127
+__device__ __forceinline__ int small_div(int t, int magic) { return (t * magic) >> 16; }
+inline int small_magic(int d) { return (65536 + d - 1) / d; }
+
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline size_t elem_size(int dtype) { return dtype == MXC_BF16 ? 2 : 4; }
 
@@ -407,6 +428,14 @@ bool window_applicable(const IgemmParams &p);
 // two patches or more for every CU, at most a third of their rows past the image
 bool window_fills_chip(const IgemmParams &p);
 int window_launch(const IgemmParams &p, hipStream_t st);
+
+// wave.hip: the same GEMM for problems that fill a fraction of the chip and for short reductions (see there).  Shapes are
+// numbered from 0; bwd: backward-data, whose shapes can all read the filter in place; bt: wm is the KRSC filter itself (see
+// IgemmParams).  wave_best: the shape of least modelled time and that time, or -1.
+const char *wave_name(int shape);
+int wave_forced(const char *name, bool bwd);
+int wave_best(long long M, int Co, int Kd, bool bwd, bool masked, double *us);
+int wave_launch(int shape, const IgemmParams &p, hipStream_t st, bool bt);
 
 // ---- prep.hip: re-packing for channel counts that are not a multiple of 8 ---------
 // Small-C (C <= 4) image packing: `pix` channels per pixel, explicit zero border, padded size Hp x Wp;
