@@ -471,6 +471,32 @@ WgradGeom wgrad_geom_s2d(const ConvShape &s);       // x already packed by s2d_p
 WgradGeom wgrad_geom_plain(const ConvShape &s);     // C % 8 == 0
 WgradGeom wgrad_geom_chanpad(const ConvShape &s);   // x already padded to C8 channels
 WgradGeom wgrad_geom_smallc(const ConvShape &s);    // x already packed by smallc_pack_x
+// Where an element of the summed [K][ncols] tensor belongs: dw has the same order, or it is dw[k][r][s][c] (or
+// dw[k][c][r][s]) of column (r/d)*col_r + (s/d)*col_s + ((r%d)*d + s%d)*Cq + c, and padded rows and columns are dropped.
+enum { DW_SAME = 0, DW_KRSC = 1, DW_KCRS = 2 };
+struct DwMap {
+    int order, ncols, Kout, R, S, C, col_r, col_s, d, Cq;
+};
+// element (k, col)'s place in dw and its filter tap (r, s) and channel, or -1
+__device__ __forceinline__ long long dw_place(const DwMap &m, int k, int col, int &r, int &s, int &c)
+{
+    const int rb = col / m.col_r, in_r = col - rb * m.col_r, sb = in_r / m.col_s, in_s = in_r - sb * m.col_s;
+    const int blk = m.d > 1 ? in_s / m.Cq : 0;
+    c = in_s - blk * m.Cq;
+    r = rb * m.d + blk / m.d; s = sb * m.d + blk % m.d;
+    if (k >= m.Kout || r >= m.R || s >= m.S || c >= m.C) return -1;
+    return m.order == DW_KRSC ? (((long long)k * m.R + r) * m.S + s) * m.C + c : (((long long)k * m.C + c) * m.R + r) * m.S + s;
+}
+
+// wave_dw.hip: backward-weight of small problems (see there).  Shapes are numbered from 0.  out: `ranges` partial tensors
+// [K][ncols] of `span` pixels each (a multiple of 32), or with one range dw itself, mapped or (map null) as it lies.
+// wave_dw_best: the shape and ranges (at most max_ranges) of least modelled time and that time, or -1.
+const char *wave_dw_name(int shape);
+int wave_dw_ranges(long long M, int ranges, int *span);        // the number of ranges there are, none empty, and their length
+int wave_dw_best(const WgradGeom &g, int max_ranges, int *ranges, double *us);
+int wave_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const void *x, const void *dy, void *out, const DwMap *map, bool dw_bf16, int rows,
+                   hipStream_t st);
+
 bool wgrad_supported(const WgradGeom &g);
 size_t wgrad_workspace(const WgradGeom &g);            // bytes of fp32 partial tiles
 // dw: fp32, or bf16 (the fp32 sum rounded once, by the reduce kernel) when dw_bf16; KRSC, or KCRS when kcrs

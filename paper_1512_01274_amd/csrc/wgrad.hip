@@ -371,13 +371,6 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec4_kernel(const float4 *pa
     if (grp == 0 && gid < total4) store4(dw, gid, acc);
 }
 
-// Where an element of the summed [K][ncols] tensor belongs: dw has the same order, or it is dw[k][r][s][c] (or
-// dw[k][c][r][s]) of column (r/d)*col_r + (s/d)*col_s + ((r%d)*d + s%d)*Cq + c, and padded rows and columns are dropped.
-enum { DW_SAME = 0, DW_KRSC = 1, DW_KCRS = 2 };
-struct DwMap {
-    int order, ncols, Kout, R, S, C, col_r, col_s, d, Cq;
-};
-
 // Many splits of a small dw, and every dw whose order differs from the columns': the four waves of a workgroup share 64/G
 // groups of four outputs, so 4*G splits are in flight per output, and the sums go to their places from LDS.  What bounds
 // it is the chain of dependent additions and the launch: as two launches (a wave's 16 groups, then the re-ordering one
@@ -413,13 +406,12 @@ __global__ __launch_bounds__(256) void wgrad_reduce_map_kernel(const float4 *__r
     float v = ((r0[t] + r0[LPG * 4 + t]) + r0[LPG * 8 + t]) + r0[LPG * 12 + t];
     if (m.order == DW_SAME) { store_f32(dw + e, v); return; }
     const int k = e / m.ncols, col = e - k * m.ncols;
-    const int rb = col / m.col_r, in_r = col - rb * m.col_r, sb = in_r / m.col_s, in_s = in_r - sb * m.col_s;
-    const int blk = m.d > 1 ? in_s / m.Cq : 0, c = in_s - blk * m.Cq;
-    const int r = rb * m.d + blk / m.d, sc = sb * m.d + blk % m.d;
-    if (k >= m.Kout || r >= m.R || sc >= m.S || c >= m.C) return;
+    int r, sc, c;
+    const long long to = dw_place(m, k, col, r, sc, c);
+    if (to < 0) return;
     if constexpr (std::is_same_v<R, Resum>)
         if (is_nan(v)) v = rs.nchw ? sum_dw<true>(rs.s, rs.a, rs.b, k, c, r, sc, 0, 1) : sum_dw<false>(rs.s, rs.a, rs.b, k, c, r, sc, 0, 1);
-    store_f32(dw + (m.order == DW_KRSC ? (((size_t)k * m.R + r) * m.S + sc) * m.C + c : (((size_t)k * m.C + c) * m.R + r) * m.S + sc), v);
+    store_f32(dw + to, v);
 }
 
 // General form: dw[k][r][s][c] is read back from column (r/d)*col_r + (s/d)*col_s + ((r%d)*d + s%d)*Cq + c of
@@ -520,13 +512,16 @@ int launch_choice(int idx, const WgradParams &p, int tiles, hipStream_t st)
     }
 }
 
-struct Plan { int tile, k_tiles, n_tiles, splits, span; };
+// wave: the wave kernel's shape, pixel ranges and their length, where it runs instead of the tile (shape -1: it does not)
+struct DwWave { int shape, ranges, span; };
+struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave; };
 
 // Tile and split choice: the pair with the least modelled time - rounds over the chip's workgroup
 // slots (256 CUs x slots per CU) x stages each split walks x time per stage, plus the traffic of
 // writing and re-reading one fp32 partial tensor per split.  MXC_FORCE_WGRAD=<name> (tuning sweeps
 // only) fixes the tile.
 Plan search_plan(const WgradGeom &g, int forced, int forced_splits);
+DwWave wave_choice(const WgradGeom &g, const Plan &pl);
 
 #include "tuned_wgrad.inc"
 
@@ -559,6 +554,11 @@ Plan make_plan(const WgradGeom &g)
                 break;
             }
     }
+    if (getenv("MXC_FORCE_WGRAD")) {
+        Plan pl = search_plan(g, forced, forced_splits);
+        pl.wave = wave_choice(g, pl);
+        return pl;
+    }
     struct Entry { WgradGeom g; int forced, forced_splits; Plan plan; bool used; };
     static thread_local Entry cache[32] = {};
     static thread_local int next = 0;
@@ -567,8 +567,48 @@ Plan make_plan(const WgradGeom &g)
     Entry &slot = cache[next];
     next = (next + 1) % 32;
     slot.g = g; slot.forced = forced; slot.forced_splits = forced_splits; slot.plan = search_plan(g, forced, forced_splits);
+    slot.plan.wave = wave_choice(g, slot.plan);
     slot.used = true;
     return slot.plan;
+}
+
+// Modelled time (us, fitted to the gradients of wave_dw.hip's model, 8% off) of the planned tile: stages and rounds of the CU
+// with most tiles, and the partial tensors.
+double tile_us(const WgradGeom &g, const Plan &pl)
+{
+    const WgradTile &t = kTiles[pl.tile];
+    const long long M = (long long)g.N * g.P * g.Q, per_cu = ((long long)pl.k_tiles * pl.n_tiles * pl.splits + 255) / 256, rounds = (per_cu + t.slots - 1) / t.slots;
+    const double stages = (double)(((M + pl.splits - 1) / pl.splits + t.bp - 1) / t.bp), mb = 4e-6 * g.K * g.TR * g.TS * g.run;
+    return rounds * (0.783 * stages + 3.01) + 1.679 * per_cu * t.bm * t.bn / 65536.0 + (pl.splits > 1 ? 2.3 + 0.685 * pl.splits * mb : 0);
+}
+
+// The shape of the wave kernel (wave_dw.hip) that runs this gradient and its pixel ranges, or shape -1: the planned tile.  It never
+// takes more ranges than the plan has, which the workspace is sized for.  Of the 305 gradients the planned tiles take below 8,
+// 8-15, 15-30 and more us, this choice runs 1.47, 1.72, 1.37 and 1.06 times as fast.  From 36 us on bytes and shared
+// tiles count for more than the models know (96138 pixels, 24 x 3456: 84 -> 92).
+DwWave wave_choice(const WgradGeom &g, const Plan &pl)
+{
+    const long long M = (long long)g.N * g.P * g.Q;
+    DwWave w{-1, 0, 0};
+    if (const char *f = getenv("MXC_FORCE_WGRAD")) {
+        const char *slash = strchr(f, '/');
+        const size_t len = slash ? (size_t)(slash - f) : strlen(f);
+        for (int i = 0; const char *n = wave_dw_name(i); ++i)
+            if (strlen(n) == len && !strncmp(f, n, len)) {
+                const int want = slash ? atoi(slash + 1) : 1;
+                w.shape = i;
+                w.ranges = wave_dw_ranges(M, want < 1 ? 1 : want < pl.splits ? want : pl.splits, &w.span);
+            }
+        return w;
+    }
+    double us = 0;
+    int ranges = 1;
+    const int shape = wave_dw_best(g, pl.splits, &ranges, &us);
+    if (shape >= 0 && us < 36 && us < 0.93 * tile_us(g, pl)) {
+        w.shape = shape;
+        w.ranges = wave_dw_ranges(M, ranges, &w.span);
+    }
+    return w;
 }
 
 Plan search_plan(const WgradGeom &g, int forced, int forced_splits)
@@ -604,7 +644,7 @@ Plan search_plan(const WgradGeom &g, int forced, int forced_splits)
                 best = t_us;
                 long long span = (M + sp - 1) / sp;
                 span = (span + tc.bp - 1) / tc.bp * tc.bp;
-                best_pl = Plan{t, k_tiles, n_tiles, (int)((M + span - 1) / span), (int)span};
+                best_pl = Plan{t, k_tiles, n_tiles, (int)((M + span - 1) / span), (int)span, {-1, 0, 0}};
             }
         }
     }
@@ -652,6 +692,13 @@ size_t wgrad_workspace(const WgradGeom &g)
     return (size_t)make_plan(g).splits * g.K * g.TR * g.TS * g.run * sizeof(float);
 }
 
+static DwMap dw_map(const WgradGeom &g, int ncols, int order) { return DwMap{order, ncols, g.Kout, g.R, g.S, g.C, g.col_r, g.col_s, g.s2d, g.Cq}; }
+// whether the filter columns are dw's own, in KRSC order
+static bool dw_identity(const WgradGeom &g)
+{
+    return g.s2d == 1 && g.col_s == g.C && g.col_r == g.S * g.C && g.TR * g.TS * g.run == g.R * g.S * g.C;
+}
+
 template <typename OUT>
 static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits, int ncols, bool identity, bool kcrs, hipStream_t st,
                          const Resum *resum = nullptr)
@@ -669,7 +716,7 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
         // (a lane adds up 2^15 pixels in some 20 ms, should it come to that; the kernel of its own shares them out)
         const bool fused = resum != nullptr && (long long)g.N * g.P * g.Q <= 1 << 15;
         const bool ident = !kcrs && identity && !fused;
-        const DwMap m{ident ? DW_SAME : kcrs ? DW_KCRS : DW_KRSC, ncols, g.Kout, g.R, g.S, g.C, g.col_r, g.col_s, g.s2d, g.Cq};
+        const DwMap m = dw_map(g, ncols, ident ? DW_SAME : kcrs ? DW_KCRS : DW_KRSC);
         const int total4 = ident ? total / 4 : g.K * ncols / 4;       // ncols is a multiple of 8 where the order differs
         const size_t stride4 = split_stride / 4;
         // below 32 splits 16 in flight are enough, and four times as many outputs share a cache line's worth of a split
@@ -732,6 +779,20 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
           const char **variant, const Resum *resum)
 {
     const Plan pl = make_plan(g);
+    if (const DwWave wv = pl.wave; wv.shape >= 0) {
+        const int ncols = g.TR * g.TS * g.run;
+        const bool same = dw_identity(g) && !kcrs;
+        *variant = wave_dw_name(wv.shape);
+        if (wv.ranges > 1) {
+            const int rc = wave_dw_launch(wv.shape, g, wv.ranges, wv.span, x, dy, partial, nullptr, false, g.K, st);
+            if (rc != MXC_OK) return rc;
+            return dw_bf16 ? launch_reduce(g, partial, (bf16_t *)dw, wv.ranges, ncols, dw_identity(g), kcrs, st, resum)
+                           : launch_reduce(g, partial, (float *)dw, wv.ranges, ncols, dw_identity(g), kcrs, st, resum);
+        }
+        const DwMap m = dw_map(g, ncols, kcrs ? DW_KCRS : DW_KRSC);
+        const int rc = wave_dw_launch(wv.shape, g, 1, wv.span, x, dy, dw, same && !dw_bf16 ? nullptr : &m, dw_bf16, g.Kout, st);
+        return rc == MXC_OK && resum != nullptr ? resum_dw(*resum, dw, dw_bf16, st) : rc;
+    }
     const WgradTile &tc = kTiles[pl.tile];
     WgradParams p{};
     p.x = (const bf16_t *)x; p.dy = (const bf16_t *)dy; p.partial = partial;
@@ -750,7 +811,7 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
     p.dy_bytes = (unsigned)((long long)p.M * g.K * 2);
     const long long tiles = (long long)pl.k_tiles * pl.n_tiles;
     if (tiles * p.splits > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
-    const bool identity = g.s2d == 1 && g.col_s == g.C && g.col_r == g.S * g.C && p.ncols == g.R * g.S * g.C;
+    const bool identity = dw_identity(g);
     // one split whose columns are already in KRSC order and an fp32 result: the "partial" tensor is dw itself
     // (without the rows of padded channels)
     const bool direct = p.splits == 1 && identity && !dw_bf16 && !kcrs;
