@@ -13,6 +13,9 @@
 // lanes on 64 contiguous bytes: 110).  A block of 16 rows x 32 elements is one direct global->LDS load: lane l brings chunk
 // (l%4) ^ (l/16) of row l/4, which makes the ds_read_b128 fetches conflict-free.  A filter that lies transposed (backward-data
 // reading the KRSC filter in place: BT) lands as 32 rows of 16*NB columns and is fetched with ds_read_b64_tr_b16.
+//
+// Measured (us, pixels x columns x reduction, igemm.hip's tile -> this kernel): 392 x 56 x 448 6.4 -> 3.4; 392 x 56 x 576 in 3x3
+// taps 6.7 -> 3.7; 2704 x 160 x 1000 10.8 -> 6.0; 46464 x 288 x 24 15.1 -> 10.9.
 #include <stdlib.h>
 #include <string.h>
 

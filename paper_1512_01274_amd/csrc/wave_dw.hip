@@ -12,8 +12,8 @@
 // first: lane 16*g + i holds columns 4*g .. 4*g + 3 of filter k = i of a block, 16 bytes of dw.
 //
 // What bounds it: the loads, 4-8 KB per wave and step, while the chip is part-filled their latency.  Measured (us with the
-// summing launch where there is one, planned tile -> this kernel): 440 pixels, 256 filters x 112 columns 8.4 -> 3.5; 1944,
-// 144 x 800 13.4 -> 5.5; 28125, 32 x 288 14 -> 7; 21318, 208 x 96 14.9 -> 9.5.  Which problems it gets: make_plan in wgrad.hip.
+// summing launch where there is one, planned tile -> this kernel): 440 pixels, 256 filters x 112 columns 8.4 -> 3.4; 1944,
+// 144 x 800 13.6 -> 5.7; 28120, 32 x 288 13.0 -> 8.4; 21318, 208 x 96 15.0 -> 10.0.  Which problems it gets: make_plan in wgrad.hip.
 #include <stdlib.h>
 #include <string.h>
 
@@ -231,15 +231,16 @@ __global__ __launch_bounds__(64 * KG) void wave_dw_kernel(const DwParams p)
     }
 }
 
-// The shapes and, for each, the time model that picks one (us, fitted to 305 gradients of 50 to 644 thousand pixels on the device,
-// 9-11% off): fixed + round * (rounds of workgroups that fit a CU) + turn * (rounds times steps per wave) + area * (blocks of the
-// CU with most tiles) + dw * (MB of dw) + with several ranges 2.75 and part * (MB of partial tensors).
-struct DwShape { int mb, nb, kg, u, ns; const char *name; float fixed, round, turn, area, dw, part; };
+// The shapes and, for each, the time model that picks one (us, fitted to 543 gradients of 50 to 740 thousand pixels on the device,
+// 9-10% off): fixed + round * (rounds of workgroups that fit a CU) + turn * (rounds times steps per wave) + mb * (MB that all
+// workgroups load) + area * (ten blocks of the CU with most tiles) + dw * (MB of dw) + with several ranges 2.45 and part * (MB of
+// partial tensors).
+struct DwShape { int mb, nb, kg, u, ns; const char *name; float fixed, round, turn, load, area, dw, part; };
 #define SHAPES(X) \
-    X(0, 2, 2, 8, 1, 4, "wgrad_wave_32x32_w8", 2.21f, 0.699f, 0.312f, 0.f, 0.893f, 1.018f) \
-    X(1, 2, 4, 8, 1, 3, "wgrad_wave_32x64_w8", 1.96f, 0.961f, 0.525f, 0.f, 0.699f, 0.767f) \
-    X(2, 4, 2, 8, 1, 3, "wgrad_wave_64x32_w8", 1.72f, 1.236f, 0.478f, 0.f, 0.549f, 0.698f) \
-    X(3, 4, 4, 8, 1, 2, "wgrad_wave_64x64_w8", 2.28f, 0.f, 0.748f, 0.070f, 0.420f, 0.610f)
+    X(0, 2, 2, 8, 1, 4, "wgrad_wave_32x32_w8", 2.53f, 0.919f, 0.197f, 0.033f, 0.f, 0.020f, 0.304f) \
+    X(1, 2, 4, 8, 1, 3, "wgrad_wave_32x64_w8", 2.28f, 1.184f, 0.370f, 0.026f, 0.f, 0.186f, 0.405f) \
+    X(2, 4, 2, 8, 1, 3, "wgrad_wave_64x32_w8", 2.31f, 1.079f, 0.354f, 0.021f, 0.f, 0.195f, 0.535f) \
+    X(3, 4, 4, 8, 1, 2, "wgrad_wave_64x64_w8", 2.57f, 0.f, 0.571f, 0.016f, 0.737f, 0.259f, 0.481f)
 #define X(I, MB, NB, KG, U, NS, NAME, ...) {MB, NB, KG, U, NS, NAME, __VA_ARGS__},
 const DwShape kShapes[] = {SHAPES(X)};
 #undef X
@@ -283,8 +284,9 @@ int wave_dw_best(const WgradGeom &g, int max_ranges, int *ranges, double *us)
             z = wave_dw_ranges(M, (int)z, &span);
             const long long per_cu = (tiles * z + 255) / 256;
             const double rounds = (double)((per_cu + slots - 1) / slots), turns = (double)((span + 32 * s.kg * s.u - 1) / (32 * s.kg * s.u));
-            double t = s.fixed + s.round * rounds + s.turn * rounds * turns + s.area * per_cu * s.mb * s.nb + s.dw * mb;
-            if (z > 1) t += 2.75 + s.part * z * mb;
+            double t = s.fixed + s.round * rounds + s.turn * rounds * turns + s.load * 1e-3 * tiles * z * turns * s.kg * s.u * (s.mb + s.nb) +
+                       s.area * 0.1 * per_cu * s.mb * s.nb + s.dw * mb;
+            if (z > 1) t += 2.45 + s.part * z * mb;
             else if (g.K != g.Kout && g.opad > 0) t += 2.4;       // sums that padding made NaN: a launch of its own looks
             if (best < 0 || t < *us) { best = i; *us = t; *ranges = (int)z; }
         }

@@ -554,38 +554,40 @@ Plan make_plan(const WgradGeom &g)
                 break;
             }
     }
-    if (getenv("MXC_FORCE_WGRAD")) {
-        Plan pl = search_plan(g, forced, forced_splits);
-        pl.wave = wave_choice(g, pl);
+    // (what the hook forces on the wave kernel is looked up again on every call)
+    const bool hook = getenv("MXC_FORCE_WGRAD") != nullptr;
+    auto with_wave = [&](Plan pl) {
+        if (hook) pl.wave = wave_choice(g, pl);
         return pl;
-    }
-    struct Entry { WgradGeom g; int forced, forced_splits; Plan plan; bool used; };
+    };
+    struct Entry { WgradGeom g; int forced, forced_splits; bool hook; Plan plan; bool used; };
     static thread_local Entry cache[32] = {};
     static thread_local int next = 0;
     for (const Entry &e : cache)
-        if (e.used && e.forced == forced && e.forced_splits == forced_splits && !memcmp(&e.g, &g, sizeof(WgradGeom))) return e.plan;
+        if (e.used && e.forced == forced && e.forced_splits == forced_splits && e.hook == hook && !memcmp(&e.g, &g, sizeof(WgradGeom))) return with_wave(e.plan);
     Entry &slot = cache[next];
     next = (next + 1) % 32;
     slot.g = g; slot.forced = forced; slot.forced_splits = forced_splits; slot.plan = search_plan(g, forced, forced_splits);
-    slot.plan.wave = wave_choice(g, slot.plan);
+    if (!hook) slot.plan.wave = wave_choice(g, slot.plan);
+    slot.hook = hook;
     slot.used = true;
-    return slot.plan;
+    return with_wave(slot.plan);
 }
 
-// Modelled time (us, fitted to the gradients of wave_dw.hip's model, 8% off) of the planned tile: stages and rounds of the CU
+// Modelled time (us, fitted to the gradients of wave_dw.hip's model, 9% off) of the planned tile: stages and rounds of the CU
 // with most tiles, and the partial tensors.
 double tile_us(const WgradGeom &g, const Plan &pl)
 {
     const WgradTile &t = kTiles[pl.tile];
     const long long M = (long long)g.N * g.P * g.Q, per_cu = ((long long)pl.k_tiles * pl.n_tiles * pl.splits + 255) / 256, rounds = (per_cu + t.slots - 1) / t.slots;
     const double stages = (double)(((M + pl.splits - 1) / pl.splits + t.bp - 1) / t.bp), mb = 4e-6 * g.K * g.TR * g.TS * g.run;
-    return rounds * (0.783 * stages + 3.01) + 1.679 * per_cu * t.bm * t.bn / 65536.0 + (pl.splits > 1 ? 2.3 + 0.685 * pl.splits * mb : 0);
+    return rounds * (0.731 * stages + 3.09) + 1.825 * per_cu * t.bm * t.bn / 65536.0 + (pl.splits > 1 ? 2.33 + 0.664 * pl.splits * mb : 0);
 }
 
 // The shape of the wave kernel (wave_dw.hip) that runs this gradient and its pixel ranges, or shape -1: the planned tile.  It never
-// takes more ranges than the plan has, which the workspace is sized for.  Of the 305 gradients the planned tiles take below 8,
-// 8-15, 15-30 and more us, this choice runs 1.47, 1.72, 1.37 and 1.06 times as fast.  From 36 us on bytes and shared
-// tiles count for more than the models know (96138 pixels, 24 x 3456: 84 -> 92).
+// takes more ranges than the plan has, which the workspace is sized for.  Of the 543 gradients it runs 1.43 times as fast as
+// the planned tiles alone (below 8, 8-15, 15-30, above 30 us: 1.43, 1.63, 1.38, 1.02).  The margin is larger from 25 us on, and
+// from 36 us on tiles that waves share move less per multiply-add (39060 pixels, 112 x 1440: 28 -> 41).
 DwWave wave_choice(const WgradGeom &g, const Plan &pl)
 {
     const long long M = (long long)g.N * g.P * g.Q;
@@ -604,7 +606,7 @@ DwWave wave_choice(const WgradGeom &g, const Plan &pl)
     double us = 0;
     int ranges = 1;
     const int shape = wave_dw_best(g, pl.splits, &ranges, &us);
-    if (shape >= 0 && us < 36 && us < 0.93 * tile_us(g, pl)) {
+    if (shape >= 0 && us < 36 && us < (us < 25 ? 0.93 : 0.86) * tile_us(g, pl)) {
         w.shape = shape;
         w.ranges = wave_dw_ranges(M, ranges, &w.span);
     }
