@@ -94,6 +94,50 @@ __device__ __forceinline__ int outside(int hw, int d, int lim)
 }
 constexpr int FAR = (-16384) & 0xFFFF;  // a packed position that is outside whatever is added to it
 
+// Result (i, j) over the taps inside the gathered tensor and nothing else, in the order tap, channel or pixel; a sum that turns
+// NaN ends there.  (The matrix-core kernels multiply a deposited zero for a tap outside, and that is NaN where the other operand is
+// infinite or NaN: such a result is itself NaN, nothing else is wrong about it, and one lane sums it once more with this.)
+template <int OP, bool NCHW>
+__device__ float sum_inside(const F32Params &p, const F32Class &cls, int i, int j, int k_lo, int k_hi)
+{
+    const ConvShape &s = p.s;
+    const int RS = s.R * s.S, PQ = s.P * s.Q;
+    const int Ci = OP == OP_BWD ? s.K : s.C, Hi = OP == OP_BWD ? s.P : s.H, Wi = OP == OP_BWD ? s.Q : s.W, plane = Hi * Wi;
+    float acc = 0.f;
+    if constexpr (OP == OP_WGRAD) {
+        const int hi = NCHW ? p.by_rs.div(j) : p.by_c.div(j), lo = j - hi * (NCHW ? RS : s.C);
+        const int tap = NCHW ? lo : hi, c = NCHW ? hi : lo, r = p.by_s.div(tap), t = tap - r * s.S;
+        for (int m = k_lo; m < k_hi && acc == acc;) {
+            const int end = min(m + 64, k_hi);
+#pragma unroll 4
+            for (; m < end; ++m) {
+                const int row = p.by_q.div(m), n = p.by_p.div(row), q = m - row * s.Q;
+                const int h = (row - n * s.P) * s.stride - s.pad + r, w = q * s.stride - s.pad + t;
+                const bool in = (unsigned)h < (unsigned)s.H && (unsigned)w < (unsigned)s.W;
+                const float dy = p.a[NCHW ? (n * s.K + i) * PQ + m - n * PQ : m * s.K + i];
+                const float x = p.b[!in ? 0 : NCHW ? (n * s.C + c) * plane + h * s.W + w : ((n * s.H + h) * s.W + w) * s.C + c];
+                if (in) acc = fmaf(dy, x, acc);
+            }
+        }
+    } else {
+        const int t2 = cls.mw.div(i), b = i - t2 * cls.Mw, n = cls.mh.div(t2), a = t2 - n * cls.Mh;
+        const int mul = OP == OP_FWD ? s.stride : 1, sgn = OP == OP_FWD ? 1 : -1;
+        for (int tr = 0; tr < cls.TR; ++tr)
+            for (int ts = 0; ts < cls.TS; ++ts) {
+                const int h = a * mul + cls.off_h + sgn * tr, w = b * mul + cls.off_w + sgn * ts;
+                if ((unsigned)h >= (unsigned)Hi || (unsigned)w >= (unsigned)Wi) continue;
+                const int rs = OP == OP_FWD ? tr * s.S + ts : (cls.ph + s.stride * tr) * s.S + cls.pw + s.stride * ts;
+                const float *x = p.a + (NCHW ? n * Ci * plane + h * Wi + w : ((n * Hi + h) * Wi + w) * Ci);
+                const float *f = p.b + (OP == OP_FWD ? (NCHW ? j * Ci * RS + rs : (j * RS + rs) * Ci) : NCHW ? j * RS + rs : rs * s.C + j);
+                const int xs = NCHW ? plane : 1, fs = OP == OP_BWD ? s.C * RS : NCHW ? RS : 1;
+#pragma unroll 4
+                for (int c = 0; c < Ci; ++c) acc = fmaf(x[c * xs], f[c * fs], acc);
+                if (acc != acc) return acc;
+            }
+    }
+    return acc;
+}
+
 // OP, layout; VA / VB: floats per lane and transfer of the two operands (4 only for KC operands); the workgroup has Z
 // groups of WR x WC waves, a wave MI x NI blocks of 32x32.
 template <int OP, bool NCHW, int VA, int VB, int WR, int WC, int MI, int NI, int Z, int NS>
@@ -512,49 +556,11 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
         row = m0 + (wv / WC) * (32 * MI) + 32 * bi + (SWAP ? al : reg);
         col = n0 + (wv % WC) * (32 * NI) + 32 * bj + (SWAP ? reg : al);
     };
-    // A tap outside the tensor is left out of the sum, but here it is a product with a deposited zero, and that is NaN where the
-    // other operand is infinite or NaN.  Such a result is itself NaN and nothing else is wrong about it: it is noted (bit
-    // `at`; one comparison a result) and summed once more over the taps inside, by one lane, in the order tap, channel or
-    // pixel.  A sum that turns NaN again ends there.
+    // A result that is NaN is noted (bit `at`; one comparison a result) and summed once more: see sum_inside.
     unsigned long long noted = 0;
     auto finish = [&](int at, long long ro, int j, float v) __attribute__((always_inline)) {
         if (v != v) noted |= 1ull << at;
         put(ro, j, v);
-    };
-    auto sum_inside = [&](int i, int j) __attribute__((always_inline)) -> float {
-        float acc = 0.f;
-        if constexpr (OP == OP_WGRAD) {
-            const int hi = NCHW ? p.by_rs.div(j) : p.by_c.div(j), lo = j - hi * (NCHW ? RS : s.C);
-            const int tap = NCHW ? lo : hi, c = NCHW ? hi : lo, r = p.by_s.div(tap), t = tap - r * s.S;
-            for (int m = k_lo; m < k_hi && acc == acc;) {
-                const int end = min(m + 64, k_hi);
-#pragma unroll 4
-                for (; m < end; ++m) {
-                    const int row = p.by_q.div(m), n = p.by_p.div(row), q = m - row * s.Q;
-                    const int h = (row - n * s.P) * s.stride - s.pad + r, w = q * s.stride - s.pad + t;
-                    const bool in = (unsigned)h < (unsigned)s.H && (unsigned)w < (unsigned)s.W;
-                    const float dy = p.a[NCHW ? (n * s.K + i) * PQ + m - n * PQ : m * s.K + i];
-                    const float x = p.b[!in ? 0 : NCHW ? (n * s.C + c) * plane + h * s.W + w : ((n * s.H + h) * s.W + w) * s.C + c];
-                    if (in) acc = fmaf(dy, x, acc);
-                }
-            }
-        } else {
-            const int t2 = cls.mw.div(i), b = i - t2 * Mw, n = cls.mh.div(t2), a = t2 - n * Mh;
-            const int mul = OP == OP_FWD ? s.stride : 1, sgn = OP == OP_FWD ? 1 : -1;
-            for (int tr = 0; tr < cls.TR; ++tr)
-                for (int ts = 0; ts < TS; ++ts) {
-                    const int h = a * mul + cls.off_h + sgn * tr, w = b * mul + cls.off_w + sgn * ts;
-                    if ((unsigned)h >= (unsigned)Hi || (unsigned)w >= (unsigned)Wi) continue;
-                    const int rs = OP == OP_FWD ? tr * s.S + ts : (ph + s.stride * tr) * s.S + pw + s.stride * ts;
-                    const float *x = p.a + (NCHW ? n * Ci * plane + h * Wi + w : ((n * Hi + h) * Wi + w) * Ci);
-                    const float *f = p.b + (OP == OP_FWD ? (NCHW ? j * Ci * RS + rs : (j * RS + rs) * Ci) : NCHW ? j * RS + rs : rs * s.C + j);
-                    const int xs = NCHW ? plane : 1, fs = OP == OP_BWD ? s.C * RS : NCHW ? RS : 1;
-#pragma unroll 4
-                    for (int c = 0; c < Ci; ++c) acc = fmaf(x[c * xs], f[c * fs], acc);
-                    if (acc != acc) return acc;
-                }
-        }
-        return acc;
     };
     // accumulator element e of a block: index along the registers 8*(e/4) + 4*half + e%4, along the lanes lane%32
     if constexpr (Z == 1) {
@@ -601,8 +607,439 @@ __global__ __launch_bounds__(64 * WR * WC * Z, MI * NI == 4 ? 2 : 1) void f32_co
             int row, col;
             place(__ffsll(noted) - 1, row, col);
             noted &= noted - 1;
-            if (row < rows && col < cols) put(row_off(row), col, sum_inside(row, col));
+            if (row < rows && col < cols) put(row_off(row), col, sum_inside<OP, NCHW>(p, cls, row, col, k_lo, k_hi));
         }
+}
+
+// ---- NHWC, whole 16-byte chunks of channels: waves that share a tile's reduction ------------------------------------------------
+// The fp32 counterparts of wave.hip and wave_dw.hip (see there for the scheme): a wave reduces its whole tile over every KG-th
+// step of 16 elements through a ring of its own, no barrier before the KG partial tiles meet in LDS.  v_mfma_f32_16x16x4_f32 with
+// the operand first whose index is contiguous in the result: lane 16*g + i holds columns 4*g .. 4*g + 3 of row i, 16 bytes of it.
+// A block of 16 rows x 16 reduction elements is one direct global->LDS load of 16 bytes per lane and one ds_read_b128, whose
+// four elements serve four MFMAs.  Operands that lie the other way round (the KRSC filter in backward-data, both in
+// backward-weight) land as 16 reduction rows of 16*B floats and are fetched with ds_read_b32.
+//
+// What bounds it: 1024 multiply-adds per 32 clocks of a SIMD, and beside them (fp32 MFMAs never overlap vector instructions) the
+// address arithmetic, which here is per 16-byte chunk and not per element: 64 MFMAs to some 90 vector instructions in the 64x64
+// tiles, where the kernel above has 8 to 57.  Measured (us, kernel above -> here; forward, dx, dw): 512 pixels 16->32
+// 3x3 4.7 -> 3.8, 7.1 -> 5.1, 9.6 -> 5.9; 4096 pixels 64->96 3x3 11.6 -> 9.0, 10.9 -> 9.8, 21.0 -> 12.0; 392 pixels 448->112 3x3
+// 23.0 -> 15.1, 12.0 -> 10.6, 18.4 -> 9.2.  Which layers these get: wave_rows, wave_wgrad.
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Tile of 16 reduction rows x 16*B floats: row r lies at row_at(r), its 16-byte chunks exchanged by chunk_swz(r), so that the four
+// rows that one fetch touches (4*g + s, g = 0..3) fall on different banks.
+template <int B> __device__ __forceinline__ int row_at(int r) { return B == 2 ? r ^ ((r >> 3) & 1) : r; }
+template <int B> __device__ __forceinline__ int chunk_swz(int r) { return ((r >> 2) & (B - 1)) << 2; }
+
+// the ring of a wave: `turns` steps through NS slots of L loads each
+template <int L, int NS, class I, class S> __device__ __forceinline__ void run_ring(float *ring, int slot_floats, int turns, I &&issue, S &&step)
+{
+    const int ahead = min(turns, NS);
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+        if (q < ahead) issue(ring + q * slot_floats);
+    int slot = 0;
+    for (int t = turns; t > NS; --t) {
+        wait_vmcnt<L * (NS - 1)>();
+        step(ring + slot * slot_floats, true);
+        slot = slot + 1 == NS ? 0 : slot + 1;
+    }
+#pragma unroll
+    for (int q = NS; q > 0; --q)
+        if (q <= ahead) {
+            if (q == 4) wait_vmcnt<L * 3>();
+            else if (q == 3) wait_vmcnt<L * 2>();
+            else if (q == 2) wait_vmcnt<L>();
+            else wait_vmcnt<0>();
+            step(ring + slot * slot_floats, false);
+            slot = slot + 1 == NS ? 0 : slot + 1;
+        }
+}
+
+// MB x NB blocks of 16 pixels x 16 columns; KG waves share a tile's reduction, MG stand side by side along the pixels.
+// TAP: a step lies in one tap (channels % 16 == 0), whose arithmetic is scalar.
+template <int OP, int MB, int NB, int KG, int MG, int NS, bool TAP>
+__global__ __launch_bounds__(64 * KG * MG) void f32_wave_kernel(const F32Params p)
+{
+    constexpr int BM = 16 * MB * MG, BN = 16 * NB, BLK = 256, SLOT = (MB + NB) * BLK, RING = NS * SLOT, L = MB + NB;
+    static_assert(L * (NS - 1) < 64 && (KG == 1 || MB * NB * 256 <= RING), "vmcnt range; a wave's partial tile must fit its ring");
+    static_assert(MB <= KG || MB % KG == 0, "wave kg finishes pixel blocks kg, kg + KG, ...");
+    static_assert(OP == OP_FWD || NB == 2 || NB == 4, "rows of a transposed filter tile");
+    __shared__ __attribute__((aligned(1024))) float ring[KG * MG * RING];
+
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int kg = wave % KG, mg = wave / KG;
+    const int per_xcd = (p.units + 7) / 8;
+    const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (unit >= p.units) return;
+    int mt = p.by_ntiles.div(unit), ci = 0;
+    const int n0 = (unit - mt * p.n_tiles) * BN;
+    const ConvShape &s = p.s;
+    if constexpr (OP == OP_BWD) {
+        while (ci + 1 < p.n_cls && mt >= p.cls[ci + 1].tile0) ++ci;
+        mt -= p.cls[ci].tile0;
+    }
+    const F32Class &cls = p.cls[ci];
+    const int m0 = mt * BM + mg * 16 * MB;
+    const int Ci = OP == OP_BWD ? s.K : s.C, Hi = OP == OP_BWD ? s.P : s.H, Wi = OP == OP_BWD ? s.Q : s.W, RS = s.R * s.S;
+    const int TS = cls.TS, T = cls.TR * TS, Kd = T * Ci;
+    const int rows = OP == OP_FWD ? p.M : s.N * cls.Mh * cls.Mw, cols = OP == OP_FWD ? s.K : s.C;
+    const int turns = (Kd + 16 * KG - 1) / (16 * KG);
+    const int px4 = Ci * 4, row4 = Wi * px4, lim_hw = pack_hw(Hi - 1, Wi - 1), ts_magic = cls.ts_magic;
+    const buf_rsrc_t rs_a = make_buf_rsrc(p.a, p.a_bytes), rs_b = make_buf_rsrc(p.b, p.b_bytes);
+
+    // ---- what this lane loads: row l/4 of every block, chunk (l%4) ^ (l/16) of its step
+    const int ld_row = lane >> 2, chunk = ((lane & 3) ^ (lane >> 4)) * 4;
+    int a_off[MB], a_hw[MB];
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+        const int m = m0 + 16 * b + ld_row, t = cls.mw.div(m), col = m - t * cls.Mw, n = cls.mh.div(t), row = t - n * cls.Mh;
+        const int mul = OP == OP_FWD ? s.stride : 1, h = row * mul + cls.off_h, w = col * mul + cls.off_w;
+        a_off[b] = (n * Hi + h) * row4 + w * px4;
+        a_hw[b] = m < rows ? pack_hw(h, w) : FAR;
+    }
+    const int in_kd = TAP ? 0 : chunk, in_off = chunk - in_kd;
+    int kd = kg * 16 + in_kd, tap = p.by_ci.div(kd), c = kd - tap * Ci, first = kg * 16;     // first: the step's
+    const int adv_t = p.by_ci.div(16 * KG), adv_c = 16 * KG - adv_t * Ci;
+    constexpr int BCH = 4 * NB, BROWS = 64 / BCH;
+    unsigned f_off[NB];
+    int f_row[NB];                       // backward: the reduction row of load j
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        if constexpr (OP == OP_BWD) {
+            const int at = BROWS * j + lane / BCH, r = row_at<NB>(at), col = n0 + ((lane % BCH) ^ chunk_swz<NB>(r)) * 4;
+            f_row[j] = r;
+            f_off[j] = col < cols ? (unsigned)col * 4u : OOB;
+        } else {
+            const int co = n0 + 16 * j + ld_row;
+            f_row[j] = 0;
+            f_off[j] = co < cols ? ((unsigned)co * (unsigned)Kd + (unsigned)in_off) * 4u : OOB;
+        }
+    }
+    auto filter_tap = [&](int t) __attribute__((always_inline)) {
+        const int j = small_div(t, ts_magic), q = t - j * TS;
+        return (cls.ph + s.stride * j) * s.S + cls.pw + s.stride * q;
+    };
+    auto issue = [&](float *dst) __attribute__((always_inline)) {
+        const bool k_ok = kd < Kd;
+        const int j = small_div(tap, ts_magic), q = tap - j * TS;
+        const int dh = OP == OP_BWD ? -j : j, dw = OP == OP_BWD ? -q : q;
+        const int t_hw = k_ok ? pack_hw(dh, dw) : FAR, base = dh * row4 + dw * px4 + (c + in_off) * 4;
+#pragma unroll
+        for (int b = 0; b < MB; ++b) lds_dma16(rs_a, outside(a_hw[b], t_hw, lim_hw) == 0 ? (unsigned)(a_off[b] + base) : OOB, dst + b * BLK);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            unsigned off;
+            if constexpr (OP == OP_BWD) {
+                const int at = first + f_row[b];
+                int t = tap, k = c + f_row[b];
+                if constexpr (!TAP) { t = p.by_ci.div(at); k = at - t * Ci; }
+                off = at < Kd && f_off[b] != OOB ? f_off[b] + (unsigned)((k * RS + filter_tap(t)) * s.C) * 4u : OOB;
+            } else off = k_ok && f_off[b] != OOB ? f_off[b] + (unsigned)kd * 4u : OOB;
+            lds_dma16(rs_b, off, dst + (MB + b) * BLK);
+        }
+        kd += KG * 16; first += KG * 16;
+        c += adv_c;
+        const int carry = c >= Ci ? 1 : 0;
+        c -= carry ? Ci : 0;
+        tap += adv_t + carry;
+    };
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int frag = i * 16 + ((g ^ (i >> 2)) & 3) * 4;
+    auto step = [&](float *src, bool refill) __attribute__((always_inline)) {
+        f32x4 fa[MB], fw[NB];
+#pragma unroll
+        for (int b = 0; b < MB; ++b) fa[b] = *reinterpret_cast<const f32x4 *>(src + b * BLK + frag);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            if constexpr (OP == OP_BWD) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) fw[j][e] = src[MB * BLK + row_at<NB>(4 * g + e) * BN + ((16 * j) ^ (chunk_swz<NB>(4 * g) * 4)) + i];
+            } else fw[j] = *reinterpret_cast<const f32x4 *>(src + (MB + j) * BLK + frag);
+        }
+        wait_lgkmcnt0();
+        pin();
+        if (refill) issue(src);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][e], fa[b][e], acc[b][j], 0, 0, 0);
+        pin();
+    };
+    run_ring<L, NS>(ring + wave * RING, SLOT, turns, issue, step);
+
+    // ---- results: columns n0 + 16*j + 4*g .. + 3 of pixel m0 + 16*b + i
+    const bool whole = (cols & 3) == 0;
+    auto store = [&](int b, const f32x4 (&v)[NB]) __attribute__((always_inline)) {
+        const int m = m0 + 16 * b + i;
+        if (m >= rows) return;
+        long long pix = m;
+        if (OP == OP_BWD && s.stride != 1) {
+            const int t = cls.mw.div(m), col = m - t * cls.Mw, n = cls.mh.div(t), row = t - n * cls.Mh;
+            pix = ((long long)n * s.H + cls.h_first + s.stride * row) * s.W + cls.v_first + s.stride * col;
+        }
+        float *out = p.out + pix * cols;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int col = n0 + 16 * j + 4 * g;
+            if (col >= cols) continue;
+            f32x4 r = v[j];
+            const bool nan = r.x != r.x || r.y != r.y || r.z != r.z || r.w != r.w;
+            if (p.outside && nan)
+#pragma unroll 1
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < cols) {
+                        const float x = e == 0 ? r.x : e == 1 ? r.y : e == 2 ? r.z : r.w;
+                        const float y = x != x ? sum_inside<OP, false>(p, cls, m, col + e, 0, 0) : x;
+                        if (e == 0) r.x = y; else if (e == 1) r.y = y; else if (e == 2) r.z = y; else r.w = y;
+                    }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (OP == OP_FWD && p.bias != nullptr && col + e < cols) r[e] += p.bias[col + e];
+                if (OP == OP_FWD && p.relu) r[e] = fmaxf(r[e], 0.f);
+                if (OP == OP_BWD && p.mask != nullptr && col + e < cols && !(p.mask[pix * cols + col + e] > 0.f)) r[e] = 0.f;
+            }
+            if (whole) *reinterpret_cast<f32x4 *>(out + col) = r;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < cols) out[col + e] = r[e];
+        }
+    };
+    if constexpr (KG == 1) {
+#pragma unroll
+        for (int b = 0; b < MB; ++b) store(b, acc[b]);
+    } else {
+        f32x4 *part = reinterpret_cast<f32x4 *>(ring);
+        constexpr int PITCH = RING / 4;
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) part[wave * PITCH + (b * NB + j) * 64 + lane] = acc[b][j];
+        __syncthreads();
+        if (kg >= MB) return;
+#pragma unroll
+        for (int b0 = 0; b0 < MB; b0 += KG) {
+            const int b = b0 + kg;
+            f32x4 v[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) v[j] = part[mg * KG * PITCH + (b * NB + j) * 64 + lane];
+#pragma unroll
+            for (int z = 1; z < KG; ++z)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) v[j] += part[(mg * KG + z) * PITCH + (b * NB + j) * 64 + lane];
+            store(b, v);
+        }
+    }
+}
+
+// dw[k][col] over one pixel range per unit, MB x NB blocks of 16 filters x 16 columns, KG waves.  LINEAR: a 1x1 filter at stride 1
+// without padding.
+template <int MB, int NB, int KG, int NS, bool LINEAR>
+__global__ __launch_bounds__(64 * KG) void f32_wave_dw_kernel(const F32Params p)
+{
+    constexpr int BLK = 256, SLOT = (MB + NB) * BLK, RING = NS * SLOT, L = MB + NB;
+    static_assert((MB == 2 || MB == 4) && (NB == 2 || NB == 4) && L * (NS - 1) < 64 && MB * NB * 256 <= RING, "config");
+    __shared__ __attribute__((aligned(1024))) float ring[KG * RING];
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int per_xcd = (p.units + 7) / 8;
+    const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (unit >= p.units) return;
+    const ConvShape &s = p.s;
+    const int z = p.by_tiles.div(unit), tile = unit - z * p.tiles, kt = p.by_ntiles.div(tile);
+    const int k0 = kt * 16 * MB, n0 = (tile - kt * p.n_tiles) * 16 * NB, cols = s.C * s.R * s.S;
+    const int m_lo = z * p.span, m_end = min(m_lo + p.span, p.M);
+    const int turns = (m_end - m_lo + 16 * KG - 1) / (16 * KG);
+    const int px4 = s.C * 4, row4 = s.W * px4, img4 = s.H * row4, lim_hw = pack_hw(s.H - 1, s.W - 1);
+    const buf_rsrc_t rs_a = make_buf_rsrc(p.a, p.a_bytes), rs_b = make_buf_rsrc(p.b, p.b_bytes);
+
+    constexpr int ACH = 4 * MB, AROWS = 64 / ACH, BCH = 4 * NB, BROWS = 64 / BCH;
+    const int m_first = m_lo + wave * 16;
+    int a_m[MB], b_m[NB];                // pixel of load j
+    unsigned a_off[MB];
+    int b_off[NB], b_q[NB], b_p[NB], b_tap[NB];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+        const int r = row_at<MB>(AROWS * j + lane / ACH), k = k0 + ((lane % ACH) ^ chunk_swz<MB>(r)) * 4;
+        a_m[j] = m_first + r;
+        a_off[j] = k < s.K ? ((unsigned)a_m[j] * (unsigned)s.K + (unsigned)k) * 4u : OOB;
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int r = row_at<NB>(BROWS * j + lane / BCH), col = n0 + ((lane % BCH) ^ chunk_swz<NB>(r)) * 4, m = m_first + r;
+        b_m[j] = m;
+        if constexpr (LINEAR) {
+            b_off[j] = col < cols ? m * px4 + col * 4 : (int)OOB;
+        } else {
+            const int tap = p.by_c.div(col), fr = p.by_s.div(tap), fs = tap - fr * s.S, t = p.by_q.div(m), n = p.by_p.div(t);
+            b_q[j] = m - t * s.Q; b_p[j] = t - n * s.P;
+            b_off[j] = n * img4 + (b_p[j] * s.stride + fr - s.pad) * row4 + (b_q[j] * s.stride + fs - s.pad) * px4 + (col - tap * s.C) * 4;
+            b_tap[j] = col < cols ? pack_hw(fr - s.pad, fs - s.pad) : FAR;
+        }
+    }
+    const unsigned a_adv = (unsigned)(KG * 16) * (unsigned)(s.K * 4);
+    const int adv_row = p.by_q.div(KG * 16), adv_q = KG * 16 - adv_row * s.Q, adv_n = p.by_p.div(adv_row), adv_p = adv_row - adv_n * s.P;
+    const int sp = s.stride * px4, sr = s.stride * row4;
+    auto issue = [&](float *dst) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            lds_dma16(rs_a, a_m[j] < m_end && a_off[j] < OOB ? a_off[j] : OOB, dst + j * BLK);
+            a_off[j] += a_off[j] < OOB ? a_adv : 0u;
+            a_m[j] += KG * 16;
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const bool in = b_m[j] < m_end;
+            b_m[j] += KG * 16;
+            if constexpr (LINEAR) {
+                lds_dma16(rs_b, in ? (unsigned)b_off[j] : OOB, dst + (MB + j) * BLK);
+                b_off[j] += (unsigned)b_off[j] < OOB ? KG * 16 * px4 : 0;
+            } else {
+                const bool ok = in && outside(pack_hw(b_p[j] * s.stride, b_q[j] * s.stride), b_tap[j], lim_hw) == 0;
+                lds_dma16(rs_b, ok ? (unsigned)b_off[j] : OOB, dst + (MB + j) * BLK);
+                int off = b_off[j] + adv_n * img4 + adv_p * sr + adv_q * sp, q = b_q[j] + adv_q;
+                const bool cq = q >= s.Q;
+                q -= cq ? s.Q : 0;
+                off += cq ? sr - s.Q * sp : 0;
+                int pr = b_p[j] + adv_p + (cq ? 1 : 0);
+                const bool cp = pr >= s.P;
+                pr -= cp ? s.P : 0;
+                off += cp ? img4 - s.P * sr : 0;
+                b_q[j] = q; b_p[j] = pr; b_off[j] = off;
+            }
+        }
+    };
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto step = [&](float *src, bool refill) __attribute__((always_inline)) {
+        float fa[MB][4], fb[NB][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int b = 0; b < MB; ++b) fa[b][e] = src[row_at<MB>(4 * g + e) * (16 * MB) + ((16 * b) ^ (chunk_swz<MB>(4 * g) * 4)) + i];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) fb[j][e] = src[MB * BLK + row_at<NB>(4 * g + e) * (16 * NB) + ((16 * j) ^ (chunk_swz<NB>(4 * g) * 4)) + i];
+        }
+        wait_lgkmcnt0();
+        pin();
+        if (refill) issue(src);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[b][e], acc[b][j], 0, 0, 0);
+        pin();
+    };
+    run_ring<L, NS>(ring + wave * RING, SLOT, turns, issue, step);
+
+    f32x4 *part = reinterpret_cast<f32x4 *>(ring);
+    constexpr int PITCH = RING / 4;
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) part[wave * PITCH + (b * NB + j) * 64 + lane] = acc[b][j];
+    __syncthreads();
+    float *out = p.out + (size_t)z * ((size_t)s.K * cols);
+    for (int blk = wave; blk < MB * NB; blk += KG) {
+        f32x4 v = part[blk * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < KG; ++w) v += part[w * PITCH + blk * 64 + lane];
+        const int k = k0 + blk / NB * 16 + i, col = n0 + blk % NB * 16 + 4 * g;
+        if (k >= s.K || col >= cols) continue;
+        const bool nan = v.x != v.x || v.y != v.y || v.z != v.z || v.w != v.w;
+        if (p.outside && nan)
+#pragma unroll 1
+            for (int e = 0; e < 4; ++e) {
+                const float x = e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
+                const float y = x != x ? sum_inside<OP_WGRAD, false>(p, p.cls[0], k, col + e, m_lo, m_end) : x;
+                if (e == 0) v.x = y; else if (e == 1) v.y = y; else if (e == 2) v.z = y; else v.w = y;
+            }
+        *reinterpret_cast<f32x4 *>(out + (size_t)k * cols + col) = v;
+    }
+}
+
+// The shapes and the time models that pick one (us, fitted to 260 layers of 0.001 to 25 GFLOP on the device, 3-10% off):
+// {fixed, mfma, turn, round, mb, area}: fixed + mfma * (hundred 16x16x16 products of the CU with most tiles) + turn * (rounds of
+// workgroups that fit a CU, times steps per wave) + round * rounds + mb * (MB written, and of the mask read) + area * (ten blocks of
+// that CU); backward-weight's {fixed, mfma, turn, round, mb, ranges, part}: with several pixel ranges + ranges + part * (MB of partial tensors).
+struct F32Wave { int mb, nb, kg, mg, ns; const char *name; float us[2][6]; };     // us: forward, backward-data
+#define F32_WAVES(X) \
+    X(0, 1, 2, 8, 1, 4, "f32_wave_16x32_split8", {{1.78f, 0.f, 0.387f, 1.43f, 0.740f, 0.f}, {2.69f, 0.f, 0.546f, 1.48f, 0.613f, 0.f}}) \
+    X(1, 2, 2, 8, 1, 4, "f32_wave_32x32_split8", {{1.72f, 0.f, 0.642f, 1.67f, 0.473f, 0.f}, {2.38f, 0.f, 0.790f, 2.19f, 0.231f, 0.f}}) \
+    X(2, 4, 2, 8, 1, 3, "f32_wave_64x32_split8", {{1.52f, 0.f, 1.14f, 2.22f, 0.299f, 0.f}, {2.36f, 0.f, 1.28f, 2.52f, 0.177f, 0.f}}) \
+    X(3, 4, 4, 8, 1, 2, "f32_wave_64x64_split8", {{1.82f, 1.60f, 0.f, 0.f, 0.501f, 1.49f}, {1.93f, 1.77f, 0.f, 0.f, 0.343f, 2.01f}}) \
+    X(4, 2, 2, 4, 2, 3, "f32_wave_64x32_split4", {{1.83f, 0.f, 0.631f, 1.61f, 0.362f, 0.f}, {2.43f, 0.f, 0.787f, 1.97f, 0.173f, 0.f}}) \
+    X(5, 2, 2, 2, 4, 2, "f32_wave_128x32_split2", {{2.96f, 1.56f, 0.148f, 0.f, 0.222f, 0.327f}, {3.83f, 1.42f, 0.322f, 0.f, 0.161f, 0.700f}}) \
+    X(6, 2, 2, 1, 4, 2, "f32_wave_128x32", {{3.87f, 1.59f, 0.223f, 0.f, 0.239f, 0.038f}, {3.99f, 1.43f, 0.310f, 0.f, 0.084f, 0.926f}})
+#define X(I, MB, NB, KG, MG, NS, NAME, ...) {MB, NB, KG, MG, NS, NAME, __VA_ARGS__},
+const F32Wave kWaves[] = {F32_WAVES(X)};
+#undef X
+constexpr int N_WAVES = sizeof(kWaves) / sizeof(kWaves[0]);
+
+struct F32WaveDw { int mb, nb, kg, ns; const char *name; float us[7]; };
+#define F32_DW_WAVES(X) \
+    X(0, 2, 2, 8, 4, "f32_wave_dw_32x32_w8", {1.52f, 0.f, 0.720f, 1.40f, 0.475f, 3.94f, 0.f}) \
+    X(1, 4, 2, 8, 3, "f32_wave_dw_64x32_w8", {1.69f, 0.f, 1.34f, 1.25f, 0.398f, 3.43f, 0.431f}) \
+    X(2, 4, 4, 8, 2, "f32_wave_dw_64x64_w8", {1.89f, 1.81f, 0.f, 1.52f, 0.454f, 2.97f, 0.677f})
+#define X(I, MB, NB, KG, NS, NAME, ...) {MB, NB, KG, NS, NAME, __VA_ARGS__},
+const F32WaveDw kDwWaves[] = {F32_DW_WAVES(X)};
+#undef X
+constexpr int N_DW_WAVES = sizeof(kDwWaves) / sizeof(kDwWaves[0]);
+
+template <int OP, int MB, int NB, int KG, int MG, int NS>
+void launch_wave(const F32Params &p, bool tap, hipStream_t st)
+{
+    const dim3 grid((unsigned)((p.units + 7) / 8 * 8)), block(64 * KG * MG);
+    if (tap) hipLaunchKernelGGL((f32_wave_kernel<OP, MB, NB, KG, MG, NS, true>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((f32_wave_kernel<OP, MB, NB, KG, MG, NS, false>), grid, block, 0, st, p);
+}
+template <int MB, int NB, int KG, int NS>
+void launch_wave_dw(const F32Params &p, bool linear, hipStream_t st)
+{
+    const dim3 grid((unsigned)((p.units + 7) / 8 * 8)), block(64 * KG);
+    if (linear) hipLaunchKernelGGL((f32_wave_dw_kernel<MB, NB, KG, NS, true>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((f32_wave_dw_kernel<MB, NB, KG, NS, false>), grid, block, 0, st, p);
+}
+
+int launch_wave_op(int op, int t, const F32Params &p, hipStream_t st)
+{
+    const bool tap = (op == OP_BWD ? p.s.K : p.s.C) % 16 == 0;
+    switch (t) {
+#define X(I, MB, NB, KG, MG, NS, ...) \
+    case I: \
+        if (op == OP_FWD) launch_wave<OP_FWD, MB, NB, KG, MG, NS>(p, tap, st); \
+        else launch_wave<OP_BWD, MB, NB, KG, MG, NS>(p, tap, st); \
+        break;
+    F32_WAVES(X)
+#undef X
+    default: return MXC_ERR_UNSUPPORTED;
+    }
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+}
+int launch_wave_dw_op(int t, const F32Params &p, hipStream_t st)
+{
+    const ConvShape &s = p.s;
+    const bool linear = s.R * s.S == 1 && s.stride == 1 && s.pad == 0;
+    switch (t) {
+#define X(I, MB, NB, KG, NS, ...) case I: launch_wave_dw<MB, NB, KG, NS>(p, linear, st); break;
+    F32_DW_WAVES(X)
+#undef X
+    default: return MXC_ERR_UNSUPPORTED;
+    }
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
 // ---- tile choice ------------------------------------------------------------------------------------------------
@@ -688,6 +1125,27 @@ double model_clocks(const F32Tile &t, long long tiles, long long k)
 
 struct F32Plan { int tile, splits, span; };
 
+// Time (us) of a tile beside the wave kernel's, fitted to the layers of its models, 2-6% off: {fixed, tile, first, work, mb} of
+// forward, backward-data and backward-weight, by the CU with most tiles: fixed + tile * tiles + first * (65536 multiply-adds of one
+// tile) + work * (of all) + mb * (MB written, and of the mask read; of all partial tensors), and 3 for the summing launch.  Zeros: a
+// tile that those layers did not get, which keeps what it has.
+const float kTileUs[N_TILES][3][5] = {
+    {{9.53f, 2.36f, 0.747f, 3.64f, 0.128f}, {5.35f, 0.f, 0.f, 3.61f, 0.435f}, {}},
+    {{6.53f, 0.886f, 1.91f, 3.71f, 0.192f}, {6.12f, 3.86f, 1.52f, 4.37f, 0.f}, {0.f, 8.10f, 0.f, 5.69f, 0.047f}},
+    {{3.45f, 0.708f, 0.987f, 4.02f, 0.245f}, {4.97f, 0.501f, 1.06f, 5.04f, 0.153f}, {2.02f, 1.79f, 1.91f, 5.24f, 0.628f}},
+    {{4.99f, 0.440f, 1.79f, 4.50f, 0.171f}, {5.29f, 1.27f, 3.79f, 4.71f, 0.082f}, {2.23f, 1.54f, 3.75f, 5.35f, 0.561f}},
+    {{}, {}, {3.62f, 0.817f, 4.20f, 6.48f, 0.596f}},
+    {{1.89f, 1.75f, 0.f, 5.00f, 0.466f}, {2.08f, 2.62f, 0.f, 7.40f, 0.181f}, {1.22f, 3.00f, 1.30f, 9.73f, 0.736f}},
+};
+double tile_us(int tile, int op, long long i, long long j, long long k, int splits, bool masked)
+{
+    const F32Tile &t = kTiles[tile];
+    const float *c = kTileUs[tile][op];
+    const double per_cu = (double)(((i + t.bm - 1) / t.bm * ((j + t.bn - 1) / t.bn) * splits + 255) / 256);
+    const double work = (double)((k + BK * t.z - 1) / (BK * t.z)) * t.z * t.bm * t.bn / 65536.0;
+    return c[0] + c[1] * per_cu + (c[2] + c[3] * per_cu) * work + c[4] * (masked ? 8e-6 : 4e-6) * i * j * splits + (splits > 1 ? 3.0 : 0.0);
+}
+
 F32Class residue_class(const ConvShape &s, int ph, int pw)
 {
     F32Class c{};
@@ -755,6 +1213,10 @@ F32Plan plan_wgrad(const ConvShape &s)
 
 }  // namespace
 
+const char *f32_wave_name(int index)
+{
+    return index < 0 ? nullptr : index < N_WAVES ? kWaves[index].name : index - N_WAVES < N_DW_WAVES ? kDwWaves[index - N_WAVES].name : nullptr;
+}
 const char *f32_tile_name(int index) { return index >= 0 && index < N_TILES ? kTiles[index].name : nullptr; }
 
 // The kernel addresses its operands with 31-bit byte offsets, packs positions into 16 bits and holds MAX_TAPS taps.
@@ -766,9 +1228,41 @@ bool f32_supported(const ConvShape &s)
            (long long)s.P * s.stride <= 8192 && (long long)s.Q * s.stride <= 8192;
 }
 
+// The wave kernel's shape for forward or backward-data, or -1: whole 16-byte chunks of channels in NHWC (of backward-data's
+// filter too), and less modelled time than tile `other`.  Chosen so, of those 260 layers forward runs 1.18 times as fast
+// (1.19 below 7 us, 1.09 above 40), backward-data 1.19; strided backward-data, whose classes differ in length, must gain more.
+int wave_rows(const ConvShape &s, int op, bool nchw, int other, bool masked)
+{
+    if (nchw || s.C % 4 != 0 || (op == OP_BWD && s.K % 4 != 0)) return -1;
+    if (const char *f = getenv("MXC_FORCE_VARIANT")) {
+        for (int i = 0; i < N_WAVES; ++i)
+            if (!strcmp(f, kWaves[i].name)) return i;
+        return -1;
+    }
+    const long long m = op == OP_FWD ? (long long)s.N * s.P * s.Q : (long long)s.N * s.H * s.W, cols = op == OP_FWD ? s.K : s.C;
+    const int taps = op == OP_FWD ? s.R * s.S : ((s.R + s.stride - 1) / s.stride) * ((s.S + s.stride - 1) / s.stride);
+    const long long k = (long long)taps * (op == OP_FWD ? s.C : s.K);
+    const double most = tile_us(other, op, m, cols, k, 1, masked) * (op == OP_BWD && s.stride > 1 ? 0.75 : 0.95);
+    double best = 0;
+    int shape = -1;
+    for (int i = 0; i < N_WAVES; ++i) {
+        const F32Wave &w = kWaves[i];
+        const float *c = w.us[op == OP_FWD ? 0 : 1];
+        const int nw = w.kg * w.mg, slots = 160 / (nw * w.ns * (w.mb + w.nb));
+        const long long per_cu = ((m + 16 * w.mb * w.mg - 1) / (16 * w.mb * w.mg) * ((cols + 16 * w.nb - 1) / (16 * w.nb)) + 255) / 256;
+        const double rounds = (double)((per_cu + slots - 1) / slots), turns = (double)((k + 16 * w.kg - 1) / (16 * w.kg));
+        const double t = c[0] + c[1] * per_cu * turns * nw * w.mb * w.nb * 0.01 + c[2] * rounds * turns + c[3] * rounds +
+                         c[4] * (masked ? 8e-6 : 4e-6) * m * cols + c[5] * per_cu * w.mb * w.nb * w.mg * 0.1;
+        if (shape < 0 || t < best) { best = t; shape = i; }
+    }
+    return best < most ? shape : -1;
+}
+
+// t: a tile of the general kernel, or -1 - (a shape of the wave kernel)
 static int run(int op, bool nchw, int t, F32Params &p, long long row_tiles, long long cols, int splits, hipStream_t st)
 {
-    const long long nt = (cols + kTiles[t].bn - 1) / kTiles[t].bn;
+    const int bn = t < 0 ? 16 * (op == OP_WGRAD ? kDwWaves[-1 - t].nb : kWaves[-1 - t].nb) : kTiles[t].bn;
+    const long long nt = (cols + bn - 1) / bn;
     if (row_tiles * nt * splits > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
     p.n_tiles = (int)nt;
     p.tiles = (int)(row_tiles * nt);
@@ -777,12 +1271,14 @@ static int run(int op, bool nchw, int t, F32Params &p, long long row_tiles, long
     p.by_ntiles = FastDiv(p.n_tiles); p.by_tiles = FastDiv(p.tiles);
     p.by_ci = FastDiv(op == OP_BWD ? s.K : s.C); p.by_c = FastDiv(s.C); p.by_rs = FastDiv(s.R * s.S); p.by_s = FastDiv(s.S);
     p.by_pq = FastDiv(s.P * s.Q); p.by_q = FastDiv(s.Q); p.by_p = FastDiv(s.P);
+    if (t < 0) return op == OP_WGRAD ? launch_wave_dw_op(-1 - t, p, st) : launch_wave_op(op, -1 - t, p, st);
     return launch_op(op, nchw, t, p, st);
 }
 
 int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y, hipStream_t st, const char **variant, const PostOp &post)
 {
-    const int t = plan_rows(s, OP_FWD).tile;
+    const int tile = plan_rows(s, OP_FWD).tile, wv = wave_rows(s, OP_FWD, nchw, tile, false), t = wv >= 0 ? -1 - wv : tile;
+    const int bm = wv >= 0 ? 16 * kWaves[wv].mb * kWaves[wv].mg : kTiles[t].bm;
     F32Params p{};
     p.a = (const float *)x; p.b = (const float *)w; p.out = (float *)y;
     p.a_bytes = (unsigned)((long long)s.N * s.C * s.H * s.W * 4);
@@ -794,13 +1290,14 @@ int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y
     F32Class &c = p.cls[0];
     c.TR = s.R; c.TS = s.S; c.Mh = s.P; c.Mw = s.Q; c.off_h = c.off_w = -s.pad;
     set_divisors(c);
-    *variant = kTiles[t].name;
-    return run(OP_FWD, nchw, t, p, (p.M + kTiles[t].bm - 1) / kTiles[t].bm, s.K, 1, st);
+    *variant = wv >= 0 ? kWaves[wv].name : kTiles[t].name;
+    return run(OP_FWD, nchw, t, p, ((long long)p.M + bm - 1) / bm, s.K, 1, st);
 }
 
 int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, void *dx, hipStream_t st, const char **variant, const PostOp &post)
 {
-    const int t = plan_rows(s, OP_BWD).tile;
+    const int tile = plan_rows(s, OP_BWD).tile, wv = wave_rows(s, OP_BWD, nchw, tile, post.mask != nullptr), t = wv >= 0 ? -1 - wv : tile;
+    const int bm = wv >= 0 ? 16 * kWaves[wv].mb * kWaves[wv].mg : kTiles[t].bm;
     F32Params p{};
     p.a = (const float *)dy; p.b = (const float *)w; p.out = (float *)dx;
     p.a_bytes = (unsigned)((long long)s.N * s.K * s.P * s.Q * 4);
@@ -815,18 +1312,61 @@ int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, v
         f = residue_class(s, c / s.stride, c % s.stride);
         set_divisors(f);
         f.tile0 = (int)tiles;
-        tiles += ((long long)s.N * f.Mh * f.Mw + kTiles[t].bm - 1) / kTiles[t].bm;
+        tiles += ((long long)s.N * f.Mh * f.Mw + bm - 1) / bm;
     }
-    *variant = kTiles[t].name;
+    *variant = wv >= 0 ? kWaves[wv].name : kTiles[t].name;
     return run(OP_BWD, nchw, t, p, tiles, s.C, 1, st);
+}
+
+// The wave kernel's shape (tile), pixel ranges and their length for backward-weight, or splits 0: the plan.  Never more ranges than
+// the plan has: the workspace is sized for those.  Of those 260 gradients 1.38 times as fast.
+static F32Plan wave_wgrad(const ConvShape &s, bool nchw, const F32Plan &pl)
+{
+    if (nchw || s.C % 4 != 0 || s.K % 4 != 0) return F32Plan{0, 0, 0};
+    const long long M = (long long)s.N * s.P * s.Q, cols = (long long)s.C * s.R * s.S;
+    auto ranges = [&](int shape, long long want) {
+        if (want > pl.splits) want = pl.splits;
+        if (want < 1) want = 1;
+        const long long span = ((M + want - 1) / want + 15) / 16 * 16;
+        return F32Plan{shape, (int)((M + span - 1) / span), (int)span};
+    };
+    if (const char *f = getenv("MXC_FORCE_WGRAD")) {
+        const char *slash = strchr(f, '/');
+        const size_t len = slash ? (size_t)(slash - f) : strlen(f);
+        for (int i = 0; i < N_DW_WAVES; ++i)
+            if (strlen(kDwWaves[i].name) == len && !strncmp(f, kDwWaves[i].name, len)) return ranges(i, slash ? atoi(slash + 1) : 1);
+        return F32Plan{0, 0, 0};
+    }
+    double best = 0.95 * tile_us(pl.tile, OP_WGRAD, s.K, cols, pl.span, pl.splits, false);
+    F32Plan chosen{0, 0, 0};
+    for (int i = 0; i < N_DW_WAVES; ++i) {
+        const F32WaveDw &w = kDwWaves[i];
+        const long long tiles = ((s.K + 16 * w.mb - 1) / (16 * w.mb)) * ((cols + 16 * w.nb - 1) / (16 * w.nb));
+        const int slots = 160 / (w.kg * w.ns * (w.mb + w.nb));
+        for (int fill = 64; fill <= 512; fill *= 2) {           // one range, then as many as give 128, 256 and 512 workgroups
+            const F32Plan p = ranges(i, fill == 64 ? 1 : fill / tiles);
+            const double per_cu = (double)((tiles * p.splits + 255) / 256), rounds = (double)(((long long)per_cu + slots - 1) / slots);
+            const double turns = (double)((p.span + 16 * w.kg - 1) / (16 * w.kg)), mb = 4e-6 * s.K * cols;
+            const double t = w.us[0] + w.us[1] * per_cu * turns * w.kg * w.mb * w.nb * 0.01 + w.us[2] * rounds * turns + w.us[3] * rounds + w.us[4] * mb +
+                             (p.splits > 1 ? w.us[5] + w.us[6] * p.splits * mb : 0.0);
+            if (t < best) { best = t; chosen = p; }
+        }
+    }
+    return chosen;
 }
 
 size_t f32_wgrad_workspace(const ConvShape &s) { return (size_t)plan_wgrad(s).splits * s.K * s.C * s.R * s.S * sizeof(float); }
 
 int f32_wgrad(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, float *partial, hipStream_t st, const char **variant)
 {
-    const F32Plan pl = plan_wgrad(s);
-    const F32Tile &tc = kTiles[pl.tile];
+    F32Plan pl = plan_wgrad(s);
+    const char *name = kTiles[pl.tile].name;
+    int bm = kTiles[pl.tile].bm;
+    if (const F32Plan wv = wave_wgrad(s, nchw, pl); wv.splits > 0) {
+        name = kDwWaves[wv.tile].name;
+        bm = 16 * kDwWaves[wv.tile].mb;
+        pl = F32Plan{-1 - wv.tile, wv.splits, wv.span};
+    }
     F32Params p{};
     p.a = (const float *)dy; p.b = (const float *)x; p.out = pl.splits > 1 ? partial : (float *)dw;
     p.a_bytes = (unsigned)((long long)s.N * s.K * s.P * s.Q * 4);
@@ -836,8 +1376,8 @@ int f32_wgrad(const ConvShape &s, bool nchw, const void *x, const void *dy, void
     p.span = pl.span;
     p.outside = s.pad > 0;
     const long long cols = (long long)s.C * s.R * s.S;
-    *variant = tc.name;
-    const int rc = run(OP_WGRAD, nchw, pl.tile, p, (s.K + tc.bm - 1) / tc.bm, cols, pl.splits, st);
+    *variant = name;
+    const int rc = run(OP_WGRAD, nchw, pl.tile, p, (s.K + bm - 1) / bm, cols, pl.splits, st);
     if (rc != MXC_OK || pl.splits == 1) return rc;
     return sum_splits(partial, dw, false, s.K * cols, pl.splits, st);
 }

@@ -311,6 +311,7 @@ int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, v
 size_t f32_wgrad_workspace(const ConvShape &s);       // bytes of fp32 partial tensors
 int f32_wgrad(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, float *partial, hipStream_t st, const char **variant);
 const char *f32_tile_name(int index);
+const char *f32_wave_name(int index);
 
 // ---- igemm.hip: bf16 MFMA implicit GEMM (NHWC/KRSC) ---------------------------
 bool igemm_fwd_supported(const ConvShape &s);
