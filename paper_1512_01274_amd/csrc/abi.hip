@@ -248,7 +248,7 @@ int fwd_nhwc(const ConvShape &s, int dtype, const void *x, const void *w, void *
     }
     if (dry || !run) return MXC_OK;
     if (f32_in_place(s, dtype)) {
-        const int rc = f32_fwd(s, false, x, w, y, st, &v, post);
+        const int rc = f32_fwd(s, false, -1, x, w, y, st, &v, post);
         set_variant("fwd", v);
         return rc;
     }
@@ -432,19 +432,29 @@ int bwd_weight_nhwc(const ConvShape &s_in, int dtype, const void *x, const void 
 }
 
 // ---- fp32, either layout: the matrix-core kernels of fp32.hip read the caller's tensors in place -----------------
-// For NCHW the scratch that the converting path would use is asked for all the same, and nothing uses it: the size query has
-// always answered more for NCHW than for NHWC (the host tests hold it to that), and callers' sizes stay what they were.
+// ... or NHWC copies of NCHW operands, where that is faster (f32_copies); the result goes to its planes by itself.  The scratch
+// for NCHW is the same either way and of the size that a converting path needs for every operand: the size query has always
+// answered so.  A prepared filter stays as it lies, so its copy takes the place of dx in the scratch and has to fit there.
 
 int run_f32(int pass, const ConvShape &s, int layout, const void *a, const void *b, void *out, const PostOp &post, Carver &fws,
             Carver &ws, hipStream_t st, bool dry, FilterMode mode)
 {
     const bool nchw = layout == MXC_NCHW;
+    const int RS = s.R * s.S;
     const size_t nx = (size_t)s.N * s.C * s.H * s.W * 4, nw = (size_t)s.K * s.C * s.R * s.S * 4, ny = (size_t)s.N * s.K * s.P * s.Q * 4;
     const char *v = "";
     if (pass == MXC_FWD) {
-        if (nchw) { ws.take(nx); ws.take(nw); ws.take(ny); }
+        void *x2 = nchw ? ws.take(nx) : nullptr, *w2 = nchw ? ws.take(nw) : nullptr;
+        if (nchw) ws.take(ny);
         if (dry) return MXC_OK;
-        const int rc = f32_fwd(s, nchw, a, b, out, st, &v, post);
+        const int copies = nchw ? f32_copies(s, false, false) : -1;
+        if (copies >= 0) {
+            const RelayJob jobs[] = {relay_to_nhwc(a, x2, s.N, s.C, s.H * s.W, s.C), relay_to_nhwc(b, w2, s.K, s.C, RS, s.C)};
+            MXC_TRY(relayout4(jobs, RS == 1 ? 1 : 2, st));
+            a = x2;
+            if (RS > 1) b = w2;
+        }
+        const int rc = f32_fwd(s, nchw, copies, a, b, out, st, &v, post);
         set_variant("fwd", v);
         return rc;
     }
@@ -452,15 +462,26 @@ int run_f32(int pass, const ConvShape &s, int layout, const void *a, const void 
         // the kernel reads the filter as it lies: its prepared form is a copy
         const bool run = mode != FILTER_PREPARE_ONLY;
         void *wc = (nchw || mode != FILTER_RAW) ? fws.take(nw) : nullptr;
+        void *dy2 = nullptr, *w2 = wc;
         if (nchw && run) {
-            ws.take(ny); ws.take(nx);
+            dy2 = ws.take(ny);
+            void *dx2 = ws.take(nx);
+            if (mode == FILTER_PREPARED) w2 = dx2;
             if (post.mask != nullptr || post.relu) ws.take(nx);
         }
         if (dry) return MXC_OK;
         if (!run) return launch_copy(b, wc, nw, st);
         PostOp post2 = post;
         post2.relu = 0;
-        const int rc = f32_bwd_data(s, nchw, a, mode == FILTER_PREPARED ? wc : b, out, st, &v, post2);
+        if (mode == FILTER_PREPARED) b = wc;
+        const int copies = nchw && (RS == 1 || nw <= nx) ? f32_copies(s, true, post2.mask != nullptr) : -1;
+        if (copies >= 0) {
+            const RelayJob jobs[] = {relay_to_nhwc(a, dy2, s.N, s.K, s.P * s.Q, s.K), relay_to_nhwc(b, w2, s.K, s.C, RS, s.C)};
+            MXC_TRY(relayout4(jobs, RS == 1 ? 1 : 2, st));
+            a = dy2;
+            if (RS > 1) b = w2;
+        }
+        const int rc = f32_bwd_data(s, nchw, copies, a, b, out, st, &v, post2);
         set_variant("bwd_data", v);
         return rc;
     }

@@ -658,8 +658,10 @@ template <int L, int NS, class I, class S> __device__ __forceinline__ void run_r
 }
 
 // MB x NB blocks of 16 pixels x 16 columns; KG waves share a tile's reduction, MG stand side by side along the pixels.
-// TAP: a step lies in one tap (channels % 16 == 0), whose arithmetic is scalar.
-template <int OP, int MB, int NB, int KG, int MG, int NS, bool TAP>
+// TAP: a step lies in one tap (channels % 16 == 0), whose arithmetic is scalar.  PLANES: the operands are NHWC copies of an NCHW
+// problem and the result goes straight to its planes: the product is formed the other way round, lane 16*g + i holds pixels
+// 4*g .. 4*g + 3 of column i.
+template <int OP, int MB, int NB, int KG, int MG, int NS, bool TAP, bool PLANES>
 __global__ __launch_bounds__(64 * KG * MG) void f32_wave_kernel(const F32Params p)
 {
     constexpr int BM = 16 * MB * MG, BN = 16 * NB, BLK = 256, SLOT = (MB + NB) * BLK, RING = NS * SLOT, L = MB + NB;
@@ -771,14 +773,59 @@ __global__ __launch_bounds__(64 * KG * MG) void f32_wave_kernel(const F32Params 
 #pragma unroll
             for (int b = 0; b < MB; ++b)
 #pragma unroll
-                for (int j = 0; j < NB; ++j) acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][e], fa[b][e], acc[b][j], 0, 0, 0);
+                for (int j = 0; j < NB; ++j) {
+                    if constexpr (PLANES) acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[b][e], fw[j][e], acc[b][j], 0, 0, 0);
+                    else acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[j][e], fa[b][e], acc[b][j], 0, 0, 0);
+                }
         pin();
     };
     run_ring<L, NS>(ring + wave * RING, SLOT, turns, issue, step);
 
     // ---- results: columns n0 + 16*j + 4*g .. + 3 of pixel m0 + 16*b + i
     const bool whole = (cols & 3) == 0;
+    auto store_planes = [&](int b, const f32x4 (&v)[NB]) __attribute__((always_inline)) {
+        const int m = m0 + 16 * b + 4 * g, plane = OP == OP_FWD ? s.P * s.Q : s.H * s.W;
+        if (m >= rows) return;
+        const bool unit = OP == OP_FWD || s.stride == 1, quad = unit && (plane & 3) == 0;      // four pixels of one image, 16 bytes
+        int img[4], at[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int t = cls.mw.div(m + e), n = cls.mh.div(t);
+            img[e] = n;
+            if (unit) at[e] = m + e - n * plane;
+            else at[e] = (cls.h_first + s.stride * (t - n * cls.Mh)) * s.W + cls.v_first + s.stride * (m + e - t * cls.Mw);
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int col = n0 + 16 * j + i;
+            if (col >= cols) continue;
+            f32x4 r = v[j];
+            const bool nan = r.x != r.x || r.y != r.y || r.z != r.z || r.w != r.w;
+            if (p.outside && nan)
+#pragma unroll 1
+                for (int e = 0; e < 4; ++e)
+                    if (m + e < rows) {
+                        const float x = e == 0 ? r.x : e == 1 ? r.y : e == 2 ? r.z : r.w;
+                        const float y = x != x ? sum_inside<OP, false>(p, cls, m + e, col, 0, 0) : x;
+                        if (e == 0) r.x = y; else if (e == 1) r.y = y; else if (e == 2) r.z = y; else r.w = y;
+                    }
+            if (OP == OP_FWD && p.bias != nullptr) r += p.bias[col];
+            long long off[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                off[e] = ((long long)img[e] * cols + col) * plane + at[e];
+                if (OP == OP_FWD && p.relu) r[e] = fmaxf(r[e], 0.f);
+                if (OP == OP_BWD && p.mask != nullptr && m + e < rows && !(p.mask[off[e]] > 0.f)) r[e] = 0.f;
+            }
+            if (quad) *reinterpret_cast<f32x4 *>(p.out + off[0]) = r;      // (rows are a multiple of plane)
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (m + e < rows) p.out[off[e]] = r[e];
+        }
+    };
     auto store = [&](int b, const f32x4 (&v)[NB]) __attribute__((always_inline)) {
+        if constexpr (PLANES) return store_planes(b, v);
         const int m = m0 + 16 * b + i;
         if (m >= rows) return;
         long long pix = m;
@@ -999,12 +1046,12 @@ const F32WaveDw kDwWaves[] = {F32_DW_WAVES(X)};
 #undef X
 constexpr int N_DW_WAVES = sizeof(kDwWaves) / sizeof(kDwWaves[0]);
 
-template <int OP, int MB, int NB, int KG, int MG, int NS>
+template <int OP, int MB, int NB, int KG, int MG, int NS, bool PLANES>
 void launch_wave(const F32Params &p, bool tap, hipStream_t st)
 {
     const dim3 grid((unsigned)((p.units + 7) / 8 * 8)), block(64 * KG * MG);
-    if (tap) hipLaunchKernelGGL((f32_wave_kernel<OP, MB, NB, KG, MG, NS, true>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((f32_wave_kernel<OP, MB, NB, KG, MG, NS, false>), grid, block, 0, st, p);
+    if (tap) hipLaunchKernelGGL((f32_wave_kernel<OP, MB, NB, KG, MG, NS, true, PLANES>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((f32_wave_kernel<OP, MB, NB, KG, MG, NS, false, PLANES>), grid, block, 0, st, p);
 }
 template <int MB, int NB, int KG, int NS>
 void launch_wave_dw(const F32Params &p, bool linear, hipStream_t st)
@@ -1014,14 +1061,14 @@ void launch_wave_dw(const F32Params &p, bool linear, hipStream_t st)
     else hipLaunchKernelGGL((f32_wave_dw_kernel<MB, NB, KG, NS, false>), grid, block, 0, st, p);
 }
 
-int launch_wave_op(int op, int t, const F32Params &p, hipStream_t st)
+int launch_wave_op(int op, bool planes, int t, const F32Params &p, hipStream_t st)
 {
     const bool tap = (op == OP_BWD ? p.s.K : p.s.C) % 16 == 0;
     switch (t) {
 #define X(I, MB, NB, KG, MG, NS, ...) \
     case I: \
-        if (op == OP_FWD) launch_wave<OP_FWD, MB, NB, KG, MG, NS>(p, tap, st); \
-        else launch_wave<OP_BWD, MB, NB, KG, MG, NS>(p, tap, st); \
+        if (op == OP_FWD) planes ? launch_wave<OP_FWD, MB, NB, KG, MG, NS, true>(p, tap, st) : launch_wave<OP_FWD, MB, NB, KG, MG, NS, false>(p, tap, st); \
+        else planes ? launch_wave<OP_BWD, MB, NB, KG, MG, NS, true>(p, tap, st) : launch_wave<OP_BWD, MB, NB, KG, MG, NS, false>(p, tap, st); \
         break;
     F32_WAVES(X)
 #undef X
@@ -1137,10 +1184,19 @@ const float kTileUs[N_TILES][3][5] = {
     {{}, {}, {3.62f, 0.817f, 4.20f, 6.48f, 0.596f}},
     {{1.89f, 1.75f, 0.f, 5.00f, 0.466f}, {2.08f, 2.62f, 0.f, 7.40f, 0.181f}, {1.22f, 3.00f, 1.30f, 9.73f, 0.736f}},
 };
-double tile_us(int tile, int op, long long i, long long j, long long k, int splits, bool masked)
+// The same for forward and backward-data of NCHW problems read in place (1218 passes of 440 layers; 2-5% off, dx 5-13%).
+const float kPlaneTileUs[N_TILES][2][5] = {
+    {{11.83f, 0.682f, 0.513f, 4.33f, 0.277f}, {6.07f, 0.f, 4.23f, 2.47f, 0.513f}},
+    {{8.07f, 1.13f, 1.66f, 5.17f, 0.142f}, {6.30f, 0.f, 3.25f, 4.71f, 0.327f}},
+    {{3.62f, 1.34f, 1.29f, 5.27f, 0.217f}, {4.19f, 1.90f, 1.93f, 5.55f, 0.224f}},
+    {{6.31f, 0.f, 3.74f, 6.58f, 0.263f}, {5.65f, 0.328f, 4.85f, 6.38f, 0.232f}},
+    {{}, {}},
+    {{1.63f, 2.97f, 0.239f, 9.21f, 0.438f}, {1.30f, 5.39f, 1.18f, 10.78f, 0.469f}},
+};
+double tile_us(int tile, int op, bool nchw, long long i, long long j, long long k, int splits, bool masked)
 {
     const F32Tile &t = kTiles[tile];
-    const float *c = kTileUs[tile][op];
+    const float *c = nchw ? kPlaneTileUs[tile][op] : kTileUs[tile][op];
     const double per_cu = (double)(((i + t.bm - 1) / t.bm * ((j + t.bn - 1) / t.bn) * splits + 255) / 256);
     const double work = (double)((k + BK * t.z - 1) / (BK * t.z)) * t.z * t.bm * t.bn / 65536.0;
     return c[0] + c[1] * per_cu + (c[2] + c[3] * per_cu) * work + c[4] * (masked ? 8e-6 : 4e-6) * i * j * splits + (splits > 1 ? 3.0 : 0.0);
@@ -1228,12 +1284,14 @@ bool f32_supported(const ConvShape &s)
            (long long)s.P * s.stride <= 8192 && (long long)s.Q * s.stride <= 8192;
 }
 
-// The wave kernel's shape for forward or backward-data, or -1: whole 16-byte chunks of channels in NHWC (of backward-data's
-// filter too), and less modelled time than tile `other`.  Chosen so, of those 260 layers forward runs 1.18 times as fast
+// The wave kernel's shape for forward or backward-data, or -1: whole 16-byte chunks of channels (of backward-data's filter too),
+// and less modelled time than tile `other`.  Chosen so, of those 260 NHWC layers forward runs 1.18 times as fast
 // (1.19 below 7 us, 1.09 above 40), backward-data 1.19; strided backward-data, whose classes differ in length, must gain more.
+// NCHW problems pay for the launch that copies their operands, the copies (3 TB/s) and, where planes are no whole groups of four
+// pixels, results that leave one by one: of 440 layers forward takes them in 190 and runs those 1.37 times as fast, dx 1.34 (strided included).
 int wave_rows(const ConvShape &s, int op, bool nchw, int other, bool masked)
 {
-    if (nchw || s.C % 4 != 0 || (op == OP_BWD && s.K % 4 != 0)) return -1;
+    if (s.C % 4 != 0 || (op == OP_BWD && s.K % 4 != 0)) return -1;
     if (const char *f = getenv("MXC_FORCE_VARIANT")) {
         for (int i = 0; i < N_WAVES; ++i)
             if (!strcmp(f, kWaves[i].name)) return i;
@@ -1242,7 +1300,14 @@ int wave_rows(const ConvShape &s, int op, bool nchw, int other, bool masked)
     const long long m = op == OP_FWD ? (long long)s.N * s.P * s.Q : (long long)s.N * s.H * s.W, cols = op == OP_FWD ? s.K : s.C;
     const int taps = op == OP_FWD ? s.R * s.S : ((s.R + s.stride - 1) / s.stride) * ((s.S + s.stride - 1) / s.stride);
     const long long k = (long long)taps * (op == OP_FWD ? s.C : s.K);
-    const double most = tile_us(other, op, m, cols, k, 1, masked) * (op == OP_BWD && s.stride > 1 ? 0.75 : 0.95);
+    const bool classes = op == OP_BWD && s.stride > 1;
+    double most = tile_us(other, op, nchw, m, cols, k, 1, masked) * (classes ? 0.75 : nchw ? 0.93 : 0.95);
+    if (nchw) {
+        const int RS = s.R * s.S, plane = op == OP_FWD ? s.P * s.Q : s.H * s.W;
+        const long long from = op == OP_FWD ? (long long)s.N * s.C * s.H * s.W : (long long)s.N * s.K * s.P * s.Q;
+        most -= 3.3 + 0.33 * 4e-6 * (from + (RS > 1 ? (long long)s.K * s.C * RS : 0)) + (classes || plane % 4 != 0 ? 0.22 * 4e-6 * m * cols : 0.0);
+        if (op == OP_FWD) most -= 0.00047 * s.N * ((s.C + 63) / 64) * ((s.H * s.W + 63) / 64);
+    }
     double best = 0;
     int shape = -1;
     for (int i = 0; i < N_WAVES; ++i) {
@@ -1271,13 +1336,20 @@ static int run(int op, bool nchw, int t, F32Params &p, long long row_tiles, long
     p.by_ntiles = FastDiv(p.n_tiles); p.by_tiles = FastDiv(p.tiles);
     p.by_ci = FastDiv(op == OP_BWD ? s.K : s.C); p.by_c = FastDiv(s.C); p.by_rs = FastDiv(s.R * s.S); p.by_s = FastDiv(s.S);
     p.by_pq = FastDiv(s.P * s.Q); p.by_q = FastDiv(s.Q); p.by_p = FastDiv(s.P);
-    if (t < 0) return op == OP_WGRAD ? launch_wave_dw_op(-1 - t, p, st) : launch_wave_op(op, -1 - t, p, st);
+    if (t < 0) return op == OP_WGRAD ? launch_wave_dw_op(-1 - t, p, st) : launch_wave_op(op, nchw, -1 - t, p, st);
     return launch_op(op, nchw, t, p, st);
 }
 
-int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y, hipStream_t st, const char **variant, const PostOp &post)
+// The wave kernel's shape that runs an NCHW problem on NHWC copies of its operands, or -1: the operands are read in place.
+int f32_copies(const ConvShape &s, bool bwd, bool masked)
 {
-    const int tile = plan_rows(s, OP_FWD).tile, wv = wave_rows(s, OP_FWD, nchw, tile, false), t = wv >= 0 ? -1 - wv : tile;
+    const int op = bwd ? OP_BWD : OP_FWD;
+    return wave_rows(s, op, true, plan_rows(s, op).tile, masked);
+}
+
+int f32_fwd(const ConvShape &s, bool nchw, int copies, const void *x, const void *w, void *y, hipStream_t st, const char **variant, const PostOp &post)
+{
+    const int tile = plan_rows(s, OP_FWD).tile, wv = nchw ? copies : wave_rows(s, OP_FWD, false, tile, false), t = wv >= 0 ? -1 - wv : tile;
     const int bm = wv >= 0 ? 16 * kWaves[wv].mb * kWaves[wv].mg : kTiles[t].bm;
     F32Params p{};
     p.a = (const float *)x; p.b = (const float *)w; p.out = (float *)y;
@@ -1294,9 +1366,10 @@ int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y
     return run(OP_FWD, nchw, t, p, ((long long)p.M + bm - 1) / bm, s.K, 1, st);
 }
 
-int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, void *dx, hipStream_t st, const char **variant, const PostOp &post)
+int f32_bwd_data(const ConvShape &s, bool nchw, int copies, const void *dy, const void *w, void *dx, hipStream_t st, const char **variant,
+                 const PostOp &post)
 {
-    const int tile = plan_rows(s, OP_BWD).tile, wv = wave_rows(s, OP_BWD, nchw, tile, post.mask != nullptr), t = wv >= 0 ? -1 - wv : tile;
+    const int tile = plan_rows(s, OP_BWD).tile, wv = nchw ? copies : wave_rows(s, OP_BWD, false, tile, post.mask != nullptr), t = wv >= 0 ? -1 - wv : tile;
     const int bm = wv >= 0 ? 16 * kWaves[wv].mb * kWaves[wv].mg : kTiles[t].bm;
     F32Params p{};
     p.a = (const float *)dy; p.b = (const float *)w; p.out = (float *)dx;
@@ -1337,7 +1410,7 @@ static F32Plan wave_wgrad(const ConvShape &s, bool nchw, const F32Plan &pl)
             if (strlen(kDwWaves[i].name) == len && !strncmp(f, kDwWaves[i].name, len)) return ranges(i, slash ? atoi(slash + 1) : 1);
         return F32Plan{0, 0, 0};
     }
-    double best = 0.95 * tile_us(pl.tile, OP_WGRAD, s.K, cols, pl.span, pl.splits, false);
+    double best = 0.95 * tile_us(pl.tile, OP_WGRAD, false, s.K, cols, pl.span, pl.splits, false);
     F32Plan chosen{0, 0, 0};
     for (int i = 0; i < N_DW_WAVES; ++i) {
         const F32WaveDw &w = kDwWaves[i];

@@ -253,6 +253,42 @@ __global__ __launch_bounds__(256) void relayout_kernel(const RelayJobs jobs, con
     }
 }
 
+// The same for plain transposes of 4-byte elements, 64 x 64 a workgroup: reads and writes of 256 contiguous bytes per wave, the
+// elements of a tile of fewer columns (the taps of a filter) in the order they lie.
+template <int NJ>
+__global__ __launch_bounds__(256) void relayout4_kernel(const RelayJobs jobs)
+{
+    constexpr int PITCH = TILE + 1;
+    __shared__ uint32_t tile[TILE * PITCH];
+    unsigned blk = blockIdx.x;
+    RelayJob q = jobs.job[0];
+#pragma unroll
+    for (int i = 1; i < NJ; ++i) {
+        const unsigned before = i == 1 ? jobs.job[0].blocks : jobs.job[0].blocks + jobs.job[1].blocks;
+        if (blockIdx.x >= before) { q = jobs.job[i]; blk = blockIdx.x - before; }
+    }
+    const unsigned gx = (unsigned)(q.cols + TILE - 1) / TILE, gy = (unsigned)q.run_tiles, b2 = blk / gx;
+    const int c0 = (int)(blk % gx) * TILE, r0 = (int)(b2 % gy) * TILE, nr = min(TILE, q.rows - r0), nc = min(TILE, q.cols - c0);
+    const long long b = b2 / gy;
+    const uint32_t *src = (const uint32_t *)q.src + b * q.src_batch + (long long)r0 * q.src_pitch + c0;
+    uint32_t *dst = (uint32_t *)q.dst + b * q.dst_batch + (long long)c0 * q.dst_pitch + r0;
+    const int t = threadIdx.x;
+    // f(i, o, in) for the places of an outer x inner tile, inner padded to a power of two that the lanes share; all loads in flight at once
+    auto each = [&](int outer, int inner, auto &&f) __attribute__((always_inline)) {
+        const int lw = 32 - __clz(inner - 1 | 3), in = t & ((1 << lw) - 1);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int o = (t >> lw) + (i << (8 - lw));
+            if (o < outer && in < inner) f(i, o, in);
+        }
+    };
+    uint32_t v[16];
+    each(nr, nc, [&](int i, int r, int c) __attribute__((always_inline)) { v[i] = src[(long long)r * q.src_pitch + c]; });
+    each(nr, nc, [&](int i, int r, int c) __attribute__((always_inline)) { tile[c * PITCH + r] = v[i]; });
+    __syncthreads();
+    each(nc, nr, [&](int, int c, int r) __attribute__((always_inline)) { dst[(long long)c * q.dst_pitch + r] = tile[c * PITCH + r]; });
+}
+
 // Few channels (c <= 8): one thread per pixel.  planar[b][c][pixels] <-> interleaved[b][pixels][c];
 // both sides are contiguous across the lanes of a wave.
 template <typename T, bool TO_INTERLEAVED>
@@ -450,6 +486,25 @@ static int launch_relayout(const RelayJobs &all, long long blocks, hipStream_t s
     else if (all.n == 1) hipLaunchKernelGGL(relayout_kernel<1>, grid, block, 0, st, all, NoResum{});
     else if (all.n == 2) hipLaunchKernelGGL(relayout_kernel<2>, grid, block, 0, st, all, NoResum{});
     else hipLaunchKernelGGL(relayout_kernel<3>, grid, block, 0, st, all, NoResum{});
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+}
+
+int relayout4(const RelayJob *jobs, int n, hipStream_t st)
+{
+    RelayJobs all{};
+    long long total = 0;
+    for (all.n = 0; all.n < n; ++all.n) {
+        RelayJob &q = all.job[all.n];
+        q = jobs[all.n];
+        q.run_tiles = (q.run + TILE - 1) / TILE;
+        const long long blocks = (long long)((q.cols + TILE - 1) / TILE) * q.run_tiles * q.batch;
+        if ((total += blocks) > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
+        q.blocks = (unsigned)blocks;
+    }
+    const dim3 grid((unsigned)total), block(256);
+    if (n == 1) hipLaunchKernelGGL(relayout4_kernel<1>, grid, block, 0, st, all);
+    else if (n == 2) hipLaunchKernelGGL(relayout4_kernel<2>, grid, block, 0, st, all);
+    else hipLaunchKernelGGL(relayout4_kernel<3>, grid, block, 0, st, all);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 

@@ -266,6 +266,8 @@ struct RelayJob {
     int C, class_C, R, S, stride;
     unsigned blocks;
 };
+// up to MAX_RELAY_JOBS plain transposes of 4-byte elements in one launch
+int relayout4(const RelayJob *jobs, int n, hipStream_t st);
 RelayJob relay_to_nhwc(const void *src, void *dst, int n, int c, int hw, int c_pitch);      // [n][c][hw] -> [n][hw][c_pitch]
 RelayJob relay_to_nchw(const void *src, void *dst, int n, int c, int hw, int c_pitch);      // [n][hw][c_pitch] -> [n][c][hw]
 RelayJob relay_pad(const void *src, void *dst, long long rows, int c, int c_pitch);         // [rows][c] -> [rows][c_pitch]
@@ -305,8 +307,11 @@ int resum_dw(const Resum &q, void *dw, bool dw_bf16, hipStream_t st);
 
 // ---- fp32.hip: fp32 matrix-core convolution, NHWC/KRSC or NCHW/KCRS operands read in place -----------------
 bool f32_supported(const ConvShape &s);
-int f32_fwd(const ConvShape &s, bool nchw, const void *x, const void *w, void *y, hipStream_t st, const char **variant, const PostOp &post);
-int f32_bwd_data(const ConvShape &s, bool nchw, const void *dy, const void *w, void *dx, hipStream_t st, const char **variant,
+// `copies`: with NCHW, what f32_copies answered (at least 0: the operands are NHWC / KRSC copies, the result goes to its planes)
+int f32_copies(const ConvShape &s, bool bwd, bool masked);
+int f32_fwd(const ConvShape &s, bool nchw, int copies, const void *x, const void *w, void *y, hipStream_t st, const char **variant,
+            const PostOp &post);
+int f32_bwd_data(const ConvShape &s, bool nchw, int copies, const void *dy, const void *w, void *dx, hipStream_t st, const char **variant,
                  const PostOp &post);
 size_t f32_wgrad_workspace(const ConvShape &s);       // bytes of fp32 partial tensors
 int f32_wgrad(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, float *partial, hipStream_t st, const char **variant);

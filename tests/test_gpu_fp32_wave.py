@@ -1,6 +1,7 @@
-"""fp32 NHWC layers of whole 16-byte chunks of channels (the wave kernels of fp32.hip), every shape of them: ragged rows, columns and
+"""fp32 layers of whole 16-byte chunks of channels (the wave kernels of fp32.hip), every shape of them: ragged rows, columns and
 reductions, steps in one tap and across taps, 1x1 filters, strides with residue classes no tap reaches, one and several
-pixel ranges of dw, infinities and NaN opposite padding."""
+pixel ranges of dw, infinities and NaN opposite padding; NCHW problems on NHWC copies, planes of whole and of broken groups of
+four pixels."""
 import numpy as np
 import pytest
 import torch
@@ -19,6 +20,7 @@ DIMS = [
     (2, 24, 12, 11, 40, 3, 3, 2, 1),
     (40, 8, 3, 3, 12, 2, 2, 1, 0),         # images of fewer pixels than a step
 ]
+LAYOUTS = ["nhwc", "nchw"]
 
 
 @pytest.fixture(scope="module")
@@ -39,13 +41,14 @@ def _case(dims):
 
 
 @pytest.mark.parametrize("dims", DIMS + [(2, 12, 8, 9, 30, 3, 3, 1, 1)])       # filters that are no multiple of 4: forward only
+@pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("name", _names(False))
-def test_forward(mxc, oracle, monkeypatch, name, dims):
+def test_forward(mxc, oracle, monkeypatch, name, layout, dims):
     monkeypatch.setenv("MXC_FORCE_VARIANT", name)
     N, C, H, W, K, R, S, st, pad = dims
     x, w, _ = _case(dims)
     bias = np.linspace(-1.0, 1.0, K).astype(np.float32)
-    run = util.Runner(mxc, dims, "f32", "nhwc")
+    run = util.Runner(mxc, dims, "f32", layout)
     y = torch.full((N * K * run.P * run.Q + 64,), 7.0, device="cuda")
     mxc.mxc_conv2d_fwd_bias_act(*dims, run.dt, run.lay, run._in(x), run._in(w), torch.from_numpy(bias).cuda(), 1, y, run._ws(mxc.MXC_FWD))
     assert mxc.mxc_last_variant().split(":")[-1] == name
@@ -55,21 +58,36 @@ def test_forward(mxc, oracle, monkeypatch, name, dims):
     assert np.all(np.abs(got - ref) <= util.tight_bound(ref, den, "f32", False)), dims
 
 
-@pytest.mark.parametrize("dims", DIMS)
+def _copies(dims, layout):
+    """whether dx of an NCHW problem can run on copies: the filter's copy has to fit where dx's would lie"""
+    N, C, H, W, K, R, S, st, pad = dims
+    return layout == "nhwc" or R * S == 1 or K * C * R * S <= N * C * H * W
+
+
+@pytest.mark.parametrize("dims", DIMS + [(3, 20, 9, 12, 12, 3, 3, 1, 1)])
+@pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("name", _names(False))
-def test_masked_input_gradient(mxc, oracle, monkeypatch, name, dims):
+def test_masked_input_gradient(mxc, oracle, monkeypatch, name, layout, dims):
     monkeypatch.setenv("MXC_FORCE_VARIANT", name)
     N, C, H, W, K, R, S, st, pad = dims
     x, w, dy = _case(dims)
-    run = util.Runner(mxc, dims, "f32", "nhwc")
+    run = util.Runner(mxc, dims, "f32", layout)
     dx = torch.full((N * C * H * W + 64,), 7.0, device="cuda")
     mxc.mxc_conv2d_bwd_data_relu(*dims, run.dt, run.lay, run._in(dy), run._in(w), run._in(x), dx, run._ws(mxc.MXC_BWD_DATA_RELU))
-    assert mxc.mxc_last_variant().split(":")[-1] == name
+    assert (mxc.mxc_last_variant().split(":")[-1] == name) == _copies(dims, layout)
     assert bool((dx[-64:] == 7.0).all())
     ref, den = oracle.conv2d_bwd_data_relu(dy, w, x, st, pad)
     got = run._out(dx[:-64], (N, C, H, W))
     assert np.all(np.abs(got - ref) <= util.tight_bound(ref, den, "f32", False)), dims
     assert np.all(got[x <= 0] == 0)
+    if layout == "nchw":                   # the prepared filter is a copy of the caller's: the same kernel, the same bits
+        a = (*dims, run.dt, run.lay)
+        plain, prepared = (torch.empty(N * C * H * W, device="cuda") for _ in range(2))
+        mxc.mxc_conv2d_bwd_data(*a, run._in(dy), run._in(w), plain, run._ws(mxc.MXC_BWD_DATA))
+        pw = run._ws(mxc.MXC_BWD_DATA_FILTER)
+        mxc.mxc_conv2d_bwd_data_prepare_filter(*a, run._in(w), pw)
+        mxc.mxc_conv2d_bwd_data_prepared(*a, run._in(dy), pw, None, prepared, run._ws(mxc.MXC_BWD_DATA_PREPARED))
+        assert torch.equal(plain, prepared)
 
 
 @pytest.mark.parametrize("ranges", [1, 3])
@@ -90,14 +108,15 @@ def test_weight_gradient(mxc, oracle, monkeypatch, name, dims, ranges):
     assert np.all(np.abs(got - ref) <= util.tight_bound(ref, den, "f32", False)), dims
 
 
+@pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
-def test_taps_outside_are_left_out(mxc, monkeypatch, bad):
+def test_taps_outside_are_left_out(mxc, monkeypatch, bad, layout):
     """A filter tap that holds no finite value meets the image only where it lies inside: the first rows of a padded layer
     must not see the filter's first row, whatever kernel sums them."""
     dims = (2, 16, 6, 7, 20, 3, 3, 1, 1)
     N, C, H, W, K, R, S, st, pad = dims
     x, w, dy = _case(dims)
-    run = util.Runner(mxc, dims, "f32", "nhwc")
+    run = util.Runner(mxc, dims, "f32", layout)
     a = (*dims, run.dt, run.lay)
     clean, worse = w.copy(), w.copy()
     worse[:, :, 0, :] = bad
@@ -107,9 +126,12 @@ def test_taps_outside_are_left_out(mxc, monkeypatch, bad):
         y = [torch.empty(N * K * H * W, device="cuda") for _ in range(2)]
         for f, out in zip((clean, worse), y):
             mxc.mxc_conv2d_fwd(*a, run._in(xp), run._in(f), out, run._ws(mxc.MXC_FWD))
-        first = [t.view(N, H, W, K)[:, 0] for t in y]
+        y = [t.view(N, H, W, K) if layout == "nhwc" else t.view(N, K, H, W).permute(0, 2, 3, 1) for t in y]
+        first = [t[:, 0] for t in y]
         assert bool(torch.isfinite(first[1]).all()) and torch.allclose(first[0], first[1], rtol=1e-5, atol=1e-5)
-        assert not bool(torch.isfinite(y[1].view(N, H, W, K)[:, 1:]).any())
+        assert not bool(torch.isfinite(y[1][:, 1:]).any())
+    if layout == "nchw":
+        return
     # dy's last row does not meet the filter's first row in dw: its pixels there lie outside x
     bad_dy = dy.copy()
     bad_dy[:, :, 0, :] = bad
