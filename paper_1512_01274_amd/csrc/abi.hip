@@ -318,8 +318,14 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
         void *w2 = fws.take(w2_bytes), *dx4 = run ? ws.take(dx4_bytes) : nullptr;
         if (dry) return MXC_OK;
         const char *v = "";
-        if (prep) MXC_TRY(igemm_bwd_data_smallc_prepare(s, w, w2, st));
+        const char *forced = getenv("MXC_FORCE_VARIANT");
+        const bool taps = taps_dx_supported(s) && (forced == nullptr ? taps_dx_faster(s) : !strcmp(forced, taps_dx_name()));
+        if (prep && !(taps && mode == FILTER_RAW)) MXC_TRY(igemm_bwd_data_smallc_prepare(s, w, w2, st));
         if (!run) return MXC_OK;
+        if (taps) {
+            set_variant("bwd_data", (std::string("smallc+") + taps_dx_name()).c_str());
+            return taps_dx(s, dy, mode == FILTER_RAW ? w : w2, mode != FILTER_RAW, igemm_bwd_data_smallc_columns(s), dx, st, post);
+        }
         const int rc = igemm_bwd_data_smallc(s, dy, w2, dx, dx4, st, &v, post);
         set_variant("bwd_data", (std::string("smallc+") + v).c_str());
         return rc;
@@ -1104,7 +1110,7 @@ const char *mxc_tile_name(int family, int index)
 {
     return family == 0 ? igemm_tile_name(index) : family == 1 ? wgrad_tile_name(index) : family == 2 ? igemm_stream_name(index)
            : family == 3 ? f32_tile_name(index) : family == 4 ? wave_name(index) : family == 5 ? wave_dw_name(index)
-           : family == 6 ? f32_wave_name(index) : nullptr;
+           : family == 6 ? f32_wave_name(index) : family == 7 && index == 0 ? taps_dx_name() : nullptr;
 }
 
 int mxc_probe_mfma(int workgroups, int iters, void *out, size_t out_bytes, double *flops, void *hip_stream)

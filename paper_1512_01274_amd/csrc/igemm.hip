@@ -1506,6 +1506,8 @@ void igemm_bwd_data_smallc_workspace(const ConvShape &s, size_t *w2_bytes, size_
     *dx4_bytes = (size_t)s.N * s.H * g.Wg * g.G * 4 * 2;
 }
 
+int igemm_bwd_data_smallc_columns(const ConvShape &s) { return smallc_bwd_geom(s).U; }
+
 int igemm_bwd_data_smallc_prepare(const ConvShape &s, const void *w, void *w2, hipStream_t st)
 {
     const SmallCBwd g = smallc_bwd_geom(s);

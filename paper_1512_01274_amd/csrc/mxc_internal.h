@@ -305,6 +305,12 @@ int direct_bwd_weight(const ConvShape &s, int dtype, const void *x, const void *
 int resum_dx(const Resum &q, void *dx, hipStream_t st);
 int resum_dw(const Resum &q, void *dw, bool dw_bf16, hipStream_t st);
 
+// ---- taps_dx.hip: backward-data of first layers at stride 1 in one launch ----------------------------------
+const char *taps_dx_name();
+bool taps_dx_supported(const ConvShape &s);
+bool taps_dx_faster(const ConvShape &s);      // of a supported layer
+int taps_dx(const ConvShape &s, const void *dy, const void *w, bool packed, int packed_cols, void *dx, hipStream_t st, const PostOp &post);
+
 // ---- fp32.hip: fp32 matrix-core convolution, NHWC/KRSC or NCHW/KCRS operands read in place -----------------
 bool f32_supported(const ConvShape &s);
 // `copies`: with NCHW, what f32_copies answered (at least 0: the operands are NHWC / KRSC copies, the result goes to its planes)
@@ -347,6 +353,7 @@ int igemm_bwd_data_image(ImageStore kind, const ConvShape &s2, const S2DStore &q
 // backward-data for C <= 4: G output columns form one GEMM row (see igemm.hip)
 bool igemm_bwd_data_smallc_supported(const ConvShape &s);
 void igemm_bwd_data_smallc_workspace(const ConvShape &s, size_t *w2_bytes, size_t *dx4_bytes);
+int igemm_bwd_data_smallc_columns(const ConvShape &s);       // dy columns per row of the packed filter
 int igemm_bwd_data_smallc_prepare(const ConvShape &s, const void *w, void *w2, hipStream_t st);
 int igemm_bwd_data_smallc(const ConvShape &s, const void *dy, const void *w2, void *dx, void *dx4, hipStream_t st,
                           const char **variant, const PostOp &post = PostOp());
