@@ -506,7 +506,7 @@ __device__ __forceinline__ long long dw_place(const DwMap &m, int k, int col, in
 // wave_dw_best: the shape and ranges (at most max_ranges) of least modelled time and that time, or -1.
 const char *wave_dw_name(int shape);
 int wave_dw_ranges(long long M, int ranges, int *span);        // the number of ranges there are, none empty, and their length
-int wave_dw_best(const WgradGeom &g, int max_ranges, int *ranges, double *us);
+int wave_dw_best(const WgradGeom &g, bool copies, int max_ranges, int *ranges, double *us);
 int wave_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const void *x, const void *dy, void *out, const DwMap *map, bool dw_bf16, int rows,
                    hipStream_t st);
 

@@ -265,7 +265,10 @@ int wave_dw_ranges(long long M, int ranges, int *span)
     return (int)((M + *span - 1) / *span);
 }
 
-int wave_dw_best(const WgradGeom &g, int max_ranges, int *ranges, double *us)
+// copies: x and dy have just been written by the launch before, so a CU's loads find them in no cache of its own XCD.  32x32, one
+// range, 112 x 80 filters: 0.25 us per step of the waves where they lie in the L2, 0.8 as copies (48 images of 11x16: 12.0 and 32.0 us;
+// 16 to 64 channels 3x3 13.6 and 21.3), and a third launch in a row costs its 2.6 us in full.
+int wave_dw_best(const WgradGeom &g, bool copies, int max_ranges, int *ranges, double *us)
 {
     const long long M = (long long)g.N * g.P * g.Q;
     const int ncols = g.TR * g.TS * g.run;
@@ -284,9 +287,9 @@ int wave_dw_best(const WgradGeom &g, int max_ranges, int *ranges, double *us)
             z = wave_dw_ranges(M, (int)z, &span);
             const long long per_cu = (tiles * z + 255) / 256;
             const double rounds = (double)((per_cu + slots - 1) / slots), turns = (double)((span + 32 * s.kg * s.u - 1) / (32 * s.kg * s.u));
-            double t = s.fixed + s.round * rounds + s.turn * rounds * turns + s.load * 1e-3 * tiles * z * turns * s.kg * s.u * (s.mb + s.nb) +
+            double t = s.fixed + s.round * rounds + (s.turn + (copies ? 0.3f : 0.f)) * rounds * turns + s.load * 1e-3 * tiles * z * turns * s.kg * s.u * (s.mb + s.nb) +
                        s.area * 0.1 * per_cu * s.mb * s.nb + s.dw * mb;
-            if (z > 1) t += 2.45 + s.part * z * mb;
+            if (z > 1) t += (copies ? 3.0 : 2.45) + s.part * z * mb;
             else if (g.K != g.Kout && g.opad > 0) t += 2.4;       // sums that padding made NaN: a launch of its own looks
             if (best < 0 || t < *us) { best = i; *us = t; *ranges = (int)z; }
         }

@@ -440,34 +440,28 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
 }
 
 // The same for dw in KCRS order: one workgroup adds up 64 channels of one k (reads contiguous along the channels),
-// passes the sums through LDS and writes the 64*R*S results as one contiguous run.  G interleaved groups of splits per
-// output keep loads in flight; their sums are added in ascending order.
-template <int G, typename OUT>
+// passes the sums through LDS and writes the 64*R*S results as one contiguous run.
+template <typename OUT>
 __global__ __launch_bounds__(256) void wgrad_reduce_kcrs_kernel(const float *__restrict__ partial, OUT *__restrict__ dw, int splits, int ncols,
                                                                 int RS, int S, int C, int c_tiles, int col_r, int col_s, int s2d, int Cq,
                                                                 size_t split_stride)
 {
-    extern __shared__ float red[];                    // [G][64 * RS], then the sums as [channel][RS] in group 0's place
+    extern __shared__ float red[];                    // the sums as [channel][RS]
     const int k = blockIdx.x / c_tiles, c0 = blockIdx.x % c_tiles * 64;
     const int n = min(C - c0, 64), items = 64 * RS;
-    for (int i = threadIdx.x; i < items * G; i += 256) {
-        const int g = i / items, e = i % items, rs = e >> 6, c = e & 63;
+    for (int e = threadIdx.x; e < items; e += 256) {
+        const int rs = e >> 6, c = e & 63;
         float acc = 0.f;
         if (c < n) {
             const int r = rs / S, s = rs % S;
             const float *src = partial + (size_t)k * ncols + (r / s2d) * col_r + (s / s2d) * col_s + ((r % s2d) * s2d + s % s2d) * Cq + c0 + c;
-            for (int z = g; z < splits; z += G) acc += src[(size_t)z * split_stride];
+            for (int z = 0; z < splits; ++z) acc += src[(size_t)z * split_stride];
         }
-        red[g * items + c * RS + rs] = acc;
+        red[c * RS + rs] = acc;
     }
     __syncthreads();
     OUT *out = dw + ((size_t)k * C + c0) * RS;
-    for (int i = threadIdx.x; i < n * RS; i += 256) {
-        float acc = 0.f;
-#pragma unroll
-        for (int g = 0; g < G; ++g) acc += red[g * items + i];
-        store_f32(out + i, acc);
-    }
+    for (int i = threadIdx.x; i < n * RS; i += 256) store_f32(out + i, red[i]);
 }
 
 // slots: workgroups that fit one CU; util: fraction of the CU's matrix peak the tile sustains (measured)
@@ -512,16 +506,17 @@ int launch_choice(int idx, const WgradParams &p, int tiles, hipStream_t st)
     }
 }
 
-// wave: the wave kernel's shape, pixel ranges and their length, where it runs instead of the tile (shape -1: it does not)
+// wave: the wave kernel's shape, pixel ranges and their length, where it runs instead of the tile (shape -1: it does not); [1]: of operands
+// that are copies written just before
 struct DwWave { int shape, ranges, span; };
-struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave; };
+struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave[2]; };
 
 // Tile and split choice: the pair with the least modelled time - rounds over the chip's workgroup
 // slots (256 CUs x slots per CU) x stages each split walks x time per stage, plus the traffic of
 // writing and re-reading one fp32 partial tensor per split.  MXC_FORCE_WGRAD=<name> (tuning sweeps
 // only) fixes the tile.
 Plan search_plan(const WgradGeom &g, int forced, int forced_splits);
-DwWave wave_choice(const WgradGeom &g, const Plan &pl);
+DwWave wave_choice(const WgradGeom &g, const Plan &pl, bool copies);
 
 #include "tuned_wgrad.inc"
 
@@ -557,7 +552,7 @@ Plan make_plan(const WgradGeom &g)
     // (what the hook forces on the wave kernel is looked up again on every call)
     const bool hook = getenv("MXC_FORCE_WGRAD") != nullptr;
     auto with_wave = [&](Plan pl) {
-        if (hook) pl.wave = wave_choice(g, pl);
+        if (hook) pl.wave[0] = pl.wave[1] = wave_choice(g, pl, false);
         return pl;
     };
     struct Entry { WgradGeom g; int forced, forced_splits; bool hook; Plan plan; bool used; };
@@ -568,7 +563,8 @@ Plan make_plan(const WgradGeom &g)
     Entry &slot = cache[next];
     next = (next + 1) % 32;
     slot.g = g; slot.forced = forced; slot.forced_splits = forced_splits; slot.plan = search_plan(g, forced, forced_splits);
-    if (!hook) slot.plan.wave = wave_choice(g, slot.plan);
+    if (!hook)
+        for (const bool copies : {false, true}) slot.plan.wave[copies] = wave_choice(g, slot.plan, copies);
     slot.hook = hook;
     slot.used = true;
     return with_wave(slot.plan);
@@ -588,7 +584,7 @@ double tile_us(const WgradGeom &g, const Plan &pl)
 // takes more ranges than the plan has, which the workspace is sized for.  Of the 543 gradients it runs 1.43 times as fast as
 // the planned tiles alone (below 8, 8-15, 15-30, above 30 us: 1.43, 1.63, 1.38, 1.02).  The margin is larger from 25 us on, and
 // from 36 us on tiles that waves share move less per multiply-add (39060 pixels, 112 x 1440: 28 -> 41).
-DwWave wave_choice(const WgradGeom &g, const Plan &pl)
+DwWave wave_choice(const WgradGeom &g, const Plan &pl, bool copies)
 {
     const long long M = (long long)g.N * g.P * g.Q;
     DwWave w{-1, 0, 0};
@@ -605,8 +601,9 @@ DwWave wave_choice(const WgradGeom &g, const Plan &pl)
     }
     double us = 0;
     int ranges = 1;
-    const int shape = wave_dw_best(g, pl.splits, &ranges, &us);
+    int shape = wave_dw_best(g, false, pl.splits, &ranges, &us);
     if (shape >= 0 && us < 36 && us < (us < 25 ? 0.93 : 0.86) * tile_us(g, pl)) {
+        if (copies) shape = wave_dw_best(g, true, pl.splits, &ranges, &us);      // (the tiles' model knows no copies either)
         w.shape = shape;
         w.ranges = wave_dw_ranges(M, ranges, &w.span);
     }
@@ -709,10 +706,11 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
     const size_t split_stride = (size_t)g.K * ncols;
     // many splits of a small dw: 16 lane groups keep enough loads in flight; otherwise 4
     const bool wide = splits >= 32 && total < 256 * 1024;
-    // KCRS: a workgroup of the reordering kernel adds up 64*R*S results; where that would be a long chain for each of its
-    // threads (112 splits of a 50x30x3x3 filter: 65 us), or its workgroups are fewer than the CUs (whole gradients, us: 28x28
-    // 64 to 10 channels 3x3 18.7 -> 11.8, 8x14x14 64 to 64 23.0 -> 11.2), the mapped reduction does it
-    const bool kcrs_long = kcrs && ((long long)splits * g.R * g.S > 128 || (long long)g.Kout * ((g.C + 63) / 64) < 256);
+    // KCRS: a workgroup of the reordering kernel adds up 64*R*S results; from four splits on, each a dependent load for each of its
+    // threads (whole gradients, us: 3x49x49 32 to 480 channels 3x3 27.3 -> 20.1, 21x12x17 404 to 510 66 -> 52), and where its workgroups are
+    // fewer than the CUs (28x28 64 to 10 channels 3x3 18.7 -> 11.8, 8x14x14 64 to 64 23.0 -> 11.2), the mapped reduction does
+    // it.  Below, its results leave in whole runs (two splits of a 480 to 224 channel 5x5 filter: 154 us against 165).
+    const bool kcrs_long = kcrs && (splits >= 4 || (long long)g.Kout * ((g.C + 63) / 64) < 256);
     const bool same = identity && total % 4 == 0 && split_stride % 4 == 0;
     if (splits > 1 && (kcrs ? kcrs_long : !identity || (same && wide))) {
         // (a lane adds up 2^15 pixels in some 20 ms, should it come to that; the kernel of its own shares them out)
@@ -740,13 +738,8 @@ static int launch_reduce(const WgradGeom &g, float *partial, OUT *dw, int splits
         const int RS = g.R * g.S, c_tiles = (g.C + 63) / 64;
         if ((long long)g.Kout * c_tiles > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
         const dim3 grid((unsigned)(g.Kout * c_tiles));
-        // eight groups of splits while their sums fit 32 KB of LDS
-        if (splits >= 4 && RS <= 16)
-            hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<8, OUT>), grid, dim3(256), (size_t)8 * 64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S,
-                               g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
-        else
-            hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<1, OUT>), grid, dim3(256), (size_t)64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S,
-                               g.C, c_tiles, g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
+        hipLaunchKernelGGL((wgrad_reduce_kcrs_kernel<OUT>), grid, dim3(256), (size_t)64 * RS * 4, st, partial, dw, splits, ncols, RS, g.S, g.C, c_tiles,
+                           g.col_r, g.col_s, g.s2d, g.Cq, split_stride);
         return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
     }
     if (same) {
@@ -781,7 +774,9 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
           const char **variant, const Resum *resum)
 {
     const Plan pl = make_plan(g);
-    if (const DwWave wv = pl.wave; wv.shape >= 0) {
+    const DwWave wv = pl.wave[kcrs];                  // an NCHW problem's operands are copies
+    if (g.R * g.S == 1) kcrs = false;                 // one tap: both orders are the same
+    if (wv.shape >= 0) {
         const int ncols = g.TR * g.TS * g.run;
         const bool same = dw_identity(g) && !kcrs;
         *variant = wave_dw_name(wv.shape);
