@@ -1241,10 +1241,8 @@ F32Plan plan_rows(const ConvShape &s, int op)
 
 // Backward-weight: tile and number of pixel ranges; every range beyond the first writes and re-reads one fp32 dw
 // (8 bytes per element at about 3 TB/s) and makes the summing launch necessary (5000 clocks: 2.2 us where it is all launch).
-F32Plan plan_wgrad(const ConvShape &s)
+F32Plan search_wgrad(const ConvShape &s, int ft, int fs)
 {
-    int fs = 0;
-    const int ft = forced_tile("MXC_FORCE_WGRAD", &fs);
     const long long M = (long long)s.N * s.P * s.Q, cols = (long long)s.C * s.R * s.S;
     double best = 1e300;
     F32Plan pl{0, 1, (int)M};
@@ -1265,6 +1263,21 @@ F32Plan plan_wgrad(const ConvShape &s)
         }
     }
     return pl;
+}
+
+// A call asks three times, at up to 7 us a search: the calling thread keeps its answers (64, each geometry's place given by its numbers).
+F32Plan plan_wgrad(const ConvShape &s)
+{
+    int fs = 0;
+    const int ft = forced_tile("MXC_FORCE_WGRAD", &fs);
+    if (ft >= 0) return search_wgrad(s, ft, fs);
+    const long long M = (long long)s.N * s.P * s.Q;
+    const int cols = s.C * s.R * s.S;
+    struct Entry { long long M; int K, cols; F32Plan plan; };
+    static thread_local Entry cache[64] = {};
+    Entry &e = cache[(unsigned)(M * 31 + s.K * 7 + cols * 3) % 64];
+    if (e.M != M || e.K != s.K || e.cols != cols) e = Entry{M, s.K, cols, search_wgrad(s, -1, 0)};
+    return e.plan;
 }
 
 }  // namespace
