@@ -769,7 +769,8 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
           const char **variant, const Resum *resum)
 {
     const Plan pl = make_plan(g);
-    const DwWave wv = pl.wave[kcrs];                  // an NCHW problem's operands are copies
+    // the operands of NCHW problems, padded channels and first layers are copies (prepared inputs too: the same kernel, the same bits)
+    const DwWave wv = pl.wave[kcrs || g.K != g.Kout || !dw_identity(g)];
     if (g.R * g.S == 1) kcrs = false;                 // one tap: both orders are the same
     if (wv.shape >= 0) {
         const int ncols = g.TR * g.TS * g.run;
