@@ -524,8 +524,11 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
             jobs[nj++] = relay_to_nhwc(b, w2, K, C, RS, s.C);
             MXC_TRY(relayout(jobs, nj, st));
         }
-        MXC_TRY(fwd_nhwc(s, MXC_BF16, x2, w2, y2, post, ws, st, dry));
-        if (dry) return MXC_OK;
+        PlaneOut direct{out, nullptr, K, false};
+        PostOp post2 = post;
+        post2.planes = &direct;
+        MXC_TRY(fwd_nhwc(s, MXC_BF16, x2, w2, y2, post2, ws, st, dry));
+        if (dry || direct.stored) return MXC_OK;
         jobs[0] = relay_to_nchw(y2, out, s.N, K, s.P * s.Q, s.K);
         return relayout(jobs, 1, st);
     }
@@ -542,9 +545,11 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
         PostOp post2 = post;
         post2.relu = 0;
         FilterMode inner = mode;
+        PlaneOut direct{out, post.mask, C, false};
+        if (run && plain && !first && !resum && igemm_bwd_data_planes(s, post.mask != nullptr)) post2.planes = &direct;
         if (!dry) {
             if (run) jobs[nj++] = relay_to_nhwc(a, dy2, s.N, K, s.P * s.Q, s.K);
-            if (run && post.mask != nullptr) {
+            if (run && post.mask != nullptr && post2.planes == nullptr) {
                 MXC_TRY(convert_x(post.mask, mask2));
                 post2.mask = mask2;
             }
@@ -557,7 +562,7 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
             MXC_TRY(relayout(jobs, nj, st));
         }
         MXC_TRY(bwd_data_nhwc(s, MXC_BF16, dy2, first ? w2 : b, dx2, post2, fws, ws, st, dry, inner, !first));
-        if (dry || !run) return MXC_OK;
+        if (dry || !run || direct.stored) return MXC_OK;
         const Resum rs{without_padding(s), true, (const bf16_t *)a, (const bf16_t *)(mode == FILTER_PREPARED ? wc : b)};
         if (first) {
             MXC_TRY(launch_transpose(dx2, out, s.N, s.H * s.W, C, 2, st));

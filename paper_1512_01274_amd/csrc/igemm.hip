@@ -1048,9 +1048,9 @@ double tile_us(const TileChoice &t, long long M, int Co, int Kd, int splits, boo
 
 // The shape of the wave kernel (wave.hip) that runs this GEMM, or -1: the planned kernel does.  In 475 of the forward and dx passes of
 // 455 random layers it does, and those the planned kernel takes below 8, 8-12, 12-20, 20-40 and more us run 1.33, 1.47, 1.32,
-// 1.29 and 1.23 times as fast (six of them more than 2% slower, 9% at worst).  The models must agree by a margin, larger from 18
-// modelled us on, and from 36 us on the planned kernel keeps what it has: what the models miss weighs more there (359464 pixels, 24
-// columns, 5x5 on 320 channels: modelled 316 against 372, measured 514 against 277; 801420 pixels, 224 x 24: 157 against 108).
+// 1.29 and 1.23 times as fast (six of them more than 2% slower, 9% at worst).  The models must agree by a margin, larger from 18 and
+// from 36 modelled us on: what they miss weighs more there (359464 pixels, 24 columns, 5x5 on 320 channels: modelled 316 against 372,
+// measured 514 against 277; 801420 pixels, 224 x 24: 93 against 128, measured 157 against 108).
 int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_split)
 {
     if (const char *f = getenv("MXC_FORCE_VARIANT")) return wave_forced(f, bwd);
@@ -1064,7 +1064,7 @@ int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_spl
     int wave = whole_launch(pl.main) ? -1 : wave_best(M, Co, Kd, bwd, masked, &us);
     if (wave >= 0) {
         const double other = tile_us(kTiles[pl.main], M, Co, Kd, can_split ? split_count(M, Co, Kd) : 1, masked);
-        if (us >= 36 || us > other * (us < 18 ? 0.92 : 0.785)) wave = -1;
+        if (us > other * (us < 18 ? 0.92 : us < 36 ? 0.785 : 0.69)) wave = -1;
     }
     e = Entry{M, Co, Kd, flags, wave};
     return wave;
@@ -1162,7 +1162,7 @@ int igemm_fwd(const ConvShape &s, const void *x, const void *w, void *y, hipStre
     const long long M = (long long)s.N * s.P * s.Q;
     if (const int wv = wave_choice(M, s.K, s.R * s.S * s.C, false, false, split_ws != nullptr && s.K % 8 == 0); wv >= 0) {
         *variant = wave_name(wv);
-        return wave_launch(wv, p, st, false);
+        return wave_launch(wv, p, st, false, post.planes);
     }
     const int sp = (split_ws != nullptr && s.K % 8 == 0) ? split_count(M, s.K, s.R * s.S * s.C) : 1;
     const Plan pl = plan_for(p, M, s.K, s.R * s.S * s.C, sp > 1);
@@ -1217,7 +1217,7 @@ int igemm_fwd_smallc(const ConvShape &s, const void *xp, const void *wp, void *y
     p.Ho = s.P; p.Wo = s.Q; p.out_mul_h = 1; p.out_mul_w = 1; p.out_off_h = 0; p.out_off_w = 0;
     if (const int wv = wave_choice((long long)s.N * s.P * s.Q, s.K, s.R * g.run, false, false, false); wv >= 0) {
         *variant = wave_name(wv);
-        return wave_launch(wv, p, st, false);
+        return wave_launch(wv, p, st, false, post.planes);
     }
     const Plan pl = plan_for(p, (long long)s.N * s.P * s.Q, s.K, s.R * g.run);
     *variant = plan_name(pl);
@@ -1314,6 +1314,12 @@ bool bwd_data_small_in_place(const ConvShape &s, bool masked)
     return 2.0 * M * s.C * Kd < 1e10;
 }
 
+// whether dx of an NCHW problem, its filter re-packed, goes straight to its planes (see PlaneOut)
+bool igemm_bwd_data_planes(const ConvShape &s, bool masked)
+{
+    return s.stride == 1 && wave_choice((long long)s.N * s.H * s.W, s.C, s.R * s.S * s.K, true, masked, s.C % 8 == 0) >= 0;
+}
+
 // A large 1x1 filter at stride 1 (FullyConnected) is read in place, as transposed tiles, when the chosen
 // tile has that variant: copying it would cost more than the slower operand fetch.
 bool bwd_data_reads_filter_in_place(const ConvShape &s)
@@ -1345,7 +1351,7 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
         const int Kd = s.R * s.S * s.K;
         if (const int wv = wave_choice(M, s.C, Kd, true, p.mask != nullptr, s.C % 8 == 0); wv >= 0) {
             *variant = wave_name(wv);
-            return wave_launch(wv, p, st, bt);
+            return wave_launch(wv, p, st, bt, post.planes);
         }
         const int sp = (split_ws != nullptr && s.C % 8 == 0) ? split_count(M, s.C, Kd) : 1;
         Plan pl = plan_for(p, M, s.C, Kd, (bt && !p.wm_by_k) || sp > 1);

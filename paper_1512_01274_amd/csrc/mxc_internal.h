@@ -59,6 +59,14 @@ struct PostOp {
     const float *bias = nullptr;   // forward: + bias[k], one fp32 value per output channel
     int relu = 0;                  // forward: max(0, .) after the bias
     const void *mask = nullptr;    // backward-data: result is 0 where mask <= 0; same shape, type and layout as dx
+    struct PlaneOut *planes = nullptr;
+};
+// An NCHW problem on NHWC copies: a kernel that can stores the result straight to its planes and says so.
+struct PlaneOut {
+    void *out;                     // [N][cols][plane]
+    const void *mask;              // PostOp::mask in that layout
+    int cols;                      // the problem's own columns
+    bool stored;
 };
 
 // keeps the halves of v (two bf16) whose mask half is > 0
@@ -340,6 +348,7 @@ int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStrea
 // whether igemm_bwd_data reads this layer's filter as it is; otherwise relay_bwd_filter makes the form it reads
 bool bwd_data_reads_filter_in_place(const ConvShape &s);
 // ... or reads the KRSC filter it is handed in place although its prepared form is the re-packed one
+bool igemm_bwd_data_planes(const ConvShape &s, bool masked);
 bool bwd_data_small_in_place(const ConvShape &s, bool masked);
 int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, void *dx, const void *wt, hipStream_t st,
                    const char **variant, const PostOp &post = PostOp(), void *split_ws = nullptr);
@@ -448,7 +457,7 @@ int window_launch(const IgemmParams &p, hipStream_t st);
 const char *wave_name(int shape);
 int wave_forced(const char *name, bool bwd);
 int wave_best(long long M, int Co, int Kd, bool bwd, bool masked, double *us);
-int wave_launch(int shape, const IgemmParams &p, hipStream_t st, bool bt);
+int wave_launch(int shape, const IgemmParams &p, hipStream_t st, bool bt, PlaneOut *planes = nullptr);
 
 // ---- prep.hip: re-packing for channel counts that are not a multiple of 8 ---------
 // Small-C (C <= 4) image packing: `pix` channels per pixel, explicit zero border, padded size Hp x Wp;
