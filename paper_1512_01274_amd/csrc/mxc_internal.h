@@ -53,6 +53,18 @@ __device__ __forceinline__ float load_f32(const bf16_t *p) { return bf16_to_f32(
 __device__ __forceinline__ void store_f32(float *p, float v) { *p = v; }
 __device__ __forceinline__ void store_f32(bf16_t *p, float v) { *p = f32_to_bf16(v); }
 
+// Order of a launch's tiles.  Each XCD, whose L2 is its own, gets `share` tiles that follow each other: what they read between
+// them is least when the tiles that share the larger operand's rows are neighbours.  bm, bn: what a tile reads of either operand.  True:
+// the row tiles of a column follow each other, which has to save a quarter (5850 pixels, 112 columns, 5x5 on 176 channels, near the
+// tie: 16.6 us with the column tiles together, 17.9 with the row tiles).
+inline bool rows_inner(long long share, long long m_tiles, double bm, long long n_tiles, double bn)
+{
+    const auto read = [&](long long inner, double inner_rows, double outer_rows) {
+        return share >= inner ? inner * inner_rows + (share + inner - 1) / inner * outer_rows : share * inner_rows + outer_rows;
+    };
+    return read(m_tiles, bm, bn) < 0.75 * read(n_tiles, bn, bm);
+}
+
 // What the kernel that produces a result applies to it before the store (the grouped forms of the
 // convolution: see mxc_conv2d_fwd_bias_act / mxc_conv2d_bwd_data_relu).  Default: nothing.
 struct PostOp {

@@ -47,7 +47,8 @@ struct WaveParams {
     int mul_h, mul_w, off_h, off_w;   // input position of tap 0: grid position * mul + off
     int ts_magic, TS, tap_h, tap_w, th2, tv2;      // taps: divisor of the tap index, steps in pixels and in bytes
     int row_inner;                    // tap t = (column step)*TR + (row step)
-    FastDiv by_ntiles, by_mw, by_mh, by_ci;
+    FastDiv by_inner, by_mw, by_mh, by_ci;
+    int rows_inner;                   // the tiles of a column follow each other, not those of a row
     int kq, kr;                       // a wave's step of KG*32 reduction elements as taps + channels
     int linear_out, Ho, Wo, out_mul_h, out_mul_w, out_off_h, out_off_w;
     int relu, bt_row2;                // bt_row2: bytes from tap to tap of a transposed filter
@@ -83,12 +84,12 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int kg = wave % KG, mg = wave / KG;
     bf16_t *mine = ring + wave * RING;
-    // consecutive workgroups go round-robin to the 8 XCDs; each XCD gets a contiguous range of tiles, column tile fastest
+    // consecutive workgroups go round-robin to the 8 XCDs; each XCD gets a contiguous range of tiles
     const int per_xcd = (p.units + 7) / 8;
     const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (unit >= p.units) return;
-    const int m_tile = p.by_ntiles.div(unit);
-    const int n0 = (unit - m_tile * p.by_ntiles.d) * BN, m0 = m_tile * BM + mg * 16 * MB;
+    const int outer = p.by_inner.div(unit), inner = unit - outer * p.by_inner.d;
+    const int n0 = (p.rows_inner ? outer : inner) * BN, m0 = (p.rows_inner ? inner : outer) * BM + mg * 16 * MB;
 
     const buf_rsrc_t rs_in = make_buf_rsrc(p.in, p.in_bytes);
     const buf_rsrc_t rs_wm = make_buf_rsrc(p.wm, p.wm_bytes);
@@ -446,7 +447,11 @@ int launch(WaveParams &p, int step, bool bt, hipStream_t st)
     const int n_tiles = (p.Co + 16 * NB - 1) / (16 * NB);
     if (m_tiles * n_tiles > 0x3FFFFFFFll || m_tiles * 16 * MB * MG > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
     p.units = (int)(m_tiles * n_tiles);
-    p.by_ntiles = FastDiv(n_tiles);
+    // A pixel's channels are read by all its taps, a filter row T times as long by one tile of columns.  Column tiles followed each other
+    // before: 128 x 4096 to 1000 classes 11.9 us, now 7.1 (each XCD read all of the filter); 8x7x7 512 to 512 3x3 forward 11.4 -> 8.6,
+    // dx 15.0 -> 10.1.
+    p.rows_inner = rows_inner((p.units + 7) / 8, m_tiles, 16.0 * MB * MG * (p.T > 1 ? 2 : 1), n_tiles, 16.0 * NB * p.T);
+    p.by_inner = FastDiv(p.rows_inner ? (int)m_tiles : n_tiles);
     p.turns = (p.Kd + 32 * KG * U - 1) / (32 * KG * U);
     p.kq = 32 * KG / p.Ci; p.kr = 32 * KG % p.Ci;
     if constexpr (NB >= 2) {

@@ -40,7 +40,8 @@ struct DwParams {
     int hw_lim, px2, row2, img2, stride, pad;
     int P, Q;
     int adv_q, adv_p, adv_n;    // KG*32 pixels further
-    FastDiv by_tiles, by_ntiles, by_q, by_p, by_run, by_ts;
+    int rows_inner;                  // (see rows_inner)
+    FastDiv by_tiles, by_inner, by_q, by_p, by_run, by_ts;
     int mapped, dw_bf16;        // the result is dw: `map` says where an element belongs
     DwMap map;
 };
@@ -68,8 +69,8 @@ __global__ __launch_bounds__(64 * KG) void wave_dw_kernel(const DwParams p)
     const int per_xcd = (p.units + 7) / 8;
     const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (unit >= p.units) return;
-    const int z = p.by_tiles.div(unit), tile = unit - z * p.tiles, kt = p.by_ntiles.div(tile);
-    const int k0 = kt * 16 * MB, n0 = (tile - kt * p.by_ntiles.d) * 16 * NB;
+    const int z = p.by_tiles.div(unit), tile = unit - z * p.tiles, outer = p.by_inner.div(tile), inner = tile - outer * p.by_inner.d;
+    const int k0 = (p.rows_inner ? inner : outer) * 16 * MB, n0 = (p.rows_inner ? outer : inner) * 16 * NB;
     const int m_lo = z * p.span, m_end = min(m_lo + p.span, p.M);
     const int turns = (m_end - m_lo + 32 * KG * U - 1) / (32 * KG * U);
 
@@ -307,7 +308,8 @@ int wave_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const vo
     p.K = g.K; p.ncols = g.TR * g.TS * g.run; p.rows = rows;
     p.span = span;
     const int n_tiles = (p.ncols + 16 * s.nb - 1) / (16 * s.nb);
-    const long long tiles = (long long)((g.K + 16 * s.mb - 1) / (16 * s.mb)) * n_tiles;
+    const int k_tiles = (g.K + 16 * s.mb - 1) / (16 * s.mb);
+    const long long tiles = (long long)k_tiles * n_tiles;
     if (tiles * ranges > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
     p.tiles = (int)tiles; p.units = (int)(tiles * ranges);
     p.x_bytes = (unsigned)((long long)g.N * g.H * g.W * g.pix * 2);
@@ -317,7 +319,10 @@ int wave_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const vo
     p.stride = g.stride; p.pad = g.pad; p.P = g.P; p.Q = g.Q;
     const int adv = 32 * s.kg, rows_adv = adv / g.Q;
     p.adv_q = adv % g.Q; p.adv_p = rows_adv % g.P; p.adv_n = rows_adv / g.P;
-    p.by_tiles = FastDiv(p.tiles); p.by_ntiles = FastDiv(n_tiles); p.by_q = FastDiv(g.Q); p.by_p = FastDiv(g.P);
+    // (several ranges: an XCD has all tiles of one, and either order reads the same)
+    const int taps = g.TR * g.TS;
+    p.rows_inner = ranges == 1 && rows_inner((p.units + 7) / 8, k_tiles, 16.0 * s.mb, n_tiles, 16.0 * s.nb * (taps > 1 ? 2.0 / taps : 1.0));      // the taps share x
+    p.by_tiles = FastDiv(p.tiles); p.by_inner = FastDiv(p.rows_inner ? k_tiles : n_tiles); p.by_q = FastDiv(g.Q); p.by_p = FastDiv(g.P);
     p.by_run = FastDiv(g.run); p.by_ts = FastDiv(g.TS);
     p.mapped = map != nullptr; p.dw_bf16 = dw_bf16;
     if (map) p.map = *map;
