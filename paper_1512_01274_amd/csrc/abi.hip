@@ -339,7 +339,8 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
         // a filter the kernel reads in place stays where it is unless the caller keeps a prepared copy
         const void *in_place = nullptr;
         if (bwd_data_reads_filter_in_place(s)) in_place = mode == FILTER_RAW ? w : wt;
-        else if (mode == FILTER_RAW && (!kcrs || s.R * s.S == 1) && bwd_data_small_in_place(s, post.mask != nullptr)) in_place = w;
+        else if (mode == FILTER_RAW && (!kcrs || s.R * s.S == 1) &&
+                 (bwd_data_small_in_place(s, post.mask != nullptr) || bwd_data_classes_in_place(s, post.mask != nullptr))) in_place = w;
         if (prep && !(in_place != nullptr && mode == FILTER_RAW)) MXC_TRY(igemm_bwd_data_prepare(s, w, wt, st, mode == FILTER_PREPARE_ONLY, kcrs));
         if (!run) return MXC_OK;
         const int rc = igemm_bwd_data(s, dy, in_place, dx, wt, st, &v, post, split_ws);

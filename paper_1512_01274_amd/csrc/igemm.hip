@@ -1314,6 +1314,34 @@ bool bwd_data_small_in_place(const ConvShape &s, bool masked)
     return 2.0 * M * s.C * Kd < 1e10;
 }
 
+// The wave kernel's shape that runs dx of a layer of stride 2, all residue classes in one launch that reads the KRSC filter as it is, or -1:
+// re-packed filter, tile kernel and zeros, each its own launch.  Of 160 layers it is chosen in 125 and runs those 1.80 times as
+// fast (none more than 3% slower): 9x10x10 128 to 128 channels 3x3 12.5 -> 4.7 us, 3x20x10 416 to 384 5x5 42.1 -> 11.6.  The margin is
+// larger from 10 modelled us on (30x49x49 128 to 352 1x1: 21.3 against 14.6).
+static int classes_wave(const ConvShape &s, bool masked)
+{
+    if (s.stride != 2 || s.C % 8 != 0) return -1;
+    if (const char *f = getenv("MXC_FORCE_VARIANT")) {
+        const int wv = wave_forced(f, true);
+        return wv >= 0 && wave_has_classes(wv) ? wv : -1;
+    }
+    struct Entry { ConvShape s; int flags, wave; };
+    static thread_local Entry cache[32] = {};
+    const int flags = masked ? 2 : 1;
+    Entry &e = cache[(unsigned)(s.N * 31 + s.H * 13 + s.W * 11 + s.C * 7 + s.K * 3 + s.R + flags) % 32];
+    if (e.flags != flags || memcmp(&e.s, &s, sizeof s)) {
+        double us = 0, other = 0;
+        const int wv = (long long)s.N * s.H * s.W <= 1 << 30 ? wave_best_classes(s, masked, &us, &other) : -1;
+        e.s = s; e.flags = flags;
+        e.wave = wv >= 0 && us < (us < 10 ? 0.8 : 0.6) * other ? wv : -1;
+    }
+    return e.wave;
+}
+bool bwd_data_classes_in_place(const ConvShape &s, bool masked)
+{
+    return real_c(s) == s.C && real_k(s) == s.K && classes_wave(s, masked) >= 0;
+}
+
 // whether dx of an NCHW problem, its filter re-packed, goes straight to its planes (see PlaneOut)
 bool igemm_bwd_data_planes(const ConvShape &s, bool masked)
 {
@@ -1359,6 +1387,11 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
         *variant = plan_name(pl);
         if (sp > 1) return launch_split(pl.main, p, M, sp, split_ws, dx, post, st, variant, bt);
         return launch_plan(pl, p, st, bt);
+    }
+    if (const int wv = classes_wave(s, p.mask != nullptr); wv >= 0) {
+        p.wm = (const bf16_t *)(bt ? w_in_place : wt);
+        *variant = wave_name(wv);
+        return wave_launch_classes(wv, s, p, st, bt);
     }
     IgemmClasses q{};
     bool zeros = false;

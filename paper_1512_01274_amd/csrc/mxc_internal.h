@@ -361,6 +361,7 @@ int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStrea
 bool bwd_data_reads_filter_in_place(const ConvShape &s);
 // ... or reads the KRSC filter it is handed in place although its prepared form is the re-packed one
 bool igemm_bwd_data_planes(const ConvShape &s, bool masked);
+bool bwd_data_classes_in_place(const ConvShape &s, bool masked);       // whether strided dx reads the KRSC filter itself
 bool bwd_data_small_in_place(const ConvShape &s, bool masked);
 int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, void *dx, const void *wt, hipStream_t st,
                    const char **variant, const PostOp &post = PostOp(), void *split_ws = nullptr);
@@ -470,6 +471,10 @@ const char *wave_name(int shape);
 int wave_forced(const char *name, bool bwd);
 int wave_best(long long M, int Co, int Kd, bool bwd, bool masked, double *us);
 int wave_launch(int shape, const IgemmParams &p, hipStream_t st, bool bt, PlaneOut *planes = nullptr);
+// dx of a layer of stride 2: bt: p.wm is the KRSC filter itself, else as igemm_bwd_data_prepare left it
+bool wave_has_classes(int shape);
+int wave_best_classes(const ConvShape &s, bool masked, double *us, double *other);
+int wave_launch_classes(int shape, const ConvShape &s, const IgemmParams &p, hipStream_t st, bool bt);
 
 // ---- prep.hip: re-packing for channel counts that are not a multiple of 8 ---------
 // Small-C (C <= 4) image packing: `pix` channels per pixel, explicit zero border, padded size Hp x Wp;

@@ -19,6 +19,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "mxc_internal.h"
 
 namespace mxc {
@@ -35,25 +37,37 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr unsigned OOB = 0x80000000u;   // a buffer offset no operand reaches: the load returns zeros
 constexpr int FAR = (-16384) & 0xFFFF;  // a packed position that is outside whatever is added to it
 
+// The output pixels of a launch, or of one residue class of strided backward-data: an Mh x Mw grid per image and its taps.
+struct WaveGrid {
+    FastDiv by_mw, by_mh;
+    int M, Kd, turns, TS, ts_magic;   // rows, reduction, a wave's sets of steps; taps: divisor of the tap index
+    int off_h, off_w;                 // input position of tap 0: grid position * mul + off
+    int out_off_h, out_off_w;
+    int tile0, tap0, tap_row, tap_col;        // classes: first row tile; class tap (j, q) is the filter's tap0 + j*tap_row + q*tap_col
+    unsigned wm_off;                  // bytes before the class's matrix in a re-packed filter
+};
 struct WaveParams {
     const bf16_t *in, *wm;
     bf16_t *out;
     const float *bias;
     const bf16_t *mask;
     unsigned in_bytes, wm_bytes;
-    int units, M, Co, Cw, Ci, Kd, T, turns;
+    WaveGrid grid;
+    int units, Co, Cw, Ci, T;         // T: taps of the filter
     int hw_lim;                       // last row and column of the image, packed
     int px2, row2, img2;              // bytes from pixel to pixel, row to row, image to image
-    int mul_h, mul_w, off_h, off_w;   // input position of tap 0: grid position * mul + off
-    int ts_magic, TS, tap_h, tap_w, th2, tv2;      // taps: divisor of the tap index, steps in pixels and in bytes
+    int mul_h, mul_w;
+    int tap_h, tap_w, th2, tv2;       // a tap's steps in pixels and in bytes
     int row_inner;                    // tap t = (column step)*TR + (row step)
-    FastDiv by_inner, by_mw, by_mh, by_ci;
+    FastDiv by_inner, by_ci;
     int rows_inner;                   // the tiles of a column follow each other, not those of a row
     int kq, kr;                       // a wave's step of KG*32 reduction elements as taps + channels
-    int linear_out, Ho, Wo, out_mul_h, out_mul_w, out_off_h, out_off_w;
-    int relu, bt_row2;                // bt_row2: bytes from tap to tap of a transposed filter
+    int linear_out, Ho, Wo, out_mul_h, out_mul_w;
+    int relu;
     int cols;                         // PLANES: the result's planes per image
 };
+constexpr int MAX_CLASSES = 4;
+struct WaveClassParams : WaveParams { WaveGrid cls[MAX_CLASSES]; int n_cls; };
 
 // How a step's 32 reduction elements lie: anyhow; in one tap, the same for all lanes (Ci % 32 == 0: the tap arithmetic is
 // scalar); or there is one tap and every pixel is inside the image (a 1x1 filter without padding, Ci % 32 == 0 too).
@@ -67,8 +81,8 @@ __device__ __forceinline__ void wait_lgkmcnt0() { asm volatile("s_waitcnt lgkmcn
 // PLANES: the operands are NHWC copies of an NCHW problem and the result goes straight to its planes: the product is formed the other
 // way round, lane 16*g + i holds pixels 4*g .. 4*g + 3 of column i.  One launch and one pass over the result less (us, forward
 // and dx): 32 to 32 channels 3x3 on 4 20x20 images 8.2 -> 6.0, 9.4 -> 7.3; 96 to 128 1x1 on 64 14x14 13.3 -> 9.1, 14.3 -> 10.9.
-template <int MB, int NB, int KG, int MG, int U, int NS, bool BT, int STEP, bool PLANES>
-__global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
+template <int MB, int NB, int KG, int MG, int U, int NS, bool BT, int STEP, bool PLANES, bool CLASSES>
+__global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const std::conditional_t<CLASSES, WaveClassParams, WaveParams> p)
 {
     constexpr int BM = 16 * MB * MG, BN = 16 * NB, NW = KG * MG;
     constexpr int BLK = 512;                                        // elements of a block: 16 rows x 32
@@ -89,7 +103,17 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
     const int unit = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (unit >= p.units) return;
     const int outer = p.by_inner.div(unit), inner = unit - outer * p.by_inner.d;
-    const int n0 = (p.rows_inner ? outer : inner) * BN, m0 = (p.rows_inner ? inner : outer) * BM + mg * 16 * MB;
+    const int n0 = (p.rows_inner ? outer : inner) * BN;
+    int m_tile = p.rows_inner ? inner : outer;
+    const WaveGrid *grid = &p.grid;
+    if constexpr (CLASSES) {
+        int c = 0;
+        while (c + 1 < p.n_cls && m_tile >= p.cls[c + 1].tile0) ++c;
+        grid = &p.cls[c];
+        m_tile -= grid->tile0;
+    }
+    const WaveGrid &gr = *grid;
+    const int m0 = m_tile * BM + mg * 16 * MB;
 
     const buf_rsrc_t rs_in = make_buf_rsrc(p.in, p.in_bytes);
     const buf_rsrc_t rs_wm = make_buf_rsrc(p.wm, p.wm_bytes);
@@ -100,10 +124,10 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
         const int m = m0 + 16 * b + ld_row;
-        const int t = p.by_mw.div(m), col = m - t * p.by_mw.d, n = p.by_mh.div(t), row = t - n * p.by_mh.d;
-        const int h = row * p.mul_h + p.off_h, w = col * p.mul_w + p.off_w;
+        const int t = gr.by_mw.div(m), col = m - t * gr.by_mw.d, n = gr.by_mh.div(t), row = t - n * gr.by_mh.d;
+        const int h = row * p.mul_h + gr.off_h, w = col * p.mul_w + gr.off_w;
         a_off[b] = n * p.img2 + h * p.row2 + w * p.px2;
-        a_hw[b] = m < p.M ? (h & 0xFFFF) | (w << 16) : FAR;
+        a_hw[b] = m < gr.M ? (h & 0xFFFF) | (w << 16) : FAR;
     }
     if constexpr (STEP == STEP_1X1) {
 #pragma unroll
@@ -127,7 +151,7 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const int co = n0 + 16 * j + ld_row;
-            f_off[j] = co < p.Cw ? ((unsigned)co * (unsigned)p.Kd + (unsigned)in_off) * 2u : OOB;
+            f_off[j] = co < p.Cw ? ((unsigned)co * (unsigned)gr.Kd + (unsigned)in_off) * 2u + (CLASSES ? gr.wm_off : 0u) : OOB;
         }
     }
     // BT: (tap, k) of the lane's filter rows: row k0 + BROWS*j + bt_r of the step.  With whole steps per tap the tap is the step's.
@@ -136,14 +160,14 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
     auto issue = [&](bf16_t *dst) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool k_ok = kd < p.Kd;
+            const bool k_ok = kd < gr.Kd;
             bf16_t *to = dst + u * (MB + NB) * BLK;
             if constexpr (STEP == STEP_1X1) {
                 // (an offset beyond the resource stays there: kd*2 < 2^31)
 #pragma unroll
                 for (int b = 0; b < MB; ++b) lds_dma16(rs_in, k_ok ? (unsigned)a_off[b] + (unsigned)kd * 2u : OOB, to + b * BLK);
             } else {
-                const int q = small_div(tap, p.ts_magic), rem = tap - q * p.TS;
+                const int q = small_div(tap, gr.ts_magic), rem = tap - q * gr.TS;
                 const int th = p.row_inner ? rem : q, tv = p.row_inner ? q : rem;
                 const int t_hw = k_ok ? (th * p.tap_h & 0xFFFF) | (tv * p.tap_w) << 16 : FAR;
                 const int base = th * p.th2 + tv * p.tv2 + ci * 2 + in_off * 2;
@@ -157,13 +181,18 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
             }
             if constexpr (BT) {
                 // filter row (k, tap) lies at (k*T + tap)*Co
+                auto filter_tap = [&](int t) __attribute__((always_inline)) {
+                    if constexpr (!CLASSES) return t;
+                    const int q = small_div(t, gr.ts_magic);
+                    return gr.tap0 + q * gr.tap_row + (t - q * gr.TS) * gr.tap_col;
+                };
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
                     const int at = bt_kd + BROWS * j + bt_r;                   // reduction element of this lane's row
                     int t = 0, k = at;
                     if constexpr (STEP == STEP_TAP) { t = tap; k = ci + BROWS * j + bt_r; }
                     if constexpr (STEP == STEP_ANY) { t = p.by_ci.div(at); k = at - t * p.Ci; }
-                    lds_dma16(rs_wm, at < p.Kd && f_off[j] != OOB ? f_off[j] + (unsigned)(k * p.T + t) * (unsigned)(p.Co * 2) : OOB,
+                    lds_dma16(rs_wm, at < gr.Kd && f_off[j] != OOB ? f_off[j] + (unsigned)(k * p.T + filter_tap(t)) * (unsigned)(p.Co * 2) : OOB,
                               to + (MB + j) * BLK);
                 }
             } else {
@@ -228,14 +257,14 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
                                              : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[u][j], fa[u][b], acc[b][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
-    // p.turns sets, of which the last NS are not followed by a refill.  Loads retire in order, so all but the youngest (NS - 1)*L
+    // gr.turns sets, of which the last NS are not followed by a refill.  Loads retire in order, so all but the youngest (NS - 1)*L
     // being done means that the oldest set has landed.
-    const int ahead = min(p.turns, NS);
+    const int ahead = min(gr.turns, NS);
 #pragma unroll
     for (int q = 0; q < NS; ++q)
         if (q < ahead) issue(mine + q * SET);
     int slot = 0;
-    for (int t = p.turns; t > NS; --t) {
+    for (int t = gr.turns; t > NS; --t) {
         wait_vmcnt<L * (NS - 1)>();
         step(mine + slot * SET, true);
         slot = slot + 1 == NS ? 0 : slot + 1;
@@ -260,11 +289,11 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
     // of blocks j and j + 1, 16 bytes leave as columns n0 + col16(j) .. + 7: the lanes of odd g take block j + 1
     auto col16 = [&](int j) __attribute__((always_inline)) { return 16 * (j + (g & 1)) + 8 * (g >> 1); };
     // PLANES: pixels m0 + 16*b + 4*g .. + 3, element 0's place in the first plane of its image, or -1
-    const int plane = PLANES ? p.by_mw.d * p.by_mh.d : 0;
+    const int plane = PLANES ? gr.by_mw.d * gr.by_mh.d : 0;
     int pix = 0;
-    auto image_of = [&](int m) __attribute__((always_inline)) { return p.by_mh.div(p.by_mw.div(m)); };
+    auto image_of = [&](int m) __attribute__((always_inline)) { return gr.by_mh.div(gr.by_mw.div(m)); };
     auto store_planes = [&](const f32x4 (&v)[NB]) __attribute__((always_inline)) {
-        if (pix >= p.M) return;
+        if (pix >= gr.M) return;
         const bool quad = (plane & 3) == 0;            // (then the four are of one image, and lie on 8 bytes)
         const int n0_img = image_of(pix), n3_img = quad ? n0_img : image_of(pix + 3);
 #pragma unroll
@@ -290,7 +319,7 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int m = pix + e, n = n0_img == n3_img ? n0_img : image_of(m);
-                if (m >= p.M) break;
+                if (m >= gr.M) break;
                 const long long to = ((long long)n * p.cols + col) * plane + (m - n * plane);
                 const bf16_t r = (bf16_t)(k[e >> 1] >> ((e & 1) * 16));
                 p.out[to] = (p.mask == nullptr || mask_keeps(p.mask + to)) ? r : (bf16_t)0;
@@ -306,10 +335,10 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const WaveParams p)
         const int m = m0 + 16 * b + i;
         at = (long long)m * p.Co + n0;
         if (!p.linear_out) {
-            const int t = p.by_mw.div(m), col = m - t * p.by_mw.d, n = p.by_mh.div(t), row = t - n * p.by_mh.d;
-            at = (((long long)n * p.Ho + (row * p.out_mul_h + p.out_off_h)) * p.Wo + (col * p.out_mul_w + p.out_off_w)) * p.Co + n0;
+            const int t = gr.by_mw.div(m), col = m - t * gr.by_mw.d, n = gr.by_mh.div(t), row = t - n * gr.by_mh.d;
+            at = (((long long)n * p.Ho + (row * p.out_mul_h + gr.out_off_h)) * p.Wo + (col * p.out_mul_w + gr.out_off_w)) * p.Co + n0;
         }
-        if (m >= p.M) at = -1;
+        if (m >= gr.M) at = -1;
         if (whole && p.mask != nullptr) {
 #pragma unroll
             for (int j = 0; j < NB; j += 2)
@@ -430,20 +459,47 @@ struct WaveShape { int mb, nb, kg, mg, u, ns; const char *name; float fixed, kb,
 const WaveShape kShapes[] = {SHAPES(X)};
 #undef X
 constexpr int N_SHAPES = sizeof(kShapes) / sizeof(kShapes[0]);
+// those that strided backward-data is built in
+#define CLASS_SHAPES(X) X(2, 2, 2, 8, 1, 1, 4) X(3, 4, 2, 8, 1, 1, 3) X(5, 4, 2, 4, 2, 1, 3) X(7, 2, 2, 1, 4, 1, 2) X(8, 2, 4, 1, 4, 1, 2)
+static bool has_classes(int shape) { return shape == 2 || shape == 3 || shape == 5 || shape == 7 || shape == 8; }
 
 template <int MB, int NB, int KG, int MG, int U, int NS, bool BT, bool PLANES>
 void launch_step(const WaveParams &p, int step, hipStream_t st)
 {
     const dim3 grid((unsigned)((p.units + 7) / 8 * 8)), block(64 * KG * MG);
-    if (step == STEP_1X1) hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, BT, STEP_1X1, PLANES>), grid, block, 0, st, p);
-    else if (step == STEP_TAP) hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, BT, STEP_TAP, PLANES>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, BT, STEP_ANY, PLANES>), grid, block, 0, st, p);
+    if (step == STEP_1X1) hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, BT, STEP_1X1, PLANES, false>), grid, block, 0, st, p);
+    else if (step == STEP_TAP) hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, BT, STEP_TAP, PLANES, false>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, BT, STEP_ANY, PLANES, false>), grid, block, 0, st, p);
+}
+
+// strided backward-data: all residue classes in one launch, those no tap reaches with a reduction of nothing
+template <int MB, int NB, int KG, int MG, int U, int NS>
+int launch_classes(WaveClassParams &p, bool bt, hipStream_t st)
+{
+    long long m_tiles = 0;
+    for (int c = 0; c < p.n_cls; ++c) {
+        p.cls[c].tile0 = (int)m_tiles;
+        p.cls[c].turns = (p.cls[c].Kd + 32 * KG * U - 1) / (32 * KG * U);
+        m_tiles += ((long long)p.cls[c].M + 16 * MB * MG - 1) / (16 * MB * MG);
+    }
+    const int n_tiles = (p.Co + 16 * NB - 1) / (16 * NB);
+    if (m_tiles * n_tiles > 0x3FFFFFFFll || m_tiles * 16 * MB * MG > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
+    p.units = (int)(m_tiles * n_tiles);
+    p.by_inner = FastDiv(n_tiles);
+    p.kq = 32 * KG / p.Ci; p.kr = 32 * KG % p.Ci;
+    const dim3 grid((unsigned)((p.units + 7) / 8 * 8)), block(64 * KG * MG);
+    const bool tap = p.Ci % 32 == 0;
+    if (bt && tap) hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, true, STEP_TAP, false, true>), grid, block, 0, st, p);
+    else if (bt) hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, true, STEP_ANY, false, true>), grid, block, 0, st, p);
+    else if (tap) hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, false, STEP_TAP, false, true>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((wave_kernel<MB, NB, KG, MG, U, NS, false, STEP_ANY, false, true>), grid, block, 0, st, p);
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
 template <int MB, int NB, int KG, int MG, int U, int NS>
 int launch(WaveParams &p, int step, bool bt, hipStream_t st)
 {
-    const long long m_tiles = ((long long)p.M + 16 * MB * MG - 1) / (16 * MB * MG);
+    const long long m_tiles = ((long long)p.grid.M + 16 * MB * MG - 1) / (16 * MB * MG);
     const int n_tiles = (p.Co + 16 * NB - 1) / (16 * NB);
     if (m_tiles * n_tiles > 0x3FFFFFFFll || m_tiles * 16 * MB * MG > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
     p.units = (int)(m_tiles * n_tiles);
@@ -452,7 +508,7 @@ int launch(WaveParams &p, int step, bool bt, hipStream_t st)
     // dx 15.0 -> 10.1.
     p.rows_inner = rows_inner((p.units + 7) / 8, m_tiles, 16.0 * MB * MG * (p.T > 1 ? 2 : 1), n_tiles, 16.0 * NB * p.T);
     p.by_inner = FastDiv(p.rows_inner ? (int)m_tiles : n_tiles);
-    p.turns = (p.Kd + 32 * KG * U - 1) / (32 * KG * U);
+    p.grid.turns = (p.grid.Kd + 32 * KG * U - 1) / (32 * KG * U);
     p.kq = 32 * KG / p.Ci; p.kr = 32 * KG % p.Ci;
     if constexpr (NB >= 2) {
         if (bt && p.cols == 0) launch_step<MB, NB, KG, MG, U, NS, true, false>(p, step, st);
@@ -491,26 +547,36 @@ int wave_best(long long M, int Co, int Kd, bool bwd, bool masked, double *us)
     return best;
 }
 
+// what the launches of all forms share
+static void fill_common(WaveParams &p, const IgemmParams &q)
+{
+    p.in = q.in; p.wm = q.wm; p.out = q.out; p.bias = q.bias; p.mask = q.mask; p.relu = q.relu;
+    p.Co = q.Co; p.Cw = q.Cw ? q.Cw : q.Co; p.Ci = q.Ci;
+    p.in_bytes = (unsigned)((long long)q.N * q.Hi * q.Wi * q.pix * 2);
+    p.hw_lim = ((q.Hi - 1) & 0xFFFF) | ((q.Wi - 1) << 16);
+    p.px2 = q.pix * 2; p.row2 = q.Wi * p.px2; p.img2 = q.Hi * p.row2;
+    p.mul_h = q.in_mul_h; p.mul_w = q.in_mul_w;
+    p.row_inner = q.tap_row_inner;
+    p.tap_h = q.tstep_h; p.tap_w = q.tstep_w;
+    p.th2 = q.tstep_h * p.row2; p.tv2 = q.tstep_w * p.px2;
+    p.by_ci = FastDiv(q.Ci);
+    p.Ho = q.Ho; p.Wo = q.Wo; p.out_mul_h = q.out_mul_h; p.out_mul_w = q.out_mul_w;
+}
+
 int wave_launch(int shape, const IgemmParams &q, hipStream_t st, bool bt, PlaneOut *planes)
 {
     WaveParams p{};
-    p.in = q.in; p.wm = q.wm; p.out = q.out; p.bias = q.bias; p.mask = q.mask; p.relu = q.relu;
-    p.M = (int)((long long)q.N * q.Mh * q.Mw);
-    p.Co = q.Co; p.Cw = q.Cw ? q.Cw : q.Co; p.Ci = q.Ci; p.T = q.TR * q.TS; p.Kd = p.T * q.Ci;
-    p.in_bytes = (unsigned)((long long)q.N * q.Hi * q.Wi * q.pix * 2);
-    p.wm_bytes = bt ? q.bt_w_bytes : (unsigned)((long long)p.Cw * p.Kd * 2);
-    p.hw_lim = ((q.Hi - 1) & 0xFFFF) | ((q.Wi - 1) << 16);
-    p.px2 = q.pix * 2; p.row2 = q.Wi * p.px2; p.img2 = q.Hi * p.row2;
-    p.mul_h = q.in_mul_h; p.mul_w = q.in_mul_w; p.off_h = q.in_off_h; p.off_w = q.in_off_w;
-    p.row_inner = q.tap_row_inner;
-    p.TS = q.tap_row_inner ? q.TR : q.TS;
-    p.ts_magic = small_magic(p.TS);
-    p.tap_h = q.tstep_h; p.tap_w = q.tstep_w;
-    p.th2 = q.tstep_h * p.row2; p.tv2 = q.tstep_w * p.px2;
-    p.by_mw = FastDiv(q.Mw); p.by_mh = FastDiv(q.Mh); p.by_ci = FastDiv(q.Ci);
+    fill_common(p, q);
+    p.T = q.TR * q.TS;
+    WaveGrid &gr = p.grid;
+    gr.M = (int)((long long)q.N * q.Mh * q.Mw);
+    gr.Kd = p.T * q.Ci;
+    gr.off_h = q.in_off_h; gr.off_w = q.in_off_w; gr.out_off_h = q.out_off_h; gr.out_off_w = q.out_off_w;
+    gr.TS = q.tap_row_inner ? q.TR : q.TS;
+    gr.ts_magic = small_magic(gr.TS);
+    gr.by_mw = FastDiv(q.Mw); gr.by_mh = FastDiv(q.Mh);
+    p.wm_bytes = bt ? q.bt_w_bytes : (unsigned)((long long)p.Cw * gr.Kd * 2);
     p.linear_out = (q.out_mul_h == 1 && q.out_mul_w == 1 && q.out_off_h == 0 && q.out_off_w == 0 && q.Mh == q.Ho && q.Mw == q.Wo) ? 1 : 0;
-    p.Ho = q.Ho; p.Wo = q.Wo; p.out_mul_h = q.out_mul_h; p.out_mul_w = q.out_mul_w; p.out_off_h = q.out_off_h; p.out_off_w = q.out_off_w;
-    p.bt_row2 = p.T * q.Co * 2;
     if (planes != nullptr && p.linear_out && !bt) {
         p.out = (bf16_t *)planes->out; p.mask = (const bf16_t *)planes->mask; p.cols = planes->cols;
         planes->stored = true;
@@ -520,6 +586,92 @@ int wave_launch(int shape, const IgemmParams &q, hipStream_t st, bool bt, PlaneO
     switch (shape) {
 #define X(I, MB, NB, KG, MG, U, NS, ...) case I: return launch<MB, NB, KG, MG, U, NS>(p, step, bt, st);
     SHAPES(X)
+#undef X
+    default: return MXC_ERR_UNSUPPORTED;
+    }
+}
+
+bool wave_has_classes(int shape) { return has_classes(shape); }
+
+// The residue classes of dx at stride 2, in the order (ph, pw): rows of the GEMM and the taps of each.
+struct ClassDims { int Mh, Mw, TR, TS, off_h, off_w, out_off_h, out_off_w; };
+static ClassDims class_dims(const ConvShape &s, int ph, int pw)
+{
+    ClassDims c{};
+    c.TR = ph < s.R ? (s.R - ph + s.stride - 1) / s.stride : 0; c.TS = pw < s.S ? (s.S - pw + s.stride - 1) / s.stride : 0;
+    // output rows h = ph - pad + stride*hh >= 0, h < H
+    c.off_h = ph >= s.pad ? 0 : (s.pad - ph + s.stride - 1) / s.stride;
+    c.off_w = pw >= s.pad ? 0 : (s.pad - pw + s.stride - 1) / s.stride;
+    c.out_off_h = ph - s.pad + s.stride * c.off_h; c.out_off_w = pw - s.pad + s.stride * c.off_w;
+    c.Mh = c.out_off_h < s.H ? (s.H - 1 - c.out_off_h) / s.stride + 1 : 0;
+    c.Mw = c.out_off_w < s.W ? (s.W - 1 - c.out_off_w) / s.stride + 1 : 0;
+    return c;
+}
+
+// The shape for dx at stride 2 and its modelled time (us, fitted to 160 layers of up to 20 GFLOP, 9-13% off): fixed + turn * (tiles times
+// steps per wave and CU, at least the longest class's) + longest * (the longest class's steps) + tile * (tiles per CU) + mb * (MB written and
+// of the mask read); and that of the re-packed filter, the tile kernel's launch over the classes and, for 1x1, the one of zeros (8% off).
+int wave_best_classes(const ConvShape &s, bool masked, double *us, double *other)
+{
+    static const struct { int shape; float fixed, turn, longest, tile, mb; } kUs[] = {
+        {2, 2.44f, 0.492f, 0.114f, 1.28f, 1.20f}, {3, 2.57f, 0.603f, 0.f, 1.34f, 1.00f}, {5, 2.71f, 0.538f, 0.f, 1.28f, 0.809f},
+        {7, 3.24f, 0.258f, 0.112f, 0.611f, 0.046f}, {8, 3.32f, 0.353f, 0.197f, 0.856f, 0.098f}};
+    const double mb = 2e-6 * s.N * s.H * s.W * s.C * (masked ? 2 : 1);
+    double gflop = 0, zeros = 0, longest = 0;
+    int best = -1;
+    for (const auto &u : kUs) {
+        const WaveShape &w = kShapes[u.shape];
+        const int bm = 16 * w.mb * w.mg, n_tiles = (s.C + 16 * w.nb - 1) / (16 * w.nb);
+        double tiles = 0, steps = 0, most = 0;
+        gflop = zeros = longest = 0;
+        for (int ph = 0; ph < s.stride; ++ph)
+            for (int pw = 0; pw < s.stride; ++pw) {
+                const ClassDims c = class_dims(s, ph, pw);
+                if (c.Mh <= 0 || c.Mw <= 0) continue;
+                const double rows = (double)s.N * c.Mh * c.Mw, t = (double)(long long)((rows + bm - 1) / bm);
+                const int Kd = c.TR * c.TS * s.K, turns = (Kd + 32 * w.kg - 1) / (32 * w.kg);
+                tiles += t * n_tiles / 256; steps += t * n_tiles * turns / 256;
+                if (turns > most) most = turns;
+                if (Kd > longest) longest = Kd;
+                gflop += 2e-9 * rows * Kd * ((s.C + 63) / 64 * 64);
+                if (Kd == 0) zeros += 2e-6 * rows * s.C;
+            }
+        const double t = u.fixed + u.turn * (steps > most ? steps : most) + u.longest * most + u.tile * (tiles > 1 ? tiles : 1) + u.mb * mb;
+        if (best < 0 || t < *us) { best = u.shape; *us = t; }
+    }
+    *other = 8.45 + 0.774 * gflop + 0.385 * mb + 0.127 * zeros + 0.00668 * longest + (s.R == 1 ? 0.2 : 0) + 0.52 * 2e-6 * s.K * s.C * s.R * s.S;
+    return best;
+}
+
+int wave_launch_classes(int shape, const ConvShape &s, const IgemmParams &q, hipStream_t st, bool bt)
+{
+    WaveClassParams p{};
+    fill_common(p, q);
+    p.T = s.R * s.S;
+    size_t wt_off = 0;
+    for (int ph = 0; ph < s.stride; ++ph)
+        for (int pw = 0; pw < s.stride; ++pw) {
+            const ClassDims c = class_dims(s, ph, pw);
+            WaveGrid g{};
+            g.off_h = c.off_h; g.off_w = c.off_w; g.out_off_h = c.out_off_h; g.out_off_w = c.out_off_w;
+            g.Kd = c.TR * c.TS * s.K;
+            g.wm_off = (unsigned)(wt_off * 2);
+            wt_off += (size_t)s.C * g.Kd;
+            if (c.Mh <= 0 || c.Mw <= 0) continue;
+            g.M = s.N * c.Mh * c.Mw;
+            g.by_mw = FastDiv(c.Mw); g.by_mh = FastDiv(c.Mh);
+            g.TS = c.TS > 0 ? c.TS : 1;
+            g.ts_magic = small_magic(g.TS);
+            g.tap0 = ph * s.S + pw; g.tap_row = s.stride * s.S; g.tap_col = s.stride;
+            // most taps first: the longest reductions start first
+            int at = p.n_cls++;
+            for (; at > 0 && p.cls[at - 1].Kd < g.Kd; --at) p.cls[at] = p.cls[at - 1];
+            p.cls[at] = g;
+        }
+    p.wm_bytes = bt ? (unsigned)((long long)s.K * s.R * s.S * s.C * 2) : (unsigned)(wt_off * 2);
+    switch (shape) {
+#define X(I, MB, NB, KG, MG, U, NS) case I: return launch_classes<MB, NB, KG, MG, U, NS>(p, bt, st);
+    CLASS_SHAPES(X)
 #undef X
     default: return MXC_ERR_UNSUPPORTED;
     }
