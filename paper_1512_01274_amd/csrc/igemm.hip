@@ -99,7 +99,7 @@ struct GridPos {
 // share a CU.
 // BT = true: the filter operand is read transposed, straight from w[K][Co] (1x1 filters): its LDS tile is
 // [reduction row][BN output columns] and its MFMA fragments come from ds_read_b64_tr_b16.
-// TI = true: channel-block-major reduction order (needs Ci % BKT == 0); a compile-time choice so that the
+// TI = true: channel-block-major reduction order (see tap_inner_order); a compile-time choice so that the
 // stage body is one basic block and the pinned interleave of address work and MFMAs survives.
 // Runs the output tile whose first row is m0 and first column n0 (split_z: its share of a split reduction).
 template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT, bool TI>
@@ -155,7 +155,7 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
 
     const int T = p.TR * p.TS;
     const int Kd = T * p.Ci;
-    const int KT = (Kd + BKT - 1) / BKT;
+    const int KT = TI ? T * ((p.Ci + BKT - 1) / BKT) : (Kd + BKT - 1) / BKT;
 
     // ---- tap table -------------------------------------------------------------------------------
     // Entry T is a sentinel whose row offset lies far outside any image: every chunk past the end
@@ -227,9 +227,11 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
     int kd2 = kd0 * 2;                             // byte offset within a filter row
     int ci2 = (kd0 % p.Ci) * 2, tap = kd0 / p.Ci;
     if constexpr (TI) {                            // stage s = (channel block s / T, tap s % T)
-        tap = k_lo % T;
         ci2 = (k_lo / T) * (BKT * 2) + ld_chunk * 16;
+        tap = ci2 < Ci2 ? k_lo % T : T;            // past the channels of a last block that is not whole: the sentinel tap
     }
+    // BT in that order: the stage's tap and first channel (a lane's own `tap` follows the chunk it brings of the other operand)
+    [[maybe_unused]] int bt_t = TI ? k_lo % T : 0, bt_c0 = TI ? k_lo / T * BKT : 0;
     const int lim_hw = ((p.Hi - 1) & 0xFFFF) | ((p.Wi - 1) << 16);
     // BT, tap-major order: (tap, k) of this lane's filter rows in the next stage
     [[maybe_unused]] int bt_tap[B_LD], bt_k[B_LD];
@@ -276,10 +278,13 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
                 // Order (channel block, tap): the pixels a workgroup reads for one channel block serve all
                 // its taps back to back, so they are still in the XCD's L2 when the next tap asks for them.
                 if constexpr (BT) {
-                    const bool ok = bt_col_ok && tap < T;
-                    const unsigned base = (unsigned)((ci2 - ld_chunk * 16) / 2 * T + tap) * (unsigned)(p.Co * 2);
+                    const unsigned base = (unsigned)(bt_c0 * T + bt_t) * (unsigned)(p.Co * 2);
+                    const int rows = p.Ci - bt_c0;                // of the block that are there: none past the last block
 #pragma unroll
-                    for (int i = 0; i < B_LD; ++i) vb[i] = ok ? b_off[i] + base : OOB;
+                    for (int i = 0; i < B_LD; ++i) vb[i] = bt_col_ok && RPLB * (wave + NW * i) + lb_sub < rows ? b_off[i] + base : OOB;
+                    const bool wrap = bt_t + 1 >= T;
+                    bt_t = wrap ? 0 : bt_t + 1;
+                    bt_c0 += wrap ? BKT : 0;
                 } else {
                     const bool k_ok = tap < T;
                     const unsigned kd = (unsigned)(tap * Ci2 + ci2);
@@ -687,6 +692,22 @@ __global__ __launch_bounds__(64 * WR * WC, (tile_min_blocks<BM, BN, BKT, NS, WR,
 }
 
 // the kernel's row steps: from load to load of a wave, and from store to store (64 lanes of 16 bytes over the wave's columns)
+// Whether the reduction runs over all taps of a block of bk channels before the next block: what the tiles of an XCD read of
+// a block then stays in its L2 from tap to tap.  Where the last block is not whole its empty chunks cost stages, which narrow tiles
+// of many channels repay (94864 pixels, 400 to 32 channels 3x3 94.9 -> 66.4 us, 151230, 288 to 32 5x5 240 -> 156, 20480, 352 to 24
+// 5x5 53.4 -> 38.9): their many workgroups read the same pixels T times, and all channels of those do not fit the L2.  Wider tiles
+// gain nothing, small problems fit it anyway (3969 pixels, 400 to 440: 65.9 against 69.6).
+const bool tap_outer_forced = getenv("MXC_TAP_OUTER") != nullptr;       // tuning sweeps only; read once
+inline bool tap_inner_order(int T, int Ci, int bk, int bn, long long M)
+{
+    if (T == 1 || tap_outer_forced) return false;
+    return Ci % bk == 0 || (bn <= 64 && Ci >= 256 && M >= 1 << 14 && (Ci + bk - 1) / bk * bk <= Ci * 1.15);
+}
+inline int stages_of(int T, int Ci, int bk, int bn, long long M)
+{
+    return tap_inner_order(T, Ci, bk, bn, M) ? T * ((Ci + bk - 1) / bk) : (T * Ci + bk - 1) / bk;
+}
+
 template <int BN, int BKT, int WR, int WC>
 void set_steps(RowStep &in, RowStep &out, int Mh, int Mw)
 {
@@ -699,7 +720,6 @@ void set_steps(RowStep &in, RowStep &out, int Mh, int Mw)
 template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT = false>
 int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end = -1)
 {
-    static const bool tap_outer_forced = getenv("MXC_TAP_OUTER") != nullptr;   // tuning sweeps only; read once
     const long long M = (long long)p.N * p.Mh * p.Mw;
     if (m_end < 0 || m_end > M) m_end = M;
     if (m_begin >= m_end) return MXC_OK;
@@ -714,8 +734,7 @@ int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end
     p.in_bytes = (unsigned)((long long)p.N * p.Hi * p.Wi * p.pix * 2);
     if (p.Cw == 0) p.Cw = p.Co;
     p.wm_bytes = BT ? p.bt_w_bytes : (unsigned)((long long)p.Cw * p.TR * p.TS * p.Ci * 2);
-    // MXC_TAP_OUTER=1 (tuning only) keeps the filter's own order, all channels of a tap before the next tap
-    p.tap_inner = (p.Ci % BKT == 0 && p.TR * p.TS > 1 && !tap_outer_forced) ? 1 : 0;
+    p.tap_inner = tap_inner_order(p.TR * p.TS, p.Ci, BKT, BN, M) ? 1 : 0;
     p.linear_out = (p.out_mul_h == 1 && p.out_mul_w == 1 && p.out_off_h == 0 && p.out_off_w == 0 && p.Mh == p.Ho && p.Mw == p.Wo) ? 1 : 0;
     // results of a large layer leave as non-temporal stores: the caches keep serving this kernel's operand reads
     static const char *nt_forced = getenv("MXC_NT_OUT");                      // tuning sweeps only; read once
@@ -724,7 +743,7 @@ int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end
     p.nt_out = nt_forced ? atoi(nt_forced) : ((long long)p.N * p.Ho * p.Wo * p.Co * 2 >= (128ll << 20) ? 1 : 0);
     if (p.splits > 1) {
         // even stage ranges; the last split may be shorter, none is empty
-        const int KT = (p.TR * p.TS * p.Ci + BKT - 1) / BKT;
+        const int KT = stages_of(p.TR * p.TS, p.Ci, BKT, BN, M);
         p.split_stages = (KT + p.splits - 1) / p.splits;
         p.splits = (KT + p.split_stages - 1) / p.split_stages;
         if (!p.linear_out || !p.partial || m_begin != 0 || m_end != M) return MXC_ERR_UNSUPPORTED;
@@ -1111,7 +1130,7 @@ int launch_split(int tc, IgemmParams p, long long M, int sp, void *split_ws, voi
     if ((MC / 4 + 255) / 256 > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
     // the launcher evens out the stage ranges, which can lower the split count: recompute it the same way
     const int bk = kTiles[tc].bk;
-    const int KT = (p.TR * p.TS * p.Ci + bk - 1) / bk, per = (KT + sp - 1) / sp, used = (KT + per - 1) / per;
+    const int KT = stages_of(p.TR * p.TS, p.Ci, bk, kTiles[tc].bn, M), per = (KT + sp - 1) / sp, used = (KT + per - 1) / per;
     static thread_local char split_name[64];
     snprintf(split_name, sizeof(split_name), "%s%s_split%d", kTiles[tc].name, bt ? "_inplace" : "", used);
     *variant = split_name;
