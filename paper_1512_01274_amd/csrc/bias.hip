@@ -177,6 +177,9 @@ BiasPlan plan(long long N, int K, long long PQ, int dtype, int layout)
         if (most < 1) most = 1;
         if (parts > most) parts = most;
         if (parts > N) parts = N;
+        // Up to 64 KB of a channel one workgroup is done before the second launch would be: 48 KB of 25x25 planes 5.8 -> 3.9 us, 64 KB
+        // 5.9 -> 4.4, of 7x7 planes 5.8 -> 5.1; from 96 KB of those and 128 KB of the others on two launches are even or faster.
+        if (N * per_image <= 64 << 10) parts = 1;
         b.parts = (int)(parts < 1 ? 1 : parts);
         return b;
     }
