@@ -1347,7 +1347,7 @@ static int classes_wave(const ConvShape &s, bool masked)
     struct Entry { ConvShape s; int flags, wave; };
     static thread_local Entry cache[32] = {};
     const int flags = masked ? 2 : 1;
-    Entry &e = cache[(unsigned)(s.N * 31 + s.H * 13 + s.W * 11 + s.C * 7 + s.K * 3 + s.R + flags) % 32];
+    Entry &e = cache[(unsigned)(s.N * 31ll + s.H * 13 + s.W * 11 + s.C * 7ll + s.K * 3ll + s.R + flags) % 32];
     if (e.flags != flags || memcmp(&e.s, &s, sizeof s)) {
         double us = 0, other = 0;
         const int wv = (long long)s.N * s.H * s.W <= 1 << 30 ? wave_best_classes(s, masked, &us, &other) : -1;

@@ -549,7 +549,7 @@ Plan make_plan(const WgradGeom &g)
     }
     struct Entry { WgradGeom g; Plan plan; bool used; };
     static thread_local Entry cache[64] = {};
-    Entry &e = cache[(unsigned)(g.N * 131 + g.H * 37 + g.W * 29 + g.K * 17 + g.C * 11 + g.R * 5 + g.stride + g.pix) % 64];
+    Entry &e = cache[(unsigned)(g.N * 131ll + g.H * 37 + g.W * 29 + g.K * 17ll + g.C * 11ll + g.R * 5 + g.stride + g.pix) % 64];
     if (e.used && !memcmp(&e.g, &g, sizeof g)) return e.plan;
     int forced = -1, splits = 0;
     for (const TunedWgrad &t : kTunedWgrad)
