@@ -348,6 +348,10 @@ const char *mxc_tile_name(int family, int index);
  * All three are 0 before any such call.  Host only. */
 void mxc_last_plan_key(long long *M, int *Co, int *Kd);
 
+/* Tuning aid: how often the calling thread has searched for the kernel that runs a problem.  A thread keeps what it
+ * found: calls and size queries of problems it has met lately do not search, and the count stands still.  Host only. */
+long long mxc_plan_searches(void);
+
 /* Measurement aid (not part of the convolution path): enqueues one launch of a
  * register-resident loop of bf16 matrix instructions (v_mfma_f32_32x32x16_bf16, fp32
  * accumulate, no memory traffic) on `workgroups` workgroups of 256 threads, `iters`

@@ -6,8 +6,11 @@
 #include <string>
 
 #include "mxc_internal.h"
+#include "plan_cache.h"
 
 namespace mxc {
+
+thread_local long long g_plan_searches = 0;
 
 namespace {
 
@@ -1109,6 +1112,8 @@ void mxc_last_plan_key(long long *M, int *Co, int *Kd)
     if (Co) *Co = co;
     if (Kd) *Kd = kd;
 }
+
+long long mxc_plan_searches(void) { return g_plan_searches; }
 
 int mxc_version(void) { return 400; }
 

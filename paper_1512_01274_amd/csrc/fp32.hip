@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "mxc_internal.h"
+#include "plan_cache.h"
 
 namespace mxc {
 
@@ -1244,6 +1245,7 @@ F32Plan plan_rows(const ConvShape &s, int op)
 // (8 bytes per element at about 3 TB/s) and makes the summing launch necessary (5000 clocks: 2.2 us where it is all launch).
 F32Plan search_wgrad(const ConvShape &s, int ft, int fs)
 {
+    ++g_plan_searches;
     const long long M = (long long)s.N * s.P * s.Q, cols = (long long)s.C * s.R * s.S;
     double best = 1e300;
     F32Plan pl{0, 1, (int)M};
@@ -1266,7 +1268,7 @@ F32Plan search_wgrad(const ConvShape &s, int ft, int fs)
     return pl;
 }
 
-// A call asks three times, at up to 7 us a search: the calling thread keeps its answers (64, each geometry's place given by its numbers).
+// A call asks three times, at up to 7 us a search: the calling thread keeps its answers.
 F32Plan plan_wgrad(const ConvShape &s)
 {
     int fs = 0;
@@ -1274,11 +1276,9 @@ F32Plan plan_wgrad(const ConvShape &s)
     if (ft >= 0) return search_wgrad(s, ft, fs);
     const long long M = (long long)s.N * s.P * s.Q;
     const int cols = s.C * s.R * s.S;
-    struct Entry { long long M; int K, cols; F32Plan plan; };
-    static thread_local Entry cache[64] = {};
-    Entry &e = cache[(unsigned)(M * 31 + s.K * 7 + cols * 3) % 64];
-    if (e.M != M || e.K != s.K || e.cols != cols) e = Entry{M, s.K, cols, search_wgrad(s, -1, 0)};
-    return e.plan;
+    struct Key { long long M; int K, cols; };
+    static thread_local PlanCache<Key, F32Plan> cache;
+    return cache.get(Key{M, s.K, cols}, [&] { return search_wgrad(s, -1, 0); });
 }
 
 }  // namespace

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "mxc_internal.h"
+#include "plan_cache.h"
 
 namespace mxc {
 
@@ -914,6 +915,7 @@ thread_local int g_key_Co = 0, g_key_Kd = 0;
 
 Plan search_plan(long long M, int Co, int Kd, bool allow_stream, bool masked)
 {
+    ++g_plan_searches;
     if (const char *f = getenv("MXC_FORCE_VARIANT")) {
         const char *plus = strchr(f, '+'), *slash = strchr(f, '/');
         const int a = tile_index(f, plus ? (size_t)(plus - f) : slash ? (size_t)(slash - f) : strlen(f));
@@ -955,18 +957,16 @@ Plan search_plan(long long M, int Co, int Kd, bool allow_stream, bool masked)
     return best;
 }
 
-// The search walks the table and every pair of shapes, and a call asks several times (size query, filter form, launch): the
-// calling thread keeps its last answers.
+// What a thread's plans are kept by; flags hold what else the answer depends on.
+struct GemmKey { long long M; int Co, Kd; long long flags; };
+
+// The search walks the table and every pair of shapes: the calling thread keeps its answers.
 Plan choose_plan(long long M, int Co, int Kd, bool allow_stream = true, bool masked = false)
 {
     g_key_M = M; g_key_Co = Co; g_key_Kd = Kd;
     if (getenv("MXC_FORCE_VARIANT")) return search_plan(M, Co, Kd, allow_stream, masked);
-    struct Entry { long long M; int Co, Kd, flags; Plan plan; };
-    static thread_local Entry cache[64] = {};
-    const int flags = 1 + (allow_stream ? 2 : 0) + (masked ? 4 : 0);       // never 0, as an unused entry's are
-    Entry &e = cache[(unsigned)(M * 31 + Co * 7 + Kd * 3 + flags) % 64];
-    if (e.M != M || e.Co != Co || e.Kd != Kd || e.flags != flags) e = Entry{M, Co, Kd, flags, search_plan(M, Co, Kd, allow_stream, masked)};
-    return e.plan;
+    static thread_local PlanCache<GemmKey, Plan> cache;
+    return cache.get(GemmKey{M, Co, Kd, (allow_stream ? 1 : 0) + (masked ? 2 : 0)}, [&] { return search_plan(M, Co, Kd, allow_stream, masked); });
 }
 
 int choose_tile(long long M, int Co, int Kd) { return choose_plan(M, Co, Kd, false).main; }
@@ -1073,20 +1073,16 @@ double tile_us(const TileChoice &t, long long M, int Co, int Kd, int splits, boo
 int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_split)
 {
     if (const char *f = getenv("MXC_FORCE_VARIANT")) return wave_forced(f, bwd);
-    struct Entry { long long M; int Co, Kd, flags, wave; };
-    static thread_local Entry cache[64] = {};
-    const int flags = 1 + (bwd ? 2 : 0) + (masked ? 4 : 0) + (can_split ? 8 : 0);
-    Entry &e = cache[(unsigned)(M * 31 + Co * 7 + Kd * 3 + flags) % 64];
-    if (e.M == M && e.Co == Co && e.Kd == Kd && e.flags == flags) return e.wave;
-    const Plan pl = choose_plan(M, Co, Kd, true, masked);
-    double us = 0;
-    int wave = whole_launch(pl.main) ? -1 : wave_best(M, Co, Kd, bwd, masked, &us);
-    if (wave >= 0) {
+    static thread_local PlanCache<GemmKey, int> cache;
+    return cache.get(GemmKey{M, Co, Kd, (bwd ? 1 : 0) + (masked ? 2 : 0) + (can_split ? 4 : 0)}, [&] {
+        ++g_plan_searches;
+        const Plan pl = choose_plan(M, Co, Kd, true, masked);
+        double us = 0;
+        const int wave = whole_launch(pl.main) ? -1 : wave_best(M, Co, Kd, bwd, masked, &us);
+        if (wave < 0) return -1;
         const double other = tile_us(kTiles[pl.main], M, Co, Kd, can_split ? split_count(M, Co, Kd) : 1, masked);
-        if (us > other * (us < 18 ? 0.92 : us < 36 ? 0.785 : 0.69)) wave = -1;
-    }
-    e = Entry{M, Co, Kd, flags, wave};
-    return wave;
+        return us > other * (us < 18 ? 0.92 : us < 36 ? 0.785 : 0.69) ? -1 : wave;
+    });
 }
 
 // out[m][co] = act(sum_z partial[z][m][co] + bias[co]) in ascending z (fixed order), 4 columns per thread
@@ -1344,17 +1340,14 @@ static int classes_wave(const ConvShape &s, bool masked)
         const int wv = wave_forced(f, true);
         return wv >= 0 && wave_has_classes(wv) ? wv : -1;
     }
-    struct Entry { ConvShape s; int flags, wave; };
-    static thread_local Entry cache[32] = {};
-    const int flags = masked ? 2 : 1;
-    Entry &e = cache[(unsigned)(s.N * 31ll + s.H * 13 + s.W * 11 + s.C * 7ll + s.K * 3ll + s.R + flags) % 32];
-    if (e.flags != flags || memcmp(&e.s, &s, sizeof s)) {
+    struct Key { ConvShape s; int masked; };
+    static thread_local PlanCache<Key, int> cache;
+    return cache.get(Key{s, masked}, [&] {
+        ++g_plan_searches;
         double us = 0, other = 0;
         const int wv = (long long)s.N * s.H * s.W <= 1 << 30 ? wave_best_classes(s, masked, &us, &other) : -1;
-        e.s = s; e.flags = flags;
-        e.wave = wv >= 0 && us < (us < 10 ? 0.8 : 0.6) * other ? wv : -1;
-    }
-    return e.wave;
+        return wv >= 0 && us < (us < 10 ? 0.8 : 0.6) * other ? wv : -1;
+    });
 }
 bool bwd_data_classes_in_place(const ConvShape &s, bool masked)
 {

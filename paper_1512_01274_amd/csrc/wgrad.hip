@@ -21,6 +21,7 @@
 
 #include <type_traits>
 
+#include "plan_cache.h"
 #include "resum.h"
 
 namespace mxc {
@@ -529,10 +530,7 @@ int tile_index(const char *name, size_t len)
 
 // Tile and split count, in this order: MXC_FORCE_WGRAD=<tile>[/<splits>] (tuning sweeps only); the table of
 // measured best choices (tuned_wgrad.inc, written by the tuning script from timings on the device) when it
-// holds this geometry; else the time model's search.  The search costs tens of microseconds, a call needs
-// its answer up to three times (size query, workspace carve-out, launch) and a training loop asks for the
-// same few geometries over and over: the calling thread keeps its answers (no locks; 64 entries, each geometry's place
-// given by its numbers: a look through 32 entries and the table cost 0.2 us, three times a call).
+// holds this geometry; else the time model's search.  The calling thread keeps its answers (plan_cache.h).
 Plan make_plan(const WgradGeom &g)
 {
     const char *f = getenv("MXC_FORCE_WGRAD");
@@ -547,22 +545,19 @@ Plan make_plan(const WgradGeom &g)
         pl.wave[0] = pl.wave[1] = wave_choice(g, pl, false);       // what the hook forces on the wave kernel is looked up on every call
         return pl;
     }
-    struct Entry { WgradGeom g; Plan plan; bool used; };
-    static thread_local Entry cache[64] = {};
-    Entry &e = cache[(unsigned)(g.N * 131ll + g.H * 37 + g.W * 29 + g.K * 17ll + g.C * 11ll + g.R * 5 + g.stride + g.pix) % 64];
-    if (e.used && !memcmp(&e.g, &g, sizeof g)) return e.plan;
-    int forced = -1, splits = 0;
-    for (const TunedWgrad &t : kTunedWgrad)
-        if (t.N == g.N && t.H == g.oH && t.W == g.oW && t.C == g.C && t.K == g.K && t.R == g.R && t.S == g.S && t.stride == g.ostride && t.pad == g.opad) {
-            forced = tile_index(t.tile, strlen(t.tile));
-            splits = forced >= 0 ? t.splits : 0;
-            break;
-        }
-    e.g = g;
-    e.plan = search_plan(g, forced, splits);
-    for (const bool copies : {false, true}) e.plan.wave[copies] = wave_choice(g, e.plan, copies);
-    e.used = true;
-    return e.plan;
+    static thread_local PlanCache<WgradGeom, Plan> cache;
+    return cache.get(g, [&] {
+        int tuned = -1, splits = 0;
+        for (const TunedWgrad &t : kTunedWgrad)
+            if (t.N == g.N && t.H == g.oH && t.W == g.oW && t.C == g.C && t.K == g.K && t.R == g.R && t.S == g.S && t.stride == g.ostride && t.pad == g.opad) {
+                tuned = tile_index(t.tile, strlen(t.tile));
+                splits = tuned >= 0 ? t.splits : 0;
+                break;
+            }
+        Plan pl = search_plan(g, tuned, splits);
+        for (const bool copies : {false, true}) pl.wave[copies] = wave_choice(g, pl, copies);
+        return pl;
+    });
 }
 
 // Modelled time (us, fitted to the gradients of wave_dw.hip's model, 9% off) of the planned tile: stages and rounds of the CU
@@ -607,6 +602,7 @@ DwWave wave_choice(const WgradGeom &g, const Plan &pl, bool copies)
 
 Plan search_plan(const WgradGeom &g, int forced, int forced_splits)
 {
+    ++g_plan_searches;
     const int RSC = g.TR * g.TS * g.run;
     const long long M = (long long)g.N * g.P * g.Q;
     Plan best_pl{};

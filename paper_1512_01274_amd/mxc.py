@@ -113,6 +113,15 @@ def mxc_last_plan_key():
     return m.value, co.value, kd.value
 
 
+_lib.mxc_plan_searches.argtypes = []
+_lib.mxc_plan_searches.restype = ctypes.c_longlong
+
+
+def mxc_plan_searches() -> int:
+    """Plan searches this thread has made so far."""
+    return _lib.mxc_plan_searches()
+
+
 def mxc_tile_names(family: int):
     """Names of the tile shapes of a kernel family (0: implicit GEMM, 1: backward-weight, 2: the streaming and the window implicit GEMM)."""
     out, i = [], 0

@@ -1,0 +1,109 @@
+"""Host checks of the plans a thread keeps: a network's layers, walked a second time in turn, find every plan kept."""
+import pytest
+import torch
+
+
+@pytest.fixture(scope="module")
+def mxc():
+    from paper_1512_01274_amd import mxc as m
+    return m
+
+
+def _resnet50(b):
+    """Bottlenecks of four stages: 1x1 reductions and expansions, 3x3, strided 1x1 projections; channels and sizes that are
+    multiples of 64 apart."""
+    out = []
+    for stage, (mid, hw) in enumerate([(64, 56), (128, 28), (256, 14), (512, 7)]):
+        cin, h_in, st = (64, 56, 1) if stage == 0 else (2 * mid, 2 * hw, 2)
+        out += [(b, cin, h_in, h_in, mid, 1, 1, st, 0), (b, cin, h_in, h_in, 4 * mid, 1, 1, st, 0), (b, mid, hw, hw, mid, 3, 3, 1, 1),
+                (b, mid, hw, hw, 4 * mid, 1, 1, 1, 0), (b, 4 * mid, hw, hw, mid, 1, 1, 1, 0)]
+    return out
+
+
+def _inception(b):
+    out = []
+    for h, c, a1, b1, b3, c1, c5, d1 in [(28, 192, 64, 96, 128, 16, 32, 32), (28, 256, 128, 128, 192, 32, 96, 64), (14, 480, 192, 96, 208, 16, 48, 64),
+                                         (14, 512, 160, 112, 224, 24, 64, 64), (14, 528, 256, 160, 320, 32, 128, 128), (7, 832, 384, 192, 384, 48, 128, 128)]:
+        out += [(b, c, h, h, a1, 1, 1, 1, 0), (b, c, h, h, b1, 1, 1, 1, 0), (b, b1, h, h, b3, 3, 3, 1, 1), (b, c, h, h, c1, 1, 1, 1, 0),
+                (b, c1, h, h, c5, 5, 5, 1, 2), (b, c, h, h, d1, 1, 1, 1, 0)]
+    return out
+
+
+def _vgg(b):
+    return [(b, 64, 112, 112, 128, 3, 3, 1, 1), (b, 128, 56, 56, 256, 3, 3, 1, 1), (b, 256, 56, 56, 256, 3, 3, 1, 1), (b, 256, 28, 28, 512, 3, 3, 1, 1),
+            (b, 512, 28, 28, 512, 3, 3, 1, 1), (b, 512, 14, 14, 512, 3, 3, 1, 1)]
+
+
+def _first(b):
+    """First layers: few channels, packed for forward and backward-weight."""
+    return [(b, c, h, h, k, r, r, st, r // 2) for c, h, k, r, st in [(3, 224, 64, 3, 1), (3, 128, 32, 5, 1), (1, 64, 64, 3, 1), (3, 224, 64, 11, 4), (3, 224, 64, 7, 2)]]
+
+
+NETS = {"resnet50_b64": _resnet50(64), "resnet50_b256": _resnet50(256), "inception_b32": _inception(32), "vgg_b32": _vgg(32), "first_b8": _first(8)}
+FORMS = [("bf16", "nhwc"), ("bf16", "nchw"), ("f32", "nhwc"), ("f32", "nchw")]
+
+
+def _codes(mxc, dtype, layout):
+    return (mxc.MXC_BF16 if dtype == "bf16" else mxc.MXC_F32), (mxc.MXC_NHWC if layout == "nhwc" else mxc.MXC_NCHW)
+
+
+def _second_walk_searches(mxc, walk):
+    first = mxc.mxc_plan_searches()
+    walk()
+    once = mxc.mxc_plan_searches()
+    walk()
+    return once - first, mxc.mxc_plan_searches() - once
+
+
+@pytest.mark.parametrize("net", NETS)
+@pytest.mark.parametrize("dtype,layout", FORMS)
+def test_size_queries_of_a_network_search_once(mxc, net, dtype, layout):
+    dt, lay = _codes(mxc, dtype, layout)
+
+    def walk():
+        for dims in NETS[net]:
+            for op in (mxc.MXC_FWD, mxc.MXC_BWD_DATA, mxc.MXC_BWD_DATA_RELU, mxc.MXC_BWD_WEIGHT):
+                mxc.mxc_conv2d_workspace_bytes(op, *dims, dt, lay)
+
+    assert _second_walk_searches(mxc, walk)[1] == 0
+
+
+@pytest.mark.parametrize("net", NETS)
+@pytest.mark.parametrize("dtype,layout", FORMS)
+def test_calls_of_a_network_search_once(mxc, net, dtype, layout):
+    """The calls themselves.  Without a GPU each ends at its first launch; those that launch their main kernel first (no operand to
+    bring into another form) have planned it by then."""
+    if torch.cuda.is_available():
+        pytest.skip("no launch with made-up pointers")
+    dt, lay = _codes(mxc, dtype, layout)
+    lib, big = mxc.raw(), 1 << 40
+    rcs = []
+
+    def walk():
+        for dims in NETS[net]:
+            a, tail = (*dims, dt, lay), (1 << 30, big, None)
+            rcs.append(lib.mxc_conv2d_fwd_bias_act(*a, 4096, 8192, 12288, 1, 16384, *tail))
+            rcs.append(lib.mxc_conv2d_bwd_weight(*a, 4096, 8192, 12288, *tail))
+            rcs.append(lib.mxc_conv2d_bwd_data(*a, 4096, 8192, 12288, *tail))
+            for mask in (None, 20480):
+                rcs.append(lib.mxc_conv2d_bwd_data_prepared(*a, 4096, 8192, big, mask, 12288, *tail))
+            if layout == "nhwc":
+                rcs.append(lib.mxc_conv2d_fwd_prepared_input(*a, 4096, big, 8192, None, 0, 12288, *tail))
+                rcs.append(lib.mxc_conv2d_bwd_weight_prepared_input(*a, 4096, big, 8192, 12288, mxc.MXC_F32, *tail))
+
+    searches = _second_walk_searches(mxc, walk)
+    assert set(rcs) == {mxc.MXC_ERR_LAUNCH}
+    assert searches[1] == 0, searches
+
+
+def test_answers_do_not_depend_on_what_was_asked_before(mxc):
+    """More geometries than are kept, asked forwards, backwards and forwards: the same sizes."""
+    import random
+    rng = random.Random(5)
+    asked = [(rng.randint(1, 64), 8 * rng.randint(1, 64), h, h, 8 * rng.randint(1, 64), r, r, rng.randint(1, 2), r // 2)
+             for _ in range(800) for h, r in [(rng.randint(7, 60), rng.choice([1, 3, 5]))]]
+    size = lambda d, op, dt: mxc.mxc_conv2d_workspace_bytes(op, *d, dt, mxc.MXC_NHWC)  # noqa: E731
+    for op, dt in [(mxc.MXC_FWD, mxc.MXC_BF16), (mxc.MXC_BWD_DATA, mxc.MXC_BF16), (mxc.MXC_BWD_WEIGHT, mxc.MXC_BF16), (mxc.MXC_BWD_WEIGHT, mxc.MXC_F32)]:
+        once = [size(d, op, dt) for d in asked]
+        assert [size(d, op, dt) for d in reversed(asked)] == once[::-1]
+        assert [size(d, op, dt) for d in asked] == once
