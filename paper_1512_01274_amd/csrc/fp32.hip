@@ -1228,6 +1228,7 @@ F32Plan plan_rows(const ConvShape &s, int op)
 {
     int t = forced_tile("MXC_FORCE_VARIANT", nullptr);
     if (t >= 0) return F32Plan{t, 1, 0};
+    ++g_plan_searches;
     double best = 1e300;
     F32Plan pl{0, 1, 0};
     for (t = 0; t < N_TILES; ++t) {
@@ -1268,19 +1269,6 @@ F32Plan search_wgrad(const ConvShape &s, int ft, int fs)
     return pl;
 }
 
-// A call asks three times, at up to 7 us a search: the calling thread keeps its answers.
-F32Plan plan_wgrad(const ConvShape &s)
-{
-    int fs = 0;
-    const int ft = forced_tile("MXC_FORCE_WGRAD", &fs);
-    if (ft >= 0) return search_wgrad(s, ft, fs);
-    const long long M = (long long)s.N * s.P * s.Q;
-    const int cols = s.C * s.R * s.S;
-    struct Key { long long M; int K, cols; };
-    static thread_local PlanCache<Key, F32Plan> cache;
-    return cache.get(Key{M, s.K, cols}, [&] { return search_wgrad(s, -1, 0); });
-}
-
 }  // namespace
 
 const char *f32_wave_name(int index)
@@ -1311,6 +1299,7 @@ int wave_rows(const ConvShape &s, int op, bool nchw, int other, bool masked)
             if (!strcmp(f, kWaves[i].name)) return i;
         return -1;
     }
+    ++g_plan_searches;
     const long long m = op == OP_FWD ? (long long)s.N * s.P * s.Q : (long long)s.N * s.H * s.W, cols = op == OP_FWD ? s.K : s.C;
     const int taps = op == OP_FWD ? s.R * s.S : ((s.R + s.stride - 1) / s.stride) * ((s.S + s.stride - 1) / s.stride);
     const long long k = (long long)taps * (op == OP_FWD ? s.C : s.K);
@@ -1354,16 +1343,28 @@ static int run(int op, bool nchw, int t, F32Params &p, long long row_tiles, long
     return launch_op(op, nchw, t, p, st);
 }
 
-// The wave kernel's shape that runs an NCHW problem on NHWC copies of its operands, or -1: the operands are read in place.
-int f32_copies(const ConvShape &s, bool bwd, bool masked)
+// The tile that runs forward or backward-data, and the wave kernel's shape that runs it instead, or -1.  The calling thread keeps its
+// answers: with them the host's part of a call (2x16x16x16 to 32, 3x3) is 0.40 us forward and 0.42 for dx, searched anew 0.62 and 0.67.
+struct F32Rows { int tile, wave; };
+static F32Rows choose_rows(const ConvShape &s, int op, bool nchw, bool masked)
 {
-    const int op = bwd ? OP_BWD : OP_FWD;
-    return wave_rows(s, op, true, plan_rows(s, op).tile, masked);
+    const auto search = [&] {
+        const int tile = plan_rows(s, op).tile;
+        return F32Rows{tile, wave_rows(s, op, nchw, tile, masked)};
+    };
+    if (getenv("MXC_FORCE_VARIANT")) return search();
+    struct Key { ConvShape s; int op, nchw, masked; };
+    static thread_local PlanCache<Key, F32Rows> cache;
+    return cache.get(Key{s, op, nchw, masked}, search);
 }
+
+// The wave kernel's shape that runs an NCHW problem on NHWC copies of its operands, or -1: the operands are read in place.
+int f32_copies(const ConvShape &s, bool bwd, bool masked) { return choose_rows(s, bwd ? OP_BWD : OP_FWD, true, masked).wave; }
 
 int f32_fwd(const ConvShape &s, bool nchw, int copies, const void *x, const void *w, void *y, hipStream_t st, const char **variant, const PostOp &post)
 {
-    const int tile = plan_rows(s, OP_FWD).tile, wv = nchw ? copies : wave_rows(s, OP_FWD, false, tile, false), t = wv >= 0 ? -1 - wv : tile;
+    const F32Rows rows = choose_rows(s, OP_FWD, nchw, false);
+    const int wv = nchw ? copies : rows.wave, t = wv >= 0 ? -1 - wv : rows.tile;
     const int bm = wv >= 0 ? 16 * kWaves[wv].mb * kWaves[wv].mg : kTiles[t].bm;
     F32Params p{};
     p.a = (const float *)x; p.b = (const float *)w; p.out = (float *)y;
@@ -1383,7 +1384,8 @@ int f32_fwd(const ConvShape &s, bool nchw, int copies, const void *x, const void
 int f32_bwd_data(const ConvShape &s, bool nchw, int copies, const void *dy, const void *w, void *dx, hipStream_t st, const char **variant,
                  const PostOp &post)
 {
-    const int tile = plan_rows(s, OP_BWD).tile, wv = nchw ? copies : wave_rows(s, OP_BWD, false, tile, post.mask != nullptr), t = wv >= 0 ? -1 - wv : tile;
+    const F32Rows rows = choose_rows(s, OP_BWD, nchw, post.mask != nullptr);
+    const int wv = nchw ? copies : rows.wave, t = wv >= 0 ? -1 - wv : rows.tile;
     const int bm = wv >= 0 ? 16 * kWaves[wv].mb * kWaves[wv].mg : kTiles[t].bm;
     F32Params p{};
     p.a = (const float *)dy; p.b = (const float *)w; p.out = (float *)dx;
@@ -1405,11 +1407,11 @@ int f32_bwd_data(const ConvShape &s, bool nchw, int copies, const void *dy, cons
     return run(OP_BWD, nchw, t, p, tiles, s.C, 1, st);
 }
 
-// The wave kernel's shape (tile), pixel ranges and their length for backward-weight, or splits 0: the plan.  Never more ranges than
-// the plan has: the workspace is sized for those.  Of those 260 gradients 1.38 times as fast.
-static F32Plan wave_wgrad(const ConvShape &s, bool nchw, const F32Plan &pl)
+// The wave kernel's shape (tile), pixel ranges and their length for backward-weight of an NHWC problem, or splits 0: the plan.  Never
+// more ranges than the plan has: the workspace is sized for those.  Of those 260 gradients 1.38 times as fast.
+static F32Plan wave_wgrad(const ConvShape &s, const F32Plan &pl)
 {
-    if (nchw || s.C % 4 != 0 || s.K % 4 != 0) return F32Plan{0, 0, 0};
+    if (s.C % 4 != 0 || s.K % 4 != 0) return F32Plan{0, 0, 0};
     const long long M = (long long)s.N * s.P * s.Q, cols = (long long)s.C * s.R * s.S;
     auto ranges = [&](int shape, long long want) {
         if (want > pl.splits) want = pl.splits;
@@ -1424,6 +1426,7 @@ static F32Plan wave_wgrad(const ConvShape &s, bool nchw, const F32Plan &pl)
             if (strlen(kDwWaves[i].name) == len && !strncmp(f, kDwWaves[i].name, len)) return ranges(i, slash ? atoi(slash + 1) : 1);
         return F32Plan{0, 0, 0};
     }
+    ++g_plan_searches;
     double best = 0.95 * tile_us(pl.tile, OP_WGRAD, false, s.K, cols, pl.span, pl.splits, false);
     F32Plan chosen{0, 0, 0};
     for (int i = 0; i < N_DW_WAVES; ++i) {
@@ -1442,14 +1445,32 @@ static F32Plan wave_wgrad(const ConvShape &s, bool nchw, const F32Plan &pl)
     return chosen;
 }
 
-size_t f32_wgrad_workspace(const ConvShape &s) { return (size_t)plan_wgrad(s).splits * s.K * s.C * s.R * s.S * sizeof(float); }
+// Both answers for backward-weight.  A call asks three times, at up to 7 us a search: the calling thread keeps them (with the wave
+// kernel's shape searched for on every call, that layer's call was 0.68 us of host time instead of 0.48).
+struct F32Dw { F32Plan plan, wave; };
+static F32Dw plan_wgrad(const ConvShape &s)
+{
+    const auto search = [&] {
+        int fs = 0;
+        const int ft = forced_tile("MXC_FORCE_WGRAD", &fs);
+        const F32Plan pl = search_wgrad(s, ft, fs);
+        return F32Dw{pl, wave_wgrad(s, pl)};
+    };
+    if (getenv("MXC_FORCE_WGRAD")) return search();
+    struct Key { long long M; int K, C, R, S; };
+    static thread_local PlanCache<Key, F32Dw> cache;
+    return cache.get(Key{(long long)s.N * s.P * s.Q, s.K, s.C, s.R, s.S}, search);
+}
+
+size_t f32_wgrad_workspace(const ConvShape &s) { return (size_t)plan_wgrad(s).plan.splits * s.K * s.C * s.R * s.S * sizeof(float); }
 
 int f32_wgrad(const ConvShape &s, bool nchw, const void *x, const void *dy, void *dw, float *partial, hipStream_t st, const char **variant)
 {
-    F32Plan pl = plan_wgrad(s);
+    const F32Dw both = plan_wgrad(s);
+    F32Plan pl = both.plan;
     const char *name = kTiles[pl.tile].name;
     int bm = kTiles[pl.tile].bm;
-    if (const F32Plan wv = wave_wgrad(s, nchw, pl); wv.splits > 0) {
+    if (const F32Plan wv = both.wave; !nchw && wv.splits > 0) {
         name = kDwWaves[wv.tile].name;
         bm = 16 * kDwWaves[wv.tile].mb;
         pl = F32Plan{-1 - wv.tile, wv.splits, wv.span};
