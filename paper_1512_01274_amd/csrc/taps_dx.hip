@@ -17,6 +17,7 @@
 // with a wait each, took 73 us where this takes 48).  Measured (us, packing + GEMM + compaction -> here): 32x224x224, 64 channels to 3,
 // 3x3 69.8 -> 48.5; 3x115x70, 64 to 3 22.7 -> 5.6; 23x25x25, 112 to 3, 5x5 58.5 -> 12.3.
 #include "mxc_internal.h"
+#include "plan_cache.h"
 
 namespace mxc {
 
@@ -222,6 +223,7 @@ const char *taps_dx_name() { return kName; }
 struct Cut { int strips, segs, rows, steps; long long units, rounds; };
 static Cut cut(const ConvShape &s)
 {
+    ++g_plan_searches;
     const int slots = 256 * (160 * 1024 / (s.R == 3 ? lds_bytes<3>(s.C) : lds_bytes<5>(s.C)));
     Cut best{};
     const int strips = (s.W + POS - s.R) / (POS - (s.R - 1));
@@ -239,15 +241,28 @@ static Cut cut(const ConvShape &s)
 // Modelled times (us) of this kernel and of the packing, GEMM and compaction it replaces, fitted to 180 layers of up to 0.5 GB of dy, 7-9%
 // and 12-17% off.  Of those 3x3 runs 2.99 times as fast as before and takes this kernel in 73 of 77, 5x5 2.65 times in 94 of 103:
 // the rest have few channels of dy, large images and a filter of many products per pixel (131x91x91, 40 to 3, 5x5: 71 against 113).
-bool taps_dx_faster(const ConvShape &s)
+static bool faster(const ConvShape &s, const Cut &c)
 {
-    const Cut c = cut(s);
     const double per_cu = (double)((c.units + 255) / 256), ks = (s.K + 31) / 32, mb = 2e-6 * s.N * s.P * s.Q * s.K;
     const double gflop = 64e-9 * s.N * s.H * ((s.W + 7) / 8) * s.R * (s.S + 7) * s.K;
     if (s.R == 3)
         return 2.85 + per_cu * c.steps * (0.0285 + 0.126 * s.C + 0.063 * ks) + 0.165 * ks * s.C + 0.07 * mb < 6.1 + 2.44 * gflop + 6.42 * ks;
     return 2.05 + c.steps * (0.363 * c.rounds + per_cu * (0.247 * s.C + 0.1 * ks)) + 0.56 * ks * s.C + 0.101 * mb < 1.67 + 1.97 * gflop + 13.4 * ks;
 }
+
+// Both answers.  The calling thread keeps them: with up to 64 cuts looked at twice a call, the host's part of dx of 32 images of 224x224
+// (3x3, 64 channels to 3) was 1.06 us instead of 0.38.
+struct TapsPlan { Cut cut; bool faster; };
+static TapsPlan plan(const ConvShape &s)
+{
+    static thread_local PlanCache<ConvShape, TapsPlan> cache;
+    return cache.get(s, [&] {
+        const Cut c = cut(s);
+        return TapsPlan{c, faster(s, c)};
+    });
+}
+
+bool taps_dx_faster(const ConvShape &s) { return plan(s).faster; }
 
 bool taps_dx_supported(const ConvShape &s)
 {
@@ -267,7 +282,7 @@ int taps_dx(const ConvShape &s, const void *dy, const void *w, bool packed, int 
     p.P = s.P; p.Q = s.Q; p.K = s.K; p.Kr = real_k(s); p.H = s.H; p.W = s.W; p.pad = s.pad;
     if (packed) { p.w_k = 1; p.w_c = packed_cols * s.R * s.K; p.w_r = s.K; p.w_s = -s.R * s.K; p.w_0 = (s.S - 1) * s.R * s.K; }
     else { p.w_k = s.R * s.S * s.C; p.w_c = 1; p.w_r = s.S * s.C; p.w_s = s.C; p.w_0 = 0; }
-    const Cut c = cut(s);
+    const Cut c = plan(s).cut;
     p.strips = c.strips; p.segs = c.segs; p.rows = c.rows; p.units = (int)c.units;
     if (s.R == 3) launch_c<3>(s.C, p, st);
     else launch_c<5>(s.C, p, st);
