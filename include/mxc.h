@@ -345,6 +345,7 @@ const char *mxc_tile_name(int family, int index);
 /* Tuning aid: the implicit GEMM (rows M, output columns Co, reduction length Kd) that the calling thread's last
  * forward or backward-data call planned - for first layers that is the GEMM on the packed operands, whose
  * dimensions the caller does not otherwise see.  The tuning script keys its table of measured plans on it.
+ * Strided backward-data of other layers, a GEMM per residue class, leaves the key of any of them or as it was.
  * All three are 0 before any such call.  Host only. */
 void mxc_last_plan_key(long long *M, int *Co, int *Kd);
 

@@ -1072,6 +1072,7 @@ double tile_us(const TileChoice &t, long long M, int Co, int Kd, int splits, boo
 // measured 514 against 277; 801420 pixels, 224 x 24: 93 against 128, measured 157 against 108).
 int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_split)
 {
+    g_key_M = M; g_key_Co = Co; g_key_Kd = Kd;
     if (const char *f = getenv("MXC_FORCE_VARIANT")) return wave_forced(f, bwd);
     static thread_local PlanCache<GemmKey, int> cache;
     return cache.get(GemmKey{M, Co, Kd, (bwd ? 1 : 0) + (masked ? 2 : 0) + (can_split ? 4 : 0)}, [&] {

@@ -46,3 +46,19 @@ def test_layers_in_turn(mxc, dtype, layout):
     for run, x, w, dy, _, _ in jobs:
         run.fwd(x, w), run.bwd_data(dy, w), run.bwd_weight(x, dy)
     assert mxc.mxc_plan_searches() == before
+
+
+def test_last_plan_key_is_the_last_calls(mxc):
+    """Forward and dx of layers in turn: the key is that of the layer just run, on the first turn (planned) and on the second (kept)."""
+    layers = [(2, 3, 64, 64, 32, 7, 7, 2, 3), (2, 64, 14, 14, 64, 3, 3, 1, 1), (2, 3, 32, 32, 32, 3, 3, 1, 1), (2, 64, 9, 9, 96, 1, 1, 1, 0)]
+    seen = []
+    for _ in range(2):
+        for dims in layers:
+            run = util.Runner(mxc, dims, "bf16", "nhwc")
+            run.fwd(np.zeros((run.N, run.C, run.H, run.W), np.float32), np.zeros((run.K, run.C, run.R, run.S), np.float32))
+            seen.append(mxc.mxc_last_plan_key())
+            assert seen[-1][:2] == (run.N * run.P * run.Q, run.K), dims
+            if run.C > 4:
+                run.bwd_data(np.zeros((run.N, run.K, run.P, run.Q), np.float32), np.zeros((run.K, run.C, run.R, run.S), np.float32))
+                assert mxc.mxc_last_plan_key() == (run.N * run.H * run.W, run.C, run.R * run.S * run.K), dims
+    assert seen[:len(layers)] == seen[len(layers):]
