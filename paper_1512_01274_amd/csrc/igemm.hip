@@ -1065,11 +1065,20 @@ double tile_us(const TileChoice &t, long long M, int Co, int Kd, int splits, boo
     return 2.37 + 1.38 * per_cu * t.bm * t.bn / 65536.0 / util * KT + 2.14 * rounds + (splits > 1 ? 1.7 + 2.19 * splits * mc : 0) + (masked ? 0.92 : 0.46) * mc;
 }
 
-// The shape of the wave kernel (wave.hip) that runs this GEMM, or -1: the planned kernel does.  In 475 of the forward and dx passes of
-// 455 random layers it does, and those the planned kernel takes below 8, 8-12, 12-20, 20-40 and more us run 1.33, 1.47, 1.32,
-// 1.29 and 1.23 times as fast (six of them more than 2% slower, 9% at worst).  The models must agree by a margin, larger from 18 and
-// from 36 modelled us on: what they miss weighs more there (359464 pixels, 24 columns, 5x5 on 320 channels: modelled 316 against 372,
-// measured 514 against 277; 801420 pixels, 224 x 24: 93 against 128, measured 157 against 108).
+// ... of a plan: its main tile on the rows it takes, and a second launch for the rest
+double plan_us(const Plan &pl, long long M, int Co, int Kd, int splits, bool masked)
+{
+    if (pl.tail < 0 || splits > 1) return tile_us(kTiles[pl.main], M, Co, Kd, splits, masked);
+    return tile_us(kTiles[pl.main], pl.rows_main, Co, Kd, 1, masked) + tile_us(kTiles[pl.tail], M - pl.rows_main, Co, Kd, 1, masked);
+}
+
+// The shape of the wave kernel (wave.hip) that runs this GEMM, or -1: the planned kernel does.  Of 600 forward and dx passes of 300
+// random layers (up to 60 GFLOP; 27% NCHW) it runs 478; those that the planned kernel takes below 8, 8-12, 12-20, 20-40 and more us
+// run 1.48, 1.68, 1.58, 1.29 and 1.49 times as fast (four of them more than 2% slower, 14% at worst: 56000 pixels, 24 columns, Kd = 1008).
+// The models must agree by a margin, larger from 18 and from 36 modelled us on, where what they miss weighs more.  Measured time over
+// the planned kernel's, mean and worst, by the ratio of the models: below 18 us at 0.85-0.92 0.87 / 0.98, at 0.92-1 0.96 / 1.40; 18-36 us
+// at 0.74-0.785 0.88 / 1.08, at 0.785-0.85 0.93 / 1.14, at 0.85-0.92 1.13 / 1.31; 36-60 us at 0.69-0.92 0.93 / 1.24; above 60 us
+// at 0.85-1 1.18 / 1.60 (359464 pixels, 24 columns, 5x5 on 320 channels: 432 us measured against 290).
 int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_split)
 {
     g_key_M = M; g_key_Co = Co; g_key_Kd = Kd;
@@ -1081,7 +1090,7 @@ int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_spl
         double us = 0;
         const int wave = whole_launch(pl.main) ? -1 : wave_best(M, Co, Kd, bwd, masked, &us);
         if (wave < 0) return -1;
-        const double other = tile_us(kTiles[pl.main], M, Co, Kd, can_split ? split_count(M, Co, Kd) : 1, masked);
+        const double other = plan_us(pl, M, Co, Kd, can_split ? split_count(M, Co, Kd) : 1, masked);
         return us > other * (us < 18 ? 0.92 : us < 36 ? 0.785 : 0.69) ? -1 : wave;
     });
 }
