@@ -1318,6 +1318,7 @@ int igemm_bwd_data_image(ImageStore kind, const ConvShape &s2, const S2DStore &q
     p.in = (const bf16_t *)dy; p.out = (bf16_t *)dx; p.s2d = q;
     p.wm = (const bf16_t *)(w2 != nullptr ? w2 : wt);
     p.wm_by_k = w2 != nullptr;
+    g_key_M = (long long)s2.N * s2.H * s2.W; g_key_Co = s2.C; g_key_Kd = s2.R * s2.S * s2.K;      // (chosen without a plan)
     *variant = kind == IMAGE_STREAM ? kStreamName : kWindowName;
     return kind == IMAGE_STREAM ? stream_launch(p, st) : window_launch(p, st);
 }

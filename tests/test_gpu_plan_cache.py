@@ -58,7 +58,10 @@ def test_last_plan_key_is_the_last_calls(mxc):
             run.fwd(np.zeros((run.N, run.C, run.H, run.W), np.float32), np.zeros((run.K, run.C, run.R, run.S), np.float32))
             seen.append(mxc.mxc_last_plan_key())
             assert seen[-1][:2] == (run.N * run.P * run.Q, run.K), dims
-            if run.C > 4:
+            if run.C > 4 or run.stride > 1:
                 run.bwd_data(np.zeros((run.N, run.K, run.P, run.Q), np.float32), np.zeros((run.K, run.C, run.R, run.S), np.float32))
+            if run.stride > 1:      # space-to-depth: 2x2 pixels of four values each, a 4x4 filter
+                assert mxc.mxc_last_plan_key() == (run.N * 35 * 35, 16, 16 * run.K), dims
+            elif run.C > 4:
                 assert mxc.mxc_last_plan_key() == (run.N * run.H * run.W, run.C, run.R * run.S * run.K), dims
     assert seen[:len(layers)] == seen[len(layers):]
