@@ -20,6 +20,7 @@ DIMS = [
     (2, 24, 12, 11, 40, 3, 3, 2, 1),
     (40, 8, 3, 3, 12, 2, 2, 1, 0),         # images of fewer pixels than a step
 ]
+RANGES = [(40, 8, 12, 9, 12, 3, 3, 2, 1), (24, 12, 20, 21, 20, 3, 3, 1, 1), (60, 36, 13, 14, 36, 1, 1, 1, 0)]      # pixels enough for several ranges
 LAYOUTS = ["nhwc", "nchw"]
 
 
@@ -91,13 +92,15 @@ def test_masked_input_gradient(mxc, oracle, monkeypatch, name, layout, dims):
 
 
 @pytest.mark.parametrize("ranges", [1, 3])
-@pytest.mark.parametrize("dims", DIMS)
+@pytest.mark.parametrize("dims", DIMS + RANGES)
 @pytest.mark.parametrize("name", _names(True))
 def test_weight_gradient(mxc, oracle, monkeypatch, name, dims, ranges):
     monkeypatch.setenv("MXC_FORCE_WGRAD", f"{name}/{ranges}")
     N, C, H, W, K, R, S, st, pad = dims
     x, w, dy = _case(dims)
     run = util.Runner(mxc, dims, "f32", "nhwc")
+    if dims in RANGES:                     # of fewer pixels the plan, which the ranges are limited to, has one or two
+        assert mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BWD_WEIGHT, *dims, run.dt, run.lay) >= 3 * 4 * w.size
     dw = torch.full((w.size + 64,), 7.0, device="cuda")
     mxc.mxc_conv2d_bwd_weight(*dims, run.dt, run.lay, run._in(x), run._in(dy), dw, run._ws(mxc.MXC_BWD_WEIGHT))
     assert mxc.mxc_last_variant().split(":")[-1] == name
@@ -132,7 +135,7 @@ def test_taps_outside_are_left_out(mxc, monkeypatch, bad, layout):
         assert not bool(torch.isfinite(y[1][:, 1:]).any())
     if layout == "nchw":
         return
-    # dy's last row does not meet the filter's first row in dw: its pixels there lie outside x
+    # dy's first row does not meet the filter's first row in dw: its pixels there lie outside x
     bad_dy = dy.copy()
     bad_dy[:, :, 0, :] = bad
     for name in _names(True):

@@ -78,6 +78,53 @@ def test_fp32(mxc, oracle, monkeypatch, tile, dims, layout):
         check(run.bwd_weight(x, dy_bad), ref, den, "f32", False, ("bwd_weight", dims, splits))
 
 
+# fp32 layers of whole 16-byte chunks of channels, of which the wave kernels store results straight to NHWC or to planes and sum what
+# is NaN once more over the taps inside: unequal sides, residue classes of dx (some without a tap, planes of broken groups of four
+# pixels), no padding, several pixel ranges of dw
+CHUNKS = [
+    (2, 16, 16, 16, 32, 3, 3, 1, 1),
+    (2, 20, 13, 9, 12, 5, 3, 1, 2),
+    (3, 36, 21, 18, 24, 3, 3, 2, 1),
+    (5, 132, 7, 6, 40, 1, 1, 1, 1),       # border results without a single tap
+    (4, 8, 9, 10, 16, 1, 1, 2, 0),        # three of four classes of dx without a tap
+    (2, 24, 9, 8, 20, 2, 3, 1, 0),
+    (40, 8, 12, 9, 12, 3, 3, 2, 1),       # pixels enough for several ranges in dw, here and below
+    (24, 12, 20, 21, 20, 3, 3, 1, 1),
+]
+
+
+@pytest.mark.filterwarnings("ignore:invalid value")
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("dims", CHUNKS)
+def test_fp32_wave(mxc, oracle, monkeypatch, dims, layout):
+    N, C, H, W, K, R, S, st, pad = dims
+    x, w, dy = gen.random_case(hash(dims) & 0xFFFF, *dims, dtype="f32", dist="normal")
+    w_bad, dy_bad = plant(w, 5), plant(dy, 6)
+    run = util.Runner(mxc, dims, "f32", layout)
+    fwd = oracle.conv2d_fwd(x, w_bad, st, pad), oracle.conv2d_fwd(np.abs(x), finite_abs(w_bad), st, pad)
+    dx = [(f, g, np.where(x > 0, oracle.conv2d_bwd_data(g, f, x.shape, st, pad), 0.0), oracle.conv2d_bwd_data(finite_abs(g), finite_abs(f), x.shape, st, pad))
+          for f, g in ((w_bad, dy), (w, dy_bad))]
+    names = mxc.mxc_tile_names(6)
+    for name in (n for n in names if "_dw_" not in n):
+        monkeypatch.setenv("MXC_FORCE_VARIANT", name)
+        check(run.fwd(x, w_bad), *fwd, "f32", False, ("fwd", name, dims))
+        assert mxc.mxc_last_variant().endswith(name)
+        for f, g, ref, den in dx:
+            got = torch.full((N * C * H * W,), 7.0, device="cuda")
+            mxc.mxc_conv2d_bwd_data_relu(*dims, run.dt, run.lay, run._in(g), run._in(f), run._in(x), got, run._ws(mxc.MXC_BWD_DATA_RELU))
+            assert mxc.mxc_last_variant().endswith(name)
+            check(run._out(got, x.shape), ref, den, "f32", False, ("bwd_data", name, dims))
+    if layout == "nchw":                  # dw of planes has no wave kernel
+        return
+    ref, den = oracle.conv2d_bwd_weight(x, dy_bad, w.shape, st, pad), oracle.conv2d_bwd_weight(np.abs(x), finite_abs(dy_bad), w.shape, st, pad)
+    for name in (n for n in names if "_dw_" in n):
+        for ranges in (1, 3) if dims in CHUNKS[-2:] else (1,):
+            monkeypatch.setenv("MXC_FORCE_WGRAD", f"{name}/{ranges}")
+            assert mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BWD_WEIGHT, *dims, run.dt, run.lay) >= ranges * 4 * w.size or ranges == 1
+            check(run.bwd_weight(x, dy_bad), ref, den, "f32", False, ("bwd_weight", name, dims, ranges))
+            assert mxc.mxc_last_variant().endswith(name)
+
+
 # bf16 layers of ragged K: general, several classes, strided and unstrided first layers (their packings have empty places
 # in the filter, too), channels of both tensors ragged, no padding
 RAGGED = [
