@@ -1,0 +1,78 @@
+"""Which kernel a layer gets by itself, and what it computes on either side of each line between two: layers that grow from one image to
+many, of which the first image holds small whole numbers (exact in bf16 and in sums of any order) and the others zeros, so that the
+first image's results and the weight gradient stay the same bits whichever kernel ran."""
+import numpy as np
+import pytest
+import torch
+
+from tests import util
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mxc():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1512_01274_amd import mxc as m
+    return m
+
+
+# dtype, layout, (C, H, W, K, R, S, stride, pad), batches, and for forward, dx and dw what the names of some batches' kernels hold and
+# those of others do not ("": all do)
+CHOICES = [
+    ("bf16", "nhwc", (64, 28, 28, 72, 3, 3, 1, 1), (1, 4, 12, 24, 48, 96, 192, 320), ("igemm_wave", "igemm_wave", "wgrad_wave")),
+    ("bf16", "nchw", (64, 28, 28, 72, 3, 3, 1, 1), (1, 4, 12, 24, 48, 96, 192, 320), ("igemm_wave", "igemm_wave", "wgrad_wave")),
+    ("bf16", "nhwc", (128, 20, 22, 128, 3, 3, 2, 1), (1, 4, 12, 24, 48, 96, 192, 384), ("igemm_wave", "igemm_wave", "")),
+    ("bf16", "nhwc", (3, 91, 91, 40, 5, 5, 1, 2), (1, 4, 16, 64, 131), ("igemm_wave", "taps_dx", "wgrad_wave")),
+    ("f32", "nhwc", (32, 20, 22, 48, 3, 3, 1, 1), (1, 4, 12, 24, 48, 96, 192), ("f32_wave", "", "")),
+    ("f32", "nhwc", (32, 20, 22, 48, 3, 3, 2, 1), (1, 4, 12, 24, 48, 96, 192), ("f32_wave", "f32_wave", "")),
+    ("f32", "nchw", (16, 16, 16, 32, 3, 3, 1, 1), (1, 4, 12, 24, 48, 96, 192), ("f32_wave", "f32_wave", "")),
+]
+
+
+def _walk(mxc, oracle, dtype, layout, shape, batches):
+    """The kernels' names, batch by batch, in each pass; every result compared with the oracle's of the first image."""
+    C, H, W, K, R, S, st, pad = shape
+    P, Q = (H + 2 * pad - R) // st + 1, (W + 2 * pad - S) // st + 1
+    rng = np.random.default_rng(C * K + st)
+    x, w, dy = (rng.integers(-2, 3, d).astype(np.float32) for d in ((1, C, H, W), (K, C, R, S), (1, K, P, Q)))
+    mask = rng.integers(0, 2, x.shape).astype(np.float32)
+    want = oracle.conv2d_fwd(x, w, st, pad), oracle.conv2d_bwd_data(dy, w, x.shape, st, pad) * mask, oracle.conv2d_bwd_weight(x, dy, w.shape, st, pad)
+    rounded = [torch.from_numpy(a).to(torch.bfloat16 if dtype == "bf16" and n < 2 else torch.float32).double().numpy() for n, a in enumerate(want)]
+    names = ([], [], [])
+    for n in batches:
+        dims = (n, *shape)
+        run = util.Runner(mxc, dims, dtype, layout)
+        a = (*dims, run.dt, run.lay)
+
+        def grown(first):
+            t = torch.zeros(n, first.size, dtype=run.tdtype, device="cuda")
+            t[0] = run._in(first).reshape(-1)
+            return t
+
+        out = [torch.full((size,), 7.0, dtype=t, device="cuda") for size, t in ((n * K * P * Q, run.tdtype), (n * x.size, run.tdtype), (w.size, torch.float32))]
+        mxc.mxc_conv2d_fwd(*a, grown(x), run._in(w), out[0], run._ws(mxc.MXC_FWD))
+        names[0].append(mxc.mxc_last_variant())
+        mxc.mxc_conv2d_bwd_data_relu(*a, grown(dy), run._in(w), grown(mask), out[1], run._ws(mxc.MXC_BWD_DATA_RELU))
+        names[1].append(mxc.mxc_last_variant())
+        mxc.mxc_conv2d_bwd_weight(*a, grown(x), grown(dy), out[2], run._ws(mxc.MXC_BWD_WEIGHT))
+        names[2].append(mxc.mxc_last_variant())
+        for i, shape_i in enumerate(((1, K, P, Q), x.shape)):
+            t = out[i].view(n, -1)
+            assert np.array_equal(run._out(t[0], shape_i), rounded[i]), (n, names[i][-1])
+            assert not bool(t[1:].any()), (n, names[i][-1])
+        got = out[2].double().cpu().numpy()
+        got = got.reshape(K, R, S, C).transpose(0, 3, 1, 2) if layout == "nhwc" else got.reshape(w.shape)
+        assert np.array_equal(got, rounded[2]), (n, names[2][-1])
+    return names
+
+
+@pytest.mark.parametrize("dtype,layout,shape,batches,kernels", CHOICES)
+def test_either_side_of_a_choice(mxc, oracle, monkeypatch, dtype, layout, shape, batches, kernels):
+    monkeypatch.delenv("MXC_FORCE_VARIANT", raising=False)
+    monkeypatch.delenv("MXC_FORCE_WGRAD", raising=False)
+    names = _walk(mxc, oracle, dtype, layout, shape, batches)
+    for got, kernel in zip(names, kernels):
+        print(got)
+        held = {kernel in name for name in got}
+        assert held == ({True, False} if kernel else {True}), got
