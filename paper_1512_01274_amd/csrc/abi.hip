@@ -567,6 +567,7 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
         }
         MXC_TRY(bwd_data_nhwc(s, MXC_BF16, dy2, first ? w2 : b, dx2, post2, fws, ws, st, dry, inner, !first));
         if (dry || !run || direct.stored) return MXC_OK;
+        if (post2.planes != nullptr) return MXC_ERR_LAUNCH;      // the mask was left in the planes' layout for that store alone
         const Resum rs{without_padding(s), true, (const bf16_t *)a, (const bf16_t *)(mode == FILTER_PREPARED ? wc : b)};
         if (first) {
             MXC_TRY(launch_transpose(dx2, out, s.N, s.H * s.W, C, 2, st));
