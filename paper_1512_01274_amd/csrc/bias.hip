@@ -177,9 +177,12 @@ BiasPlan plan(long long N, int K, long long PQ, int dtype, int layout)
         if (most < 1) most = 1;
         if (parts > most) parts = most;
         if (parts > N) parts = N;
-        // Up to 64 KB of a channel one workgroup is done before the second launch would be: 48 KB of 25x25 planes 5.8 -> 3.9 us, 64 KB
-        // 5.9 -> 4.4, of 7x7 planes 5.8 -> 5.1; from 96 KB of those and 128 KB of the others on two launches are even or faster.
-        if (N * per_image <= 64 << 10) parts = 1;
+        // Up to 64 KB of a channel one workgroup is done before the second launch would be, if its threads have at most 20 loads; elements
+        // behind a plane's last whole piece are loads of their own, and four at a time are in flight.  us, one launch / two, bf16, 16
+        // channels: 48 KB of 8x8 planes, 12 loads 3.3 / 4.4; 64 KB, 16 loads 3.7 / 4.5, of 14x14 planes, 18 loads 4.8 / 4.8, of 5x5, 21 loads
+        // 6.5 / 5.6, of 9 elements, 28 loads 7.8 / 5.7, of 15, 68 loads 9.2 / 6.6, of one, 128 loads 16.1 / 7.3.  Over 197 sizes of both types one
+        // launch takes 0.83 of the time of two at 14-16 loads, 0.89 at 16-20, 1.05 at 20-24, 1.29 above 40.
+        if (N * per_image <= 64 << 10 && N * (PQ / V + PQ % V) <= 20 * 256) parts = 1;
         b.parts = (int)(parts < 1 ? 1 : parts);
         return b;
     }

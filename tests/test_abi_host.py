@@ -243,6 +243,17 @@ def test_bias_gradient_limits(mxc):
         assert mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BIAS_GRAD, *dims, dt, mxc.MXC_NHWC) > 0
 
 
+def test_bias_gradient_of_many_small_planes_is_shared(mxc):
+    """NCHW: elements behind a plane's whole 16-byte pieces are loads of their own, and planes of fewer than a piece hold nothing else;
+    one workgroup per channel would walk them one after another.  The scratch holds a partial sum per share and channel."""
+    size = lambda n, pq, dt: mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BIAS_GRAD, n, 1, pq, 1, 64, 1, 1, 1, 0, dt, mxc.MXC_NCHW)  # noqa: E731
+    one = size(1, 1, mxc.MXC_BF16)
+    for n, pq, dt in [(32768, 1, mxc.MXC_BF16), (4681, 7, mxc.MXC_BF16), (2730, 12, mxc.MXC_BF16), (16384, 1, mxc.MXC_F32), (5461, 3, mxc.MXC_F32)]:
+        assert size(n, pq, dt) >= 3 * one, (n, pq)
+    for n, pq, dt in [(4096, 8, mxc.MXC_BF16), (668, 49, mxc.MXC_BF16), (4096, 4, mxc.MXC_F32)]:
+        assert size(n, pq, dt) == one, (n, pq)
+
+
 def test_bias_gradient_shares_of_planes():
     """The two 31-bit counts of the NCHW kernel, over the plan's rule replayed here: whole 16-byte pieces of a workgroup's planes,
     and its planes times the elements behind the last piece."""
