@@ -260,13 +260,9 @@ __global__ __launch_bounds__(256) void relayout4_kernel(const RelayJobs jobs)
 {
     constexpr int PITCH = TILE + 1;
     __shared__ uint32_t tile[TILE * PITCH];
-    unsigned blk = blockIdx.x;
-    RelayJob q = jobs.job[0];
-#pragma unroll
-    for (int i = 1; i < NJ; ++i) {
-        const unsigned before = i == 1 ? jobs.job[0].blocks : jobs.job[0].blocks + jobs.job[1].blocks;
-        if (blockIdx.x >= before) { q = jobs.job[i]; blk = blockIdx.x - before; }
-    }
+    const bool second = NJ == 2 && blockIdx.x >= jobs.job[0].blocks;
+    const RelayJob &q = jobs.job[second ? 1 : 0];
+    const unsigned blk = blockIdx.x - (second ? jobs.job[0].blocks : 0u);
     const unsigned gx = (unsigned)(q.cols + TILE - 1) / TILE, gy = (unsigned)q.run_tiles, b2 = blk / gx;
     const int c0 = (int)(blk % gx) * TILE, r0 = (int)(b2 % gy) * TILE, nr = min(TILE, q.rows - r0), nc = min(TILE, q.cols - c0);
     const long long b = b2 / gy;
@@ -491,6 +487,7 @@ static int launch_relayout(const RelayJobs &all, long long blocks, hipStream_t s
 
 int relayout4(const RelayJob *jobs, int n, hipStream_t st)
 {
+    if (n < 1 || n > 2) return MXC_ERR_UNSUPPORTED;
     RelayJobs all{};
     long long total = 0;
     for (all.n = 0; all.n < n; ++all.n) {
@@ -503,8 +500,7 @@ int relayout4(const RelayJob *jobs, int n, hipStream_t st)
     }
     const dim3 grid((unsigned)total), block(256);
     if (n == 1) hipLaunchKernelGGL(relayout4_kernel<1>, grid, block, 0, st, all);
-    else if (n == 2) hipLaunchKernelGGL(relayout4_kernel<2>, grid, block, 0, st, all);
-    else hipLaunchKernelGGL(relayout4_kernel<3>, grid, block, 0, st, all);
+    else hipLaunchKernelGGL(relayout4_kernel<2>, grid, block, 0, st, all);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 

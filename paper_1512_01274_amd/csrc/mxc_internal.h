@@ -286,7 +286,7 @@ struct RelayJob {
     int C, class_C, R, S, stride;
     unsigned blocks;
 };
-// up to MAX_RELAY_JOBS plain transposes of 4-byte elements in one launch
+// one or two plain transposes of 4-byte elements in one launch
 int relayout4(const RelayJob *jobs, int n, hipStream_t st);
 RelayJob relay_to_nhwc(const void *src, void *dst, int n, int c, int hw, int c_pitch);      // [n][c][hw] -> [n][hw][c_pitch]
 RelayJob relay_to_nchw(const void *src, void *dst, int n, int c, int hw, int c_pitch);      // [n][hw][c_pitch] -> [n][c][hw]
