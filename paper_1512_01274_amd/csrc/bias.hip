@@ -192,7 +192,8 @@ BiasPlan plan(long long N, int K, long long PQ, int dtype, int layout)
     b.left = N * PQ % b.fold;
     const bool one = b.fold == 1 && b.rows <= 4096;
     b.cpb = b.chunks < (one ? 4 : BT) ? b.chunks : (one ? 4 : BT);
-    // wide rows: equal column blocks of at most 256 chunks, so that four row groups keep loads in flight
+    // wide rows: equal column blocks of at most 256 chunks, so that 1024 threads are four row groups with loads in flight (256 threads are
+    // one, with eight loads each)
     if (!one && b.cpb > MAX_CPB) b.cpb = MAX_CPB;
     if (one) { b.parts = 1; return b; }
     const long long col_blocks = (b.chunks + b.cpb - 1) / b.cpb;

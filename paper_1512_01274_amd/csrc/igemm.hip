@@ -692,7 +692,6 @@ __global__ __launch_bounds__(64 * WR * WC, (tile_min_blocks<BM, BN, BKT, NS, WR,
     igemm_tile<BM, BN, BKT, NS, WR, WC, false, TI>(p, m0, n_tile * BN, 0);
 }
 
-// the kernel's row steps: from load to load of a wave, and from store to store (64 lanes of 16 bytes over the wave's columns)
 // Whether the reduction runs over all taps of a block of bk channels before the next block: what the tiles of an XCD read of
 // a block then stays in its L2 from tap to tap.  Where the last block is not whole its empty chunks cost stages, which narrow tiles
 // of many channels repay (94864 pixels, 400 to 32 channels 3x3 94.9 -> 66.4 us, 151230, 288 to 32 5x5 240 -> 156, 20480, 352 to 24
@@ -709,6 +708,7 @@ inline int stages_of(int T, int Ci, int bk, int bn, long long M)
     return tap_inner_order(T, Ci, bk, bn, M) ? T * ((Ci + bk - 1) / bk) : (T * Ci + bk - 1) / bk;
 }
 
+// the kernel's row steps: from load to load of a wave, and from store to store (64 lanes of 16 bytes over the wave's columns)
 template <int BN, int BKT, int WR, int WC>
 void set_steps(RowStep &in, RowStep &out, int Mh, int Mw)
 {

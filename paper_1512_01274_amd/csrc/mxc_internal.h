@@ -359,10 +359,11 @@ size_t igemm_bwd_data_split_bytes(const ConvShape &s);   // scratch for a split 
 int igemm_bwd_data_prepare(const ConvShape &s, const void *w, void *wt, hipStream_t st, bool copy_in_place_filter, bool kcrs = false);
 // whether igemm_bwd_data reads this layer's filter as it is; otherwise relay_bwd_filter makes the form it reads
 bool bwd_data_reads_filter_in_place(const ConvShape &s);
-// ... or reads the KRSC filter it is handed in place although its prepared form is the re-packed one
-bool igemm_bwd_data_planes(const ConvShape &s, bool masked);
-bool bwd_data_classes_in_place(const ConvShape &s, bool masked);       // whether strided dx reads the KRSC filter itself
+// ... or reads the KRSC filter it is handed in place although its prepared form is the re-packed one; strided dx likewise
 bool bwd_data_small_in_place(const ConvShape &s, bool masked);
+bool bwd_data_classes_in_place(const ConvShape &s, bool masked);
+// whether dx of an NCHW problem, its filter re-packed, goes straight to its planes (see PlaneOut)
+bool igemm_bwd_data_planes(const ConvShape &s, bool masked);
 int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, void *dx, const void *wt, hipStream_t st,
                    const char **variant, const PostOp &post = PostOp(), void *split_ws = nullptr);
 // stride-1 backward-data whose result is stored un-packed from space-to-depth order: the kernel that can and should, or none
@@ -433,7 +434,7 @@ struct IgemmParams {
     int f32_out;         // store the fp32 accumulators to `partial` ([m][co], one split) instead of a rounded result to `out`
     int nt_out;          // the 16-byte result stores are non-temporal
     unsigned out_bytes;  // size of the output tensor when below 2 GiB (buffer stores with range-checked offsets), else 0
-    int tap_inner;       // reduction order (Ci % BKT == 0 only): 1 = all taps of a channel block before the next block
+    int tap_inner;       // reduction order (see tap_inner_order): 1 = all taps of a channel block before the next block
     // applied to the accumulators before the store (all optional)
     const float *bias;   // + bias[co]
     int relu;            // max(0, .)
