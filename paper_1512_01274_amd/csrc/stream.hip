@@ -11,9 +11,9 @@
 //     and stored;
 //   * waves are SPECIALISED: loader waves issue the asynchronous global->LDS loads of the ring and nothing
 //     else, compute waves read operands, run the MFMAs and store results.  Loads and stores then never share
-//     a wave's memory counter, which matters because a counter that holds both kinds can only be waited on
-//     to zero (they complete out of order with respect to each other), and that would empty the ring at every
-//     tile end.
+//     a wave's memory counter.  It counts both, and completion is reported in the order of issue (the AMDGPU
+//     backend's user guide, memory model of gfx90a and gfx942), so that a wait for a load would also wait for
+//     the stores issued before it, at every tile end.
 // One workgroup barrier per stage hands a landed stage to the compute waves and a consumed slot back to the
 // loaders.  Compute wave v owns rows 32v..32v+31 of the row tile and all BN columns (v_mfma_f32_32x32x16_bf16,
 // fp32 accumulators, which start from the bias); results leave through a per-wave LDS staging area as 16-byte
