@@ -14,9 +14,12 @@
  * One stride and one pad serve both axes; dilation 1, groups 1, no bias in the three plain calls;
  * cross-correlation (no filter flip); x outside the image reads as 0.
  * Infinities and NaN: in fp32, and in the gradients of bf16 layers whose K is no multiple of 8, a tap outside the image
- * is left out of the sum whatever the other operand holds.  Every other bf16 call multiplies padding, and the places
+ * is left out of the sum whatever the other operand holds.  Every other bf16 call may multiply padding, and the places
  * that the packings of first layers (C <= 4) leave empty, as zeros: there an infinite or NaN element of one operand
- * makes NaN of the results in whose window, or packed block, it meets such a place.  Finite inputs are not affected.
+ * makes NaN of the results in whose window, or packed block, it meets such a place.  Whether it does depends on the
+ * kernel that runs the layer, and so on its sizes (backward-data of first layers at stride 1 has one of either kind).
+ * A ReLU makes 0 of a NaN in fp32; in bf16 it makes 0 or, where the NaN has no sign, leaves it, by kernel again.
+ * Finite inputs are not affected.
  *
  * Common rules for every call.
  *   - All data pointers are DEVICE pointers on the current HIP device, 16-byte
@@ -338,8 +341,9 @@ int mxc_version(void);
  * family 5: their backward-weight, family 6: fp32 NHWC layers of whole 16-byte chunks of channels, backward-weight last,
  * family 7: dx of first layers at stride 1), NULL past the last.  These are the names that
  * mxc_last_variant() reports and that the tuning hooks MXC_FORCE_VARIANT=<name>[+<name of the shape for the
- * rows the last whole round leaves>] and MXC_FORCE_WGRAD=<name>[/<splits>] (environment, read per call) accept;
- * the tuning script and the tests walk the list.  Static host memory. */
+ * rows the last whole round leaves>] and MXC_FORCE_WGRAD=<name>[/<splits>] (environment, read per call) accept.
+ * The tests walk the list; the tuning script times families 0 to 2, whose plans it tabulates: the others are chosen
+ * beside a plan by time models.  Static host memory. */
 const char *mxc_tile_name(int family, int index);
 
 /* Tuning aid: the implicit GEMM (rows M, output columns Co, reduction length Kd) that the calling thread's last

@@ -10,6 +10,9 @@ Candidates are forced through the library's own tuning hooks (MXC_FORCE_VARIANT=
 MXC_FORCE_WGRAD=<tile>[/<splits>]), so what is timed is exactly what a table hit will run.  Between timed
 calls a 512 MiB buffer is rewritten so that a layer's operands come from HBM as they do inside a network
 step, not from the caches a repeated call would warm.  Inputs are random tensors of the layers' shapes.
+
+The tables hold plans of the tiled, the streaming and the window kernel.  Whether a wave kernel runs a layer in its plan's place is
+the library's choice by the time models of both; a table entry decides which plan is modelled.
 """
 import argparse
 import os
