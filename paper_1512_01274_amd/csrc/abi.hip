@@ -139,12 +139,14 @@ bool padded_k_resums_dx(const ConvShape &s8) { return s8.Kr != 0 && (s8.C <= 4 |
 bool padded_k_resums_dw(const ConvShape &s8) { return s8.Kr != 0 && s8.pad > 0; }
 
 // NHWC gradients of ragged K that are so small that one thread per result, in one launch, is done before the padded path's
-// launches are.  us, one thread / padded, launches of a graph, 450 shapes:
+// launches are.  us, one thread / padded, launches of a graph:
 // dx: the one-thread kernel takes 2.4 + 0.11 per step of its chain (K times the taps that reach a pixel, and two for every
-// tap it looks at) up to 2^18 results and more beyond; padding dy and the GEMM take 7, with resum_dx 11, first layers
-// 13-18 (where pixels of all stride classes share a wave, which then walks every tap).  128x4096 to 10 classes 5.5 / 7.3,
-// 8x64x14x14 3x3 K=4 8.1 / 11.8, K=6 10.2 / 11.5, K=9 13.4 / 10.9; 3x32x32 3x3 K=10 12.2 / 16.0, K=20 20.5 / 18.4; with
-// 400 thousand results 3x3 K=3 10.9 / 12.2, K=4 12.0 / 11.7, 1x1 K=28 7.2 / 7.3, K=36 8.2 / 7.3.
+// tap it looks at) up to 2^18 results and more beyond; padding dy and the GEMM take 5-6, with resum_dx 8-10, first layers
+// 8-14 (where pixels of all stride classes share a wave, which then walks every tap).  128x4096 to 10 classes 5.7 / 5.6,
+// 8x64x14x14 3x3 K=4 8.3 / 9.8, K=6 10.4 / 9.8, K=9 13.7 / 8.7; 3x32x32 3x3 K=10 11.7 / 7.8, K=20 20.1 / 8.3; with
+// 400 thousand results 3x3 K=3 10.8 / 10.8, K=4 12.0 / 10.8, 1x1 K=20 6.6 / 5.5, K=28 7.5 / 5.5.  Over 390 layers the faster of the two would
+// take 3.8% less than these lines' choices; no line moved by itself saves more than 0.2% of that.  Most of it is images of a few pixels,
+// whose chain counts taps that no pixel has (4x256, one pixel, 5x5 K=2: 3.3 / 9.8).
 bool small_ragged_dx(const ConvShape &s)
 {
     const bool first = s.C <= 4, resums = padded_k_resums_dx(with_padded_k(s));
@@ -155,11 +157,12 @@ bool small_ragged_dx(const ConvShape &s)
     if (out > 1 << 18) return chain <= (resums && !first ? 45 : 30);
     return chain <= (first ? 108 : resums ? 78 : 42);
 }
-// dw, by its multiply-adds, while the pixels are few enough for the one-thread kernel's ranges: 8x512 to 10 classes 4.5 / 5.3,
-// 32x512 to 10 5.5 / 5.2; 128x512 to 2 (131 thousand) 5.3 / 5.7, to 4 (262 thousand) 6.2 / 5.6; 28x28 64 to 1 channel 3x3 (451
-// thousand) 7.1 / 10.8, to 2 (903 thousand) 8.3 / 10.7, 8x14x14 64 to 2 (1.8 million) 11.1 / 11.1; 8x28x28 16 to 1 (6272 pixels)
-// 12.7 / 7.5.  Above 4 channels the line lies where heads break even; convolutions of 0.1-0.6 million, which the tests of ragged
-// channels want on the matrix cores, lose up to 1.7 us by it.
+// dw, by its multiply-adds, while the pixels are few enough for the one-thread kernel's ranges: 8x512 to 10 classes 4.5 / 5.2,
+// 32x512 to 10 5.5 / 5.2; 128x512 to 2 (131 thousand) 5.4 / 4.8, to 4 (262 thousand) 6.3 / 4.9; 28x28 64 to 1 channel 3x3 (451
+// thousand) 7.1 / 8.6, to 2 (903 thousand) 8.3 / 8.7, 8x14x14 64 to 2 (1.8 million) 11.3 / 8.9; 8x28x28 16 to 1 (6272 pixels)
+// 13.3 / 10.1.  Above 4 channels the line lies where heads break even; convolutions of 0.1-0.6 million, which the tests of ragged
+// channels want on the matrix cores, lose up to 2.3 us by it, first layers up to 6
+// (over 243 layers the faster of the two would take 4% less).
 bool small_ragged_dw(const ConvShape &s)
 {
     const long long m = (long long)s.N * s.P * s.Q;

@@ -1185,8 +1185,9 @@ const float kTileUs[N_TILES][3][5] = {
     {{}, {}, {3.62f, 0.817f, 4.20f, 6.48f, 0.596f}},
     {{1.89f, 1.75f, 0.f, 5.00f, 0.466f}, {2.08f, 2.62f, 0.f, 7.40f, 0.181f}, {1.22f, 3.00f, 1.30f, 9.73f, 0.736f}},
 };
-// The same for forward and backward-data of NCHW problems read in place (1218 passes of 440 layers; 2-5% off, dx 5-13%; the
-// first tile's fixed time is lower than the fit's 11.8, which cost a 1x1 16->96 layer on 20 37x37 images 13.7 us against 9.9).
+// The same for forward and backward-data of NCHW problems read in place (1218 passes of 440 layers; 2-5% off, dx 5-13%).  The first
+// tile's fixed time in forward is 8.0 and not the fit's 11.8: of the layers that get another kernel by it, 40 random ones run in 0.82 of the
+// time (0.62 to 1.08; 20x41x41 1x1 20 to 68 on 30 images 14.5 us against 19.5).
 const float kPlaneTileUs[N_TILES][2][5] = {
     {{8.0f, 0.682f, 0.513f, 4.33f, 0.277f}, {6.07f, 0.f, 4.23f, 2.47f, 0.513f}},
     {{8.07f, 1.13f, 1.66f, 5.17f, 0.142f}, {6.30f, 0.f, 3.25f, 4.71f, 0.327f}},
