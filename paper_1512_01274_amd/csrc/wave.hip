@@ -282,6 +282,7 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const std::condition
 
     // ---- results: this lane's columns n0 + 16*j + 4*g .. + 3 of pixel m0 + 16*b + i -------------------------------------
     const bool whole = NB > 1 && (p.Co & 7) == 0;     // uniform: results leave 16 bytes at a time
+    const bool masked = p.mask != nullptr && (!CLASSES || gr.Kd > 0);      // (what no tap reaches is 0 whatever the mask says)
     const out_rsrc_t rs_bias = make_out_rsrc(const_cast<float *>(p.bias), p.bias != nullptr ? (unsigned)p.Cw * 4u : 0u);
     float bias[4 * NB];
     u32x4 mask[NB > 1 ? NB / 2 : 1];
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const std::condition
             at = (((long long)n * p.Ho + (row * p.out_mul_h + gr.out_off_h)) * p.Wo + (col * p.out_mul_w + gr.out_off_w)) * p.Co + n0;
         }
         if (m >= gr.M) at = -1;
-        if (whole && p.mask != nullptr) {
+        if (whole && masked) {
 #pragma unroll
             for (int j = 0; j < NB; j += 2)
                 mask[j / 2] = at >= 0 && n0 + col16(j) < p.Co ? *reinterpret_cast<const u32x4 *>(p.mask + at + col16(j)) : u32x4{0, 0, 0, 0};
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(64 * KG * MG) void wave_kernel(const std::condition
                 const u32x2 s0 = __builtin_amdgcn_permlane16_swap(pair(4 * j), pair(4 * j + 4), false, false);
                 const u32x2 s1 = __builtin_amdgcn_permlane16_swap(pair(4 * j + 2), pair(4 * j + 6), false, false);
                 u32x4 o = {s0.x, s1.x, s0.y, s1.y};
-                if (p.mask != nullptr) {
+                if (masked) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = mask_bf16x2(o[e], mask[j / 2][e]);
                 }
@@ -610,20 +611,22 @@ static ClassDims class_dims(const ConvShape &s, int ph, int pw)
 
 // The shape for dx at stride 2 and its modelled time (us, fitted to 160 layers of up to 20 GFLOP, 9-13% off): fixed + turn * (tiles times
 // steps per wave and CU, at least the longest class's) + longest * (the longest class's steps) + tile * (tiles per CU) + mb * (MB written and
-// of the mask read); and that of the re-packed filter, the tile kernel's launch over the classes and, for 1x1, the one of zeros (8% off).
+// of the mask read, which is where a tap reaches); and that of the re-packed filter and the tile kernel's launch over the classes (8%
+// off).  A 1x1 filter reaches one class of four and zeros are a launch of their own: a fit of its own, to 294 layers with and without a
+// mask, 9% off.  (With the mask of all pixels counted in a fit for both it was 24% too long for masked layers, and layers went to the
+// wave kernel that take longer there: 63 images of 29x29, 216 to 176 channels 15.7 us and 26.6, 146 of 42x42, 192 to 176 37.5 and 67.7.)
 int wave_best_classes(const ConvShape &s, bool masked, double *us, double *other)
 {
     static const struct { int shape; float fixed, turn, longest, tile, mb; } kUs[] = {
         {2, 2.44f, 0.492f, 0.114f, 1.28f, 1.20f}, {3, 2.57f, 0.603f, 0.f, 1.34f, 1.00f}, {5, 2.71f, 0.538f, 0.f, 1.28f, 0.809f},
         {7, 3.24f, 0.258f, 0.112f, 0.611f, 0.046f}, {8, 3.32f, 0.353f, 0.197f, 0.856f, 0.098f}};
-    const double mb = 2e-6 * s.N * s.H * s.W * s.C * (masked ? 2 : 1);
-    double gflop = 0, zeros = 0, longest = 0;
+    double gflop = 0, zeros = 0, longest = 0, mb = 0;
     int best = -1;
     for (const auto &u : kUs) {
         const WaveShape &w = kShapes[u.shape];
         const int bm = 16 * w.mb * w.mg, n_tiles = (s.C + 16 * w.nb - 1) / (16 * w.nb);
         double tiles = 0, steps = 0, most = 0;
-        gflop = zeros = longest = 0;
+        gflop = zeros = longest = mb = 0;
         for (int ph = 0; ph < s.stride; ++ph)
             for (int pw = 0; pw < s.stride; ++pw) {
                 const ClassDims c = class_dims(s, ph, pw);
@@ -635,11 +638,13 @@ int wave_best_classes(const ConvShape &s, bool masked, double *us, double *other
                 if (Kd > longest) longest = Kd;
                 gflop += 2e-9 * rows * Kd * ((s.C + 63) / 64 * 64);
                 if (Kd == 0) zeros += 2e-6 * rows * s.C;
+                else mb += 2e-6 * rows * s.C * (masked ? 2 : 1);
             }
-        const double t = u.fixed + u.turn * (steps > most ? steps : most) + u.longest * most + u.tile * (tiles > 1 ? tiles : 1) + u.mb * mb;
+        const double t = u.fixed + u.turn * (steps > most ? steps : most) + u.longest * most + u.tile * (tiles > 1 ? tiles : 1) + u.mb * (mb + zeros);
         if (best < 0 || t < *us) { best = u.shape; *us = t; }
     }
-    *other = 8.45 + 0.774 * gflop + 0.385 * mb + 0.127 * zeros + 0.00668 * longest + (s.R == 1 ? 0.2 : 0) + 0.52 * 2e-6 * s.K * s.C * s.R * s.S;
+    if (s.R * s.S == 1) *other = 9.28 + 0.902 * gflop + 0.125 * mb + 0.206 * zeros + 0.133 * 2e-6 * s.N * s.P * s.Q * s.K;
+    else *other = 8.45 + 0.774 * gflop + 0.385 * (mb + zeros) + 0.127 * zeros + 0.00668 * longest + 0.52 * 2e-6 * s.K * s.C * s.R * s.S;
     return best;
 }
 
