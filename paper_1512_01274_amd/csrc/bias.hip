@@ -10,6 +10,7 @@ namespace {
 
 constexpr int BT = 1024;
 constexpr int SHORT_CHUNKS = 4096;   // 64 KB
+constexpr int SHORT_CPB = 64;        // 256 threads are four row groups
 constexpr int MAX_CPB = 256;      // 16-byte chunks of a row that a workgroup covers
 
 template <typename T> constexpr int VEC = 16 / (int)sizeof(T);
@@ -33,8 +34,8 @@ template <typename T> __device__ __forceinline__ void add_vec(float (&acc)[VEC<T
 // a multiple of a chunk, else up to 8), so that a chunk covers the same channels in every row.  Workgroup (x, y) owns
 // chunks [x*cpb, x*cpb + cpb) of the rows [y*rows_per_wg, + rows_per_wg); its 1024 threads form 1024/cpb row groups,
 // whose sums meet in LDS (in two steps, each in ascending order).  out: [gridDim.y][width].  (1024 threads with four loads each in
-// flight, or BT = 256 with eight for shares up to 64 KB, where starting and joining sixteen waves is most of the time: 32 KB
-// 3.4 -> 2.7 us, 55 shares of 33 KB 4.7 -> 4.1.)
+// flight, or BT = 256 with eight for shares up to 64 KB of at most 64 chunks a row, where starting and joining sixteen waves is most of the
+// time: 32 KB 3.4 -> 2.7 us, 55 shares of 33 KB 4.7 -> 4.1.)
 template <typename T, int BT>
 __global__ __launch_bounds__(BT) void bias_grad_rows_kernel(const uint4 *__restrict__ dy, float *__restrict__ out, long long rows, int chunks,
                                                             int cpb, int rows_per_wg)
@@ -192,8 +193,7 @@ BiasPlan plan(long long N, int K, long long PQ, int dtype, int layout)
     b.left = N * PQ % b.fold;
     const bool one = b.fold == 1 && b.rows <= 4096;
     b.cpb = b.chunks < (one ? 4 : BT) ? b.chunks : (one ? 4 : BT);
-    // wide rows: equal column blocks of at most 256 chunks, so that 1024 threads are four row groups with loads in flight (256 threads are
-    // one, with eight loads each)
+    // wide rows: equal column blocks of at most 256 chunks, so that 1024 threads are four row groups with loads in flight
     if (!one && b.cpb > MAX_CPB) b.cpb = MAX_CPB;
     if (one) { b.parts = 1; return b; }
     const long long col_blocks = (b.chunks + b.cpb - 1) / b.cpb;
@@ -222,7 +222,9 @@ int run(const BiasPlan &b, long long N, int K, long long PQ, int layout, const T
     if (per > 0x7FFFFFFFll) return MXC_ERR_SHAPE;
     const int used = (int)((b.rows + per - 1) / per);          // 0: only left-over pixels
     const dim3 grid((unsigned)((b.chunks + b.cpb - 1) / b.cpb), (unsigned)used);
-    if (used > 0 && per * b.cpb <= SHORT_CHUNKS)
+    // Few long rows leave 256 threads one or two row groups and each a chain of loads.  Time with 256 threads over that with 1024, 438 tensors
+    // of 8 to 1024 channels, by chunks a row: below 8 0.86, 8-64 0.95 (1.05 at worst), 64-128 1.01 (1.08), 128-256 1.09 (1.17).
+    if (used > 0 && b.cpb <= SHORT_CPB && per * b.cpb <= SHORT_CHUNKS)
         hipLaunchKernelGGL((bias_grad_rows_kernel<T, 256>), grid, dim3(256), 0, st, (const uint4 *)dy, out, b.rows, b.chunks, b.cpb, (int)per);
     else if (used > 0)
         hipLaunchKernelGGL((bias_grad_rows_kernel<T, BT>), grid, dim3(BT), 0, st, (const uint4 *)dy, out, b.rows, b.chunks, b.cpb, (int)per);
