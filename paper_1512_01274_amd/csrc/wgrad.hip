@@ -635,7 +635,7 @@ Plan search_plan(const WgradGeom &g, int forced, int forced_splits)
                 best = t_us;
                 long long span = (M + sp - 1) / sp;
                 span = (span + tc.bp - 1) / tc.bp * tc.bp;
-                best_pl = Plan{t, k_tiles, n_tiles, (int)((M + span - 1) / span), (int)span, {-1, 0, 0}};
+                best_pl = Plan{t, k_tiles, n_tiles, (int)((M + span - 1) / span), (int)span, {{-1, 0, 0}, {-1, 0, 0}}};
             }
         }
     }
