@@ -26,6 +26,7 @@ CHOICES = [
     ("bf16", "nhwc", (3, 91, 91, 40, 5, 5, 1, 2), (1, 4, 16, 64, 131), ("igemm_wave", "taps_dx", "wgrad_wave")),
     ("f32", "nhwc", (32, 20, 22, 48, 3, 3, 1, 1), (1, 4, 12, 24, 48, 96, 192), ("f32_wave", "", "")),
     ("f32", "nhwc", (32, 20, 22, 48, 3, 3, 2, 1), (1, 4, 12, 24, 48, 96, 192), ("f32_wave", "f32_wave", "")),
+    ("f32", "nhwc", (192, 13, 13, 384, 3, 3, 1, 1), (1, 48, 192), ("f32_wave", "f32_wave", "f32_wave")),
     ("f32", "nchw", (16, 16, 16, 32, 3, 3, 1, 1), (1, 4, 12, 24, 48, 96, 192), ("f32_wave", "f32_wave", "")),
 ]
 
