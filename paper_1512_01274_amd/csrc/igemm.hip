@@ -1343,10 +1343,10 @@ bool bwd_data_small_in_place(const ConvShape &s, bool masked)
 // The wave kernel's shape that runs dx of a layer of stride 2, all residue classes in one launch that reads the KRSC filter as it is, or -1:
 // re-packed filter, tile kernel and zeros, each its own launch.  Of 420 layers (250 of them masked, 294 1x1) it is chosen in 286 and runs
 // those 2.2 times as fast (none slower): 9x10x10 128 to 128 channels 3x3 12.5 -> 4.7 us, 5x24x24 32 to 480 1x1 11.7 -> 4.1.  A prepared filter
-// saves the other path its first launch, and has to give the same bits: of 175 layers chosen 1.53 times as fast, five more than 3% slower (15%
+// saves the other path its first launch, and has to give the same bits: of 175 layers chosen 1.53 times as fast, six more than 3% slower (15%
 // at worst).  The margin is larger from 10 modelled us on, of 1x1 filters from 7.5.  Measured time over the other path's by the ratio of the
 // models: 1x1, below 8 us at 0.7-0.8 0.67 (0.82 at worst), 8-10 us at 0.6-0.8 0.96 (1.26), 10-20 us at 0.8-1 1.21 (1.56); 3x3, 10-20 us
-// at 0.5-0.6 0.55, with a prepared filter up to 1.37, at 0.6-0.8 0.97 (1.27).
+// at 0.5-0.6 0.55, with a prepared filter up to 1.37, at 0.6-0.8 0.98 (1.27).
 static int classes_wave(const ConvShape &s, bool masked)
 {
     if (s.stride != 2 || s.C % 8 != 0) return -1;

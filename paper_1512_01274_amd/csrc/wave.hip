@@ -613,7 +613,7 @@ static ClassDims class_dims(const ConvShape &s, int ph, int pw)
 // steps per wave and CU, at least the longest class's) + longest * (the longest class's steps) + tile * (tiles per CU) + mb * (MB written and
 // of the mask read, which is where a tap reaches); and that of the re-packed filter and the tile kernel's launch over the classes (8%
 // off).  A 1x1 filter reaches one class of four and zeros are a launch of their own: a fit of its own, to 294 layers with and without a
-// mask, 9% off.  (With the mask of all pixels counted in a fit for both it was 24% too long for masked layers, and layers went to the
+// mask, 9% off.  (With the mask of all pixels counted in a fit for both it was a quarter too long for masked layers, and layers went to the
 // wave kernel that take longer there: 63 images of 29x29, 216 to 176 channels 15.7 us and 26.6, 146 of 42x42, 192 to 176 37.5 and 67.7.)
 int wave_best_classes(const ConvShape &s, bool masked, double *us, double *other)
 {
