@@ -1,4 +1,7 @@
 """Host checks of the plans a thread keeps: a network's layers, walked a second time in turn, find every plan kept."""
+import struct
+import threading
+
 import pytest
 import torch
 
@@ -107,3 +110,38 @@ def test_answers_do_not_depend_on_what_was_asked_before(mxc):
         once = [size(d, op, dt) for d in asked]
         assert [size(d, op, dt) for d in reversed(asked)] == once[::-1]
         assert [size(d, op, dt) for d in asked] == once
+
+
+def test_a_new_thread_clears_little(mxc):
+    """The library's thread-local storage is allocated and cleared before a thread's first call: the sets of entries are not part of it."""
+    with open(mxc.raw()._name, "rb") as f:
+        head = f.read(64)
+        phoff, (phentsize, phnum) = struct.unpack_from("<Q", head, 32)[0], struct.unpack_from("<HH", head, 54)
+        f.seek(phoff)
+        table = f.read(phentsize * phnum)
+    sizes = [struct.unpack_from("<Q", table, i * phentsize + 40)[0] for i in range(phnum) if struct.unpack_from("<I", table, i * phentsize)[0] == 7]   # PT_TLS
+    assert len(sizes) == 1 and sizes[0] <= 16 << 10, sizes
+
+
+def test_threads_in_turn(mxc):
+    """Each thread searches for itself, once, and finds the same sizes; what it kept goes with it."""
+    dims = NETS["resnet50_b64"]
+    asked = [(op, d, dt) for d in dims for op in (mxc.MXC_FWD, mxc.MXC_BWD_DATA, mxc.MXC_BWD_WEIGHT) for dt in (mxc.MXC_BF16, mxc.MXC_F32)]
+    walk = lambda: [mxc.mxc_conv2d_workspace_bytes(op, *d, dt, mxc.MXC_NHWC) for op, d, dt in asked]  # noqa: E731
+    want, seen = walk(), []
+
+    def one():
+        got = walk()
+        first = mxc.mxc_plan_searches()
+        seen.append((got == want, walk() == want, first > 0, mxc.mxc_plan_searches() - first))
+
+    for _ in range(4):
+        t = threading.Thread(target=one)
+        t.start()
+        t.join()
+    together = [threading.Thread(target=one) for _ in range(4)]
+    for t in together:
+        t.start()
+    for t in together:
+        t.join()
+    assert seen == [(True, True, True, 0)] * 8
