@@ -161,8 +161,8 @@ bool small_ragged_dx(const ConvShape &s)
 // 32x512 to 10 5.5 / 5.2; 128x512 to 2 (131 thousand) 5.4 / 4.8, to 4 (262 thousand) 6.3 / 4.9; 28x28 64 to 1 channel 3x3 (451
 // thousand) 7.1 / 8.6, to 2 (903 thousand) 8.3 / 8.7, 8x14x14 64 to 2 (1.8 million) 11.3 / 8.9; 8x28x28 16 to 1 (6272 pixels)
 // 13.3 / 10.1.  Above 4 channels the line lies where heads break even; convolutions of 0.1-0.6 million, which the tests of ragged
-// channels want on the matrix cores, lose up to 2.3 us by it, first layers up to 6
-// (over 243 layers the faster of the two would take 4% less).
+// channels want on the matrix cores, lose up to 2.3 us by it, first layers up to 6 (over 243 layers the faster of the two would
+// take 4% less).
 bool small_ragged_dw(const ConvShape &s)
 {
     const long long m = (long long)s.N * s.P * s.Q;

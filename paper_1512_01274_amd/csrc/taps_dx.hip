@@ -14,9 +14,10 @@
 // What bounds it: the steps, of which the two barriers, the LDS reads of the taps and the latencies between them are most; dy itself comes
 // at 4.2 TB/s.  The ring is never drained: the stores of a step are issued after its loads, and the waits of the next step count them
 // as younger operations that may be open still.  (A wave's counter holds loads and stores alike and completion is reported in the order of
-// issue: the AMDGPU backend's user guide, memory model of gfx90a and gfx942.)  Products of pixels outside dy are stored as zeros, so that the sum needs no condition (conditional reads, which became branches
-// with a wait each, took 73 us where this takes 48).  Measured (us, packing + GEMM + compaction -> here): 32x224x224, 64 channels to 3,
-// 3x3 69.8 -> 48.5; 3x115x70, 64 to 3 22.7 -> 5.6; 23x25x25, 112 to 3, 5x5 58.5 -> 12.3.
+// issue: the AMDGPU backend's user guide, memory model of gfx90a and gfx942.)  Products of pixels outside dy are stored as zeros, so that
+// the sum needs no condition (conditional reads, which became branches with a wait each, took 73 us where this takes 48).  Measured (us,
+// packing + GEMM + compaction -> here): 32x224x224, 64 channels to 3, 3x3 69.8 -> 48.5; 3x115x70, 64 to 3 22.7 -> 5.6; 23x25x25, 112 to 3,
+// 5x5 58.5 -> 12.3.
 #include "mxc_internal.h"
 #include "plan_cache.h"
 

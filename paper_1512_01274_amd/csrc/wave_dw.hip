@@ -268,9 +268,9 @@ int wave_dw_ranges(long long M, int ranges, int *span)
 
 // copies: x and dy have just been written by the launch before, so a CU's loads find them in no cache of its own XCD.  32x32, one
 // range, 112 x 80 filters: 0.25 us per step of the waves where they lie in the L2, 0.8 as copies (48 images of 11x16: 12.0 and 32.0 us;
-// 16 to 64 channels 3x3 13.6 and 21.3), and a third launch in a row costs its 2.6 us in full.  The model's term
-// is 0.3 a step for every shape: over 220 gradients of copies its choices take as long as with 0.55 (within 0.1% in the mean), and 4.5% less than
-// without a term.
+// 16 to 64 channels 3x3 13.6 and 21.3), and a third launch in a row costs its 2.6 us in full.  The model's
+// term is 0.3 a step for every shape: over 220 gradients of copies its choices take as long as with 0.55 (within 0.1% in the mean), and
+// 4.5% less than without a term.
 int wave_dw_best(const WgradGeom &g, bool copies, int max_ranges, int *ranges, double *us)
 {
     const long long M = (long long)g.N * g.P * g.Q;
