@@ -23,6 +23,7 @@
 // workgroups into fp32 partial tiles that a finishing kernel adds in a fixed order.  A large 1x1
 // filter can be read in place for backward-data (BT kernels: transposed LDS tiles).  The epilogue
 // can add a bias, apply ReLU, and zero results under a mask.
+#include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -102,8 +103,14 @@ struct GridPos {
 // [reduction row][BN output columns] and its MFMA fragments come from ds_read_b64_tr_b16.
 // TI = true: channel-block-major reduction order (see tap_inner_order); a compile-time choice so that the
 // stage body is one basic block and the pinned interleave of address work and MFMAs survives.
+// ZR = true: dx of a 1x1 filter at stride 2.  The rows of the GEMM are the pixels of even row and column; the other three of each 2x2
+// block, which no tap reaches, are written as zeros beside them.  What bounds it is writing dx, of which the GEMM by itself
+// has a quarter in pieces of one pixel.  us, the zeros as a launch of their own -> here, tensors coming from memory: 512 to 256 channels at
+// 56x56, batch 256, 149 -> 143 (4.3 TB/s), with a mask 172 -> 156; 240 to 320, batch 128 86 -> 61 and 106 -> 88; 176 to 176 at 70x70,
+// batch 100, 69 -> 56; small layers lose the launch: 256 to 128 at 28x28, batch 64, 12.6 -> 9.2.  (Half of the workgroups writing
+// their zeros before the reduction, so that not all write at once: 0.98 to 1.25 of this.)
 // Runs the output tile whose first row is m0 and first column n0 (split_z: its share of a split reduction).
-template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT, bool TI>
+template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT, bool TI, bool ZR = false>
 __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, const int n0, const int split_z)
 {
     constexpr int NW = WR * WC, NT = 64 * NW;
@@ -525,6 +532,9 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
         const int st_r = lane / CPR, st_c = lane % CPR;
         unsigned st_off[MI][NST];
         uint4 st_mask[MI][NST];
+        // ZR: whether the pixel to the right of the store's is in the image (bit of z_right), and the one below (z_below)
+        static_assert(MI * NST <= 32, "a bit per store");
+        [[maybe_unused]] unsigned z_right = 0, z_below = 0;
         if (fast_store) {
             const bool col_ok = n0 + wave_n + st_c * 8 < p.Co;
             const int m = m0 + wave_m + st_r, co2 = p.Co * 2;      // this lane's row of the first store; RPI further for each next
@@ -539,6 +549,10 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
 #pragma unroll
                 for (int k = 0; k < MI * NST; ++k) {
                     st_off[k / NST][k % NST] = col_ok && m + k * RPI < p.m_end ? off : OOB;
+                    if constexpr (ZR) {
+                        z_right |= 2 * g.b + 1 < p.Wo ? 1u << k : 0u;
+                        z_below |= 2 * g.a + 1 < p.Ho ? 1u << k : 0u;
+                    }
                     if (k + 1 < MI * NST)
                         off += (unsigned)g.advance(p.out_step, p.Mh, p.Mw, p.Ho * p.Wo * co2, p.out_mul_h * p.Wo * co2, p.out_mul_w * co2);
                 }
@@ -569,6 +583,15 @@ __device__ __forceinline__ void igemm_tile(const IgemmParams &p, const int m0, c
                     if (p.mask != nullptr) v = mask_bf16x8(v, st_mask[i][k]);
                     if (p.nt_out) buffer_store16_nt(rs_out, st_off[i][k], v);
                     else buffer_store16(rs_out, st_off[i][k], v);
+                    if constexpr (ZR) {            // (an offset that the resource rejects stays one: the output is below 2^31)
+                        const int at = i * NST + k;
+                        const unsigned right = (unsigned)(p.Co * 2), below = (unsigned)p.Wo * right;
+                        const unsigned o1 = (z_right >> at) & 1 ? st_off[i][k] + right : OOB, o2 = (z_below >> at) & 1 ? st_off[i][k] + below : OOB;
+                        const unsigned o3 = (z_below >> at) & 1 ? o1 + below : OOB;
+                        const uint4 z = make_uint4(0, 0, 0, 0);
+                        if (p.nt_out) { buffer_store16_nt(rs_out, o1, z); buffer_store16_nt(rs_out, o2, z); buffer_store16_nt(rs_out, o3, z); }
+                        else { buffer_store16(rs_out, o1, z); buffer_store16(rs_out, o2, z); buffer_store16(rs_out, o3, z); }
+                    }
                 }
             } else {
 #pragma unroll
@@ -645,7 +668,7 @@ __device__ __forceinline__ int tile_unit(int units)
 template <int BM, int BN, int BKT, int NS, int WR, int WC>
 constexpr int tile_min_blocks = (WR * WC == 4 && NS * (BM + BN) * BKT * 2 <= 80 * 1024) ? 2 : 1;
 
-template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT, bool TI>
+template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT, bool TI, bool ZR = false>
 __global__ __launch_bounds__(64 * WR * WC, (tile_min_blocks<BM, BN, BKT, NS, WR, WC>)) void igemm_kernel(const IgemmParams p)
 {
     const int total = p.m_tiles * p.n_tiles;
@@ -653,7 +676,7 @@ __global__ __launch_bounds__(64 * WR * WC, (tile_min_blocks<BM, BN, BKT, NS, WR,
     const int unit = tile_unit(units);
     if (unit >= units) return;
     const int logical = unit % total;
-    igemm_tile<BM, BN, BKT, NS, WR, WC, BT, TI>(p, p.m_begin + (logical / p.n_tiles) * BM, (logical % p.n_tiles) * BN, unit / total);
+    igemm_tile<BM, BN, BKT, NS, WR, WC, BT, TI, ZR>(p, p.m_begin + (logical / p.n_tiles) * BM, (logical % p.n_tiles) * BN, unit / total);
 }
 
 // Strided backward-data: all residue classes of (h+pad, v+pad) mod stride that some tap reaches in one launch, the classes
@@ -717,6 +740,10 @@ void set_steps(RowStep &in, RowStep &out, int Mh, int Mw)
     out = row_step(64 % CPR == 0 ? 64 / CPR : 1, Mh, Mw);
 }
 
+// the tiles that are built with ZR: those that read the filter in place as well (has_bt)
+template <int BM, int BN, int NW>
+constexpr bool tile_zeroes = (BM == 128 && BN <= 128 && NW == 4) || (BM == 256 && BN == 256) || (BM == 64 && BN == 128);
+
 // Launches the tile shape on GEMM rows [m_begin, m_end) of the problem (m_end < 0: to the last row).
 template <int BM, int BN, int BKT, int NS, int WR, int WC, bool BT = false>
 int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end = -1)
@@ -752,6 +779,16 @@ int launch(IgemmParams p, hipStream_t st, long long m_begin = 0, long long m_end
     const long long total = (long long)p.m_tiles * p.n_tiles * (p.splits > 1 ? p.splits : 1);
     if (total > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
     const int grid = (int)((total + 7) / 8) * 8;
+    if (p.zero_rest) {
+        if constexpr (tile_zeroes<BM, BN, WR * WC>) {
+            if (p.out_bytes == 0 || (p.Co & 7) != 0) return MXC_ERR_UNSUPPORTED;      // the buffer stores write them
+            // Non-temporal stores reach memory as they are: of rows that are no multiple of 64 bytes in pieces of less (dx of 1-900 MB, 176
+            // channels 71-350 us against 30-200, 80 channels 40-60 against 30-40; multiples of 32 channels gain from 200 MB on, 320 of them 1.3 times)
+            if (p.Co % 32 != 0) p.nt_out = 0;
+            hipLaunchKernelGGL((igemm_kernel<BM, BN, BKT, NS, WR, WC, BT, false, true>), dim3((unsigned)grid), dim3(64 * WR * WC), 0, st, p);
+            return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
+        } else return MXC_ERR_UNSUPPORTED;
+    }
     if (p.tap_inner) {
         hipLaunchKernelGGL((igemm_kernel<BM, BN, BKT, NS, WR, WC, BT, true>), dim3((unsigned)grid), dim3(64 * WR * WC), 0, st, p);
         return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
@@ -1340,13 +1377,45 @@ bool bwd_data_small_in_place(const ConvShape &s, bool masked)
     return 2.0 * M * s.C * Kd < 1e10;
 }
 
-// The wave kernel's shape that runs dx of a layer of stride 2, all residue classes in one launch that reads the KRSC filter as it is, or -1:
-// re-packed filter, tile kernel and zeros, each its own launch.  Of 420 layers (250 of them masked, 294 1x1) it is chosen in 286 and runs
-// those 2.2 times as fast (none slower): 9x10x10 128 to 128 channels 3x3 12.5 -> 4.7 us, 5x24x24 32 to 480 1x1 11.7 -> 4.1.  A prepared filter
-// saves the other path its first launch, and has to give the same bits: of 175 layers chosen 1.53 times as fast, six more than 3% slower (15%
-// at worst).  The margin is larger from 10 modelled us on, of 1x1 filters from 7.5.  Measured time over the other path's by the ratio of the
-// models: 1x1, below 8 us at 0.7-0.8 0.67 (0.82 at worst), 8-10 us at 0.6-0.8 0.96 (1.26), 10-20 us at 0.8-1 1.21 (1.56); 3x3, 10-20 us
-// at 0.5-0.6 0.55, with a prepared filter up to 1.37, at 0.6-0.8 0.98 (1.27).
+// Whether the launch of the GEMM can write the zeros too (ZR): dx of a 1x1 filter at stride 2
+static bool zeroes_rest(const ConvShape &s)
+{
+    return s.R * s.S == 1 && s.stride == 2 && s.pad % 2 == 0 && s.C % 8 == 0 && (long long)s.N * s.H * s.W * s.C * 2 < 0x7FFF0000ll;
+}
+static long long even_pixels(const ConvShape &s) { return (long long)s.N * ((s.H + 1) / 2) * ((s.W + 1) / 2); }
+
+// ... and the tile that runs it.  Time models (us, fitted to 580 such layers of up to 900 MB of dx, 6-10% off; of another 193 the chosen
+// tile takes 1.5% more than the fastest): launch, and the root of the squares of the CU's share of work (rounds of workgroups, stages,
+// tiles) and of the MB that are moved (dx, mask, dy once per column tile), which run beside each other.  The tiles' general model
+// knows no dx of four times its rows: 40071 pixels, 80 to 16 channels 14.2 -> 6.5 us.
+static int zeroing_tile(const ConvShape &s, bool masked, double *us)
+{
+    static const struct { int tile; float fixed, round, stage, area, out, mask, in; } kUs[] = {
+        {0, 4.16f, 0.903f, 0.563f, 1.69f, 0.144f, 0.171f, 0.052f}, {1, 1.12f, 9.03f, 0.294f, 0.267f, 0.165f, 0.205f, 0.165f},
+        {4, 3.20f, 1.52f, 0.732f, 1.34f, 0.227f, 0.090f, 0.f},     {6, 4.12f, 0.f, 1.149f, 1.84f, 0.200f, 0.058f, 0.014f},
+        {11, 3.44f, 0.559f, 0.724f, 3.27f, 0.104f, 0.294f, 0.022f}};
+    const long long M = even_pixels(s);
+    const int KT = (s.K + 63) / 64;
+    int best = -1;
+    for (const auto &u : kUs) {
+        const TileChoice &t = kTiles[u.tile];
+        const long long n_tiles = (s.C + t.bn - 1) / t.bn, per_cu = ((M + t.bm - 1) / t.bm * n_tiles + 255) / 256, rounds = (per_cu + t.slots - 1) / t.slots;
+        const double work = u.round * rounds + (u.stage * KT + u.area) * per_cu * t.bm * t.bn / 16384.0;
+        const double moved = 2e-6 * (u.out * s.N * s.H * s.W * s.C + (masked ? u.mask * M * s.C : 0.) + (double)u.in * M * s.K * n_tiles);
+        const double v = u.fixed + sqrt(work * work + moved * moved);
+        if (best < 0 || v < *us) { best = u.tile; *us = v; }
+    }
+    return best;
+}
+
+// The wave kernel's shape that runs dx of a layer of stride 2, all residue classes in one launch that reads the KRSC filter as it is, or -1.
+// Filters of several taps: against re-packed filter, tile kernel and zeros, each its own launch; of the layers it is chosen for none runs
+// slower: 9x10x10 128 to 128 channels 3x3 12.5 -> 4.7 us.  A prepared filter saves the other path its first launch, and has to give the
+// same bits: six of 175 layers more than 3% slower (15% at worst).  The margin is larger from 10 modelled us on.  Measured time over the
+// other path's by the ratio of the models: 10-20 us at 0.5-0.6 0.55, with a prepared filter up to 1.37, at 0.6-0.8 0.98 (1.27).
+// 1x1 filters: against the tile that writes the zeros too, one launch as well.  Of 193 layers the kernel chosen takes 3.4% more than the
+// fastest of the five wave shapes and five tiles, as much with a line at 0.95 or 1.05; the wave kernel takes 0.7-0.9 of the tile's time
+// below 5 us, as long at 5-6, 1.1 at 6-7.5, 1.4 at 7.5-10 and 1.5 to 2.1 above.
 static int classes_wave(const ConvShape &s, bool masked)
 {
     if (s.stride != 2 || s.C % 8 != 0) return -1;
@@ -1358,14 +1427,33 @@ static int classes_wave(const ConvShape &s, bool masked)
     static thread_local PlanCache<Key, int> cache;
     return cache.get(Key{s, masked}, [&] {
         ++g_plan_searches;
-        double us = 0, other = 0;
+        double us = 0, other = 0, tile_us = 0;
         const int wv = (long long)s.N * s.H * s.W <= 1 << 30 ? wave_best_classes(s, masked, &us, &other) : -1;
+        if (wv >= 0 && zeroes_rest(s)) return zeroing_tile(s, masked, &tile_us) >= 0 && us < 1.03 * tile_us ? wv : -1;
         return wv >= 0 && us < (us < (s.R * s.S == 1 ? 7.5 : 10) ? 0.8 : 0.5) * other ? wv : -1;
     });
 }
+
+// The plan of a 1x1 filter at stride 2: see zeroing_tile; the tuning hook's where it is set
+static Plan zeroing_plan(const ConvShape &s, bool masked)
+{
+    const long long M = even_pixels(s);
+    if (getenv("MXC_FORCE_VARIANT")) return choose_plan(M, s.C, s.K, true, masked);
+    g_key_M = M; g_key_Co = s.C; g_key_Kd = s.K;
+    double us = 0;
+    return Plan{zeroing_tile(s, masked, &us), -1, M};
+}
+
+// Whether dx at stride 2 of a call that is handed the KRSC filter itself reads it in place: the wave kernel always, and the tiles that
+// write the zeros: bound by what they write, they take 0.98 of the time on a filter that was re-packed first (90 layers of 10 to 84 GFLOP,
+// 0.92 to 1.02), 2 us less on small ones.
 bool bwd_data_classes_in_place(const ConvShape &s, bool masked)
 {
-    return real_c(s) == s.C && real_k(s) == s.K && classes_wave(s, masked) >= 0;
+    if (real_c(s) != s.C || real_k(s) != s.K) return false;
+    if (classes_wave(s, masked) >= 0) return true;
+    if (!zeroes_rest(s)) return false;
+    const Plan pl = zeroing_plan(s, masked);
+    return has_bt(pl.main) && (pl.tail < 0 || has_bt(pl.tail));
 }
 
 // whether dx of an NCHW problem, its filter re-packed, goes straight to its planes (see PlaneOut)
@@ -1420,7 +1508,7 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
         return wave_launch_classes(wv, s, p, st, bt);
     }
     IgemmClasses q{};
-    bool zeros = false;
+    bool zeros = false, zeroed = false;
     size_t wt_off = 0;
     long long rows = 0, area = 0;          // GEMM rows with taps, and their taps
     for (int ph = 0; ph < s.stride; ++ph) {
@@ -1442,10 +1530,14 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
             IgemmParams one = p;
             one.wm = c.wm; one.TR = c.TR; one.TS = c.TS; one.Mh = c.Mh; one.Mw = c.Mw;
             one.in_off_h = c.in_off_h; one.in_off_w = c.in_off_w; one.out_off_h = c.out_off_h; one.out_off_w = c.out_off_w;
-            const Plan pl = plan_for(one, (long long)s.N * c.Mh * c.Mw, s.C, c.TR * c.TS * s.K);
+            const bool rest = zeroes_rest(s);
+            const Plan pl = rest && !getenv("MXC_FORCE_VARIANT") ? zeroing_plan(s, p.mask != nullptr) : plan_for(one, (long long)s.N * c.Mh * c.Mw, s.C, c.TR * c.TS * s.K);
             if (pl.main == STREAM_TILE || (s.R == 1 && s.S == 1)) {
                 // one class alone (1x1), or one that the plan gives to the streaming kernel (short reductions): a launch of its own
-                const int rc = launch_plan(pl, one, st);
+                zeroed = rest && has_bt(pl.main) && (pl.tail < 0 || has_bt(pl.tail));
+                one.zero_rest = zeroed;
+                if (bt) { one.wm = (const bf16_t *)w_in_place; one.bt_w_bytes = (unsigned)((long long)s.K * s.C * 2); }
+                const int rc = launch_plan(pl, one, st, bt);
                 if (rc != MXC_OK) return rc;
                 *variant = plan_name(pl);
                 continue;
@@ -1458,7 +1550,7 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
             q.c[at] = c;
         }
     }
-    if (zeros) {
+    if (zeros && !zeroed) {
         unsigned zh = 0, zw = 0;
         for (int c = 0; c < s.stride; ++c) {
             zh |= c >= s.R ? 1u << c : 0u;

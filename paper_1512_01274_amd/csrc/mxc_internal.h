@@ -432,6 +432,7 @@ struct IgemmParams {
     int tap_row_inner;   // tap t = (column step)*TR + (row step) instead of (row step)*TS + (column step)
     S2DStore s2d;        // `out` is the image and not the GEMM's [m][co]
     int f32_out;         // store the fp32 accumulators to `partial` ([m][co], one split) instead of a rounded result to `out`
+    int zero_rest;       // dx of a 1x1 filter at stride 2: the three pixels of a 2x2 block that no tap reaches are written too, as zeros
     int nt_out;          // the 16-byte result stores are non-temporal
     unsigned out_bytes;  // size of the output tensor when below 2 GiB (buffer stores with range-checked offsets), else 0
     int tap_inner;       // reduction order (see tap_inner_order): 1 = all taps of a channel block before the next block
