@@ -1132,6 +1132,41 @@ int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_spl
     });
 }
 
+// Whether a plan's tiles read a filter in place in a small problem: see bwd_data_small_in_place
+bool small_in_place(const Plan &pl, long long M, int Co, int Kd)
+{
+    return !whole_launch(pl.main) && has_bt(pl.main) && (pl.tail < 0 || has_bt(pl.tail)) && 2.0 * M * Co * Kd < 1e10;
+}
+
+// The shape of the run kernel (runs.hip) that runs this GEMM, or -1: the wave kernel or the plan does, whichever it is without the run
+// kernel.  Those read the filter of small dx in place, where this one needs the re-pack, a launch of 4.3 us; of an NCHW problem
+// the wave kernel stores the result to its planes, which is a re-layout less.  Measured time over the other kernel's, mean and worst, by the
+// ratio of the models (320 layers of 0.4 to 400 GFLOP, forward and dx): below 0.7 0.66 / 0.95, at 0.7-0.8 0.76 / 0.99, at 0.8-0.9
+// 0.90 / 1.04, at 0.9-0.95 0.95 / 1.14, at 0.95-1 0.97 / 1.15, above 1 1.2 and more.  Plans of the streaming and window kernels come from
+// the measured table and stay.
+int run_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool planes)
+{
+    if (!run_applicable(p)) return -1;
+    const long long M = (long long)p.N * p.Mh * p.Mw;
+    const int Kd = p.TR * p.TS * p.Ci;
+    g_key_M = M; g_key_Co = p.Co; g_key_Kd = Kd;
+    if (const char *f = getenv("MXC_FORCE_VARIANT")) return run_forced(f, p);
+    struct Key { long long M; int Co, Ci, TR, TS; long long flags; };
+    static thread_local PlanCache<Key, int> cache;
+    return cache.get(Key{M, p.Co, p.Ci, p.TR, p.TS, (bwd ? 1 : 0) + (masked ? 2 : 0) + (can_split ? 4 : 0) + (planes ? 8 : 0)}, [&] {
+        ++g_plan_searches;
+        double us = 0, other = 0;
+        const int run = run_best(M, p.Co, p.Ci, p.TR, p.TS, masked, &us);
+        const int wave = wave_choice(M, p.Co, Kd, bwd, masked, can_split);
+        const Plan pl = choose_plan(M, p.Co, Kd, true, masked);
+        if (whole_launch(pl.main) || (wave >= 0 && planes)) return -1;
+        if (wave >= 0) wave_best(M, p.Co, Kd, bwd, masked, &other);
+        else other = plan_us(pl, M, p.Co, Kd, can_split ? split_count(M, p.Co, Kd) : 1, masked);
+        if (bwd && (wave >= 0 || small_in_place(pl, M, p.Co, Kd))) us += 4.3;
+        return us < 0.9 * other ? run : -1;
+    });
+}
+
 // out[m][co] = act(sum_z partial[z][m][co] + bias[co]) in ascending z (fixed order), 4 columns per thread
 __global__ __launch_bounds__(256) void split_finish_kernel(const float *__restrict__ partial, bf16_t *__restrict__ out, long long MC,
                                                            int Co, int Cw, int splits, const float *__restrict__ bias, int relu,
@@ -1222,6 +1257,10 @@ int igemm_fwd(const ConvShape &s, const void *x, const void *w, void *y, hipStre
     p.in_mul_h = s.stride; p.in_mul_w = s.stride; p.in_off_h = -s.pad; p.in_off_w = -s.pad;
     p.Ho = s.P; p.Wo = s.Q; p.out_mul_h = 1; p.out_mul_w = 1; p.out_off_h = 0; p.out_off_w = 0;
     const long long M = (long long)s.N * s.P * s.Q;
+    if (const int rv = run_choice(p, false, false, split_ws != nullptr && s.K % 8 == 0, post.planes != nullptr); rv >= 0) {
+        *variant = run_name(rv);
+        return run_launch(rv, p, st);
+    }
     if (const int wv = wave_choice(M, s.K, s.R * s.S * s.C, false, false, split_ws != nullptr && s.K % 8 == 0); wv >= 0) {
         *variant = wave_name(wv);
         return wave_launch(wv, p, st, false, post.planes);
@@ -1371,10 +1410,9 @@ bool bwd_data_small_in_place(const ConvShape &s, bool masked)
     if (real_c(s) != s.C || s.C % 8 != 0 || s.stride != 1 || bwd_data_reads_filter_in_place(s)) return false;
     const long long M = (long long)s.N * s.H * s.W;
     const int Kd = s.R * s.S * s.K;
+    if (run_choice(bwd_data_params(s), true, masked, true, false) >= 0) return false;
     if (wave_choice(M, s.C, Kd, true, masked, true) >= 0 || bwd_data_streams_filter(s, masked)) return true;
-    const Plan pl = choose_plan(M, s.C, Kd, true, masked);
-    if (whole_launch(pl.main) || !has_bt(pl.main) || (pl.tail >= 0 && !has_bt(pl.tail))) return false;
-    return 2.0 * M * s.C * Kd < 1e10;
+    return small_in_place(choose_plan(M, s.C, Kd, true, masked), M, s.C, Kd);
 }
 
 // Whether the launch of the GEMM can write the zeros too (ZR): dx of a 1x1 filter at stride 2
@@ -1491,6 +1529,10 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
         p.wm_by_k = bt && !bwd_data_reads_filter_in_place(s) && bwd_data_streams_filter(s, p.mask != nullptr);
         const long long M = (long long)s.N * s.H * s.W;
         const int Kd = s.R * s.S * s.K;
+        if (const int rv = bt ? -1 : run_choice(p, true, p.mask != nullptr, s.C % 8 == 0, post.planes != nullptr); rv >= 0) {
+            *variant = run_name(rv);
+            return run_launch(rv, p, st);
+        }
         if (const int wv = wave_choice(M, s.C, Kd, true, p.mask != nullptr, s.C % 8 == 0); wv >= 0) {
             *variant = wave_name(wv);
             return wave_launch(wv, p, st, bt, post.planes);

@@ -465,6 +465,12 @@ bool window_applicable(const IgemmParams &p);
 // two patches or more for every CU, at most a third of their rows past the image
 bool window_fills_chip(const IgemmParams &p);
 int window_launch(const IgemmParams &p, hipStream_t st);
+// runs.hip: the same GEMM for stride-1 filters of 3 or 5 columns whose output rows are as wide as the input's (see there)
+const char *run_name(int shape);
+int run_forced(const char *name, const IgemmParams &p);
+bool run_applicable(const IgemmParams &p);
+int run_best(long long M, int Co, int Ci, int TR, int TS, bool masked, double *us);      // the shape of least modelled time and that time
+int run_launch(int shape, IgemmParams p, hipStream_t st);
 
 // wave.hip: the same GEMM for problems that fill a fraction of the chip and for short reductions (see there).  Shapes are
 // numbered from 0; bwd: backward-data, whose shapes can all read the filter in place; bt: wm is the KRSC filter itself (see
