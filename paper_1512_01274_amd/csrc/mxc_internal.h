@@ -544,6 +544,15 @@ int wave_dw_best(const WgradGeom &g, bool copies, int max_ranges, int *ranges, d
 int wave_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const void *x, const void *dy, void *out, const DwMap *map, bool dw_bf16, int rows,
                    hipStream_t st);
 
+// runs_dw.hip: backward-weight of stride-1 filters of 3 or 5 columns whose output rows are as wide as the input's (see there).  out: partial
+// tensors as above, or with one range dw itself where its columns are in KRSC order
+const char *run_dw_name(int shape);
+bool run_dw_applicable(const WgradGeom &g);
+bool run_dw_has(int shape, int columns);       // whether the shape is built for filters of so many columns
+int run_dw_ranges(int shape, long long M, int ranges, int *span);
+int run_dw_best(const WgradGeom &g, int most_ranges, int *ranges, int *span, double *us);      // the shape of least modelled time, as wave_dw_best
+int run_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const void *x, const void *dy, float *out, int rows, hipStream_t st);
+
 bool wgrad_supported(const WgradGeom &g);
 size_t wgrad_workspace(const WgradGeom &g);            // bytes of fp32 partial tiles
 // dw: fp32, or bf16 (the fp32 sum rounded once, by the reduce kernel) when dw_bf16; KRSC, or KCRS when kcrs

@@ -510,7 +510,8 @@ int launch_choice(int idx, const WgradParams &p, int tiles, hipStream_t st)
 // wave: the wave kernel's shape, pixel ranges and their length, where it runs instead of the tile (shape -1: it does not); [1]: of operands
 // that are copies written just before
 struct DwWave { int shape, ranges, span; };
-struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave[2]; };
+// run: the run kernel's (runs_dw.hip), likewise
+struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave[2], run; };
 
 // Tile and split choice: the pair with the least modelled time - rounds over the chip's workgroup
 // slots (256 CUs x slots per CU) x stages each split walks x time per stage, plus the traffic of
@@ -518,6 +519,7 @@ struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave[2]; };
 // only) fixes the tile.
 Plan search_plan(const WgradGeom &g, int forced, int forced_splits);
 DwWave wave_choice(const WgradGeom &g, const Plan &pl, bool copies);
+DwWave run_choice(const WgradGeom &g, const Plan &pl);
 
 #include "tuned_wgrad.inc"
 
@@ -542,7 +544,8 @@ Plan make_plan(const WgradGeom &g)
         const int splits = forced >= 0 && slash ? atoi(slash + 1) : 0;
         if (last.forced != forced || last.splits != splits || memcmp(&last.g, &g, sizeof g)) last = Entry{g, forced, splits, search_plan(g, forced, splits)};
         Plan pl = last.plan;
-        pl.wave[0] = pl.wave[1] = wave_choice(g, pl, false);       // what the hook forces on the wave kernel is looked up on every call
+        pl.wave[0] = pl.wave[1] = wave_choice(g, pl, false);       // what the hook forces on the wave or run kernel is looked up on every call
+        pl.run = run_choice(g, pl);
         return pl;
     }
     static thread_local PlanCache<WgradGeom, Plan> cache;
@@ -556,6 +559,7 @@ Plan make_plan(const WgradGeom &g)
             }
         Plan pl = search_plan(g, tuned, splits);
         for (const bool copies : {false, true}) pl.wave[copies] = wave_choice(g, pl, copies);
+        pl.run = run_choice(g, pl);
         return pl;
     });
 }
@@ -600,6 +604,38 @@ DwWave wave_choice(const WgradGeom &g, const Plan &pl, bool copies)
     return w;
 }
 
+// The shape of the run kernel that runs this gradient and its pixel ranges, no more than the plan has, or shape -1: the wave kernel or
+// the planned tile does, whichever it is without it.  Measured time over the other kernel's, mean and worst, by the ratio of the models
+// (340 layers of 0.6 to 400 GFLOP): below 0.7 0.67 / 0.96, at 0.7-0.8 0.79 / 1.01, at 0.8-0.9 0.88 / 1.06, at 0.9-0.95 0.93 / 1.23,
+// at 0.95-1 0.99 / 1.12, above 1 1.2 and more.  256x256 tiles run up to a quarter faster than modelled: below 0.74 0.93 / 0.96, at
+// 0.75-0.83 0.99 / 1.03.
+DwWave run_choice(const WgradGeom &g, const Plan &pl)
+{
+    DwWave w{-1, 0, 0};
+    if (!run_dw_applicable(g)) return w;
+    const long long M = (long long)g.N * g.P * g.Q;
+    if (const char *f = getenv("MXC_FORCE_WGRAD")) {
+        const char *slash = strchr(f, '/');
+        const size_t len = slash ? (size_t)(slash - f) : strlen(f);
+        for (int i = 0; const char *n = run_dw_name(i); ++i)
+            if (strlen(n) == len && !strncmp(f, n, len) && run_dw_has(i, g.TS)) {
+                const int want = slash ? atoi(slash + 1) : 1;
+                w.shape = i;
+                w.ranges = run_dw_ranges(i, M, want < pl.splits ? want : pl.splits, &w.span);
+            }
+        return w;
+    }
+    DwWave best{-1, 0, 0};
+    double us = 0, other = tile_us(g, pl);
+    best.shape = run_dw_best(g, pl.splits, &best.ranges, &best.span, &us);
+    if (pl.wave[0].shape >= 0) {
+        int ranges = 1;
+        wave_dw_best(g, false, pl.splits, &ranges, &other);
+    }
+    const double line = pl.wave[0].shape < 0 && kTiles[pl.tile].bm == 256 && kTiles[pl.tile].bn == 256 ? 0.74 : 0.9;
+    return best.shape >= 0 && us < line * other ? best : w;
+}
+
 Plan search_plan(const WgradGeom &g, int forced, int forced_splits)
 {
     ++g_plan_searches;
@@ -635,7 +671,7 @@ Plan search_plan(const WgradGeom &g, int forced, int forced_splits)
                 best = t_us;
                 long long span = (M + sp - 1) / sp;
                 span = (span + tc.bp - 1) / tc.bp * tc.bp;
-                best_pl = Plan{t, k_tiles, n_tiles, (int)((M + span - 1) / span), (int)span, {{-1, 0, 0}, {-1, 0, 0}}};
+                best_pl = Plan{t, k_tiles, n_tiles, (int)((M + span - 1) / span), (int)span, {{-1, 0, 0}, {-1, 0, 0}}, {-1, 0, 0}};
             }
         }
     }
@@ -769,6 +805,15 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
     // the operands of NCHW problems, padded channels and first layers are copies (prepared inputs too: the same kernel, the same bits)
     const DwWave wv = pl.wave[kcrs || g.K != g.Kout || !dw_identity(g)];
     if (g.R * g.S == 1) kcrs = false;                 // one tap: both orders are the same
+    if (pl.run.shape >= 0) {
+        const bool identity = dw_identity(g), direct = pl.run.ranges == 1 && identity && !dw_bf16 && !kcrs;
+        *variant = run_dw_name(pl.run.shape);
+        const int rc = run_dw_launch(pl.run.shape, g, pl.run.ranges, pl.run.span, x, dy, direct ? (float *)dw : partial, direct ? g.Kout : g.K, st);
+        if (rc != MXC_OK) return rc;
+        if (direct) return resum != nullptr ? resum_dw(*resum, dw, false, st) : MXC_OK;
+        return dw_bf16 ? launch_reduce(g, partial, (bf16_t *)dw, pl.run.ranges, g.TR * g.TS * g.run, identity, kcrs, st, resum)
+                       : launch_reduce(g, partial, (float *)dw, pl.run.ranges, g.TR * g.TS * g.run, identity, kcrs, st, resum);
+    }
     if (wv.shape >= 0) {
         const int ncols = g.TR * g.TS * g.run;
         const bool same = dw_identity(g) && !kcrs;

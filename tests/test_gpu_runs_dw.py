@@ -1,0 +1,78 @@
+"""Backward-weight by the kernel whose taps of a filter row share their pixels: every shape, as one range of pixels and as several: ragged
+channels on both sides, images narrower and shorter than the filter, stages that span many images, filters of other heights than widths,
+padded channels, KCRS and bf16 results."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1512_01274_amd import inputs as gen
+from tests import util
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ["32x64", "64x64", "128x32", "128x64", "256x64", "96x64", "192x64", "32x128", "64x128", "256x32"]
+# N, C, H, W, K, R, S, pad: Q = W where S = 2*pad + 1
+DIMS = [
+    (6, 40, 9, 11, 72, 3, 3, 1),
+    (3, 24, 7, 7, 136, 5, 5, 2),
+    (9, 72, 5, 1, 40, 5, 5, 2),            # no tap but the middle column's meets a pixel
+    (2, 8, 3, 2, 8, 3, 3, 1),              # twelve pixels
+    (37, 96, 8, 8, 200, 3, 3, 1),
+    (5, 16, 6, 37, 48, 1, 3, 1),           # P = H + 2
+    (3, 48, 8, 5, 16, 5, 3, 1),            # P = H - 2
+    (60, 32, 1, 3, 264, 3, 5, 2),          # a stage of 128 pixels is some 14 images
+    (6, 30, 12, 13, 50, 3, 3, 1),          # padded channels on both sides
+    (1, 64, 9, 150, 64, 5, 5, 2),
+]
+
+
+@pytest.fixture(scope="module")
+def mxc():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1512_01274_amd import mxc as m
+    return m
+
+
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("ranges", [1, 4])
+@pytest.mark.parametrize("name,dims", [(n, d) for n in NAMES for d in DIMS if not (n in ("96x64", "192x64") and d[6] == 5)])      # (sums of 3*5 blocks do not fit)
+def test_weight_gradient(mxc, oracle, monkeypatch, name, dims, ranges, layout):
+    N, C, H, W, K, R, S, pad = dims
+    full = (N, C, H, W, K, R, S, 1, pad)
+    x, w, dy = gen.random_case(hash(dims) & 0xFFFF, *full, dtype="bf16", dist="normal")
+    run = util.Runner(mxc, full, "bf16", layout)
+    a = (*full, run.dt, run.lay)
+    monkeypatch.setenv("MXC_FORCE_WGRAD", f"wgrad_run_{name}/{ranges}")
+    ref = oracle.conv2d_bwd_weight(x, dy, w.shape, 1, pad)
+    den = oracle.conv2d_bwd_weight(np.abs(x), np.abs(dy), w.shape, 1, pad)
+    for dtype, call, op in ((torch.float32, mxc.mxc_conv2d_bwd_weight, mxc.MXC_BWD_WEIGHT), (torch.bfloat16, mxc.mxc_conv2d_bwd_weight_bf16, mxc.MXC_BWD_WEIGHT_BF16)):
+        dw = torch.full((w.size + 64,), 7.0, dtype=dtype, device="cuda")
+        call(*a, run._in(x), run._in(dy), dw, run._ws(op))
+        assert mxc.mxc_last_variant().endswith("wgrad_run_" + name)
+        assert bool((dw[w.size:] == 7.0).all())
+        got = dw[:w.size].double().cpu().numpy()
+        got = got.reshape(K, R, S, C).transpose(0, 3, 1, 2) if layout == "nhwc" else got.reshape(w.shape)
+        assert np.all(np.abs(got - ref) <= util.tight_bound(ref, den, "bf16", dtype == torch.bfloat16)), dims
+
+
+@pytest.mark.filterwarnings("ignore:invalid value")
+def test_infinities_beside_the_borders(mxc, oracle, monkeypatch):
+    """An infinite x at a row's end is not multiplied with what lies outside dy: results whose window does not hold it stay finite."""
+    full = (3, 16, 5, 6, 16, 3, 3, 1, 1)
+    x, w, dy = gen.random_case(5, *full, dtype="bf16", dist="normal")
+    x[1, 2, 2, 5] = np.inf
+    x[2, 3, 4, 0] = np.inf
+    run = util.Runner(mxc, full, "bf16", "nhwc")
+    monkeypatch.setenv("MXC_FORCE_WGRAD", "wgrad_run_64x64/1")
+    got, ref = run.bwd_weight(x, dy), oracle.conv2d_bwd_weight(x, dy, w.shape, 1, 1)
+    assert np.array_equal(np.isfinite(got), np.isfinite(ref)) and not np.isfinite(ref).all() and np.isfinite(ref[:, 2, :, 0]).any()
+
+
+def test_chosen(mxc):
+    dims = (64, 64, 28, 28, 96, 5, 5, 1, 2)
+    a = (*dims, mxc.MXC_BF16, mxc.MXC_NHWC)
+    x = torch.zeros(64, 28, 28, 64, dtype=torch.bfloat16, device="cuda")
+    dy = torch.zeros(64, 28, 28, 96, dtype=torch.bfloat16, device="cuda")
+    dw = torch.empty(96, 5, 5, 64, device="cuda")
+    mxc.mxc_conv2d_bwd_weight(*a, x, dy, dw, mxc.alloc_workspace(mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BWD_WEIGHT, *a)))
+    assert "wgrad_run_" in mxc.mxc_last_variant() and bool((dw == 0).all())
