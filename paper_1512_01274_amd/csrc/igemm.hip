@@ -1132,18 +1132,11 @@ int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_spl
     });
 }
 
-// Whether a plan's tiles read a filter in place in a small problem: see bwd_data_small_in_place
-bool small_in_place(const Plan &pl, long long M, int Co, int Kd)
-{
-    return !whole_launch(pl.main) && has_bt(pl.main) && (pl.tail < 0 || has_bt(pl.tail)) && 2.0 * M * Co * Kd < 1e10;
-}
-
 // The shape of the run kernel (runs.hip) that runs this GEMM, or -1: the wave kernel or the plan does, whichever it is without the run
-// kernel.  Those read the filter of small dx in place, where this one needs the re-pack, a launch of 4.3 us; of an NCHW problem
-// the wave kernel stores the result to its planes, which is a re-layout less.  Measured time over the other kernel's, mean and worst, by the
-// ratio of the models (320 layers of 0.4 to 400 GFLOP, forward and dx): below 0.7 0.66 / 0.95, at 0.7-0.8 0.76 / 0.99, at 0.8-0.9
-// 0.90 / 1.04, at 0.9-0.95 0.95 / 1.14, at 0.95-1 0.97 / 1.15, above 1 1.2 and more.  Plans of the streaming and window kernels come from
-// the measured table and stay.
+// kernel.  Of an NCHW problem the wave kernel stores the result to its planes, which is a re-layout less.  Measured time over the other
+// kernel's, mean and worst, by the ratio of the models (320 layers of 0.4 to 400 GFLOP, forward and dx): below 0.7 0.66 / 0.95, at
+// 0.7-0.8 0.76 / 0.99, at 0.8-0.9 0.90 / 1.04, at 0.9-0.95 0.95 / 1.14, at 0.95-1 0.97 / 1.15, above 1 1.2 and more.  Plans of the
+// streaming and window kernels come from the measured table and stay.
 int run_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool planes)
 {
     if (!run_applicable(p)) return -1;
@@ -1162,7 +1155,6 @@ int run_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool
         if (whole_launch(pl.main) || (wave >= 0 && planes)) return -1;
         if (wave >= 0) wave_best(M, p.Co, Kd, bwd, masked, &other);
         else other = plan_us(pl, M, p.Co, Kd, can_split ? split_count(M, p.Co, Kd) : 1, masked);
-        if (bwd && (wave >= 0 || small_in_place(pl, M, p.Co, Kd))) us += 4.3;
         return us < 0.9 * other ? run : -1;
     });
 }
@@ -1404,15 +1396,18 @@ int igemm_bwd_data_image(ImageStore kind, const ConvShape &s2, const S2DStore &q
 // of the reduction, same bits.  Measured over 60 shapes, masked or not: below 2 GFLOP every tile with the variant gains
 // (64x128 2 us, 128x32 and 128x64 3.6 us of 12), at 4-10 GFLOP 2-3 us of 25-35, and from 12 GFLOP on it loses with
 // 64x128 (15%) and breaks even with the others, which is where the line lies.
-// The streaming kernel transposes the filter into its resident copy at any size.
+// The streaming kernel transposes the filter into its resident copy at any size, and the run kernel reads it in place (72 layers of up to 170 GFLOP:
+// 1.01 of the time with a re-packed filter, which takes 4 to 5 us to make; 1.12 at worst).
 bool bwd_data_small_in_place(const ConvShape &s, bool masked)
 {
     if (real_c(s) != s.C || s.C % 8 != 0 || s.stride != 1 || bwd_data_reads_filter_in_place(s)) return false;
     const long long M = (long long)s.N * s.H * s.W;
     const int Kd = s.R * s.S * s.K;
-    if (run_choice(bwd_data_params(s), true, masked, true, false) >= 0) return false;
+    if (run_choice(bwd_data_params(s), true, masked, true, false) >= 0) return true;
     if (wave_choice(M, s.C, Kd, true, masked, true) >= 0 || bwd_data_streams_filter(s, masked)) return true;
-    return small_in_place(choose_plan(M, s.C, Kd, true, masked), M, s.C, Kd);
+    const Plan pl = choose_plan(M, s.C, Kd, true, masked);
+    if (whole_launch(pl.main) || !has_bt(pl.main) || (pl.tail >= 0 && !has_bt(pl.tail))) return false;
+    return 2.0 * M * s.C * Kd < 1e10;
 }
 
 // Whether the launch of the GEMM can write the zeros too (ZR): dx of a 1x1 filter at stride 2
@@ -1529,9 +1524,9 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
         p.wm_by_k = bt && !bwd_data_reads_filter_in_place(s) && bwd_data_streams_filter(s, p.mask != nullptr);
         const long long M = (long long)s.N * s.H * s.W;
         const int Kd = s.R * s.S * s.K;
-        if (const int rv = bt ? -1 : run_choice(p, true, p.mask != nullptr, s.C % 8 == 0, post.planes != nullptr); rv >= 0) {
+        if (const int rv = run_choice(p, true, p.mask != nullptr, s.C % 8 == 0, post.planes != nullptr); rv >= 0) {
             *variant = run_name(rv);
-            return run_launch(rv, p, st);
+            return run_launch(rv, p, st, bt);
         }
         if (const int wv = wave_choice(M, s.C, Kd, true, p.mask != nullptr, s.C % 8 == 0); wv >= 0) {
             *variant = wave_name(wv);

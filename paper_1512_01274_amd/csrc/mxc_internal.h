@@ -470,7 +470,7 @@ const char *run_name(int shape);
 int run_forced(const char *name, const IgemmParams &p);
 bool run_applicable(const IgemmParams &p);
 int run_best(long long M, int Co, int Ci, int TR, int TS, bool masked, double *us);      // the shape of least modelled time and that time
-int run_launch(int shape, IgemmParams p, hipStream_t st);
+int run_launch(int shape, IgemmParams p, hipStream_t st, bool bt = false);      // bt: wm is the KRSC filter
 
 // wave.hip: the same GEMM for problems that fill a fraction of the chip and for short reductions (see there).  Shapes are
 // numbered from 0; bwd: backward-data, whose shapes can all read the filter in place; bt: wm is the KRSC filter itself (see

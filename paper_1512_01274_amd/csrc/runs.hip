@@ -28,6 +28,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef bf16x4 __attribute__((address_space(3))) * lds_bf16x4_ptr;
 
 constexpr unsigned OOB = 0x80000000u;   // a buffer offset no operand reaches: the load returns zeros
 constexpr int CB = 32;                  // channels per stage
@@ -49,7 +51,10 @@ template <int BM, int BN, int TS, int NS, int NW>
 constexpr int min_blocks = NW > 4 ? 2 : lds_bytes<BM, BN, TS, NS> <= 53 * 1024 ? 3 : lds_bytes<BM, BN, TS, NS> <= 80 * 1024 ? 2 : 1;      // waves per SIMD
 
 // BM x BN output tile, WR x WC waves, TS filter columns, NS stages in the ring
-template <int BM, int BN, int TS, int NS, int WR, int WC>
+// BT: backward-data from the KRSC filter itself, whose row (k, r, s) is a run of output columns: a tap's tile is panels of 32 columns, 32
+// rows of 64 bytes each, fetched with ds_read_b64_tr_b16 (the four rows of one read lie in different banks).  Same products in the same
+// order as with the re-packed filter, without the launch that makes it (4 to 5 us).
+template <int BM, int BN, int TS, int NS, int WR, int WC, bool BT>
 __global__ __launch_bounds__(64 * WR * WC, (min_blocks<BM, BN, TS, NS, WR * WC>)) void run_kernel(const IgemmParams p)
 {
     constexpr int NW = WR * WC, NT = 64 * NW;
@@ -93,13 +98,20 @@ __global__ __launch_bounds__(64 * WR * WC, (min_blocks<BM, BN, TS, NS, WR * WC>)
         place(i, m0 - HALO + ld_sub + (decltype(i)::value + 1 < A_LD ? RPL * (wave + NW * decltype(i)::value) : BM));
     });
     unsigned b_off[B_LD];
+    [[maybe_unused]] int b_rows = 0;  // BT: bit i: load i brings the second half of a panel's rows
     int b_at[B_LD];                   // where the load's rows lie in the slot
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
         int idx = wave + NW * i;
         if (idx > B_LOADS - 1) idx = B_LOADS - 1;                 // (the same bytes as another wave)
-        const int s = idx * RPL / BN, co = n0 + idx * RPL % BN + ld_sub;
-        b_off[i] = co < p.Co ? (unsigned)(co * Kd2 + s * Ci2 + ld_chunk * 16) : OOB;
+        if constexpr (BT) {           // half a panel
+            const int s = idx / 2 / (BN / 32), co = n0 + idx / 2 % (BN / 32) * 32 + (lane & 3) * 8;
+            b_off[i] = co < p.Co ? (unsigned)((((idx & 1) * RPL + ld_sub) * p.TR * TS + s) * p.Co + co) * 2u : OOB;
+            b_rows |= (idx & 1) << i;
+        } else {
+            const int s = idx * RPL / BN, co = n0 + idx * RPL % BN + ld_sub;
+            b_off[i] = co < p.Co ? (unsigned)(co * Kd2 + s * Ci2 + ld_chunk * 16) : OOB;
+        }
         b_at[i] = A_SZ + idx * RPL * ROW;
     }
     // the stage that addresses are worked out for next: filter row st_r of channel block st_c
@@ -113,9 +125,16 @@ __global__ __launch_bounds__(64 * WR * WC, (min_blocks<BM, BN, TS, NS, WR * WC>)
             const int h = a_h[Tk] + st_r * p.tstep_h;
             va[Tk] = c_ok && (unsigned)h < (unsigned)p.Hi ? (unsigned)(a_off[Tk] + st_r * step_h2 + st_c2) : OOB;
         } else {
-            const unsigned at = (unsigned)(st_r * TS * Ci2 + st_c2);
+            if constexpr (BT) {
+                const unsigned at = (unsigned)((st_c2 / 2 * p.TR + st_r) * TS * p.Co) * 2u;
+                const int rows = p.Ci - st_c2 / 2;                 // of the block that are there: none past the last one
 #pragma unroll
-            for (int i = 0; i < B_LD; ++i) vb[i] = c_ok ? b_off[i] + at : OOB;
+                for (int i = 0; i < B_LD; ++i) vb[i] = ld_sub + ((b_rows >> i) & 1) * RPL < rows && !(b_off[i] & OOB) ? b_off[i] + at : OOB;
+            } else {
+                const unsigned at = (unsigned)(st_r * TS * Ci2 + st_c2);
+#pragma unroll
+                for (int i = 0; i < B_LD; ++i) vb[i] = c_ok ? b_off[i] + at : OOB;
+            }
             const bool wrap = st_r + 1 == p.TR;
             st_r = wrap ? 0 : st_r + 1;
             st_c2 += wrap ? ROW : 0;
@@ -140,12 +159,18 @@ __global__ __launch_bounds__(64 * WR * WC, (min_blocks<BM, BN, TS, NS, WR * WC>)
             a_at[i][s] = (unsigned)(q + shift) < (unsigned)p.Wi ? at * ROW + ((frag_kg ^ ((at >> 2) & 3)) << 4) : A_SZ + B_SZ + (frag_kg << 4);
         }
     }
+    const int tr_at = A_SZ + wave_n * ROW + ((lane >> 5) * 8 + ((lane & 15) >> 2)) * ROW + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;      // BT
     const int b_lane = A_SZ + (wave_n + frag_row) * ROW + ((frag_kg ^ ((frag_row >> 2) & 3)) << 4);
     struct Frags { bf16x8 a[MI], b[NI]; };
     auto read_task = [&](auto t, Frags &f, int slot, auto k) __attribute__((always_inline)) {
         constexpr int Tk = decltype(t)::value, S = decltype(k)::value / 2, X = (decltype(k)::value & 1) << 5;
         if constexpr (Tk < MI) f.a[Tk] = *reinterpret_cast<const bf16x8 *>(smem + slot * SLOT + (a_at[Tk][S] ^ X));
-        else f.b[Tk - MI] = *reinterpret_cast<const bf16x8 *>(smem + slot * SLOT + (S * BN + (Tk - MI) * 32) * ROW + (b_lane ^ X));
+        else if constexpr (BT) {
+            const char *q = smem + slot * SLOT + (S * BN + (Tk - MI) * 32) * ROW + (decltype(k)::value & 1) * 16 * ROW + tr_at;
+            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)q);
+            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(q + 4 * ROW));
+            f.b[Tk - MI] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        } else f.b[Tk - MI] = *reinterpret_cast<const bf16x8 *>(smem + slot * SLOT + (S * BN + (Tk - MI) * 32) * ROW + (b_lane ^ X));
     };
     constexpr int N_READ = MI + NI;
     const float bias_t = (p.bias != nullptr && tid < BN && n0 + tid < p.Cw) ? p.bias[n0 + tid] : 0.f;      // used after the loop
@@ -288,32 +313,33 @@ const RunShape kShapes[] = {
 constexpr int N_SHAPES = sizeof(kShapes) / sizeof(kShapes[0]);
 
 template <int BM, int BN, int TS, int NS, int WR, int WC>
-int launch(IgemmParams p, hipStream_t st)
+int launch(IgemmParams p, hipStream_t st, bool bt)
 {
     const long long mt = ((long long)p.M + BM - 1) / BM;
     p.n_tiles = (p.Co + BN - 1) / BN;
     if (mt * p.n_tiles > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
     p.m_tiles = (int)mt;
     const int grid = (p.m_tiles * p.n_tiles + 7) / 8 * 8;
-    hipLaunchKernelGGL((run_kernel<BM, BN, TS, NS, WR, WC>), dim3((unsigned)grid), dim3(64 * WR * WC), 0, st, p);
+    if (bt) hipLaunchKernelGGL((run_kernel<BM, BN, TS, NS, WR, WC, true>), dim3((unsigned)grid), dim3(64 * WR * WC), 0, st, p);
+    else hipLaunchKernelGGL((run_kernel<BM, BN, TS, NS, WR, WC, false>), dim3((unsigned)grid), dim3(64 * WR * WC), 0, st, p);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 
 template <int TS>
-int launch_shape(int shape, const IgemmParams &p, hipStream_t st)
+int launch_shape(int shape, const IgemmParams &p, hipStream_t st, bool bt)
 {
     switch (shape) {
-    case 0: return launch<128, 32, TS, 2, 4, 1>(p, st);
-    case 1: return launch<256, 32, TS, 2, 4, 1>(p, st);
-    case 2: return launch<128, 64, TS, 2, 2, 2>(p, st);
-    case 3: return launch<192, 64, TS, 2, 2, 2>(p, st);
-    case 4: return launch<256, 64, TS, 2, 4, 1>(p, st);
-    case 5: return launch<384, 64, TS, 2, 4, 1>(p, st);
-    case 6: return launch<256, 96, TS, 2, 4, 1>(p, st);
-    case 7: return launch<192, 128, TS, 2, 2, 2>(p, st);
-    case 8: return launch<256, 128, TS, 2, 4, 2>(p, st);
-    case 9: return launch<256, 192, TS, 2, 4, 2>(p, st);
-    case 10: if constexpr (TS == 3) return launch<256, 256, TS, 2, 2, 4>(p, st);
+    case 0: return launch<128, 32, TS, 2, 4, 1>(p, st, bt);
+    case 1: return launch<256, 32, TS, 2, 4, 1>(p, st, bt);
+    case 2: return launch<128, 64, TS, 2, 2, 2>(p, st, bt);
+    case 3: return launch<192, 64, TS, 2, 2, 2>(p, st, bt);
+    case 4: return launch<256, 64, TS, 2, 4, 1>(p, st, bt);
+    case 5: return launch<384, 64, TS, 2, 4, 1>(p, st, bt);
+    case 6: return launch<256, 96, TS, 2, 4, 1>(p, st, bt);
+    case 7: return launch<192, 128, TS, 2, 2, 2>(p, st, bt);
+    case 8: return launch<256, 128, TS, 2, 4, 2>(p, st, bt);
+    case 9: return launch<256, 192, TS, 2, 4, 2>(p, st, bt);
+    case 10: if constexpr (TS == 3) return launch<256, 256, TS, 2, 2, 4>(p, st, bt);
     }
     return MXC_ERR_UNSUPPORTED;
 }
@@ -356,16 +382,16 @@ bool run_applicable(const IgemmParams &p)
            M + (long long)p.Mh * p.Mw + 512 < 0x7FFFFFFFll && M * p.Co * 2 < 0x7FFF0000ll && (long long)p.N * p.Hi * p.Wi * p.pix * 2 < 0x7FFF0000ll;
 }
 
-int run_launch(int shape, IgemmParams p, hipStream_t st)
+int run_launch(int shape, IgemmParams p, hipStream_t st, bool bt)
 {
     if (!run_applicable(p) || shape < 0 || shape >= N_SHAPES || p.TS > kShapes[shape].most_ts) return MXC_ERR_UNSUPPORTED;
     p.M = p.N * p.Mh * p.Mw;
     p.in_bytes = (unsigned)((long long)p.N * p.Hi * p.Wi * p.pix * 2);
     if (p.Cw == 0) p.Cw = p.Co;
-    p.wm_bytes = (unsigned)((long long)p.Cw * p.TR * p.TS * p.Ci * 2);
+    p.wm_bytes = bt ? p.bt_w_bytes : (unsigned)((long long)p.Cw * p.TR * p.TS * p.Ci * 2);
     p.out_bytes = (unsigned)((long long)p.M * p.Co * 2);
     p.nt_out = p.out_bytes >= 128u << 20 ? 1 : 0;
-    return p.TS == 3 ? launch_shape<3>(shape, p, st) : launch_shape<5>(shape, p, st);
+    return p.TS == 3 ? launch_shape<3>(shape, p, st, bt) : launch_shape<5>(shape, p, st, bt);
 }
 
 }  // namespace mxc
