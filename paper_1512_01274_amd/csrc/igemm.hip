@@ -1159,6 +1159,30 @@ int run_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool
     });
 }
 
+// Whether the streaming kernel runs a 1x1 filter at stride 1 that the measured table does not hold, in the wave kernel's or the plan's place (of
+// an NCHW problem the wave kernel stays, see run_choice).  Measured time over the plan's, mean and worst, by the ratio of the models (420
+// layers of 20 to 900 MB): plans modelled at 20-40 us at 0.7-0.9 0.82 / 0.99, at 0.9-1 0.92 / 1.11, above 1 0.98 / 1.36; from 40 us on below 0.8
+// 0.77 / 1.00, at 0.8-0.95 0.84 / 1.13, at 0.95-1 0.86 / 1.11, above 0.92 / 1.25; over the wave kernel's from 40 us on 0.85 / 1.02 at
+// 0.9-1.1, below 40 us 1.06 / 1.4 at 0.95-1.1.  What the tiles lose is that a CU's loads wait while it stores.
+bool stream_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool planes)
+{
+    if (p.TR * p.TS != 1 || p.in_mul_h != 1 || p.in_mul_w != 1 || getenv("MXC_FORCE_VARIANT") || !stream_applicable(p)) return false;
+    const long long M = (long long)p.N * p.Mh * p.Mw;
+    g_key_M = M; g_key_Co = p.Co; g_key_Kd = p.Ci;
+    static thread_local PlanCache<GemmKey, bool> cache;
+    return cache.get(GemmKey{M, p.Co, p.Ci, (bwd ? 1 : 0) + (masked ? 2 : 0) + (can_split ? 4 : 0) + (planes ? 8 : 0)}, [&] {
+        ++g_plan_searches;
+        double other = 0;
+        const int wave = wave_choice(M, p.Co, p.Ci, bwd, masked, can_split);
+        const Plan pl = choose_plan(M, p.Co, p.Ci, true, masked);
+        if (whole_launch(pl.main) || (wave >= 0 && planes)) return false;
+        if (wave >= 0) wave_best(M, p.Co, p.Ci, bwd, masked, &other);
+        else other = plan_us(pl, M, p.Co, p.Ci, can_split ? split_count(M, p.Co, p.Ci) : 1, masked);
+        const double us = stream_us(p, masked);
+        return us < other * (other >= 40 ? 1. : 0.9);
+    });
+}
+
 // out[m][co] = act(sum_z partial[z][m][co] + bias[co]) in ascending z (fixed order), 4 columns per thread
 __global__ __launch_bounds__(256) void split_finish_kernel(const float *__restrict__ partial, bf16_t *__restrict__ out, long long MC,
                                                            int Co, int Cw, int splits, const float *__restrict__ bias, int relu,
@@ -1252,6 +1276,10 @@ int igemm_fwd(const ConvShape &s, const void *x, const void *w, void *y, hipStre
     if (const int rv = run_choice(p, false, false, split_ws != nullptr && s.K % 8 == 0, post.planes != nullptr); rv >= 0) {
         *variant = run_name(rv);
         return run_launch(rv, p, st);
+    }
+    if (stream_choice(p, false, false, split_ws != nullptr && s.K % 8 == 0, post.planes != nullptr)) {
+        *variant = kStreamName;
+        return stream_launch(p, st);
     }
     if (const int wv = wave_choice(M, s.K, s.R * s.S * s.C, false, false, split_ws != nullptr && s.K % 8 == 0); wv >= 0) {
         *variant = wave_name(wv);
@@ -1403,7 +1431,8 @@ bool bwd_data_small_in_place(const ConvShape &s, bool masked)
     if (real_c(s) != s.C || s.C % 8 != 0 || s.stride != 1 || bwd_data_reads_filter_in_place(s)) return false;
     const long long M = (long long)s.N * s.H * s.W;
     const int Kd = s.R * s.S * s.K;
-    if (run_choice(bwd_data_params(s), true, masked, true, false) >= 0) return true;
+    const IgemmParams p = bwd_data_params(s);
+    if (run_choice(p, true, masked, true, false) >= 0 || stream_choice(p, true, masked, true, false)) return true;
     if (wave_choice(M, s.C, Kd, true, masked, true) >= 0 || bwd_data_streams_filter(s, masked)) return true;
     const Plan pl = choose_plan(M, s.C, Kd, true, masked);
     if (whole_launch(pl.main) || !has_bt(pl.main) || (pl.tail >= 0 && !has_bt(pl.tail))) return false;
@@ -1527,6 +1556,11 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
         if (const int rv = run_choice(p, true, p.mask != nullptr, s.C % 8 == 0, post.planes != nullptr); rv >= 0) {
             *variant = run_name(rv);
             return run_launch(rv, p, st, bt);
+        }
+        if (!bwd_data_reads_filter_in_place(s) && stream_choice(p, true, p.mask != nullptr, s.C % 8 == 0, post.planes != nullptr)) {
+            *variant = kStreamName;
+            p.wm_by_k = bt;
+            return stream_launch(p, st);
         }
         if (const int wv = wave_choice(M, s.C, Kd, true, p.mask != nullptr, s.C % 8 == 0); wv >= 0) {
             *variant = wave_name(wv);

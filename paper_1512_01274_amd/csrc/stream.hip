@@ -55,7 +55,7 @@ struct StreamParams {
     int d_n, d_a, d_b;   // one row tile further = d_n images + d_a rows + d_b columns of the output grid (d_a < Mh, d_b < Mw)
 };
 
-// NC compute waves (row tile BM = 32*NC), NL loader waves, column tile BN (32, 64 or 128), NS ring stages.
+// NC compute waves (row tile BM = 32*NC), NL loader waves, column tile BN (32, 64, 96 or 128), NS ring stages.
 // Dynamic LDS: [filter BN x KT*64][ring NS x BM x 64][staging NC x 32 x min(BN,64)][tap table][bias BN].
 // EPI: how results leave.  EPI_MASK: zeroed where p.mask <= 0; EPI_S2D: un-packed into an image (p.s2d).  (Variants of their
 // own: their registers would spill the plain one.)
@@ -278,6 +278,7 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
 #pragma unroll
         for (int jj = 0; jj < JN; ++jj) {
             const int j = jc * JN + jj;
+            if (j >= NI) continue;                  // 96 columns: a pass of 64 and one of 32
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) {
                 const int c = jj * 4 + g4;
@@ -315,6 +316,7 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
     const bool fast_store = p.linear_out;
     constexpr int RPI = 64 / CPR;                   // staged rows per store instruction
     const int st_r = lane / CPR, st_c = lane % CPR;
+    const int col_end = min(p.Co, n0 + BN);
     const unsigned st_lane_off = (unsigned)((st_r * p.Co + n0 + st_c * 8) * 2);
     const bf16_t *st_src = stg + st_r * EW + stg_chunk(st_r, st_c);   // RPI is a multiple of CPR << LB: same chunk position for every k
 
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
     // byte offset of store k of staging pass jc of the tile whose rows of this wave begin at m0; rows past the end of the
     // range and columns past Co: an offset the resource rejects
     auto store_off = [&](int m0, int jc, int k) __attribute__((always_inline)) {
-        const bool ok = n0 + jc * 64 + st_c * 8 < p.Co && st_r + k * RPI < wg_hi - m0;
+        const bool ok = n0 + jc * 64 + st_c * 8 < col_end && st_r + k * RPI < wg_hi - m0;
         return ok ? st_lane_off + (unsigned)m0 * (unsigned)(p.Co * 2) + (unsigned)(jc * 128 + k * RPI * p.Co * 2) : OOB;   // below 2^32: the output is below 2^31
     };
     static_assert(EPI != EPI_S2D || BN <= 64, "one staging pass");
@@ -420,7 +422,7 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
                 const int r = idx / CPR, c = idx % CPR;
                 const int m = m0 + r, co = n0 + jc * 64 + c * 8;
                 uint4 v = swap_halves(*reinterpret_cast<const uint4 *>(stg + r * EW + stg_chunk(r, c)), (r >> 3) & 1);
-                if (m < wg_hi && co < p.Co) {
+                if (m < wg_hi && co < col_end) {
                     long long pix = m;
                     if (!p.linear_out) {
                         const unsigned b = (unsigned)m % (unsigned)p.Mw, t2 = (unsigned)m / (unsigned)p.Mw;
@@ -458,11 +460,11 @@ long long stream_lds(int nc, int ns, int bn, int KT)
 // MXC_STREAM_SHAPE=<compute waves>x<stages> (tuning sweeps only) picks one.
 const int kForms[][2] = {{8, 3}, {4, 4}, {4, 3}, {4, 6}};
 
-// Column tile: the smallest of 32 / 64 / 128 that holds min(Co, 128).
+// Column tile: the smallest of 32 / 64 / 128 that holds min(Co, 128), or 96 where that many tiles of 96 hold Co too.
 StreamConfig stream_config(const IgemmParams &p)
 {
     const int Kd = p.TR * p.TS * p.Ci, KT = (Kd + BK - 1) / BK;
-    const int bn = p.Co <= 32 ? 32 : p.Co <= 64 ? 64 : 128;
+    const int bn = p.Co <= 32 ? 32 : p.Co <= 64 ? 64 : (p.Co + 95) / 96 == (p.Co + 127) / 128 ? 96 : 128;
     int want_nc = 0, want_ns = 0;
     if (const char *f = getenv("MXC_STREAM_SHAPE")) {
         if (sscanf(f, "%dx%d", &want_nc, &want_ns) != 2) want_nc = want_ns = 0;
@@ -500,13 +502,18 @@ int launch_stream_m(StreamParams sp, int lds, hipStream_t st)
     n_wg_m = (int)((rows + sp.rows_per_wg - 1) / sp.rows_per_wg);
     sp.n_wg_m = n_wg_m;
     sp.units = n_wg_m * p.n_tiles;
-    sp.per_xcd = ((sp.units + 7) / 8 + p.n_tiles - 1) / p.n_tiles * p.n_tiles;
+    // whole row ranges for each XCD, unless that leaves one of them more workgroups than it holds at a time (three column tiles: 33 on 32 CUs, the
+    // last of them after the others: 29x29, 64 to 352 channels, batch 10 21 us, now 10)
+    const int even = (sp.units + 7) / 8, whole = (even + p.n_tiles - 1) / p.n_tiles * p.n_tiles;
+    sp.per_xcd = whole <= 32 * per_cu ? whole : even;
     // Cache policy, measured on 1x1 layers of 56x56 images: results of a large layer leave as non-temporal stores
     // (the next reader finds them in HBM whatever the policy, and the caches keep serving this kernel's reads);
     // activations that no second workgroup and no second tap will ask for arrive as non-temporal loads.
     // MXC_STREAM_NT=<bits> (tuning sweeps only) overrides.
     const long long in_bytes = (long long)p.N * p.Hi * p.Wi * p.pix * 2, out_bytes = (long long)p.N * p.Ho * p.Wo * p.Co * 2;
-    sp.nt = (out_bytes >= (32ll << 20) ? 1 : 0) | ((in_bytes >= (64ll << 20) && p.n_tiles == 1 && p.TR * p.TS == 1) ? 2 : 0);
+    // Rows that are no whole number of 64 (stores) and 128 bytes (loads) would go through memory in pieces of less: 32 to 80 channels at
+    // 64x64, batch 114, 57 -> 26 us, 144 to 24 at 73x73, batch 210, 120 -> 89.
+    sp.nt = (out_bytes >= (32ll << 20) && p.Co % 32 == 0 ? 1 : 0) | ((in_bytes >= (64ll << 20) && p.n_tiles == 1 && p.TR * p.TS == 1 && p.Ci % 64 == 0) ? 2 : 0);
     if (const char *f = getenv("MXC_STREAM_NT")) sp.nt = atoi(f);
     sp.out_bytes = EPI == EPI_S2D ? (unsigned)((long long)p.N * p.s2d.H * p.s2d.W * p.s2d.C * 2) : (unsigned)((long long)p.N * p.Ho * p.Wo * p.Co * 2);
     sp.d_n = BM / (p.Mh * p.Mw);
@@ -531,6 +538,7 @@ int launch_stream_bn(const StreamParams &sp, const StreamConfig &c, hipStream_t 
 {
     if (c.bn == 32) return launch_stream<NC, NL, 32, NS>(sp, c.lds, st);
     if (c.bn == 64) return launch_stream<NC, NL, 64, NS>(sp, c.lds, st);
+    if (c.bn == 96) return launch_stream<NC, NL, 96, NS>(sp, c.lds, st);
     return launch_stream<NC, NL, 128, NS>(sp, c.lds, st);
 }
 
@@ -545,6 +553,22 @@ bool stream_applicable(const IgemmParams &p)
     if (Kd % 8 != 0 || p.Ci % 8 != 0 || (p.Co & 7) != 0) return false;      // 16-byte chunks within a tap's run; 16-byte stores
     if (p.TR * p.TS > MAX_TAPS) return false;
     return stream_config(p).ok;
+}
+
+// Time model (us) of 1x1 filters at stride 1, fitted to 420 layers of 20 to 900 MB, forward and masked dx, 7 to 8% off: launch, the MB that
+// are fetched (once per column tile), stored and read as a mask, and of the workgroup with most rows its stages, their MFMAs, its tiles and their columns.
+double stream_us(const IgemmParams &p, bool masked)
+{
+    static const double k8[] = {5.97, 0.168, 0.135, 0.352, 0.312, 0.0358, 0, 0.361}, k4[] = {6.58, 0.104, 0.0155, 0.335, 0.34, 0.0305, 0.873, 0};
+    const StreamConfig c = stream_config(p);
+    const double *k = c.nc == 8 ? k8 : k4;
+    const long long M = (long long)p.N * p.Mh * p.Mw;
+    const int KT = (p.Ci + BK - 1) / BK, n_tiles = (p.Co + c.bn - 1) / c.bn, bm = 32 * c.nc;
+    int per_cu = 160 * 1024 / c.lds;
+    if (per_cu > 12 / (c.nc + c.nc / 2)) per_cu = 12 / (c.nc + c.nc / 2);
+    const long long m_tiles = (M + bm - 1) / bm, fit = 256 * per_cu / n_tiles, wgs = fit < 1 ? 1 : fit > m_tiles ? m_tiles : fit;
+    const double tiles = (double)((((M + wgs - 1) / wgs + 31) / 32 * 32 + bm - 1) / bm), mco = 1e-6 * M * p.Co;
+    return k[0] + k[1] * 1e-6 * M * p.Ci * n_tiles + k[2] * mco + (masked ? k[3] * mco : 0) + tiles * (k[4] * KT + k[5] * KT * c.bn / 32 + k[6] + k[7] * (c.bn / 32));
 }
 
 int stream_launch(const IgemmParams &p, hipStream_t st)
