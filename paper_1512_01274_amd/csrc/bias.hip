@@ -192,7 +192,11 @@ BiasPlan plan(long long N, int K, long long PQ, int dtype, int layout)
     b.rows = N * PQ / b.fold;
     b.left = N * PQ % b.fold;
     const bool one = b.fold == 1 && b.rows <= 4096;
-    b.cpb = b.chunks < (one ? 4 : BT) ? b.chunks : (one ? 4 : BT);
+    // Its 1024 threads are then up to 1024 row groups: fewer loads each, one after another, as long as not too many workgroups fetch the same
+    // lines.  us, 4 chunks a workgroup -> these, in a graph: 1300 rows of 32 bf16 channels 4.1 -> 3.4, 2940 of 144 5.3 -> 4.7; one chunk would
+    // take 3751 rows of 320 from 7.5 to 8.8, 4000 of 512 from 5.6 to 12.
+    const int narrow = b.rows <= 1024 ? 4 : b.rows <= 2048 ? 2 : b.chunks <= 24 ? 1 : 4;
+    b.cpb = b.chunks < (one ? narrow : BT) ? b.chunks : (one ? narrow : BT);
     // wide rows: equal column blocks of at most 256 chunks, so that 1024 threads are four row groups with loads in flight
     if (!one && b.cpb > MAX_CPB) b.cpb = MAX_CPB;
     if (one) { b.parts = 1; return b; }
