@@ -41,10 +41,10 @@ constexpr int RPL = 16;                 // pixels that one wave-wide load fills
 struct RunDwParams {
     const bf16_t *x, *dy;
     float *partial;      // [splits][K][ncols]
-    int H, W, P, C, K, R, pad, M;
+    int H, W, P, Q, C, K, R, pad, M;      // M: positions, rows of W
     int c_tiles, tiles, n_wg, span, rows, ncols;
     int step_p, step_q;  // a stage's pixels as images (in step_off alone), rows and columns, and as bytes of x
-    unsigned step_off;
+    unsigned step_off, dy_step, dy_wrap;   // ... of dy, and from a row's last position to the next row's first
     int inc0, inc1;      // 16 pixels, and those from a wave's second k-step to the next stage's first, modulo W
     unsigned x_bytes, dy_bytes;
 };
@@ -57,10 +57,12 @@ template <int I> using IC = std::integral_constant<int, I>;
 template <class F, int... I> __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) { (f(IC<I>{}), ...); }
 template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
-template <int MI, int TS, int WK, int WC, int WP, int NS>
+// IN: no padding, and dy rows of Q = W - TS + 1 (layers in space-to-depth form).  The positions are x's, rows of W; tap s reads s further on, and the
+// last TS - 1 positions of a row have neither dy nor, so that nothing is multiplied with what is not there, x.
+template <int MI, int TS, bool IN, int WK, int WC, int WP, int NS>
 __global__ __launch_bounds__(64 * WK * WC * WP, 2) void run_dw_kernel(const RunDwParams p)
 {
-    constexpr int NW = WK * WC * WP, HALO = TS / 2, BP = 32 * WP;
+    constexpr int NW = WK * WC * WP, HALO = IN ? 0 : TS / 2, BP = 32 * WP;
     constexpr int NKP = MI * WK, NCP = WC;                         // panels
     constexpr int GROUPS = BP / RPL, SETS = NW / GROUPS;           // a wave loads pixels 16*(wave % GROUPS) ... of every SETS-th panel
     constexpr int DY_LD = (NKP + SETS - 1) / SETS, X_LD = (NCP + SETS - 1) / SETS, L = DY_LD + X_LD + 1;
@@ -89,7 +91,10 @@ __global__ __launch_bounds__(64 * WK * WC * WP, 2) void run_dw_kernel(const RunD
     const buf_rsrc_t rs_x = make_buf_rsrc(p.x, p.x_bytes), rs_dy = make_buf_rsrc(p.dy, p.dy_bytes);
     const int sub = lane >> 2, chunk = lane & 3, group = wave % GROUPS, set = wave / GROUPS;
     const int px2 = p.C * 2, k2 = p.K * 2;
-    unsigned dy_off = (unsigned)(m_begin + group * RPL + sub) * (unsigned)k2;      // of the lane's pixel; past the tensor's end the load returns zeros
+    // dy of the lane's position; past the tensor's end the load returns zeros
+    const int dy_m = m_begin + group * RPL + sub, dy_row = IN ? (int)((unsigned)dy_m / (unsigned)p.W) : 0;
+    int dy_q = IN ? dy_m - dy_row * p.W : 0;
+    unsigned dy_off = (unsigned)(IN ? dy_row * p.Q + dy_q : dy_m) * (unsigned)k2;
     unsigned dy_col[DY_LD], x_col[X_LD], e_col;
 #pragma unroll
     for (int i = 0; i < DY_LD; ++i) {
@@ -131,8 +136,16 @@ __global__ __launch_bounds__(64 * WK * WC * WP, 2) void run_dw_kernel(const RunD
     auto addr_task = [&](auto t) __attribute__((always_inline)) {
         constexpr int Tk = decltype(t)::value;
         if constexpr (Tk < DY_LD) {
-            va[Tk] = (dy_col[Tk] & OOB) ? OOB : dy_off + dy_col[Tk];
-            if constexpr (Tk + 1 == DY_LD) dy_off += (unsigned)(BP * k2);
+            va[Tk] = (dy_col[Tk] & OOB) || (IN && dy_q >= p.Q) ? OOB : dy_off + dy_col[Tk];
+            if constexpr (Tk + 1 == DY_LD) {
+                dy_off += p.dy_step;
+                if constexpr (IN) {
+                    dy_q += p.step_q;
+                    const bool c = dy_q >= p.W;
+                    dy_q -= c ? p.W : 0;
+                    dy_off -= c ? p.dy_wrap : 0u;
+                }
+            }
         } else if constexpr (Tk + 1 < L) {
             va[Tk] = (unsigned)xp.h < (unsigned)p.H ? (x_col[Tk - DY_LD] & OOB ? OOB : xp.off + x_col[Tk - DY_LD]) : OOB;
             if constexpr (Tk + 2 == L) advance(xp);
@@ -170,7 +183,8 @@ __global__ __launch_bounds__(64 * WK * WC * WP, 2) void run_dw_kernel(const RunD
     auto read_b = [&](int slot, int ks, auto s) __attribute__((always_inline)) {
         constexpr int D = decltype(s)::value - HALO;
         const int at = b_at + (D + HALO) * ROW;
-        if constexpr (D == 0) return read8(slot, at, at + 4 * ROW, ks * 16 * ROW);
+        if constexpr (!IN && D == 0) return read8(slot, at, at + 4 * ROW, ks * 16 * ROW);
+        if constexpr (IN) return read8(slot, q_lo < p.Q ? at : Z_AT + tr_byte, q_hi < p.Q ? at + 4 * ROW : Z_AT + tr_byte, ks * 16 * ROW);
         const bool lo = D < 0 ? q_lo >= -D : q_lo < p.W - D, hi = D < 0 ? q_hi >= -D : q_hi < p.W - D;
         return read8(slot, lo ? at : Z_AT + tr_byte, hi ? at + 4 * ROW : Z_AT + tr_byte, ks * 16 * ROW);
     };
@@ -288,21 +302,21 @@ const RunDwShape kShapes[] = {
 };
 constexpr int N_SHAPES = sizeof(kShapes) / sizeof(kShapes[0]);
 
-template <int TS>
+template <int TS, bool IN>
 void launch(int shape, const RunDwParams &p, hipStream_t st)
 {
     const dim3 grid((unsigned)((p.n_wg + 7) / 8 * 8)), block(512);
     switch (shape) {
-    case 0: hipLaunchKernelGGL((run_dw_kernel<1, TS, 1, 2, 4, 3>), grid, block, 0, st, p); break;
-    case 1: hipLaunchKernelGGL((run_dw_kernel<2, TS, 1, 2, 4, 3>), grid, block, 0, st, p); break;
-    case 2: hipLaunchKernelGGL((run_dw_kernel<2, TS, 2, 1, 4, 3>), grid, block, 0, st, p); break;
-    case 3: hipLaunchKernelGGL((run_dw_kernel<2, TS, 2, 2, 2, 4>), grid, block, 0, st, p); break;
-    case 4: hipLaunchKernelGGL((run_dw_kernel<2, TS, 4, 2, 1, 4>), grid, block, 0, st, p); break;
-    case 5: if constexpr (TS == 3) hipLaunchKernelGGL((run_dw_kernel<3, TS, 1, 2, 4, 3>), grid, block, 0, st, p); break;
-    case 6: if constexpr (TS == 3) hipLaunchKernelGGL((run_dw_kernel<3, TS, 2, 2, 2, 4>), grid, block, 0, st, p); break;
-    case 7: hipLaunchKernelGGL((run_dw_kernel<1, TS, 1, 4, 2, 4>), grid, block, 0, st, p); break;
-    case 9: hipLaunchKernelGGL((run_dw_kernel<2, TS, 4, 1, 2, 4>), grid, block, 0, st, p); break;
-    case 8: hipLaunchKernelGGL((run_dw_kernel<2, TS, 1, 4, 2, 4>), grid, block, 0, st, p); break;
+    case 0: hipLaunchKernelGGL((run_dw_kernel<1, TS, IN, 1, 2, 4, 3>), grid, block, 0, st, p); break;
+    case 1: hipLaunchKernelGGL((run_dw_kernel<2, TS, IN, 1, 2, 4, 3>), grid, block, 0, st, p); break;
+    case 2: hipLaunchKernelGGL((run_dw_kernel<2, TS, IN, 2, 1, 4, 3>), grid, block, 0, st, p); break;
+    case 3: hipLaunchKernelGGL((run_dw_kernel<2, TS, IN, 2, 2, 2, 4>), grid, block, 0, st, p); break;
+    case 4: hipLaunchKernelGGL((run_dw_kernel<2, TS, IN, 4, 2, 1, 4>), grid, block, 0, st, p); break;
+    case 5: if constexpr (TS == 3) hipLaunchKernelGGL((run_dw_kernel<3, TS, IN, 1, 2, 4, 3>), grid, block, 0, st, p); break;
+    case 6: if constexpr (TS == 3) hipLaunchKernelGGL((run_dw_kernel<3, TS, IN, 2, 2, 2, 4>), grid, block, 0, st, p); break;
+    case 7: hipLaunchKernelGGL((run_dw_kernel<1, TS, IN, 1, 4, 2, 4>), grid, block, 0, st, p); break;
+    case 9: hipLaunchKernelGGL((run_dw_kernel<2, TS, IN, 4, 1, 2, 4>), grid, block, 0, st, p); break;
+    case 8: hipLaunchKernelGGL((run_dw_kernel<2, TS, IN, 1, 4, 2, 4>), grid, block, 0, st, p); break;
     }
 }
 
@@ -312,8 +326,8 @@ const char *run_dw_name(int shape) { return shape >= 0 && shape < N_SHAPES ? kSh
 
 bool run_dw_applicable(const WgradGeom &g)
 {
-    const long long M = (long long)g.N * g.P * g.Q;
-    return (g.TS == 3 || g.TS == 5) && g.stride == 1 && g.Q == g.W && g.pad == g.TS / 2 && g.run == g.pix && g.pix % 8 == 0 && g.K % 8 == 0 &&
+    const long long M = (long long)g.N * g.P * g.W;
+    return (((g.TS == 3 || g.TS == 5) && g.Q == g.W && g.pad == g.TS / 2) || (g.TS == 3 && g.Q == g.W - 2 && g.pad == 0)) && g.stride == 1 && g.run == g.pix && g.pix % 8 == 0 && g.K % 8 == 0 &&
            M + (long long)g.P * g.W + 2048 < 0x7FFFFFFFll;
 }
 
@@ -330,7 +344,7 @@ int run_dw_ranges(int shape, long long M, int ranges, int *span)
 
 int run_dw_best(const WgradGeom &g, int most_ranges, int *ranges, int *span, double *us)
 {
-    const long long M = (long long)g.N * g.P * g.Q;
+    const long long M = (long long)g.N * g.P * g.W;
     const double mb = 4e-6 * g.K * g.TR * g.TS * g.run;
     int best = -1;
     for (int i = 0; i < N_SHAPES; ++i) {
@@ -357,7 +371,7 @@ int run_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const voi
     const RunDwShape &s = kShapes[shape];
     RunDwParams p{};
     p.x = (const bf16_t *)x; p.dy = (const bf16_t *)dy; p.partial = out;
-    p.H = g.H; p.W = g.W; p.P = g.P; p.C = g.pix; p.K = g.K; p.R = g.TR; p.pad = g.pad; p.M = g.N * g.P * g.Q;
+    p.H = g.H; p.W = g.W; p.P = g.P; p.Q = g.Q; p.C = g.pix; p.K = g.K; p.R = g.TR; p.pad = g.pad; p.M = g.N * g.P * g.W;
     p.c_tiles = (g.pix + 32 * s.wc - 1) / (32 * s.wc);
     const long long tiles = (long long)p.c_tiles * g.TR * ((g.K + 32 * s.mi * s.wk - 1) / (32 * s.mi * s.wk));
     if (tiles * ranges > 0x3FFFFFFFll) return MXC_ERR_SHAPE;
@@ -365,10 +379,13 @@ int run_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const voi
     const int bp = 32 * s.wp;
     p.step_q = bp % g.W; p.step_p = bp / g.W % g.P;
     p.step_off = (unsigned)((bp + (long long)(bp / g.W / g.P) * (g.H - g.P) * g.W) * g.pix * 2);
+    p.dy_step = (unsigned)((bp / g.W * g.Q + bp % g.W) * (long long)g.K * 2); p.dy_wrap = (unsigned)((g.W - g.Q) * g.K * 2);
     p.inc0 = 16 % g.W; p.inc1 = (bp - 16) % g.W;
     p.x_bytes = (unsigned)((long long)g.N * g.H * g.W * g.pix * 2);
-    p.dy_bytes = (unsigned)((long long)p.M * g.K * 2);
-    if (g.TS == 3) launch<3>(shape, p, st); else launch<5>(shape, p, st);
+    p.dy_bytes = (unsigned)((long long)g.N * g.P * g.Q * g.K * 2);
+    if (g.Q != g.W) launch<3, true>(shape, p, st);
+    else if (g.TS == 3) launch<3, false>(shape, p, st);
+    else launch<5, false>(shape, p, st);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_LAUNCH;
 }
 

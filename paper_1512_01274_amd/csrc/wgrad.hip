@@ -613,7 +613,7 @@ DwWave run_choice(const WgradGeom &g, const Plan &pl)
 {
     DwWave w{-1, 0, 0};
     if (!run_dw_applicable(g)) return w;
-    const long long M = (long long)g.N * g.P * g.Q;
+    const long long M = (long long)g.N * g.P * g.W;
     if (const char *f = getenv("MXC_FORCE_WGRAD")) {
         const char *slash = strchr(f, '/');
         const size_t len = slash ? (size_t)(slash - f) : strlen(f);

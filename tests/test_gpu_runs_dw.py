@@ -11,7 +11,7 @@ from tests import util
 pytestmark = pytest.mark.gpu
 
 NAMES = ["32x64", "64x64", "128x32", "128x64", "256x64", "96x64", "192x64", "32x128", "64x128", "256x32"]
-# N, C, H, W, K, R, S, pad: Q = W where S = 2*pad + 1
+# N, C, H, W, K, R, S, pad: Q = W where S = 2*pad + 1, or S = 3 without padding
 DIMS = [
     (6, 40, 9, 11, 72, 3, 3, 1),
     (3, 24, 7, 7, 136, 5, 5, 2),
@@ -23,7 +23,13 @@ DIMS = [
     (60, 32, 1, 3, 264, 3, 5, 2),          # a stage of 128 pixels is some 14 images
     (6, 30, 12, 13, 50, 3, 3, 1),          # padded channels on both sides
     (1, 64, 9, 150, 64, 5, 5, 2),
+    (3, 40, 9, 11, 72, 3, 3, 0),           # no padding: positions of x without dy
+    (2, 64, 4, 150, 48, 3, 3, 0),
+    (37, 96, 8, 8, 200, 5, 3, 0),
+    (5, 16, 5, 3, 24, 3, 3, 0),            # one column of dy
 ]
+# first layers in space-to-depth form
+FIRST = [(3, 3, 43, 39, 40, 11, 11, 4, 2), (2, 1, 64, 67, 16, 11, 11, 4, 2), (6, 4, 35, 50, 96, 5, 5, 2, 2)]
 
 
 @pytest.fixture(scope="module")
@@ -35,16 +41,17 @@ def mxc():
 
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])
 @pytest.mark.parametrize("ranges", [1, 4])
-@pytest.mark.parametrize("name,dims", [(n, d) for n in NAMES for d in DIMS if not (n in ("96x64", "192x64") and d[6] == 5)])      # (sums of 3*5 blocks do not fit)
+@pytest.mark.parametrize("name,dims", [(n, d) for n in NAMES for d in DIMS + FIRST if not (n in ("96x64", "192x64") and d[6] == 5 and len(d) == 8)])      # (sums of 3*5 blocks do not fit)
 def test_weight_gradient(mxc, oracle, monkeypatch, name, dims, ranges, layout):
-    N, C, H, W, K, R, S, pad = dims
-    full = (N, C, H, W, K, R, S, 1, pad)
+    N, C, H, W, K, R, S, pad = dims[:7] + dims[-1:]
+    full = dims if len(dims) == 9 else (*dims[:7], 1, pad)
+    st = full[7]
     x, w, dy = gen.random_case(hash(dims) & 0xFFFF, *full, dtype="bf16", dist="normal")
     run = util.Runner(mxc, full, "bf16", layout)
     a = (*full, run.dt, run.lay)
     monkeypatch.setenv("MXC_FORCE_WGRAD", f"wgrad_run_{name}/{ranges}")
-    ref = oracle.conv2d_bwd_weight(x, dy, w.shape, 1, pad)
-    den = oracle.conv2d_bwd_weight(np.abs(x), np.abs(dy), w.shape, 1, pad)
+    ref = oracle.conv2d_bwd_weight(x, dy, w.shape, st, pad)
+    den = oracle.conv2d_bwd_weight(np.abs(x), np.abs(dy), w.shape, st, pad)
     for dtype, call, op in ((torch.float32, mxc.mxc_conv2d_bwd_weight, mxc.MXC_BWD_WEIGHT), (torch.bfloat16, mxc.mxc_conv2d_bwd_weight_bf16, mxc.MXC_BWD_WEIGHT_BF16)):
         dw = torch.full((w.size + 64,), 7.0, dtype=dtype, device="cuda")
         call(*a, run._in(x), run._in(dy), dw, run._ws(op))
@@ -66,6 +73,12 @@ def test_infinities_beside_the_borders(mxc, oracle, monkeypatch):
     monkeypatch.setenv("MXC_FORCE_WGRAD", "wgrad_run_64x64/1")
     got, ref = run.bwd_weight(x, dy), oracle.conv2d_bwd_weight(x, dy, w.shape, 1, 1)
     assert np.array_equal(np.isfinite(got), np.isfinite(ref)) and not np.isfinite(ref).all() and np.isfinite(ref[:, 2, :, 0]).any()
+    full = (3, 16, 6, 8, 16, 3, 3, 1, 0)
+    x, w, dy = gen.random_case(6, *full, dtype="bf16", dist="normal")
+    x[1, 2, 5, 7] = np.inf
+    run = util.Runner(mxc, full, "bf16", "nhwc")
+    got, ref = run.bwd_weight(x, dy), oracle.conv2d_bwd_weight(x, dy, w.shape, 1, 0)
+    assert np.array_equal(np.isfinite(got), np.isfinite(ref)) and not np.isfinite(ref).all() and np.isfinite(ref[:, 2]).any()
 
 
 def test_chosen(mxc):
