@@ -309,8 +309,11 @@ int bwd_data_nhwc(const ConvShape &s, int dtype, const void *dy, const void *w, 
         if (bwd_data_reads_filter_in_place(s2)) in_place = wt;
         else if (mode == FILTER_RAW && (direct == IMAGE_STREAM || (direct == IMAGE_NONE && bwd_data_small_in_place(s2, false)))) in_place = w2;
         if (prep) {
-            MXC_TRY(s2d_pack_w(s, w, w2, st));
-            if (in_place != w2) MXC_TRY(igemm_bwd_data_prepare(s2, w2, wt, st, true));
+            if (in_place == nullptr) MXC_TRY(s2d_pack_wt(s, w, wt, st));
+            else {
+                MXC_TRY(s2d_pack_w(s, w, w2, st));
+                if (in_place != w2) MXC_TRY(igemm_bwd_data_prepare(s2, w2, wt, st, true));
+            }
         }
         if (!run) return MXC_OK;
         if (direct != IMAGE_NONE) MXC_TRY(igemm_bwd_data_image(direct, s2, image, dy, in_place, wt, dx, st, &v));

@@ -499,6 +499,7 @@ bool s2d_applicable(const ConvShape &s);
 ConvShape s2d_shape(const ConvShape &s);      // the equivalent stride-1 problem: x2[N][H2][W2][C2], w2[K][R2][S2][C2]
 int s2d_pack_x(const ConvShape &s, const void *x, void *x2, hipStream_t st);
 int s2d_pack_w(const ConvShape &s, const void *w, void *w2, hipStream_t st);
+int s2d_pack_wt(const ConvShape &s, const void *w, void *wt, hipStream_t st);       // ... as igemm_bwd_data_prepare makes of it
 int s2d_unpack_dx(const ConvShape &s, const void *dx2, void *dx, hipStream_t st, const void *mask = nullptr);   // mask: see PostOp
 bool igemm_fwd_smallc_supported(const ConvShape &s);
 int igemm_fwd_smallc(const ConvShape &s, const void *xp, const void *wp, void *y, hipStream_t st, const char **variant,
