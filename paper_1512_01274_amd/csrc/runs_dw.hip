@@ -342,7 +342,11 @@ int run_dw_ranges(int shape, long long M, int ranges, int *span)
     return (int)((M + *span - 1) / *span);
 }
 
-int run_dw_best(const WgradGeom &g, int most_ranges, int *ranges, int *span, double *us)
+// What a dw of so many MB costs besides, where its order is not the columns' (copies): the pass that sums its ranges finds every place, and of one
+// range it is a pass that the wave kernel does without (4 images of 14x14, 491 to 300 channels, 3x3: 24 us).
+double dw_places_us(int ranges, double mb) { return ranges == 1 ? 3 + 4 * mb : mb; }
+
+int run_dw_best(const WgradGeom &g, int most_ranges, bool copies, int *ranges, int *span, double *us)
 {
     const long long M = (long long)g.N * g.P * g.W;
     const double mb = 4e-6 * g.K * g.TR * g.TS * g.run;
@@ -358,7 +362,7 @@ int run_dw_best(const WgradGeom &g, int most_ranges, int *ranges, int *span, dou
             last = n;
             const double rounds = (double)((tiles * n + 255) / 256), stages = (double)(len / (32 * s.wp));
             const double t = s.fixed + rounds * stages * (s.tap * g.TS + s.stage) + s.block * rounds * g.TS * s.mi + (n > 1 ? s.sum + s.parts * n * mb : 0) +
-                             s.tile * tiles * n / 256.0 + s.out * mb;
+                             s.tile * tiles * n / 256.0 + s.out * mb + (copies ? dw_places_us(n, mb) : 0);
             if (best < 0 || t < *us) { best = i; *us = t; *ranges = n; *span = len; }
         }
     }

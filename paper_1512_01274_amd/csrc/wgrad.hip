@@ -511,7 +511,7 @@ int launch_choice(int idx, const WgradParams &p, int tiles, hipStream_t st)
 // that are copies written just before
 struct DwWave { int shape, ranges, span; };
 // run: the run kernel's (runs_dw.hip), likewise
-struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave[2], run; };
+struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave[2], run[2]; };
 
 // Tile and split choice: the pair with the least modelled time - rounds over the chip's workgroup
 // slots (256 CUs x slots per CU) x stages each split walks x time per stage, plus the traffic of
@@ -519,7 +519,7 @@ struct Plan { int tile, k_tiles, n_tiles, splits, span; DwWave wave[2], run; };
 // only) fixes the tile.
 Plan search_plan(const WgradGeom &g, int forced, int forced_splits);
 DwWave wave_choice(const WgradGeom &g, const Plan &pl, bool copies);
-DwWave run_choice(const WgradGeom &g, const Plan &pl);
+DwWave run_choice(const WgradGeom &g, const Plan &pl, bool copies);
 
 #include "tuned_wgrad.inc"
 
@@ -545,7 +545,7 @@ Plan make_plan(const WgradGeom &g)
         if (last.forced != forced || last.splits != splits || memcmp(&last.g, &g, sizeof g)) last = Entry{g, forced, splits, search_plan(g, forced, splits)};
         Plan pl = last.plan;
         pl.wave[0] = pl.wave[1] = wave_choice(g, pl, false);       // what the hook forces on the wave or run kernel is looked up on every call
-        pl.run = run_choice(g, pl);
+        pl.run[0] = pl.run[1] = run_choice(g, pl, false);
         return pl;
     }
     static thread_local PlanCache<WgradGeom, Plan> cache;
@@ -559,7 +559,7 @@ Plan make_plan(const WgradGeom &g)
             }
         Plan pl = search_plan(g, tuned, splits);
         for (const bool copies : {false, true}) pl.wave[copies] = wave_choice(g, pl, copies);
-        pl.run = run_choice(g, pl);
+        for (const bool copies : {false, true}) pl.run[copies] = run_choice(g, pl, copies);
         return pl;
     });
 }
@@ -609,7 +609,10 @@ DwWave wave_choice(const WgradGeom &g, const Plan &pl, bool copies)
 // (340 layers of 0.6 to 400 GFLOP): below 0.7 0.67 / 0.96, at 0.7-0.8 0.79 / 1.01, at 0.8-0.9 0.88 / 1.06, at 0.9-0.95 0.93 / 1.23,
 // at 0.95-1 0.99 / 1.12, above 1 1.2 and more.  256x256 tiles run up to a quarter faster than modelled: below 0.74 0.93 / 0.96, at
 // 0.75-0.83 0.99 / 1.03.
-DwWave run_choice(const WgradGeom &g, const Plan &pl)
+// copies: dw's order or rows are not the columns' (NCHW, padded channels, first layers), for which the wave kernel of one range stores its results
+// where they belong and this one takes another pass (dw_places_us).  The models know it less well: with a line of 0.9, 17 of 110 such
+// layers ran 2 to 12% slower than before, all against the wave kernel; with 0.75 29 change kernel, 0.83 in the mean, 0.97 at worst.
+DwWave run_choice(const WgradGeom &g, const Plan &pl, bool copies)
 {
     DwWave w{-1, 0, 0};
     if (!run_dw_applicable(g)) return w;
@@ -626,13 +629,15 @@ DwWave run_choice(const WgradGeom &g, const Plan &pl)
         return w;
     }
     DwWave best{-1, 0, 0};
-    double us = 0, other = tile_us(g, pl);
-    best.shape = run_dw_best(g, pl.splits, &best.ranges, &best.span, &us);
-    if (pl.wave[0].shape >= 0) {
+    const double mb = 4e-6 * g.K * g.TR * g.TS * g.run;
+    double us = 0, other = tile_us(g, pl) + (copies ? dw_places_us(pl.splits, mb) : 0);
+    best.shape = run_dw_best(g, pl.splits, copies, &best.ranges, &best.span, &us);
+    if (pl.wave[copies].shape >= 0) {
         int ranges = 1;
-        wave_dw_best(g, false, pl.splits, &ranges, &other);
+        wave_dw_best(g, copies, pl.splits, &ranges, &other);
+        if (copies && ranges > 1) other += dw_places_us(ranges, mb);
     }
-    const double line = pl.wave[0].shape < 0 && kTiles[pl.tile].bm == 256 && kTiles[pl.tile].bn == 256 ? 0.74 : 0.9;
+    const double line = pl.wave[copies].shape >= 0 ? (copies ? 0.75 : 0.9) : kTiles[pl.tile].bm == 256 && kTiles[pl.tile].bn == 256 ? 0.74 : 0.9;
     return best.shape >= 0 && us < line * other ? best : w;
 }
 
@@ -671,7 +676,7 @@ Plan search_plan(const WgradGeom &g, int forced, int forced_splits)
                 best = t_us;
                 long long span = (M + sp - 1) / sp;
                 span = (span + tc.bp - 1) / tc.bp * tc.bp;
-                best_pl = Plan{t, k_tiles, n_tiles, (int)((M + span - 1) / span), (int)span, {{-1, 0, 0}, {-1, 0, 0}}, {-1, 0, 0}};
+                best_pl = Plan{t, k_tiles, n_tiles, (int)((M + span - 1) / span), (int)span, {{-1, 0, 0}, {-1, 0, 0}}, {{-1, 0, 0}, {-1, 0, 0}}};
             }
         }
     }
@@ -803,16 +808,17 @@ int wgrad(const WgradGeom &g, const void *x, const void *dy, void *dw, bool dw_b
 {
     const Plan pl = make_plan(g);
     // the operands of NCHW problems, padded channels and first layers are copies (prepared inputs too: the same kernel, the same bits)
-    const DwWave wv = pl.wave[kcrs || g.K != g.Kout || !dw_identity(g)];
+    const bool copies = kcrs || g.K != g.Kout || !dw_identity(g);
+    const DwWave wv = pl.wave[copies], run = pl.run[copies];
     if (g.R * g.S == 1) kcrs = false;                 // one tap: both orders are the same
-    if (pl.run.shape >= 0) {
-        const bool identity = dw_identity(g), direct = pl.run.ranges == 1 && identity && !dw_bf16 && !kcrs;
-        *variant = run_dw_name(pl.run.shape);
-        const int rc = run_dw_launch(pl.run.shape, g, pl.run.ranges, pl.run.span, x, dy, direct ? (float *)dw : partial, direct ? g.Kout : g.K, st);
+    if (run.shape >= 0) {
+        const bool identity = dw_identity(g), direct = run.ranges == 1 && identity && !dw_bf16 && !kcrs;
+        *variant = run_dw_name(run.shape);
+        const int rc = run_dw_launch(run.shape, g, run.ranges, run.span, x, dy, direct ? (float *)dw : partial, direct ? g.Kout : g.K, st);
         if (rc != MXC_OK) return rc;
         if (direct) return resum != nullptr ? resum_dw(*resum, dw, false, st) : MXC_OK;
-        return dw_bf16 ? launch_reduce(g, partial, (bf16_t *)dw, pl.run.ranges, g.TR * g.TS * g.run, identity, kcrs, st, resum)
-                       : launch_reduce(g, partial, (float *)dw, pl.run.ranges, g.TR * g.TS * g.run, identity, kcrs, st, resum);
+        return dw_bf16 ? launch_reduce(g, partial, (bf16_t *)dw, run.ranges, g.TR * g.TS * g.run, identity, kcrs, st, resum)
+                       : launch_reduce(g, partial, (float *)dw, run.ranges, g.TR * g.TS * g.run, identity, kcrs, st, resum);
     }
     if (wv.shape >= 0) {
         const int ncols = g.TR * g.TS * g.run;

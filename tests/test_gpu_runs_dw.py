@@ -89,3 +89,14 @@ def test_chosen(mxc):
     dw = torch.empty(96, 5, 5, 64, device="cuda")
     mxc.mxc_conv2d_bwd_weight(*a, x, dy, dw, mxc.alloc_workspace(mxc.mxc_conv2d_workspace_bytes(mxc.MXC_BWD_WEIGHT, *a)))
     assert "wgrad_run_" in mxc.mxc_last_variant() and bool((dw == 0).all())
+
+
+def test_padded_channels_of_one_range(mxc, oracle):
+    """A large dw of few pixels with channels that are padded: the wave kernel, which stores it in place without another pass."""
+    dims = (4, 491, 14, 14, 300, 3, 3, 1, 1)
+    x, w, dy = gen.random_case(9, *dims, dtype="bf16", dist="normal")
+    run = util.Runner(mxc, dims, "bf16", "nhwc")
+    got = run.bwd_weight(x, dy)
+    assert "wgrad_run_" not in mxc.mxc_last_variant()
+    ref, den = (oracle.conv2d_bwd_weight(f(x), f(dy), w.shape, 1, 1) for f in (lambda t: t, np.abs))
+    assert np.all(np.abs(got - ref) <= util.tight_bound(ref, den, "bf16", False))
