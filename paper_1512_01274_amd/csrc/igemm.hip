@@ -1477,9 +1477,8 @@ static int zeroing_tile(const ConvShape &s, bool masked, double *us)
 // slower: 9x10x10 128 to 128 channels 3x3 12.5 -> 4.7 us.  A prepared filter saves the other path its first launch, and has to give the
 // same bits: six of 175 layers more than 3% slower (15% at worst).  The margin is larger from 10 modelled us on.  Measured time over the
 // other path's by the ratio of the models: 10-20 us at 0.5-0.6 0.55, with a prepared filter up to 1.37, at 0.6-0.8 0.98 (1.27).
-// 1x1 filters: against the tile that writes the zeros too, one launch as well.  Of 193 layers the kernel chosen takes 3.4% more than the
-// fastest of the five wave shapes and five tiles, as much with a line at 0.95 or 1.05; the wave kernel takes 0.7-0.9 of the tile's time
-// below 5 us, as long at 5-6, 1.1 at 6-7.5, 1.4 at 7.5-10 and 1.5 to 2.1 above.
+// 1x1 filters: against the tile that writes the zeros too, one launch as well.  Of 5386 layers of up to 80 MB the kernel chosen takes 1.4% more than
+// the fastest of the five wave shapes and five tiles (1.27 times as long at worst), as much with a line at 1.03 or 1.1, 1.9% with one at 0.95.
 static int classes_wave(const ConvShape &s, bool masked)
 {
     if (s.stride != 2 || s.C % 8 != 0) return -1;
@@ -1493,7 +1492,7 @@ static int classes_wave(const ConvShape &s, bool masked)
         ++g_plan_searches;
         double us = 0, other = 0, tile_us = 0;
         const int wv = (long long)s.N * s.H * s.W <= 1 << 30 ? wave_best_classes(s, masked, &us, &other) : -1;
-        if (wv >= 0 && zeroes_rest(s)) return zeroing_tile(s, masked, &tile_us) >= 0 && us < 1.03 * tile_us ? wv : -1;
+        if (wv >= 0 && zeroes_rest(s)) return zeroing_tile(s, masked, &tile_us) >= 0 && us < 1.06 * tile_us ? wv : -1;
         return wv >= 0 && us < (us < (s.R * s.S == 1 ? 7.5 : 10) ? 0.8 : 0.5) * other ? wv : -1;
     });
 }

@@ -16,6 +16,7 @@
 //
 // Measured (us, pixels x columns x reduction, igemm.hip's tile -> this kernel): 392 x 56 x 448 6.4 -> 3.4; 392 x 56 x 576 in 3x3
 // taps 6.7 -> 3.7; 2704 x 160 x 1000 10.8 -> 6.0; 46464 x 288 x 24 15.1 -> 10.9.
+#include <math.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -620,14 +621,18 @@ int wave_best_classes(const ConvShape &s, bool masked, double *us, double *other
     static const struct { int shape; float fixed, turn, longest, tile, mb; } kUs[] = {
         {2, 2.44f, 0.492f, 0.114f, 1.28f, 1.20f}, {3, 2.57f, 0.603f, 0.f, 1.34f, 1.00f}, {5, 2.71f, 0.538f, 0.f, 1.28f, 0.809f},
         {7, 3.24f, 0.258f, 0.112f, 0.611f, 0.046f}, {8, 3.32f, 0.353f, 0.197f, 0.856f, 0.098f}};
-    // 1x1 filters, of which three classes have no tap: fitted to 570 layers below 14 us, 6-12% off
-    static const decltype(kUs) kUs1x1 = {
-        {2, 2.18f, 0.f, 0.369f, 1.64f, 1.15f}, {3, 2.17f, 0.f, 0.549f, 1.70f, 1.05f}, {5, 1.76f, 0.f, 0.437f, 2.39f, 0.403f},
-        {7, 3.26f, 0.351f, 0.f, 0.650f, 0.104f}, {8, 3.33f, 0.f, 0.521f, 0.885f, 0.146f}};
+    // 1x1 filters, of which three classes have no tap: fitted to 5386 layers, those below 16 us, 3% off (8 waves a tile) and 5-6%.  Their tiles of
+    // zeros count like the others where a CU holds one workgroup at a time: one tile more than the chip has CUs is 1.7 to 2.5 us (12 images
+    // of 16x16, 96 to 448 channels: 288 tiles of 32x32 7.1 us, 144 of 64x32 5.1).  Of 3007 layers the shape chosen takes 0.5% more than the
+    // fastest; with tiles counted in fractions of the chip 1.5%, and a tenth to 1.42 times as long in 125.
+    static const struct { int shape; float fixed, longest, round, work, tile, mb; } kUs1x1[] = {
+        {2, 3.93f, 0.227f, 1.70f, 1.22f, 0.f, 0.f}, {3, 4.21f, 0.325f, 2.18f, 1.50f, 0.f, 0.f}, {5, 4.29f, 0.373f, 2.46f, 1.77f, 0.f, 0.f},
+        {7, 3.91f, 0.301f, 0.962f, 0.399f, 0.165f, 0.177f}, {8, 4.33f, 0.468f, 1.91f, 0.390f, 0.173f, 0.150f}};
+    const bool one = s.R * s.S == 1;
     double gflop = 0, zeros = 0, longest = 0, mb = 0;
     int best = -1;
-    for (const auto &u : s.R * s.S == 1 ? kUs1x1 : kUs) {
-        const WaveShape &w = kShapes[u.shape];
+    for (int i = 0; i < 5; ++i) {
+        const WaveShape &w = kShapes[one ? kUs1x1[i].shape : kUs[i].shape];
         const int bm = 16 * w.mb * w.mg, n_tiles = (s.C + 16 * w.nb - 1) / (16 * w.nb);
         double tiles = 0, steps = 0, most = 0;
         gflop = zeros = longest = mb = 0;
@@ -644,10 +649,18 @@ int wave_best_classes(const ConvShape &s, bool masked, double *us, double *other
                 if (Kd == 0) zeros += 2e-6 * rows * s.C;
                 else mb += 2e-6 * rows * s.C * (masked ? 2 : 1);
             }
-        const double t = u.fixed + u.turn * (steps > most ? steps : most) + u.longest * most + u.tile * (tiles > 1 ? tiles : 1) + u.mb * (mb + zeros);
-        if (best < 0 || t < *us) { best = u.shape; *us = t; }
+        double t;
+        if (one) {
+            const auto &u = kUs1x1[i];
+            const int slots = 160 / (w.kg * w.mg * w.ns * w.u * (w.mb + w.nb));
+            t = u.fixed + u.longest * most + u.round * (ceil(ceil(tiles) / slots) - 1) + u.work * steps + u.tile * tiles + u.mb * (mb + zeros);
+        } else {
+            const auto &u = kUs[i];
+            t = u.fixed + u.turn * (steps > most ? steps : most) + u.longest * most + u.tile * (tiles > 1 ? tiles : 1) + u.mb * (mb + zeros);
+        }
+        if (best < 0 || t < *us) { best = one ? kUs1x1[i].shape : kUs[i].shape; *us = t; }
     }
-    if (s.R * s.S == 1) *other = 9.28 + 0.902 * gflop + 0.125 * mb + 0.206 * zeros + 0.133 * 2e-6 * s.N * s.P * s.Q * s.K;
+    if (one) *other = 9.28 + 0.902 * gflop + 0.125 * mb + 0.206 * zeros + 0.133 * 2e-6 * s.N * s.P * s.Q * s.K;
     else *other = 8.45 + 0.774 * gflop + 0.385 * (mb + zeros) + 0.127 * zeros + 0.00668 * longest + 0.52 * 2e-6 * s.K * s.C * s.R * s.S;
     return best;
 }
