@@ -191,12 +191,13 @@ BiasPlan plan(long long N, int K, long long PQ, int dtype, int layout)
     b.chunks = K * b.fold / V;
     b.rows = N * PQ / b.fold;
     b.left = N * PQ % b.fold;
-    const bool one = b.fold == 1 && b.rows <= 4096;
-    // Its 1024 threads are then up to 1024 row groups: fewer loads each, one after another, as long as not too many workgroups fetch the same
-    // lines.  us, 4 chunks a workgroup -> these, in a graph: 1300 rows of 32 bf16 channels 4.1 -> 3.4, 2940 of 144 5.3 -> 4.7; one chunk would
-    // take 3751 rows of 320 from 7.5 to 8.8, 4000 of 512 from 5.6 to 12.
-    const int narrow = b.rows <= 1024 ? 4 : b.rows <= 2048 ? 2 : b.chunks <= 24 ? 1 : 4;
-    b.cpb = b.chunks < (one ? narrow : BT) ? b.chunks : (one ? narrow : BT);
+    // One share in blocks of few columns: more workgroups, and with a block within SHORT_CHUNKS the kernel of 256 threads (see run), as long as not too
+    // many of them fetch the same lines.  Time over that of 4 chunks, which from 1025 rows on are 1024 threads, in a graph, 3162 tensors, mean and
+    // worst: 1025 to 2048 rows, 2 chunks: of rows of 3 to 20 chunks 0.88 / 1.11, of 21 to 63 1.01 / 1.30, of 64 1.34 / 1.46, of more 1.04 / 1.26; up
+    // to 4096 rows, 1 chunk: of 2 to 10 0.86 / 1.13, of 11 to 15 0.99 / 1.23, of 16 1.39 / 1.49, of 17 to 24 1.09 / 1.38.
+    const bool one = b.fold == 1 && b.rows <= SHORT_CHUNKS;
+    const int within = b.rows <= SHORT_CHUNKS / 4 ? 4 : b.rows <= SHORT_CHUNKS / 2 ? 2 : 1, width = one ? (b.chunks <= 10 * within ? within : 4) : BT;
+    b.cpb = b.chunks < width ? b.chunks : width;
     // wide rows: equal column blocks of at most 256 chunks, so that 1024 threads are four row groups with loads in flight
     if (!one && b.cpb > MAX_CPB) b.cpb = MAX_CPB;
     if (one) { b.parts = 1; return b; }

@@ -8,7 +8,10 @@ pytestmark = pytest.mark.gpu
 
 CASES = [(1, 1, 1, 1), (2, 8, 3, 3), (1, 7, 1, 1), (3, 7, 5, 9), (5, 30, 33, 31), (64, 20, 33, 7), (70, 96, 13, 13), (9, 1000, 5, 5), (17, 2600, 1, 1),
          (3, 2056, 41, 43), (200, 129, 11, 9), (1, 64, 300, 301), (40, 16, 57, 57), (2, 4096, 1, 1), (130, 6, 12, 20),
-         (1, 512, 65, 65), (1, 520, 65, 65), (3, 63, 20, 20), (3, 65, 20, 20)]       # 64 chunks a row and one more or less
+         (1, 512, 65, 65), (1, 520, 65, 65), (3, 63, 20, 20), (3, 65, 20, 20),       # 64 chunks a row and one more or less
+         # one share in blocks of 4, 2 and 1 chunks: the lines at 1024, 2048 and 4096 rows, and at 20 and 10 chunks a row
+         (1, 80, 32, 32), (1, 80, 25, 41), (1, 160, 25, 41), (1, 168, 25, 41), (2, 160, 32, 32), (2, 84, 32, 32), (1, 80, 3, 683), (1, 88, 3, 683), (1, 40, 3, 683),
+         (1, 44, 3, 683), (4, 80, 32, 32), (4, 88, 32, 32), (4, 8, 32, 32), (1, 80, 17, 241), (1, 24, 17, 241)]
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
