@@ -537,6 +537,7 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
         PlaneOut direct{out, nullptr, K, false};
         PostOp post2 = post;
         post2.planes = &direct;
+        post2.copied = true;
         MXC_TRY(fwd_nhwc(s, MXC_BF16, x2, w2, y2, post2, ws, st, dry));
         if (dry || direct.stored) return MXC_OK;
         jobs[0] = relay_to_nchw(y2, out, s.N, K, s.P * s.Q, s.K);
@@ -554,6 +555,7 @@ int run_bf16_nchw(int pass, const ConvShape &s, const void *a, const void *b, vo
         void *mask2 = run && (post.mask != nullptr || post.relu) ? ws.take(nx) : nullptr;   // see run_pass
         PostOp post2 = post;
         post2.relu = 0;
+        post2.copied = true;
         FilterMode inner = mode;
         PlaneOut direct{out, post.mask, C, false};
         if (run && plain && !first && !resum && igemm_bwd_data_planes(s, post.mask != nullptr)) post2.planes = &direct;

@@ -1267,7 +1267,7 @@ int igemm_fwd(const ConvShape &s, const void *x, const void *w, void *y, hipStre
               void *split_ws)
 {
     IgemmParams p{};
-    p.bias = post.bias; p.relu = post.relu;
+    p.bias = post.bias; p.relu = post.relu; p.copied = post.copied;
     p.in = (const bf16_t *)x; p.wm = (const bf16_t *)w; p.out = (bf16_t *)y;
     p.N = s.N; p.Hi = s.H; p.Wi = s.W; p.Ci = s.C; p.pix = s.C; p.Co = s.K; p.Cw = real_k(s);
     p.TR = s.R; p.TS = s.S; p.tstep_h = 1; p.tstep_w = 1;
@@ -1548,7 +1548,7 @@ int igemm_bwd_data(const ConvShape &s, const void *dy, const void *w_in_place, v
     const bool bt = w_in_place != nullptr;
     IgemmParams p = bwd_data_params(s);
     p.in = (const bf16_t *)dy; p.out = (bf16_t *)dx;
-    p.mask = (const bf16_t *)post.mask;
+    p.mask = (const bf16_t *)post.mask; p.copied = post.copied;
     if (s.stride == 1) {
         p.wm = bt ? (const bf16_t *)w_in_place : (const bf16_t *)wt;
         p.wm_by_k = bt && !bwd_data_reads_filter_in_place(s) && bwd_data_streams_filter(s, p.mask != nullptr);

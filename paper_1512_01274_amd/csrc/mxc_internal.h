@@ -72,6 +72,7 @@ struct PostOp {
     int relu = 0;                  // forward: max(0, .) after the bias
     const void *mask = nullptr;    // backward-data: result is 0 where mask <= 0; same shape, type and layout as dx
     struct PlaneOut *planes = nullptr;
+    bool copied = false;           // the result is a copy that a re-layout reads next
 };
 // An NCHW problem on NHWC copies: a kernel that can stores the result straight to its planes and says so.
 struct PlaneOut {
@@ -434,6 +435,7 @@ struct IgemmParams {
     int f32_out;         // store the fp32 accumulators to `partial` ([m][co], one split) instead of a rounded result to `out`
     int zero_rest;       // dx of a 1x1 filter at stride 2: the three pixels of a 2x2 block that no tap reaches are written too, as zeros
     int nt_out;          // the 16-byte result stores are non-temporal
+    int copied;          // see PostOp
     unsigned out_bytes;  // size of the output tensor when below 2 GiB (buffer stores with range-checked offsets), else 0
     int tap_inner;       // reduction order (see tap_inner_order): 1 = all taps of a channel block before the next block
     // applied to the accumulators before the store (all optional)
