@@ -1162,10 +1162,8 @@ int run_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool
 }
 
 // Whether the streaming kernel runs a 1x1 filter at stride 1 that the measured table does not hold, in the wave kernel's or the plan's place (of
-// an NCHW problem the wave kernel stays, see run_choice).  Measured time over the plan's, mean and worst, by the ratio of the models (420
-// layers of 20 to 900 MB): plans modelled at 20-40 us at 0.7-0.9 0.82 / 0.99, at 0.9-1 0.92 / 1.11, above 1 0.98 / 1.36; from 40 us on below 0.8
-// 0.77 / 1.00, at 0.8-0.95 0.84 / 1.13, at 0.95-1 0.86 / 1.11, above 0.92 / 1.25; over the wave kernel's from 40 us on 0.85 / 1.02 at
-// 0.9-1.1, below 40 us 1.06 / 1.4 at 0.95-1.1.  What the tiles lose is that a CU's loads wait while it stores.
+// an NCHW problem the wave kernel stays, see run_choice), by the models of both (stream_pays).  What the tiles lose is that a CU's loads
+// wait while it stores.
 bool stream_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool planes)
 {
     if (p.TR * p.TS != 1 || p.in_mul_h != 1 || p.in_mul_w != 1 || getenv("MXC_FORCE_VARIANT") || !stream_applicable(p)) return false;
@@ -1180,8 +1178,7 @@ bool stream_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, 
         if (whole_launch(pl.main) || (wave >= 0 && planes)) return false;
         if (wave >= 0) wave_best(M, p.Co, p.Ci, bwd, masked, &other);
         else other = plan_us(pl, M, p.Co, p.Ci, can_split ? split_count(M, p.Co, p.Ci) : 1, masked);
-        const double us = stream_us(p, masked);
-        return us < other * (other >= 40 ? 1. : 0.9);
+        return stream_pays(p, masked, other);
     });
 }
 

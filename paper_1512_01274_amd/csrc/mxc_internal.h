@@ -460,7 +460,7 @@ int winograd_fwd(const ConvShape &s, const void *x, const void *w, void *y, void
 // and the launch over all rows (both take p as a launch site fills it: the fields the launcher derives -
 // M, row range, tile counts, byte sizes, linear_out, tap_inner - are ignored and recomputed).
 bool stream_applicable(const IgemmParams &p);
-double stream_us(const IgemmParams &p, bool masked);      // modelled time of a 1x1 filter at stride 1
+bool stream_pays(const IgemmParams &p, bool masked, double other);      // 1x1 filters at stride 1: rather than a kernel modelled at `other` us
 int stream_launch(const IgemmParams &p, hipStream_t st);
 // window.hip: the same GEMM for multi-tap stride-1 layers of at most 64 input channels, from an LDS-resident input
 // window and filter (see there); same conventions as the streaming kernel.

@@ -48,7 +48,7 @@ struct StreamParams {
     int n_wg_m;      // workgroups per column tile; workgroup w of them owns rows [m_begin + w*rows_per_wg, + rows_per_wg)
     int rows_per_wg; // a multiple of 32
     int units;       // n_wg_m * n_tiles (the grid is rounded up to whole XCD rounds)
-    int per_xcd;     // units per XCD, a multiple of n_tiles
+    int per_xcd;     // units per XCD: whole row ranges, a multiple of n_tiles, where that leaves none more than it holds (launch_stream_m)
     int b_bytes;     // LDS bytes of the resident filter tile: BN * KT * 128
     int nt;          // bit 0: results leave as non-temporal stores, bit 1: activations arrive as non-temporal loads
     unsigned out_bytes;   // size of the output tensor (< 2^31)
@@ -85,7 +85,8 @@ __global__ __launch_bounds__(64 * (NC + NL)) void stream_kernel(const StreamPara
     const bool loader = wave >= NC;
 
     // Workgroup -> (row range, column tile).  Consecutive workgroup ids are dealt round-robin to the 8 XCDs;
-    // the column tiles of one row range get ids of the same XCD, so the activations they share meet in one L2.
+    // the column tiles of one row range get ids of the same XCD, so the activations they share meet in one L2 (all but the ranges that lie
+    // across two XCDs where those share the units evenly: see per_xcd).
     const int unit = (blockIdx.x & 7) * sp.per_xcd + (blockIdx.x >> 3);
     if (unit >= sp.units) return;
     const int n_tile = unit % p.n_tiles, wg_m = unit / p.n_tiles;
@@ -571,6 +572,27 @@ double stream_us(const IgemmParams &p, bool masked)
     const long long m_tiles = (M + bm - 1) / bm, fit = 256 * per_cu / n_tiles, wgs = fit < 1 ? 1 : fit > m_tiles ? m_tiles : fit;
     const double tiles = (double)((((M + wgs - 1) / wgs + 31) / 32 * 32 + bm - 1) / bm), mco = 1e-6 * M * p.Co;
     return k[0] + k[1] * 1e-6 * M * p.Ci * n_tiles + k[2] * mco + (masked ? k[3] * mco : 0) + tiles * (k[4] * KT + k[5] * KT * c.bn / 32 + k[6] + k[7] * (c.bn / 32));
+}
+
+// Whether this kernel runs such a layer where the other one is modelled at `other` us.  Measured time over the other's, every call on tensors that
+// come from memory, mean and worst, by the ratio of the models (5483 NHWC layers of 20 to 900 MB, 5196 of them after the two rules below): others
+// of 20-40 us below 0.8 0.72 / 1.06, at 0.8-0.9 0.76 / 1.10; from 40 us on below 0.8 0.75 / 1.19, at 0.8-0.9 0.79 / 1.15, at 0.9-1 0.82 /
+// 1.35 (10 of 862 more than 3% slower).  Of 420 earlier layers those of 20-40 us had 0.92 / 1.11 at 0.9-1 and 0.98 / 1.36 above, those from 40 us
+// on 0.92 / 1.25 above 1.
+bool stream_pays(const IgemmParams &p, bool masked, double other)
+{
+    const StreamConfig c = stream_config(p);
+    const int KT = (p.Ci + BK - 1) / BK, n_tiles = (p.Co + c.bn - 1) / c.bn;
+    double line = other >= 40 ? 1. : 0.9;
+    if (!masked && n_tiles > 1) {
+        // Rows that are no whole number of 64 bytes, in parts by two column tiles: the stores, which are not non-temporal there (with such ones it
+        // would be 1.6 times as long), leave in pieces of lines, and one stage of products does not hide it: from 120 MB on 1.08 / 1.33 (121
+        // layers of 16 to 64 to 176, 208 or 240 channels; with 144 the second tile is narrow: 0.82).
+        if (KT == 1 && p.Co % 32 != 0 && p.Co > 160 && (long long)p.N * p.Mh * p.Mw * p.Co * 2 >= 120ll << 20) return false;
+        // Three stages in the four-wave form against tiles of 256 columns, which fetch the activations half as often: above 0.85 0.96 / 1.28 (166).
+        if (c.nc == 4 && KT == 3 && n_tiles % 2 == 0 && line > 0.85) line = 0.85;
+    }
+    return stream_us(p, masked) < line * other;
 }
 
 int stream_launch(const IgemmParams &p, hipStream_t st)
