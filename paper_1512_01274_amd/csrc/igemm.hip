@@ -1134,9 +1134,11 @@ int wave_choice(long long M, int Co, int Kd, bool bwd, bool masked, bool can_spl
 
 // The shape of the run kernel (runs.hip) that runs this GEMM, or -1: the wave kernel or the plan does, whichever it is without the run
 // kernel.  Of an NCHW problem the wave kernel stores the result to its planes, which is a re-layout less.  Measured time over the other
-// kernel's, mean and worst, by the ratio of the models (320 layers of 0.4 to 400 GFLOP, forward and dx): below 0.7 0.66 / 0.95, at
-// 0.7-0.8 0.76 / 0.99, at 0.8-0.9 0.90 / 1.04, at 0.9-0.95 0.97 / 1.14, from 60 us on 0.90 / 1.08, at 0.95-1 0.97 / 1.15, above 1 1.2 and
-// more.  Plans of the streaming and window kernels come from the measured table and stay.
+// kernel's, mean and worst, by the ratio of the models (12685 layers of 0.3 to 300 GFLOP, forward and dx): others below 60 us at 0.8-0.85 0.82 /
+// 1.11, at 0.85-0.9 0.86 / 1.16; from 60 us on at 0.85-0.9 0.86 / 1.16, at 0.9-0.95 0.89 / 1.12, at 0.95-1 0.91 / 1.07; 320 earlier layers had 1.2
+// and more above 1.  Wave kernels below 8 modelled us, whose launch weighs most, at 0.85-0.875 0.84 / 1.01, at 0.875-0.9 1.01 / 1.15 (201
+// layers, half of them more than 3% slower); plans of a split reduction 0.95 / 1.08 and 1.00 / 1.16.  Plans of the streaming and window
+// kernels come from the measured table and stay.
 int run_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool planes)
 {
     if (!run_applicable(p)) return -1;
@@ -1154,10 +1156,12 @@ int run_choice(const IgemmParams &p, bool bwd, bool masked, bool can_split, bool
         const Plan pl = choose_plan(M, p.Co, Kd, true, masked);
         if (whole_launch(pl.main) || (wave >= 0 && planes)) return -1;
         if (wave >= 0) wave_best(M, p.Co, Kd, bwd, masked, &other);
-        else other = plan_us(pl, M, p.Co, Kd, can_split ? split_count(M, p.Co, Kd) : 1, masked);
+        const int splits = wave < 0 && can_split ? split_count(M, p.Co, Kd) : 1;
+        if (wave < 0) other = plan_us(pl, M, p.Co, Kd, splits, masked);
         // two launches take longer than modelled, at 0.9-1 0.87 / 0.98 (9 layers), but not with tiles of 256x256: 0.97 / 1.15 (5)
         const bool largest = wave < 0 && pl.main == 1, two = wave < 0 && pl.tail >= 0;
-        return us < (largest ? 0.9 : two ? 1. : other >= 60 ? 0.95 : 0.9) * other ? run : -1;
+        const bool close = splits > 1 || (wave >= 0 && other < 8);
+        return us < (close ? 0.875 : largest ? 0.9 : two ? 1. : other >= 60 ? 0.95 : 0.9) * other ? run : -1;
     });
 }
 

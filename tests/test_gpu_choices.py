@@ -79,6 +79,20 @@ def test_either_side_of_a_choice(mxc, oracle, monkeypatch, dtype, layout, shape,
         assert held == ({True, False} if kernel else {True}), got
 
 
+# Layers that the kernels sharing pixels among the taps of a filter row run 1.06 to 1.2 times as long as the kernel they leave it to: (N, C, H, W, K, R), the
+# pass (0 forward, 1 dx with a mask).  Wave kernels of a few us and split reductions.
+LEFT = [((28, 32, 16, 15, 96, 3), 0), ((13, 512, 8, 14, 32, 3), 1), ((163, 384, 8, 8, 64, 5), 0), ((2, 480, 24, 24, 352, 5), 1)]
+
+
+@pytest.mark.parametrize("dims,which", LEFT)
+def test_left_by_the_run_kernels(mxc, oracle, monkeypatch, dims, which):
+    monkeypatch.delenv("MXC_FORCE_VARIANT", raising=False)
+    monkeypatch.delenv("MXC_FORCE_WGRAD", raising=False)
+    N, C, H, W, K, R = dims
+    name, = _walk(mxc, oracle, "bf16", "nhwc", (C, H, W, K, R, R, 1, R // 2), (N,))[which]
+    assert "_run_" not in name, name
+
+
 # 1x1 at stride 2, of whose dx three pixels in four are zeros: N, C, H, W, K and whether the wave kernel runs it (5x24x24 4.1 us where the
 # other path takes 11.7; the last four with a mask 26.6, 67.7, 47.8 and 65.9 where the other path takes 15.7, 37.5, 30.1 and 50.5)
 STRIDED_1X1 = [(1, 64, 14, 14, 128, True), (5, 32, 24, 24, 480, True), (8, 128, 28, 28, 256, True), (63, 216, 29, 29, 176, False), (146, 192, 42, 42, 176, False),
