@@ -606,12 +606,13 @@ DwWave wave_choice(const WgradGeom &g, const Plan &pl, bool copies)
 
 // The shape of the run kernel that runs this gradient and its pixel ranges, no more than the plan has, or shape -1: the wave kernel or
 // the planned tile does, whichever it is without it.  Measured time over the other kernel's, mean and worst, by the ratio of the models
-// (340 layers of 0.6 to 400 GFLOP): below 0.7 0.67 / 0.96, at 0.7-0.8 0.79 / 1.01, at 0.8-0.9 0.88 / 1.06, at 0.9-0.95 0.93 / 1.23,
-// at 0.95-1 0.99 / 1.12, above 1 1.2 and more.  256x256 tiles run up to a quarter faster than modelled: below 0.74 0.93 / 0.96, at
-// 0.75-0.83 0.99 / 1.03.
+// (5329 layers of 0.3 to 300 GFLOP).  Tiles: at 0.8-0.85 0.84 / 1.07, at 0.85-0.9 0.87 / 1.14; but blocks of 128x32 at 0.8-0.825 0.92 / 1.10, at
+// 0.825-0.9 0.96 / 1.16 (34 of 125 more than 3% slower).  Tiles of 256x256 run up to a quarter faster than modelled: at 0.65-0.7 0.93 / 1.11, at
+// 0.7-0.725 0.95 / 1.05, at 0.725-0.74 1.00 / 1.14.  Wave kernel: at 0.8-0.85 0.87 / 1.06, at 0.85-0.9 0.94 / 1.08.  Of 340 earlier layers those above
+// 1 took 1.2 and more.
 // copies: dw's order or rows are not the columns' (NCHW, padded channels, first layers), for which the wave kernel of one range stores its results
-// where they belong and this one takes another pass (dw_places_us).  The models know it less well: with a line of 0.9, 17 of 110 such
-// layers ran 2 to 12% slower than before, all against the wave kernel; with 0.75 29 change kernel, 0.83 in the mean, 0.97 at worst.
+// where they belong and this one takes another pass (dw_places_us).  The models know it less well: against the wave kernel at 0.65-0.7 0.93 /
+// 1.03, at 0.7-0.75 0.95 / 1.07, above 2 to 12% slower in 17 of 110.
 DwWave run_choice(const WgradGeom &g, const Plan &pl, bool copies)
 {
     DwWave w{-1, 0, 0};
@@ -637,7 +638,8 @@ DwWave run_choice(const WgradGeom &g, const Plan &pl, bool copies)
         wave_dw_best(g, copies, pl.splits, &ranges, &other);
         if (copies && ranges > 1) other += dw_places_us(ranges, mb);
     }
-    const double line = pl.wave[copies].shape >= 0 ? (copies ? 0.75 : 0.9) : kTiles[pl.tile].bm == 256 && kTiles[pl.tile].bn == 256 ? 0.74 : 0.9;
+    const bool largest = kTiles[pl.tile].bm == 256 && kTiles[pl.tile].bn == 256, narrow = best.shape >= 0 && !strcmp(run_dw_name(best.shape), "wgrad_run_128x32");
+    const double line = pl.wave[copies].shape >= 0 ? (copies ? 0.75 : 0.9) : largest ? 0.725 : narrow ? 0.825 : 0.9;
     return best.shape >= 0 && us < line * other ? best : w;
 }
 

@@ -80,8 +80,9 @@ def test_either_side_of_a_choice(mxc, oracle, monkeypatch, dtype, layout, shape,
 
 
 # Layers that the kernels sharing pixels among the taps of a filter row run 1.06 to 1.2 times as long as the kernel they leave it to: (N, C, H, W, K, R), the
-# pass (0 forward, 1 dx with a mask).  Wave kernels of a few us and split reductions.
-LEFT = [((28, 32, 16, 15, 96, 3), 0), ((13, 512, 8, 14, 32, 3), 1), ((163, 384, 8, 8, 64, 5), 0), ((2, 480, 24, 24, 352, 5), 1)]
+# pass (0 forward, 1 dx with a mask, 2 dw).  Wave kernels of a few us and split reductions; dw in blocks of 128x32, and against tiles of 256x256.
+LEFT = [((28, 32, 16, 15, 96, 3), 0), ((13, 512, 8, 14, 32, 3), 1), ((163, 384, 8, 8, 64, 5), 0), ((2, 480, 24, 24, 352, 5), 1),
+        ((23, 16, 52, 52, 512, 3), 2), ((10, 80, 63, 63, 352, 3), 2), ((147, 80, 15, 15, 480, 3), 2), ((54, 352, 41, 10, 240, 5), 2)]
 
 
 @pytest.mark.parametrize("dims,which", LEFT)
