@@ -339,7 +339,8 @@ int mxc_version(void);
  * for short reductions and "igemm_window" for multi-tap stride-1 layers of at most 64 channels, each one plan that
  * runs only where its filter tile fits on chip, family 3: fp32, family 4: the implicit GEMM of small problems,
  * family 5: their backward-weight, family 6: fp32 NHWC layers of whole 16-byte chunks of channels, backward-weight last,
- * family 7: dx of first layers at stride 1), NULL past the last.  These are the names that
+ * family 7: dx of first layers at stride 1, family 8: the implicit GEMM of 3- and 5-column filters at stride 1 whose taps of
+ * a filter row share their pixels, family 9: their backward-weight), NULL past the last.  These are the names that
  * mxc_last_variant() reports and that the tuning hooks MXC_FORCE_VARIANT=<name>[+<name of the shape for the
  * rows the last whole round leaves>] and MXC_FORCE_WGRAD=<name>[/<splits>] (environment, read per call) accept.
  * The tests walk the list; the tuning script times families 0 to 2, whose plans it tabulates: the others are chosen

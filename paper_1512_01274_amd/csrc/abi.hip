@@ -1130,7 +1130,8 @@ const char *mxc_tile_name(int family, int index)
 {
     return family == 0 ? igemm_tile_name(index) : family == 1 ? wgrad_tile_name(index) : family == 2 ? igemm_stream_name(index)
            : family == 3 ? f32_tile_name(index) : family == 4 ? wave_name(index) : family == 5 ? wave_dw_name(index)
-           : family == 6 ? f32_wave_name(index) : family == 7 && index == 0 ? taps_dx_name() : nullptr;
+           : family == 6 ? f32_wave_name(index) : family == 7 ? (index == 0 ? taps_dx_name() : nullptr) : family == 8 ? run_name(index)
+           : family == 9 ? run_dw_name(index) : nullptr;
 }
 
 int mxc_probe_mfma(int workgroups, int iters, void *out, size_t out_bytes, double *flops, void *hip_stream)

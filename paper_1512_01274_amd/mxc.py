@@ -123,7 +123,8 @@ def mxc_plan_searches() -> int:
 
 
 def mxc_tile_names(family: int):
-    """Names of the tile shapes of a kernel family (0: implicit GEMM, 1: backward-weight, 2: the streaming and the window implicit GEMM)."""
+    """Names of the tile shapes of a kernel family, 0 to 9 as include/mxc.h lists them (0: implicit GEMM, 1: backward-weight, 2: the streaming and
+    the window implicit GEMM)."""
     out, i = [], 0
     while True:
         n = _lib.mxc_tile_name(family, i)

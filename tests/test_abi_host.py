@@ -266,3 +266,13 @@ def test_bias_gradient_shares_of_planes():
                     parts = max(1, min((512 + K - 1) // K, max(1, N * PQ * (16 // V) // (16 << 10)), N))
                     per = (N + parts - 1) // parts
                     assert per * (PQ // V) < 2 ** 30 and per * (PQ % V) < 2 ** 32, (V, K, PQ, N)
+
+
+def test_tile_names(mxc):
+    """Every kernel shape has a name of its own in one of ten families."""
+    families = [mxc.mxc_tile_names(f) for f in range(10)]
+    names = [n for f in families for n in f]
+    assert all(families) and len(set(names)) == len(names)
+    for family, prefix in ((4, "igemm_wave_"), (5, "wgrad_wave_"), (8, "igemm_run_"), (9, "wgrad_run_")):
+        assert all(n.startswith(prefix) for n in families[family])
+    assert mxc.mxc_tile_name(10, 0) is None and all(mxc.mxc_tile_name(f, -1) is None for f in range(10))

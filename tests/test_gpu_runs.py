@@ -9,10 +9,14 @@ from tests import util
 
 pytestmark = pytest.mark.gpu
 
-TILES = ["128x32", "256x32", "128x64", "192x64", "256x64", "384x64", "256x96", "192x128", "256x128", "256x192", "256x256"]
 # N, C, H, W, K, R, S, pad: Q = W where S = 2*pad + 1
 DIMS = [(3, 40, 9, 7, 24, 3, 3, 1), (2, 8, 11, 13, 104, 5, 5, 2), (1, 16, 1, 1, 8, 3, 3, 1), (5, 72, 1, 2, 40, 5, 5, 2), (4, 32, 16, 24, 264, 3, 3, 1),
         (2, 24, 6, 37, 200, 1, 3, 1), (3, 48, 8, 5, 16, 5, 3, 1), (2, 64, 9, 12, 136, 3, 5, 2), (37, 96, 8, 8, 64, 3, 3, 1)]
+
+
+def _tiles():
+    from paper_1512_01274_amd import mxc as m
+    return [n.removeprefix("igemm_run_") for n in m.mxc_tile_names(8)]
 
 
 @pytest.fixture(scope="module")
@@ -23,7 +27,7 @@ def mxc():
 
 
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])
-@pytest.mark.parametrize("tile,dims", [(t, d) for t in TILES for d in DIMS if not (t == "256x256" and d[6] == 5)])      # (the filter rows of five taps do not fit)
+@pytest.mark.parametrize("tile,dims", [(t, d) for t in _tiles() for d in DIMS if not (t == "256x256" and d[6] == 5)])      # (the filter rows of five taps do not fit)
 def test_forward_and_dx(mxc, monkeypatch, tile, dims, layout):
     N, C, H, W, K, R, S, pad = dims
     name = "igemm_run_" + tile

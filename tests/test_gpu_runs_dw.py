@@ -10,7 +10,6 @@ from tests import util
 
 pytestmark = pytest.mark.gpu
 
-NAMES = ["32x64", "64x64", "128x32", "128x64", "256x64", "96x64", "192x64", "32x128", "64x128", "256x32"]
 # N, C, H, W, K, R, S, pad: Q = W where S = 2*pad + 1, or S = 3 without padding
 DIMS = [
     (6, 40, 9, 11, 72, 3, 3, 1),
@@ -32,6 +31,11 @@ DIMS = [
 FIRST = [(3, 3, 43, 39, 40, 11, 11, 4, 2), (2, 1, 64, 67, 16, 11, 11, 4, 2), (6, 4, 35, 50, 96, 5, 5, 2, 2)]
 
 
+def _names():
+    from paper_1512_01274_amd import mxc as m
+    return [n.removeprefix("wgrad_run_") for n in m.mxc_tile_names(9)]
+
+
 @pytest.fixture(scope="module")
 def mxc():
     assert torch.cuda.is_available(), "GPU tests need a GPU"
@@ -41,7 +45,7 @@ def mxc():
 
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])
 @pytest.mark.parametrize("ranges", [1, 4])
-@pytest.mark.parametrize("name,dims", [(n, d) for n in NAMES for d in DIMS + FIRST if not (n in ("96x64", "192x64") and d[6] == 5 and len(d) == 8)])      # (sums of 3*5 blocks do not fit)
+@pytest.mark.parametrize("name,dims", [(n, d) for n in _names() for d in DIMS + FIRST if not (n in ("96x64", "192x64") and d[6] == 5 and len(d) == 8)])      # (sums of 3*5 blocks do not fit)
 def test_weight_gradient(mxc, oracle, monkeypatch, name, dims, ranges, layout):
     N, C, H, W, K, R, S, pad = dims[:7] + dims[-1:]
     full = dims if len(dims) == 9 else (*dims[:7], 1, pad)
