@@ -1048,10 +1048,10 @@ bool igemm_dims_ok(long long in_elems, long long wm_elems, long long M, int Hi, 
            Wi + span <= 8192 && taps <= MAX_TAPS;
 }
 
-// dx of the residue classes no tap reaches (a 1x1 filter at stride 2 leaves three of four): zeros.  One workgroup per image
-// row; `zero_h` / `zero_w`: bit (coordinate + pad) % stride of the rows / columns without a tap.  Kept out of the launch
-// above: interleaved with the matrix work the same stores ran at a third of the rate they reach alone (1x1 stride-2
-// 256->512 at 56x56, batch 256: 308 MB).
+// dx of the residue classes that no tap reaches: zeros, where neither the tiles of a 1x1 filter at stride 2 write them beside their results
+// (ZR) nor the wave kernel, whose classes they are.  What is left: strides of 3 and 4 with filters of fewer rows or columns, odd padding,
+// channels that are no multiple of 8, dx of 2 GiB and more, tiles without ZR.  One workgroup per image row; `zero_h` / `zero_w`: bit
+// (coordinate + pad) % stride of the rows / columns without a tap.
 template <int V>      // channels per store: 8 (16 bytes) or 1
 __global__ __launch_bounds__(256) void zero_classes_kernel(bf16_t *__restrict__ dx, int H, int W, int C, int stride, int pad, unsigned zero_h,
                                                            unsigned zero_w)

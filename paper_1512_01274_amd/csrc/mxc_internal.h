@@ -554,8 +554,8 @@ const char *run_dw_name(int shape);
 bool run_dw_applicable(const WgradGeom &g);
 bool run_dw_has(int shape, int columns);       // whether the shape is built for filters of so many columns
 int run_dw_ranges(int shape, long long M, int ranges, int *span);
-int run_dw_best(const WgradGeom &g, int most_ranges, bool copies, int *ranges, int *span, double *us);
-double dw_places_us(int ranges, double mb);      // the shape of least modelled time, as wave_dw_best
+int run_dw_best(const WgradGeom &g, int most_ranges, bool copies, int *ranges, int *span, double *us);      // the shape of least modelled time, as wave_dw_best
+double dw_places_us(int ranges, double mb);      // what a dw of so many MB costs besides on copies (see there)
 int run_dw_launch(int shape, const WgradGeom &g, int ranges, int span, const void *x, const void *dy, float *out, int rows, hipStream_t st);
 
 bool wgrad_supported(const WgradGeom &g);

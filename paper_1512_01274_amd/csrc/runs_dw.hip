@@ -284,6 +284,8 @@ __global__ __launch_bounds__(64 * WK * WC * WP, 2) void run_dw_kernel(const RunD
     });
 }
 
+// Of the shapes for 5 columns four hold more than 256 registers and keep some that the loop does not touch in scratch (128x32 six, 256x32 two,
+// 128x64 and 256x64 one), written before it and read after it; their times below are with that.
 // A shape and its time model (us, fitted to 340 layers of 0.6 to 400 GFLOP in up to five ranges each; 2 to 6% off, and the choice takes 0.3%
 // more than the fastest): launch, a stage's MFMAs and its own time on the CU with most tiles, their results, a second launch and the partial
 // tensors it adds, tiles, dw.

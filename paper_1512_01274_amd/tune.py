@@ -11,8 +11,9 @@ MXC_FORCE_WGRAD=<tile>[/<splits>]), so what is timed is exactly what a table hit
 calls a 512 MiB buffer is rewritten so that a layer's operands come from HBM as they do inside a network
 step, not from the caches a repeated call would warm.  Inputs are random tensors of the layers' shapes.
 
-The tables hold plans of the tiled, the streaming and the window kernel.  Whether a wave kernel runs a layer in its plan's place is
-the library's choice by the time models of both; a table entry decides which plan is modelled.
+The tables hold plans of the tiled, the streaming and the window kernel.  Whether a wave or a run kernel runs a layer in its plan's place is
+the library's choice by the time models of both; a table entry decides which plan is modelled.  A plan of the streaming or the window
+kernel that the table holds stays.  dx of 1x1 filters at stride 2 has time models of its own and does not ask the table.
 """
 import argparse
 import os
