@@ -13,8 +13,8 @@
 // ascending order at the end.  Tiles lie in LDS in panels of 32 channels, 64 bytes a pixel, so that the four pixel rows of a transposing read
 // are in different banks whatever row comes first.
 //
-// Measured (us with the sum of the pixel ranges, the tile that ran it before -> this kernel): 128x27x27, 5x5, 64 to 192 channels 82 -> 57 (1013
-// TFLOP/s); 105x40x56, 3x3, 256 to 192 235 -> 182; 99x72x72, 5x5, 128 to 32 294 -> 181; 70x40x77, 3x3, 176 to 32 78 -> 40; 163x19x19, 3x3,
+// Measured (us with the sum of the pixel ranges, the tile that ran it before -> this kernel): 128x27x27, 5x5, 64 to 192 channels 75 -> 57 (1009
+// TFLOP/s, the matrix pipe 0.60 busy); 105x40x56, 3x3, 256 to 192 235 -> 182; 99x72x72, 5x5, 128 to 32 294 -> 181; 70x40x77, 3x3, 176 to 32 78 -> 40; 163x19x19, 3x3,
 // 224 to 144 71 -> 52.  64x28x28, 3x3, 512 to 512 203 -> 213: whole 256x256 tiles stay the faster ones there, and the wave
 // kernel below some 12 us.
 #include <stdlib.h>
