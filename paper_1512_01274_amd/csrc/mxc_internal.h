@@ -435,12 +435,12 @@ struct IgemmParams {
     int f32_out;         // store the fp32 accumulators to `partial` ([m][co], one split) instead of a rounded result to `out`
     int zero_rest;       // dx of a 1x1 filter at stride 2: the three pixels of a 2x2 block that no tap reaches are written too, as zeros
     int nt_out;          // the 16-byte result stores are non-temporal
-    int copied;          // see PostOp
     unsigned out_bytes;  // size of the output tensor when below 2 GiB (buffer stores with range-checked offsets), else 0
     int tap_inner;       // reduction order (see tap_inner_order): 1 = all taps of a channel block before the next block
     // applied to the accumulators before the store (all optional)
     const float *bias;   // + bias[co]
     int relu;            // max(0, .)
+    int copied;          // see PostOp (here, where the fields before it leave a gap: the kernels' arguments stay where they are)
     const bf16_t *mask;  // indexed like `out`: the stored value is 0 where mask <= 0
 };
 
