@@ -9,11 +9,12 @@
 // shifted rows.  Pixels that the shift takes across an image row's end are zeros: the lane reads a row of zeros instead, at an
 // address worked out once per tile.  A stage is a filter row's taps over 32 channels: 2*TS k-steps, with one barrier.
 //
-// Measured (us, the kernel that ran it before -> this one): 128x27x27, 5x5, 64 to 192 channels forward 70 -> 61 (935 TFLOP/s), its dx 77
-// -> 58; 56x63x63, 3x3, 160 to 80 95 -> 62; 206x21x21, 5x5, 288 to 24 100 -> 46; 101x49x49, 3x3, dx of 32 to 144 60 -> 43; 252x31x31,
-// 3x3, dx of 56 to 224 118 -> 78.  What bounds it then are the operand fetches of narrow tiles (256x64: 1 KB per MFMA) and, for wide
-// ones, the MFMAs (1100 to 1160 TFLOP/s, as igemm.hip's large tiles, which stay the faster ones there).  Counters: the matrix pipe is 0.37 to 0.61
-// busy; LDS bank conflicts cost 0.4 (images of 112 columns) to 1.35 cycles (27) per active one: the lanes that read zeros read one address.
+// Measured (us, the kernel that ran it before -> this one): 128x27x27, 5x5, 64 to 192 channels forward 70 -> 61 (935 TFLOP/s; 72 -> 65 on a
+// slower box), its dx 77 -> 58; 56x63x63, 3x3, 160 to 80 95 -> 62; 206x21x21, 5x5, 288 to 24 100 -> 46; 101x49x49, 3x3, dx of 32 to 144 60 ->
+// 43; 252x31x31, 3x3, dx of 56 to 224 118 -> 78.  What bounds it then are the operand fetches of narrow tiles (256x64: 1 KB per MFMA) and,
+// for wide ones, the MFMAs (1100 to 1160 TFLOP/s, as igemm.hip's large tiles, which stay the faster ones there).  Counters: the matrix pipe
+// is 0.37 to 0.62 busy; LDS bank conflicts cost 0.4 (images of 112 columns) to 1.35 cycles (27) per active one: lanes that read zeros read
+// one address.
 #include <stdlib.h>
 #include <string.h>
 
